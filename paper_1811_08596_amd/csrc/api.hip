@@ -1,5 +1,6 @@
 // C ABI of libfftsp.so (see include/fftsp.h): argument checks, workspace carving, launch order.
 #include "../../include/fftsp.h"
+#include "chunk.h"
 #include "internal.h"
 #include "twiddle_table.h"
 
@@ -228,6 +229,17 @@ int apply_quantizer(Plan* p, const fftsp_quantizer* q, uint32_t* static_vmax)
     return FFTSP_OK;
 }
 
+// The receiver for chunks that fit one workgroup; its per-record verdicts go to the workspace at byte offset `verd`.
+hipError_t decompress_chunks(const Plan& p, const PeerList& streams, int npeers, int plain, const CodecArgs& a, float* out,
+                             float gain, uint8_t* ws, size_t verd, Tables t, hipStream_t s)
+{
+    const size_t count = p.C * (size_t)npeers;
+    if (count > 0xffffffffu || verd / 4 > 0xffffffffu) return hipErrorInvalidValue;
+    const StatusNote note{(uint32_t)count, (uint32_t)(verd / 4)};
+    return launch_chunk_decompress(streams, npeers, plain, p.logL, a, out, p.n, gain, reinterpret_cast<uint32_t*>(ws + p.ws.status),
+                                   note, reinterpret_cast<uint32_t*>(ws + verd), t, s);
+}
+
 // The receiver's inverse transform of the codec's own spectrum buffer (uniform chunks).  The decode kernels that
 // ran before it on this stream have cleared the control block.
 hipError_t inverse_of_decoded(const Plan& p, const float* spec, uint32_t sstride, int pair_log, float* out, uint8_t* ws,
@@ -289,8 +301,10 @@ int fftsp_rfft(const float* d_grad, size_t n, uint32_t chunk_len, float* d_spec,
     Tables t;
     if (get_tables(&t) != hipSuccess) return FFTSP_EHIP;
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (p.logL <= kChunkMaxLogL) return hip_status(launch_chunk_rfft(d_grad, n, p.logL, p.C, d_spec, p.L / 2 + 1, t, s));
     return hip_status(launch_rfft(d_grad, n, p.logL, p.C, d_spec, p.L / 2 + 1, reinterpret_cast<float2*>(ws + p.ws.mid), t,
-                                  nullptr, nullptr, 0, nullptr, 0, nullptr, nullptr, reinterpret_cast<hipStream_t>(stream)));
+                                  nullptr, nullptr, 0, 0, nullptr, nullptr, s));
 }
 
 int fftsp_irfft(const float* d_spec, size_t n, uint32_t chunk_len, float* d_grad_out, void* d_workspace,
@@ -306,8 +320,10 @@ int fftsp_irfft(const float* d_spec, size_t n, uint32_t chunk_len, float* d_grad
     Tables t;
     if (get_tables(&t) != hipSuccess) return FFTSP_EHIP;
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (p.logL <= kChunkMaxLogL) return hip_status(launch_chunk_irfft(d_spec, p.L / 2 + 1, n, p.logL, p.C, d_grad_out, t, s));
     return hip_status(launch_irfft(d_spec, p.L / 2 + 1, n, p.logL, p.C, d_grad_out, reinterpret_cast<float2*>(ws + p.ws.mid), t,
-                                   0, 1.0f, nullptr, reinterpret_cast<hipStream_t>(stream)));
+                                   0, 1.0f, nullptr, s));
 }
 
 int fftsp_encode_spectrum_q(const float* d_spec, size_t n, uint32_t chunk_len, float theta, int bits, void* d_packed,
@@ -386,11 +402,12 @@ static int compress_impl(const float* d_grad, size_t n, uint32_t chunk_len, floa
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
     uint8_t* out = static_cast<uint8_t*>(d_packed);
     float* spec = reinterpret_cast<float*>(ws + p.ws.spec);
-    int hist_done = 0;
     CodecArgs a = codec_args(p, theta);
     a.static_vmax = static_vmax;
     a.sstride = padded_bins(p.L);
     uint32_t* ctl = reinterpret_cast<uint32_t*>(ws + p.ws.status);
+    if (p.logL <= kChunkMaxLogL)
+        return hip_status(launch_chunk_compress(d_grad, n, p.logL, a, out, out + kStreamHeader, ctl, t, s));
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws + p.ws.hist);
     float2* mid = reinterpret_cast<float2*>(ws + p.ws.mid);
     const FusedKnobs knobs = fused_knobs();
@@ -403,14 +420,14 @@ static int compress_impl(const float* d_grad, size_t n, uint32_t chunk_len, floa
             e = launch_fused_rfft(d_grad, n, p.logL, p.C, reinterpret_cast<float2*>(spec), a.sstride, mid, t, hist, ctl,
                                   knobs, s);
         if (e == hipSuccess)
-            e = launch_rfft(d_grad, n, p.logL, p.C, spec, a.sstride, mid, t, hist, hist, p.C * kHistBins, &hist_done, 1,
+            e = launch_rfft(d_grad, n, p.logL, p.C, spec, a.sstride, mid, t, hist, hist, p.C * kHistBins, 1,
                             &a.pair_log, nullptr, s, ctl + kCtlGaveUpWord);
     } else {
         e = launch_rfft(d_grad, n, p.logL, p.C, spec, a.sstride, mid, t, hist, ctl,
-                        (p.ws.hist - p.ws.status) / 4 + p.C * kHistBins, &hist_done, 1, &a.pair_log, nullptr, s);
+                        (p.ws.hist - p.ws.status) / 4 + p.C * kHistBins, 1, &a.pair_log, nullptr, s);
     }
     if (e == hipSuccess)
-        e = launch_encode(spec, a, out, out + kStreamHeader, ws, p.ws, hist_done, s);
+        e = launch_encode(spec, a, out, out + kStreamHeader, ws, p.ws, 1, s);
     return hip_status(e);
 }
 
@@ -489,6 +506,11 @@ int fftsp_decompress_q(const void* d_packed, size_t packed_bytes, float* d_grad_
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     float* spec = reinterpret_cast<float*>(ws + p.ws.spec);
     CodecArgs a = codec_args(p, theta);
+    if (p.logL <= kChunkMaxLogL) {
+        PeerList one{};
+        one.p[0] = in;
+        return hip_status(decompress_chunks(p, one, 1, 1, a, d_grad_out, 1.0f, ws, p.ws.sel, t, s));
+    }
     a.sstride = padded_bins(p.L);
     a.pair_log = fft_pair_log(p.logL);
     hipError_t e = launch_decode(in, in + kStreamHeader, a, spec, ws, p.ws, 1, 1, s);
@@ -563,6 +585,8 @@ int fftsp_decompress_accumulate(const void* const* d_packed, int npeers, size_t 
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     float* spec = reinterpret_cast<float*>(ws + p.ws.spec);
     CodecArgs a = codec_args(p, theta);
+    if (p.logL <= kChunkMaxLogL)
+        return hip_status(decompress_chunks(p, peers, npeers, 0, a, d_grad_out, scale, ws, pw.verd, t, s));
     a.sstride = padded_bins(p.L);
     a.pair_log = fft_pair_log(p.logL);
     hipError_t e = launch_decode_peers(peers, npeers, a, spec, ws, p.ws, pw, s);
@@ -985,14 +1009,17 @@ int fftsp_compress_segments(const float* d_grad, const size_t* seg_offsets, int 
         const Workspace w = region_workspace(b.count, b.L, (size_t)lane * region);
         CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
         a.write_header = (bi == 0);
+        const int logL = log2_exact(b.L);
+        if (logL <= kChunkMaxLogL)
+            return launch_chunk_compress(d_grad, 0, logL, a, out, out + kStreamHeader,
+                                         bi == 0 ? reinterpret_cast<uint32_t*>(ws) : nullptr, t, st);
         float* spec = reinterpret_cast<float*>(ws + w.spec);
-        int hist_done = 0;
-        hipError_t pe = launch_rfft(d_grad, 0, log2_exact(b.L), b.count, spec, a.sstride,
+        hipError_t pe = launch_rfft(d_grad, 0, logL, b.count, spec, a.sstride,
                                     reinterpret_cast<float2*>(ws + w.mid), t, reinterpret_cast<uint32_t*>(ws + w.hist),
                                     reinterpret_cast<uint32_t*>(ws + w.status),
-                                    (w.hist - w.status) / 4 + b.count * (size_t)kHistBins, &hist_done, 1, &a.pair_log,
+                                    (w.hist - w.status) / 4 + b.count * (size_t)kHistBins, 1, &a.pair_log,
                                     &b.tab, st);
-        if (pe == hipSuccess) pe = launch_encode(spec, a, out, out + kStreamHeader, ws, w, hist_done, st);
+        if (pe == hipSuccess) pe = launch_encode(spec, a, out, out + kStreamHeader, ws, w, 1, st);
         return pe;
     });
     return hip_status(e);
@@ -1029,11 +1056,19 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
             Workspace w = region_workspace(b.count, b.L, (size_t)lane * region);
             w.status = 0;
             CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
-            a.pair_log = fft_pair_log(log2_exact(b.L));
+            a.write_header = bi == 0;  // the header is looked at once
+            const int logL = log2_exact(b.L);
+            if (logL <= kChunkMaxLogL) {
+                PeerList one{};
+                one.p[0] = in;
+                return launch_chunk_decompress(one, 1, 1, logL, a, d_grad_out, 0, 1.0f, reinterpret_cast<uint32_t*>(ws),
+                                               StatusNote{0u, 0u}, nullptr, t, st);
+            }
+            a.pair_log = fft_pair_log(logL);
             float* spec = reinterpret_cast<float*>(ws + w.spec);
             hipError_t pe = launch_decode(in, in + kStreamHeader, a, spec, ws, w, bi == 0, 0, st);
             if (pe == hipSuccess)
-                pe = launch_irfft(spec, a.sstride, 0, log2_exact(b.L), b.count, d_grad_out,
+                pe = launch_irfft(spec, a.sstride, 0, logL, b.count, d_grad_out,
                                   reinterpret_cast<float2*>(ws + w.mid), t, a.pair_log != 0, 1.0f, &b.tab, st);
             return pe;
         });
@@ -1044,9 +1079,17 @@ int fftsp_device_status(const void* d_workspace, int* status_out)
 {
     if (!d_workspace || !status_out) return FFTSP_EINVAL;
     if (hipDeviceSynchronize() != hipSuccess) return FFTSP_EHIP;
-    uint32_t v = 0;
-    if (hipMemcpy(&v, d_workspace, sizeof(v), hipMemcpyDeviceToHost) != hipSuccess) return FFTSP_EHIP;
-    *status_out = (int)v;
+    uint32_t v[5] = {};
+    if (hipMemcpy(v, d_workspace, sizeof(v), hipMemcpyDeviceToHost) != hipSuccess) return FFTSP_EHIP;
+    uint32_t worst = v[0];
+    if (v[4] == kStatusNoteMagic && v[2] > 0) {  // one verdict per record instead of the status word (chunk.h)
+        std::vector<uint32_t> verdicts(v[2]);
+        if (hipMemcpy(verdicts.data(), static_cast<const uint8_t*>(d_workspace) + (size_t)v[3] * 4, verdicts.size() * 4,
+                      hipMemcpyDeviceToHost) != hipSuccess)
+            return FFTSP_EHIP;
+        worst = std::max(worst, *std::max_element(verdicts.begin(), verdicts.end()));
+    }
+    *status_out = (int)worst;
     return FFTSP_OK;
 }
 

@@ -1,0 +1,1119 @@
+// Chunk-resident codec: chunks of up to 2^15 samples go through the whole sender, or the whole receiver, in one
+// workgroup, so that a gradient is read once and only the packed record is written (and the other way round).
+//
+// A chunk of L = 2M samples (M = 2^LOGM complex points, LOGM = 4 .. 14) is at most 128 KiB of complex values, which
+// fits the LDS of a compute unit together with a 16 KiB twiddle table.  The sender is
+//     samples -> first FFT stage in registers -> LDS stages -> real-FFT split into registers
+//     -> exact radix select on the registers -> ranks from ballots -> Algorithm 1 -> record image in LDS -> memory
+// and the receiver
+//     record image -> LDS -> (word, prefix) table of the bitmap -> dequantised bins in registers -> LDS
+//     -> inverse split -> first inverse stage in registers -> LDS stages -> last stage straight to memory.
+// Between the two ends nothing leaves the workgroup: no spectrum, no histogram and no candidate list in memory, and one
+// launch where the per-tile kernels (codec.hip) take ten.  The transform's arithmetic is that of fft_core.h.
+//
+// What bounds it: vector instruction issue (about 70 instructions per bin in the transform and the split, 60 in select and
+// pack) and, for the longest chunks, the few waves one workgroup per compute unit leaves.  Measured on 25.6 M samples,
+// compress + decompress, against the per-tile kernels with their ten sweeps and 16 KiB of histogram per chunk:
+// L = 2^12 636 -> 124 us, one chunk of 2^10 91 -> 22 us.
+//
+// A workgroup holds 2^LOGE complex points, i.e. one chunk, or several when they are short.  Every chunk belongs to a
+// group of WAVES waves.  Up to M = 1024 that is a single wave: waves then share nothing but the twiddle table and run
+// without a workgroup barrier.
+#include "chunk.h"
+#include "codec_core.h"
+#include "fft_core.h"
+
+#include <type_traits>
+
+namespace fftsp {
+namespace {
+
+template <int LOGM, int NTHREADS>
+struct Geo {
+    static constexpr int M = 1 << LOGM;
+    // 16 points per lane; 8 at M = 2^9, so that a wave still has one chunk
+    static constexpr int LOGE = LOGM > 12 ? LOGM : (LOGM == 9 ? 11 : 12), E = 1 << LOGE;
+    static constexpr int NT = NTHREADS, NW = NT / 64;
+    static constexpr int T = E / M;                            // chunks per workgroup
+    static constexpr int WAVES = NW > T ? NW / T : 1;          // waves per chunk
+    static constexpr int CPW = T > NW ? T / NW : 1;            // chunks a group takes one after the other
+    static constexpr int GROUPS = NW / WAVES;
+    static constexpr int NL = 64 * WAVES;                      // lanes per group
+    static constexpr int R = M / NL > 1 ? M / NL : 1;          // rows of 64 bins per wave
+    static constexpr int LR = M < 64 ? M : 64;                 // bins of a row that exist
+    static constexpr int HB = M <= 256 ? 0 : (M <= 2048 ? 11 : 12);  // first radix digit; 0: bisection
+    static constexpr int WC = M >= 32 ? M / 32 : 1;            // bitmap words of a chunk without the Nyquist bin's
+    static constexpr int TABLE_WORDS = T * WC;
+    static constexpr int TW = LOGM <= 11 ? M : 2048 + (1 << (LOGM - 11));  // entries of the stage twiddle table
+    // LDS bytes of a group: its complex values, later its histogram, candidate list and record image
+    static constexpr int DATA = E / GROUPS * 8, REGION = DATA > (4 << HB) ? DATA : (4 << HB);
+    // record image of one chunk of up to 16-bit codes, in words; short chunks keep theirs beside the data
+    static constexpr int IMAGE = HB ? 0 : ((16 + 4 * (M / 32 + 1) + 4 * (M + 1) + 16) / 4 + 3) & ~3;
+};
+// measured: 8 points per lane beat 16 at M = 2^12 (twice the waves on the same LDS); above it the radix-16 first
+// stage wants 16
+template <int LOGM>
+constexpr int uniform_threads()
+{
+    return LOGM <= 11 ? 256 : (LOGM <= 13 ? 512 : 1024);
+}
+
+// Orders LDS accesses among the waves of a group.  LDS operations of one wave complete in order, so within a wave
+// it is the compiler alone that has to be held back.
+template <int WAVES>
+__device__ __forceinline__ void group_sync()
+{
+    if constexpr (WAVES == 1) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        __syncthreads();
+    }
+}
+
+// Complex values of all chunks of a workgroup lie behind each other in LDS; the low four index bits are XORed with the
+// next four, so that both "consecutive" accesses and the stride-8 and stride-16 ones of the first stages spread
+// over all banks.
+__device__ __forceinline__ constexpr int flat(int g) { return g ^ ((g >> 4) & 15); }
+// flat(g + o) from flat(g), for a constant o that shares no bit with g: the XOR is linear, so the part of o above the
+// low four bits is an address offset and only what it does to those bits costs an instruction (often nothing)
+__device__ __forceinline__ int flat_plus(int flat_g, int o) { return (flat_g ^ (flat(o) & 15)) + (o & ~15); }
+
+// ------------------------------------------------------------------- FFT ----
+// Stage twiddles exp(-2 pi i e / R): the whole table up to R = 2048; above it the 2048 coarse entries and the
+// R / 2048 fine ones behind them, multiplied where a stage needs the fine part (the last one).
+template <int LOGR, int NT>
+__device__ __forceinline__ void load_chunk_twiddles(float2* tw, const Tables& tb, int tid)
+{
+    if constexpr (LOGR <= 11) {
+        for (int e = tid; e < (1 << LOGR); e += NT) tw[e] = tb.hi[e << (11 - LOGR)];
+    } else {
+        for (int e = tid; e < 2048; e += NT) tw[e] = tb.hi[e];
+        if (tid < (1 << (LOGR - 11))) tw[2048 + tid] = tb.lo[tid << (22 - LOGR)];
+    }
+}
+template <int LOGR, int SHIFT>
+__device__ __forceinline__ float2 stage_twiddle(const float2* tw, int idx)
+{
+    if constexpr (LOGR <= 11)
+        return tw[idx << SHIFT];
+    else if constexpr (SHIFT >= LOGR - 11)
+        return tw[idx << (SHIFT - (LOGR - 11))];
+    else
+        return cmul(tw[idx >> (LOGR - 11 - SHIFT)], tw[2048 + ((idx << SHIFT) & ((1 << (LOGR - 11)) - 1))]);
+}
+
+// Butterfly q of a lane: transform b, index j.  A wave's butterflies are consecutive, so its points are too.
+template <int LOGR, int LOGE, int NT, int RL>
+struct Butterflies {
+    static constexpr int PER = (1 << (LOGE - RL)) / NT, RHO = 1 << RL, STEP = 1 << (LOGR - RL);
+    static_assert(PER >= 1, "every lane has work");
+    static __device__ __forceinline__ int index(int tid, int q)
+    {
+        return (tid >> 6) * (64 * PER) + q * 64 + (tid & 63);
+    }
+    static __device__ __forceinline__ int j(int w) { return w & (STEP - 1); }
+    static __device__ __forceinline__ int b(int w) { return w >> (LOGR - RL); }
+};
+
+template <int LOGR, int LOGE, int NT, bool INV, int NS_LOG, int RL>
+__device__ __forceinline__ void stage_compute(float2 (&v)[(1 << (LOGE - RL)) / NT][1 << RL], const float2* tw, int tid)
+{
+    using B = Butterflies<LOGR, LOGE, NT, RL>;
+#pragma unroll
+    for (int q = 0; q < B::PER; ++q) {
+        if constexpr (NS_LOG > 0) {
+            const int k = B::j(B::index(tid, q)) & ((1 << NS_LOG) - 1);
+#pragma unroll
+            for (int t = 1; t < B::RHO; ++t) {
+                const float2 c = stage_twiddle<LOGR, LOGR - NS_LOG - RL>(tw, t * k);
+                v[q][t] = INV ? cmulc(v[q][t], c) : cmul(v[q][t], c);
+            }
+        }
+        butterfly<RL, INV>(v[q]);
+    }
+}
+
+// out(b, i, o, value) receives output i + o of transform b; o is a constant multiple of what i can reach
+template <int LOGR, int LOGE, int NT, int NS_LOG, int RL, typename Out>
+__device__ __forceinline__ void stage_outputs(const float2 (&v)[(1 << (LOGE - RL)) / NT][1 << RL], int tid, Out&& out)
+{
+    using B = Butterflies<LOGR, LOGE, NT, RL>;
+#pragma unroll
+    for (int q = 0; q < B::PER; ++q) {
+        const int w = B::index(tid, q), j = B::j(w), b = B::b(w), k = j & ((1 << NS_LOG) - 1);
+        const int base = ((j >> NS_LOG) << (NS_LOG + RL)) + k;
+#pragma unroll
+        for (int t = 0; t < B::RHO; ++t) out(b, base, t << NS_LOG, v[q][t]);
+    }
+}
+template <int LOGR, int LOGE, int NT, int NS_LOG, int RL>
+__device__ __forceinline__ void stage_to_lds(const float2 (&v)[(1 << (LOGE - RL)) / NT][1 << RL], float2* d, int tid)
+{
+    stage_outputs<LOGR, LOGE, NT, NS_LOG, RL>(v, tid, [&](int b, int i, int o, float2 z) {
+        d[flat_plus(flat((b << LOGR) + i), o)] = z;
+    });
+}
+
+// The stages from NS_LOG applied levels on, data in LDS and visible.  TO_LDS: the result goes back to d (visible to
+// the group afterwards); otherwise the last stage hands every value to out (see stage_outputs).
+template <int LOGR, int LOGE, int NT, int WAVES, bool INV, int NS_LOG, bool TO_LDS, typename Out>
+__device__ __forceinline__ void fft_rest(float2* d, const float2* tw, int tid, Out&& out)
+{
+    if constexpr (NS_LOG < LOGR) {
+        constexpr int RL = stage_radix_log(LOGR - NS_LOG);
+        using B = Butterflies<LOGR, LOGE, NT, RL>;
+        constexpr bool LAST = NS_LOG + RL == LOGR;
+        float2 v[B::PER][B::RHO];
+#pragma unroll
+        for (int q = 0; q < B::PER; ++q) {
+            const int w = B::index(tid, q), f = flat((B::b(w) << LOGR) + B::j(w));
+#pragma unroll
+            for (int t = 0; t < B::RHO; ++t) v[q][t] = d[flat_plus(f, t * B::STEP)];
+        }
+        stage_compute<LOGR, LOGE, NT, INV, NS_LOG, RL>(v, tw, tid);
+        if constexpr (LAST && !TO_LDS) {
+            stage_outputs<LOGR, LOGE, NT, NS_LOG, RL>(v, tid, out);
+        } else {
+            group_sync<WAVES>();
+            stage_to_lds<LOGR, LOGE, NT, NS_LOG, RL>(v, d, tid);
+            group_sync<WAVES>();
+            if constexpr (!LAST) fft_rest<LOGR, LOGE, NT, WAVES, INV, NS_LOG + RL, TO_LDS>(d, tw, tid, out);
+        }
+    }
+}
+
+// first stage of an R-point transform: its inputs are v[q][t] = point j + t*R/RHO of transform b
+template <int LOGR, int LOGE, int NT, int WAVES, bool INV, bool TO_LDS, int RL, typename Out>
+__device__ __forceinline__ void fft_from_registers(float2 (&v)[(1 << (LOGE - RL)) / NT][1 << RL], float2* d, const float2* tw,
+                                                   int tid, Out&& out)
+{
+    static_assert(RL == stage_radix_log(LOGR), "the plan's first radix");
+    stage_compute<LOGR, LOGE, NT, INV, 0, RL>(v, tw, tid);
+    if constexpr (RL == LOGR && !TO_LDS) {
+        stage_outputs<LOGR, LOGE, NT, 0, RL>(v, tid, out);
+    } else {
+        stage_to_lds<LOGR, LOGE, NT, 0, RL>(v, d, tid);
+        group_sync<WAVES>();
+        fft_rest<LOGR, LOGE, NT, WAVES, INV, RL, TO_LDS>(d, tw, tid, out);
+    }
+}
+struct NoOut {
+    __device__ void operator()(int, int, int, float2) const {}
+};
+
+// Forward transform of chunks c0 .. c0+T-1 (those below cend exist) up to Z[k] in d, visible to the group.
+// The stage twiddle table must have been filled before (the barrier for it is taken here, behind the loads).
+template <typename G, int LOGM, bool TABLE>
+__device__ __forceinline__ void forward_tile(const float* __restrict__ in, size_t n, size_t c0, size_t cend, int aligned,
+                                             const TableArg<TABLE>& tab, float2* d, const float2* tw, int tid)
+{
+    constexpr int RL = stage_radix_log(LOGM);
+    using B = Butterflies<LOGM, G::LOGE, G::NT, RL>;
+    float2 v[B::PER][B::RHO];
+    const bool whole = !TABLE && aligned && (c0 + G::T) * (size_t)(2 * G::M) <= n;
+    if (whole) {
+        const float2* src = reinterpret_cast<const float2*>(in) + c0 * (size_t)G::M;
+#pragma unroll
+        for (int q = 0; q < B::PER; ++q) {
+            const int w = B::index(tid, q), g = (B::b(w) << LOGM) + B::j(w);
+#pragma unroll
+            for (int t = 0; t < B::RHO; ++t) v[q][t] = src[g + t * B::STEP];
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < B::PER; ++q) {
+            const int w = B::index(tid, q);
+            const Span sp = chunk_span<TABLE>(tab, c0 + B::b(w), cend, 2 * G::M, n, aligned);
+#pragma unroll
+            for (int t = 0; t < B::RHO; ++t)
+                v[q][t] = load_pair(in, sp.first + 2 * (size_t)(B::j(w) + t * B::STEP), sp.limit, sp.pairs);
+        }
+    }
+    __syncthreads();
+    fft_from_registers<LOGM, G::LOGE, G::NT, G::WAVES, false, true, RL>(v, d, tw, tid, NoOut());
+}
+
+// W_L^k for the even/odd split of a chunk of 2^(LOGM+1) samples
+template <int LOGM>
+__device__ __forceinline__ float2 split_twiddle(const Tables& tb, int k)
+{
+    if constexpr (LOGM <= 10)
+        return tb.hi[k << (10 - LOGM)];
+    else
+        return cmul(tb.hi[k >> (LOGM - 10)], tb.lo[(k & ((1 << (LOGM - 10)) - 1)) << (21 - LOGM)]);
+}
+// X[k], 0 <= k < M, from Z[k] and Z[M-k]
+template <int LOGM>
+__device__ __forceinline__ float2 split_bin(float2 a, float2 b, int k, const Tables& tb)
+{
+    const float2 x = split_fwd(a, b, split_twiddle<LOGM>(tb, k));
+    return k == 0 ? make_float2(a.x + a.y, 0.f) : x;
+}
+template <int LOGM>
+__device__ __forceinline__ float2 nyquist_bin(const float2* d, int base)
+{
+    const float2 a = d[flat(base)];
+    return make_float2(a.x - a.y, 0.f);
+}
+
+// --------------------------------------------------------- select and pack ----
+struct GroupScratch {
+    uint32_t bucket, need, count, listed;
+    uint32_t a[16], b[16], v[16];
+};
+
+constexpr uint32_t kListCap = 256;  // keys of the threshold's bucket that are finished from a list
+
+// The `need`-th largest of `count` listed keys that share all bits above `low`: tau grows bit by bit, a ballot counts
+// the keys at or above each trial.  On return need = how many keys equal to tau are still to take, of `equal`.
+// A trial that leaves exactly `need` keys ends the search: those are the ones.
+template <int NR>
+__device__ __forceinline__ void search_list(const uint32_t* list, uint32_t count, int low, int lane, uint32_t& tau,
+                                            uint32_t& need, uint32_t& equal)
+{
+    uint32_t key[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) key[i] = (uint32_t)(lane + 64 * i) < count ? list[lane + 64 * i] : 0u;
+    if (count == need) {
+        equal = need;
+        return;
+    }
+    for (int bit = low - 1; bit >= 0; --bit) {
+        const uint32_t t = tau | (1u << bit);
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) cnt += (uint32_t)__popcll(__ballot(key[i] >= t));
+        if (cnt >= need) tau = t;
+        if (cnt == need) {
+            equal = need;
+            return;
+        }
+    }
+    uint32_t above = 0;
+    equal = 0;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        above += (uint32_t)__popcll(__ballot(key[i] > tau));
+        equal += (uint32_t)__popcll(__ballot((uint32_t)(lane + 64 * i) < count && key[i] == tau));
+    }
+    need -= above;
+}
+
+// Steps 2-4 of the sender for one chunk whose bins (samples) lie in the registers of a group of WAVES waves:
+// z[r]: bin (wave * R + r) * 64 + lane (lane < LR); zn (TAIL): the chunk's last bin, the same value in every lane.
+// lds: the group's own words (histogram, candidate list); image: its record image.  wg_most: a word of the workgroup,
+// zero on entry, through which several groups of several waves agree on the path they take together.
+// live = false groups (no such chunk) write nothing; groups of several waves call this together.
+template <bool REAL, int R, bool TAIL, int LR, int WAVES, int GROUPS, int HB>
+__device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z)[R], typename Elem<REAL>::T zn, uint32_t* lds,
+                                                uint32_t* image, GroupScratch& gs, uint32_t* wg_most, int tid,
+                                                const PackArgs& a, uint32_t word3, uint8_t* __restrict__ record, bool live)
+{
+    constexpr int NL = 64 * WAVES;
+    constexpr bool SHARED = WAVES > 1 && GROUPS > 1;
+    constexpr uint32_t CODES = Elem<REAL>::kCodes;
+    const int lane = tid & 63, tg = tid & (NL - 1), wig = __builtin_amdgcn_readfirstlane(tg >> 6);
+    const bool tail = TAIL && wig == WAVES - 1;  // this wave owns the last bin
+    auto ones = [](uint64_t m) __attribute__((always_inline)) { return (uint32_t)__popcll(m); };
+    auto among = [&](bool p) __attribute__((always_inline)) { return __ballot(LR == 64 ? p : (p && lane < LR)); };
+    const uint32_t keyn = TAIL ? (uint32_t)__builtin_amdgcn_readfirstlane((int)key_of(zn)) : 0u;
+    uint32_t key[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) key[r] = key_of(z[r]);
+
+    // ---- the k-th largest key ----
+    uint32_t tau = 0, need = a.k, equal = 0;
+    if constexpr (HB == 0) {
+        // few keys: bisection on the key's bits, one ballot per row and bit, until a trial leaves exactly k keys
+        bool open = true;
+        for (int bit = 30; bit >= 0 && open; --bit) {
+            const uint32_t t = tau | (1u << bit);
+            uint32_t cnt = tail && keyn >= t ? 1u : 0u;
+#pragma unroll
+            for (int r = 0; r < R; ++r) cnt += ones(among(key[r] >= t));
+            if (cnt >= need) tau = t;
+            open = cnt != need;
+        }
+        equal = need;
+        if (open) {
+            uint32_t above = tail && keyn > tau ? 1u : 0u;
+            equal = tail && keyn == tau ? 1u : 0u;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                above += ones(among(key[r] > tau));
+                equal += ones(among(key[r] == tau));
+            }
+            need -= above;
+        }
+    } else {
+        // One radix digit of NB bits at `shift` among the keys whose bits from shift + NB up equal those of tau:
+        // counts in LDS, scanned from the top.  A lane scans PER consecutive counters; their places are swizzled in
+        // quads so that the lanes' 16-byte reads spread over the banks.
+        auto digit = [&](auto nb_tag, int shift) __attribute__((always_inline)) {
+            constexpr int NB = decltype(nb_tag)::value, BINS = 1 << NB;
+            constexpr int PER = BINS > NL ? BINS / NL : 1, QUADS = PER / 4;
+            constexpr int LOGPER = PER == 1 ? 0 : PER == 2 ? 1 : PER == 4 ? 2 : PER == 8 ? 3 : PER == 16 ? 4 : 5;
+            static_assert((1 << LOGPER) == PER, "counters per lane");
+            auto place = [](uint32_t i) __attribute__((always_inline)) {
+                if constexpr (QUADS > 1)
+                    return i ^ (((i >> LOGPER) & (uint32_t)(QUADS - 1)) << 2);
+                else
+                    return i;
+            };
+            for (int i = 4 * tg; i < BINS; i += 4 * NL) *reinterpret_cast<uint4*>(lds + i) = make_uint4(0u, 0u, 0u, 0u);
+            if (tg == 0) {
+                gs.bucket = 0u;
+                gs.need = 0u;
+                gs.count = 0u;
+                gs.listed = 0u;
+            }
+            group_sync<WAVES>();
+            const int top = shift + NB;
+            const uint32_t prefix = top >= 31 ? 0u : tau >> top;
+            auto add = [&](uint32_t k) __attribute__((always_inline)) {
+                if (top >= 31 || k >> top == prefix) atomicAdd(&lds[place((k >> shift) & (uint32_t)(BINS - 1))], 1u);
+            };
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (LR == 64 || lane < LR) add(key[r]);
+            if (tail && lane == 0) add(keyn);
+            group_sync<WAVES>();
+            uint32_t cnt[PER], sum = 0;
+            const bool mine = PER > 1 || tg < BINS;
+            const int base = BINS - PER - tg * PER;  // this lane's counters, [base, base + PER), from the top down
+            if constexpr (PER >= 4) {
+                const uint32_t b0 = place((uint32_t)base);  // base is a multiple of PER, so quad q sits at b0 ^ 4q
+#pragma unroll
+                for (int q = 0; q < QUADS; ++q) {
+                    const uint4 v = *reinterpret_cast<const uint4*>(lds + (b0 ^ (uint32_t)(4 * q)));
+                    cnt[4 * q] = v.x;
+                    cnt[4 * q + 1] = v.y;
+                    cnt[4 * q + 2] = v.z;
+                    cnt[4 * q + 3] = v.w;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < PER; ++i) cnt[i] = mine ? lds[base + i] : 0u;
+            }
+#pragma unroll
+            for (int i = 0; i < PER; ++i) sum += cnt[i];
+            const uint32_t incl = wave_scan_incl(sum);
+            uint32_t before = incl - sum;
+            if constexpr (WAVES > 1) {
+                if (lane == 63) gs.a[wig] = incl;
+                __syncthreads();
+#pragma unroll
+                for (int w = 0; w < WAVES - 1; ++w) before += w < wig ? gs.a[w] : 0u;
+            }
+            if (before < need && before + sum >= need) {
+                uint32_t run = before;
+#pragma unroll
+                for (int i = PER - 1; i >= 0; --i) {
+                    if (run < need && run + cnt[i] >= need) {
+                        gs.bucket = (uint32_t)(base + i);
+                        gs.need = need - run;
+                        gs.count = cnt[i];
+                        if (SHARED) atomicMax(wg_most, cnt[i]);
+                    }
+                    run += cnt[i];
+                }
+            }
+            group_sync<WAVES>();
+            tau |= (uint32_t)__builtin_amdgcn_readfirstlane((int)gs.bucket) << shift;
+            need = (uint32_t)__builtin_amdgcn_readfirstlane((int)gs.need);
+            equal = (uint32_t)__builtin_amdgcn_readfirstlane((int)gs.count);
+        };
+        constexpr int LOW1 = 31 - HB, LOW2 = LOW1 - 10;
+        digit(std::integral_constant<int, HB>(), LOW1);
+        const bool listed = (SHARED ? (uint32_t)__builtin_amdgcn_readfirstlane((int)*wg_most) : equal) <= kListCap;
+        if (listed) {
+            const uint32_t count = equal, prefix = tau >> LOW1;
+            uint32_t mine = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) mine += ones(among(key[r] >> LOW1 == prefix));
+            const bool tail_in = tail && keyn >> LOW1 == prefix;
+            mine += tail_in ? 1u : 0u;
+            uint32_t off = 0;
+            if (WAVES > 1) {
+                if (lane == 0) off = atomicAdd(&gs.listed, mine);
+                off = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const bool in = (LR == 64 || lane < LR) && key[r] >> LOW1 == prefix;
+                const uint64_t m = __ballot(in);
+                const uint32_t at = off + prefix_popc(m);
+                if (in && at < kListCap) lds[at] = key[r];  // k = 0 selects an arbitrary bucket and drops it below
+                off += ones(m);
+            }
+            if (tail_in && lane == 0 && off < kListCap) lds[off] = keyn;
+            group_sync<WAVES>();
+            if (count <= 64u)
+                search_list<1>(lds, count, LOW1, lane, tau, need, equal);
+            else
+                search_list<4>(lds, count, LOW1, lane, tau, need, equal);
+        } else {
+            // heavy ties, or a long chunk: two more digits over the registers
+            group_sync<WAVES>();  // everyone has read the first digit's result
+            digit(std::integral_constant<int, 10>(), LOW2);
+            group_sync<WAVES>();
+            digit(std::integral_constant<int, LOW2>(), 0);
+        }
+    }
+    if (a.k == 0) {
+        tau = 0xFFFFFFFFu;
+        need = equal = 0;
+    }
+
+    // ---- survivors: everything above tau and the first `need` bins equal to it ----
+    uint64_t fm[R];
+    bool fn;  // the last bin survives
+    uint32_t nfl = 0, vmax = 0;
+    // usually all bins equal to tau are wanted; in the other case their order across the group counts
+    const bool ties = need != equal;
+    if (ties || SHARED) {
+        uint32_t eqrun = 0;
+        if constexpr (WAVES > 1) {
+            uint32_t neq = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) neq += ones(among(key[r] == tau));
+            if (lane == 0) gs.a[wig] = neq;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < WAVES - 1; ++w) eqrun += w < wig ? gs.a[w] : 0u;
+            eqrun = (uint32_t)__builtin_amdgcn_readfirstlane((int)eqrun);
+        }
+        const uint32_t take = ties ? need : 0xFFFFFFFFu;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint64_t em = among(key[r] == tau);
+            fm[r] = among(key[r] > tau || (key[r] == tau && eqrun + prefix_popc(em) < take));
+            eqrun += ones(em);
+        }
+        fn = tail && (keyn > tau || (keyn == tau && eqrun < take));
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) fm[r] = among(key[r] >= tau);
+        fn = tail && keyn >= tau;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        nfl += ones(fm[r]);
+        const uint32_t vb = __builtin_amdgcn_inverse_ballot_w64(fm[r]) ? vbits_of(z[r]) : 0u;
+        vmax = vb > vmax ? vb : vmax;
+    }
+    vmax = wave_max(vmax);
+    if (fn) {
+        const uint32_t vb = (uint32_t)__builtin_amdgcn_readfirstlane((int)vbits_of(zn));
+        vmax = vb > vmax ? vb : vmax;
+        ++nfl;
+    }
+    uint32_t rank = 0;
+    if constexpr (WAVES > 1) {
+        if (lane == 0) {
+            gs.b[wig] = nfl;
+            gs.v[wig] = vmax;
+        }
+    }
+    const int bits = a.bits, shift = 23 - a.m;
+    const uint32_t image_words = (bits == 32 ? 4u + a.W : a.S / 4u);
+    // The image's code words and padding start from zero; 8-bit codes overwrite whole units, so that only the words from
+    // the last code on matter.
+    const uint32_t zero_from = 4u + a.W + (bits == 8 ? CODES * a.k / 4u : 0u);
+    for (uint32_t i = zero_from + (uint32_t)tg; i < image_words; i += NL) image[i] = 0u;
+    group_sync<WAVES>();
+    if constexpr (WAVES > 1) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            rank += w < wig ? gs.b[w] : 0u;
+            const uint32_t v = gs.v[w];
+            vmax = v > vmax ? v : vmax;
+        }
+        rank = (uint32_t)__builtin_amdgcn_readfirstlane((int)rank);
+        vmax = (uint32_t)__builtin_amdgcn_readfirstlane((int)vmax);
+    }
+    if (a.static_vmax) vmax = a.static_vmax;
+    uint32_t pbase = 0;
+    if (bits != 32) {
+        const int64_t pb = (int64_t)(vmax >> shift) - (int64_t)((1u << (bits - 1)) - 2u);
+        pbase = pb < 1 ? 1u : (uint32_t)pb;
+    }
+    if (tg < 4) image[tg] = tg == 0 ? pbase : (tg == 1 ? vmax : (tg == 2 ? a.k : word3));
+
+    // ---- bitmap ----
+    if constexpr (LR == 64) {
+        if (lane == 0) {
+            uint32_t* words = image + 4 + wig * 2 * R;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                words[2 * r] = (uint32_t)fm[r];
+                words[2 * r + 1] = (uint32_t)(fm[r] >> 32);
+            }
+        }
+        if (tail && lane == 0) image[4 + WAVES * 2 * R] = fn ? 1u : 0u;  // the last bin opens a word of its own
+    } else if (lane < (int)a.W) {
+        const uint64_t all = TAIL ? fm[0] | ((uint64_t)(fn ? 1u : 0u) << LR) : fm[0];
+        image[4 + lane] = lane ? (uint32_t)(all >> 32) : (uint32_t)all;
+    }
+
+    // ---- Algorithm 1 and the codes ----
+    uint32_t* codes = image + 4 + a.W;
+    uint32_t* direct = reinterpret_cast<uint32_t*>(record) + 4 + a.W;  // 32-bit codes go straight to memory
+    auto code = [&](const typename Elem<REAL>::T& x, int h, int width) __attribute__((always_inline)) {
+        if constexpr (REAL)
+            return quantize(__float_as_uint(x), pbase, width, shift);
+        else
+            return quantize(__float_as_uint(h ? x.y : x.x), pbase, width, shift);
+    };
+    auto put = [&](auto mode, const typename Elem<REAL>::T& x, uint32_t rk) __attribute__((always_inline)) {
+        constexpr int MODE = decltype(mode)::value;
+        if constexpr (MODE == 8) {
+            if constexpr (REAL)
+                reinterpret_cast<uint8_t*>(codes)[rk] = (uint8_t)code(x, 0, 8);
+            else
+                reinterpret_cast<uint16_t*>(codes)[rk] = (uint16_t)(code(x, 0, 8) | (code(x, 1, 8) << 8));
+        } else if constexpr (MODE == 32) {
+            if (live) {
+                direct[CODES * rk] = code(x, 0, 32);
+                if constexpr (!REAL) direct[CODES * rk + 1] = code(x, 1, 32);
+            }
+        } else {
+            uint32_t both = code(x, 0, bits);
+            if constexpr (!REAL) both |= code(x, 1, bits) << bits;  // at most 32 bits
+            const uint32_t width = CODES * (uint32_t)bits, p = width * rk, sh = p & 31u;
+            atomicOr(&codes[p >> 5], both << sh);
+            if (sh + width > 32u) atomicOr(&codes[(p >> 5) + 1], both >> (32u - sh));
+        }
+    };
+    auto all = [&](auto mode) __attribute__((always_inline)) {
+        uint32_t run = rank;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (__builtin_amdgcn_inverse_ballot_w64(fm[r])) put(mode, z[r], run + prefix_popc(fm[r]));
+            run += ones(fm[r]);
+        }
+        if (fn && lane == 0) put(mode, zn, run);
+    };
+    if (bits == 8)
+        all(std::integral_constant<int, 8>());
+    else if (bits == 32)
+        all(std::integral_constant<int, 32>());
+    else
+        all(std::integral_constant<int, 0>());
+    group_sync<WAVES>();
+    if (live) {
+        const uint32_t whole = image_words / 4u;
+        uint4* dst = reinterpret_cast<uint4*>(record);
+        for (uint32_t i = (uint32_t)tg; i < whole; i += NL) dst[i] = reinterpret_cast<const uint4*>(image)[i];
+        if (bits == 32) {
+            uint32_t* rec = reinterpret_cast<uint32_t*>(record);
+            for (uint32_t i = 4u * whole + (uint32_t)tg; i < image_words; i += NL) rec[i] = image[i];
+            for (uint32_t i = 4u + a.W + CODES * a.k + (uint32_t)tg; i < a.S / 4u; i += NL) rec[i] = 0u;  // padding
+        }
+    }
+}
+
+// what the first workgroup of a call leaves in the control block (see chunk.h)
+__device__ __forceinline__ void write_control(uint32_t* __restrict__ ctl, const StatusNote& note, int tid)
+{
+    if (tid == 0) {
+        ctl[0] = 0u;
+        ctl[1] = 0u;
+        ctl[2] = note.count;
+        ctl[3] = note.offset;
+        ctl[4] = note.count ? kStatusNoteMagic : 0u;
+    }
+}
+
+template <bool TABLE>
+__device__ __forceinline__ size_t record_of(const TableArg<TABLE>& tab, size_t c, uint32_t S)
+{
+    if constexpr (TABLE)
+        return (size_t)tab.t.roff[c];
+    else
+        return c * (size_t)S;
+}
+
+// Sender: one workgroup per T chunks.
+template <int LOGM, int NT, bool TABLE>
+__global__ __launch_bounds__(NT) void k_chunk_compress(const float* __restrict__ in, size_t n, size_t C, int aligned,
+                                                       Tables tb, PackArgs a, uint8_t* __restrict__ stream,
+                                                       uint8_t* __restrict__ records, HeaderInfo hdr,
+                                                       uint32_t* __restrict__ ctl, TableArg<TABLE> tab)
+{
+    using G = Geo<LOGM, NT>;
+    extern __shared__ __attribute__((aligned(16))) float2 smem[];
+    __shared__ GroupScratch gs[G::GROUPS];
+    __shared__ uint32_t wg_most;
+    const int tid = threadIdx.x, lane = tid & 63, group = tid / G::NL, wig = (tid >> 6) % G::WAVES;
+    uint8_t* region = reinterpret_cast<uint8_t*>(smem) + group * G::REGION;
+    // the workgroup's point g lies at d[flat(g)]; a group's points are a multiple of 256, so its base moves freely
+    float2* d = reinterpret_cast<float2*>(region) - group * (G::E / G::GROUPS);
+    float2* tw = smem + G::GROUPS * G::REGION / 8;
+    uint32_t* images = reinterpret_cast<uint32_t*>(tw + G::TW);  // short chunks only
+    const size_t c0 = (size_t)blockIdx.x * G::T;
+    if (blockIdx.x == 0) {
+        if (ctl) write_control(ctl, StatusNote{0u, 0u}, tid);
+        if (hdr.write && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
+    }
+    if (tid == 0) wg_most = 0u;
+    load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
+    forward_tile<G, LOGM, TABLE>(in, n, c0, C, aligned, tab, d, tw, tid);
+    uint32_t* mine = reinterpret_cast<uint32_t*>(region);
+    auto bins_of = [&](int b, float2 (&z)[G::R], float2& zn) __attribute__((always_inline)) {
+        const int base = b << LOGM;
+        if constexpr (G::M < 64) {
+            const int k = lane & (G::M - 1);
+            z[0] = split_bin<LOGM>(d[flat(base + k)], d[flat(base + ((G::M - k) & (G::M - 1)))], k, tb);
+        } else {
+            // rows of 64 bins upwards from k, and of their mirrors downwards: M - k is 64 - lane into a row that only its
+            // number changes, except in lane 0
+            const int k0 = wig * G::R * 64 + lane, f = flat(base + k0);
+            const int g = flat(base + G::M - (wig + 1) * G::R * 64 + ((64 - lane) & 63));
+#pragma unroll
+            for (int r = 0; r < G::R; ++r) {
+                const int first = base + ((G::M - (wig * G::R + r) * 64) & (G::M - 1));
+                const int mirror = lane == 0 ? flat(first) : flat_plus(g, (G::R - 1 - r) * 64);
+                const int k = k0 + r * 64;
+                z[r] = split_fwd(d[flat_plus(f, r * 64)], d[mirror], split_twiddle<LOGM>(tb, k));
+            }
+            if (wig == 0) {
+                const float2 a = d[flat(base)];
+                if (lane == 0) z[0] = make_float2(a.x + a.y, 0.f);
+            }
+        }
+        zn = nyquist_bin<LOGM>(d, base);
+    };
+    auto pack = [&](int i, const float2 (&z)[G::R], float2 zn, uint32_t* image) __attribute__((always_inline)) {
+        const size_t c = c0 + (size_t)(group * G::CPW + i);
+        const bool live = c < C;
+        select_and_pack<false, G::R, true, G::LR, G::WAVES, G::GROUPS, G::HB>(
+            z, zn, mine, image, gs[group], &wg_most, tid, a, a.word3, records + (live ? record_of<TABLE>(tab, c, a.S) : 0), live);
+    };
+    if constexpr (G::HB == 0) {
+        for (int i = 0; i < G::CPW; ++i) {  // the bins stay in LDS until their turn comes
+            if (c0 + (size_t)(group * G::CPW + i) >= C) break;  // single-wave groups: no barrier is skipped
+            float2 z[G::R], zn;
+            bins_of(group * G::CPW + i, z, zn);
+            pack(i, z, zn, images + group * G::IMAGE);
+            group_sync<G::WAVES>();
+        }
+    } else {
+        // the bins move into registers and their LDS becomes histogram, candidate list and record image
+        static_assert(G::CPW == 1, "one chunk per group");
+        float2 z[G::R], zn;
+        bins_of(group, z, zn);
+        group_sync<G::WAVES>();
+        pack(0, z, zn, mine + kListCap);
+    }
+}
+
+// ---------------------------------------------------------------- receiver ----
+// Receiver: one workgroup per T chunks; several peers' streams are summed bin by bin in list order.
+// region: LDS bytes of a group for its complex values or its record images, whichever is larger (single-wave groups run
+// without barriers, so no group may touch another's bytes).
+template <int LOGM, int NT, bool TABLE>
+__global__ __launch_bounds__(NT) void k_chunk_decompress(PeerList streams, uint32_t npeers, int plain, size_t C, Tables tb,
+                                                         PackArgs a, HeaderInfo hdr, float* __restrict__ out, size_t n,
+                                                         int aligned, float gain, uint32_t region, uint32_t image_stride,
+                                                         uint32_t* __restrict__ ctl, StatusNote note,
+                                                         uint32_t* __restrict__ verdicts, TableArg<TABLE> tab)
+{
+    using G = Geo<LOGM, NT>;
+    constexpr int RL = stage_radix_log(LOGM);
+    using B = Butterflies<LOGM, G::LOGE, NT, RL>;
+    extern __shared__ __attribute__((aligned(16))) float2 smem[];
+    __shared__ uint2 words[G::TABLE_WORDS];
+    __shared__ float2 nyquist[G::T];
+    __shared__ GroupScratch gs[G::GROUPS];
+    const int tid = threadIdx.x, lane = tid & 63, group = tid / G::NL, tg = tid & (G::NL - 1), wig = tg >> 6;
+    float2* tw = reinterpret_cast<float2*>(reinterpret_cast<uint8_t*>(smem) + (size_t)G::GROUPS * region);
+    uint8_t* images = reinterpret_cast<uint8_t*>(smem) + (size_t)group * region;
+    // the workgroup's point g lies at d[flat(g)]; a group's points are a multiple of 256, so its base moves freely
+    float2* d = reinterpret_cast<float2*>(images) - group * (G::E / G::GROUPS);
+    const size_t c0 = (size_t)blockIdx.x * G::T;
+    const int bits = a.bits, shift = 23 - a.m;
+    const uint32_t code_base = 16u + 4u * a.W, last_rank = a.k ? a.k - 1u : 0u;
+    if (blockIdx.x == 0 && verdicts) write_control(ctl, note, tid);
+    load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
+
+    // value of the kept bin of this rank, codes in the record image; MODE: 8, 32, or 0 for the other widths
+    auto value = [&](auto mode, const uint8_t* codes, uint32_t pbase, uint32_t rank, bool set) __attribute__((always_inline)) {
+        constexpr int MODE = decltype(mode)::value;
+        rank = rank < last_rank ? rank : last_rank;  // a corrupt bitmap must not point outside the record
+        if constexpr (MODE == 32) {
+            const uint2 v = *reinterpret_cast<const uint2*>(codes + 8u * rank);
+            return make_float2(__uint_as_float(set ? v.x : 0u), __uint_as_float(set ? v.y : 0u));
+        } else {
+            uint32_t both;
+            int width = bits;
+            if constexpr (MODE == 8) {
+                both = *reinterpret_cast<const uint16_t*>(codes + 2u * rank);
+                width = 8;
+            } else {
+                const uint32_t p = 2u * (uint32_t)bits * rank;
+                const uint32_t* w = reinterpret_cast<const uint32_t*>(codes) + (p >> 5);  // a word past the codes at most
+                both = __builtin_amdgcn_alignbit(w[1], w[0], p & 31u);                     // 2 * 16 bits at most
+            }
+            both = set ? both : 0u;
+            return make_float2(__uint_as_float(dequantize(both, pbase, width, shift)),
+                               __uint_as_float(dequantize(both >> width, pbase, width, shift)));
+        }
+    };
+
+    float2 x[B::PER][B::RHO], xn = make_float2(0.f, 0.f);
+    for (uint32_t peer = 0; peer < npeers; ++peer) {
+        const uint8_t* stream = streams.p[peer];
+        // the group's records, one behind the other
+        for (int i = 0; i < G::CPW; ++i) {
+            const int b = group * G::CPW + i;
+            const size_t c = c0 + (size_t)b;
+            if (c >= C) break;
+            const uint4* src = reinterpret_cast<const uint4*>(stream + 64 + record_of<TABLE>(tab, c, a.S));
+            uint4* dst = reinterpret_cast<uint4*>(images + (uint32_t)i * image_stride);
+            for (uint32_t j = (uint32_t)tg; j < a.S / 16u; j += G::NL) dst[j] = src[j];
+        }
+        group_sync<G::WAVES>();
+        // bitmap words with the number of set bits before each; the total tells a corrupt record
+        {
+            constexpr int WORDS = G::CPW * G::WC;  // of this group
+            const bool has = tg < WORDS;
+            const int i = has ? tg / G::WC : 0, wi = has ? tg % G::WC : 0, b = group * G::CPW + i;
+            const bool live = c0 + (size_t)b < C;
+            const uint32_t* rec = reinterpret_cast<const uint32_t*>(images + (uint32_t)i * image_stride);
+            uint32_t word = has && live ? rec[4 + wi] : 0u;
+            uint32_t tail_bit;
+            if constexpr (LOGM == 4) {
+                tail_bit = (word >> 16) & 1u;
+                word &= 0xFFFFu;
+            } else {
+                tail_bit = has && live ? rec[4 + G::WC] & 1u : 0u;
+            }
+            const uint32_t count = (uint32_t)__popc(word);
+            uint32_t incl = count;
+            constexpr int SEG = G::WC < 64 ? G::WC : 64;
+#pragma unroll
+            for (int o = 1; o < SEG; o <<= 1) {
+                const uint32_t u = __shfl_up(incl, o, 64);
+                if ((lane & (SEG - 1)) >= o) incl += u;
+            }
+            if constexpr (G::WC > 64) {
+                if (lane == 63) gs[group].a[wig] = incl;
+                __syncthreads();
+#pragma unroll
+                for (int w = 0; w < G::WC / 64 - 1; ++w) incl += w < wig ? gs[group].a[w] : 0u;
+            }
+            if (has) {
+                words[group * WORDS + tg] = make_uint2(word, incl - count);
+                if (wi == G::WC - 1) {  // this lane knows the chunk's total: the last bin and the verdict are its
+                    const uint32_t total = incl;
+                    float2 v = make_float2(0.f, 0.f);
+                    uint32_t verdict = 0;
+                    if (live) {
+                        const uint8_t* codes = reinterpret_cast<const uint8_t*>(rec) + code_base;
+                        const bool set = tail_bit && a.k > 0;
+                        v = bits == 32 ? value(std::integral_constant<int, 32>(), codes, rec[0], total, set)
+                                       : value(std::integral_constant<int, 0>(), codes, rec[0], total, set);
+                        bool bad = total + tail_bit != a.k || rec[2] != a.k || rec[3] != a.word3;
+                        const size_t c = c0 + (size_t)b;
+                        if (c == 0 && hdr.write) bad = bad || header_bad(hdr, reinterpret_cast<const uint32_t*>(stream));
+                        verdict = bad ? 6u : 0u;
+                        if (verdicts)
+                            verdicts[(size_t)peer * C + c] = verdict;
+                        else if (verdict)
+                            atomicMax(ctl, verdict);
+                    }
+                    xn = plain ? v : make_float2(xn.x + v.x, xn.y + v.y);
+                }
+            }
+        }
+        group_sync<G::WAVES>();
+        auto bins = [&](auto mode) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < B::PER; ++q) {
+                const int w = B::index(tid, q), j = B::j(w), b = B::b(w);
+                const uint8_t* image = images + (uint32_t)(b - group * G::CPW) * image_stride;
+                const uint32_t pbase = *reinterpret_cast<const uint32_t*>(image);
+                const uint2* row = words + b * G::WC;
+#pragma unroll
+                for (int t = 0; t < B::RHO; ++t) {
+                    const int i = j + t * B::STEP;
+                    const uint2 e = B::STEP >= 32 ? row[(j >> 5) + t * (B::STEP / 32)] : row[i >> 5];
+                    const uint32_t bit = 1u << ((B::STEP >= 32 ? j : i) & 31);
+                    const uint32_t rank = e.y + (uint32_t)__popc(e.x & (bit - 1u));
+                    const float2 v = value(mode, image + code_base, pbase, rank, (e.x & bit) != 0u && a.k > 0);
+                    if (plain) {
+                        x[q][t] = v;
+                    } else {
+                        const float2 prev = peer == 0 ? make_float2(0.f, 0.f) : x[q][t];
+                        x[q][t] = make_float2(prev.x + v.x, prev.y + v.y);
+                    }
+                }
+            }
+        };
+        if (bits == 8)
+            bins(std::integral_constant<int, 8>());
+        else if (bits == 32)
+            bins(std::integral_constant<int, 32>());
+        else
+            bins(std::integral_constant<int, 0>());
+        group_sync<G::WAVES>();  // the images may be overwritten
+    }
+    // the spectrum goes through LDS once, so that every lane can pick its bins' mirrors
+#pragma unroll
+    for (int q = 0; q < B::PER; ++q) {
+        const int w = B::index(tid, q), f = flat((B::b(w) << LOGM) + B::j(w));
+#pragma unroll
+        for (int t = 0; t < B::RHO; ++t) d[flat_plus(f, t * B::STEP)] = x[q][t];
+    }
+    if (tg < G::CPW * G::WC && tg % G::WC == G::WC - 1) nyquist[group * G::CPW + tg / G::WC] = xn;
+    if constexpr (G::WAVES == 1) __syncthreads();  // the twiddle table
+    group_sync<G::WAVES>();
+#pragma unroll
+    for (int q = 0; q < B::PER; ++q) {
+        const int w = B::index(tid, q), j = B::j(w), b = B::b(w);
+#pragma unroll
+        for (int t = 0; t < B::RHO; ++t) {
+            const int k = j + t * B::STEP;
+            // M - k = (STEP - j) + (RHO - 1 - t) * STEP for j > 0
+            const int mirror = j == 0 ? flat((b << LOGM) + ((G::M - t * B::STEP) & (G::M - 1)))
+                                      : flat_plus(flat((b << LOGM) + B::STEP - j), (B::RHO - 1 - t) * B::STEP);
+            float2 p = d[mirror], s = x[q][t];
+            if (t == 0 && k == 0) {  // imaginary parts of the DC and Nyquist bins are ignored
+                p = make_float2(nyquist[b].x, 0.f);
+                s.y = 0.f;
+            }
+            x[q][t] = split_inv(s, p, split_twiddle<LOGM>(tb, k));
+        }
+    }
+    group_sync<G::WAVES>();
+    const float scale = gain * (1.0f / (float)(2 * G::M));
+    const bool whole = !TABLE && aligned && (c0 + G::T) * (size_t)(2 * G::M) <= n;
+    if (whole) {
+        float2* dst = reinterpret_cast<float2*>(out) + c0 * (size_t)G::M;
+        fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
+            dst[(b << LOGM) + i + o] = make_float2(v.x * scale, v.y * scale);
+        });
+    } else {
+        fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
+            const Span sp = chunk_span<TABLE>(tab, c0 + (size_t)b, C, 2 * G::M, n, aligned);
+            store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, sp.pairs, make_float2(v.x * scale, v.y * scale));
+        });
+    }
+}
+
+// ------------------------------------------------- stage-level transforms ----
+template <int LOGM, int NT>
+__global__ __launch_bounds__(NT) void k_chunk_rfft(const float* __restrict__ in, size_t n, size_t C, int aligned, Tables tb,
+                                                   float2* __restrict__ spec, uint32_t sstride)
+{
+    using G = Geo<LOGM, NT>;
+    extern __shared__ __attribute__((aligned(16))) float2 smem[];
+    float2* d = smem;
+    float2* tw = smem + G::E;
+    const int tid = threadIdx.x;
+    const size_t c0 = (size_t)blockIdx.x * G::T;
+    load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
+    forward_tile<G, LOGM, false>(in, n, c0, C, aligned, TableArg<false>(), d, tw, tid);
+    __syncthreads();
+    for (int w = tid; w < G::E; w += NT) {
+        const int k = w & (G::M - 1), b = w >> LOGM;
+        if (c0 + (size_t)b >= C) continue;
+        float2* X = spec + (c0 + (size_t)b) * (size_t)sstride;
+        const int base = b << LOGM;
+        X[k] = split_bin<LOGM>(d[flat(base + k)], d[flat(base + ((G::M - k) & (G::M - 1)))], k, tb);
+        if (k == 0) X[G::M] = nyquist_bin<LOGM>(d, b << LOGM);
+    }
+}
+
+template <int LOGM, int NT>
+__global__ __launch_bounds__(NT) void k_chunk_irfft(const float2* __restrict__ spec, uint32_t sstride, size_t C, Tables tb,
+                                                    float* __restrict__ out, size_t n, int aligned)
+{
+    using G = Geo<LOGM, NT>;
+    constexpr int RL = stage_radix_log(LOGM);
+    using B = Butterflies<LOGM, G::LOGE, NT, RL>;
+    extern __shared__ __attribute__((aligned(16))) float2 smem[];
+    float2* d = smem;
+    float2* tw = smem + G::E;
+    const int tid = threadIdx.x;
+    const size_t c0 = (size_t)blockIdx.x * G::T;
+    load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
+    float2 x[B::PER][B::RHO];
+#pragma unroll
+    for (int q = 0; q < B::PER; ++q) {
+        const int w = B::index(tid, q), j = B::j(w);
+        const size_t c = c0 + (size_t)B::b(w);
+#pragma unroll
+        for (int t = 0; t < B::RHO; ++t) {
+            const int k = j + t * B::STEP;
+            x[q][t] = make_float2(0.f, 0.f);
+            if (c < C) {
+                const float2* X = spec + c * (size_t)sstride;
+                float2 s = X[k], p = X[G::M - k];
+                if (k == 0) s.y = p.y = 0.f;
+                x[q][t] = split_inv(s, p, split_twiddle<LOGM>(tb, k));
+            }
+        }
+    }
+    __syncthreads();
+    const float scale = 1.0f / (float)(2 * G::M);
+    fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
+        const Span sp = chunk_span<false>(TableArg<false>(), c0 + (size_t)b, C, 2 * G::M, n, aligned);
+        store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, sp.pairs, make_float2(v.x * scale, v.y * scale));
+    });
+}
+
+// ---------------------------------------------------------------- launch ----
+template <typename K>
+hipError_t allow_lds(K kernel, size_t bytes)
+{
+    if (bytes <= 48 * 1024) return hipSuccess;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
+PackArgs pack_args(const CodecArgs& a)
+{
+    PackArgs p;
+    p.k = a.k;
+    p.W = (codec_bins(a.L, a.time_domain) + 31) / 32;
+    p.S = (uint32_t)a.S;
+    p.word3 = a.word3;
+    p.static_vmax = a.static_vmax;
+    p.bits = a.bits;
+    p.m = a.m;
+    return p;
+}
+HeaderInfo header_info(const CodecArgs& a, int write)
+{
+    return HeaderInfo{write, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S,
+                      a.hdr_theta, a.time_domain ? 1u : 0u, (uint32_t)a.hdr_scale};
+}
+int alignment(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; }
+
+template <int LOGM, bool TABLE>
+hipError_t compress_as(const float* in, size_t n, const CodecArgs& a, uint8_t* stream, uint8_t* records, uint32_t* ctl,
+                       Tables t, hipStream_t s)
+{
+    constexpr int NT = uniform_threads<LOGM>();
+    using G = Geo<LOGM, NT>;
+    const size_t lds = (size_t)G::GROUPS * (G::REGION + 4 * G::IMAGE) + (size_t)G::TW * sizeof(float2);
+    auto kern = k_chunk_compress<LOGM, NT, TABLE>;
+    const hipError_t e = allow_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    FFTSP_LAUNCH("chunk_compress", kern, dim3((unsigned)((a.C + G::T - 1) / G::T)), dim3(NT), lds, s, in, n, a.C,
+                 alignment(in), t, pack_args(a), stream, records, header_info(a, a.write_header), ctl,
+                 table_arg<TABLE>(a.tab));
+    return hipGetLastError();
+}
+
+template <int LOGM, bool TABLE>
+hipError_t decompress_as(const PeerList& streams, int npeers, int plain, const CodecArgs& a, float* out, size_t n, float gain,
+                         uint32_t* ctl, const StatusNote& note, uint32_t* verdicts, Tables t, hipStream_t s)
+{
+    constexpr int NT = uniform_threads<LOGM>();
+    using G = Geo<LOGM, NT>;
+    const uint32_t stride = (uint32_t)a.S + 16u;  // slack: a code is fetched as two words
+    const size_t need = (size_t)G::CPW * stride, data = (size_t)(G::E / G::GROUPS) * sizeof(float2);
+    const size_t region = need > data ? need : data;  // both are multiples of 16
+    const size_t lds = G::GROUPS * region + (size_t)G::TW * sizeof(float2);
+    auto kern = k_chunk_decompress<LOGM, NT, TABLE>;
+    const hipError_t e = allow_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    FFTSP_LAUNCH("chunk_decompress", kern, dim3((unsigned)((a.C + G::T - 1) / G::T)), dim3(NT), lds, s, streams,
+                 (uint32_t)npeers, plain, a.C, t, pack_args(a), header_info(a, a.write_header), out, n, alignment(out), gain,
+                 (uint32_t)region, stride, ctl, note, verdicts, table_arg<TABLE>(a.tab));
+    return hipGetLastError();
+}
+
+template <int LOGM>
+hipError_t rfft_as(const float* in, size_t n, size_t C, float2* spec, uint32_t sstride, Tables t, hipStream_t s)
+{
+    constexpr int NT = uniform_threads<LOGM>();
+    using G = Geo<LOGM, NT>;
+    const size_t lds = (size_t)(G::E + G::TW) * sizeof(float2);
+    auto kern = k_chunk_rfft<LOGM, NT>;
+    const hipError_t e = allow_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    FFTSP_LAUNCH("rfft_chunk", kern, dim3((unsigned)((C + G::T - 1) / G::T)), dim3(NT), lds, s, in, n, C, alignment(in), t,
+                 spec, sstride);
+    return hipGetLastError();
+}
+template <int LOGM>
+hipError_t irfft_as(const float2* spec, uint32_t sstride, size_t n, size_t C, float* out, Tables t, hipStream_t s)
+{
+    constexpr int NT = uniform_threads<LOGM>();
+    using G = Geo<LOGM, NT>;
+    const size_t lds = (size_t)(G::E + G::TW) * sizeof(float2);
+    auto kern = k_chunk_irfft<LOGM, NT>;
+    const hipError_t e = allow_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    FFTSP_LAUNCH("irfft_chunk", kern, dim3((unsigned)((C + G::T - 1) / G::T)), dim3(NT), lds, s, spec, sstride, C, t, out, n,
+                 alignment(out));
+    return hipGetLastError();
+}
+
+}  // namespace
+
+#define FFTSP_CHUNK_SIZES(X) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14)
+
+hipError_t launch_chunk_compress(const float* in, size_t n, int logL, const CodecArgs& a, uint8_t* stream, uint8_t* records,
+                                 uint32_t* ctl, Tables t, hipStream_t s)
+{
+    if (a.C > 0x7fffffffu || (a.tab && a.C > (size_t)kMaxTableChunks)) return hipErrorInvalidValue;
+    switch (logL - 1) {
+#define X(p) \
+    case p:  \
+        return a.tab ? compress_as<p, true>(in, n, a, stream, records, ctl, t, s) \
+                     : compress_as<p, false>(in, n, a, stream, records, ctl, t, s);
+        FFTSP_CHUNK_SIZES(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_chunk_decompress(const PeerList& streams, int npeers, int plain, int logL, const CodecArgs& a, float* out,
+                                   size_t n, float gain, uint32_t* ctl, const StatusNote& note, uint32_t* verdicts, Tables t,
+                                   hipStream_t s)
+{
+    if (a.C > 0x7fffffffu || (a.tab && a.C > (size_t)kMaxTableChunks)) return hipErrorInvalidValue;
+    switch (logL - 1) {
+#define X(p) \
+    case p:  \
+        return a.tab ? decompress_as<p, true>(streams, npeers, plain, a, out, n, gain, ctl, note, verdicts, t, s) \
+                     : decompress_as<p, false>(streams, npeers, plain, a, out, n, gain, ctl, note, verdicts, t, s);
+        FFTSP_CHUNK_SIZES(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_chunk_rfft(const float* in, size_t n, int logL, size_t C, float* spec, uint32_t sstride, Tables t,
+                             hipStream_t s)
+{
+    if (C > 0x7fffffffu) return hipErrorInvalidValue;
+    switch (logL - 1) {
+#define X(p) \
+    case p: return rfft_as<p>(in, n, C, reinterpret_cast<float2*>(spec), sstride, t, s);
+        FFTSP_CHUNK_SIZES(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_chunk_irfft(const float* spec, uint32_t sstride, size_t n, int logL, size_t C, float* out, Tables t,
+                              hipStream_t s)
+{
+    if (C > 0x7fffffffu) return hipErrorInvalidValue;
+    switch (logL - 1) {
+#define X(p) \
+    case p: return irfft_as<p>(reinterpret_cast<const float2*>(spec), sstride, n, C, out, t, s);
+        FFTSP_CHUNK_SIZES(X)
+#undef X
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace fftsp

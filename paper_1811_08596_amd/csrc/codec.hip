@@ -14,7 +14,7 @@
 // survivor counts and finds the survivors' largest component, which fixes eps
 // (pbase) of Algorithm 1.  A last pass flags, ranks (wave ballots + popcounts),
 // quantizes and bit-packs.
-#include "internal.h"
+#include "codec_core.h"
 
 namespace fftsp {
 namespace {
@@ -23,55 +23,6 @@ constexpr int NT = kTileThreads;     // 256 lanes = 4 waves
 constexpr int ROWS = 8;              // rows of 64 bins per wave
 constexpr int WAVE_BINS = ROWS * 64; // 512
 static_assert(kTile == 4 * WAVE_BINS, "tile geometry");
-
-// The sign bit is masked: a finite sum of squares has none, and a NaN that carries one must still land inside the
-// 31-bit key space the histogram and the radix digits are sized for (selection among non-finite bins is then
-// ordinary integer work on their bit patterns, and exactly k bins survive whatever the input holds).
-__device__ __forceinline__ uint32_t key_of(float2 z)
-{
-    return __float_as_uint(__fmaf_rn(z.x, z.x, __fmul_rn(z.y, z.y))) & 0x7FFFFFFFu;
-}
-__device__ __forceinline__ uint32_t vbits_of(float2 z)
-{
-    const uint32_t a = __float_as_uint(z.x) & 0x7FFFFFFFu, b = __float_as_uint(z.y) & 0x7FFFFFFFu;
-    return a > b ? a : b;
-}
-// What is ranked and coded is either a complex frequency bin (two codes) or, for time-domain Top-k, a sample of
-// the gradient itself (one code; the rank key is the bit pattern of |x|, an exact magnitude order).
-__device__ __forceinline__ uint32_t key_of(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
-__device__ __forceinline__ uint32_t vbits_of(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
-template <bool REAL>
-struct Elem {
-    using T = float2;
-    static constexpr uint32_t kCodes = 2;
-    static __device__ __forceinline__ T zero() { return make_float2(0.f, 0.f); }
-};
-template <>
-struct Elem<true> {
-    using T = float;
-    static constexpr uint32_t kCodes = 1;
-    static __device__ __forceinline__ T zero() { return 0.f; }
-};
-// samples of chunk c that exist (time domain: the last chunk may end early, the rest counts as zeros)
-template <bool REAL>
-__device__ __forceinline__ uint32_t present_of(size_t n, size_t c, uint32_t B)
-{
-    if constexpr (REAL) {
-        const size_t left = n - c * (size_t)B;
-        return left < (size_t)B ? (uint32_t)left : B;
-    } else {
-        return B;
-    }
-}
-
-// a plain 16-byte value that the compiler keeps in registers
-typedef uint32_t u32x4 __attribute__((vector_size(16)));
-
-// number of set bits of a wave-uniform mask below this lane (v_mbcnt_lo/hi: two instructions, no 64-bit math)
-__device__ __forceinline__ uint32_t prefix_popc(uint64_t mask)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
 
 // Cooperative load of one tile of the spectrum buffer, [tbase, tbase+count), into LDS as whole 16-byte pieces.
 // A tile is contiguous in the buffer in either bin order (paired runs are tile-aligned), so lanes then pick
@@ -108,16 +59,6 @@ __device__ __forceinline__ void tile_to_lds(const uint32_t* __restrict__ X, uint
         for (uint32_t i = tid; i < count; i += kTileThreads) stage[i] = unpack_half2(X[tbase + i]);
     }
 }
-
-// What a kernel's input or output array holds: samples (time domain), or complex bins as binary32 or binary16 pairs.
-template <bool REAL, bool HALF>
-struct Stored {
-    using T = typename Cx<HALF>::One;
-};
-template <bool HALF>
-struct Stored<true, HALF> {
-    using T = float;
-};
 
 // Time domain: samples [tbase, tbase + kTile) of a chunk, zeros from `present` on.
 __device__ __forceinline__ void tile_to_lds(const float* __restrict__ X, uint32_t tbase, uint32_t present, float* stage,
@@ -162,45 +103,6 @@ __device__ __forceinline__ uint32_t slot_of(const RowSlots& s, int r, uint32_t j
 {
     if (s.linear) return r == 0 ? s.first : s.lin + (uint32_t)(r * s.step);
     return spec_index(j0 + (uint32_t)r * 64u, pair_log) - tbase;
-}
-
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ uint32_t wave_max(uint32_t v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t u = __shfl_xor(v, o, 64);
-        v = u > v ? u : v;
-    }
-    return v;
-}
-
-// 32bit_to_Nbit of Algorithm 1 (value > max clamps to the top code; below eps flushes to the zero code)
-__device__ __forceinline__ uint32_t quantize(uint32_t fbits, uint32_t pbase, int bits, int shift)
-{
-    if (bits == 32) return fbits;
-    const uint32_t Mmax = (1u << (bits - 1)) - 1u;
-    const uint32_t q = (fbits & 0x7FFFFFFFu) >> shift;
-    uint32_t c = 0;
-    if (q >= pbase) {
-        c = q - pbase + 1u;
-        c = c > Mmax ? Mmax : c;
-    }
-    const uint32_t sign = c ? (fbits >> 31) : 0u;
-    return (sign << (bits - 1)) | c;
-}
-// Nbit_to_32bit of Algorithm 1
-__device__ __forceinline__ uint32_t dequantize(uint32_t code, uint32_t pbase, int bits, int shift)
-{
-    if (bits == 32) return code;
-    const uint32_t Mmax = (1u << (bits - 1)) - 1u;
-    const uint32_t c = code & Mmax, sign = (code >> (bits - 1)) & 1u;
-    return c ? (((c - 1u + pbase) << shift) | (sign << 31)) : 0u;
 }
 
 __global__ void k_zero_u32(uint32_t* p, size_t count)
@@ -507,15 +409,6 @@ __device__ __forceinline__ void walk_tiles(const uint2* __restrict__ cd, const u
 
 constexpr int kStageBatch = 9;  // tiles whose candidates a wave of k_resolve fetches in one go
 
-struct HeaderInfo {
-    int write;
-    uint64_t n;
-    uint32_t L, C, N, m, k, S;
-    float theta;
-    uint32_t domain;  // 0: records hold frequency bins, 1: samples (time-domain Top-k)
-    uint32_t scale;   // log2 of the factor on the spectrum (two's complement; half-precision variant), else 0
-};
-
 // One workgroup per chunk: finish the radix select on the candidates, break ties by bin order,
 // scan the tiles, find the survivors' largest component, write the record header and zero the
 // code words that two tiles will share.
@@ -800,26 +693,7 @@ __global__ __launch_bounds__(RT) void k_resolve(uint32_t Tn, uint32_t k, int bit
     const uint32_t rec_words = (uint32_t)(S / 4) - 4u - W;
     for (uint32_t w = code_words + tid; w < rec_words; w += RT) codes[w] = 0u;
 
-    if (hdr.write && c == 0 && tid < 16) {
-        uint32_t v = 0;
-        switch (tid) {
-            case 0: v = 0x31505346u; break;  // "FSP1"
-            case 1: v = 1u; break;
-            case 2: v = (uint32_t)hdr.n; break;
-            case 3: v = (uint32_t)(hdr.n >> 32); break;
-            case 4: v = hdr.L; break;
-            case 5: v = hdr.C; break;
-            case 6: v = hdr.N; break;
-            case 7: v = hdr.m; break;
-            case 8: v = hdr.k; break;
-            case 9: v = hdr.S; break;
-            case 10: v = __float_as_uint(hdr.theta); break;
-            case 11: v = hdr.domain; break;
-            case 12: v = hdr.scale; break;
-            default: break;
-        }
-        reinterpret_cast<uint32_t*>(stream)[tid] = v;
-    }
+    if (hdr.write && c == 0 && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
 }
 
 // ------------------------------------------------------------------ emit ----
@@ -1039,12 +913,7 @@ __device__ __forceinline__ void group_prefix_chunk(const uint8_t* __restrict__ s
     }
     if (tid == 0) {
         bool bad = s_carry != k || rec[2] != k || rec[3] != word3;
-        if (hdr.write && first_of_stream) {
-            const uint32_t* h = reinterpret_cast<const uint32_t*>(stream);
-            bad = bad || h[0] != 0x31505346u || h[1] != 1u || h[2] != (uint32_t)hdr.n ||
-                  h[3] != (uint32_t)(hdr.n >> 32) || h[4] != hdr.L || h[5] != hdr.C || h[6] != hdr.N ||
-                  h[7] != hdr.m || h[8] != hdr.k || h[9] != hdr.S || h[11] != hdr.domain || h[12] != hdr.scale;
-        }
+        if (hdr.write && first_of_stream) bad = bad || header_bad(hdr, reinterpret_cast<const uint32_t*>(stream));
         *verdict = bad ? 6u : 0u;
     }
 }
@@ -1496,7 +1365,7 @@ hipError_t launch_zero_control(uint8_t* ws_base, const Workspace& w, size_t C, h
 hipError_t launch_clear_status(uint8_t* ws_base, const Workspace& w, hipStream_t s)
 {
     FFTSP_LAUNCH("zero_fill", k_zero_u32, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(ws_base + w.status),
-                 (size_t)1);
+                 (size_t)5);  // the status word and the note on verdicts behind it
     return hipGetLastError();
 }
 

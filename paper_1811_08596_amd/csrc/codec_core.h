@@ -1,0 +1,160 @@
+// Device-side building blocks of selection, Algorithm 1 and packing (shared by the per-tile kernels in codec.hip and
+// the chunk-resident kernels in chunk.hip).  Internal: nothing here is part of the C ABI.
+#pragma once
+#include "internal.h"
+
+namespace fftsp {
+namespace {
+
+// The sign bit is masked: a finite sum of squares has none, and a NaN that carries one must still land inside the
+// 31-bit key space the histogram and the radix digits are sized for (selection among non-finite bins is then
+// ordinary integer work on their bit patterns, and exactly k bins survive whatever the input holds).
+__device__ __forceinline__ uint32_t key_of(float2 z)
+{
+    return __float_as_uint(__fmaf_rn(z.x, z.x, __fmul_rn(z.y, z.y))) & 0x7FFFFFFFu;
+}
+__device__ __forceinline__ uint32_t vbits_of(float2 z)
+{
+    const uint32_t a = __float_as_uint(z.x) & 0x7FFFFFFFu, b = __float_as_uint(z.y) & 0x7FFFFFFFu;
+    return a > b ? a : b;
+}
+// What is ranked and coded is either a complex frequency bin (two codes) or, for time-domain Top-k, a sample of
+// the gradient itself (one code; the rank key is the bit pattern of |x|, an exact magnitude order).
+__device__ __forceinline__ uint32_t key_of(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
+__device__ __forceinline__ uint32_t vbits_of(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
+template <bool REAL>
+struct Elem {
+    using T = float2;
+    static constexpr uint32_t kCodes = 2;
+    static __device__ __forceinline__ T zero() { return make_float2(0.f, 0.f); }
+};
+template <>
+struct Elem<true> {
+    using T = float;
+    static constexpr uint32_t kCodes = 1;
+    static __device__ __forceinline__ T zero() { return 0.f; }
+};
+// samples of chunk c that exist (time domain: the last chunk may end early, the rest counts as zeros)
+template <bool REAL>
+__device__ __forceinline__ uint32_t present_of(size_t n, size_t c, uint32_t B)
+{
+    if constexpr (REAL) {
+        const size_t left = n - c * (size_t)B;
+        return left < (size_t)B ? (uint32_t)left : B;
+    } else {
+        return B;
+    }
+}
+
+// a plain 16-byte value that the compiler keeps in registers
+typedef uint32_t u32x4 __attribute__((vector_size(16)));
+
+// number of set bits of a wave-uniform mask below this lane (v_mbcnt_lo/hi: two instructions, no 64-bit math)
+__device__ __forceinline__ uint32_t prefix_popc(uint64_t mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// What a kernel's input or output array holds: samples (time domain), or complex bins as binary32 or binary16 pairs.
+template <bool REAL, bool HALF>
+struct Stored {
+    using T = typename Cx<HALF>::One;
+};
+template <bool HALF>
+struct Stored<true, HALF> {
+    using T = float;
+};
+
+// Scans and reductions over the 64 lanes with data-parallel-primitive moves (shifts within rows of 16 lanes, then
+// broadcasts across rows): one instruction per step where a shuffle through LDS takes an address and a round trip.
+// Lanes a move does not reach contribute zero.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_scan_incl(uint32_t x)
+{
+    x += dpp_or_zero<0x111, 0xF>(x);  // row_shr:1
+    x += dpp_or_zero<0x112, 0xF>(x);
+    x += dpp_or_zero<0x114, 0xF>(x);
+    x += dpp_or_zero<0x118, 0xF>(x);
+    x += dpp_or_zero<0x142, 0xA>(x);  // lane 15 of rows 0 and 2 into rows 1 and 3
+    x += dpp_or_zero<0x143, 0xC>(x);  // lane 31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_incl(v), 63);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    auto most = [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a > b ? a : b; };
+    v = most(v, dpp_or_zero<0x111, 0xF>(v));
+    v = most(v, dpp_or_zero<0x112, 0xF>(v));
+    v = most(v, dpp_or_zero<0x114, 0xF>(v));
+    v = most(v, dpp_or_zero<0x118, 0xF>(v));
+    v = most(v, dpp_or_zero<0x142, 0xA>(v));
+    v = most(v, dpp_or_zero<0x143, 0xC>(v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// 32bit_to_Nbit of Algorithm 1 (value > max clamps to the top code; below eps flushes to the zero code)
+__device__ __forceinline__ uint32_t quantize(uint32_t fbits, uint32_t pbase, int bits, int shift)
+{
+    if (bits == 32) return fbits;
+    const int top = (1 << (bits - 1)) - 1;
+    const int q = (int)((fbits & 0x7FFFFFFFu) >> shift) - (int)(pbase - 1u);  // both are below 2^31
+    const int c = q < 0 ? 0 : (q > top ? top : q);
+    const uint32_t sign = c ? (fbits >> 31) : 0u;
+    return (sign << (bits - 1)) | (uint32_t)c;
+}
+// Nbit_to_32bit of Algorithm 1; bits of `code` above the lowest `bits` are ignored
+__device__ __forceinline__ uint32_t dequantize(uint32_t code, uint32_t pbase, int bits, int shift)
+{
+    if (bits == 32) return code;
+    const uint32_t c = code & ((1u << (bits - 1)) - 1u);
+    const uint32_t v = ((c + (pbase - 1u)) << shift) | ((code << (32 - bits)) & 0x80000000u);
+    return c ? v : 0u;
+}
+
+struct HeaderInfo {
+    int write;
+    uint64_t n;
+    uint32_t L, C, N, m, k, S;
+    float theta;
+    uint32_t domain;  // 0: records hold frequency bins, 1: samples (time-domain Top-k)
+    uint32_t scale;   // log2 of the factor on the spectrum (two's complement; half-precision variant), else 0
+};
+constexpr uint32_t kMagic = 0x31505346u;  // "FSP1"
+// word i of the 64-byte stream header
+__device__ __forceinline__ uint32_t header_word(const HeaderInfo& hdr, int i)
+{
+    switch (i) {
+        case 0: return kMagic;
+        case 1: return 1u;
+        case 2: return (uint32_t)hdr.n;
+        case 3: return (uint32_t)(hdr.n >> 32);
+        case 4: return hdr.L;
+        case 5: return hdr.C;
+        case 6: return hdr.N;
+        case 7: return hdr.m;
+        case 8: return hdr.k;
+        case 9: return hdr.S;
+        case 10: return __float_as_uint(hdr.theta);
+        case 11: return hdr.domain;
+        case 12: return hdr.scale;
+        default: return 0u;
+    }
+}
+// whether a received stream header disagrees with what the caller asked for (theta is informative only)
+__device__ __forceinline__ bool header_bad(const HeaderInfo& hdr, const uint32_t* __restrict__ h)
+{
+    bool bad = false;
+    for (int i = 0; i < 13; ++i)
+        if (i != 10) bad = bad || h[i] != header_word(hdr, i);
+    return bad;
+}
+
+}  // namespace
+}  // namespace fftsp

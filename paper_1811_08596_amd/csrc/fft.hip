@@ -7,9 +7,9 @@
 // M = L/2 complex samples z[j] = x[2j] + i x[2j+1]; an M-point complex FFT is followed
 // by the even/odd split X[k] = E[k] + W_L^k O[k].  The M-point FFT is a Stockham
 // autosort FFT held entirely in LDS (radix 8/4/2 register butterflies, one LDS
-// round trip per stage).  M <= 2^13 fits one workgroup ("small" kernels, several
-// chunks per workgroup when M is tiny).  Larger M is factored M = N1*N2 and done
-// in two LDS-resident passes with a transposed intermediate:
+// round trip per stage).  M <= 2^14 fits one workgroup (chunk.hip, which keeps the rest of
+// the codec there too).  Larger M is factored M = N1*N2 and done in two LDS-resident
+// passes with a transposed intermediate (this file):
 //   pass A: for a tile of TA adjacent columns n2, N1-point FFTs over n1 (stride N2),
 //           times W_M^(n2 k1), stored as runs of N1 values per n2 (row k1 next to row N1-k1);
 //   pass B: for a tile of rows k1 together with the mirrored rows N1-k1, N2-point
@@ -42,111 +42,6 @@ template <int LOGN1>
 constexpr int spread_parts()
 {
     return portions<LOGN1 - 3, kSpreadA>();
-}
-
-// Where chunk c's samples live: elements [first, limit) of the gradient; pairs != 0 allows 8-byte accesses.
-struct Span {
-    size_t first, limit;
-    int pairs;
-};
-template <bool TABLE>
-__device__ __forceinline__ Span chunk_span(const TableArg<TABLE>& tab, size_t c, size_t C, size_t chunk_len, size_t n,
-                                           int aligned8)
-{
-    Span sp;
-    if constexpr (TABLE) {
-        if (c < C) {
-            sp.first = tab.t.goff[c];
-            sp.limit = sp.first + tab.t.glen[c];
-        } else {
-            sp.first = sp.limit = 0;
-        }
-        sp.pairs = aligned8 && !(sp.first & 1u);
-    } else {
-        sp.first = c * chunk_len;
-        sp.limit = n;
-        sp.pairs = aligned8;
-    }
-    return sp;
-}
-
-// ------------------------------------------------------------------ small ---
-// M = 2^LOGM <= 2^13 complex points per chunk, 2^(LOGE-LOGM) chunks per workgroup.
-template <int LOGM, int LOGE, int NT, bool TABLE>
-__global__ __launch_bounds__(NT) void k_fwd_small(const float* __restrict__ in, size_t n, size_t C,
-                                                  float2* __restrict__ spec, uint32_t sstride, Tables tb, int aligned,
-                                                  TableArg<TABLE> tab)
-{
-    constexpr int M = 1 << LOGM, LOGT = LOGE - LOGM, ELEMS = 1 << LOGE;
-    extern __shared__ float2 smem[];
-    float2* d = smem;
-    float2* tw = smem + ELEMS;
-    const int tid = threadIdx.x;
-    const size_t c0 = (size_t)blockIdx.x << LOGT;
-    load_stage_twiddles<LOGM, NT>(tw, tb, tid);
-#pragma unroll
-    for (int q = 0; q < ELEMS / NT; ++q) {
-        const int w = tid + q * NT, i = w & (M - 1), b = w >> LOGM;
-        const Span sp = chunk_span<TABLE>(tab, c0 + b, C, 2 * M, n, aligned);
-        d[sw_idx<LOGT>(i, b)] = load_pair(in, sp.first + 2 * (size_t)i, sp.limit, sp.pairs);
-    }
-    __syncthreads();
-    run_fft<LOGM, LOGT, NT, false>(d, tw, tid);
-#pragma unroll
-    for (int q = 0; q < ELEMS / NT; ++q) {
-        const int w = tid + q * NT, k = w & (M - 1), b = w >> LOGM;
-        const size_t c = c0 + b;
-        if (c >= C) continue;
-        float2* out = spec + c * (size_t)sstride;
-        const float2 a = d[sw_idx<LOGT>(k, b)];
-        if (k == 0) {
-            out[0] = make_float2(a.x + a.y, 0.f);
-            out[M] = make_float2(a.x - a.y, 0.f);
-        } else {
-            const float2 bq = d[sw_idx<LOGT>(M - k, b)];
-            out[k] = split_fwd(a, bq, twiddle(tb, (uint32_t)k << (21 - LOGM)));
-        }
-    }
-}
-
-template <int LOGM, int LOGE, int NT, bool TABLE>
-__global__ __launch_bounds__(NT) void k_inv_small(const float2* __restrict__ spec, uint32_t sstride, size_t n, size_t C,
-                                                  float* __restrict__ out, Tables tb, int aligned, float gain,
-                                                  TableArg<TABLE> tab)
-{
-    constexpr int M = 1 << LOGM, LOGT = LOGE - LOGM, ELEMS = 1 << LOGE;
-    extern __shared__ float2 smem[];
-    float2* d = smem;
-    float2* tw = smem + ELEMS;
-    const int tid = threadIdx.x;
-    const size_t c0 = (size_t)blockIdx.x << LOGT;
-    load_stage_twiddles<LOGM, NT>(tw, tb, tid);
-#pragma unroll
-    for (int q = 0; q < ELEMS / NT; ++q) {
-        const int w = tid + q * NT, k = w & (M - 1), b = w >> LOGM;
-        const size_t c = c0 + b;
-        float2 z = make_float2(0.f, 0.f);
-        if (c < C) {
-            const float2* X = spec + c * (size_t)sstride;
-            float2 a = X[k], bq = X[M - k];
-            if (k == 0) {  // imaginary parts of the DC and Nyquist bins are ignored
-                a.y = 0.f;
-                bq.y = 0.f;
-            }
-            z = split_inv(a, bq, twiddle(tb, (uint32_t)k << (21 - LOGM)));
-        }
-        d[sw_idx<LOGT>(k, b)] = z;
-    }
-    __syncthreads();
-    run_fft<LOGM, LOGT, NT, true>(d, tw, tid);
-    const float scale = gain * (1.0f / (float)(2 * M));  // 1/L is a power of two: the product is gain, rescaled exactly
-#pragma unroll
-    for (int q = 0; q < ELEMS / NT; ++q) {
-        const int w = tid + q * NT, i = w & (M - 1), b = w >> LOGM;
-        const Span sp = chunk_span<TABLE>(tab, c0 + b, C, 2 * M, n, aligned);
-        float2 v = d[sw_idx<LOGT>(i, b)];
-        store_pair(out, sp.first + 2 * (size_t)i, sp.limit, sp.pairs, make_float2(v.x * scale, v.y * scale));
-    }
 }
 
 // Software pipeline of the persistent two-pass kernels.  Vector-memory results return in issue order and are
@@ -717,44 +612,12 @@ __global__ __launch_bounds__(kNT) void k_inv_a(const typename Cx<HALF>::One* __r
 }
 
 // ---------------------------------------------------------------- launch ----
-constexpr int kSmallNT = 256;
-
 template <typename K>
 hipError_t set_lds(K kernel, size_t bytes)
 {
     if (bytes <= 48 * 1024) return hipSuccess;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)bytes);
-}
-
-template <int LOGM, bool TABLE>
-hipError_t small_fwd(const float* in, size_t n, size_t C, float2* spec, uint32_t sstride, Tables t, int aligned,
-                     const ChunkTable* tab, hipStream_t s)
-{
-    constexpr int LOGE = LOGM >= 12 ? LOGM : 12;
-    const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGM)) * sizeof(float2);
-    auto kern = k_fwd_small<LOGM, LOGE, kSmallNT, TABLE>;
-    hipError_t e = set_lds(kern, lds);
-    if (e != hipSuccess) return e;
-    const size_t per = (size_t)1 << (LOGE - LOGM);
-    FFTSP_LAUNCH("rfft_small", kern, dim3((unsigned)((C + per - 1) / per)), dim3(kSmallNT), lds, s, in, n, C, spec, sstride,
-                 t, aligned, table_arg<TABLE>(tab));
-    return hipGetLastError();
-}
-
-template <int LOGM, bool TABLE>
-hipError_t small_inv(const float2* spec, uint32_t sstride, size_t n, size_t C, float* out, Tables t, int aligned,
-                     float gain, const ChunkTable* tab, hipStream_t s)
-{
-    constexpr int LOGE = LOGM >= 12 ? LOGM : 12;
-    const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGM)) * sizeof(float2);
-    auto kern = k_inv_small<LOGM, LOGE, kSmallNT, TABLE>;
-    hipError_t e = set_lds(kern, lds);
-    if (e != hipSuccess) return e;
-    const size_t per = (size_t)1 << (LOGE - LOGM);
-    FFTSP_LAUNCH("irfft_small", kern, dim3((unsigned)((C + per - 1) / per)), dim3(kSmallNT), lds, s, spec, sstride, n, C,
-                 out, t, aligned, gain, table_arg<TABLE>(tab));
-    return hipGetLastError();
 }
 
 // persistent grid: workgroups walk contiguous runs of tiles; two of them are resident per compute unit (512 on
@@ -862,11 +725,6 @@ hipError_t inv_a(const float2* mid_f32, int logM, size_t C, float* out, size_t n
 
 }  // namespace
 
-#define FFTSP_SMALL_CASES(X) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13)
-
-// hist (optional, u32[C][kHistBins]): receives the 12-bit histogram of the keys' top bits when the two-pass
-// kernels run; they first clear zero_words words at zero_ptr (which must cover hist).  *hist_done = 1 if the
-// FFT filled hist, 0 if the caller still has to clear and fill it (single-workgroup sizes).
 int fft_pair_log(int logL)
 {
     const int logM = logL - 1;
@@ -874,7 +732,7 @@ int fft_pair_log(int logL)
 }
 
 hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spec, uint32_t sstride, float2* mid,
-                       Tables t, uint32_t* hist, uint32_t* zero_ptr, size_t zero_words, int* hist_done, int pair_spec,
+                       Tables t, uint32_t* hist, uint32_t* zero_ptr, size_t zero_words, int pair_spec,
                        int* pair_log, const ChunkTable* tab, hipStream_t s, const uint32_t* only_if)
 {
     if (pair_log) *pair_log = 0;
@@ -885,17 +743,7 @@ hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spe
     const uintptr_t addr = reinterpret_cast<uintptr_t>(in);
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     float2* sp = reinterpret_cast<float2*>(spec);
-    if (hist_done) *hist_done = 0;
-    if (C * ((size_t)1 << (logM > 13 ? logM - 13 : 0)) > 0x7fffffffu) return hipErrorInvalidValue;
-    switch (logM) {
-#define X(p) \
-    case p: \
-        return tab ? small_fwd<p, true>(in, n, C, sp, sstride, t, aligned & 1, tab, s) \
-                   : small_fwd<p, false>(in, n, C, sp, sstride, t, aligned & 1, nullptr, s);
-        FFTSP_SMALL_CASES(X)
-#undef X
-        default: break;
-    }
+    if (logM < 15 || C * ((size_t)1 << (logM - 13)) > 0x7fffffffu) return hipErrorInvalidValue;
     // the codec stores its own spectrum in the paired order and wants the histogram; the stage-level entry point
     // wants neither
     if ((hist != nullptr) != (pair_spec != 0)) return hipErrorInvalidValue;
@@ -905,7 +753,6 @@ hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spe
     (tab ? fwd_a<p, true, false>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, tab, 1.0f, s, only_if)      \
          : fwd_a<p, false, false>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, nullptr, 1.0f, s, only_if))
     switch (logN1) {
-        case 7: e = FWD_A(7); break;
         case 8: e = FWD_A(8); break;
         case 9: e = FWD_A(9); break;
         case 10: e = FWD_A(10); break;
@@ -914,7 +761,6 @@ hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spe
     }
 #undef FWD_A
     if (e != hipSuccess) return e;
-    if (hist_done) *hist_done = hist != nullptr;
     if (pair_log && pair_spec) *pair_log = logN1;
     if (hist) {
         switch (logN2) {
@@ -942,16 +788,7 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
     const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     const float2* sp = reinterpret_cast<const float2*>(spec);
-    if (C * ((size_t)1 << (logM > 13 ? logM - 13 : 0)) > 0x7fffffffu) return hipErrorInvalidValue;
-    switch (logM) {
-#define X(p) \
-    case p: \
-        return tab ? small_inv<p, true>(sp, sstride, n, C, out, t, aligned & 1, gain, tab, s) \
-                   : small_inv<p, false>(sp, sstride, n, C, out, t, aligned & 1, gain, nullptr, s);
-        FFTSP_SMALL_CASES(X)
-#undef X
-        default: break;
-    }
+    if (logM < 15 || C * ((size_t)1 << (logM - 13)) > 0x7fffffffu) return hipErrorInvalidValue;
     const int logN1 = (logM + 1) / 2, logN2 = logM / 2;
     hipError_t e;
     if (pair_spec) {
@@ -976,7 +813,6 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
     (tab ? inv_a<p, true, false>(mid, logM, C, out, n, t, aligned, gain, tab, s, only_if) \
          : inv_a<p, false, false>(mid, logM, C, out, n, t, aligned, gain, nullptr, s, only_if))
     switch (logN1) {
-        case 7: return INV_A(7);
         case 8: return INV_A(8);
         case 9: return INV_A(9);
         case 10: return INV_A(10);

@@ -8,14 +8,16 @@ namespace {
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+// Fused multiply-adds are written out wherever two products meet: left to the compiler, which product is rounded first
+// depends on the kernel around it, and kernels that must agree bit for bit would not.
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 {
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_float2(__fmaf_rn(a.x, b.x, -(a.y * b.y)), __fmaf_rn(a.x, b.y, a.y * b.x));
 }
 // a * conj(b)
 __device__ __forceinline__ float2 cmulc(float2 a, float2 b)
 {
-    return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+    return make_float2(__fmaf_rn(a.x, b.x, a.y * b.y), __fmaf_rn(a.y, b.x, -(a.x * b.y)));
 }
 
 // exp(-2 pi i E / 2^22), E < 2^22
@@ -69,21 +71,18 @@ __device__ __forceinline__ void bf8(float2* v)
     float2 o[4] = {v[1], v[3], v[5], v[7]};
     bf4<INV>(e);
     bf4<INV>(o);
-    // o[k] *= W8^k
-    float2 o1 = o[1], o3 = o[3];
-    if (INV) {
-        o[1] = make_float2(c * (o1.x - o1.y), c * (o1.x + o1.y));
-        o[3] = make_float2(-c * (o3.x + o3.y), c * (o3.x - o3.y));
-    } else {
-        o[1] = make_float2(c * (o1.x + o1.y), c * (o1.y - o1.x));
-        o[3] = make_float2(c * (o3.y - o3.x), -c * (o3.x + o3.y));
-    }
+    // v[k], v[k+4] = e[k] +- W8^k o[k]; the odd powers of W8 are (1 -+ i) / sqrt(2) times a real factor
+    v[0] = cadd(e[0], o[0]);
+    v[4] = csub(e[0], o[0]);
     o[2] = rot90<INV>(o[2]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        v[k] = cadd(e[k], o[k]);
-        v[k + 4] = csub(e[k], o[k]);
-    }
+    v[2] = cadd(e[2], o[2]);
+    v[6] = csub(e[2], o[2]);
+    const float2 o1 = INV ? make_float2(o[1].x - o[1].y, o[1].x + o[1].y) : make_float2(o[1].x + o[1].y, o[1].y - o[1].x);
+    const float2 o3 = INV ? make_float2(-(o[3].x + o[3].y), o[3].x - o[3].y) : make_float2(o[3].y - o[3].x, -(o[3].x + o[3].y));
+    v[1] = make_float2(__fmaf_rn(c, o1.x, e[1].x), __fmaf_rn(c, o1.y, e[1].y));
+    v[5] = make_float2(__fmaf_rn(-c, o1.x, e[1].x), __fmaf_rn(-c, o1.y, e[1].y));
+    v[3] = make_float2(__fmaf_rn(c, o3.x, e[3].x), __fmaf_rn(c, o3.y, e[3].y));
+    v[7] = make_float2(__fmaf_rn(-c, o3.x, e[3].x), __fmaf_rn(-c, o3.y, e[3].y));
 }
 
 // 16 points: four radix-4 butterflies over n1 (elements n0, n0+4, n0+8, n0+12), the inner twiddles W16^(n0 k0),
@@ -102,8 +101,8 @@ __device__ __forceinline__ void bf16(float2* v)
     }
     // W16^m = (cos(m pi/8), -sin(m pi/8)), conjugated for the inverse
     auto rot = [](float2 a, float wr, float wi) {  // a * (wr + i wi) forward, a * (wr - i wi) inverse
-        return INV ? make_float2(a.x * wr + a.y * wi, a.y * wr - a.x * wi)
-                   : make_float2(a.x * wr - a.y * wi, a.y * wr + a.x * wi);
+        return INV ? make_float2(__fmaf_rn(a.x, wr, a.y * wi), __fmaf_rn(a.y, wr, -(a.x * wi)))
+                   : make_float2(__fmaf_rn(a.x, wr, -(a.y * wi)), __fmaf_rn(a.y, wr, a.x * wi));
     };
     y[1][1] = rot(y[1][1], c1, -s1);   // W^1
     y[1][2] = rot(y[1][2], h, -h);     // W^2
@@ -243,12 +242,39 @@ __device__ __forceinline__ void store_pair(float* __restrict__ out, size_t gi, s
 }
 
 
+// Where chunk c's samples live: elements [first, limit) of the gradient; pairs != 0 allows 8-byte accesses.
+struct Span {
+    size_t first, limit;
+    int pairs;
+};
+template <bool TABLE>
+__device__ __forceinline__ Span chunk_span(const TableArg<TABLE>& tab, size_t c, size_t C, size_t chunk_len, size_t n,
+                                           int aligned8)
+{
+    Span sp;
+    if constexpr (TABLE) {
+        if (c < C) {
+            sp.first = tab.t.goff[c];
+            sp.limit = sp.first + tab.t.glen[c];
+        } else {
+            sp.first = sp.limit = 0;
+        }
+        sp.pairs = aligned8 && !(sp.first & 1u);
+    } else {
+        sp.first = c * chunk_len;
+        sp.limit = n;
+        sp.pairs = aligned8;
+    }
+    return sp;
+}
+
+
 // X[k] from a = Z[k], b = Z[M-k], w = W_L^k   (0 < k < M)
 __device__ __forceinline__ float2 split_fwd(float2 a, float2 b, float2 w)
 {
     const float er = 0.5f * (a.x + b.x), ei = 0.5f * (a.y - b.y);
     const float dr = 0.5f * (a.x - b.x), di = 0.5f * (a.y + b.y);
-    return make_float2(er + (w.x * di + w.y * dr), ei - (w.x * dr - w.y * di));
+    return make_float2(er + __fmaf_rn(w.x, di, w.y * dr), ei - __fmaf_rn(w.x, dr, -(w.y * di)));
 }
 
 // 2 Z[k] from a = X[k], b = X[M-k], w = W_L^k  (the factor 1/2 is folded into the final 1/L)
@@ -256,7 +282,7 @@ __device__ __forceinline__ float2 split_inv(float2 a, float2 b, float2 w)
 {
     const float er = a.x + b.x, ei = a.y - b.y;
     const float dr = a.x - b.x, di = a.y + b.y;
-    const float orr = w.x * dr + w.y * di, oi = w.x * di - w.y * dr;  // conj(w) * d
+    const float orr = __fmaf_rn(w.x, dr, w.y * di), oi = __fmaf_rn(w.x, di, -(w.y * dr));  // conj(w) * d
     return make_float2(er - oi, ei + orr);
 }
 

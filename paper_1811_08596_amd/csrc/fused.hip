@@ -712,7 +712,6 @@ hipError_t launch_fused_rfft(const float* in, size_t n, int logL, size_t C, floa
                      scratch, spec, sstride, t, hist, ctl, knobs.spin_limit);                     \
     } while (0)
     switch (logM) {
-        case 14: FFTSP_FUSED_FWD(7, 7); break;
         case 15: FFTSP_FUSED_FWD(8, 7); break;
         case 16: FFTSP_FUSED_FWD(8, 8); break;
         case 17: FFTSP_FUSED_FWD(9, 8); break;
@@ -742,7 +741,6 @@ hipError_t launch_fused_irfft(const float2* spec, uint32_t sstride, size_t n, in
                      aligned, gain, scratch, out, t, ctl, knobs.spin_limit);                         \
     } while (0)
     switch (logM) {
-        case 14: FFTSP_FUSED_INV(7, 7); break;
         case 15: FFTSP_FUSED_INV(8, 7); break;
         case 16: FFTSP_FUSED_INV(8, 8); break;
         case 17: FFTSP_FUSED_INV(9, 8); break;

@@ -85,19 +85,20 @@ constexpr int kKeyShift = 31 - kHistBits;     // bucket = key >> 19
 constexpr size_t kControlBytes = 4096;  // control block at the start of every workspace
 constexpr int kCtlGaveUpWord = 1;       // u32 index of the fused kernels' give-up word inside the control block
 
-// The fused transforms (fused.hip) take chunk lengths 2^15 .. 2^20 and address three turn buffers of 4 MiB per XCD
+// The fused transforms (fused.hip) take chunk lengths 2^16 .. 2^20 and address three turn buffers of 4 MiB per XCD
 // inside the intermediate's region, so they take calls whose own intermediate is at least that large (96 MiB: about
 // 25 million samples); smaller calls keep the per-pass kernels and their workspace stays what those need.
 constexpr size_t kFusedScratchBytes = (size_t)8 * 3 * 64 * 8192 * 8;
 static inline bool fused_shape(int logL, size_t C)
 {
     const int logM = logL - 1;
-    return logM >= 14 && logM <= 19 && (C << logL) * 4 >= kFusedScratchBytes;
+    return logM >= 15 && logM <= 19 && (C << logL) * 4 >= kFusedScratchBytes;
 }
 
 // Where everything lives inside the caller's workspace (byte offsets, 256-aligned).
 struct Workspace {
     size_t status;    // u32[1024] control block: word 0 = device status, word 1 = "the fused transform gave up",
+                      //           words 2..4 = where per-record verdicts are (chunk.h),
                       //           from word 32 on the hand-over counters of the fused kernels (fused.hip)
     size_t hist;      // u32[C][kHistBins]         (directly after status: one fill zeroes both)
     size_t sel;       // u32[C][8]  bstar, need, tau, quota, pbase, vmax, -, decode verdict
@@ -215,22 +216,21 @@ std::string report();
 // per-device tables; returns hipSuccess or the failing HIP error
 hipError_t get_tables(Tables* out);
 
-// FFT launchers (fft.hip).  Chunk c covers in[c*L, min(n, (c+1)*L)), zero beyond n.
+// FFT launchers of the two-pass chunk lengths, 2^16 and up (fft.hip).  Chunk c covers in[c*L, min(n, (c+1)*L)), zero beyond n.
 // spec: chunk c's L/2+1 bins start at spec + 2*c*sstride floats (sstride in complex bins: L/2+1 for the dense
 // layout of the stage-level entry points, a multiple of 16 inside the codec so that every chunk starts on a
-// 128-byte line); mid: C*L floats of scratch (unused when L <= 2^14).
-// hist (optional): u32[C][kHistBins]; the two-pass kernels clear zero_words words at zero_ptr (covering hist and
-// the status words) and fill hist, setting *hist_done = 1; otherwise the caller clears and fills it.
-// pair_spec != 0 asks the two-pass kernels to write the spectrum in paired order; *pair_log receives log2(N1)
-// if they did, 0 otherwise (single-workgroup sizes always write natural order).
+// 128-byte line); mid: C*L floats of scratch.
+// hist (optional): u32[C][kHistBins]; the kernels clear zero_words words at zero_ptr (covering hist and the status
+// words) and fill hist.  pair_spec != 0 (exactly when hist is given): the spectrum is written in paired order and
+// *pair_log receives log2(N1), otherwise 0.
 // tab != nullptr: per-tensor launch, chunk c is in[tab->goff[c] .. + tab->glen[c]) (n is not used)
 // only_if (optional, two-pass sizes): device word; the kernels return at once unless it is non-zero
 hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spec, uint32_t sstride, float2* mid,
-                       Tables t, uint32_t* hist, uint32_t* zero_ptr, size_t zero_words, int* hist_done, int pair_spec,
+                       Tables t, uint32_t* hist, uint32_t* zero_ptr, size_t zero_words, int pair_spec,
                        int* pair_log, const ChunkTable* tab, hipStream_t s, const uint32_t* only_if = nullptr);
-// log2(N1) of the two-pass factorisation for chunk length 2^logL, 0 for single-workgroup sizes
+// log2(N1) of the two-pass factorisation for chunk length 2^logL (2^15 and up; 2^15 in the half-precision variant only)
 int fft_pair_log(int logL);
-// pair_spec != 0: the spectrum is in paired order (two-pass sizes only); the output is gain/L times the plain sum
+// pair_spec != 0: the spectrum is in paired order; the output is gain/L times the plain sum
 hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL, size_t C, float* out, float2* mid,
                         Tables t, int pair_spec, float gain, const ChunkTable* tab, hipStream_t s,
                         const uint32_t* only_if = nullptr);
