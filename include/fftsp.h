@@ -218,8 +218,9 @@ int fftsp_topk_decompress(const void* d_packed, size_t packed_bytes, float* d_gr
 /* ---- per-tensor variant: segment i = d_grad[seg_offsets[i] .. seg_offsets[i+1]) is one chunk of
  *      L_i = max(32, next power of two >= its size); seg_offsets (nseg+1 entries, ascending) is on the HOST
  *      and is consumed before the call returns.  Sizes above 2^22 are FFTSP_EUNSUPPORTED.
- *      Records follow tensor order in the stream.  Tensors that pad to the same L_i run together as the chunks
- *      of shared launches (up to 64 at a time), so the cost grows with the number of distinct lengths rather
+ *      Records follow tensor order in the stream.  Tensors of up to 2^15 samples, whatever their lengths, run as one
+ *      launch per direction (up to 128 at a time).  Longer ones that pad to the same L_i run together as the chunks of
+ *      shared launch sets (up to 64 at a time), so their cost grows with the number of distinct lengths rather
  *      than with the number of tensors.  These launch sets run on up to four streams at once (the caller's and
  *      streams of the library's own that fork from and join back into it, so the call is still one unit of work
  *      on the caller's stream and can be captured into a graph); the workspace holds one region per stream, each

@@ -764,9 +764,22 @@ struct SegBatch {
     ChunkTable tab;
 };
 
-// Groups the tensors by padded length (ascending) and cuts every group into launch sets.  Records keep tensor
-// order in the stream: tensor i's record starts rec_off[i] bytes after the stream header.
-static std::vector<SegBatch> plan_segments(const size_t* off, int nseg, float theta, int bits, bool with_tables)
+// A launch of tensors that fit one workgroup each (chunk.h).
+struct TensorLaunch {
+    uint32_t pieces;
+    int top_logL;
+    TensorTable tab;
+};
+
+// How a per-tensor call is launched: the tensors of up to 2^kChunkMaxLogL samples in as few launches as the table
+// allows, longest first; the longer ones grouped by padded length (ascending), every group cut into launch sets.
+// Records keep tensor order in the stream: tensor i's record starts rec_off[i] bytes after the stream header.
+struct SegmentPlan {
+    std::vector<TensorLaunch> shorts;
+    std::vector<SegBatch> batches;
+    size_t short_count = 0;
+};
+static SegmentPlan plan_segments(const size_t* off, int nseg, float theta, int bits, bool with_tables)
 {
     std::vector<uint32_t> len(nseg);
     std::vector<size_t> rec_off(nseg);
@@ -779,15 +792,48 @@ static std::vector<SegBatch> plan_segments(const size_t* off, int nseg, float th
         order[i] = i;
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return len[a] < len[b]; });
-    std::vector<SegBatch> out;
-    for (int j = 0; j < nseg; ++j) {
-        const int i = order[j];
-        if (out.empty() || out.back().L != len[i] || out.back().count == batch_cap(len[i])) {
-            out.emplace_back();
-            out.back().L = len[i];
-            out.back().count = 0;
+    SegmentPlan out;
+    size_t first_long = 0;
+    while (first_long < order.size() && len[order[first_long]] <= (1u << kChunkMaxLogL)) ++first_long;
+    out.short_count = first_long;
+    if (with_tables) {
+        uint32_t used = 0;  // entries of the open launch
+        for (size_t j = first_long; j-- > 0;) {  // longest first
+            const int i = order[j];
+            const int logL = log2_exact(len[i]);
+            if (out.shorts.empty() || used == (uint32_t)kMaxTensors) {
+                out.shorts.emplace_back();
+                TensorLaunch& l = out.shorts.back();
+                l.pieces = 0;
+                l.top_logL = logL;
+                l.tab.base = (uint32_t)(first_long - 1 - j);
+                for (int g = 0; g < kChunkMaxLogL - 4; ++g) {
+                    const uint32_t L = 1u << (g + 5);
+                    l.tab.kept[g] = kept(L, theta);
+                    l.tab.stride[g] = (uint32_t)record_stride(L, l.tab.kept[g], bits);
+                }
+                used = 0;
+            }
+            TensorLaunch& l = out.shorts.back();
+            l.tab.goff[used] = off[i];
+            l.tab.glen[used] = (uint32_t)(off[i + 1] - off[i]);
+            l.tab.roff[used] = rec_off[i];
+            TensorPiece* last = l.pieces ? &l.tab.piece[l.pieces - 1] : nullptr;
+            if (last && last->logm == logL - 1 && last->count < tensors_per_workgroup(logL))
+                ++last->count;
+            else
+                l.tab.piece[l.pieces++] = TensorPiece{(uint8_t)used, 1, (uint8_t)(logL - 1), 0};
+            ++used;
         }
-        SegBatch& b = out.back();
+    }
+    for (size_t j = first_long; j < order.size(); ++j) {
+        const int i = order[j];
+        if (out.batches.empty() || out.batches.back().L != len[i] || out.batches.back().count == batch_cap(len[i])) {
+            out.batches.emplace_back();
+            out.batches.back().L = len[i];
+            out.batches.back().count = 0;
+        }
+        SegBatch& b = out.batches.back();
         if (with_tables) {
             b.tab.goff[b.count] = off[i];
             b.tab.glen[b.count] = (uint32_t)(off[i + 1] - off[i]);
@@ -798,7 +844,7 @@ static std::vector<SegBatch> plan_segments(const size_t* off, int nseg, float th
     return out;
 }
 
-// The launch sets of a per-tensor call are independent chains of short kernels (most tensors are small), so they
+// The launch sets of the longer tensors are independent chains of short kernels, so they
 // run on up to kSegLanes streams at once: the caller's and streams of the library's own that fork from and join
 // back into the caller's through events.  The call stays one unit of work on the caller's stream and can be
 // captured into a graph.  Every lane works in a workspace region of its own, sized for the largest launch set.
@@ -826,11 +872,18 @@ static int segment_lanes(size_t nbatches)
     return (int)(nbatches < (size_t)kSegLanes ? nbatches : (size_t)kSegLanes);
 }
 
+// where the short tensors' verdicts are: behind the lanes' regions, or behind a control block of their own
+static size_t segment_verdicts(const SegmentPlan& plan)
+{
+    const size_t lanes = (size_t)segment_lanes(plan.batches.size()) * segment_region_bytes(plan.batches);
+    return lanes > kControlBytes ? lanes : kControlBytes;
+}
+
 size_t fftsp_workspace_bytes_segments(const size_t* seg_offsets, int nseg, int bits)
 {
     if (segments_ok(seg_offsets, nseg) != FFTSP_OK || mantissa(bits) < 0) return 0;
-    const std::vector<SegBatch> batches = plan_segments(seg_offsets, nseg, 0.5f, bits, false);
-    return (size_t)segment_lanes(batches.size()) * segment_region_bytes(batches);
+    const SegmentPlan plan = plan_segments(seg_offsets, nseg, 0.5f, bits, false);
+    return segment_verdicts(plan) + align256(plan.short_count * 4);
 }
 
 // Heaviest launch set first, each onto the lane with the least work so far (work = samples); lane 0 is the caller's
@@ -960,24 +1013,31 @@ static Workspace region_workspace(size_t count, uint32_t L, size_t region_offset
     return w;
 }
 
-static CodecArgs segment_args(const SegBatch& b, const size_t* seg_offsets, int nseg, float theta, int bits, int m)
+// the stream header's part of the arguments
+static CodecArgs segment_header(const size_t* seg_offsets, int nseg, float theta, int bits, int m)
 {
     CodecArgs a{};
-    a.C = b.count;
-    a.L = b.L;
-    a.k = kept(b.L, theta);
     a.bits = bits;
     a.m = m;
-    a.S = record_stride(b.L, a.k, bits);
-    a.word3 = b.L;
-    a.sstride = padded_bins(b.L);
-    a.tab = &b.tab;
     a.hdr_n = seg_offsets[nseg] - seg_offsets[0];
     a.hdr_L = 0;
     a.hdr_C = (uint32_t)nseg;
     a.hdr_k = 0;
     a.hdr_S = 0;
     a.hdr_theta = theta;
+    return a;
+}
+
+static CodecArgs segment_args(const SegBatch& b, const size_t* seg_offsets, int nseg, float theta, int bits, int m)
+{
+    CodecArgs a = segment_header(seg_offsets, nseg, theta, bits, m);
+    a.C = b.count;
+    a.L = b.L;
+    a.k = kept(b.L, theta);
+    a.S = record_stride(b.L, a.k, bits);
+    a.word3 = b.L;
+    a.sstride = padded_bins(b.L);
+    a.tab = &b.tab;
     return a;
 }
 
@@ -998,30 +1058,36 @@ int fftsp_compress_segments(const float* d_grad, const size_t* seg_offsets, int 
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
     uint8_t* out = static_cast<uint8_t*>(d_packed);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const std::vector<SegBatch> batches = plan_segments(seg_offsets, nseg, theta, bits, true);
+    const SegmentPlan plan = plan_segments(seg_offsets, nseg, theta, bits, true);
+    const std::vector<SegBatch>& batches = plan.batches;
     const size_t region = segment_region_bytes(batches);
     const int lanes = prof::enabled() ? 1 : segment_lanes(batches.size());  // per-kernel timing wants one chain
     const std::vector<int> lane_of = assign_lanes(batches, lanes);
-    const hipError_t e = run_on_lanes(s, lane_of, lanes, [&](size_t bi, hipStream_t st, int lane) {
-        const SegBatch& b = batches[bi];
-        // every lane clears and uses the status words and histograms of its own region; nothing on the sender
-        // raises a status, and the caller reads the first region's word
-        const Workspace w = region_workspace(b.count, b.L, (size_t)lane * region);
-        CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
-        a.write_header = (bi == 0);
-        const int logL = log2_exact(b.L);
-        if (logL <= kChunkMaxLogL)
-            return launch_chunk_compress(d_grad, 0, logL, a, out, out + kStreamHeader,
-                                         bi == 0 ? reinterpret_cast<uint32_t*>(ws) : nullptr, t, st);
-        float* spec = reinterpret_cast<float*>(ws + w.spec);
-        hipError_t pe = launch_rfft(d_grad, 0, logL, b.count, spec, a.sstride,
-                                    reinterpret_cast<float2*>(ws + w.mid), t, reinterpret_cast<uint32_t*>(ws + w.hist),
-                                    reinterpret_cast<uint32_t*>(ws + w.status),
-                                    (w.hist - w.status) / 4 + b.count * (size_t)kHistBins, 1, &a.pair_log,
-                                    &b.tab, st);
-        if (pe == hipSuccess) pe = launch_encode(spec, a, out, out + kStreamHeader, ws, w, 1, st);
-        return pe;
-    });
+    hipError_t e = hipSuccess;
+    for (size_t i = 0; i < plan.shorts.size() && e == hipSuccess; ++i) {
+        CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
+        hdr.write_header = i == 0;
+        // the longer tensors' kernels clear the control block; without any, the first of these launches does
+        e = launch_tensors_compress(d_grad, plan.shorts[i].tab, plan.shorts[i].pieces, plan.shorts[i].top_logL,
+                                    QuantizerArgs{bits, m}, hdr, out, out + kStreamHeader,
+                                    i == 0 && batches.empty() ? reinterpret_cast<uint32_t*>(ws) : nullptr, t, s);
+    }
+    if (e == hipSuccess && !batches.empty())
+        e = run_on_lanes(s, lane_of, lanes, [&](size_t bi, hipStream_t st, int lane) {
+            const SegBatch& b = batches[bi];
+            // every lane clears and uses the status words and histograms of its own region; nothing on the sender
+            // raises a status, and the caller reads the first region's word
+            const Workspace w = region_workspace(b.count, b.L, (size_t)lane * region);
+            CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
+            a.write_header = bi == 0 && plan.shorts.empty();
+            float* spec = reinterpret_cast<float*>(ws + w.spec);
+            hipError_t pe = launch_rfft(d_grad, 0, log2_exact(b.L), b.count, spec, a.sstride,
+                                        reinterpret_cast<float2*>(ws + w.mid), t, reinterpret_cast<uint32_t*>(ws + w.hist),
+                                        reinterpret_cast<uint32_t*>(ws + w.status),
+                                        (w.hist - w.status) / 4 + b.count * (size_t)kHistBins, 1, &a.pair_log, &b.tab, st);
+            if (pe == hipSuccess) pe = launch_encode(spec, a, out, out + kStreamHeader, ws, w, 1, st);
+            return pe;
+        });
     return hip_status(e);
 }
 
@@ -1043,32 +1109,36 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
     const uint8_t* in = static_cast<const uint8_t*>(d_packed);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    const std::vector<SegBatch> batches = plan_segments(seg_offsets, nseg, theta, bits, true);
+    const SegmentPlan plan = plan_segments(seg_offsets, nseg, theta, bits, true);
+    const std::vector<SegBatch>& batches = plan.batches;
     const size_t region = segment_region_bytes(batches);
     const int lanes = prof::enabled() ? 1 : segment_lanes(batches.size());
     const std::vector<int> lane_of = assign_lanes(batches, lanes);
-    // every launch set raises the one status word at the start of the workspace, from whatever lane it runs on:
-    // it is cleared here, before the lanes fork
-    hipError_t e = launch_clear_status(ws, make_workspace(1, 32), s);
-    if (e == hipSuccess)
+    // every launch set of longer tensors raises the one status word at the start of the workspace, from whatever lane
+    // it runs on: it is cleared here, before the lanes fork.  The short ones leave verdicts.
+    hipError_t e = hipSuccess;
+    if (!batches.empty()) e = launch_clear_status(ws, make_workspace(1, 32), s);
+    const size_t verd = segment_verdicts(plan);
+    if (verd / 4 > 0xffffffffu) return FFTSP_EHIP;
+    for (size_t i = 0; i < plan.shorts.size() && e == hipSuccess; ++i) {
+        CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
+        hdr.write_header = i == 0;
+        const StatusNote note{i == 0 ? (uint32_t)plan.short_count : 0u, (uint32_t)(verd / 4)};
+        e = launch_tensors_decompress(in, plan.shorts[i].tab, plan.shorts[i].pieces, plan.shorts[i].top_logL,
+                                      QuantizerArgs{bits, m}, hdr, d_grad_out, reinterpret_cast<uint32_t*>(ws), note,
+                                      batches.empty(), reinterpret_cast<uint32_t*>(ws + verd), t, s);
+    }
+    if (e == hipSuccess && !batches.empty())
         e = run_on_lanes(s, lane_of, lanes, [&](size_t bi, hipStream_t st, int lane) {
             const SegBatch& b = batches[bi];
             Workspace w = region_workspace(b.count, b.L, (size_t)lane * region);
             w.status = 0;
             CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
-            a.write_header = bi == 0;  // the header is looked at once
-            const int logL = log2_exact(b.L);
-            if (logL <= kChunkMaxLogL) {
-                PeerList one{};
-                one.p[0] = in;
-                return launch_chunk_decompress(one, 1, 1, logL, a, d_grad_out, 0, 1.0f, reinterpret_cast<uint32_t*>(ws),
-                                               StatusNote{0u, 0u}, nullptr, t, st);
-            }
-            a.pair_log = fft_pair_log(logL);
+            a.pair_log = fft_pair_log(log2_exact(b.L));
             float* spec = reinterpret_cast<float*>(ws + w.spec);
-            hipError_t pe = launch_decode(in, in + kStreamHeader, a, spec, ws, w, bi == 0, 0, st);
+            hipError_t pe = launch_decode(in, in + kStreamHeader, a, spec, ws, w, bi == 0 && plan.shorts.empty(), 0, st);
             if (pe == hipSuccess)
-                pe = launch_irfft(spec, a.sstride, 0, logL, b.count, d_grad_out,
+                pe = launch_irfft(spec, a.sstride, 0, log2_exact(b.L), b.count, d_grad_out,
                                   reinterpret_cast<float2*>(ws + w.mid), t, a.pair_log != 0, 1.0f, &b.tab, st);
             return pe;
         });

@@ -22,15 +22,43 @@ struct StatusNote {
 };
 constexpr uint32_t kStatusNoteMagic = 0x46535653u;
 
-// Sender.  a.tab != nullptr: per-tensor launch (records at a.tab->roff).  ctl (optional): the workspace's control block.
+// Sender.  ctl: the workspace's control block.
 hipError_t launch_chunk_compress(const float* in, size_t n, int logL, const CodecArgs& a, uint8_t* stream, uint8_t* records,
                                  uint32_t* ctl, Tables t, hipStream_t s);
 // Receiver.  streams: whole packed streams (64-byte header first).  plain: one stream, taken as it is; otherwise the
-// streams are summed in list order, starting from zero.  verdicts (optional): u32[npeers][C], announced by `note`;
-// nullptr: a bad record raises ctl[0], which is then not cleared here (a.write_header = check the stream header).
+// streams are summed in list order, starting from zero.  verdicts: u32[npeers][C], announced by `note`.
 hipError_t launch_chunk_decompress(const PeerList& streams, int npeers, int plain, int logL, const CodecArgs& a, float* out,
                                    size_t n, float gain, uint32_t* ctl, const StatusNote& note, uint32_t* verdicts, Tables t,
                                    hipStream_t s);
+
+// Per-tensor calls: the tensors of up to 2^kChunkMaxLogL samples, longest first, cut into launches of kMaxTensors.  The
+// table travels by value as a kernel argument (no host-to-device copy to order against the stream).
+constexpr int kMaxTensors = 128;
+struct TensorPiece {  // what one workgroup does: entries first .. first+count-1, all of 2^(logm+1) samples
+    uint8_t first, count, logm, pad;
+};
+struct TensorTable {
+    uint64_t goff[kMaxTensors];  // element offset of the tensor's first sample in the gradient
+    uint64_t roff[kMaxTensors];  // byte offset of its record from the first record of the stream
+    uint32_t glen[kMaxTensors];  // samples present; the rest of the chunk is zero
+    TensorPiece piece[kMaxTensors];
+    uint32_t kept[kChunkMaxLogL - 4], stride[kChunkMaxLogL - 4];  // kept bins and record bytes, by logm - 4
+    uint32_t base;               // number of the table's first entry among all such tensors of the call
+};
+static_assert(sizeof(TensorTable) <= 3584, "kernel arguments are at most 4 KiB");
+struct QuantizerArgs {
+    int bits, m;
+};
+int tensors_per_workgroup(int logL);
+// top_logL: the longest in the table; hdr: stream header (written or checked iff hdr.write_header).
+// ctl (optional on the sender): the control block, cleared by the sender.
+hipError_t launch_tensors_compress(const float* in, const TensorTable& t, uint32_t pieces, int top_logL, const QuantizerArgs& q,
+                                   const CodecArgs& hdr, uint8_t* stream, uint8_t* records, uint32_t* ctl, Tables tb,
+                                   hipStream_t s);
+// note.count != 0: this launch leaves the note in the control block (clear: and clears the status word)
+hipError_t launch_tensors_decompress(const uint8_t* stream, const TensorTable& t, uint32_t pieces, int top_logL,
+                                     const QuantizerArgs& q, const CodecArgs& hdr, float* out, uint32_t* ctl,
+                                     const StatusNote& note, int clear, uint32_t* verdicts, Tables tb, hipStream_t s);
 // stage-level transforms, dense natural-order spectra
 hipError_t launch_chunk_rfft(const float* in, size_t n, int logL, size_t C, float* spec, uint32_t sstride, Tables t,
                              hipStream_t s);

@@ -21,12 +21,22 @@
 // without a workgroup barrier.
 #include "chunk.h"
 #include "codec_core.h"
+#define FFTSP_FMA_WRITTEN_OUT
 #include "fft_core.h"
 
 #include <type_traits>
 
 namespace fftsp {
 namespace {
+
+// every LOGM there is
+#define FFTSP_CHUNK_SIZES(X) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14)
+
+struct GroupScratch {
+    uint32_t bucket, need, count, listed;
+    uint32_t a[16], b[16], v[16];
+};
+static_assert(sizeof(GroupScratch) % 16 == 0, "the LDS regions behind it stay aligned");
 
 template <int LOGM, int NTHREADS>
 struct Geo {
@@ -47,6 +57,9 @@ struct Geo {
     static constexpr int TW = LOGM <= 11 ? M : 2048 + (1 << (LOGM - 11));  // entries of the stage twiddle table
     // LDS bytes of a group: its complex values, later its histogram, candidate list and record image
     static constexpr int DATA = E / GROUPS * 8, REGION = DATA > (4 << HB) ? DATA : (4 << HB);
+    static constexpr int RECEIVER_FRONT_RAW = TABLE_WORDS * 8 + T * 8;  // bitmap words with their prefixes, Nyquist bins
+    static constexpr int SCRATCH = GROUPS * (int)sizeof(GroupScratch) + 16;  // and the word the groups agree through
+    static constexpr int RECEIVER_FRONT = SCRATCH + (RECEIVER_FRONT_RAW + 15) / 16 * 16;
     // record image of one chunk of up to 16-bit codes, in words; short chunks keep theirs beside the data
     static constexpr int IMAGE = HB ? 0 : ((16 + 4 * (M / 32 + 1) + 4 * (M + 1) + 16) / 4 + 3) & ~3;
 };
@@ -203,18 +216,63 @@ struct NoOut {
     __device__ void operator()(int, int, int, float2) const {}
 };
 
-// Forward transform of chunks c0 .. c0+T-1 (those below cend exist) up to Z[k] in d, visible to the group.
+// Which chunks a workgroup holds in its T slots, and where their samples and records are.
+// Uniform calls: chunks c0 .. c0+T-1 of a gradient cut into equal pieces.
+struct UniformChunks {
+    size_t first_sample, n, first_record, c0;
+    uint32_t slots, chunk_len, S;  // slots: chunks from c0 on that exist
+    int aligned;
+    __device__ __forceinline__ UniformChunks(size_t n_, size_t C, uint32_t T, uint32_t L, uint32_t S_, int aligned_)
+        : n(n_), c0((size_t)blockIdx.x * T), chunk_len(L), S(S_), aligned(aligned_)
+    {
+        first_sample = c0 * L;
+        first_record = c0 * S;
+        slots = C - c0 < (size_t)T ? (uint32_t)(C - c0) : T;
+    }
+    __device__ __forceinline__ bool exists(int b) const { return (uint32_t)b < slots; }
+    __device__ __forceinline__ Span span(int b) const { return Span{first_sample + (size_t)((uint32_t)b * chunk_len), n, aligned}; }
+    // all T slots hold whole chunks: the samples are one aligned run from first_sample on
+    __device__ __forceinline__ bool whole(int T) const { return aligned && first_sample + (size_t)((uint32_t)T * chunk_len) <= n; }
+    __device__ __forceinline__ size_t record(int b) const { return first_record + (size_t)((uint32_t)b * S); }
+    __device__ __forceinline__ size_t verdict(int b) const { return c0 + (size_t)b; }
+};
+// Per-tensor calls: one tensor in the first slot of each group (spread over workgroups rather than packed: there are
+// few of them, and it is their latency that counts).  A lane only ever asks for its own group's slots.
+struct ListedChunk {
+    size_t first_sample, first_record, number;
+    uint32_t length;
+    int slot, aligned;  // slot: -1 if the group has none
+    __device__ __forceinline__ ListedChunk(const TensorTable& t, const TensorPiece& piece, int group, int cpw, int aligned_)
+    {
+        const bool has = group < (int)piece.count;
+        const uint32_t entry = (uint32_t)piece.first + (has ? (uint32_t)group : 0u);
+        first_sample = t.goff[entry];
+        first_record = t.roff[entry];
+        length = t.glen[entry];
+        number = (size_t)(t.base + entry);
+        slot = has ? group * cpw : -1;
+        aligned = aligned_ && !(first_sample & 1u);
+    }
+    __device__ __forceinline__ bool exists(int b) const { return b == slot; }
+    __device__ __forceinline__ Span span(int b) const
+    {
+        return exists(b) ? Span{first_sample, first_sample + length, aligned} : Span{0, 0, 0};
+    }
+    __device__ __forceinline__ bool whole(int) const { return false; }
+    __device__ __forceinline__ size_t record(int) const { return first_record; }
+    __device__ __forceinline__ size_t verdict(int) const { return number; }
+};
+
+// Forward transform of the workgroup's chunks up to Z[k] in d, visible to the group.
 // The stage twiddle table must have been filled before (the barrier for it is taken here, behind the loads).
-template <typename G, int LOGM, bool TABLE>
-__device__ __forceinline__ void forward_tile(const float* __restrict__ in, size_t n, size_t c0, size_t cend, int aligned,
-                                             const TableArg<TABLE>& tab, float2* d, const float2* tw, int tid)
+template <typename G, int LOGM, typename Where>
+__device__ __forceinline__ void forward_tile(const float* __restrict__ in, const Where& where, float2* d, const float2* tw, int tid)
 {
     constexpr int RL = stage_radix_log(LOGM);
     using B = Butterflies<LOGM, G::LOGE, G::NT, RL>;
     float2 v[B::PER][B::RHO];
-    const bool whole = !TABLE && aligned && (c0 + G::T) * (size_t)(2 * G::M) <= n;
-    if (whole) {
-        const float2* src = reinterpret_cast<const float2*>(in) + c0 * (size_t)G::M;
+    if (where.whole(G::T)) {
+        const float2* src = reinterpret_cast<const float2*>(in + where.first_sample);
 #pragma unroll
         for (int q = 0; q < B::PER; ++q) {
             const int w = B::index(tid, q), g = (B::b(w) << LOGM) + B::j(w);
@@ -225,7 +283,7 @@ __device__ __forceinline__ void forward_tile(const float* __restrict__ in, size_
 #pragma unroll
         for (int q = 0; q < B::PER; ++q) {
             const int w = B::index(tid, q);
-            const Span sp = chunk_span<TABLE>(tab, c0 + B::b(w), cend, 2 * G::M, n, aligned);
+            const Span sp = where.span(B::b(w));
 #pragma unroll
             for (int t = 0; t < B::RHO; ++t)
                 v[q][t] = load_pair(in, sp.first + 2 * (size_t)(B::j(w) + t * B::STEP), sp.limit, sp.pairs);
@@ -259,11 +317,6 @@ __device__ __forceinline__ float2 nyquist_bin(const float2* d, int base)
 }
 
 // --------------------------------------------------------- select and pack ----
-struct GroupScratch {
-    uint32_t bucket, need, count, listed;
-    uint32_t a[16], b[16], v[16];
-};
-
 constexpr uint32_t kListCap = 256;  // keys of the threshold's bucket that are finished from a list
 
 // The `need`-th largest of `count` listed keys that share all bits above `low`: tau grows bit by bit, a ballot counts
@@ -615,52 +668,52 @@ __device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z
     }
 }
 
+// record geometry of tensors of 2^(logm+1) samples
+__device__ __forceinline__ PackArgs pack_args_of(const QuantizerArgs& q, const TensorTable& t, uint32_t logm)
+{
+    PackArgs a;
+    a.k = t.kept[logm - 4u];
+    a.W = ((1u << logm) + 32u) / 32u;
+    a.S = t.stride[logm - 4u];
+    a.word3 = 2u << logm;
+    a.static_vmax = 0u;
+    a.bits = q.bits;
+    a.m = q.m;
+    return a;
+}
+
 // what the first workgroup of a call leaves in the control block (see chunk.h)
-__device__ __forceinline__ void write_control(uint32_t* __restrict__ ctl, const StatusNote& note, int tid)
+__device__ __forceinline__ void write_control(uint32_t* __restrict__ ctl, const StatusNote& note, bool clear, int tid)
 {
     if (tid == 0) {
-        ctl[0] = 0u;
-        ctl[1] = 0u;
+        if (clear) {
+            ctl[0] = 0u;
+            ctl[1] = 0u;
+        }
         ctl[2] = note.count;
         ctl[3] = note.offset;
         ctl[4] = note.count ? kStatusNoteMagic : 0u;
     }
 }
 
-template <bool TABLE>
-__device__ __forceinline__ size_t record_of(const TableArg<TABLE>& tab, size_t c, uint32_t S)
-{
-    if constexpr (TABLE)
-        return (size_t)tab.t.roff[c];
-    else
-        return c * (size_t)S;
-}
-
-// Sender: one workgroup per T chunks.
-template <int LOGM, int NT, bool TABLE>
-__global__ __launch_bounds__(NT) void k_chunk_compress(const float* __restrict__ in, size_t n, size_t C, int aligned,
-                                                       Tables tb, PackArgs a, uint8_t* __restrict__ stream,
-                                                       uint8_t* __restrict__ records, HeaderInfo hdr,
-                                                       uint32_t* __restrict__ ctl, TableArg<TABLE> tab)
+// Sender of one workgroup.
+template <int LOGM, int NT, typename Where>
+__device__ __forceinline__ void compress_workgroup(const float* __restrict__ in, const Where& where, const Tables& tb,
+                                                   const PackArgs& a, uint8_t* __restrict__ records, uint8_t* lds, int tid)
 {
     using G = Geo<LOGM, NT>;
-    extern __shared__ __attribute__((aligned(16))) float2 smem[];
-    __shared__ GroupScratch gs[G::GROUPS];
-    __shared__ uint32_t wg_most;
-    const int tid = threadIdx.x, lane = tid & 63, group = tid / G::NL, wig = (tid >> 6) % G::WAVES;
-    uint8_t* region = reinterpret_cast<uint8_t*>(smem) + group * G::REGION;
+    const int lane = tid & 63, group = tid / G::NL, wig = (tid >> 6) % G::WAVES;
+    GroupScratch* gs = reinterpret_cast<GroupScratch*>(lds);
+    uint32_t* wg_most = reinterpret_cast<uint32_t*>(gs + G::GROUPS);
+    uint8_t* regions = lds + G::SCRATCH;
+    uint8_t* region = regions + group * G::REGION;
     // the workgroup's point g lies at d[flat(g)]; a group's points are a multiple of 256, so its base moves freely
     float2* d = reinterpret_cast<float2*>(region) - group * (G::E / G::GROUPS);
-    float2* tw = smem + G::GROUPS * G::REGION / 8;
+    float2* tw = reinterpret_cast<float2*>(regions + G::GROUPS * G::REGION);
     uint32_t* images = reinterpret_cast<uint32_t*>(tw + G::TW);  // short chunks only
-    const size_t c0 = (size_t)blockIdx.x * G::T;
-    if (blockIdx.x == 0) {
-        if (ctl) write_control(ctl, StatusNote{0u, 0u}, tid);
-        if (hdr.write && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
-    }
-    if (tid == 0) wg_most = 0u;
+    if (tid == 0) *wg_most = 0u;
     load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
-    forward_tile<G, LOGM, TABLE>(in, n, c0, C, aligned, tab, d, tw, tid);
+    forward_tile<G, LOGM>(in, where, d, tw, tid);
     uint32_t* mine = reinterpret_cast<uint32_t*>(region);
     auto bins_of = [&](int b, float2 (&z)[G::R], float2& zn) __attribute__((always_inline)) {
         const int base = b << LOGM;
@@ -687,14 +740,14 @@ __global__ __launch_bounds__(NT) void k_chunk_compress(const float* __restrict__
         zn = nyquist_bin<LOGM>(d, base);
     };
     auto pack = [&](int i, const float2 (&z)[G::R], float2 zn, uint32_t* image) __attribute__((always_inline)) {
-        const size_t c = c0 + (size_t)(group * G::CPW + i);
-        const bool live = c < C;
+        const int b = group * G::CPW + i;
+        const bool live = where.exists(b);
         select_and_pack<false, G::R, true, G::LR, G::WAVES, G::GROUPS, G::HB>(
-            z, zn, mine, image, gs[group], &wg_most, tid, a, a.word3, records + (live ? record_of<TABLE>(tab, c, a.S) : 0), live);
+            z, zn, mine, image, gs[group], wg_most, tid, a, a.word3, records + (live ? where.record(b) : 0), live);
     };
     if constexpr (G::HB == 0) {
         for (int i = 0; i < G::CPW; ++i) {  // the bins stay in LDS until their turn comes
-            if (c0 + (size_t)(group * G::CPW + i) >= C) break;  // single-wave groups: no barrier is skipped
+            if (!where.exists(group * G::CPW + i)) break;  // single-wave groups: no barrier is skipped
             float2 z[G::R], zn;
             bins_of(group * G::CPW + i, z, zn);
             pack(i, z, zn, images + group * G::IMAGE);
@@ -710,33 +763,93 @@ __global__ __launch_bounds__(NT) void k_chunk_compress(const float* __restrict__
     }
 }
 
+template <int LOGM, int NT>
+__global__ __launch_bounds__(NT) void k_chunk_compress(const float* __restrict__ in, size_t n, size_t C, int aligned,
+                                                       Tables tb, PackArgs a, uint8_t* __restrict__ stream,
+                                                       uint8_t* __restrict__ records, HeaderInfo hdr,
+                                                       uint32_t* __restrict__ ctl)
+{
+    using G = Geo<LOGM, NT>;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0) {
+        write_control(ctl, StatusNote{0u, 0u}, true, tid);
+        if (tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
+    }
+    const UniformChunks where(n, C, G::T, 2u * G::M, a.S, aligned);
+    compress_workgroup<LOGM, NT>(in, where, tb, a, records, lds, tid);
+}
+
+// lanes a tensor of 2^(LOGM+1) samples gets in a per-tensor launch
+template <int LOGM>
+constexpr int tensor_threads()
+{
+    return uniform_threads<LOGM>();
+}
+template <typename G>
+__device__ __forceinline__ ListedChunk listed(const TensorTable& t, const TensorPiece& piece, int aligned, int tid)
+{
+    return ListedChunk(t, piece, tid / G::NL, G::CPW, aligned);
+}
+template <int LOGM>
+__device__ __forceinline__ void compress_tensors(const float* __restrict__ in, const TensorTable& t, const TensorPiece& piece,
+                                                 int aligned, const Tables& tb, const PackArgs& a,
+                                                 uint8_t* __restrict__ records, uint8_t* lds, int tid)
+{
+    constexpr int NT = tensor_threads<LOGM>();
+    if (tid >= NT) return;
+    compress_workgroup<LOGM, NT>(in, listed<Geo<LOGM, NT>>(t, piece, aligned, tid), tb, a, records, lds, tid);
+}
+
+// The tensors of a per-tensor call that fit one workgroup, whatever their lengths, as one launch: workgroup i does the
+// tensors of piece i.  Waves its length has no use for leave at once (an ended wave takes part in no barrier).
+// TOP: the longest a launch may hold, 2^(TOP+1) samples.
+template <int TOP>
+__global__ __launch_bounds__(tensor_threads<TOP>()) void k_tensors_compress(const float* __restrict__ in, int aligned, Tables tb,
+                                                                            QuantizerArgs q, uint8_t* __restrict__ stream,
+                                                                            uint8_t* __restrict__ records, HeaderInfo hdr,
+                                                                            uint32_t* __restrict__ ctl, TensorTable t)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0) {
+        if (ctl) write_control(ctl, StatusNote{0u, 0u}, true, tid);
+        if (hdr.write && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
+    }
+    const TensorPiece piece = t.piece[blockIdx.x];
+    const PackArgs a = pack_args_of(q, t, piece.logm);
+#define X(p) else if (p <= TOP && piece.logm == p) compress_tensors<(p <= TOP ? p : 4)>(in, t, piece, aligned, tb, a, records, lds, tid);
+    if (false) {
+    }
+    FFTSP_CHUNK_SIZES(X)
+#undef X
+}
+
 // ---------------------------------------------------------------- receiver ----
-// Receiver: one workgroup per T chunks; several peers' streams are summed bin by bin in list order.
+// Receiver of one workgroup; several peers' streams are summed bin by bin in list order.
 // region: LDS bytes of a group for its complex values or its record images, whichever is larger (single-wave groups run
 // without barriers, so no group may touch another's bytes).
-template <int LOGM, int NT, bool TABLE>
-__global__ __launch_bounds__(NT) void k_chunk_decompress(PeerList streams, uint32_t npeers, int plain, size_t C, Tables tb,
-                                                         PackArgs a, HeaderInfo hdr, float* __restrict__ out, size_t n,
-                                                         int aligned, float gain, uint32_t region, uint32_t image_stride,
-                                                         uint32_t* __restrict__ ctl, StatusNote note,
-                                                         uint32_t* __restrict__ verdicts, TableArg<TABLE> tab)
+template <int LOGM, int NT, typename Where>
+__device__ __forceinline__ void decompress_workgroup(const PeerList& streams, uint32_t npeers, int plain, const Where& where,
+                                                     const Tables& tb, const PackArgs& a, const HeaderInfo& hdr,
+                                                     float* __restrict__ out, float gain, uint32_t region,
+                                                     uint32_t image_stride, size_t per_peer, uint32_t* __restrict__ verdicts,
+                                                     uint8_t* lds, int tid)
 {
     using G = Geo<LOGM, NT>;
     constexpr int RL = stage_radix_log(LOGM);
     using B = Butterflies<LOGM, G::LOGE, NT, RL>;
-    extern __shared__ __attribute__((aligned(16))) float2 smem[];
-    __shared__ uint2 words[G::TABLE_WORDS];
-    __shared__ float2 nyquist[G::T];
-    __shared__ GroupScratch gs[G::GROUPS];
-    const int tid = threadIdx.x, lane = tid & 63, group = tid / G::NL, tg = tid & (G::NL - 1), wig = tg >> 6;
-    float2* tw = reinterpret_cast<float2*>(reinterpret_cast<uint8_t*>(smem) + (size_t)G::GROUPS * region);
-    uint8_t* images = reinterpret_cast<uint8_t*>(smem) + (size_t)group * region;
+    const int lane = tid & 63, group = tid / G::NL, tg = tid & (G::NL - 1), wig = tg >> 6;
+    GroupScratch* gs = reinterpret_cast<GroupScratch*>(lds);
+    uint2* words = reinterpret_cast<uint2*>(lds + G::SCRATCH);
+    float2* nyquist = reinterpret_cast<float2*>(words + G::TABLE_WORDS);
+    uint8_t* regions = lds + G::RECEIVER_FRONT;
+    uint8_t* images = regions + (size_t)group * region;
+    float2* tw = reinterpret_cast<float2*>(regions + (size_t)G::GROUPS * region);
     // the workgroup's point g lies at d[flat(g)]; a group's points are a multiple of 256, so its base moves freely
     float2* d = reinterpret_cast<float2*>(images) - group * (G::E / G::GROUPS);
-    const size_t c0 = (size_t)blockIdx.x * G::T;
     const int bits = a.bits, shift = 23 - a.m;
     const uint32_t code_base = 16u + 4u * a.W, last_rank = a.k ? a.k - 1u : 0u;
-    if (blockIdx.x == 0 && verdicts) write_control(ctl, note, tid);
     load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
 
     // value of the kept bin of this rank, codes in the record image; MODE: 8, 32, or 0 for the other widths
@@ -769,9 +882,8 @@ __global__ __launch_bounds__(NT) void k_chunk_decompress(PeerList streams, uint3
         // the group's records, one behind the other
         for (int i = 0; i < G::CPW; ++i) {
             const int b = group * G::CPW + i;
-            const size_t c = c0 + (size_t)b;
-            if (c >= C) break;
-            const uint4* src = reinterpret_cast<const uint4*>(stream + 64 + record_of<TABLE>(tab, c, a.S));
+            if (!where.exists(b)) break;
+            const uint4* src = reinterpret_cast<const uint4*>(stream + 64 + where.record(b));
             uint4* dst = reinterpret_cast<uint4*>(images + (uint32_t)i * image_stride);
             for (uint32_t j = (uint32_t)tg; j < a.S / 16u; j += G::NL) dst[j] = src[j];
         }
@@ -781,7 +893,7 @@ __global__ __launch_bounds__(NT) void k_chunk_decompress(PeerList streams, uint3
             constexpr int WORDS = G::CPW * G::WC;  // of this group
             const bool has = tg < WORDS;
             const int i = has ? tg / G::WC : 0, wi = has ? tg % G::WC : 0, b = group * G::CPW + i;
-            const bool live = c0 + (size_t)b < C;
+            const bool live = where.exists(b);
             const uint32_t* rec = reinterpret_cast<const uint32_t*>(images + (uint32_t)i * image_stride);
             uint32_t word = has && live ? rec[4 + wi] : 0u;
             uint32_t tail_bit;
@@ -810,20 +922,15 @@ __global__ __launch_bounds__(NT) void k_chunk_decompress(PeerList streams, uint3
                 if (wi == G::WC - 1) {  // this lane knows the chunk's total: the last bin and the verdict are its
                     const uint32_t total = incl;
                     float2 v = make_float2(0.f, 0.f);
-                    uint32_t verdict = 0;
                     if (live) {
                         const uint8_t* codes = reinterpret_cast<const uint8_t*>(rec) + code_base;
                         const bool set = tail_bit && a.k > 0;
                         v = bits == 32 ? value(std::integral_constant<int, 32>(), codes, rec[0], total, set)
                                        : value(std::integral_constant<int, 0>(), codes, rec[0], total, set);
                         bool bad = total + tail_bit != a.k || rec[2] != a.k || rec[3] != a.word3;
-                        const size_t c = c0 + (size_t)b;
+                        const size_t c = where.verdict(b);
                         if (c == 0 && hdr.write) bad = bad || header_bad(hdr, reinterpret_cast<const uint32_t*>(stream));
-                        verdict = bad ? 6u : 0u;
-                        if (verdicts)
-                            verdicts[(size_t)peer * C + c] = verdict;
-                        else if (verdict)
-                            atomicMax(ctl, verdict);
+                        verdicts[(size_t)peer * per_peer + c] = bad ? 6u : 0u;
                     }
                     xn = plain ? v : make_float2(xn.x + v.x, xn.y + v.y);
                 }
@@ -890,18 +997,70 @@ __global__ __launch_bounds__(NT) void k_chunk_decompress(PeerList streams, uint3
     }
     group_sync<G::WAVES>();
     const float scale = gain * (1.0f / (float)(2 * G::M));
-    const bool whole = !TABLE && aligned && (c0 + G::T) * (size_t)(2 * G::M) <= n;
-    if (whole) {
-        float2* dst = reinterpret_cast<float2*>(out) + c0 * (size_t)G::M;
+    if (where.whole(G::T)) {
+        float2* dst = reinterpret_cast<float2*>(out + where.first_sample);
         fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
             dst[(b << LOGM) + i + o] = make_float2(v.x * scale, v.y * scale);
         });
     } else {
         fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
-            const Span sp = chunk_span<TABLE>(tab, c0 + (size_t)b, C, 2 * G::M, n, aligned);
+            const Span sp = where.span(b);
             store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, sp.pairs, make_float2(v.x * scale, v.y * scale));
         });
     }
+}
+
+template <int LOGM, int NT>
+__global__ __launch_bounds__(NT) void k_chunk_decompress(PeerList streams, uint32_t npeers, int plain, size_t C, Tables tb,
+                                                         PackArgs a, HeaderInfo hdr, float* __restrict__ out, size_t n,
+                                                         int aligned, float gain, uint32_t region, uint32_t image_stride,
+                                                         uint32_t* __restrict__ ctl, StatusNote note,
+                                                         uint32_t* __restrict__ verdicts)
+{
+    using G = Geo<LOGM, NT>;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0) write_control(ctl, note, true, tid);
+    const UniformChunks where(n, C, G::T, 2u * G::M, a.S, aligned);
+    decompress_workgroup<LOGM, NT>(streams, npeers, plain, where, tb, a, hdr, out, gain, region, image_stride, C, verdicts, lds,
+                                   tid);
+}
+
+// LDS bytes of a receiver group in a per-tensor launch: one record image
+__host__ __device__ constexpr uint32_t tensor_region(uint32_t stride, uint32_t data)
+{
+    return stride + 16u > data ? stride + 16u : data;
+}
+template <int LOGM>
+__device__ __forceinline__ void decompress_tensors(const PeerList& streams, const TensorTable& t, const TensorPiece& piece,
+                                                   int aligned, const Tables& tb, const PackArgs& a, const HeaderInfo& hdr,
+                                                   float* __restrict__ out, uint32_t* __restrict__ verdicts, uint8_t* lds, int tid)
+{
+    constexpr int NT = tensor_threads<LOGM>();
+    using G = Geo<LOGM, NT>;
+    if (tid >= NT) return;
+    decompress_workgroup<LOGM, NT>(streams, 1u, 1, listed<G>(t, piece, aligned, tid), tb, a, hdr, out, 1.0f,
+                                   tensor_region(a.S, G::DATA), a.S + 16u, 0, verdicts, lds, tid);
+}
+
+template <int TOP>
+__global__ __launch_bounds__(tensor_threads<TOP>()) void k_tensors_decompress(PeerList streams, Tables tb, QuantizerArgs q,
+                                                                              HeaderInfo hdr, float* __restrict__ out, int aligned,
+                                                                              uint32_t* __restrict__ ctl, StatusNote note,
+                                                                              int clear, uint32_t* __restrict__ verdicts,
+                                                                              TensorTable t)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0 && note.count) write_control(ctl, note, clear != 0, tid);
+    const TensorPiece piece = t.piece[blockIdx.x];
+    const PackArgs a = pack_args_of(q, t, piece.logm);
+#define X(p) \
+    else if (p <= TOP && piece.logm == p) decompress_tensors<(p <= TOP ? p : 4)>(streams, t, piece, aligned, tb, a, hdr, out, verdicts, lds, tid);
+    if (false) {
+    }
+    FFTSP_CHUNK_SIZES(X)
+#undef X
 }
 
 // ------------------------------------------------- stage-level transforms ----
@@ -916,7 +1075,7 @@ __global__ __launch_bounds__(NT) void k_chunk_rfft(const float* __restrict__ in,
     const int tid = threadIdx.x;
     const size_t c0 = (size_t)blockIdx.x * G::T;
     load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
-    forward_tile<G, LOGM, false>(in, n, c0, C, aligned, TableArg<false>(), d, tw, tid);
+    forward_tile<G, LOGM>(in, UniformChunks(n, C, G::T, 2u * G::M, 0u, aligned), d, tw, tid);
     __syncthreads();
     for (int w = tid; w < G::E; w += NT) {
         const int k = w & (G::M - 1), b = w >> LOGM;
@@ -961,7 +1120,7 @@ __global__ __launch_bounds__(NT) void k_chunk_irfft(const float2* __restrict__ s
     __syncthreads();
     const float scale = 1.0f / (float)(2 * G::M);
     fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
-        const Span sp = chunk_span<false>(TableArg<false>(), c0 + (size_t)b, C, 2 * G::M, n, aligned);
+        const Span sp = UniformChunks(n, C, G::T, 2u * G::M, 0u, aligned).span(b);
         store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, sp.pairs, make_float2(v.x * scale, v.y * scale));
     });
 }
@@ -993,38 +1152,50 @@ HeaderInfo header_info(const CodecArgs& a, int write)
 }
 int alignment(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; }
 
-template <int LOGM, bool TABLE>
+template <int LOGM, int NT>
+constexpr size_t sender_lds()
+{
+    using G = Geo<LOGM, NT>;
+    return G::SCRATCH + (size_t)G::GROUPS * (G::REGION + 4 * G::IMAGE) + (size_t)G::TW * sizeof(float2);
+}
+template <int LOGM, int NT>
+constexpr size_t receiver_lds(size_t region)
+{
+    using G = Geo<LOGM, NT>;
+    return G::RECEIVER_FRONT + G::GROUPS * region + (size_t)G::TW * sizeof(float2);
+}
+
+template <int LOGM>
 hipError_t compress_as(const float* in, size_t n, const CodecArgs& a, uint8_t* stream, uint8_t* records, uint32_t* ctl,
                        Tables t, hipStream_t s)
 {
     constexpr int NT = uniform_threads<LOGM>();
     using G = Geo<LOGM, NT>;
-    const size_t lds = (size_t)G::GROUPS * (G::REGION + 4 * G::IMAGE) + (size_t)G::TW * sizeof(float2);
-    auto kern = k_chunk_compress<LOGM, NT, TABLE>;
+    constexpr size_t lds = sender_lds<LOGM, NT>();
+    auto kern = k_chunk_compress<LOGM, NT>;
     const hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     FFTSP_LAUNCH("chunk_compress", kern, dim3((unsigned)((a.C + G::T - 1) / G::T)), dim3(NT), lds, s, in, n, a.C,
-                 alignment(in), t, pack_args(a), stream, records, header_info(a, a.write_header), ctl,
-                 table_arg<TABLE>(a.tab));
+                 alignment(in), t, pack_args(a), stream, records, header_info(a, 1), ctl);
     return hipGetLastError();
 }
 
-template <int LOGM, bool TABLE>
+template <int LOGM>
 hipError_t decompress_as(const PeerList& streams, int npeers, int plain, const CodecArgs& a, float* out, size_t n, float gain,
                          uint32_t* ctl, const StatusNote& note, uint32_t* verdicts, Tables t, hipStream_t s)
 {
     constexpr int NT = uniform_threads<LOGM>();
     using G = Geo<LOGM, NT>;
     const uint32_t stride = (uint32_t)a.S + 16u;  // slack: a code is fetched as two words
-    const size_t need = (size_t)G::CPW * stride, data = (size_t)(G::E / G::GROUPS) * sizeof(float2);
+    const size_t need = (size_t)G::CPW * stride, data = G::DATA;
     const size_t region = need > data ? need : data;  // both are multiples of 16
-    const size_t lds = G::GROUPS * region + (size_t)G::TW * sizeof(float2);
-    auto kern = k_chunk_decompress<LOGM, NT, TABLE>;
+    const size_t lds = receiver_lds<LOGM, NT>(region);
+    auto kern = k_chunk_decompress<LOGM, NT>;
     const hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     FFTSP_LAUNCH("chunk_decompress", kern, dim3((unsigned)((a.C + G::T - 1) / G::T)), dim3(NT), lds, s, streams,
-                 (uint32_t)npeers, plain, a.C, t, pack_args(a), header_info(a, a.write_header), out, n, alignment(out), gain,
-                 (uint32_t)region, stride, ctl, note, verdicts, table_arg<TABLE>(a.tab));
+                 (uint32_t)npeers, plain, a.C, t, pack_args(a), header_info(a, 1), out, n, alignment(out), gain,
+                 (uint32_t)region, stride, ctl, note, verdicts);
     return hipGetLastError();
 }
 
@@ -1057,17 +1228,13 @@ hipError_t irfft_as(const float2* spec, uint32_t sstride, size_t n, size_t C, fl
 
 }  // namespace
 
-#define FFTSP_CHUNK_SIZES(X) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14)
-
 hipError_t launch_chunk_compress(const float* in, size_t n, int logL, const CodecArgs& a, uint8_t* stream, uint8_t* records,
                                  uint32_t* ctl, Tables t, hipStream_t s)
 {
-    if (a.C > 0x7fffffffu || (a.tab && a.C > (size_t)kMaxTableChunks)) return hipErrorInvalidValue;
+    if (a.C > 0x7fffffffu) return hipErrorInvalidValue;
     switch (logL - 1) {
 #define X(p) \
-    case p:  \
-        return a.tab ? compress_as<p, true>(in, n, a, stream, records, ctl, t, s) \
-                     : compress_as<p, false>(in, n, a, stream, records, ctl, t, s);
+    case p: return compress_as<p>(in, n, a, stream, records, ctl, t, s);
         FFTSP_CHUNK_SIZES(X)
 #undef X
         default: return hipErrorInvalidValue;
@@ -1078,16 +1245,82 @@ hipError_t launch_chunk_decompress(const PeerList& streams, int npeers, int plai
                                    size_t n, float gain, uint32_t* ctl, const StatusNote& note, uint32_t* verdicts, Tables t,
                                    hipStream_t s)
 {
-    if (a.C > 0x7fffffffu || (a.tab && a.C > (size_t)kMaxTableChunks)) return hipErrorInvalidValue;
+    if (a.C > 0x7fffffffu) return hipErrorInvalidValue;
     switch (logL - 1) {
 #define X(p) \
-    case p:  \
-        return a.tab ? decompress_as<p, true>(streams, npeers, plain, a, out, n, gain, ctl, note, verdicts, t, s) \
-                     : decompress_as<p, false>(streams, npeers, plain, a, out, n, gain, ctl, note, verdicts, t, s);
+    case p: return decompress_as<p>(streams, npeers, plain, a, out, n, gain, ctl, note, verdicts, t, s);
         FFTSP_CHUNK_SIZES(X)
 #undef X
         default: return hipErrorInvalidValue;
     }
+}
+
+int tensors_per_workgroup(int logL)
+{
+    switch (logL - 1) {
+#define X(p) \
+    case p: return Geo<p, tensor_threads<p>()>::GROUPS;
+        FFTSP_CHUNK_SIZES(X)
+#undef X
+        default: return 1;
+    }
+}
+
+// LDS a launch of these pieces needs: that of its most demanding one
+static size_t tensors_lds(const TensorTable& t, uint32_t pieces, bool sender)
+{
+    size_t most = 0;
+    for (uint32_t i = 0; i < pieces; ++i) {
+        size_t need = 0;
+        switch (t.piece[i].logm) {
+#define X(p)                                                                                                                 \
+    case p:                                                                                                                  \
+        need = sender ? sender_lds<p, tensor_threads<p>()>()                                                                 \
+                      : receiver_lds<p, tensor_threads<p>()>(tensor_region(t.stride[p - 4], Geo<p, tensor_threads<p>()>::DATA)); \
+        break;
+            FFTSP_CHUNK_SIZES(X)
+#undef X
+            default: break;
+        }
+        most = need > most ? need : most;
+    }
+    return most;
+}
+
+hipError_t launch_tensors_compress(const float* in, const TensorTable& t, uint32_t pieces, int top_logL, const QuantizerArgs& q,
+                                   const CodecArgs& hdr, uint8_t* stream, uint8_t* records, uint32_t* ctl, Tables tb,
+                                   hipStream_t s)
+{
+    const size_t lds = tensors_lds(t, pieces, true);
+    const bool low = top_logL <= 12;
+    const hipError_t e = low ? allow_lds(k_tensors_compress<11>, lds) : allow_lds(k_tensors_compress<14>, lds);
+    if (e != hipSuccess) return e;
+    if (low)
+        FFTSP_LAUNCH("tensors_compress", k_tensors_compress<11>, dim3(pieces), dim3(tensor_threads<11>()), lds, s, in,
+                     alignment(in), tb, q, stream, records, header_info(hdr, hdr.write_header), ctl, t);
+    else
+        FFTSP_LAUNCH("tensors_compress", k_tensors_compress<14>, dim3(pieces), dim3(tensor_threads<14>()), lds, s, in,
+                     alignment(in), tb, q, stream, records, header_info(hdr, hdr.write_header), ctl, t);
+    return hipGetLastError();
+}
+
+hipError_t launch_tensors_decompress(const uint8_t* stream, const TensorTable& t, uint32_t pieces, int top_logL,
+                                     const QuantizerArgs& q, const CodecArgs& hdr, float* out, uint32_t* ctl,
+                                     const StatusNote& note, int clear, uint32_t* verdicts, Tables tb, hipStream_t s)
+{
+    const size_t lds = tensors_lds(t, pieces, false);
+    const bool low = top_logL <= 12;
+    const hipError_t e = low ? allow_lds(k_tensors_decompress<11>, lds) : allow_lds(k_tensors_decompress<14>, lds);
+    if (e != hipSuccess) return e;
+    PeerList one{};
+    one.p[0] = stream;
+    if (low)
+        FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<11>, dim3(pieces), dim3(tensor_threads<11>()), lds, s, one, tb, q,
+                     header_info(hdr, hdr.write_header), out, alignment(out), ctl, note, clear, verdicts, t);
+    else
+        FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<14>, dim3(pieces), dim3(tensor_threads<14>()), lds, s, one, tb, q,
+                     header_info(hdr, hdr.write_header), out, alignment(out), ctl, note, clear, verdicts, t);
+    return hipGetLastError();
 }
 
 hipError_t launch_chunk_rfft(const float* in, size_t n, int logL, size_t C, float* spec, uint32_t sstride, Tables t,

@@ -8,16 +8,25 @@ namespace {
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-// Fused multiply-adds are written out wherever two products meet: left to the compiler, which product is rounded first
-// depends on the kernel around it, and kernels that must agree bit for bit would not.
+// Where two products meet, one of them ends up inside a fused multiply-add.  Left to the compiler, which one depends on
+// the kernel around it, and kernels that must agree bit for bit would not: chunk.hip, where several kernels compute the
+// same transform, asks for the fused operations to be written out (FFTSP_FMA_WRITTEN_OUT).  The two-pass kernels are the
+// only ones of their lengths and keep the compiler's choice, and with it the results they have always given.
+#ifdef FFTSP_FMA_WRITTEN_OUT
+__device__ __forceinline__ float prod_sum(float a, float b, float c, float d) { return __fmaf_rn(a, b, c * d); }
+__device__ __forceinline__ float prod_diff(float a, float b, float c, float d) { return __fmaf_rn(a, b, -(c * d)); }
+#else
+__device__ __forceinline__ float prod_sum(float a, float b, float c, float d) { return a * b + c * d; }
+__device__ __forceinline__ float prod_diff(float a, float b, float c, float d) { return a * b - c * d; }
+#endif
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 {
-    return make_float2(__fmaf_rn(a.x, b.x, -(a.y * b.y)), __fmaf_rn(a.x, b.y, a.y * b.x));
+    return make_float2(prod_diff(a.x, b.x, a.y, b.y), prod_sum(a.x, b.y, a.y, b.x));
 }
 // a * conj(b)
 __device__ __forceinline__ float2 cmulc(float2 a, float2 b)
 {
-    return make_float2(__fmaf_rn(a.x, b.x, a.y * b.y), __fmaf_rn(a.y, b.x, -(a.x * b.y)));
+    return make_float2(prod_sum(a.x, b.x, a.y, b.y), prod_diff(a.y, b.x, a.x, b.y));
 }
 
 // exp(-2 pi i E / 2^22), E < 2^22
@@ -71,6 +80,7 @@ __device__ __forceinline__ void bf8(float2* v)
     float2 o[4] = {v[1], v[3], v[5], v[7]};
     bf4<INV>(e);
     bf4<INV>(o);
+#ifdef FFTSP_FMA_WRITTEN_OUT
     // v[k], v[k+4] = e[k] +- W8^k o[k]; the odd powers of W8 are (1 -+ i) / sqrt(2) times a real factor
     v[0] = cadd(e[0], o[0]);
     v[4] = csub(e[0], o[0]);
@@ -83,6 +93,23 @@ __device__ __forceinline__ void bf8(float2* v)
     v[5] = make_float2(__fmaf_rn(-c, o1.x, e[1].x), __fmaf_rn(-c, o1.y, e[1].y));
     v[3] = make_float2(__fmaf_rn(c, o3.x, e[3].x), __fmaf_rn(c, o3.y, e[3].y));
     v[7] = make_float2(__fmaf_rn(-c, o3.x, e[3].x), __fmaf_rn(-c, o3.y, e[3].y));
+#else
+    // o[k] *= W8^k
+    float2 o1 = o[1], o3 = o[3];
+    if (INV) {
+        o[1] = make_float2(c * (o1.x - o1.y), c * (o1.x + o1.y));
+        o[3] = make_float2(-c * (o3.x + o3.y), c * (o3.x - o3.y));
+    } else {
+        o[1] = make_float2(c * (o1.x + o1.y), c * (o1.y - o1.x));
+        o[3] = make_float2(c * (o3.y - o3.x), -c * (o3.x + o3.y));
+    }
+    o[2] = rot90<INV>(o[2]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = cadd(e[k], o[k]);
+        v[k + 4] = csub(e[k], o[k]);
+    }
+#endif
 }
 
 // 16 points: four radix-4 butterflies over n1 (elements n0, n0+4, n0+8, n0+12), the inner twiddles W16^(n0 k0),
@@ -101,8 +128,8 @@ __device__ __forceinline__ void bf16(float2* v)
     }
     // W16^m = (cos(m pi/8), -sin(m pi/8)), conjugated for the inverse
     auto rot = [](float2 a, float wr, float wi) {  // a * (wr + i wi) forward, a * (wr - i wi) inverse
-        return INV ? make_float2(__fmaf_rn(a.x, wr, a.y * wi), __fmaf_rn(a.y, wr, -(a.x * wi)))
-                   : make_float2(__fmaf_rn(a.x, wr, -(a.y * wi)), __fmaf_rn(a.y, wr, a.x * wi));
+        return INV ? make_float2(prod_sum(a.x, wr, a.y, wi), prod_diff(a.y, wr, a.x, wi))
+                   : make_float2(prod_diff(a.x, wr, a.y, wi), prod_sum(a.y, wr, a.x, wi));
     };
     y[1][1] = rot(y[1][1], c1, -s1);   // W^1
     y[1][2] = rot(y[1][2], h, -h);     // W^2
@@ -274,7 +301,7 @@ __device__ __forceinline__ float2 split_fwd(float2 a, float2 b, float2 w)
 {
     const float er = 0.5f * (a.x + b.x), ei = 0.5f * (a.y - b.y);
     const float dr = 0.5f * (a.x - b.x), di = 0.5f * (a.y + b.y);
-    return make_float2(er + __fmaf_rn(w.x, di, w.y * dr), ei - __fmaf_rn(w.x, dr, -(w.y * di)));
+    return make_float2(er + prod_sum(w.x, di, w.y, dr), ei - prod_diff(w.x, dr, w.y, di));
 }
 
 // 2 Z[k] from a = X[k], b = X[M-k], w = W_L^k  (the factor 1/2 is folded into the final 1/L)
@@ -282,7 +309,7 @@ __device__ __forceinline__ float2 split_inv(float2 a, float2 b, float2 w)
 {
     const float er = a.x + b.x, ei = a.y - b.y;
     const float dr = a.x - b.x, di = a.y + b.y;
-    const float orr = __fmaf_rn(w.x, dr, w.y * di), oi = __fmaf_rn(w.x, di, -(w.y * dr));  // conj(w) * d
+    const float orr = prod_sum(w.x, dr, w.y, di), oi = prod_diff(w.x, di, w.y, dr);  // conj(w) * d
     return make_float2(er - oi, ei + orr);
 }
 
