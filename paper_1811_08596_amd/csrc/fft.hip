@@ -26,6 +26,24 @@
 namespace fftsp {
 namespace {
 
+// Complex points of a tile (a power of two; 16 per lane).  A tile of 2^13 is 64 KiB of LDS, two workgroups of 512 lanes per
+// compute unit.  A tile of 2^14 has a workgroup of 1024 lanes and the compute unit to itself; it is taken where the smaller
+// one would touch memory in pieces of less than a 128-byte line:
+//   second pass, rows of 2^10 (64 -> 128 bytes): 138 M samples in chunks of 2^22, forward 313 -> 230 us, inverse 348 -> 268
+//     (with rows of 2^9, already a line wide: 101 -> 106 and 109 -> 127);
+//   inverse first pass, columns of 2^10 (stores of 64 -> 128 bytes): 62 M samples in chunks of 2^20, 116 -> 101 us, and
+//     the next call's forward first pass, which runs while those lines are written back, 135 -> 119; columns of 2^11
+//     (32 -> 64 bytes): 468 -> 300 us.
+// The forward first pass, which only reads in narrow pieces, was slower that way (columns of 2^10: 119 -> 124 us; of 2^11:
+// 340 us against 327 with four 2^13-point tiles of a line walked in step).
+// And only where there is such a tile for every compute unit: one to four chunks of 2^20 are 3 % faster in more, smaller tiles.
+constexpr int kTileFA = 13;
+constexpr int kWideMin = 10;  // columns (inverse first pass) or rows (second passes) of at least 2^kWideMin
+constexpr size_t kWideTiles = 256;
+inline bool wide_tiles(size_t C, int logM) { return (C << (logM - 14)) >= kWideTiles; }
+constexpr int tile_lanes(int loge) { return 1 << (loge - 4); }
+constexpr int kLanePairs = 8;  // pairs of adjacent points a lane holds
+
 // The next tile's loads are issued in at most this many portions: one before the LDS stages, one after each of the
 // first stages.  A wave that issues a whole tile's loads at once stands in the issue until the memory pipeline has
 // taken them; in portions the stages in between proceed meanwhile.
@@ -58,19 +76,19 @@ constexpr int spread_parts()
 // alone, so a workgroup looks them up once for all its tiles.
 template <int LOGN1>
 struct PassARatios {
-    static constexpr int HP = (1 << LOGN1) / 2;
-    static constexpr int KN = HP >= kNT ? HP / kNT : 1;
+    static constexpr int NT = tile_lanes(kTileFA), HP = (1 << LOGN1) / 2;
+    static constexpr int KN = HP >= NT ? HP / NT : 1;
     float2 a[KN], b[KN];
 };
 template <int LOGN1>
 __device__ __forceinline__ PassARatios<LOGN1> pass_a_ratios(const Tables& tb, int logM, int tid)
 {
-    constexpr int N1 = 1 << LOGN1, HP = N1 / 2, KN = PassARatios<LOGN1>::KN;
-    constexpr int DC = HP >= kNT ? 1 : kNT / HP;
+    constexpr int N1 = 1 << LOGN1, HP = N1 / 2, KN = PassARatios<LOGN1>::KN, NT = PassARatios<LOGN1>::NT;
+    constexpr int DC = HP >= NT ? 1 : NT / HP;
     PassARatios<LOGN1> r;
 #pragma unroll
     for (int kk = 0; kk < KN; ++kk) {
-        const uint32_t kp = (uint32_t)(tid + kk * kNT) & (HP - 1);
+        const uint32_t kp = (uint32_t)(tid + kk * NT) & (HP - 1);
         r.a[kk] = twiddle(tb, ((uint32_t)DC * kp) << (22 - logM));
         r.b[kk] = twiddle(tb, ((uint32_t)DC * mirror_row(kp, N1)) << (22 - logM));
     }
@@ -85,7 +103,7 @@ __device__ __forceinline__ void fwd_a_tile(uint32_t t, uint32_t tiles, int logM,
                                            const Tables& tb, float2* d, const float2* tw, int tid, float in_scale,
                                            const PassARatios<LOGN1>& ratio, Prefetch prefetch)
 {
-    constexpr int NT = kNT, LOGE = kLogE, PER2 = kPer / 2;
+    constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE), PER2 = kLanePairs;
     constexpr int N1 = 1 << LOGN1, LOGT = LOGE - LOGN1;
     constexpr int HP = N1 / 2, LOGHP = LOGN1 - 1;  // row pairs per column
     constexpr int KN = HP >= NT ? HP / NT : 1;   // distinct row pairs per lane in the store loop
@@ -142,7 +160,7 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t n
                                           uint32_t t, uint32_t tend, uint32_t tstep, float2* d, const float2* tw, int tid0,
                                           const TableArg<TABLE>& tab, float in_scale)
 {
-    constexpr int NT = kNT, LOGE = kLogE, PER2 = kPer / 2;
+    constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE), PER2 = kLanePairs;
     constexpr int N1 = 1 << LOGN1, LOGT = LOGE - LOGN1, TA = 1 << LOGT;
     static_assert(LOGT >= 2 && (NT % (TA / 2)) == 0, "tile shape");
     const uint32_t M = 1u << logM, N2 = M >> LOGN1, tiles = N2 >> LOGT;
@@ -198,13 +216,13 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t n
 
 // `aligned`: bit 0 = input is 8-byte aligned, bit 1 = 16-byte aligned.
 template <int LOGN1, bool TABLE, bool HALF>
-__global__ __launch_bounds__(kNT) void k_fwd_a(const float* __restrict__ in, size_t n, int logM,
+__global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __restrict__ in, size_t n, int logM,
                                                typename Cx<HALF>::One* __restrict__ mid, Tables tb, int aligned,
                                                uint32_t total, uint32_t per_wg, int glog, uint32_t* __restrict__ zero_ptr,
                                                uint32_t zero_words, TableArg<TABLE> tab, float in_scale,
                                                const uint32_t* __restrict__ only_if)
 {
-    constexpr int NT = kNT, ELEMS = 1 << kLogE;
+    constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE), ELEMS = 1 << LOGE;
     if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
     // clears the status words and key histograms the next kernels of the sender accumulate into
     for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < zero_words; i += gridDim.x * NT) zero_ptr[i] = 0u;
@@ -215,7 +233,7 @@ __global__ __launch_bounds__(kNT) void k_fwd_a(const float* __restrict__ in, siz
     uint32_t t, tend;
     if (!grouped_run(total, per_wg, glog, t, tend)) return;
     load_stage_twiddles<LOGN1, NT>(tw, tb, tid0);
-    const uint32_t tiles = (1u << logM) >> kLogE;  // tiles per chunk
+    const uint32_t tiles = (1u << logM) >> LOGE;  // tiles per chunk
     bool fast = (aligned & 2) != 0;
     if constexpr (TABLE) {
         // every tensor this run touches fills its chunk and starts on a 16-byte boundary
@@ -242,8 +260,8 @@ __global__ __launch_bounds__(kNT) void k_fwd_a(const float* __restrict__ in, siz
 // selects) so that its LDS reads can be issued ahead in batches instead of one wait per read.
 // HALF (CODEC only): the intermediate is read and the spectrum written as binary16 pairs; the histogram counts
 // the keys of the values as stored, which are the ones the selection will see.
-template <int LOGN2, bool CODEC, bool HALF>
-__global__ __launch_bounds__(kNT) void k_fwd_b(const typename Cx<HALF>::One* __restrict__ mid, int logM,
+template <int LOGN2, int LOGE, bool CODEC, bool HALF>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b(const typename Cx<HALF>::One* __restrict__ mid, int logM,
                                                typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride, Tables tb,
                                                uint32_t* __restrict__ hist, uint32_t total, uint32_t per_wg,
                                                float mid_scale, const uint32_t* __restrict__ only_if)
@@ -251,7 +269,7 @@ __global__ __launch_bounds__(kNT) void k_fwd_b(const typename Cx<HALF>::One* __r
     static_assert(CODEC || !HALF, "binary16 storage is the codec's own");
     if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
     using Two = typename Cx<HALF>::Two;
-    constexpr int NT = kNT, LOGE = kLogE, PER2 = kPer / 2;
+    constexpr int NT = tile_lanes(LOGE), PER2 = kLanePairs;
     constexpr int N2 = 1 << LOGN2, LOGT = LOGE - LOGN2, ELEMS = 1 << LOGE;
     constexpr int LOGP = LOGT - 1, P = 1 << LOGP;  // slot pairs per tile
     static_assert(LOGT >= 1 && NT % P == 0, "a lane keeps one slot pair");
@@ -272,8 +290,9 @@ __global__ __launch_bounds__(kNT) void k_fwd_b(const typename Cx<HALF>::One* __r
         for (int i = tid0; i < kHistLdsWords; i += NT) h16[i] = 0u;
     constexpr int DK = NT >> LOGP;  // k2 step between a lane's consecutive pairs
     static_assert(2 * kSplitStep * (PER2 - 1) < 16, "split twiddle steps stay inside the 32nd-root table");
-    // the LDS histogram has 16-bit counters and a tile adds at most 2^13 + 1 keys: flush after at most 7 tiles
-    constexpr uint32_t kFlushEvery = 7;
+    // the LDS histogram has 16-bit counters and a tile adds at most 2^LOGE + 1 keys
+    constexpr uint32_t kFlushEvery = 65535u / ((1u << LOGE) + 1u);
+    static_assert(LOGE != 13 || kFlushEvery == 7, "flush after at most 7 tiles");
     constexpr int BATCH = 4;  // pairs whose LDS reads are issued together
     static_assert(PER2 % BATCH == 0, "batches divide the store loop");
 
@@ -393,8 +412,8 @@ __global__ __launch_bounds__(kNT) void k_fwd_b(const typename Cx<HALF>::One* __r
 // Inverse pass B: undo the split, inverse N2-point FFTs over k2, times conj W_M^(n2 k1).
 // PAIR: the spectrum is read in the paired order (the codec's own buffer), otherwise in natural bin order.
 // HALF (PAIR only): spectrum and intermediate are binary16 pairs.
-template <int LOGN2, bool PAIR, bool HALF>
-__global__ __launch_bounds__(kNT) void k_inv_b(const typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride, int logM,
+template <int LOGN2, int LOGE, bool PAIR, bool HALF>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b(const typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride, int logM,
                                                typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total,
                                                uint32_t per_wg, float mid_scale, const uint32_t* __restrict__ only_if)
 {
@@ -402,7 +421,7 @@ __global__ __launch_bounds__(kNT) void k_inv_b(const typename Cx<HALF>::One* __r
     if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
     using One = typename Cx<HALF>::One;
     using Two = typename Cx<HALF>::Two;
-    constexpr int NT = kNT, LOGE = kLogE, PER2 = kPer / 2;
+    constexpr int NT = tile_lanes(LOGE), PER2 = kLanePairs;
     constexpr int N2 = 1 << LOGN2, LOGT = LOGE - LOGN2, ELEMS = 1 << LOGE;
     constexpr int LOGP = LOGT - 1, P = 1 << LOGP;
     static_assert(LOGT >= 1 && NT % P == 0, "a lane keeps one slot pair");
@@ -526,15 +545,15 @@ __global__ __launch_bounds__(kNT) void k_inv_b(const typename Cx<HALF>::One* __r
 
 // Inverse pass A: inverse N1-point FFTs over k1 for a tile of columns n2; writes the real samples.
 // `aligned`: bit 0 = output is 8-byte aligned, bit 1 = 16-byte aligned.
-template <int LOGN1, bool TABLE, bool HALF>
-__global__ __launch_bounds__(kNT) void k_inv_a(const typename Cx<HALF>::One* __restrict__ mid, int logM,
+template <int LOGN1, int LOGE, bool TABLE, bool HALF>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HALF>::One* __restrict__ mid, int logM,
                                                float* __restrict__ out, size_t n, Tables tb, int aligned, uint32_t total,
                                                uint32_t per_wg, int glog, float gain, TableArg<TABLE> tab,
                                                const uint32_t* __restrict__ only_if)
 {
     using Two = typename Cx<HALF>::Two;
     if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
-    constexpr int NT = kNT, LOGE = kLogE, PER2 = kPer / 2;
+    constexpr int NT = tile_lanes(LOGE), PER2 = kLanePairs;
     constexpr int N1 = 1 << LOGN1, LOGT = LOGE - LOGN1, TA = 1 << LOGT, ELEMS = 1 << LOGE;
     constexpr int HP = N1 / 2, LOGHP = LOGN1 - 1;
     static_assert(LOGT >= 2 && (NT % (TA / 2)) == 0, "tile shape");
@@ -638,7 +657,10 @@ Grid persistent_grid(size_t total, uint32_t kMaxWgs = 512)
 
 // pass A: 2^glog workgroups (b, b+8, ...) share a run of aligned tile groups; per_wg counts tile groups and wgs
 // is a multiple of 8 * 2^glog
-constexpr int kGroupLog = 1;
+// a pass A tile is 2^(loge - LOGN1) columns of 8 bytes; the tiles of a 128-byte line (two at least) are walked in step
+constexpr int group_log(int loge, int logn1) { return loge - logn1 >= 3 ? 1 : 2; }
+// most workgroups of a launch: the figures below are for two resident workgroups per compute unit
+constexpr uint32_t most_wgs(int loge, uint32_t with_two) { return loge == 13 ? with_two : with_two / 2; }
 constexpr uint32_t kPassAWgs = 2048;  // most workgroups the forward pass A is cut into
 Grid grouped_grid(size_t groups, int glog, uint32_t kMaxWgs = 512)
 {
@@ -657,70 +679,97 @@ hipError_t fwd_a(const float* in, size_t n, int logM, size_t C, float2* mid_f32,
                  uint32_t* zero_ptr, uint32_t zero_words, const ChunkTable* tab, float in_scale, hipStream_t s,
                  const uint32_t* only_if = nullptr)
 {
-    const size_t lds = ((size_t)(1 << kLogE) + (1 << LOGN1)) * sizeof(float2);
+    constexpr int LOGE = kTileFA;
+    const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN1)) * sizeof(float2);
     auto kern = k_fwd_a<LOGN1, TABLE, HALF>;
     auto* mid = reinterpret_cast<typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
-    const size_t total = C * (((size_t)1 << (logM - LOGN1)) >> (kLogE - LOGN1));
-    const int glog = logM - kLogE >= kGroupLog ? kGroupLog : 1;  // a chunk has 2^(logM-kLogE) >= 2 tiles
+    const size_t total = C * (((size_t)1 << (logM - LOGN1)) >> (LOGE - LOGN1));
+    constexpr int glog = group_log(LOGE, LOGN1);  // a chunk has at least that many tiles
     // measured: 143 us against 149 with 512; a stand-by launch (only_if) takes the small grid, which leaves sooner
-    const Grid g = grouped_grid(total >> glog, glog, only_if ? 512 : kPassAWgs);
-    FFTSP_LAUNCH(only_if ? "rfft_pass_a_standby" : "rfft_pass_a", kern, dim3(g.wgs), dim3(kNT), lds, s, in, n, logM, mid,
+    const Grid g = grouped_grid(total >> glog, glog, most_wgs(LOGE, only_if ? 512 : kPassAWgs));
+    FFTSP_LAUNCH(only_if ? "rfft_pass_a_standby" : "rfft_pass_a", kern, dim3(g.wgs), dim3(tile_lanes(LOGE)), lds, s, in, n, logM, mid,
                  t, aligned, (uint32_t)(total >> glog), g.per_wg, glog, zero_ptr, zero_words, table_arg<TABLE>(tab),
                  in_scale, only_if);
     return hipGetLastError();
 }
 
-template <int LOGN2, bool CODEC, bool HALF>
-hipError_t fwd_b(const float2* mid_f32, int logM, size_t C, float2* spec_f32, uint32_t sstride, Tables t, uint32_t* hist,
-                 float mid_scale, hipStream_t s, const uint32_t* only_if = nullptr)
+template <int LOGN2, int LOGE, bool CODEC, bool HALF>
+hipError_t fwd_b_tiled(const float2* mid_f32, int logM, size_t C, float2* spec_f32, uint32_t sstride, Tables t, uint32_t* hist,
+                 float mid_scale, hipStream_t s, const uint32_t* only_if)
 {
-    const size_t lds = ((size_t)(1 << kLogE) + (1 << LOGN2)) * sizeof(float2) + kHistLdsWords * sizeof(uint32_t);
-    auto kern = k_fwd_b<LOGN2, CODEC, HALF>;
+    const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN2)) * sizeof(float2) + kHistLdsWords * sizeof(uint32_t);
+    auto kern = k_fwd_b<LOGN2, LOGE, CODEC, HALF>;
     auto* mid = reinterpret_cast<const typename Cx<HALF>::One*>(mid_f32);
     auto* spec = reinterpret_cast<typename Cx<HALF>::One*>(spec_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
-    const size_t total = C * (((size_t)1 << (logM - LOGN2)) >> (kLogE - LOGN2));
-    const Grid g = persistent_grid(total);
-    FFTSP_LAUNCH(only_if ? "rfft_pass_b_standby" : "rfft_pass_b", kern, dim3(g.wgs), dim3(kNT), lds, s, mid, logM, spec,
+    const size_t total = C * (((size_t)1 << (logM - LOGN2)) >> (LOGE - LOGN2));
+    const Grid g = persistent_grid(total, most_wgs(LOGE, 512));
+    FFTSP_LAUNCH(only_if ? "rfft_pass_b_standby" : "rfft_pass_b", kern, dim3(g.wgs), dim3(tile_lanes(LOGE)), lds, s, mid, logM, spec,
                  sstride, t, hist, (uint32_t)total, g.per_wg, mid_scale, only_if);
     return hipGetLastError();
 }
 
-template <int LOGN2, bool PAIR, bool HALF>
-hipError_t inv_b(const float2* spec_f32, uint32_t sstride, int logM, size_t C, float2* mid_f32, Tables t, float mid_scale,
-                 hipStream_t s, const uint32_t* only_if = nullptr)
+template <int LOGN2, int LOGE, bool PAIR, bool HALF>
+hipError_t inv_b_tiled(const float2* spec_f32, uint32_t sstride, int logM, size_t C, float2* mid_f32, Tables t, float mid_scale,
+                 hipStream_t s, const uint32_t* only_if)
 {
-    const size_t lds = ((size_t)(1 << kLogE) + (1 << LOGN2)) * sizeof(float2);
-    auto kern = k_inv_b<LOGN2, PAIR, HALF>;
+    const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN2)) * sizeof(float2);
+    auto kern = k_inv_b<LOGN2, LOGE, PAIR, HALF>;
     auto* spec = reinterpret_cast<const typename Cx<HALF>::One*>(spec_f32);
     auto* mid = reinterpret_cast<typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
-    const size_t total = C * (((size_t)1 << (logM - LOGN2)) >> (kLogE - LOGN2));
-    const Grid g = persistent_grid(total, only_if ? 512 : 1536);  // measured: 117 us against 126 with 512
-    FFTSP_LAUNCH(only_if ? "irfft_pass_b_standby" : "irfft_pass_b", kern, dim3(g.wgs), dim3(kNT), lds, s, spec, sstride,
+    const size_t total = C * (((size_t)1 << (logM - LOGN2)) >> (LOGE - LOGN2));
+    const Grid g = persistent_grid(total, most_wgs(LOGE, only_if ? 512 : 1536));  // measured: 117 us against 126 with 512
+    FFTSP_LAUNCH(only_if ? "irfft_pass_b_standby" : "irfft_pass_b", kern, dim3(g.wgs), dim3(tile_lanes(LOGE)), lds, s, spec, sstride,
                  logM, mid, t, (uint32_t)total, g.per_wg, mid_scale, only_if);
     return hipGetLastError();
 }
 
-template <int LOGN1, bool TABLE, bool HALF>
-hipError_t inv_a(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
-                 const ChunkTable* tab, hipStream_t s, const uint32_t* only_if = nullptr)
+template <int LOGN1, int LOGE, bool TABLE, bool HALF>
+hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
+                 const ChunkTable* tab, hipStream_t s, const uint32_t* only_if)
 {
-    const size_t lds = ((size_t)(1 << kLogE) + (1 << LOGN1)) * sizeof(float2);
-    auto kern = k_inv_a<LOGN1, TABLE, HALF>;
+    const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN1)) * sizeof(float2);
+    auto kern = k_inv_a<LOGN1, LOGE, TABLE, HALF>;
     auto* mid = reinterpret_cast<const typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
-    const size_t total = C * (((size_t)1 << (logM - LOGN1)) >> (kLogE - LOGN1));
-    const int glog = logM - kLogE >= kGroupLog ? kGroupLog : 1;
-    const Grid g = grouped_grid(total >> glog, glog);
-    FFTSP_LAUNCH(only_if ? "irfft_pass_a_standby" : "irfft_pass_a", kern, dim3(g.wgs), dim3(kNT), lds, s, mid, logM, out,
+    const size_t total = C * (((size_t)1 << (logM - LOGN1)) >> (LOGE - LOGN1));
+    constexpr int glog = group_log(LOGE, LOGN1);
+    const Grid g = grouped_grid(total >> glog, glog, most_wgs(LOGE, 512));
+    FFTSP_LAUNCH(only_if ? "irfft_pass_a_standby" : "irfft_pass_a", kern, dim3(g.wgs), dim3(tile_lanes(LOGE)), lds, s, mid, logM, out,
                  n, t, aligned, (uint32_t)(total >> glog), g.per_wg, glog, gain, table_arg<TABLE>(tab), only_if);
     return hipGetLastError();
+}
+
+// the tile size by the rule at the top of the file
+template <int LOGN2, bool CODEC, bool HALF>
+hipError_t fwd_b(const float2* mid, int logM, size_t C, float2* spec, uint32_t sstride, Tables t, uint32_t* hist,
+                 float mid_scale, hipStream_t s, const uint32_t* only_if = nullptr)
+{
+    if constexpr (LOGN2 >= kWideMin)
+        if (wide_tiles(C, logM)) return fwd_b_tiled<LOGN2, 14, CODEC, HALF>(mid, logM, C, spec, sstride, t, hist, mid_scale, s, only_if);
+    return fwd_b_tiled<LOGN2, 13, CODEC, HALF>(mid, logM, C, spec, sstride, t, hist, mid_scale, s, only_if);
+}
+template <int LOGN2, bool PAIR, bool HALF>
+hipError_t inv_b(const float2* spec, uint32_t sstride, int logM, size_t C, float2* mid, Tables t, float mid_scale,
+                 hipStream_t s, const uint32_t* only_if = nullptr)
+{
+    if constexpr (LOGN2 >= kWideMin)
+        if (wide_tiles(C, logM)) return inv_b_tiled<LOGN2, 14, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
+    return inv_b_tiled<LOGN2, 13, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
+}
+template <int LOGN1, bool TABLE, bool HALF>
+hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
+                 const ChunkTable* tab, hipStream_t s, const uint32_t* only_if = nullptr)
+{
+    if constexpr (LOGN1 >= kWideMin)
+        if (wide_tiles(C, logM)) return inv_a_tiled<LOGN1, 14, TABLE, HALF>(mid, logM, C, out, n, t, aligned, gain, tab, s, only_if);
+    return inv_a_tiled<LOGN1, 13, TABLE, HALF>(mid, logM, C, out, n, t, aligned, gain, tab, s, only_if);
 }
 
 }  // namespace
