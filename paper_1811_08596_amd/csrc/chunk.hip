@@ -317,43 +317,6 @@ __device__ __forceinline__ float2 nyquist_bin(const float2* d, int base)
 }
 
 // --------------------------------------------------------- select and pack ----
-constexpr uint32_t kListCap = 256;  // keys of the threshold's bucket that are finished from a list
-
-// The `need`-th largest of `count` listed keys that share all bits above `low`: tau grows bit by bit, a ballot counts
-// the keys at or above each trial.  On return need = how many keys equal to tau are still to take, of `equal`.
-// A trial that leaves exactly `need` keys ends the search: those are the ones.
-template <int NR>
-__device__ __forceinline__ void search_list(const uint32_t* list, uint32_t count, int low, int lane, uint32_t& tau,
-                                            uint32_t& need, uint32_t& equal)
-{
-    uint32_t key[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) key[i] = (uint32_t)(lane + 64 * i) < count ? list[lane + 64 * i] : 0u;
-    if (count == need) {
-        equal = need;
-        return;
-    }
-    for (int bit = low - 1; bit >= 0; --bit) {
-        const uint32_t t = tau | (1u << bit);
-        uint32_t cnt = 0;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) cnt += (uint32_t)__popcll(__ballot(key[i] >= t));
-        if (cnt >= need) tau = t;
-        if (cnt == need) {
-            equal = need;
-            return;
-        }
-    }
-    uint32_t above = 0;
-    equal = 0;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) {
-        above += (uint32_t)__popcll(__ballot(key[i] > tau));
-        equal += (uint32_t)__popcll(__ballot((uint32_t)(lane + 64 * i) < count && key[i] == tau));
-    }
-    need -= above;
-}
-
 // Steps 2-4 of the sender for one chunk whose bins (samples) lie in the registers of a group of WAVES waves:
 // z[r]: bin (wave * R + r) * 64 + lane (lane < LR); zn (TAIL): the chunk's last bin, the same value in every lane.
 // lds: the group's own words (histogram, candidate list); image: its record image.  wg_most: a word of the workgroup,

@@ -16,6 +16,8 @@
 // quantizes and bit-packs.
 #include "codec_core.h"
 
+#include <type_traits>
+
 namespace fftsp {
 namespace {
 
@@ -327,24 +329,21 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
 }
 
 // --------------------------------------------------------------- resolve ----
-constexpr int RT = 1024;           // lanes of the per-chunk workgroup
+constexpr int RT = 1024;           // lanes of the per-chunk workgroups of the decoder's prefix kernels
 constexpr int RW = RT / 64;        // 16 waves
 constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1025
 
-// inclusive scan over 1024 lanes; tmp has 16 entries
-__device__ __forceinline__ uint32_t block_scan_incl_1024(uint32_t v, uint32_t* tmp)
+// inclusive scan over the NW waves of a workgroup; tmp has NW entries
+template <int NW>
+__device__ __forceinline__ uint32_t block_scan_incl(uint32_t v, uint32_t* tmp)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = __shfl_up(x, o, 64);
-        if (lane >= o) x += u;
-    }
+    const uint32_t x = wave_scan_incl(v);
     if (lane == 63) tmp[wave] = x;
     __syncthreads();
     uint32_t add = 0;
-    for (int w = 0; w < wave; ++w) add += tmp[w];
+#pragma unroll
+    for (int w = 0; w < NW - 1; ++w) add += w < wave ? tmp[w] : 0u;
     __syncthreads();
     return x + add;
 }
@@ -359,340 +358,274 @@ __device__ __forceinline__ size_t record_offset(const TableArg<TABLE>& tab, size
         return c * S;
 }
 
-// Candidates that did not fit in LDS are walked from memory.
-constexpr int kWalk = 8;  // further rows of 64 candidates of one tile fetched in one round trip
-// All tiles of a chunk, a wave per tile, kWalkTiles tiles per round trip: the first row of candidates of each tile of
-// a batch (usually all a tile has) is fetched before any is used.  begin(t) and end(t) bracket tile t's rows, which
-// go to row(entry, valid) in candidate order; all three are called by the whole wave.
-constexpr int kWalkTiles = 8;
-template <typename B, typename R, typename E>
-__device__ __forceinline__ void walk_tiles(const uint2* __restrict__ cd, const uint32_t* tnc, uint32_t Tn, int wave, int lane,
-                                           B&& begin, R&& row, E&& end)
+// One workgroup per chunk: finish the radix select on the candidates, break ties by bin order, scan the tiles, find the
+// survivors' largest component, write the record header and zero the code words that two tiles will share.
+//
+// Bound by what one compute unit can issue and by memory round trips, so the candidates are looked at twice only.  The first
+// sweep (a wave per tile, kFetch tiles in flight, a lane per candidate: a tile has about 40) counts their second digit.
+// The second one counts per tile those above the two digits' common prefix, takes their range and lists the few that
+// share it (ten or so of a million bins).  The list settles the threshold, and its members are added to their tiles
+// afterwards.  More than kListCap of them (runs of equal keys) take a third digit and a third sweep.
+// KEPT: the first sweep leaves the candidates in LDS, in slots of 64 per tile, for the second one.
+// Counting the second digit in k_collect instead saved a sweep here but cost that kernel more (43 -> 52 us: its atomics
+// meet in memory).
+// Measured, us per call, against three digits and three more sweeps by 16 waves: one chunk of 2^16 16 -> 9, sixty of
+// 2^20 24 -> 18, thirty-three of 2^22 87 -> 44.
+constexpr int kFetch = 8;  // tiles of a wave fetched in one round trip
+template <bool TABLE, int NW, bool KEPT>
+__global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, int bits, int m, uint32_t W, size_t S,
+                                                     uint32_t word3, uint32_t static_vmax, uint32_t codes_per_bin,
+                                                     uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
+                                                     uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
+                                                     uint8_t* __restrict__ records, uint8_t* __restrict__ stream,
+                                                     HeaderInfo hdr, TableArg<TABLE> tab)
 {
-    for (uint32_t t0 = (uint32_t)wave; t0 < Tn; t0 += RW * kWalkTiles) {
-        uint2 first[kWalkTiles];
-#pragma unroll
-        for (int u = 0; u < kWalkTiles; ++u) {
-            const uint32_t t = t0 + (uint32_t)u * RW;
-            const uint32_t nc = t < Tn ? tnc[t] : 0u;
-            // lanes past the end read their tile's first slot (always allocated) and drop it
-            first[u] = cd[(size_t)(t < Tn ? t : 0u) * kTile + ((uint32_t)lane < nc ? (uint32_t)lane : 0u)];
-        }
-#pragma unroll
-        for (int u = 0; u < kWalkTiles; ++u) {
-            const uint32_t t = t0 + (uint32_t)u * RW;
-            if (t < Tn) {
-                const uint32_t nc = tnc[t];
-                begin(t);
-                if (nc) row(first[u], (uint32_t)lane < nc);
-                if (nc > 64u) {  // long runs of equal keys (a chunk of zeros) fill whole tiles
-                    const uint2* tile_cands = cd + (size_t)t * kTile;
-                    for (uint32_t i0 = 64u; i0 < nc; i0 += 64u * kWalk) {
-                        uint2 e[kWalk];
-#pragma unroll
-                        for (int v = 0; v < kWalk; ++v) {
-                            const uint32_t i = i0 + (uint32_t)v * 64u + (uint32_t)lane;
-                            e[v] = tile_cands[i < nc ? i : 0u];
-                        }
-#pragma unroll
-                        for (int v = 0; v < kWalk; ++v) {
-                            const uint32_t r0 = i0 + (uint32_t)v * 64u;
-                            if (r0 < nc) row(e[v], r0 + (uint32_t)lane < nc);
-                        }
-                    }
-                }
-                end(t);
-            }
-        }
-    }
-}
-
-constexpr int kStageBatch = 9;  // tiles whose candidates a wave of k_resolve fetches in one go
-
-// One workgroup per chunk: finish the radix select on the candidates, break ties by bin order,
-// scan the tiles, find the survivors' largest component, write the record header and zero the
-// code words that two tiles will share.
-// KEYS: a candidate's second word equals its key (time domain: both are the pattern of |x|), so only keys are
-// staged and the stage holds twice as many candidates.
-template <bool TABLE, bool KEYS>
-__global__ __launch_bounds__(RT) void k_resolve(uint32_t Tn, uint32_t k, int bits, int m, uint32_t W, size_t S,
-                                                uint32_t word3, uint32_t stage_cap, uint32_t static_vmax,
-                                                uint32_t codes_per_bin,
-                                                uint32_t* __restrict__ sel,
-                                                const uint32_t* __restrict__ tinfo, uint32_t* __restrict__ tscan,
-                                                const uint2* __restrict__ cand, uint8_t* __restrict__ records,
-                                                uint8_t* __restrict__ stream, HeaderInfo hdr, TableArg<TABLE> tab)
-{
-    __shared__ uint32_t h[1024];
-    __shared__ uint32_t tmp[RW];
-    __shared__ uint32_t tgt[MAX_TILES], teq[MAX_TILES], ttake[MAX_TILES], trank[MAX_TILES], tsurv[MAX_TILES];
-    __shared__ uint32_t toff[MAX_TILES], tnc[MAX_TILES], tdef[MAX_TILES], tvd[MAX_TILES];
-    __shared__ uint32_t s_digit, s_need, s_vmax, s_carry[2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int LANES = NW * 64;
+    extern __shared__ __attribute__((aligned(16))) uint2 kept[];
+    __shared__ uint32_t h[kHist2Bins], list[kListCap], list_at[kListCap], list_vb[kListCap];
+    __shared__ uint32_t tmp[NW], tgt[MAX_TILES], teq[MAX_TILES], tnc[MAX_TILES];
+    __shared__ uint32_t s_listed, s_digit, s_need, s_count, s_vmax;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t c = blockIdx.x;
+    const uint4* ti = reinterpret_cast<const uint4*>(tinfo + c * Tn * 4);
+    const uint2* cd = cand + c * Tn * (size_t)kTile;
     const uint32_t bstar = sel[c * 8 + 0];
     uint32_t need = sel[c * 8 + 1];
-    const uint32_t* ti = tinfo + c * Tn * 4;
-    const uint2* cd = cand + c * Tn * (size_t)kTile;
-    uint32_t tau = 0xFFFFFFFFu, quota = 0;
 
-    // Stage the candidates in LDS when they fit (they are read four times below): tile t's candidates go to
-    // stage[toff[t] ..).  Otherwise every pass reads them from global memory.
-    extern __shared__ float2 smem[];
-    uint2* stage = reinterpret_cast<uint2*>(smem);
-    uint32_t* stage_keys = reinterpret_cast<uint32_t*>(smem);
-    auto staged_key = [&](uint32_t i) __attribute__((always_inline)) {
-        if constexpr (KEYS)
-            return stage_keys[i];
-        else
-            return stage[i].x;
+    // per-tile summaries: kept bins and their range, candidates
+    uint32_t vm = 0;  // per-lane maximum over survivors
+    bool more = false;
+    for (uint32_t t = tid; t < Tn; t += LANES) {
+        const uint4 info = ti[t];
+        tgt[t] = info.x;
+        teq[t] = 0u;
+        tnc[t] = info.z;
+        vm = info.x && info.y > vm ? info.y : vm;
+        more = more || info.z > 64u;
+    }
+    for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
+    if (tid == 0) s_digit = s_need = s_count = s_listed = s_vmax = 0u;  // defined even if no digit qualifies
+    const bool heavy = __syncthreads_or(more);
+    const bool any = need > 0;  // else nothing is kept (k = 0), and there are no candidates
+
+    auto count_of = [&](uint32_t t) __attribute__((always_inline)) {
+        return t < Tn ? (uint32_t)__builtin_amdgcn_readfirstlane((int)tnc[t]) : 0u;
     };
-    if (tid == 0) s_carry[0] = 0;
-    __syncthreads();
-    for (uint32_t base = 0; base < Tn; base += RT) {
-        const uint32_t t = base + tid;
-        uint32_t nc = 0;
-        if (t < Tn) {  // the per-tile summaries are read once; every later pass takes them from LDS
-            const uint4 info = reinterpret_cast<const uint4*>(ti)[t];
-            tdef[t] = info.x;
-            tvd[t] = info.y;
-            tnc[t] = nc = info.z;
-        }
-        const uint32_t carry = s_carry[0];
-        const uint32_t incl = block_scan_incl_1024(nc, tmp);
-        if (t < Tn) toff[t] = carry + incl - nc;
-        __syncthreads();
-        if (tid == RT - 1) s_carry[0] = carry + incl;
-        __syncthreads();
-    }
-    const bool staged = s_carry[0] <= stage_cap;
-    if (staged) {
-        // A wave per tile, kStageBatch tiles in flight per wave: a tile's candidates are one contiguous run (about 40
-        // for a 2^20 chunk), so a wave fetches them with one coalesced load, and all loads of a batch are issued
-        // before the first is used: one memory round trip per batch, no search for the tile a candidate belongs to.
-        for (uint32_t t0 = (uint32_t)wave; t0 < Tn; t0 += RW * kStageBatch) {
-            uint2 v[kStageBatch];
+    // row(t, r, e, valid) for every row of 64 candidates of this wave's tiles
+    auto sweep = [&](auto first, auto&& row) __attribute__((always_inline)) {
+        constexpr bool STORE = KEPT && decltype(first)::value, LOAD = KEPT && !decltype(first)::value;
+        for (uint32_t t0 = (uint32_t)wave; t0 < Tn; t0 += NW * kFetch) {
+            uint2 e[kFetch];
 #pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const uint32_t t = t0 + (uint32_t)u * RW;
-                const uint32_t nc = t < Tn ? tnc[t] : 0u;
-                // lanes past the end read their tile's first slot (always allocated) and drop it
-                v[u] = cd[(size_t)(t < Tn ? t : 0u) * kTile + ((uint32_t)lane < nc ? (uint32_t)lane : 0u)];
+            for (int v = 0; v < kFetch; ++v) {
+                // slots behind a tile's last candidate are allocated; what they hold is dropped
+                const uint32_t t = t0 + (uint32_t)(v * NW) < Tn ? t0 + (uint32_t)(v * NW) : 0u;
+                e[v] = LOAD ? kept[t * 64u + lane] : (cd + (size_t)t * kTile)[lane];
             }
 #pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const uint32_t t = t0 + (uint32_t)u * RW;
-                if (t < Tn && (uint32_t)lane < tnc[t]) {
-                    if constexpr (KEYS)
-                        stage_keys[toff[t] + (uint32_t)lane] = v[u].x;
-                    else
-                        stage[toff[t] + (uint32_t)lane] = v[u];
-                }
-            }
-            // the rare tile with more than a row of candidates (runs of equal keys)
-#pragma unroll 1
-            for (int u = 0; u < kStageBatch; ++u) {
-                const uint32_t t = t0 + (uint32_t)u * RW;
-                if (t >= Tn) break;
-                const uint32_t nc = tnc[t], o = toff[t];
-                for (uint32_t i = 64u + (uint32_t)lane; i < nc; i += 64u) {
-                    const uint2 e = cd[(size_t)t * kTile + i];
-                    if constexpr (KEYS)
-                        stage_keys[o + i] = e.x;
-                    else
-                        stage[o + i] = e;
-                }
-            }
-        }
-    }
-    __syncthreads();
-
-    if (need > 0) {
-        uint32_t prefix = bstar << kKeyShift;
-        // two more digits: bits 18..9, then bits 8..0
-        for (int pass = 0; pass < 2; ++pass) {
-            const int shift = pass == 0 ? 9 : 0;
-            const uint32_t dmask = pass == 0 ? 1023u : 511u;
-            const uint32_t pmask = pass == 0 ? (0xFFFFFFFFu << kKeyShift) : (0xFFFFFFFFu << 9);
-            h[tid] = 0u;
-            if (tid == 0) {  // defined even if no digit qualifies (the counts then disagree with the histogram)
-                s_digit = 0u;
-                s_need = 0u;
-            }
-            __syncthreads();
-            if (staged) {
-                const uint32_t total = s_carry[0];
-                for (uint32_t i = tid; i < total; i += RT) {
-                    const uint32_t key = staged_key(i);
-                    if ((key & pmask) == prefix) atomicAdd(&h[(key >> shift) & dmask], 1u);
-                }
-            } else {
-                walk_tiles(cd, tnc, Tn, wave, lane, [](uint32_t) {}, [&](uint2 e, bool valid) {
-                    const bool hit = valid && (e.x & pmask) == prefix;
-                    const uint32_t digit = (e.x >> shift) & dmask;
-                    const uint64_t act = __ballot(hit);
-                    if (act) {
-                        // a row whose keys share the digit (a run of equal values, e.g. zeros) is one atomic
-                        const int first = __ffsll((unsigned long long)act) - 1;
-                        const uint32_t d0 = __shfl(digit, first, 64);
-                        if (__ballot(hit && digit == d0) == act) {
-                            if (lane == first) atomicAdd(&h[d0], (uint32_t)__popcll(act));
-                        } else if (hit) {
-                            atomicAdd(&h[digit], 1u);
-                        }
+            for (int v = 0; v < kFetch; ++v) {
+                const uint32_t t = t0 + (uint32_t)(v * NW), nc = count_of(t);
+                if (STORE && t < Tn) kept[t * 64u + lane] = e[v];
+                row(t, 0u, e[v], (uint32_t)lane < nc);
+                if (heavy)
+                    for (uint32_t i0 = 64u; i0 < nc; i0 += 64u) {
+                        const bool valid = i0 + (uint32_t)lane < nc;
+                        row(t, i0, cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)], valid);
                     }
-                }, [](uint32_t) {});
             }
-            __syncthreads();
-            const uint32_t bin = 1023u - (uint32_t)tid;  // scan from the top digit down
-            const uint32_t cnt = h[bin];
-            const uint32_t incl = block_scan_incl_1024(cnt, tmp);
-            const uint32_t excl = incl - cnt;
-            if (excl < need && incl >= need) {
-                s_digit = bin;
-                s_need = need - excl;
-            }
-            __syncthreads();
-            prefix |= s_digit << shift;
-            need = s_need;
-            __syncthreads();
         }
-        tau = prefix;
-        quota = need;  // bins equal to tau still to take, in bin order
+    };
+    // candidates' next digit: d, counted for the lanes of `act` that want it
+    auto count_digit = [&](bool hit, uint32_t d, bool run_likely) __attribute__((always_inline)) {
+        if (run_likely) {
+            const uint64_t act = __ballot(hit);
+            if (!act) return;
+            // a row whose keys share the digit (a run of equal values, e.g. zeros) is one atomic
+            const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __ffsll((unsigned long long)act) - 1);
+            if (__ballot(hit && d == d0) == act) {
+                if (lane == 0) atomicAdd(&h[d0], (uint32_t)__popcll(act));
+                return;
+            }
+        }
+        if (hit) atomicAdd(&h[d], 1u);
+    };
+    if (any)
+        sweep(std::true_type(), [&](uint32_t, uint32_t i0, uint2 e, bool valid) {
+            count_digit(valid, (e.x >> kHist2Shift) & (uint32_t)(kHist2Bins - 1), i0 != 0);
+        });
+    __syncthreads();
+    constexpr int PER = kHist2Bins / LANES;
+    static_assert(PER >= 1, "a lane scans whole counters");
+    // scan from the top digit down
+    uint32_t cnt[PER], sum = 0;
+    const int base = kHist2Bins - PER - tid * PER;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        cnt[i] = h[base + i];
+        sum += cnt[i];
     }
-
-    // per tile: candidates above tau and equal to tau
-    if (staged) {
-        // one lane per tile walks that tile's staged candidates (about 40 for a 2^20 chunk): no ballots, no
-        // wave-serial loop over tiles
-        for (uint32_t t = tid; t < Tn; t += RT) {
-            const uint32_t nc = tnc[t], o = toff[t];
-            uint32_t gt = 0, eq = 0;
-            for (uint32_t i = 0; i < nc; ++i) {
-                const uint32_t key = staged_key(o + i);
-                gt += key > tau;
-                eq += key == tau;
-            }
-            tgt[t] = gt;
-            teq[t] = eq;
+    uint32_t run = block_scan_incl<NW>(sum, tmp) - sum;
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+        if (run < need && run + cnt[i] >= need) {
+            s_digit = (uint32_t)(base + i);
+            s_need = need - run;
+            s_count = cnt[i];
         }
-    } else {
-        uint32_t gt = 0, eq = 0;  // wave-uniform counts from ballots
-        walk_tiles(cd, tnc, Tn, wave, lane, [&](uint32_t) { gt = eq = 0; }, [&](uint2 e, bool valid) {
-            gt += (uint32_t)__popcll(__ballot(valid && e.x > tau));
-            eq += (uint32_t)__popcll(__ballot(valid && e.x == tau));
-        }, [&](uint32_t t) {
-            if (lane == 0) {
-                tgt[t] = gt;
-                teq[t] = eq;
+        run += cnt[i];
+    }
+    __syncthreads();
+    need = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_need);
+    uint32_t equal = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_count);
+    const int prefix = (int)((bstar << kHist2Bits) | s_digit);  // the top bits of the threshold's key
+    const bool few = equal <= kListCap;
+    uint32_t tau = any ? (uint32_t)prefix << kHist2Shift : 0xFFFFFFFFu, quota = 0;
+    bool ties = false;
+    if (any && few) {
+        sweep(std::false_type(), [&](uint32_t t, uint32_t i0, uint2 e, bool valid) {
+            const int top = valid ? (int)(e.x >> kHist2Shift) : -1;
+            const uint64_t above = __ballot(top > prefix), same = __ballot(top == prefix);
+            vm = top > prefix && e.y > vm ? e.y : vm;
+            if (above && lane == 0) tgt[t] += (uint32_t)__popcll(above);
+            if (same && top == prefix) {
+                const uint32_t at = atomicAdd(&s_listed, 1u);
+                if (at < kListCap) {
+                    list[at] = e.x;
+                    list_at[at] = t * (uint32_t)kTile + i0 + (uint32_t)lane;
+                    list_vb[at] = e.y;
+                }
             }
         });
-    }
-    if (tid == 0) {
-        s_carry[0] = 0;
-        s_carry[1] = 0;
-        s_vmax = 0;
-    }
-    __syncthreads();
-
-    // scan over tiles: equal-key prefix decides who gets the tie quota, survivor prefix gives the ranks
-    for (uint32_t base = 0; base < Tn; base += RT) {
-        const uint32_t t = base + tid;
-        const bool in = t < Tn;
-        const uint32_t eq = in ? teq[t] : 0u;
-        const uint32_t ceq = s_carry[0], crk = s_carry[1];
-        const uint32_t eqincl = block_scan_incl_1024(eq, tmp);
-        const uint32_t eqpre = ceq + eqincl - eq;
-        const uint32_t take = eqpre >= quota ? 0u : (eq < quota - eqpre ? eq : quota - eqpre);
-        const uint32_t surv = in ? (tdef[t] + tgt[t] + take) : 0u;
-        const uint32_t rkincl = block_scan_incl_1024(surv, tmp);
-        // ranks never leave [0, k]: whatever the counts say, the code words of a tile stay inside the record
-        const uint32_t rank_raw = crk + rkincl - surv;
-        const uint32_t rank = rank_raw < k ? rank_raw : k;
-        if (in) {
-            ttake[t] = take;
-            trank[t] = rank;
-            tsurv[t] = surv < k - rank ? surv : k - rank;
-            tscan[(c * Tn + t) * 2 + 0] = rank;
-            tscan[(c * Tn + t) * 2 + 1] = eqpre;
-        }
         __syncthreads();
-        if (tid == RT - 1) {
-            s_carry[0] = ceq + eqincl;
-            s_carry[1] = crk + rkincl;
-        }
-        __syncthreads();
-    }
-
-    // largest component over the survivors (not needed when the caller fixed the range: Sec. 3.2.1, static max)
-    uint32_t vm = 0;  // per-lane running maximum, reduced once at the end
-    if (static_vmax) {
-        // nothing to find
-    } else if (staged) {
-        for (uint32_t t = tid; t < Tn; t += RT) {
-            const uint32_t nc = tnc[t], o = toff[t], take = ttake[t];
-            if (tdef[t]) vm = tvd[t] > vm ? tvd[t] : vm;
-            uint32_t eqrun = 0;  // candidates equal to tau seen so far, in bin order
-            for (uint32_t i = 0; i < nc; ++i) {
-                uint2 e;
-                if constexpr (KEYS)
-                    e = make_uint2(stage_keys[o + i], stage_keys[o + i]);
-                else
-                    e = stage[o + i];
-                const bool iseq = e.x == tau;
-                const bool kept = e.x > tau || (iseq && eqrun < take);
-                eqrun += iseq;
-                if (kept) vm = e.y > vm ? e.y : vm;
+        const uint32_t listed = equal;
+        search_list<4>(list, listed, kHist2Shift, lane, tau, need, equal);
+        quota = need;
+        ties = equal != quota;
+        for (uint32_t i = tid; i < listed; i += LANES) {
+            const uint32_t x = list[i], at = list_at[i];
+            bool kept = x >= tau;
+            if (ties && x == tau) {  // the first of them, in bin order
+                uint32_t before = 0;
+                for (uint32_t j = 0; j < listed; ++j) before += list[j] == tau && list_at[j] < at;
+                kept = before < quota;
+                atomicAdd(&teq[at / (uint32_t)kTile], 1u);
+            }
+            if (kept) {
+                atomicAdd(&tgt[at / (uint32_t)kTile], 1u);
+                vm = list_vb[i] > vm ? list_vb[i] : vm;
             }
         }
-    } else {
-        uint32_t take = 0, eqrun = 0;
-        walk_tiles(cd, tnc, Tn, wave, lane, [&](uint32_t t) {
-            take = ttake[t];
-            if (lane == 0 && tdef[t]) vm = tvd[t] > vm ? tvd[t] : vm;
-            eqrun = 0;
-        }, [&](uint2 e, bool valid) {
-            const bool iseq = valid && e.x == tau;
-            const uint64_t em = __ballot(iseq);
-            const bool kept = valid && (e.x > tau || (iseq && eqrun + prefix_popc(em) < take));
-            if (kept) vm = e.y > vm ? e.y : vm;
-            eqrun += (uint32_t)__popcll(em);
-        }, [](uint32_t) {});
+        __syncthreads();
+    } else if (any) {
+        for (int i = tid; i < 512; i += LANES) h[i] = 0u;
+        __syncthreads();
+        sweep(std::false_type(), [&](uint32_t, uint32_t, uint2 e, bool valid) {
+            count_digit(valid && (int)(e.x >> kHist2Shift) == prefix, e.x & 511u, true);
+        });
+        __syncthreads();
+        if (tid == 0) {
+            uint32_t above = 0;
+            int d = 511;
+            while (d > 0 && above + h[d] < need) above += h[d--];
+            s_digit = (uint32_t)d;
+            s_need = need - above;
+            s_count = h[d];
+        }
+        __syncthreads();
+        tau |= s_digit;
+        quota = s_need;
+        equal = s_count;
+        ties = equal != quota;
+        sweep(std::false_type(), [&](uint32_t t, uint32_t, uint2 e, bool valid) {
+            const uint64_t gm = __ballot(valid && e.x > tau), em = __ballot(valid && e.x == tau);
+            if (lane == 0 && (gm | em)) {
+                tgt[t] += (uint32_t)__popcll(gm);
+                teq[t] += (uint32_t)__popcll(em);
+            }
+            vm = valid && (ties ? e.x > tau : e.x >= tau) && e.y > vm ? e.y : vm;
+        });
+        __syncthreads();
     }
-    vm = wave_max(vm);
-    if (lane == 0 && vm) atomicMax(&s_vmax, vm);
-    __syncthreads();
+    const bool count_equal = any && !few;  // tgt does not hold the kept ones of the bins equal to tau yet
 
-    const uint32_t vmax = static_vmax ? static_vmax : s_vmax;
-    uint32_t pbase = 0;
-    if (bits != 32) {
-        const int shift = 23 - m;
-        const int64_t pb = (int64_t)(vmax >> shift) - (int64_t)((1u << (bits - 1)) - 2u);
-        pbase = pb < 1 ? 1u : (uint32_t)pb;
-    }
+    // scan over tiles: equal-key prefix decides who gets the tie quota, survivor prefix gives the ranks
     uint32_t* rec = reinterpret_cast<uint32_t*>(records + record_offset<TABLE>(tab, c, S));
-    if (tid == 0) {
-        sel[c * 8 + 2] = tau;
-        sel[c * 8 + 3] = quota;
-        sel[c * 8 + 4] = pbase;
-        sel[c * 8 + 5] = vmax;
-        rec[0] = pbase;
-        rec[1] = vmax;
-        rec[2] = k;
-        rec[3] = word3;
-    }
     uint32_t* codes = rec + 4 + W;
     const uint32_t twoN = codes_per_bin * (uint32_t)bits;  // code bits per kept bin
-    for (uint32_t t = tid; t < Tn; t += RT) {
-        if (tsurv[t]) {
-            codes[(twoN * trank[t]) >> 5] = 0u;
-            codes[(twoN * (trank[t] + tsurv[t]) - 1u) >> 5] = 0u;
+    uint32_t eqcarry = 0, rankcarry = 0;
+    for (uint32_t b0 = 0; b0 < Tn; b0 += LANES) {
+        const uint32_t t = b0 + tid;
+        uint32_t surv = t < Tn ? tgt[t] : 0u, eq = t < Tn ? teq[t] : 0u, eqpre = 0;
+        if (ties) {
+            const uint32_t incl = block_scan_incl<NW>(eq, tmp);
+            eqpre = eqcarry + incl - eq;
+            eq = eqpre >= quota ? 0u : (eq < quota - eqpre ? eq : quota - eqpre);
+            if (tid == LANES - 1) s_count = incl;
+        }
+        if (count_equal) {
+            surv += eq;
+            if (t < Tn) teq[t] = eq;
+        }
+        const uint32_t incl = block_scan_incl<NW>(surv, tmp);
+        const uint32_t before = rankcarry + incl - surv;
+        // ranks never leave [0, k]: whatever the counts say, the code words of a tile stay inside the record
+        const uint32_t rank = before < k ? before : k;
+        surv = surv < k - rank ? surv : k - rank;
+        if (t < Tn) {
+            // where all bins equal to tau are taken, a prefix of zero (and an endless quota) says so
+            *reinterpret_cast<uint2*>(tscan + (c * Tn + t) * 2) = make_uint2(rank, eqpre);
+            if (surv) {
+                codes[(twoN * rank) >> 5] = 0u;
+                codes[(twoN * (rank + surv) - 1u) >> 5] = 0u;
+            }
+        }
+        if (b0 + LANES < Tn) {
+            if (tid == LANES - 1) s_digit = incl;
+            __syncthreads();
+            rankcarry += s_digit;
+            if (ties) eqcarry += s_count;
+            __syncthreads();
         }
     }
     const uint32_t code_words = (twoN * k + 31u) >> 5;
     const uint32_t rec_words = (uint32_t)(S / 4) - 4u - W;
-    for (uint32_t w = code_words + tid; w < rec_words; w += RT) codes[w] = 0u;
+    for (uint32_t w = code_words + tid; w < rec_words; w += LANES) codes[w] = 0u;
 
+    // largest component over the survivors (not needed when the caller fixed the range: Sec. 3.2.1, static max)
+    if (!static_vmax) {
+        if (count_equal && ties) {
+            __syncthreads();
+            for (uint32_t t = (uint32_t)wave; t < Tn; t += NW) {
+                const uint32_t nc = count_of(t), take = teq[t];
+                uint32_t eqrun = 0;  // bins of the tile equal to tau seen so far
+                for (uint32_t i0 = 0; i0 < nc && eqrun < take; i0 += 64u) {
+                    const bool valid = i0 + (uint32_t)lane < nc;
+                    const uint2 e = cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)];
+                    const bool iseq = valid && e.x == tau;
+                    const uint64_t em = __ballot(iseq);
+                    vm = iseq && eqrun + prefix_popc(em) < take && e.y > vm ? e.y : vm;
+                    eqrun += (uint32_t)__popcll(em);
+                }
+            }
+        }
+        vm = wave_max(vm);
+        if (lane == 0 && vm) atomicMax(&s_vmax, vm);
+        __syncthreads();
+    }
+    if (tid == 0) {
+        const uint32_t vmax = static_vmax ? static_vmax : s_vmax;
+        uint32_t pbase = 0;
+        if (bits != 32) {
+            const int shift = 23 - m;
+            const int64_t pb = (int64_t)(vmax >> shift) - (int64_t)((1u << (bits - 1)) - 2u);
+            pbase = pb < 1 ? 1u : (uint32_t)pb;
+        }
+        sel[c * 8 + 2] = tau;
+        sel[c * 8 + 3] = ties ? quota : 0xFFFFFFFFu;
+        sel[c * 8 + 4] = pbase;
+        sel[c * 8 + 5] = vmax;
+        *reinterpret_cast<uint4*>(rec) = make_uint4(pbase, vmax, k, word3);
+    }
     if (hdr.write && c == 0 && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
 }
 
@@ -903,7 +836,7 @@ __device__ __forceinline__ void group_prefix_chunk(const uint8_t* __restrict__ s
         const uint32_t g = base + 2 * (uint32_t)tid;
         const uint32_t cnt0 = group_count(g), cnt1 = group_count(g + 1);
         const uint32_t carry = s_carry;
-        const uint32_t incl = block_scan_incl_1024(cnt0 + cnt1, tmp);
+        const uint32_t incl = block_scan_incl<RW>(cnt0 + cnt1, tmp);
         const uint32_t before = carry + incl - cnt0 - cnt1;
         if (g < G) gprefix[g] = before;
         if (g + 1 < G) gprefix[g + 1] = before + cnt0;
@@ -1347,7 +1280,7 @@ __global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npe
 
 }  // namespace
 
-// status words and histograms are adjacent: one fill
+// control block and histograms are adjacent: one fill
 static hipError_t launch_zero_hist(uint8_t* ws_base, const Workspace& w, size_t C, hipStream_t s)
 {
     uint32_t* status = reinterpret_cast<uint32_t*>(ws_base + w.status);
@@ -1410,35 +1343,37 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
     HeaderInfo h{a.write_header, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S,
                  a.hdr_theta, a.time_domain ? 1u : 0u, (uint32_t)a.hdr_scale};
     const uint32_t codes_per_bin = a.time_domain ? 1u : 2u;
-    // up to 12 Ki candidates (96 KiB) are staged in LDS by the per-chunk workgroup, 24 Ki where keys alone suffice
-    constexpr uint32_t kStageCap = 12 * 1024;
-    const uint32_t stage_cap = a.time_domain ? 2 * kStageCap : kStageCap;
-    {
-        // set on every call (a host-side table write): the attribute belongs to the current device, and a flag
-        // remembered across calls would be neither per device nor safe between host threads
-        const void* fn = a.tab           ? reinterpret_cast<const void*>(k_resolve<true, false>)
-                         : a.time_domain ? reinterpret_cast<const void*>(k_resolve<false, true>)
-                                         : reinterpret_cast<const void*>(k_resolve<false, false>);
-        const hipError_t e =
-            hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kStageCap * sizeof(uint2)));
-        if (e != hipSuccess) return e;
-    }
     if (a.tab && a.C > (size_t)kMaxTableChunks) return hipErrorInvalidValue;
-#define FFTSP_RESOLVE(TABLE, KEYS)                                                                                    \
-    FFTSP_LAUNCH("resolve", (k_resolve<TABLE, KEYS>), dim3((unsigned)a.C), dim3(RT), kStageCap * sizeof(uint2), s, Tn, \
-                 a.k, a.bits, a.m, W, a.S, a.word3, stage_cap, a.static_vmax, codes_per_bin, sel, tinfo, tscan, cand,  \
-                 records, stream_base, h, table_arg<TABLE>(a.tab))
+    // few waves for few tiles: their barriers are cheaper than more hands
+#define FFTSP_RESOLVE_AS(TABLE, NW, KEPT)                                                                              \
+    do {                                                                                                               \
+        const size_t lds = KEPT ? (size_t)Tn * 512u : 0u;                                                              \
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_resolve<TABLE, NW, KEPT>),            \
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                \
+        if (e != hipSuccess) return e;                                                                                 \
+        FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW, KEPT>), dim3((unsigned)a.C), dim3(NW * 64), lds, s, Tn, a.k,     \
+                     a.bits, a.m, W, a.S, a.word3, a.static_vmax, codes_per_bin, sel, tinfo, tscan, cand, records,     \
+                     stream_base, h, table_arg<TABLE>(a.tab));                                                         \
+    } while (0)
+#define FFTSP_RESOLVE(TABLE)                                                                                           \
+    do {                                                                                                               \
+        if (Tn <= 40u)                                                                                                 \
+            FFTSP_RESOLVE_AS(TABLE, 4, true);                                                                          \
+        else if (Tn <= 130u)                                                                                           \
+            FFTSP_RESOLVE_AS(TABLE, 8, true);                                                                          \
+        else if (Tn <= 270u) /* 135 KiB beside the kernel's other 20 */                                                \
+            FFTSP_RESOLVE_AS(TABLE, 16, true);                                                                         \
+        else                                                                                                           \
+            FFTSP_RESOLVE_AS(TABLE, 16, false);                                                                        \
+    } while (0)
 #define FFTSP_EMIT(TABLE, REAL, HALF, src)                                                                            \
     FFTSP_LAUNCH("emit", (k_emit<TABLE, REAL, HALF>), dim3((unsigned)(a.C * Tn)), dim3(NT), 0, s, src, a.sstride,     \
                  a.pair_log, B, Tn, W, a.bits, a.m, a.S, sel, tscan, records, table_arg<TABLE>(a.tab), a.n)
     if (a.tab) {
-        FFTSP_RESOLVE(true, false);
+        FFTSP_RESOLVE(true);
         FFTSP_EMIT(true, false, false, X);
     } else {
-        if (a.time_domain)
-            FFTSP_RESOLVE(false, true);
-        else
-            FFTSP_RESOLVE(false, false);
+        FFTSP_RESOLVE(false);
         if (a.time_domain)
             FFTSP_EMIT(false, true, false, spec);
         else if (a.half)
@@ -1447,6 +1382,7 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
             FFTSP_EMIT(false, false, false, X);
     }
 #undef FFTSP_RESOLVE
+#undef FFTSP_RESOLVE_AS
 #undef FFTSP_EMIT
     return hipGetLastError();
 }

@@ -81,6 +81,9 @@ constexpr int kTileThreads = 256;
 constexpr int kHistBits = 12;                 // first radix-select digit: top 12 bits of the 31-bit key
 constexpr int kHistBins = 1 << kHistBits;
 constexpr int kKeyShift = 31 - kHistBits;     // bucket = key >> 19
+constexpr int kHist2Bits = 10;                // second digit, counted among the bins of the threshold's bucket
+constexpr int kHist2Bins = 1 << kHist2Bits;
+constexpr int kHist2Shift = kKeyShift - kHist2Bits;
 
 constexpr size_t kControlBytes = 4096;  // control block at the start of every workspace
 constexpr int kCtlGaveUpWord = 1;       // u32 index of the fused kernels' give-up word inside the control block
