@@ -26,54 +26,85 @@ constexpr int ROWS = 8;              // rows of 64 bins per wave
 constexpr int WAVE_BINS = ROWS * 64; // 512
 static_assert(kTile == 4 * WAVE_BINS, "tile geometry");
 
-// Cooperative load of one tile of the spectrum buffer, [tbase, tbase+count), into LDS as whole 16-byte pieces.
-// A tile is contiguous in the buffer in either bin order (paired runs are tile-aligned), so lanes then pick
-// their own bins from LDS at spec_index(j) - tbase instead of issuing half-dense global loads.
-__device__ __forceinline__ void tile_to_lds(const float2* __restrict__ X, uint32_t tbase, uint32_t count,
-                                            uint32_t sstride, float2* stage, int tid)
+// The tile at X to LDS, as whole 16-byte pieces where it is complete and X aligned.  A tile is contiguous in the spectrum
+// buffer in either bin order (paired runs are tile-aligned).
+template <typename T>
+__device__ __forceinline__ void tile_to_lds(const T* __restrict__ X, uint32_t count, bool aligned, T* stage, int tid)
 {
-    if (count == (uint32_t)kTile && (sstride & 1u) == 0) {  // chunk base and tile base are 16-byte aligned
-        const float4* src = reinterpret_cast<const float4*>(X + tbase);
+    constexpr int PER = 16 / (int)sizeof(T);
+    if (count == (uint32_t)kTile && aligned) {
+        const float4* src = reinterpret_cast<const float4*>(X);
         float4* dst = reinterpret_cast<float4*>(stage);
 #pragma unroll
-        for (int i = 0; i < kTile / 2 / kTileThreads; ++i) dst[tid + i * kTileThreads] = src[tid + i * kTileThreads];
+        for (int i = 0; i < kTile / PER / kTileThreads; ++i) dst[tid + i * kTileThreads] = src[tid + i * kTileThreads];
     } else {
-        for (uint32_t i = tid; i < count; i += kTileThreads) stage[i] = X[tbase + i];
+        for (uint32_t i = tid; i < count; i += kTileThreads) stage[i] = X[i];
     }
 }
 
-// The same from a spectrum stored as binary16 pairs (half-precision variant): converted on the way into LDS, so
-// everything behind it works on binary32 values as before.
-__device__ __forceinline__ void tile_to_lds(const uint32_t* __restrict__ X, uint32_t tbase, uint32_t count,
-                                            uint32_t sstride, float2* stage, int tid)
+// A wave's 512 units of the tile at X (whose first `count` units exist), in memory or in LDS: row r of 64 starts at the
+// tile's unit row0 + 64 r.  In paired order a row's slots are two apart, upwards in the lower half of its run and downwards
+// in the upper one, whose first bin N1/2 sits at position 1, off that line (a run has at least 128 positions and a tile
+// is whole runs, so a row lies in one half of one run).
+template <typename T, typename E>
+__device__ __forceinline__ void load_units(const T* __restrict__ X, uint32_t row0, uint32_t count, int lane, int pair_log,
+                                           E (&z)[ROWS])
 {
-    if (count == (uint32_t)kTile && (sstride & 3u) == 0) {  // four bins per 16 bytes
-        const uint4* src = reinterpret_cast<const uint4*>(X + tbase);
-        float4* dst = reinterpret_cast<float4*>(stage);
+    T raw[ROWS];
+    if (count < (uint32_t)kTile) {  // the end of a chunk: units that do not exist read its last one, or count as zeros
 #pragma unroll
-        for (int i = 0; i < kTile / 4 / kTileThreads; ++i) {
-            const int idx = tid + i * kTileThreads;
-            const uint4 v = src[idx];
-            dst[2 * idx] = cx_load(make_uint2(v.x, v.y));
-            dst[2 * idx + 1] = cx_load(make_uint2(v.z, v.w));
+        for (int r = 0; r < ROWS; ++r) {
+            const uint32_t j = row0 + (uint32_t)(r * 64 + lane);
+            const bool in = j < count;
+            const uint32_t at = count ? spec_index(in ? j : count - 1u, pair_log) : 0u;
+            raw[r] = count ? X[at] : T();
+            if constexpr (std::is_same_v<T, float>) raw[r] = in ? raw[r] : 0.f;
+        }
+    } else if (pair_log == 0) {
+        const T* p = X + row0 + lane;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) raw[r] = p[r * 64];
+    } else if (pair_log >= 10) {
+        const uint32_t N1 = 1u << pair_log, half = N1 / 2, run = row0 & ~(N1 - 1u), k1 = row0 - run;
+        if (k1 < half) {
+            const T* p = X + run + 2u * (k1 + (uint32_t)lane);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) raw[r] = p[r * 128];
+        } else {
+            const uint32_t last = run + 2u * (N1 - k1 - 64u * (ROWS - 1) - (uint32_t)lane) + 1u;  // row ROWS-1
+            const T* p = X + last;
+#pragma unroll
+            for (int r = 1; r < ROWS; ++r) raw[r] = p[(ROWS - 1 - r) * 128];
+            raw[0] = X[k1 == half && lane == 0 ? run + 1u : last + 128u * (ROWS - 1)];
         }
     } else {
-        for (uint32_t i = tid; i < count; i += kTileThreads) stage[i] = unpack_half2(X[tbase + i]);
+        const uint32_t N1 = 1u << pair_log, half = N1 / 2;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const uint32_t row = row0 + (uint32_t)r * 64u, run = row & ~(N1 - 1u), k1 = row - run;
+            const uint32_t slot = k1 < half ? run + 2u * (k1 + (uint32_t)lane) : run + 2u * (N1 - k1 - (uint32_t)lane) + 1u;
+            raw[r] = X[k1 == half && lane == 0 ? run + 1u : slot];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        if constexpr (std::is_same_v<T, float>)
+            z[r] = raw[r];
+        else
+            z[r] = cx_load(raw[r]);
     }
 }
-
-// Time domain: samples [tbase, tbase + kTile) of a chunk, zeros from `present` on.
-__device__ __forceinline__ void tile_to_lds(const float* __restrict__ X, uint32_t tbase, uint32_t present, float* stage,
-                                            int tid)
+// units of the tile at tbase that hold data (samples: the last chunk may end early, the rest counts as zeros)
+template <bool REAL>
+__device__ __forceinline__ uint32_t units_in_tile(size_t n, size_t c, uint32_t B, uint32_t tbase)
 {
-    if (tbase + (uint32_t)kTile <= present) {  // chunks start on multiples of 32 samples of a 16-byte aligned gradient
-        const float4* src = reinterpret_cast<const float4*>(X + tbase);
-        float4* dst = reinterpret_cast<float4*>(stage);
-#pragma unroll
-        for (int i = 0; i < kTile / 4 / kTileThreads; ++i) dst[tid + i * kTileThreads] = src[tid + i * kTileThreads];
-    } else {
-        for (uint32_t i = tid; i < (uint32_t)kTile; i += kTileThreads) stage[i] = tbase + i < present ? X[tbase + i] : 0.f;
-    }
+    const uint32_t end = present_of<REAL>(n, c, B);
+    return end <= tbase ? 0u : (end - tbase < (uint32_t)kTile ? end - tbase : (uint32_t)kTile);
+}
+// lanes of the row of 64 units starting at unit j of a chunk of B that exist
+__device__ __forceinline__ uint64_t row_mask(uint32_t j, uint32_t B)
+{
+    return j + 64u <= B ? ~0ull : (j >= B ? 0ull : (1ull << (B - j)) - 1ull);
 }
 
 // In-tile slot (position in the spectrum buffer minus the tile base) of this lane's bin in each of the wave's
@@ -257,6 +288,11 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
 
 // --------------------------------------------------------------- collect ----
 // Per tile: count and range of the bins kept outright, and the candidates in bin order.
+//
+// Bound by the read of the spectrum.  Binary32 bins pass through LDS: a wave's own rows are half of every line of their
+// run, and fetching each line for two waves was slower (62 M samples in chunks of 2^20: 52 against 44 us).  Samples
+// lie in order, and binary16 bins are half the bytes: those are read straight into registers, without the barrier
+// (62 M samples 51 -> 42, binary16 32 -> 29).
 template <bool REAL, bool HALF>
 __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF>::T* __restrict__ spec, uint32_t sstride,
                                                 int pair_log, uint32_t B, uint32_t Tn, const uint32_t* __restrict__ sel,
@@ -264,30 +300,29 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
 {
     using E = typename Elem<REAL>::T;
     __shared__ uint32_t wcnt[4], wdef[4], wvmax[4];
-    __shared__ E stage[kTile];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t c = blockIdx.x / Tn;
     const uint32_t tile = blockIdx.x % Tn;
-    const typename Stored<REAL, HALF>::T* X = spec + c * (size_t)sstride;
-    const uint32_t tbase = tile * kTile;
-    if constexpr (REAL)
-        tile_to_lds(X, tbase, present_of<REAL>(n, c, B), stage, tid);
-    else
-        tile_to_lds(X, tbase, B - tbase < (uint32_t)kTile ? B - tbase : (uint32_t)kTile, sstride, stage, tid);
-    const uint32_t bstar = sel[c * 8 + 0];
-    __syncthreads();
-    const uint32_t j0 = tbase + wave * WAVE_BINS + lane;
-    const RowSlots slots = row_slots(j0, tbase, pair_log);
+    const uint32_t tbase = tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
+    const typename Stored<REAL, HALF>::T* X = spec + c * (size_t)sstride + tbase;
+    const uint32_t bstar = sel[c * 8 + 0], count = units_in_tile<REAL>(n, c, B, tbase);
+    E z[ROWS];
+    if constexpr (REAL || HALF) {
+        load_units(X, row0, count, lane, pair_log, z);
+    } else {
+        __shared__ __align__(16) E stage[kTile];
+        tile_to_lds(X, count, (sstride & 1u) == 0, stage, tid);
+        __syncthreads();
+        load_units(stage, row0, count, lane, pair_log, z);
+    }
     uint32_t key[ROWS], vb[ROWS];
     uint64_t cm[ROWS];
     uint32_t ndef = 0, vmax = 0, ncand = 0, mine = 0;  // mine: bit r set = this lane's bin of row r is a candidate
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-        const uint32_t j = j0 + r * 64;
-        const bool valid = j < B;
-        const E z = valid ? stage[slot_of(slots, r, j0, tbase, pair_log)] : Elem<REAL>::zero();
-        key[r] = key_of(z);
-        vb[r] = vbits_of(z);
+        const bool valid = tbase + row0 + (uint32_t)(r * 64 + lane) < B;
+        key[r] = key_of(z[r]);
+        vb[r] = vbits_of(z[r]);
         const uint32_t bucket = key[r] >> kKeyShift;
         const bool isdef = valid && bucket > bstar;
         const bool iscand = valid && bucket == bstar;
@@ -631,6 +666,13 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, in
 
 // ------------------------------------------------------------------ emit ----
 // Per tile: flags, ranks, Algorithm 1 codes, bit-packing, bitmap words.
+//
+// Bound by the latency of its loads and by instruction issue.  Everything about a row of 64 units that is the same for all its lanes (place in
+// the tile, existing lanes, flags as a 64-bit mask, counts) is scalar, and bins
+// come straight from memory into registers: by way of LDS, binary32 ones took as long, binary16 ones 50 us for 45.  Samples
+// do pass through LDS, in 16-byte loads (50 us for 55).
+// Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against shuffles and vector masks: 70 -> 67 us,
+// binary16 bins 60 -> 45, 15 % of the samples kept at 32 bits 98 -> 50; one chunk of 2^16 8 -> 7.
 template <bool TABLE, bool REAL, bool HALF>
 __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, uint32_t sstride, int pair_log,
                                              uint32_t B, uint32_t Tn, uint32_t W, int bits, int m, size_t S,
@@ -639,157 +681,159 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
 {
     using E = typename Elem<REAL>::T;
     constexpr uint32_t CODES = Elem<REAL>::kCodes;
-    __shared__ __align__(16) uint32_t cw[kTile * 2 + 8];  // code words of this tile (bits = 32 worst case), see shw
-    __shared__ uint32_t bmw[kTile / 32];
+    constexpr int CW = kTile * (int)CODES / 2 + 8;                       // words for codes of up to 16 bits, see shw
+    __shared__ __align__(16) uint32_t cw[CW];
+    __shared__ __align__(16) uint64_t bmw[kTile / 64];
     __shared__ uint32_t weq[4], wfl[4];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t c = blockIdx.x / Tn;
     const uint32_t tile = blockIdx.x % Tn;
     const uint32_t tau = sel[c * 8 + 2], quota = sel[c * 8 + 3], pbase = sel[c * 8 + 4];
     const uint32_t rank0 = tscan[(c * Tn + tile) * 2 + 0], eq0 = tscan[(c * Tn + tile) * 2 + 1];
-    const uint32_t twoN = CODES * (uint32_t)bits;  // code bits per kept bin
+    const uint32_t twoN = CODES * (uint32_t)bits;  // code bits per kept unit
     const int shift = 23 - m;
-    const uint32_t lds_words = (uint32_t)kTile * twoN / 32u + 2u + 3u;
 
-    // the spectrum tile is staged in the LDS words that later hold the packed codes
-    const typename Stored<REAL, HALF>::T* X = spec + c * (size_t)sstride;
-    E* stage = reinterpret_cast<E*>(cw);
-    static_assert(sizeof(cw) >= kTile * sizeof(float2), "the code buffer doubles as the tile staging area");
-    const uint32_t tbase = tile * kTile;
-    if constexpr (REAL)
-        tile_to_lds(X, tbase, present_of<REAL>(n, c, B), stage, tid);
-    else
-        tile_to_lds(X, tbase, B - tbase < (uint32_t)kTile ? B - tbase : (uint32_t)kTile, sstride, stage, tid);
-    __syncthreads();
-    const uint32_t j0 = tbase + wave * WAVE_BINS + lane;
-    const RowSlots slots = row_slots(j0, tbase, pair_log);
+    const uint32_t tbase = tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;  // row0: this wave's first unit in the tile
+    const typename Stored<REAL, HALF>::T* X = spec + c * (size_t)sstride + tbase;
+    const uint32_t count = units_in_tile<REAL>(n, c, B, tbase);
     E z[ROWS];
-    uint64_t em[ROWS], fm[ROWS];
-    uint32_t neq = 0, gtbits = 0, eqbits = 0;  // bit r = this lane's bin of row r is above / equal to the threshold
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        const uint32_t j = j0 + r * 64;
-        const bool valid = j < B;
-        z[r] = valid ? stage[slot_of(slots, r, j0, tbase, pair_log)] : Elem<REAL>::zero();
-        const uint32_t key = key_of(z[r]);
-        const bool gt = valid && key > tau, eq = valid && key == tau;
-        gtbits |= (uint32_t)gt << r;
-        eqbits |= (uint32_t)eq << r;
-        em[r] = __ballot(eq);
-        neq += (uint32_t)__popcll(em[r]);
+    if constexpr (REAL) {
+        __shared__ __align__(16) E stage[kTile];
+        tile_to_lds(X, count, true, stage, tid);  // chunks start on multiples of 32 samples of a 16-byte aligned gradient
+        __syncthreads();
+        load_units(stage, row0, count, lane, 0, z);
+    } else {
+        load_units(X, row0, count, lane, pair_log, z);
     }
-    if (lane == 0) weq[wave] = neq;
-    __syncthreads();  // every lane has taken its bins out of the staging area
-    for (uint32_t i = tid; i < lds_words; i += NT) cw[i] = 0u;  // ordered before the code writes by the next barrier
-    uint32_t eqrun = eq0;
-    for (int w = 0; w < wave; ++w) eqrun += weq[w];
-    uint32_t nfl = 0, flbits = 0;
+    if (bits != 32)  // 32-bit codes go straight to memory
+        for (uint32_t i = 4u * tid; i < (uint32_t)kTile * twoN / 32u + 8u; i += 4u * NT)
+            *reinterpret_cast<uint4*>(cw + i) = make_uint4(0u, 0u, 0u, 0u);
+    uint64_t fm[ROWS];
+    uint32_t nfl = 0;
+    if (quota == 0xFFFFFFFFu) {  // every unit equal to the threshold is wanted
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        bool flag = (gtbits >> r) & 1u;
-        if (em[r]) {  // wave-uniform: ties are rare, skip their bookkeeping otherwise
-            flag = flag || (((eqbits >> r) & 1u) && eqrun + prefix_popc(em[r]) < quota);
-            eqrun += (uint32_t)__popcll(em[r]);
+        for (int r = 0; r < ROWS; ++r) fm[r] = __ballot(key_of(z[r]) >= tau);
+        if (tbase + (uint32_t)kTile > B) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) fm[r] &= row_mask(tbase + row0 + r * 64u, B);
         }
-        flbits |= (uint32_t)flag << r;
-        fm[r] = __ballot(flag);
-        nfl += (uint32_t)__popcll(fm[r]);
+    } else {
+        uint32_t key[ROWS], neq = 0;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            key[r] = key_of(z[r]);
+            fm[r] = __ballot(key[r] == tau) & row_mask(tbase + row0 + r * 64u, B);
+            neq += (uint32_t)__popcll(fm[r]);
+        }
+        if (lane == 0) weq[wave] = neq;
+        __syncthreads();
+        uint32_t eqrun = eq0;
+#pragma unroll
+        for (int w = 0; w < 3; ++w) eqrun += w < wave ? weq[w] : 0u;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const uint64_t em = fm[r];
+            const bool eq = __builtin_amdgcn_inverse_ballot_w64(em);
+            fm[r] = (__ballot(key[r] > tau) & row_mask(tbase + row0 + r * 64u, B)) | __ballot(eq && eqrun + prefix_popc(em) < quota);
+            eqrun += (uint32_t)__popcll(em);
+        }
     }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) nfl += (uint32_t)__popcll(fm[r]);
     if (lane == 0) {
         wfl[wave] = nfl;
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            bmw[(wave * ROWS + r) * 2 + 0] = (uint32_t)fm[r];
-            bmw[(wave * ROWS + r) * 2 + 1] = (uint32_t)(fm[r] >> 32);
-        }
+        for (int r = 0; r < ROWS; ++r) bmw[wave * ROWS + r] = fm[r];
     }
     __syncthreads();
-    uint32_t rank = rank0;
-    for (int w = 0; w < wave; ++w) rank += wfl[w];
-    const uint32_t total = wfl[0] + wfl[1] + wfl[2] + wfl[3];
-    const uint32_t w0 = (twoN * rank0) >> 5;
     uint32_t* rec = reinterpret_cast<uint32_t*>(records + record_offset<TABLE>(tab, c, S));
     uint32_t* bitmap = rec + 4;
     uint32_t* codes = bitmap + W;
+    if (tid < kTile / 32) {
+        const uint32_t wi = tile * (kTile / 32) + tid;
+        if (wi < W) bitmap[wi] = reinterpret_cast<const uint32_t*>(bmw)[tid];
+    }
+    uint32_t rank = 0, total = 0;  // survivors of the tile before this wave's, and all of them
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const uint32_t v = (uint32_t)__builtin_amdgcn_readfirstlane((int)wfl[w]);
+        rank += w < wave ? v : 0u;
+        total += v;
+    }
+    if (total == 0) return;
+    const uint32_t w0 = (twoN * rank0) >> 5;
     // The tile's code words are built in LDS at cw[shw + i] for the record's word w0 + i, with shw chosen so that an
     // LDS word and its place in memory are aligned alike: whole 16-byte groups then go out as one store each.
     const uint32_t shw = (uint32_t)((reinterpret_cast<uintptr_t>(codes + w0) >> 2) & 3u);
-    // the one or two binary32 patterns a bin is coded from
-    auto part = [](const E& v, int h) __attribute__((always_inline)) {
+    // the one or two binary32 patterns a unit is coded from
+    auto code = [&](const E& v, int h, int width) __attribute__((always_inline)) {
         if constexpr (REAL)
-            return __float_as_uint(v);
+            return quantize(__float_as_uint(v), pbase, width, shift);
         else
-            return __float_as_uint(h ? v.y : v.x);
+            return quantize(__float_as_uint(h ? v.y : v.x), pbase, width, shift);
     };
+    // put(unit, its rank inside the tile) for every survivor
+    auto survivors = [&](auto&& put) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            if (__builtin_amdgcn_inverse_ballot_w64(fm[r])) put(z[r], rank + prefix_popc(fm[r]));
+            rank += (uint32_t)__popcll(fm[r]);
+        }
+    };
+    if (bits == 32) {
+        uint32_t* dst = codes + CODES * rank0;
+        const uint32_t room = (uint32_t)(S / 4) - 4u - W;
+        survivors([&](const E& v, uint32_t rk) {
+            if (CODES * (rank0 + rk + 1u) > room) return;  // never, unless the counts of the tiles disagree
+            if constexpr (REAL)
+                dst[rk] = code(v, 0, 32);
+            else
+                *reinterpret_cast<uint2*>(dst + 2u * rk) = make_uint2(code(v, 0, 32), code(v, 1, 32));
+        });
+        return;
+    }
     if (bits == 8) {
         // 8-bit codes: a survivor is one aligned 16-bit store (bin) or one byte (sample), no read-modify-write
-        uint16_t* cw16 = reinterpret_cast<uint16_t*>(cw);
-        uint8_t* cw8 = reinterpret_cast<uint8_t*>(cw);
-        const uint32_t base16 = rank0 - 2u * w0 + 2u * shw;  // first survivor's 16-bit slot inside cw (two codes each)
-        const uint32_t base8 = rank0 - 4u * w0 + 4u * shw;   // first survivor's byte inside cw (one code each)
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            if ((flbits >> r) & 1u) {
-                const uint32_t rk = rank + prefix_popc(fm[r]);
-                const uint32_t cre = quantize(part(z[r], 0), pbase, 8, shift);
-                if constexpr (REAL) {
-                    cw8[base8 + (rk - rank0)] = (uint8_t)cre;
-                } else {
-                    const uint32_t cim = quantize(part(z[r], 1), pbase, 8, shift);
-                    cw16[base16 + (rk - rank0)] = (uint16_t)(cre | (cim << 8));
-                }
-            }
-            rank += (uint32_t)__popcll(fm[r]);
+        if constexpr (REAL) {
+            uint8_t* dst = reinterpret_cast<uint8_t*>(cw) + (rank0 - 4u * w0 + 4u * shw);
+            survivors([&](const E& v, uint32_t rk) { dst[rk] = (uint8_t)code(v, 0, 8); });
+        } else {
+            uint16_t* dst = reinterpret_cast<uint16_t*>(cw) + (rank0 - 2u * w0 + 2u * shw);
+            survivors([&](const E& v, uint32_t rk) { dst[rk] = (uint16_t)(code(v, 0, 8) | (code(v, 1, 8) << 8)); });
         }
     } else {
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            if ((flbits >> r) & 1u) {
-                const uint32_t rk = rank + prefix_popc(fm[r]);
-                const uint32_t cre = quantize(part(z[r], 0), pbase, bits, shift);
-                const uint32_t cim = quantize(part(z[r], 1), pbase, bits, shift);
-                uint32_t p = twoN * rk - (w0 << 5) + (shw << 5);  // bit position inside cw
-#pragma unroll
-                for (int h = 0; h < (int)CODES; ++h) {
-                    const uint32_t code = h ? cim : cre;
-                    const uint32_t wi = p >> 5, sh = p & 31u;
-                    atomicOr(&cw[wi], code << sh);
-                    if (sh + (uint32_t)bits > 32u) atomicOr(&cw[wi + 1], code >> (32u - sh));
-                    p += (uint32_t)bits;
-                }
-            }
-            rank += (uint32_t)__popcll(fm[r]);
-        }
+        const uint32_t p0 = twoN * rank0 - (w0 << 5) + (shw << 5);  // first survivor's bit position inside cw
+        survivors([&](const E& v, uint32_t rk) {
+            uint32_t both = code(v, 0, bits);
+            if constexpr (!REAL) both |= code(v, 1, bits) << bits;  // at most 32 bits
+            const uint32_t p = p0 + twoN * rk, wi = p >> 5, sh = p & 31u;
+            atomicOr(&cw[wi], both << sh);
+            if (sh + twoN > 32u) atomicOr(&cw[wi + 1], both >> (32u - sh));
+        });
     }
     __syncthreads();
-    if (tid < kTile / 32) {
-        const uint32_t wi = tile * (kTile / 32) + tid;
-        if (wi < W) bitmap[wi] = bmw[tid];
-    }
-    if (total) {
-        const uint32_t w1 = (twoN * (rank0 + total) - 1u) >> 5;
-        const uint32_t rec_words = (uint32_t)(S / 4) - 4u - W;  // code words the record has room for
-        const uint32_t nw_all = w1 - w0 + 1u;
-        const uint32_t nw = w0 >= rec_words ? 0u : (nw_all < rec_words - w0 ? nw_all : rec_words - w0);
-        // group g = LDS words 4g .. 4g+3 = record words w0 - shw + 4g .. (16-byte aligned in memory)
-        const uint32_t groups = (shw + nw + 3u) >> 2;
-        uint32_t* gbase = codes + w0 - shw;
-        for (uint32_t g = tid; g < groups; g += NT) {
-            const uint32_t i0 = 4u * g;  // LDS index of the group's first word; its tile word index is i0 - shw
-            if (i0 >= shw + 1u && i0 + 3u + 1u < shw + nw) {
-                // all four words lie strictly inside the tile's run
-                *reinterpret_cast<uint4*>(gbase + i0) = *reinterpret_cast<const uint4*>(cw + i0);
-            } else {
+    const uint32_t w1 = (twoN * (rank0 + total) - 1u) >> 5;
+    const uint32_t rec_words = (uint32_t)(S / 4) - 4u - W;  // code words the record has room for
+    const uint32_t nw_all = w1 - w0 + 1u;
+    const uint32_t nw = w0 >= rec_words ? 0u : (nw_all < rec_words - w0 ? nw_all : rec_words - w0);
+    // group g = LDS words 4g .. 4g+3 = record words w0 - shw + 4g .. (16-byte aligned in memory)
+    const uint32_t groups = (shw + nw + 3u) >> 2;
+    uint32_t* gbase = codes + w0 - shw;
+    for (uint32_t g = tid; g < groups; g += NT) {
+        const uint32_t i0 = 4u * g;  // LDS index of the group's first word; its tile word index is i0 - shw
+        if (i0 >= shw + 1u && i0 + 3u + 1u < shw + nw) {
+            // all four words lie strictly inside the tile's run
+            *reinterpret_cast<uint4*>(gbase + i0) = *reinterpret_cast<const uint4*>(cw + i0);
+        } else {
 #pragma unroll
-                for (uint32_t j = 0; j < 4u; ++j) {
-                    const uint32_t li = i0 + j;
-                    if (li < shw || li >= shw + nw) continue;
-                    const uint32_t i = li - shw, v = cw[li];
-                    if (i == 0 || i == nw - 1u)
-                        atomicOr(&codes[w0 + i], v);  // may be shared with the neighbouring tile (zeroed by k_resolve)
-                    else
-                        codes[w0 + i] = v;
-                }
+            for (uint32_t j = 0; j < 4u; ++j) {
+                const uint32_t li = i0 + j;
+                if (li < shw || li >= shw + nw) continue;
+                const uint32_t i = li - shw, v = cw[li];
+                if (i == 0 || i == nw - 1u)
+                    atomicOr(&codes[w0 + i], v);  // may be shared with the neighbouring tile (zeroed by k_resolve)
+                else
+                    codes[w0 + i] = v;
             }
         }
     }
