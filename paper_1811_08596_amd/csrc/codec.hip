@@ -107,37 +107,6 @@ __device__ __forceinline__ uint64_t row_mask(uint32_t j, uint32_t B)
     return j + 64u <= B ? ~0ull : (j >= B ? 0ull : (1ull << (B - j)) - 1ull);
 }
 
-// In-tile slot (position in the spectrum buffer minus the tile base) of this lane's bin in each of the wave's
-// rows (bins j0, j0 + 64, ...).  The 512 bins of a wave lie in one half of one paired run when a run has at least
-// 1024 positions, so the slot is linear in the row and costs one add instead of the whole index computation;
-// shorter runs go through spec_index row by row.
-struct RowSlots {
-    uint32_t first;  // row 0 (the run's middle bin N1/2 sits at position 1, off the line of the other rows)
-    uint32_t lin;    // row r >= 1: lin + r * step
-    int step;
-    bool linear;
-};
-__device__ __forceinline__ RowSlots row_slots(uint32_t j0, uint32_t tbase, int pair_log)
-{
-    RowSlots s;
-    s.linear = pair_log == 0 || pair_log >= 10;
-    s.first = s.lin = j0 - tbase;
-    s.step = 64;
-    if (pair_log >= 10) {
-        const uint32_t N1 = 1u << pair_log, k1 = j0 & (N1 - 1u), run = j0 - k1 - tbase;
-        const bool upper = k1 >= N1 / 2;
-        s.lin = run + (upper ? 2u * (N1 - k1) + 1u : 2u * k1);
-        s.first = k1 == N1 / 2 ? run + 1u : s.lin;
-        s.step = upper ? -128 : 128;
-    }
-    return s;
-}
-__device__ __forceinline__ uint32_t slot_of(const RowSlots& s, int r, uint32_t j0, uint32_t tbase, int pair_log)
-{
-    if (s.linear) return r == 0 ? s.first : s.lin + (uint32_t)(r * s.step);
-    return spec_index(j0 + (uint32_t)r * 64u, pair_log) - tbase;
-}
-
 __global__ void k_zero_u32(uint32_t* p, size_t count)
 {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -927,398 +896,282 @@ __global__ __launch_bounds__(RT) void k_group_prefix_peers(PeerList streams, uin
         for (uint32_t i = threadIdx.x; i < (uint32_t)(kControlBytes / 4); i += RT) status[i] = 0u;
 }
 
-// Persistent decoder.  A workgroup walks tiles of 2048 bins (blockIdx, blockIdx + grid, ...), one wave per
-// group of 16 bitmap words.  The kept bins of a wave's 512 bins have consecutive ranks, so their codes are one
-// contiguous byte range of the record: the wave fetches that range with 16-byte loads into its own LDS window
-// and picks the codes out of LDS by rank (a per-bin gather from global memory costs one memory instruction per
-// row of 64 bins and was measured at a quarter of the kernel's time).  The work on a tile is a chain of two
-// dependent memory round trips (bitmap word and group prefix, then the codes) before anything can be stored, so
-// the kernel is software-pipelined: while one item is dequantised, the codes of the next and the bitmap words
-// of the one after are in flight.  All loads are unconditional (clamped to addresses inside the record).
-//
-// With P > 1 peers (receiver under an allgather: Sec. 4, implementation) an item is (tile, peer): a tile's bins
-// are summed over the peers in list order in registers, starting from zero, and stored once.
-struct DecHead {
-    uint32_t word, run, pbase;  // this lane's bitmap word (lanes 0..15), kept bins before the wave's group, record pbase
-};
-
-// NL = 16-byte loads per lane: 1 for codes of up to 8 bits, 2 up to 16, 4 for 32
-template <int NL>
-struct DecCodes {
-    u32x4 main[NL];
-    u32x4 tail;  // lane 0: the 16 bytes behind the main window (the window starts on a 16-byte boundary <= the first code)
-};
-
-struct DecItem {
-    uint32_t t, peer;  // tile index over all chunks, index into the peer list
-};
-
-// VEC: the spectrum buffer is the codec's own (chunks padded to 16 bins, 16-byte aligned): whole-line stores, and
-// the one bin a partial tile may write past the chunk's last bin lands in the padding.
-// verd: header verdict of (peer, chunk) at verd[peer * C + chunk].
-// One stream.
-// REAL: time-domain records (one code per kept sample); `spec` is then the gradient itself, chunk stride B = L
-// samples, written up to sample n only.
-// HALF: the spectrum is written as binary16 pairs (half-precision variant).
-template <int NL, bool VEC, bool TABLE, bool REAL, bool HALF>
-__global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ records, size_t S, uint32_t B, uint32_t W,
-                                               uint32_t k, int bits, int m, uint32_t Tn, uint32_t total, size_t C,
-                                               const uint32_t* __restrict__ gprefix, const uint32_t* __restrict__ sel,
-                                               uint32_t* __restrict__ status,
-                                               typename Stored<REAL, HALF>::T* __restrict__ spec, uint32_t sstride,
-                                               int pair_log, TableArg<TABLE> tab, size_t n)
+// A word every lane reads: by a scalar load, from memory that this kernel does not write.
+template <typename T>
+__device__ __forceinline__ T scalar_load(const T* p)
 {
-    using E = typename Elem<REAL>::T;
-    constexpr uint32_t CODES = Elem<REAL>::kCodes;
-    constexpr int kWin = NL * 1024 + 32;  // bytes of LDS per wave: main window, tail, slack for the 3-word read
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // header verdicts of k_group_prefix raise the status word
-    for (size_t c = (size_t)blockIdx.x * NT + tid; c < C; c += (size_t)gridDim.x * NT) {
-        const uint32_t verdict = sel[c * 8 + 7];
-        if (verdict) atomicMax(status, verdict);
-    }
-    const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
-    const int shift = 23 - m;
-    const uint32_t code_base = 16u + 4u * W;  // byte offset of the codes inside a record
-    __shared__ __attribute__((aligned(16))) E stage[kTile];
-    __shared__ __attribute__((aligned(16))) uint8_t cwin_all[4 * kWin];
-    uint8_t* cwin = cwin_all + wave * kWin;
+    return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
 
-    auto record_of = [&](uint32_t t) __attribute__((always_inline)) {
-        return records + record_offset<TABLE>(tab, t / Tn, S);
-    };
-    auto load_head = [&](uint32_t t, bool live) __attribute__((always_inline)) {
-        if (!live) t = 0;
-        const uint32_t* rec = reinterpret_cast<const uint32_t*>(record_of(t));
-        const uint32_t g = (t % Tn) * (kTile / 32 / GROUP_WORDS) + wave;
-        const uint32_t wi = g * GROUP_WORDS + lane;
-        const bool has = live && lane < GROUP_WORDS && wi < W;
-        DecHead h;
-        h.word = rec[4 + (has ? wi : 0u)];
-        h.run = gprefix[(size_t)(t / Tn) * G + (g < G ? g : 0u)];
-        h.pbase = rec[0];
-        if (!has) h.word = 0u;
-        return h;
-    };
-    // rank of this lane's bin in row r if its bit is set; advances run past the row
-    auto row_rank = [&](const DecHead& h, int r, uint32_t& run, bool& set) __attribute__((always_inline)) {
-        const uint32_t lo = __shfl(h.word, 2 * r, 64), hi = __shfl(h.word, 2 * r + 1, 64);
-        const uint64_t mask = (uint64_t)lo | ((uint64_t)hi << 32);
-        const uint32_t half = lane < 32 ? lo : hi;
-        set = ((half >> (lane & 31)) & 1u) && k > 0;
-        uint32_t rank = run + prefix_popc(mask);
-        run += (uint32_t)__popcll(mask);
-        return rank < k ? rank : (k ? k - 1u : 0u);  // a corrupt bitmap must not point outside the record
-    };
-    // first byte of the wave's LDS window inside the record: the 16-byte boundary at or below its first code
-    auto window_start = [&](const DecHead& h) __attribute__((always_inline)) {
-        const uint32_t first = h.run < k ? h.run : (k ? k - 1u : 0u);
-        return (code_base + ((CODES * (uint32_t)bits * first) >> 3)) & ~15u;
-    };
-    auto load_codes = [&](uint32_t t, bool live, const DecHead& h, DecCodes<NL>& cd) __attribute__((always_inline)) {
-        if (!live) t = 0;
-        const uint8_t* rec = record_of(t);
-        const uint32_t start = window_start(h), last = (uint32_t)S - 16u;  // S is a multiple of 16, at least 32
+// What a wave needs of one record to decode its 512 units (16 bitmap words, group g of the chunk).
+template <int NL>
+struct WaveCodes {
+    uint64_t fm[ROWS];   // kept units of each row
+    uint32_t run;        // kept units of the chunk before the wave's
+    uint32_t pbase;      // from the record's header
+    uint32_t rel;        // bit position of the wave's first code inside its window
+    u32x4 main[NL ? NL : 1], tail;
+};
+
+// NL: 16-byte loads per lane.  The codes of a wave's kept units are one contiguous byte range of the record.  Up to 16 bits
+// wide they are fetched as a window of NL * 1024 + 16 bytes from the 16-byte boundary below the first one (lanes past the
+// last code's 16 bytes repeat them), and picked out of LDS by rank; 32-bit codes (NL = 0) need no unpacking and are read by
+// rank from memory, a row's being adjacent.  The header, the bitmap words and the prefix are scalar loads.
+template <int NL, uint32_t CODES>
+__device__ __forceinline__ void fetch_codes(const uint8_t* __restrict__ record, size_t S, uint32_t W, uint32_t g, int bits,
+                                            const uint32_t* __restrict__ gprefix, int lane, WaveCodes<NL>& wc)
+{
+    const uint32_t* rec = reinterpret_cast<const uint32_t*>(record);
+    const uint32_t w0 = g * GROUP_WORDS;
+    wc.pbase = scalar_load(rec);
+    wc.run = scalar_load(gprefix + (w0 < W ? g : 0u));
+    if (w0 + GROUP_WORDS <= W) {
+        const uint64_t* p = reinterpret_cast<const uint64_t*>(rec + 4 + w0);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) wc.fm[r] = scalar_load(p + r);
+    } else {
+        const uint32_t w = w0 + (uint32_t)lane, v = w < W ? rec[4 + w] : 0u;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            wc.fm[r] = (uint32_t)__builtin_amdgcn_readlane((int)v, 2 * r) |
+                       ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)v, 2 * r + 1) << 32);
+    }
+    if constexpr (NL > 0) {
+        const uint32_t kept = w0 + GROUP_WORDS < W ? scalar_load(gprefix + g + 1u) - wc.run : (uint32_t)WAVE_BINS;
+        const uint32_t width = CODES * (uint32_t)bits, last = (uint32_t)S - 16u;  // S is a multiple of 16, at least 32
+        const uint32_t first = 8u * (16u + 4u * W) + width * wc.run;             // bit position in the record
+        const uint32_t start = (first >> 3) & ~15u, end = (first + width * kept) >> 3 & ~15u;
+        const uint32_t lim = end < last ? end : last;  // a corrupt bitmap must not point outside the record
+        wc.rel = first - 8u * start;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             const uint32_t off = start + (uint32_t)(i * 1024 + lane * 16);
-            cd.main[i] = *reinterpret_cast<const u32x4*>(rec + (off < last ? off : last));
+            wc.main[i] = *reinterpret_cast<const u32x4*>(record + (off < lim ? off : lim));
         }
         const uint32_t off = start + (uint32_t)(NL * 1024);
-        cd.tail = *reinterpret_cast<const u32x4*>(rec + (off < last ? off : last));
-    };
-    auto finish = [&](uint32_t t, const DecHead& h, const DecCodes<NL>& cd) __attribute__((always_inline)) {
-        const uint32_t tile = t % Tn, tbase = tile * kTile;
-        const uint32_t j0 = tbase + wave * WAVE_BINS + lane;
-        const RowSlots slots = row_slots(j0, tbase, pair_log);
-#pragma unroll
-        for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(cwin + i * 1024 + lane * 16) = cd.main[i];
-        if (lane == 0) *reinterpret_cast<u32x4*>(cwin + NL * 1024) = cd.tail;
-        __syncthreads();  // codes visible to the wave; the previous tile's stage has been read by everyone
-        const uint32_t start = window_start(h);
-        uint32_t run = h.run;
-        // The tile's bins occupy one contiguous range of the spectrum buffer in either bin order (paired runs are
-        // tile-aligned), so values are placed in LDS at their in-tile position and written out as whole lines.
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            bool set;
-            const uint32_t rank = row_rank(h, r, run, set);
-            E out = Elem<REAL>::zero();
-            if (set) {
-                const uint32_t p = CODES * (uint32_t)bits * rank;             // bit offset of the bin's codes
-                uint32_t cre, cim = 0u;
-                if (bits == 8) {
-                    if constexpr (REAL) {
-                        cre = cwin[code_base + (p >> 3) - start];
-                    } else {
-                        const uint32_t v = *reinterpret_cast<const uint16_t*>(cwin + (code_base + (p >> 3) - start));
-                        cre = v & 0xFFu;
-                        cim = v >> 8;
-                    }
-                } else {
-                    const uint32_t* w = reinterpret_cast<const uint32_t*>(cwin + (code_base + 4u * (p >> 5) - start));
-                    const uint32_t keep = bits == 32 ? 0xFFFFFFFFu : ((1u << bits) - 1u);
-                    const uint32_t sh = p & 31u;
-                    if constexpr (REAL) {
-                        const uint64_t w01 = (uint64_t)w[0] | ((uint64_t)w[1] << 32);
-                        cre = (uint32_t)(w01 >> sh) & keep;
-                    } else {
-                        const uint32_t w0 = w[0], w1 = w[1], w2 = w[2];
-                        const uint32_t q = sh + (uint32_t)bits;
-                        const uint64_t w01 = (uint64_t)w0 | ((uint64_t)w1 << 32), w12 = (uint64_t)w1 | ((uint64_t)w2 << 32);
-                        cre = (uint32_t)(w01 >> sh) & keep;
-                        cim = (uint32_t)((q >= 32u ? w12 : w01) >> (q & 31u)) & keep;
-                    }
-                }
-                if constexpr (REAL) {
-                    out = __uint_as_float(dequantize(cre, h.pbase, bits, shift));
-                } else {
-                    out.x = __uint_as_float(dequantize(cre, h.pbase, bits, shift));
-                    out.y = __uint_as_float(dequantize(cim, h.pbase, bits, shift));
-                }
-            }
-            const uint32_t j = j0 + r * 64;
-            if (j < B) stage[slot_of(slots, r, j0, tbase, pair_log)] = out;
-        }
-        __syncthreads();
-        typename Stored<REAL, HALF>::T* X = spec + (size_t)(t / Tn) * (size_t)sstride;
-        if constexpr (REAL) {
-            // samples of this tile that exist in the gradient (the last chunk may end inside or before the tile)
-            const uint32_t present = present_of<REAL>(n, t / Tn, B);
-            const uint32_t count = present > tbase ? (present - tbase < (uint32_t)kTile ? present - tbase : (uint32_t)kTile) : 0u;
-            if (VEC && count == (uint32_t)kTile) {
-                float4* dst = reinterpret_cast<float4*>(X + tbase);
-                const float4* src = reinterpret_cast<const float4*>(stage);
-#pragma unroll
-                for (int i = 0; i < kTile / 4 / NT; ++i) dst[tid + i * NT] = src[tid + i * NT];
-            } else {
-                for (uint32_t i = tid; i < count; i += NT) X[tbase + i] = stage[i];
-            }
-        } else if constexpr (HALF) {
-            const uint32_t count = B - tbase < (uint32_t)kTile ? B - tbase : (uint32_t)kTile;
-            if constexpr (VEC) {  // four bins per 16-byte store; up to three land in the chunk's padding
-                uint4* dst = reinterpret_cast<uint4*>(X + tbase);
-                const float4* src = reinterpret_cast<const float4*>(stage);
-#pragma unroll
-                for (int i = 0; i < kTile / 4 / NT; ++i) {
-                    const uint32_t idx = (uint32_t)(tid + i * NT);
-                    if (4u * idx < count) {
-                        const uint2 a = cx_store<true>(src[2 * idx]), b = cx_store<true>(src[2 * idx + 1]);
-                        dst[idx] = make_uint4(a.x, a.y, b.x, b.y);
-                    }
-                }
-            } else {
-                for (uint32_t i = tid; i < count; i += NT) X[tbase + i] = pack_half2(stage[i]);
-            }
-        } else {
-            const uint32_t count = B - tbase < (uint32_t)kTile ? B - tbase : (uint32_t)kTile;
-            if constexpr (VEC) {
-                float4* dst = reinterpret_cast<float4*>(X + tbase);
-                const float4* src = reinterpret_cast<const float4*>(stage);
-#pragma unroll
-                for (int i = 0; i < kTile / 2 / NT; ++i) {
-                    const uint32_t idx = (uint32_t)(tid + i * NT);
-                    if (2u * idx < count) dst[idx] = src[idx];
-                }
-            } else {
-                for (uint32_t i = tid; i < count; i += NT) X[tbase + i] = stage[i];
-            }
-        }
-    };
-
-    // Three register sets rotate by name through a loop body written out three times: rotating by assignment
-    // would copy registers that loads are still filling, and a copy waits for its load.
-    uint32_t t = blockIdx.x;
-    const uint32_t step = gridDim.x;
-    if (t >= total) return;
-    DecHead h0, h1, h2;
-    DecCodes<NL> c0, c1, c2;
-    // tile t is in (hc, cc), tile t+1 in (hn, cn); fetches what tiles t+1 and t+2 need, then finishes tile t
-    auto advance = [&](const DecHead& hc, const DecCodes<NL>& cc, const DecHead& hn, DecCodes<NL>& cn, DecHead& hn2) __attribute__((always_inline)) {
-        const bool more = t + step < total;
-        const bool more2 = more && t + 2 * step < total;
-        hn2 = load_head(more2 ? t + 2 * step : 0u, more2);
-        load_codes(more ? t + step : 0u, more, hn, cn);
-        finish(t, hc, cc);
-        t += step;
-        return more;
-    };
-    h0 = load_head(t, true);
-    h1 = load_head(t + step, t + step < total);
-    load_codes(t, true, h0, c0);
-    for (;;) {
-        if (!advance(h0, c0, h1, c1, h2)) break;
-        if (!advance(h1, c1, h2, c2, h0)) break;
-        if (!advance(h2, c2, h0, c0, h1)) break;
+        wc.tail = *reinterpret_cast<const u32x4*>(record + (off < lim ? off : lim));
     }
 }
 
-// The decoder for several peers' streams: same pipeline, items are (tile, peer).
-template <int NL, bool VEC>
-__global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npeers, size_t S, uint32_t B, uint32_t W,
-                                               uint32_t k, int bits, int m, uint32_t Tn, uint32_t total, size_t C,
-                                               const uint32_t* __restrict__ gprefix, const uint32_t* __restrict__ verd,
-                                               uint32_t* __restrict__ status,
-                                               float2* __restrict__ spec, uint32_t sstride, int pair_log)
-{
-    constexpr int kWin = NL * 1024 + 32;  // bytes of LDS per wave: main window, tail, slack for the 3-word read
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t P = npeers;
-    // header verdicts of the group-prefix kernel raise the status word
-    for (size_t i = (size_t)blockIdx.x * NT + tid; i < C * P; i += (size_t)gridDim.x * NT) {
-        const uint32_t verdict = verd[i];
-        if (verdict) atomicMax(status, verdict);
-    }
-    const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
-    const int shift = 23 - m;
-    const uint32_t code_base = 16u + 4u * W;  // byte offset of the codes inside a record
-    __shared__ float2 stage[kTile];
-    __shared__ __attribute__((aligned(16))) uint8_t cwin_all[4 * kWin];
-    uint8_t* cwin = cwin_all + wave * kWin;
-    const uint32_t step = gridDim.x;
+template <int NL>
+constexpr int kWindow = NL * 1024 + 32;  // bytes of LDS per wave: the window and slack for a two-word read
+typedef u32x4 __attribute__((may_alias)) u32x4_any;
+typedef uint32_t __attribute__((may_alias)) u32_any;
+typedef uint16_t __attribute__((may_alias)) u16_any;
 
-    auto record_of = [&](DecItem it) __attribute__((always_inline)) {
-        return recs.p[it.peer] + (size_t)(it.t / Tn) * S;
-    };
-    auto next_item = [&](DecItem it) __attribute__((always_inline)) {
-        DecItem n;
-        const bool last_peer = it.peer + 1u == P;
-        n.peer = last_peer ? 0u : it.peer + 1u;
-        n.t = last_peer ? it.t + step : it.t;
-        return n;
-    };
-    // live = false: the item does not exist; the loads are still issued, to item (0, 0)
-    auto load_head = [&](DecItem it, bool live) __attribute__((always_inline)) {
-        if (!live) it.t = it.peer = 0;
-        const uint32_t* rec = reinterpret_cast<const uint32_t*>(record_of(it));
-        const uint32_t g = (it.t % Tn) * (kTile / 32 / GROUP_WORDS) + wave;
-        const uint32_t wi = g * GROUP_WORDS + lane;
-        const bool has = live && lane < GROUP_WORDS && wi < W;
-        DecHead h;
-        h.word = rec[4 + (has ? wi : 0u)];
-        h.run = gprefix[((size_t)it.peer * C + it.t / Tn) * G + (g < G ? g : 0u)];
-        h.pbase = rec[0];
-        if (!has) h.word = 0u;
-        return h;
-    };
-    // rank of this lane's bin in row r if its bit is set; advances run past the row
-    auto row_rank = [&](const DecHead& h, int r, uint32_t& run, bool& set) __attribute__((always_inline)) {
-        const uint32_t lo = __shfl(h.word, 2 * r, 64), hi = __shfl(h.word, 2 * r + 1, 64);
-        const uint64_t mask = (uint64_t)lo | ((uint64_t)hi << 32);
-        const uint32_t half = lane < 32 ? lo : hi;
-        set = ((half >> (lane & 31)) & 1u) && k > 0;
-        uint32_t rank = run + prefix_popc(mask);
-        run += (uint32_t)__popcll(mask);
-        return rank < k ? rank : (k ? k - 1u : 0u);  // a corrupt bitmap must not point outside the record
-    };
-    // first byte of the wave's LDS window inside the record: the 16-byte boundary at or below its first code
-    auto window_start = [&](const DecHead& h) __attribute__((always_inline)) {
-        const uint32_t first = h.run < k ? h.run : (k ? k - 1u : 0u);
-        return (code_base + ((2u * (uint32_t)bits * first) >> 3)) & ~15u;
-    };
-    auto load_codes = [&](DecItem it, bool live, const DecHead& h, DecCodes<NL>& cd) __attribute__((always_inline)) {
-        if (!live) it.t = it.peer = 0;
-        const uint8_t* rec = record_of(it);
-        const uint32_t start = window_start(h), last = (uint32_t)S - 16u;  // S is a multiple of 16, at least 32
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            const uint32_t off = start + (uint32_t)(i * 1024 + lane * 16);
-            cd.main[i] = *reinterpret_cast<const u32x4*>(rec + (off < last ? off : last));
-        }
-        const uint32_t off = start + (uint32_t)(NL * 1024);
-        cd.tail = *reinterpret_cast<const u32x4*>(rec + (off < last ? off : last));
-    };
-    float2 acc[ROWS];  // this lane's bins of the tile being summed over the peers
-    auto finish = [&](DecItem it, const DecHead& h, const DecCodes<NL>& cd) __attribute__((always_inline)) {
-        const uint32_t tile = it.t % Tn, tbase = tile * kTile;
-        const uint32_t j0 = tbase + wave * WAVE_BINS + lane;
-        const RowSlots slots = row_slots(j0, tbase, pair_log);
-#pragma unroll
-        for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4*>(cwin + i * 1024 + lane * 16) = cd.main[i];
-        if (lane == 0) *reinterpret_cast<u32x4*>(cwin + NL * 1024) = cd.tail;
-        __syncthreads();  // codes visible to the wave; the previous tile's stage has been read by everyone
-        const uint32_t start = window_start(h);
-        uint32_t run = h.run;
+// put(row, value) for all rows, zero where a unit is not kept.  The window is the wave's own: no barrier.
+template <int NL, bool REAL, typename Put>
+__device__ __forceinline__ void unpack_codes(const WaveCodes<NL>& wc, const uint8_t* __restrict__ record, size_t S, uint32_t W,
+                                             int bits, int shift, int lane, uint8_t* window, Put&& put)
+{
+    using E = typename Elem<REAL>::T;
+    constexpr uint32_t CODES = Elem<REAL>::kCodes;
+    if constexpr (NL == 0) {
+        const uint32_t* codes = reinterpret_cast<const uint32_t*>(record) + 4 + W;
+        const uint32_t room = (uint32_t)(S / 4) - 4u - W;  // code words the record has room for
+        E v[ROWS];
+        uint32_t first = CODES * wc.run;  // a row's first code
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            bool set;
-            const uint32_t rank = row_rank(h, r, run, set);
-            float2 out = make_float2(0.f, 0.f);
-            if (set) {
-                const uint32_t p = 2u * (uint32_t)bits * rank;                // bit offset of the pair in the codes
-                uint32_t cre, cim;
-                if (bits == 8) {
-                    const uint32_t v = *reinterpret_cast<const uint16_t*>(cwin + (code_base + (p >> 3) - start));
-                    cre = v & 0xFFu;
-                    cim = v >> 8;
+            const uint32_t at = first + CODES * prefix_popc(wc.fm[r]);
+            v[r] = Elem<REAL>::zero();
+            if (__builtin_amdgcn_inverse_ballot_w64(wc.fm[r]) && at + CODES <= room) __builtin_memcpy(&v[r], codes + at, sizeof(E));
+            first += CODES * (uint32_t)__popcll(wc.fm[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) put(r, v[r]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) *reinterpret_cast<u32x4_any*>(window + i * 1024 + lane * 16) = wc.main[i];
+        if (lane == 0) *reinterpret_cast<u32x4_any*>(window + NL * 1024) = wc.tail;
+        __builtin_amdgcn_wave_barrier();
+        uint32_t base = (wc.pbase - 1u) << shift;
+        asm("" : "+v"(base));  // in a vector register, so that it is the addend of a shift-and-add
+        auto rows = [&](auto narrow) __attribute__((always_inline)) {
+            constexpr bool BYTES = decltype(narrow)::value;
+            const uint32_t nb = BYTES ? 8u : (uint32_t)bits;
+            uint32_t raw[ROWS];
+            uint32_t at = BYTES ? wc.rel >> 3 : wc.rel;  // a row's first code in the window, in bytes or bits
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                const uint32_t rank = prefix_popc(wc.fm[r]), kept = (uint32_t)__popcll(wc.fm[r]);
+                if constexpr (BYTES && REAL) {
+                    raw[r] = window[at + rank];
+                    at += kept;
+                } else if constexpr (BYTES) {
+                    raw[r] = *reinterpret_cast<const u16_any*>(window + (at + 2u * rank));
+                    at += 2u * kept;
                 } else {
-                    const uint32_t* w = reinterpret_cast<const uint32_t*>(cwin + (code_base + 4u * (p >> 5) - start));
-                    const uint32_t w0 = w[0], w1 = w[1], w2 = w[2];
-                    const uint32_t sh = p & 31u, q = sh + (uint32_t)bits;
-                    const uint64_t w01 = (uint64_t)w0 | ((uint64_t)w1 << 32), w12 = (uint64_t)w1 | ((uint64_t)w2 << 32);
-                    const uint32_t keep = bits == 32 ? 0xFFFFFFFFu : ((1u << bits) - 1u);
-                    cre = (uint32_t)(w01 >> sh) & keep;
-                    cim = (uint32_t)((q >= 32u ? w12 : w01) >> (q & 31u)) & keep;
+                    const uint32_t p = at + CODES * nb * rank;
+                    const u32_any* w = reinterpret_cast<const u32_any*>(window + 4u * (p >> 5));
+                    raw[r] = __builtin_amdgcn_alignbit(w[1], w[0], p);  // a unit's codes are at most 32 bits
+                    at += CODES * nb * kept;
                 }
-                out.x = __uint_as_float(dequantize(cre, h.pbase, bits, shift));
-                out.y = __uint_as_float(dequantize(cim, h.pbase, bits, shift));
             }
-            const float2 prev = it.peer == 0 ? make_float2(0.f, 0.f) : acc[r];
-            acc[r] = make_float2(prev.x + out.x, prev.y + out.y);
-        }
-        if (it.peer + 1u != P) {
-            __syncthreads();  // every lane has picked its codes before the next item overwrites the window
-            return;
-        }
-        // The tile's bins occupy one contiguous range of the spectrum buffer in either bin order (paired runs are
-        // tile-aligned), so the sums are placed in LDS at their in-tile position and written out as whole lines.
 #pragma unroll
-        for (int r = 0; r < ROWS; ++r)
-            if (j0 + (uint32_t)r * 64u < B) stage[slot_of(slots, r, j0, tbase, pair_log)] = acc[r];
-        __syncthreads();
-        float2* X = spec + (size_t)(it.t / Tn) * (size_t)sstride;
-        const uint32_t count = B - tbase < (uint32_t)kTile ? B - tbase : (uint32_t)kTile;
-        if constexpr (VEC) {
-            float4* dst = reinterpret_cast<float4*>(X + tbase);
-            const float4* src = reinterpret_cast<const float4*>(stage);
-#pragma unroll
-            for (int i = 0; i < kTile / 2 / NT; ++i) {
-                const uint32_t idx = (uint32_t)(tid + i * NT);
-                if (2u * idx < count) dst[idx] = src[idx];
+            for (int r = 0; r < ROWS; ++r) {
+                const uint32_t codes = __builtin_amdgcn_inverse_ballot_w64(wc.fm[r]) ? raw[r] : 0u;
+                if constexpr (REAL) {
+                    put(r, __uint_as_float(dequantize_field(codes, 0u, nb, base, shift)));
+                } else {
+                    put(r, make_float2(__uint_as_float(dequantize_field(codes, 0u, nb, base, shift)),
+                                       __uint_as_float(dequantize_field(codes, nb, nb, base, shift))));
+                }
             }
-        } else {
-            for (uint32_t i = tid; i < count; i += NT) X[tbase + i] = stage[i];
-        }
-    };
-
-    // Three register sets rotate by name through a loop body written out three times: rotating by assignment
-    // would copy registers that loads are still filling, and a copy waits for its load.
-    DecItem cur;
-    cur.t = blockIdx.x;
-    cur.peer = 0;
-    if (cur.t >= total) return;
-    DecHead h0, h1, h2;
-    DecCodes<NL> c0, c1, c2;
-    // item `cur` is in (hc, cc), the next one in (hn, cn); fetches what the next two items need, then finishes cur
-    auto advance = [&](const DecHead& hc, const DecCodes<NL>& cc, const DecHead& hn, DecCodes<NL>& cn, DecHead& hn2) __attribute__((always_inline)) {
-        const DecItem nxt = next_item(cur), nx2 = next_item(nxt);
-        const bool more = nxt.t < total, more2 = more && nx2.t < total;
-        hn2 = load_head(nx2, more2);
-        load_codes(nxt, more, hn, cn);
-        finish(cur, hc, cc);
-        cur = nxt;
-        return more;
-    };
-    h0 = load_head(cur, true);
-    {
-        const DecItem nxt = next_item(cur);
-        h1 = load_head(nxt, nxt.t < total);
+        };
+        if (NL == 1 && bits == 8)
+            rows(std::true_type{});
+        else
+            rows(std::false_type{});
+        __builtin_amdgcn_wave_barrier();
     }
-    load_codes(cur, true, h0, c0);
-    for (;;) {
-        if (!advance(h0, c0, h1, c1, h2)) break;
-        if (!advance(h1, c1, h2, c2, h0)) break;
-        if (!advance(h2, c2, h0, c0, h1)) break;
+}
+
+// The wave's units to their slots of a staged tile (see load_units).
+template <typename T>
+__device__ __forceinline__ void place_units(T* stage, uint32_t row0, int lane, int pair_log, const T (&z)[ROWS])
+{
+    if (pair_log == 0) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) stage[row0 + (uint32_t)(lane + r * 64)] = z[r];
+        return;
+    }
+    const uint32_t N1 = 1u << pair_log, half = N1 / 2;
+    if (pair_log >= 10) {
+        const uint32_t run = row0 & ~(N1 - 1u), k1 = row0 - run;
+        if (k1 < half) {
+            T* p = stage + run + 2u * (k1 + (uint32_t)lane);
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) p[r * 128] = z[r];
+        } else {
+            const uint32_t last = run + 2u * (N1 - k1 - 64u * (ROWS - 1) - (uint32_t)lane) + 1u;  // row ROWS-1
+            T* p = stage + last;
+#pragma unroll
+            for (int r = 1; r < ROWS; ++r) p[(ROWS - 1 - r) * 128] = z[r];
+            stage[k1 == half && lane == 0 ? run + 1u : last + 128u * (ROWS - 1)] = z[0];
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const uint32_t row = row0 + (uint32_t)r * 64u, run = row & ~(N1 - 1u), k1 = row - run;
+            const uint32_t slot = k1 < half ? run + 2u * (k1 + (uint32_t)lane) : run + 2u * (N1 - k1 - (uint32_t)lane) + 1u;
+            stage[k1 == half && lane == 0 ? run + 1u : slot] = z[r];
+        }
+    }
+}
+
+// A staged tile to memory.  vec: the spectrum buffer is the codec's own (chunks padded to 16 bins, 16-byte aligned):
+// 16-byte stores, whose last one may reach past the chunk's last bin into the padding.
+template <typename T>
+__device__ __forceinline__ void tile_from_lds(T* __restrict__ X, const T* stage, uint32_t count, bool vec, int tid)
+{
+    constexpr int PER = 16 / (int)sizeof(T);
+    if (vec) {
+        float4* dst = reinterpret_cast<float4*>(X);
+        const float4* src = reinterpret_cast<const float4*>(stage);
+#pragma unroll
+        for (int i = 0; i < kTile / PER / NT; ++i) {
+            const uint32_t idx = (uint32_t)(tid + i * NT);
+            if ((uint32_t)PER * idx < count) dst[idx] = src[idx];
+        }
+    } else {
+        for (uint32_t i = tid; i < count; i += NT) X[i] = stage[i];
+    }
+}
+
+// One stream: a workgroup per tile, a wave per 512 units.  The header verdict of chunk c is in sel[8c + 7].
+// REAL: time-domain records (one code per kept sample); `spec` is then the gradient itself, chunk stride B = L
+// samples, written up to sample n only.
+// HALF: the spectrum is written as binary16 pairs (half-precision variant).
+//
+// Bound by the stores of the decoded units, and by instruction issue: everything that is the same for a row's 64 lanes
+// (its flags as a mask, counts, addresses) is scalar.  Two dependent round trips (bitmap and prefix, then codes) are
+// covered by the seven workgroups that a compute unit holds.
+// Measured, 62 M samples in chunks of 2^20, against persistent workgroups with software-pipelined loads whose flags and
+// ranks were per lane: half of the bins kept as 8-bit codes 62 -> 54 us (298 MB of traffic), binary16 bins 52 -> 33, 15 % of
+// the samples kept at 32 bits 93 -> 62; chunks of 2^22 (138 M samples) 136 -> 112.
+template <int NL, bool TABLE, bool REAL, bool HALF>
+__global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ records, size_t S, uint32_t B, uint32_t W,
+                                               int bits, int m, uint32_t Tn, const uint32_t* __restrict__ gprefix,
+                                               const uint32_t* __restrict__ sel, uint32_t* __restrict__ status,
+                                               typename Stored<REAL, HALF>::T* __restrict__ spec, uint32_t sstride, bool vec,
+                                               int pair_log, TableArg<TABLE> tab, size_t n)
+{
+    using T = typename Stored<REAL, HALF>::T;
+    __shared__ __align__(16) uint8_t windows[NL ? 4 * kWindow<NL> : 16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const size_t c = blockIdx.x / Tn;
+    const uint32_t tile = blockIdx.x % Tn, tbase = tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
+    const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
+    const uint8_t* record = records + record_offset<TABLE>(tab, c, S);
+    uint8_t* window = windows + (NL ? wave * kWindow<NL> : 0);
+    WaveCodes<NL> wc;
+    fetch_codes<NL, Elem<REAL>::kCodes>(record, S, W, tile * (kTile / 32 / GROUP_WORDS) + wave, bits, gprefix + c * G, lane, wc);
+    T z[ROWS];
+    unpack_codes<NL, REAL>(wc, record, S, W, bits, 23 - m, lane, window, [&](int r, const typename Elem<REAL>::T& v) {
+        if constexpr (HALF)
+            z[r] = pack_half2(v);
+        else
+            z[r] = v;
+    });
+    T* X = spec + c * (size_t)sstride + tbase;
+    const uint32_t count = units_in_tile<REAL>(n, c, B, tbase);
+    if constexpr (REAL) {
+        X += row0 + (uint32_t)lane;
+        if (count == (uint32_t)kTile) {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) X[r * 64] = z[r];
+        } else {
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
+                if (row0 + (uint32_t)(r * 64 + lane) < count) X[r * 64] = z[r];
+        }
+    } else {
+        __shared__ __align__(16) T stage[kTile];
+        place_units(stage, row0, lane, pair_log, z);
+        __syncthreads();
+        tile_from_lds(X, stage, count, vec, tid);
+    }
+    if (tile == 0 && tid == 0) {
+        const uint32_t verdict = sel[c * 8 + 7];
+        if (verdict) atomicMax(status, verdict);
+    }
+}
+
+// Several peers' streams (receiver under an allgather: Sec. 4, implementation): the same, the units summed over the
+// peers in list order in registers, starting from zero, and stored once.  Header verdicts at verd[peer * C + chunk].
+// Bound by instruction issue (two thirds of the vector slots).  Fetching the next peer's codes before unpacking this
+// one's changed nothing.  Measured, eight peers of 62 M samples, half of the bins kept as 8-bit codes: 354 -> 181 us.
+template <int NL>
+__global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npeers, size_t S, uint32_t B, uint32_t W, int bits,
+                                                     int m, uint32_t Tn, size_t C, const uint32_t* __restrict__ gprefix,
+                                                     const uint32_t* __restrict__ verd, uint32_t* __restrict__ status,
+                                                     float2* __restrict__ spec, uint32_t sstride, bool vec, int pair_log)
+{
+    __shared__ __align__(16) uint8_t windows[NL ? 4 * kWindow<NL> : 16];
+    __shared__ __align__(16) float2 stage[kTile];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const size_t c = blockIdx.x / Tn;
+    const uint32_t tile = blockIdx.x % Tn, tbase = tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
+    const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
+    uint8_t* window = windows + (NL ? wave * kWindow<NL> : 0);
+    float2 acc[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) acc[r] = make_float2(0.f, 0.f);
+    for (uint32_t p = 0; p < npeers; ++p) {
+        const uint8_t* record = recs.p[p] + c * S;
+        WaveCodes<NL> wc;
+        fetch_codes<NL, 2>(record, S, W, tile * (kTile / 32 / GROUP_WORDS) + wave, bits, gprefix + (p * C + c) * G, lane, wc);
+        unpack_codes<NL, false>(wc, record, S, W, bits, 23 - m, lane, window, [&](int r, const float2& v) {
+            acc[r] = make_float2(acc[r].x + v.x, acc[r].y + v.y);
+        });
+    }
+    place_units(stage, row0, lane, pair_log, acc);
+    __syncthreads();
+    tile_from_lds(spec + c * (size_t)sstride + tbase, stage, units_in_tile<false>(0, c, B, tbase), vec, tid);
+    if (tile == 0 && (uint32_t)tid < npeers) {
+        const uint32_t verdict = verd[(size_t)tid * C + c];
+        if (verdict) atomicMax(status, verdict);
     }
 }
 
@@ -1438,63 +1291,38 @@ static hipError_t launch_decode_kernel(const PeerList& recs, uint32_t npeers, co
                                        hipStream_t s)
 {
     const uint32_t B = codec_bins(a.L, a.time_domain), W = (B + 31) / 32, Tn = codec_tiles(a.L, a.time_domain);
-    // persistent grid: about two rounds of the workgroups a chip holds at once (six to eight per compute unit);
-    // measured best at 4096 (2048: +10 %, one workgroup per tile: +8 %)
-    const uint32_t total = (uint32_t)(a.C * Tn);
-    const uint32_t grid = total < 4096u ? total : 4096u;
-#define FFTSP_DECODE(NL, VEC)                                                                                      \
-    do {                                                                                                           \
-        if (peers_layout)                                                                                          \
-            FFTSP_LAUNCH("decode", (k_decode_peers<NL, VEC>), dim3(grid), dim3(NT), 0, s, recs, npeers, a.S, B, W,  \
-                         a.k, a.bits, a.m, Tn, total, a.C, gprefix, verd, status,                                  \
-                         reinterpret_cast<float2*>(spec), a.sstride, a.pair_log);                                  \
-        else if (a.tab)                                                                                            \
-            FFTSP_LAUNCH("decode", (k_decode<NL, VEC, true, false, false>), dim3(grid), dim3(NT), 0, s, recs.p[0], \
-                         a.S, B, W, a.k, a.bits, a.m, Tn, total, a.C, gprefix, verd, status,                       \
-                         reinterpret_cast<float2*>(spec), a.sstride, a.pair_log, table_arg<true>(a.tab), a.n);     \
-        else if (a.half)                                                                                           \
-            FFTSP_LAUNCH("decode", (k_decode<NL, VEC, false, false, true>), dim3(grid), dim3(NT), 0, s, recs.p[0], \
-                         a.S, B, W, a.k, a.bits, a.m, Tn, total, a.C, gprefix, verd, status,                       \
-                         reinterpret_cast<uint32_t*>(spec), a.sstride, a.pair_log, table_arg<false>(a.tab), a.n);  \
-        else                                                                                                       \
-            FFTSP_LAUNCH("decode", (k_decode<NL, VEC, false, false, false>), dim3(grid), dim3(NT), 0, s,           \
-                         recs.p[0], a.S, B, W, a.k, a.bits, a.m, Tn, total, a.C, gprefix, verd, status,            \
-                         reinterpret_cast<float2*>(spec), a.sstride, a.pair_log, table_arg<false>(a.tab), a.n);    \
-    } while (0)
+    const dim3 grid((unsigned)(a.C * Tn));
     if (a.half && (peers_layout || a.tab || a.time_domain)) return hipErrorInvalidValue;
-    if (a.time_domain) {
-        // one code per sample: a wave's 512 samples are at most 1 KiB of codes up to 16 bits, 2 KiB at 32
-        if (peers_layout || a.tab || a.pair_log) return hipErrorInvalidValue;
-        const bool vec16 = (reinterpret_cast<uintptr_t>(spec) & 15u) == 0;
-#define FFTSP_DECODE_REAL(NL, VEC)                                                                                 \
-    FFTSP_LAUNCH("decode", (k_decode<NL, VEC, false, true, false>), dim3(grid), dim3(NT), 0, s, recs.p[0], a.S, B, W, \
-                 a.k, a.bits, a.m, Tn, total, a.C, gprefix, verd, status, spec, a.sstride, 0,                      \
-                 table_arg<false>(nullptr), a.n)
-        if (a.bits <= 16) {
-            if (vec16)
-                FFTSP_DECODE_REAL(1, true);
-            else
-                FFTSP_DECODE_REAL(1, false);
-        } else {
-            if (vec16)
-                FFTSP_DECODE_REAL(2, true);
-            else
-                FFTSP_DECODE_REAL(2, false);
-        }
-#undef FFTSP_DECODE_REAL
-        return hipGetLastError();
-    }
+    if (a.time_domain && (peers_layout || a.tab || a.pair_log)) return hipErrorInvalidValue;
     const bool vec = a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0;
-    // code widths are 3..16 or 32 bits
-    const int nl = a.bits <= 8 ? 1 : a.bits <= 16 ? 2 : 4;
-    switch (nl * 2 + (vec ? 1 : 0)) {
-        case 2: FFTSP_DECODE(1, false); break;
-        case 3: FFTSP_DECODE(1, true); break;
-        case 4: FFTSP_DECODE(2, false); break;
-        case 5: FFTSP_DECODE(2, true); break;
-        case 8: FFTSP_DECODE(4, false); break;
-        default: FFTSP_DECODE(4, true); break;
-    }
+#define FFTSP_DECODE_AS(NL, TABLE, REAL, HALF, T)                                                                      \
+    FFTSP_LAUNCH("decode", (k_decode<NL, TABLE, REAL, HALF>), grid, dim3(NT), 0, s, recs.p[0], a.S, B, W, a.bits, a.m, \
+                 Tn, gprefix, verd, status, reinterpret_cast<T*>(spec), a.sstride, vec, a.pair_log,                    \
+                 table_arg<TABLE>(a.tab), a.n)
+#define FFTSP_DECODE(NL)                                                                                               \
+    do {                                                                                                               \
+        if (peers_layout)                                                                                              \
+            FFTSP_LAUNCH("decode", k_decode_peers<NL>, grid, dim3(NT), 0, s, recs, npeers, a.S, B, W, a.bits, a.m, Tn, \
+                         a.C, gprefix, verd, status, reinterpret_cast<float2*>(spec), a.sstride, vec, a.pair_log);     \
+        else if (a.tab)                                                                                                \
+            FFTSP_DECODE_AS(NL, true, false, false, float2);                                                           \
+        else if (a.half)                                                                                               \
+            FFTSP_DECODE_AS(NL, false, false, true, uint32_t);                                                         \
+        else                                                                                                           \
+            FFTSP_DECODE_AS(NL, false, false, false, float2);                                                          \
+    } while (0)
+    // code widths are 3..16 or 32 bits; the codes of a wave's 512 units are at most 1 KiB for 16 bits a unit, else 2 KiB
+    if (a.time_domain && a.bits <= 16)
+        FFTSP_DECODE_AS(1, false, true, false, float);
+    else if (a.time_domain)
+        FFTSP_DECODE_AS(0, false, true, false, float);
+    else if (a.bits <= 8)
+        FFTSP_DECODE(1);
+    else if (a.bits <= 16)
+        FFTSP_DECODE(2);
+    else
+        FFTSP_DECODE(0);
+#undef FFTSP_DECODE_AS
 #undef FFTSP_DECODE
     return hipGetLastError();
 }

@@ -118,6 +118,14 @@ __device__ __forceinline__ uint32_t dequantize(uint32_t code, uint32_t pbase, in
     return c ? v : 0u;
 }
 
+// The same for the code at bit `at` of a word, up to 16 bits wide; base = (pbase - 1) << shift.
+__device__ __forceinline__ uint32_t dequantize_field(uint32_t word, uint32_t at, uint32_t bits, uint32_t base, int shift)
+{
+    const uint32_t c = __builtin_amdgcn_ubfe(word, at, bits - 1u);
+    const uint32_t v = (((c << shift) + base) & 0x7FFFFFFFu) | ((word << (32u - bits - at)) & 0x80000000u);
+    return c ? v : 0u;
+}
+
 constexpr uint32_t kListCap = 256;  // keys of the threshold's bucket that are finished from a list
 
 // The `need`-th largest of `count` listed keys that share all bits above `low`: tau grows bit by bit, a ballot counts
