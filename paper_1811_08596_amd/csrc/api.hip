@@ -229,6 +229,14 @@ int apply_quantizer(Plan* p, const fftsp_quantizer* q, uint32_t* static_vmax)
     return FFTSP_OK;
 }
 
+// All chunks of one stream to units; verdicts go where the sender would keep its tile prefixes.
+hipError_t decode_stream(const Plan& p, const uint8_t* in, const CodecArgs& a, float* units, uint8_t* ws, hipStream_t s)
+{
+    if (p.C > 0xffffffffu || p.ws.tscan / 4 > 0xffffffffu) return hipErrorInvalidValue;
+    const StatusNote note{(uint32_t)p.C, (uint32_t)(p.ws.tscan / 4)};
+    return launch_decode(in, in + kStreamHeader, a, units, ws, p.ws, 1, reinterpret_cast<uint32_t*>(ws + p.ws.tscan), &note, s);
+}
+
 // The receiver for chunks that fit one workgroup; its per-record verdicts go to the workspace at byte offset `verd`.
 hipError_t decompress_chunks(const Plan& p, const PeerList& streams, int npeers, int plain, const CodecArgs& a, float* out,
                              float gain, uint8_t* ws, size_t verd, Tables t, hipStream_t s)
@@ -253,9 +261,9 @@ hipError_t inverse_of_decoded(const Plan& p, const float* spec, uint32_t sstride
                                           gain, ctl, knobs, s);
         if (e != hipSuccess) return e;
         // stand-by: the per-pass kernels redo the transform if the fused kernel gave up
-        return launch_irfft(spec, sstride, p.n, p.logL, p.C, out, mid, t, 1, gain, nullptr, s, ctl + kCtlGaveUpWord);
+        return launch_irfft(spec, sstride, p.n, p.logL, p.C, out, mid, t, 1, gain, s, ctl + kCtlGaveUpWord);
     }
-    return launch_irfft(spec, sstride, p.n, p.logL, p.C, out, mid, t, pair_log != 0, gain, nullptr, s);
+    return launch_irfft(spec, sstride, p.n, p.logL, p.C, out, mid, t, pair_log != 0, gain, s);
 }
 
 }  // namespace
@@ -304,7 +312,7 @@ int fftsp_rfft(const float* d_grad, size_t n, uint32_t chunk_len, float* d_spec,
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (p.logL <= kChunkMaxLogL) return hip_status(launch_chunk_rfft(d_grad, n, p.logL, p.C, d_spec, p.L / 2 + 1, t, s));
     return hip_status(launch_rfft(d_grad, n, p.logL, p.C, d_spec, p.L / 2 + 1, reinterpret_cast<float2*>(ws + p.ws.mid), t,
-                                  nullptr, nullptr, 0, 0, nullptr, nullptr, s));
+                                  nullptr, nullptr, 0, 0, nullptr, s));
 }
 
 int fftsp_irfft(const float* d_spec, size_t n, uint32_t chunk_len, float* d_grad_out, void* d_workspace,
@@ -323,7 +331,7 @@ int fftsp_irfft(const float* d_spec, size_t n, uint32_t chunk_len, float* d_grad
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (p.logL <= kChunkMaxLogL) return hip_status(launch_chunk_irfft(d_spec, p.L / 2 + 1, n, p.logL, p.C, d_grad_out, t, s));
     return hip_status(launch_irfft(d_spec, p.L / 2 + 1, n, p.logL, p.C, d_grad_out, reinterpret_cast<float2*>(ws + p.ws.mid), t,
-                                   0, 1.0f, nullptr, s));
+                                   0, 1.0f, s));
 }
 
 int fftsp_encode_spectrum_q(const float* d_spec, size_t n, uint32_t chunk_len, float theta, int bits, void* d_packed,
@@ -370,7 +378,7 @@ int fftsp_decode_spectrum_q(const void* d_packed, size_t packed_bytes, size_t n,
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
     const uint8_t* in = static_cast<const uint8_t*>(d_packed);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    hipError_t e = launch_decode(in, in + kStreamHeader, codec_args(p, theta), d_spec, ws, p.ws, 1, 1, s);
+    hipError_t e = decode_stream(p, in, codec_args(p, theta), d_spec, ws, s);
     return hip_status(e);
 }
 
@@ -421,10 +429,10 @@ static int compress_impl(const float* d_grad, size_t n, uint32_t chunk_len, floa
                                   knobs, s);
         if (e == hipSuccess)
             e = launch_rfft(d_grad, n, p.logL, p.C, spec, a.sstride, mid, t, hist, hist, p.C * kHistBins, 1,
-                            &a.pair_log, nullptr, s, ctl + kCtlGaveUpWord);
+                            &a.pair_log, s, ctl + kCtlGaveUpWord);
     } else {
         e = launch_rfft(d_grad, n, p.logL, p.C, spec, a.sstride, mid, t, hist, ctl,
-                        (p.ws.hist - p.ws.status) / 4 + p.C * kHistBins, 1, &a.pair_log, nullptr, s);
+                        (p.ws.hist - p.ws.status) / 4 + p.C * kHistBins, 1, &a.pair_log, s);
     }
     if (e == hipSuccess)
         e = launch_encode(spec, a, out, out + kStreamHeader, ws, p.ws, 1, s);
@@ -513,7 +521,7 @@ int fftsp_decompress_q(const void* d_packed, size_t packed_bytes, float* d_grad_
     }
     a.sstride = padded_bins(p.L);
     a.pair_log = fft_pair_log(p.logL);
-    hipError_t e = launch_decode(in, in + kStreamHeader, a, spec, ws, p.ws, 1, 1, s);
+    hipError_t e = decode_stream(p, in, a, spec, ws, s);
     if (e == hipSuccess) e = inverse_of_decoded(p, spec, a.sstride, a.pair_log, d_grad_out, ws, t, 1.0f, s);
     return hip_status(e);
 }
@@ -657,7 +665,7 @@ int fftsp_decompress_h(const void* d_packed, size_t packed_bytes, float* d_grad_
     a.pair_log = fft_pair_log(p.logL);
     a.half = 1;
     a.hdr_scale = scale_log2;
-    hipError_t e = launch_decode(in, in + kStreamHeader, a, reinterpret_cast<float*>(ws + p.ws.spec), ws, p.ws, 1, 1, s);
+    hipError_t e = decode_stream(p, in, a, reinterpret_cast<float*>(ws + p.ws.spec), ws, s);
     if (e == hipSuccess)
         e = launch_irfft_half(ws + p.ws.spec, a.sstride, n, p.logL, p.C, d_grad_out, ws + p.ws.mid, t,
                               std::ldexp(1.0f, -scale_log2), s);
@@ -720,8 +728,7 @@ int fftsp_topk_decompress(const void* d_packed, size_t packed_bytes, float* d_gr
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
     const uint8_t* in = static_cast<const uint8_t*>(d_packed);
     const CodecArgs a = topk_args(p, theta);
-    return hip_status(launch_decode(in, in + kStreamHeader, a, d_grad_out, ws, p.ws, 1, 1,
-                                    reinterpret_cast<hipStream_t>(stream)));
+    return hip_status(decode_stream(p, in, a, d_grad_out, ws, reinterpret_cast<hipStream_t>(stream)));
 }
 
 /* ---------------- per-tensor variant: one single-chunk codec per segment ---------------- */
@@ -747,22 +754,9 @@ size_t fftsp_packed_bytes_segments(const size_t* seg_offsets, int nseg, float th
     return total;
 }
 
-// Tensors that pad to the same chunk length L run as the chunks of one launch set, at most this many at a time
-// (the per-launch table holds kMaxTableChunks; long chunks are also capped at 2^26 samples per launch set so that the
-// workspace stays a small multiple of the largest tensor).
-static size_t batch_cap(uint32_t L)
-{
-    const size_t by_size = ((size_t)1 << 26) / L;
-    const size_t cap = by_size < (size_t)kMaxTableChunks ? by_size : (size_t)kMaxTableChunks;
-    return cap < 1 ? 1 : cap;
-}
-
-// One launch set of the per-tensor path: `count` tensors of padded length L.
-struct SegBatch {
-    uint32_t L;
-    size_t count;
-    ChunkTable tab;
-};
+// The longer tensors run in launch sets of at most kMaxLongTensors (the per-launch table), together at most 2^26 padded
+// samples, so that the workspace stays a small multiple of the largest tensor.
+constexpr uint32_t kMaxLongUnits = (1u << 26) >> (kLongUnitLog + 1);
 
 // A launch of tensors that fit one workgroup each (chunk.h).
 struct TensorLaunch {
@@ -772,11 +766,11 @@ struct TensorLaunch {
 };
 
 // How a per-tensor call is launched: the tensors of up to 2^kChunkMaxLogL samples in as few launches as the table
-// allows, longest first; the longer ones grouped by padded length (ascending), every group cut into launch sets.
+// allows, longest first; the longer ones in launch sets of any lengths, shortest first.
 // Records keep tensor order in the stream: tensor i's record starts rec_off[i] bytes after the stream header.
 struct SegmentPlan {
     std::vector<TensorLaunch> shorts;
-    std::vector<SegBatch> batches;
+    std::vector<LongBatch> longs;
     size_t short_count = 0;
 };
 static SegmentPlan plan_segments(const size_t* off, int nseg, float theta, int bits, bool with_tables)
@@ -827,85 +821,54 @@ static SegmentPlan plan_segments(const size_t* off, int nseg, float theta, int b
         }
     }
     for (size_t j = first_long; j < order.size(); ++j) {
-        const int i = order[j];
-        if (out.batches.empty() || out.batches.back().L != len[i] || out.batches.back().count == batch_cap(len[i])) {
-            out.batches.emplace_back();
-            out.batches.back().L = len[i];
-            out.batches.back().count = 0;
+        const int i = order[j], logM = log2_exact(len[i]) - 1;
+        const uint32_t units = 1u << (logM - kLongUnitLog);
+        if (out.longs.empty() || out.longs.back().count == (uint32_t)kMaxLongTensors || out.longs.back().units + units > kMaxLongUnits) {
+            out.longs.emplace_back();
+            out.longs.back().count = out.longs.back().units = 0;
         }
-        SegBatch& b = out.batches.back();
-        if (with_tables) {
-            b.tab.goff[b.count] = off[i];
-            b.tab.glen[b.count] = (uint32_t)(off[i + 1] - off[i]);
-            b.tab.roff[b.count] = rec_off[i];
-        }
-        ++b.count;
+        LongBatch& b = out.longs.back();
+        LongTensor& x = b.tab.t[b.count];
+        x.goff = off[i];
+        x.roff = rec_off[i];
+        x.glen = (uint32_t)(off[i + 1] - off[i]);
+        x.kept = with_tables ? kept(len[i], theta) : 0u;
+        x.stride = with_tables ? (uint32_t)record_stride(len[i], x.kept, bits) : 0u;
+        x.base = (uint16_t)b.units;
+        x.logM = (uint8_t)logM;
+        x.pad = 0;
+        b.tab.tiles.at[b.count] = (uint16_t)long_tile(x, b.count);
+        b.tab.tiles.first = 0;
+        b.units += units;
+        b.tab.tiles.count = ++b.count;
     }
     return out;
 }
 
-// The launch sets of the longer tensors are independent chains of short kernels, so they
-// run on up to kSegLanes streams at once: the caller's and streams of the library's own that fork from and join
-// back into the caller's through events.  The call stays one unit of work on the caller's stream and can be
-// captured into a graph.  Every lane works in a workspace region of its own, sized for the largest launch set.
-constexpr int kSegLanes = 4;
-struct SegLanes {
+// The tensors that fit a workgroup each and the longer ones are independent, so the former run on a stream of the library's
+// own that forks from and joins back into the caller's through events.  The call stays one unit of work on the caller's
+// stream and can be captured into a graph.
+struct SideStream {
     bool ready = false;
-    hipStream_t s[kSegLanes - 1];
-    hipEvent_t fork, join[kSegLanes - 1];
+    hipStream_t s;
+    hipEvent_t fork, join;
 };
-static SegLanes g_seg_lanes[64];
-static std::mutex g_seg_mutex;  // held while a call enqueues: the events are shared by all calls on a device
+static SideStream g_side[64];
+static std::mutex g_side_mutex;  // held while a call enqueues: the events are shared by all calls on a device
 
-static size_t segment_region_bytes(const std::vector<SegBatch>& batches)
-{
-    size_t best = 0;
-    for (const SegBatch& b : batches) {
-        const size_t t = make_workspace(b.count, b.L).total;
-        best = t > best ? t : best;
-    }
-    return align256(best);
-}
-
-static int segment_lanes(size_t nbatches)
-{
-    return (int)(nbatches < (size_t)kSegLanes ? nbatches : (size_t)kSegLanes);
-}
-
-// where the short tensors' verdicts are: behind the lanes' regions, or behind a control block of their own
+// where the tensors' verdicts are: behind the longer ones' workspace, or behind a control block of their own
 static size_t segment_verdicts(const SegmentPlan& plan)
 {
-    const size_t lanes = (size_t)segment_lanes(plan.batches.size()) * segment_region_bytes(plan.batches);
-    return lanes > kControlBytes ? lanes : kControlBytes;
+    size_t most = kControlBytes;
+    for (const LongBatch& b : plan.longs) most = std::max(most, make_long_workspace(b).total);
+    return align256(most);
 }
 
 size_t fftsp_workspace_bytes_segments(const size_t* seg_offsets, int nseg, int bits)
 {
     if (segments_ok(seg_offsets, nseg) != FFTSP_OK || mantissa(bits) < 0) return 0;
     const SegmentPlan plan = plan_segments(seg_offsets, nseg, 0.5f, bits, false);
-    return segment_verdicts(plan) + align256(plan.short_count * 4);
-}
-
-// Heaviest launch set first, each onto the lane with the least work so far (work = samples); lane 0 is the caller's
-// stream.  Returns the lane of every launch set.
-static std::vector<int> assign_lanes(const std::vector<SegBatch>& batches, int lanes)
-{
-    std::vector<size_t> order(batches.size());
-    for (size_t i = 0; i < order.size(); ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) {
-        return batches[a].count * (size_t)batches[a].L > batches[b].count * (size_t)batches[b].L;
-    });
-    std::vector<size_t> load((size_t)lanes, 0);
-    std::vector<int> lane_of(batches.size(), 0);
-    for (size_t i : order) {
-        int best = 0;
-        for (int l = 1; l < lanes; ++l)
-            if (load[(size_t)l] < load[(size_t)best]) best = l;
-        lane_of[i] = best;
-        // a launch set costs its samples plus a fixed price for its ten or so launches
-        load[(size_t)best] += batches[i].count * (size_t)batches[i].L + ((size_t)1 << 18);
-    }
-    return lane_of;
+    return segment_verdicts(plan) + align256((size_t)nseg * 4);
 }
 
 }  // extern "C" (a template cannot have C linkage)
@@ -921,97 +884,71 @@ static hipError_t capture_of(hipStream_t s, unsigned long long* id)
     return hipSuccess;
 }
 
-static void destroy_lanes(SegLanes& ln, int streams, int joins, bool fork)
-{
-    for (int i = 0; i < streams; ++i) (void)hipStreamDestroy(ln.s[i]);
-    for (int i = 0; i < joins; ++i) (void)hipEventDestroy(ln.join[i]);
-    if (fork) (void)hipEventDestroy(ln.fork);
-}
-
-// body(launch set index, stream, lane) enqueues one launch set; sets of one lane run in index order on its stream.
-// The side streams belong to the device, not to a caller.  A caller that records its stream into a graph pulls them
-// into that capture until it ends, so a call falls back to the caller's stream alone (lane 0, the same result,
-// the launch sets one after the other) when a side stream is being recorded into a capture other than the
-// caller's own, and when the side streams do not exist yet and the caller is recording (nothing is created while a
-// capture is open).
-template <typename F>
-static hipError_t run_on_lanes(hipStream_t user, const std::vector<int>& lane_of, int lanes, F&& body)
+// side(stream) and main(stream) enqueue independent work; main's stream is the caller's.
+// The side stream belongs to the device, not to a caller.  A caller that records its stream into a graph pulls it into that
+// capture until it ends, so a call falls back to the caller's stream alone (the same result, one after the other) when the
+// side stream is being recorded into a capture other than the caller's own, and when it does not exist yet and the caller is
+// recording (nothing is created while a capture is open).
+template <typename S, typename M>
+static hipError_t run_beside(hipStream_t user, S&& side, M&& main)
 {
     auto serial = [&]() {
-        for (size_t bi = 0; bi < lane_of.size(); ++bi) {
-            const hipError_t e = body(bi, user, 0);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
+        const hipError_t e = side(user);
+        return e == hipSuccess ? main(user) : e;
     };
-    if (lanes <= 1) return serial();
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(g_seg_mutex);
-    SegLanes& ln = g_seg_lanes[dev];
-    unsigned long long mine = 0;
+    std::lock_guard<std::mutex> lock(g_side_mutex);
+    SideStream& st = g_side[dev];
+    unsigned long long mine = 0, theirs = 0;
     e = capture_of(user, &mine);
     if (e != hipSuccess) return e;
-    if (!ln.ready) {
+    if (!st.ready) {
         if (mine != 0) return serial();
-        int streams = 0, joins = 0;
-        for (int i = 0; i < kSegLanes - 1 && e == hipSuccess; ++i) {
-            e = hipStreamCreateWithFlags(&ln.s[i], hipStreamNonBlocking);  // default priority
-            if (e != hipSuccess) break;
-            ++streams;
-            e = hipEventCreateWithFlags(&ln.join[i], hipEventDisableTiming);
-            if (e == hipSuccess) ++joins;
+        e = hipStreamCreateWithFlags(&st.s, hipStreamNonBlocking);  // default priority
+        if (e != hipSuccess) return e;
+        e = hipEventCreateWithFlags(&st.fork, hipEventDisableTiming);
+        if (e == hipSuccess) {
+            e = hipEventCreateWithFlags(&st.join, hipEventDisableTiming);
+            if (e != hipSuccess) (void)hipEventDestroy(st.fork);
         }
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&ln.fork, hipEventDisableTiming);
-        if (e != hipSuccess) {
-            destroy_lanes(ln, streams, joins, false);  // the next call starts over
+        if (e != hipSuccess) {  // the next call starts over
+            (void)hipStreamDestroy(st.s);
             return e;
         }
-        ln.ready = true;
+        st.ready = true;
     }
-    for (int l = 1; l < lanes; ++l) {
-        unsigned long long theirs = 0;
-        e = capture_of(ln.s[l - 1], &theirs);
-        if (e != hipSuccess) return e;
-        if (theirs != 0 && theirs != mine) return serial();
-    }
-    e = hipEventRecord(ln.fork, user);
-    for (int l = 1; l < lanes && e == hipSuccess; ++l) e = hipStreamWaitEvent(ln.s[l - 1], ln.fork, 0);
+    e = capture_of(st.s, &theirs);
     if (e != hipSuccess) return e;
-    // every lane that was forked is joined again, whatever happens in between
-    hipError_t first = hipSuccess;
-    for (int l = 0; l < lanes; ++l) {
-        hipStream_t st = l == 0 ? user : ln.s[l - 1];
-        for (size_t bi = 0; bi < lane_of.size() && first == hipSuccess; ++bi)
-            if (lane_of[bi] == l) first = body(bi, st, l);
-        if (l > 0) {
-            hipError_t j = hipEventRecord(ln.join[l - 1], st);
-            if (j == hipSuccess) j = hipStreamWaitEvent(user, ln.join[l - 1], 0);
-            if (first == hipSuccess) first = j;
-        }
-    }
-    return first;
+    if (theirs != 0 && theirs != mine) return serial();
+    e = hipEventRecord(st.fork, user);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st.s, st.fork, 0);
+    if (e != hipSuccess) return e;
+    // what was forked is joined again, whatever happens in between
+    hipError_t first = side(st.s);
+    if (first == hipSuccess) first = main(user);
+    e = hipEventRecord(st.join, st.s);
+    if (e == hipSuccess) e = hipStreamWaitEvent(user, st.join, 0);
+    return first == hipSuccess ? e : first;
+}
+
+// Beside each other only where the longer tensors take a while: the event calls cost the host 46 us a call (sender and
+// receiver 92), which a short chain of kernels does not hide.  ResNet-50 (34 M padded samples in longer tensors): 512 -> 471
+// us; ResNet-20 (0.2 M): 111 -> 133.  Per-kernel timing wants one chain.
+constexpr uint32_t kSideUnits = 1u << (23 - kLongUnitLog);
+template <typename S, typename M>
+static hipError_t run_segments(const SegmentPlan& plan, hipStream_t user, S&& side, M&& main)
+{
+    uint32_t units = 0;
+    for (const LongBatch& b : plan.longs) units += b.units;
+    if (!plan.shorts.empty() && units >= kSideUnits && !prof::enabled()) return run_beside(user, side, main);
+    const hipError_t e = side(user);
+    return e == hipSuccess ? main(user) : e;
 }
 
 extern "C" {
-
-// a lane's workspace: the usual layout, moved to the lane's region
-static Workspace region_workspace(size_t count, uint32_t L, size_t region_offset)
-{
-    Workspace w = make_workspace(count, L);
-    w.status += region_offset;
-    w.hist += region_offset;
-    w.sel += region_offset;
-    w.tinfo += region_offset;
-    w.tscan += region_offset;
-    w.cand += region_offset;
-    w.prefix += region_offset;
-    w.spec += region_offset;
-    w.mid += region_offset;
-    return w;
-}
 
 // the stream header's part of the arguments
 static CodecArgs segment_header(const size_t* seg_offsets, int nseg, float theta, int bits, int m)
@@ -1028,16 +965,11 @@ static CodecArgs segment_header(const size_t* seg_offsets, int nseg, float theta
     return a;
 }
 
-static CodecArgs segment_args(const SegBatch& b, const size_t* seg_offsets, int nseg, float theta, int bits, int m)
+static CodecArgs segment_args(const LongBatch& b, const size_t* seg_offsets, int nseg, float theta, int bits, int m)
 {
     CodecArgs a = segment_header(seg_offsets, nseg, theta, bits, m);
     a.C = b.count;
-    a.L = b.L;
-    a.k = kept(b.L, theta);
-    a.S = record_stride(b.L, a.k, bits);
-    a.word3 = b.L;
-    a.sstride = padded_bins(b.L);
-    a.tab = &b.tab;
+    a.tab = &b;
     return a;
 }
 
@@ -1059,33 +991,32 @@ int fftsp_compress_segments(const float* d_grad, const size_t* seg_offsets, int 
     uint8_t* out = static_cast<uint8_t*>(d_packed);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const SegmentPlan plan = plan_segments(seg_offsets, nseg, theta, bits, true);
-    const std::vector<SegBatch>& batches = plan.batches;
-    const size_t region = segment_region_bytes(batches);
-    const int lanes = prof::enabled() ? 1 : segment_lanes(batches.size());  // per-kernel timing wants one chain
-    const std::vector<int> lane_of = assign_lanes(batches, lanes);
-    hipError_t e = hipSuccess;
-    for (size_t i = 0; i < plan.shorts.size() && e == hipSuccess; ++i) {
-        CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
-        hdr.write_header = i == 0;
-        // the longer tensors' kernels clear the control block; without any, the first of these launches does
-        e = launch_tensors_compress(d_grad, plan.shorts[i].tab, plan.shorts[i].pieces, plan.shorts[i].top_logL,
-                                    QuantizerArgs{bits, m}, hdr, out, out + kStreamHeader,
-                                    i == 0 && batches.empty() ? reinterpret_cast<uint32_t*>(ws) : nullptr, t, s);
-    }
-    if (e == hipSuccess && !batches.empty())
-        e = run_on_lanes(s, lane_of, lanes, [&](size_t bi, hipStream_t st, int lane) {
-            const SegBatch& b = batches[bi];
-            // every lane clears and uses the status words and histograms of its own region; nothing on the sender
-            // raises a status, and the caller reads the first region's word
-            const Workspace w = region_workspace(b.count, b.L, (size_t)lane * region);
-            CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
-            a.write_header = bi == 0 && plan.shorts.empty();
-            float* spec = reinterpret_cast<float*>(ws + w.spec);
-            hipError_t pe = launch_rfft(d_grad, 0, log2_exact(b.L), b.count, spec, a.sstride,
-                                        reinterpret_cast<float2*>(ws + w.mid), t, reinterpret_cast<uint32_t*>(ws + w.hist),
-                                        reinterpret_cast<uint32_t*>(ws + w.status),
-                                        (w.hist - w.status) / 4 + b.count * (size_t)kHistBins, 1, &a.pair_log, &b.tab, st);
-            if (pe == hipSuccess) pe = launch_encode(spec, a, out, out + kStreamHeader, ws, w, 1, st);
+    const hipError_t e = run_segments(
+        plan, s,
+        [&](hipStream_t st) {
+            hipError_t pe = hipSuccess;
+            for (size_t i = 0; i < plan.shorts.size() && pe == hipSuccess; ++i) {
+                CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
+                hdr.write_header = i == 0;
+                // the longer tensors' kernels clear the control block; without any, the first of these launches does
+                pe = launch_tensors_compress(d_grad, plan.shorts[i].tab, plan.shorts[i].pieces, plan.shorts[i].top_logL,
+                                             QuantizerArgs{bits, m}, hdr, out, out + kStreamHeader,
+                                             i == 0 && plan.longs.empty() ? reinterpret_cast<uint32_t*>(ws) : nullptr, t, st);
+            }
+            return pe;
+        },
+        [&](hipStream_t st) {
+            hipError_t pe = hipSuccess;
+            for (size_t i = 0; i < plan.longs.size() && pe == hipSuccess; ++i) {
+                const LongBatch& b = plan.longs[i];
+                const Workspace w = make_long_workspace(b);
+                CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
+                a.write_header = i == 0 && plan.shorts.empty();
+                float2* spec = reinterpret_cast<float2*>(ws + w.spec);
+                pe = launch_rfft_long(d_grad, b, spec, reinterpret_cast<float2*>(ws + w.mid), t, reinterpret_cast<uint32_t*>(ws + w.hist),
+                                      reinterpret_cast<uint32_t*>(ws + w.status), (w.hist - w.status) / 4 + b.count * (size_t)kHistBins, st);
+                if (pe == hipSuccess) pe = launch_encode(reinterpret_cast<float*>(spec), a, out, out + kStreamHeader, ws, w, 1, st);
+            }
             return pe;
         });
     return hip_status(e);
@@ -1110,36 +1041,37 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
     const uint8_t* in = static_cast<const uint8_t*>(d_packed);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const SegmentPlan plan = plan_segments(seg_offsets, nseg, theta, bits, true);
-    const std::vector<SegBatch>& batches = plan.batches;
-    const size_t region = segment_region_bytes(batches);
-    const int lanes = prof::enabled() ? 1 : segment_lanes(batches.size());
-    const std::vector<int> lane_of = assign_lanes(batches, lanes);
-    // every launch set of longer tensors raises the one status word at the start of the workspace, from whatever lane
-    // it runs on: it is cleared here, before the lanes fork.  The short ones leave verdicts.
-    hipError_t e = hipSuccess;
-    if (!batches.empty()) e = launch_clear_status(ws, make_workspace(1, 32), s);
     const size_t verd = segment_verdicts(plan);
     if (verd / 4 > 0xffffffffu) return FFTSP_EHIP;
-    for (size_t i = 0; i < plan.shorts.size() && e == hipSuccess; ++i) {
-        CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
-        hdr.write_header = i == 0;
-        const StatusNote note{i == 0 ? (uint32_t)plan.short_count : 0u, (uint32_t)(verd / 4)};
-        e = launch_tensors_decompress(in, plan.shorts[i].tab, plan.shorts[i].pieces, plan.shorts[i].top_logL,
-                                      QuantizerArgs{bits, m}, hdr, d_grad_out, reinterpret_cast<uint32_t*>(ws), note,
-                                      batches.empty(), reinterpret_cast<uint32_t*>(ws + verd), t, s);
-    }
-    if (e == hipSuccess && !batches.empty())
-        e = run_on_lanes(s, lane_of, lanes, [&](size_t bi, hipStream_t st, int lane) {
-            const SegBatch& b = batches[bi];
-            Workspace w = region_workspace(b.count, b.L, (size_t)lane * region);
-            w.status = 0;
-            CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
-            a.pair_log = fft_pair_log(log2_exact(b.L));
-            float* spec = reinterpret_cast<float*>(ws + w.spec);
-            hipError_t pe = launch_decode(in, in + kStreamHeader, a, spec, ws, w, bi == 0 && plan.shorts.empty(), 0, st);
-            if (pe == hipSuccess)
-                pe = launch_irfft(spec, a.sstride, 0, log2_exact(b.L), b.count, d_grad_out,
-                                  reinterpret_cast<float2*>(ws + w.mid), t, a.pair_log != 0, 1.0f, &b.tab, st);
+    uint32_t* verdicts = reinterpret_cast<uint32_t*>(ws + verd);
+    const StatusNote note{(uint32_t)nseg, (uint32_t)(verd / 4)};
+    const hipError_t e = run_segments(
+        plan, s,
+        [&](hipStream_t st) {
+            hipError_t pe = hipSuccess;
+            for (size_t i = 0; i < plan.shorts.size() && pe == hipSuccess; ++i) {
+                CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
+                hdr.write_header = i == 0;
+                pe = launch_tensors_decompress(in, plan.shorts[i].tab, plan.shorts[i].pieces, plan.shorts[i].top_logL,
+                                               QuantizerArgs{bits, m}, hdr, d_grad_out, reinterpret_cast<uint32_t*>(ws),
+                                               i == 0 ? note : StatusNote{0u, 0u}, 1, verdicts, t, st);
+            }
+            return pe;
+        },
+        [&](hipStream_t st) {
+            hipError_t pe = hipSuccess;
+            size_t done = plan.short_count;
+            for (size_t i = 0; i < plan.longs.size() && pe == hipSuccess; ++i) {
+                const LongBatch& b = plan.longs[i];
+                const Workspace w = make_long_workspace(b);
+                const bool leads = i == 0 && plan.shorts.empty();
+                const CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
+                float* spec = reinterpret_cast<float*>(ws + w.spec);
+                pe = launch_decode(in, in + kStreamHeader, a, spec, ws, w, leads, verdicts + done, leads ? &note : nullptr, st);
+                if (pe == hipSuccess)
+                    pe = launch_irfft_long(reinterpret_cast<float2*>(spec), b, d_grad_out, reinterpret_cast<float2*>(ws + w.mid), t, st);
+                done += b.count;
+            }
             return pe;
         });
     return hip_status(e);
@@ -1152,7 +1084,7 @@ int fftsp_device_status(const void* d_workspace, int* status_out)
     uint32_t v[5] = {};
     if (hipMemcpy(v, d_workspace, sizeof(v), hipMemcpyDeviceToHost) != hipSuccess) return FFTSP_EHIP;
     uint32_t worst = v[0];
-    if (v[4] == kStatusNoteMagic && v[2] > 0) {  // one verdict per record instead of the status word (chunk.h)
+    if (v[4] == kStatusNoteMagic && v[2] > 0) {  // one verdict per record
         std::vector<uint32_t> verdicts(v[2]);
         if (hipMemcpy(verdicts.data(), static_cast<const uint8_t*>(d_workspace) + (size_t)v[3] * 4, verdicts.size() * 4,
                       hipMemcpyDeviceToHost) != hipSuccess)

@@ -14,14 +14,6 @@ struct PackArgs {
     int bits, m;
 };
 
-// A launch that decodes every record in one go has no earlier kernel that could clear the status word before a record
-// raises it.  Such a launch stores one verdict per record instead, and this note in words 2..4 of the control block:
-// how many there are, where (in words from the workspace's start), and a magic word.  fftsp_device_status looks at both.
-struct StatusNote {
-    uint32_t count, offset;
-};
-constexpr uint32_t kStatusNoteMagic = 0x46535653u;
-
 // Sender.  ctl: the workspace's control block.
 hipError_t launch_chunk_compress(const float* in, size_t n, int logL, const CodecArgs& a, uint8_t* stream, uint8_t* records,
                                  uint32_t* ctl, Tables t, hipStream_t s);

@@ -16,6 +16,7 @@
 // quantizes and bit-packs.
 #include "codec_core.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace fftsp {
@@ -213,13 +214,56 @@ __device__ __forceinline__ uint32_t block_scan_incl_256(uint32_t v, uint32_t* tm
     return x + add;
 }
 
+// What a workgroup of the codec kernels works on: a chunk and one of its tiles.  Uniform launches: all chunks are alike, and
+// everything about them but the index comes with the launch.  Tables (per-tensor calls): looked up.
+struct Place {
+    uint32_t chunk, tile;        // tile: number within the chunk
+    uint32_t B, Tn, W, k;        // bins, tiles, bitmap words, kept bins of the chunk
+    uint32_t tile0, group0;      // the chunk's first tile and its first group of bitmap words, in the launch's work areas
+    size_t spec, record, S;      // its spectrum (in bins), its record (byte offset and size)
+    uint32_t word3;
+    int pair_log;
+};
+struct Shape {  // of a uniform launch
+    uint32_t B, Tn, W, k, sstride, word3;
+    size_t S;
+    int pair_log;
+};
+template <bool TABLE>
+__device__ __forceinline__ Place place_of(const Shape& u, const TableArg<TABLE>& tab, uint32_t chunk, uint32_t tile)
+{
+    if constexpr (TABLE) {
+        const LongTensor& x = tab.t.t[chunk];
+        const uint32_t M = 1u << x.logM;
+        return Place{chunk, tile, M + 1u, M / (uint32_t)kTile + 1u, M / 32u + 1u, x.kept, long_tile(x, chunk), long_group(x, chunk),
+                     long_spec(x, chunk), (size_t)x.roff, x.stride, 2u * M, long_pair_log(x)};
+    } else {
+        const uint32_t G = (u.W + 15u) / 16u;
+        return Place{chunk, tile, u.B, u.Tn, u.W, u.k, chunk * u.Tn, chunk * G, chunk * (size_t)u.sstride, chunk * u.S, u.S,
+                     u.word3, u.pair_log};
+    }
+}
+// a workgroup per tile
+template <bool TABLE>
+__device__ __forceinline__ Place place_of_tile(const Shape& u, const TableArg<TABLE>& tab)
+{
+    if constexpr (TABLE) {
+        const LongShare share = long_share(tab.t.tiles);
+        return place_of<TABLE>(u, tab, share.tensor, share.blk);
+    } else {
+        return place_of<TABLE>(u, tab, blockIdx.x / u.Tn, blockIdx.x % u.Tn);
+    }
+}
+
 // Per chunk: the bucket b* holding the k-th largest key, and how many of its bins are still needed.
-__global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__ hist, uint32_t k,
-                                                    uint32_t* __restrict__ sel)
+template <bool TABLE>
+__global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__ hist, Shape u, uint32_t* __restrict__ sel,
+                                                    TableArg<TABLE> tab)
 {
     __shared__ uint32_t tmp[4];
     const int tid = threadIdx.x;
     const size_t c = blockIdx.x;
+    const uint32_t k = place_of<TABLE>(u, tab, blockIdx.x, 0u).k;
     constexpr int PER = kHistBins / NT;  // 16 buckets per lane, lane t owns the buckets counted from the top
     uint32_t loc[PER];
     uint32_t s = 0;
@@ -262,25 +306,25 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
 // run, and fetching each line for two waves was slower (62 M samples in chunks of 2^20: 52 against 44 us).  Samples
 // lie in order, and binary16 bins are half the bytes: those are read straight into registers, without the barrier
 // (62 M samples 51 -> 42, binary16 32 -> 29).
-template <bool REAL, bool HALF>
-__global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF>::T* __restrict__ spec, uint32_t sstride,
-                                                int pair_log, uint32_t B, uint32_t Tn, const uint32_t* __restrict__ sel,
-                                                uint32_t* __restrict__ tinfo, uint2* __restrict__ cand, size_t n)
+template <bool TABLE, bool REAL, bool HALF>
+__global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u,
+                                                const uint32_t* __restrict__ sel, uint32_t* __restrict__ tinfo,
+                                                uint2* __restrict__ cand, TableArg<TABLE> tab, size_t n)
 {
     using E = typename Elem<REAL>::T;
     __shared__ uint32_t wcnt[4], wdef[4], wvmax[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const size_t c = blockIdx.x / Tn;
-    const uint32_t tile = blockIdx.x % Tn;
-    const uint32_t tbase = tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
-    const typename Stored<REAL, HALF>::T* X = spec + c * (size_t)sstride + tbase;
-    const uint32_t bstar = sel[c * 8 + 0], count = units_in_tile<REAL>(n, c, B, tbase);
+    const Place at = place_of_tile<TABLE>(u, tab);
+    const uint32_t B = at.B, tbase = at.tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
+    const int pair_log = at.pair_log;
+    const typename Stored<REAL, HALF>::T* X = spec + at.spec + tbase;
+    const uint32_t bstar = sel[at.chunk * 8 + 0], count = units_in_tile<REAL>(n, at.chunk, B, tbase);
     E z[ROWS];
     if constexpr (REAL || HALF) {
         load_units(X, row0, count, lane, pair_log, z);
     } else {
         __shared__ __align__(16) E stage[kTile];
-        tile_to_lds(X, count, (sstride & 1u) == 0, stage, tid);
+        tile_to_lds(X, count, TABLE || (u.sstride & 1u) == 0, stage, tid);
         __syncthreads();
         load_units(stage, row0, count, lane, pair_log, z);
     }
@@ -313,14 +357,14 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
     __syncthreads();
     uint32_t off = 0;
     for (int w = 0; w < wave; ++w) off += wcnt[w];
-    uint2* out = cand + (c * Tn + tile) * (size_t)kTile;
+    uint2* out = cand + blockIdx.x * (size_t)kTile;
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         if ((mine >> r) & 1u) out[off + prefix_popc(cm[r])] = make_uint2(key[r], vb[r]);
         off += (uint32_t)__popcll(cm[r]);
     }
     if (tid == 0) {
-        uint32_t* ti = tinfo + (c * Tn + tile) * 4;
+        uint32_t* ti = tinfo + (size_t)blockIdx.x * 4;
         ti[0] = wdef[0] + wdef[1] + wdef[2] + wdef[3];
         uint32_t m = wvmax[0];
         m = wvmax[1] > m ? wvmax[1] : m;
@@ -352,16 +396,6 @@ __device__ __forceinline__ uint32_t block_scan_incl(uint32_t v, uint32_t* tmp)
     return x + add;
 }
 
-// byte offset of chunk c's record from the first record of the launch: c * S, or from the table in per-tensor launches
-template <bool TABLE>
-__device__ __forceinline__ size_t record_offset(const TableArg<TABLE>& tab, size_t c, size_t S)
-{
-    if constexpr (TABLE)
-        return (size_t)tab.t.roff[c];
-    else
-        return c * S;
-}
-
 // One workgroup per chunk: finish the radix select on the candidates, break ties by bin order, scan the tiles, find the
 // survivors' largest component, write the record header and zero the code words that two tiles will share.
 //
@@ -376,9 +410,9 @@ __device__ __forceinline__ size_t record_offset(const TableArg<TABLE>& tab, size
 // Measured, us per call, against three digits and three more sweeps by 16 waves: one chunk of 2^16 16 -> 9, sixty of
 // 2^20 24 -> 18, thirty-three of 2^22 87 -> 44.
 constexpr int kFetch = 8;  // tiles of a wave fetched in one round trip
+constexpr uint32_t kKeptTiles = 270;  // 135 KiB beside the kernel's other 20
 template <bool TABLE, int NW, bool KEPT>
-__global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, int bits, int m, uint32_t W, size_t S,
-                                                     uint32_t word3, uint32_t static_vmax, uint32_t codes_per_bin,
+__global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, uint32_t static_vmax, uint32_t codes_per_bin,
                                                      uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
                                                      uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
                                                      uint8_t* __restrict__ records, uint8_t* __restrict__ stream,
@@ -391,8 +425,11 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, in
     __shared__ uint32_t s_listed, s_digit, s_need, s_count, s_vmax;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t c = blockIdx.x;
-    const uint4* ti = reinterpret_cast<const uint4*>(tinfo + c * Tn * 4);
-    const uint2* cd = cand + c * Tn * (size_t)kTile;
+    const Place at = place_of<TABLE>(u, tab, blockIdx.x, 0u);
+    const uint32_t Tn = at.Tn, k = at.k, W = at.W, word3 = at.word3;
+    const size_t S = at.S;
+    const uint4* ti = reinterpret_cast<const uint4*>(tinfo + (size_t)at.tile0 * 4);
+    const uint2* cd = cand + at.tile0 * (size_t)kTile;
     const uint32_t bstar = sel[c * 8 + 0];
     uint32_t need = sel[c * 8 + 1];
 
@@ -416,8 +453,8 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, in
         return t < Tn ? (uint32_t)__builtin_amdgcn_readfirstlane((int)tnc[t]) : 0u;
     };
     // row(t, r, e, valid) for every row of 64 candidates of this wave's tiles
-    auto sweep = [&](auto first, auto&& row) __attribute__((always_inline)) {
-        constexpr bool STORE = KEPT && decltype(first)::value, LOAD = KEPT && !decltype(first)::value;
+    auto sweep_as = [&](auto keep, auto first, auto&& row) __attribute__((always_inline)) {
+        constexpr bool STORE = decltype(keep)::value && decltype(first)::value, LOAD = decltype(keep)::value && !decltype(first)::value;
         for (uint32_t t0 = (uint32_t)wave; t0 < Tn; t0 += NW * kFetch) {
             uint2 e[kFetch];
 #pragma unroll
@@ -438,6 +475,12 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, in
                     }
             }
         }
+    };
+    auto sweep = [&](auto first, auto&& row) __attribute__((always_inline)) {
+        if (TABLE && KEPT && Tn > kKeptTiles)  // beside tensors whose candidates do fit
+            sweep_as(std::false_type{}, first, row);
+        else
+            sweep_as(std::bool_constant<KEPT>{}, first, row);
     };
     // candidates' next digit: d, counted for the lanes of `act` that want it
     auto count_digit = [&](bool hit, uint32_t d, bool run_likely) __attribute__((always_inline)) {
@@ -553,7 +596,7 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, in
     const bool count_equal = any && !few;  // tgt does not hold the kept ones of the bins equal to tau yet
 
     // scan over tiles: equal-key prefix decides who gets the tie quota, survivor prefix gives the ranks
-    uint32_t* rec = reinterpret_cast<uint32_t*>(records + record_offset<TABLE>(tab, c, S));
+    uint32_t* rec = reinterpret_cast<uint32_t*>(records + at.record);
     uint32_t* codes = rec + 4 + W;
     const uint32_t twoN = codes_per_bin * (uint32_t)bits;  // code bits per kept bin
     uint32_t eqcarry = 0, rankcarry = 0;
@@ -577,7 +620,7 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, in
         surv = surv < k - rank ? surv : k - rank;
         if (t < Tn) {
             // where all bins equal to tau are taken, a prefix of zero (and an endless quota) says so
-            *reinterpret_cast<uint2*>(tscan + (c * Tn + t) * 2) = make_uint2(rank, eqpre);
+            *reinterpret_cast<uint2*>(tscan + (size_t)(at.tile0 + t) * 2) = make_uint2(rank, eqpre);
             if (surv) {
                 codes[(twoN * rank) >> 5] = 0u;
                 codes[(twoN * (rank + surv) - 1u) >> 5] = 0u;
@@ -643,8 +686,7 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(uint32_t Tn, uint32_t k, in
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against shuffles and vector masks: 70 -> 67 us,
 // binary16 bins 60 -> 45, 15 % of the samples kept at 32 bits 98 -> 50; one chunk of 2^16 8 -> 7.
 template <bool TABLE, bool REAL, bool HALF>
-__global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, uint32_t sstride, int pair_log,
-                                             uint32_t B, uint32_t Tn, uint32_t W, int bits, int m, size_t S,
+__global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u, int bits, int m,
                                              const uint32_t* __restrict__ sel, const uint32_t* __restrict__ tscan,
                                              uint8_t* __restrict__ records, TableArg<TABLE> tab, size_t n)
 {
@@ -655,15 +697,17 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
     __shared__ __align__(16) uint64_t bmw[kTile / 64];
     __shared__ uint32_t weq[4], wfl[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const size_t c = blockIdx.x / Tn;
-    const uint32_t tile = blockIdx.x % Tn;
+    const Place at = place_of_tile<TABLE>(u, tab);
+    const uint32_t c = at.chunk, tile = at.tile, B = at.B, W = at.W;
+    const size_t S = at.S;
+    const int pair_log = at.pair_log;
     const uint32_t tau = sel[c * 8 + 2], quota = sel[c * 8 + 3], pbase = sel[c * 8 + 4];
-    const uint32_t rank0 = tscan[(c * Tn + tile) * 2 + 0], eq0 = tscan[(c * Tn + tile) * 2 + 1];
+    const uint32_t rank0 = tscan[(size_t)blockIdx.x * 2 + 0], eq0 = tscan[(size_t)blockIdx.x * 2 + 1];
     const uint32_t twoN = CODES * (uint32_t)bits;  // code bits per kept unit
     const int shift = 23 - m;
 
     const uint32_t tbase = tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;  // row0: this wave's first unit in the tile
-    const typename Stored<REAL, HALF>::T* X = spec + c * (size_t)sstride + tbase;
+    const typename Stored<REAL, HALF>::T* X = spec + at.spec + tbase;
     const uint32_t count = units_in_tile<REAL>(n, c, B, tbase);
     E z[ROWS];
     if constexpr (REAL) {
@@ -715,7 +759,7 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
         for (int r = 0; r < ROWS; ++r) bmw[wave * ROWS + r] = fm[r];
     }
     __syncthreads();
-    uint32_t* rec = reinterpret_cast<uint32_t*>(records + record_offset<TABLE>(tab, c, S));
+    uint32_t* rec = reinterpret_cast<uint32_t*>(records + at.record);
     uint32_t* bitmap = rec + 4;
     uint32_t* codes = bitmap + W;
     if (tid < kTile / 32) {
@@ -864,36 +908,38 @@ __device__ __forceinline__ void group_prefix_chunk(const uint8_t* __restrict__ s
     }
 }
 
+// what the first kernel of a receiver's call leaves in the control block
+__device__ __forceinline__ void write_control(uint32_t* __restrict__ ctl, const StatusNote& note, int tid, int lanes)
+{
+    // cleared as a whole: also the hand-over words of the fused inverse transform that may follow
+    for (int i = tid; i < (int)(kControlBytes / 4); i += lanes)
+        ctl[i] = i == 2 ? note.count : (i == 3 ? note.offset : (i == 4 ? kStatusNoteMagic : 0u));
+}
+
 template <bool TABLE>
 __global__ __launch_bounds__(RT) void k_group_prefix(const uint8_t* __restrict__ stream,
-                                                     const uint8_t* __restrict__ records, size_t S, uint32_t W,
-                                                     uint32_t k, uint32_t word3, HeaderInfo hdr,
-                                                     uint32_t* __restrict__ gprefix, uint32_t* __restrict__ sel,
-                                                     uint32_t* __restrict__ status, int reset_status,
-                                                     TableArg<TABLE> tab)
+                                                     const uint8_t* __restrict__ records, Shape u, HeaderInfo hdr,
+                                                     uint32_t* __restrict__ gprefix, uint32_t* __restrict__ verdicts,
+                                                     uint32_t* __restrict__ ctl, StatusNote note, TableArg<TABLE> tab)
 {
-    const size_t c = blockIdx.x;
-    const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
-    group_prefix_chunk(stream, records + record_offset<TABLE>(tab, c, S), c == 0, W, k, word3, hdr, gprefix + c * G,
-                       sel + c * 8 + 7);
-    // The whole control block is cleared: the status word (raised again by k_decode, which runs after this kernel)
-    // and the hand-over words of the fused inverse transform that may follow.
-    if (reset_status && c == 0)
-        for (uint32_t i = threadIdx.x; i < (uint32_t)(kControlBytes / 4); i += RT) status[i] = 0u;
+    const Place at = place_of<TABLE>(u, tab, blockIdx.x, 0u);
+    group_prefix_chunk(stream, records + at.record, blockIdx.x == 0, at.W, at.k, at.word3, hdr, gprefix + at.group0,
+                       verdicts + blockIdx.x);
+    if (ctl && blockIdx.x == 0) write_control(ctl, note, threadIdx.x, RT);
 }
 
 // The same for several peers' streams: workgroup (peer, chunk).
 __global__ __launch_bounds__(RT) void k_group_prefix_peers(PeerList streams, uint32_t C, size_t S, uint32_t W, uint32_t k,
                                                            HeaderInfo hdr, uint32_t* __restrict__ gprefix,
-                                                           uint32_t* __restrict__ verd, uint32_t* __restrict__ status)
+                                                           uint32_t* __restrict__ verdicts, uint32_t* __restrict__ ctl,
+                                                           StatusNote note)
 {
     const uint32_t peer = blockIdx.x / C, c = blockIdx.x % C;
     const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
     const uint8_t* stream = streams.p[peer];
     group_prefix_chunk(stream, stream + 64 + (size_t)c * S, c == 0, W, k, 0u, hdr,
-                       gprefix + ((size_t)peer * C + c) * G, verd + (size_t)peer * C + c);
-    if (blockIdx.x == 0)  // the whole control block, as k_group_prefix does
-        for (uint32_t i = threadIdx.x; i < (uint32_t)(kControlBytes / 4); i += RT) status[i] = 0u;
+                       gprefix + ((size_t)peer * C + c) * G, verdicts + (size_t)peer * C + c);
+    if (blockIdx.x == 0) write_control(ctl, note, threadIdx.x, RT);
 }
 
 // A word every lane reads: by a scalar load, from memory that this kernel does not write.
@@ -1079,7 +1125,7 @@ __device__ __forceinline__ void tile_from_lds(T* __restrict__ X, const T* stage,
     }
 }
 
-// One stream: a workgroup per tile, a wave per 512 units.  The header verdict of chunk c is in sel[8c + 7].
+// One stream: a workgroup per tile, a wave per 512 units.
 // REAL: time-domain records (one code per kept sample); `spec` is then the gradient itself, chunk stride B = L
 // samples, written up to sample n only.
 // HALF: the spectrum is written as binary16 pairs (half-precision variant).
@@ -1091,22 +1137,21 @@ __device__ __forceinline__ void tile_from_lds(T* __restrict__ X, const T* stage,
 // ranks were per lane: half of the bins kept as 8-bit codes 62 -> 54 us (298 MB of traffic), binary16 bins 52 -> 33, 15 % of
 // the samples kept at 32 bits 93 -> 62; chunks of 2^22 (138 M samples) 136 -> 112.
 template <int NL, bool TABLE, bool REAL, bool HALF>
-__global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ records, size_t S, uint32_t B, uint32_t W,
-                                               int bits, int m, uint32_t Tn, const uint32_t* __restrict__ gprefix,
-                                               const uint32_t* __restrict__ sel, uint32_t* __restrict__ status,
-                                               typename Stored<REAL, HALF>::T* __restrict__ spec, uint32_t sstride, bool vec,
-                                               int pair_log, TableArg<TABLE> tab, size_t n)
+__global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ records, Shape u, int bits, int m,
+                                               const uint32_t* __restrict__ gprefix,
+                                               typename Stored<REAL, HALF>::T* __restrict__ spec, bool vec,
+                                               TableArg<TABLE> tab, size_t n)
 {
     using T = typename Stored<REAL, HALF>::T;
     __shared__ __align__(16) uint8_t windows[NL ? 4 * kWindow<NL> : 16];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const size_t c = blockIdx.x / Tn;
-    const uint32_t tile = blockIdx.x % Tn, tbase = tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
-    const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
-    const uint8_t* record = records + record_offset<TABLE>(tab, c, S);
+    const Place at = place_of_tile<TABLE>(u, tab);
+    const uint32_t W = at.W, tbase = at.tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
+    const size_t S = at.S;
+    const uint8_t* record = records + at.record;
     uint8_t* window = windows + (NL ? wave * kWindow<NL> : 0);
     WaveCodes<NL> wc;
-    fetch_codes<NL, Elem<REAL>::kCodes>(record, S, W, tile * (kTile / 32 / GROUP_WORDS) + wave, bits, gprefix + c * G, lane, wc);
+    fetch_codes<NL, Elem<REAL>::kCodes>(record, S, W, at.tile * (kTile / 32 / GROUP_WORDS) + wave, bits, gprefix + at.group0, lane, wc);
     T z[ROWS];
     unpack_codes<NL, REAL>(wc, record, S, W, bits, 23 - m, lane, window, [&](int r, const typename Elem<REAL>::T& v) {
         if constexpr (HALF)
@@ -1114,8 +1159,8 @@ __global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ recor
         else
             z[r] = v;
     });
-    T* X = spec + c * (size_t)sstride + tbase;
-    const uint32_t count = units_in_tile<REAL>(n, c, B, tbase);
+    T* X = spec + at.spec + tbase;
+    const uint32_t count = units_in_tile<REAL>(n, at.chunk, at.B, tbase);
     if constexpr (REAL) {
         X += row0 + (uint32_t)lane;
         if (count == (uint32_t)kTile) {
@@ -1128,24 +1173,19 @@ __global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ recor
         }
     } else {
         __shared__ __align__(16) T stage[kTile];
-        place_units(stage, row0, lane, pair_log, z);
+        place_units(stage, row0, lane, at.pair_log, z);
         __syncthreads();
         tile_from_lds(X, stage, count, vec, tid);
-    }
-    if (tile == 0 && tid == 0) {
-        const uint32_t verdict = sel[c * 8 + 7];
-        if (verdict) atomicMax(status, verdict);
     }
 }
 
 // Several peers' streams (receiver under an allgather: Sec. 4, implementation): the same, the units summed over the
-// peers in list order in registers, starting from zero, and stored once.  Header verdicts at verd[peer * C + chunk].
+// peers in list order in registers, starting from zero, and stored once.
 // Bound by instruction issue (two thirds of the vector slots).  Fetching the next peer's codes before unpacking this
 // one's changed nothing.  Measured, eight peers of 62 M samples, half of the bins kept as 8-bit codes: 354 -> 181 us.
 template <int NL>
 __global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npeers, size_t S, uint32_t B, uint32_t W, int bits,
                                                      int m, uint32_t Tn, size_t C, const uint32_t* __restrict__ gprefix,
-                                                     const uint32_t* __restrict__ verd, uint32_t* __restrict__ status,
                                                      float2* __restrict__ spec, uint32_t sstride, bool vec, int pair_log)
 {
     __shared__ __align__(16) uint8_t windows[NL ? 4 * kWindow<NL> : 16];
@@ -1169,10 +1209,6 @@ __global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npe
     place_units(stage, row0, lane, pair_log, acc);
     __syncthreads();
     tile_from_lds(spec + c * (size_t)sstride + tbase, stage, units_in_tile<false>(0, c, B, tbase), vec, tid);
-    if (tile == 0 && (uint32_t)tid < npeers) {
-        const uint32_t verdict = verd[(size_t)tid * C + c];
-        if (verdict) atomicMax(status, verdict);
-    }
 }
 
 }  // namespace
@@ -1192,118 +1228,127 @@ hipError_t launch_zero_control(uint8_t* ws_base, const Workspace& w, size_t C, h
     return launch_zero_hist(ws_base, w, C, s);
 }
 
-hipError_t launch_clear_status(uint8_t* ws_base, const Workspace& w, hipStream_t s)
+static Shape shape_of(const CodecArgs& a)
 {
-    FFTSP_LAUNCH("zero_fill", k_zero_u32, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(ws_base + w.status),
-                 (size_t)5);  // the status word and the note on verdicts behind it
-    return hipGetLastError();
+    const uint32_t B = codec_bins(a.L, a.time_domain);
+    return Shape{B, codec_tiles(a.L, a.time_domain), (B + 31) / 32, a.k, a.sstride, a.word3, a.S, a.pair_log};
+}
+// chunks and tiles of a launch; the longest chunk's tiles
+struct Extent {
+    size_t chunks, tiles;
+    uint32_t most;
+};
+static Extent extent_of(const CodecArgs& a)
+{
+    if (!a.tab) {
+        const uint32_t Tn = codec_tiles(a.L, a.time_domain);
+        return Extent{a.C, a.C * Tn, Tn};
+    }
+    Extent x{a.tab->count, ((size_t)a.tab->units << (kLongUnitLog - 11)) + a.tab->count, 0};
+    for (uint32_t i = 0; i < a.tab->count; ++i) x.most = std::max(x.most, (1u << a.tab->tab.t[i].logM) / (uint32_t)kTile + 1u);
+    return x;
 }
 
 hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_base, uint8_t* records,
                          uint8_t* ws_base, const Workspace& w, int hist_ready, hipStream_t s)
 {
-    const uint32_t B = codec_bins(a.L, a.time_domain), Tn = codec_tiles(a.L, a.time_domain), W = (B + 31) / 32;
+    const Shape u = shape_of(a);
+    const Extent x = extent_of(a);
     const float2* X = reinterpret_cast<const float2*>(spec);
+    const uint32_t* Xh = reinterpret_cast<const uint32_t*>(spec);
     uint32_t* hist = reinterpret_cast<uint32_t*>(ws_base + w.hist);
     uint32_t* sel = reinterpret_cast<uint32_t*>(ws_base + w.sel);
     uint32_t* tinfo = reinterpret_cast<uint32_t*>(ws_base + w.tinfo);
     uint32_t* tscan = reinterpret_cast<uint32_t*>(ws_base + w.tscan);
     uint2* cand = reinterpret_cast<uint2*>(ws_base + w.cand);
-    if (a.C * (size_t)Tn > 0x7fffffffu || Tn > (uint32_t)MAX_TILES) return hipErrorInvalidValue;
+    if (x.tiles > 0x7fffffffu || x.most > (uint32_t)MAX_TILES) return hipErrorInvalidValue;
     if (a.time_domain && (a.tab || a.pair_log || hist_ready)) return hipErrorInvalidValue;
     // binary16 spectra come from the two-pass FFT only, which also fills the histogram
     if (a.half && (a.tab || a.time_domain || !a.pair_log || !hist_ready)) return hipErrorInvalidValue;
-    const uint32_t* Xh = reinterpret_cast<const uint32_t*>(spec);
+    if (a.tab && !hist_ready) return hipErrorInvalidValue;
 
     if (!hist_ready) {
         hipError_t e = launch_zero_hist(ws_base, w, a.C, s);
         if (e != hipSuccess) return e;
-        const uint32_t groups = (Tn + HIST_TILES - 1) / HIST_TILES;
-        const uint32_t sgroups = (Tn + kHistSampleTiles - 1) / kHistSampleTiles;
+        const uint32_t groups = (u.Tn + HIST_TILES - 1) / HIST_TILES;
+        const uint32_t sgroups = (u.Tn + kHistSampleTiles - 1) / kHistSampleTiles;
         if (a.time_domain)
             FFTSP_LAUNCH("hist", k_hist_samples, dim3((unsigned)(a.C * sgroups)), dim3(NT), 0, s, spec, a.L, sgroups,
                          hist, a.n);
         else
-            FFTSP_LAUNCH("hist", k_hist, dim3((unsigned)(a.C * groups)), dim3(NT), 0, s, X, a.sstride, a.pair_log, B,
+            FFTSP_LAUNCH("hist", k_hist, dim3((unsigned)(a.C * groups)), dim3(NT), 0, s, X, a.sstride, a.pair_log, u.B,
                          groups, hist);
     }
-    FFTSP_LAUNCH("find_bucket", k_find_bucket, dim3((unsigned)a.C), dim3(NT), 0, s, hist, a.k, sel);
-    if (a.time_domain)
-        FFTSP_LAUNCH("collect", (k_collect<true, false>), dim3((unsigned)(a.C * Tn)), dim3(NT), 0, s, spec, a.sstride, 0,
-                     B, Tn, sel, tinfo, cand, a.n);
-    else if (a.half)
-        FFTSP_LAUNCH("collect", (k_collect<false, true>), dim3((unsigned)(a.C * Tn)), dim3(NT), 0, s, Xh, a.sstride,
-                     a.pair_log, B, Tn, sel, tinfo, cand, a.n);
-    else
-        FFTSP_LAUNCH("collect", (k_collect<false, false>), dim3((unsigned)(a.C * Tn)), dim3(NT), 0, s, X, a.sstride,
-                     a.pair_log, B, Tn, sel, tinfo, cand, a.n);
     HeaderInfo h{a.write_header, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S,
                  a.hdr_theta, a.time_domain ? 1u : 0u, (uint32_t)a.hdr_scale};
     const uint32_t codes_per_bin = a.time_domain ? 1u : 2u;
-    if (a.tab && a.C > (size_t)kMaxTableChunks) return hipErrorInvalidValue;
-    // few waves for few tiles: their barriers are cheaper than more hands
-#define FFTSP_RESOLVE_AS(TABLE, NW, KEPT)                                                                              \
-    do {                                                                                                               \
-        const size_t lds = KEPT ? (size_t)Tn * 512u : 0u;                                                              \
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_resolve<TABLE, NW, KEPT>),            \
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                \
-        if (e != hipSuccess) return e;                                                                                 \
-        FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW, KEPT>), dim3((unsigned)a.C), dim3(NW * 64), lds, s, Tn, a.k,     \
-                     a.bits, a.m, W, a.S, a.word3, a.static_vmax, codes_per_bin, sel, tinfo, tscan, cand, records,     \
-                     stream_base, h, table_arg<TABLE>(a.tab));                                                         \
-    } while (0)
-#define FFTSP_RESOLVE(TABLE)                                                                                           \
-    do {                                                                                                               \
-        if (Tn <= 40u)                                                                                                 \
-            FFTSP_RESOLVE_AS(TABLE, 4, true);                                                                          \
-        else if (Tn <= 130u)                                                                                           \
-            FFTSP_RESOLVE_AS(TABLE, 8, true);                                                                          \
-        else if (Tn <= 270u) /* 135 KiB beside the kernel's other 20 */                                                \
-            FFTSP_RESOLVE_AS(TABLE, 16, true);                                                                         \
-        else                                                                                                           \
-            FFTSP_RESOLVE_AS(TABLE, 16, false);                                                                        \
-    } while (0)
-#define FFTSP_EMIT(TABLE, REAL, HALF, src)                                                                            \
-    FFTSP_LAUNCH("emit", (k_emit<TABLE, REAL, HALF>), dim3((unsigned)(a.C * Tn)), dim3(NT), 0, s, src, a.sstride,     \
-                 a.pair_log, B, Tn, W, a.bits, a.m, a.S, sel, tscan, records, table_arg<TABLE>(a.tab), a.n)
-    if (a.tab) {
-        FFTSP_RESOLVE(true);
+    const dim3 per_tile((unsigned)x.tiles), per_chunk((unsigned)x.chunks);
+    auto select = [&](auto table) {
+        constexpr bool TABLE = decltype(table)::value;
+        const TableArg<TABLE> tab = table_arg<TABLE>(a.tab);
+        FFTSP_LAUNCH("find_bucket", k_find_bucket<TABLE>, per_chunk, dim3(NT), 0, s, hist, u, sel, tab);
+        if constexpr (TABLE) {
+            FFTSP_LAUNCH("collect", (k_collect<true, false, false>), per_tile, dim3(NT), 0, s, X, u, sel, tinfo, cand, tab, a.n);
+        } else {
+            if (a.time_domain)
+                FFTSP_LAUNCH("collect", (k_collect<false, true, false>), per_tile, dim3(NT), 0, s, spec, u, sel, tinfo, cand, tab, a.n);
+            else if (a.half)
+                FFTSP_LAUNCH("collect", (k_collect<false, false, true>), per_tile, dim3(NT), 0, s, Xh, u, sel, tinfo, cand, tab, a.n);
+            else
+                FFTSP_LAUNCH("collect", (k_collect<false, false, false>), per_tile, dim3(NT), 0, s, X, u, sel, tinfo, cand, tab, a.n);
+        }
+        // few waves for few tiles: their barriers are cheaper than more hands
+        auto resolve = [&](auto waves, auto keep) {
+            constexpr int NW = decltype(waves)::value;
+            constexpr bool KEPT = decltype(keep)::value;
+            const size_t lds = KEPT ? (size_t)std::min(x.most, kKeptTiles) * 512u : 0u;
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_resolve<TABLE, NW, KEPT>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+            FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW, KEPT>), per_chunk, dim3(NW * 64), lds, s, u, a.bits, a.m, a.static_vmax,
+                         codes_per_bin, sel, tinfo, tscan, cand, records, stream_base, h, tab);
+            return hipGetLastError();
+        };
+        if (x.most <= 40u) return resolve(std::integral_constant<int, 4>{}, std::true_type{});
+        if (x.most <= 130u) return resolve(std::integral_constant<int, 8>{}, std::true_type{});
+        if constexpr (!TABLE)
+            if (x.most > kKeptTiles) return resolve(std::integral_constant<int, 16>{}, std::false_type{});
+        return resolve(std::integral_constant<int, 16>{}, std::true_type{});
+    };
+    const hipError_t e = a.tab ? select(std::true_type{}) : select(std::false_type{});
+    if (e != hipSuccess) return e;
+#define FFTSP_EMIT(TABLE, REAL, HALF, src)                                                                             \
+    FFTSP_LAUNCH("emit", (k_emit<TABLE, REAL, HALF>), per_tile, dim3(NT), 0, s, src, u, a.bits, a.m, sel, tscan, records, \
+                 table_arg<TABLE>(a.tab), a.n)
+    if (a.tab)
         FFTSP_EMIT(true, false, false, X);
-    } else {
-        FFTSP_RESOLVE(false);
-        if (a.time_domain)
-            FFTSP_EMIT(false, true, false, spec);
-        else if (a.half)
-            FFTSP_EMIT(false, false, true, Xh);
-        else
-            FFTSP_EMIT(false, false, false, X);
-    }
-#undef FFTSP_RESOLVE
-#undef FFTSP_RESOLVE_AS
+    else if (a.time_domain)
+        FFTSP_EMIT(false, true, false, spec);
+    else if (a.half)
+        FFTSP_EMIT(false, false, true, Xh);
+    else
+        FFTSP_EMIT(false, false, false, X);
 #undef FFTSP_EMIT
     return hipGetLastError();
 }
 
-// the decode kernel proper: one stream with its verdicts in the sel array (chunk c: word 8c+7), or the peer
-// list with verdicts at verd[peer * C + c]
+// the decode kernel proper, of one stream or of the peer list
 static hipError_t launch_decode_kernel(const PeerList& recs, uint32_t npeers, const CodecArgs& a, float* spec,
-                                       const uint32_t* gprefix, const uint32_t* verd, uint32_t* status, bool peers_layout,
-                                       hipStream_t s)
+                                       const uint32_t* gprefix, bool peers_layout, hipStream_t s)
 {
-    const uint32_t B = codec_bins(a.L, a.time_domain), W = (B + 31) / 32, Tn = codec_tiles(a.L, a.time_domain);
-    const dim3 grid((unsigned)(a.C * Tn));
+    const Shape u = shape_of(a);
+    const dim3 grid((unsigned)extent_of(a).tiles);
     if (a.half && (peers_layout || a.tab || a.time_domain)) return hipErrorInvalidValue;
     if (a.time_domain && (peers_layout || a.tab || a.pair_log)) return hipErrorInvalidValue;
-    const bool vec = a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0;
+    const bool vec = a.tab || (a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0);
 #define FFTSP_DECODE_AS(NL, TABLE, REAL, HALF, T)                                                                      \
-    FFTSP_LAUNCH("decode", (k_decode<NL, TABLE, REAL, HALF>), grid, dim3(NT), 0, s, recs.p[0], a.S, B, W, a.bits, a.m, \
-                 Tn, gprefix, verd, status, reinterpret_cast<T*>(spec), a.sstride, vec, a.pair_log,                    \
-                 table_arg<TABLE>(a.tab), a.n)
+    FFTSP_LAUNCH("decode", (k_decode<NL, TABLE, REAL, HALF>), grid, dim3(NT), 0, s, recs.p[0], u, a.bits, a.m, gprefix, \
+                 reinterpret_cast<T*>(spec), vec, table_arg<TABLE>(a.tab), a.n)
 #define FFTSP_DECODE(NL)                                                                                               \
     do {                                                                                                               \
         if (peers_layout)                                                                                              \
-            FFTSP_LAUNCH("decode", k_decode_peers<NL>, grid, dim3(NT), 0, s, recs, npeers, a.S, B, W, a.bits, a.m, Tn, \
-                         a.C, gprefix, verd, status, reinterpret_cast<float2*>(spec), a.sstride, vec, a.pair_log);     \
+            FFTSP_LAUNCH("decode", k_decode_peers<NL>, grid, dim3(NT), 0, s, recs, npeers, a.S, u.B, u.W, a.bits, a.m, \
+                         u.Tn, a.C, gprefix, reinterpret_cast<float2*>(spec), a.sstride, vec, a.pair_log);             \
         else if (a.tab)                                                                                                \
             FFTSP_DECODE_AS(NL, true, false, false, float2);                                                           \
         else if (a.half)                                                                                               \
@@ -1328,42 +1373,44 @@ static hipError_t launch_decode_kernel(const PeerList& recs, uint32_t npeers, co
 }
 
 hipError_t launch_decode(const uint8_t* stream_base, const uint8_t* records, const CodecArgs& a, float* spec,
-                         uint8_t* ws_base, const Workspace& w, int check_header, int reset_status, hipStream_t s)
+                         uint8_t* ws_base, const Workspace& w, int check_header, uint32_t* verdicts, const StatusNote* note,
+                         hipStream_t s)
 {
-    const uint32_t B = codec_bins(a.L, a.time_domain), W = (B + 31) / 32, Tn = codec_tiles(a.L, a.time_domain);
-    uint32_t* status = reinterpret_cast<uint32_t*>(ws_base + w.status);
-    uint32_t* sel = reinterpret_cast<uint32_t*>(ws_base + w.sel);
+    const Shape u = shape_of(a);
+    const Extent x = extent_of(a);
+    uint32_t* ctl = note ? reinterpret_cast<uint32_t*>(ws_base + w.status) : nullptr;
     uint32_t* gprefix = reinterpret_cast<uint32_t*>(ws_base + w.prefix);
-    if (a.C * (size_t)Tn > 0x7fffffffu) return hipErrorInvalidValue;
+    if (x.tiles > 0x7fffffffu) return hipErrorInvalidValue;
     HeaderInfo h{check_header, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S,
                  a.hdr_theta, a.time_domain ? 1u : 0u, (uint32_t)a.hdr_scale};
-    if (a.tab && a.C > (size_t)kMaxTableChunks) return hipErrorInvalidValue;
+    const StatusNote none{0u, 0u};
     if (a.tab)
-        FFTSP_LAUNCH("group_prefix", k_group_prefix<true>, dim3((unsigned)a.C), dim3(RT), 0, s, stream_base, records, a.S,
-                     W, a.k, a.word3, h, gprefix, sel, status, reset_status, table_arg<true>(a.tab));
+        FFTSP_LAUNCH("group_prefix", k_group_prefix<true>, dim3((unsigned)x.chunks), dim3(RT), 0, s, stream_base, records, u, h,
+                     gprefix, verdicts, ctl, note ? *note : none, table_arg<true>(a.tab));
     else
-        FFTSP_LAUNCH("group_prefix", k_group_prefix<false>, dim3((unsigned)a.C), dim3(RT), 0, s, stream_base, records, a.S,
-                     W, a.k, a.word3, h, gprefix, sel, status, reset_status, table_arg<false>(a.tab));
+        FFTSP_LAUNCH("group_prefix", k_group_prefix<false>, dim3((unsigned)x.chunks), dim3(RT), 0, s, stream_base, records, u, h,
+                     gprefix, verdicts, ctl, note ? *note : none, table_arg<false>(a.tab));
     PeerList recs{};
     recs.p[0] = records;
-    return launch_decode_kernel(recs, 1u, a, spec, gprefix, sel, status, false, s);
+    return launch_decode_kernel(recs, 1u, a, spec, gprefix, false, s);
 }
 
 hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecArgs& a, float* spec, uint8_t* ws_base,
                                const Workspace& w, const PeerWorkspace& pw, hipStream_t s)
 {
-    const uint32_t B = a.L / 2 + 1, W = (B + 31) / 32, Tn = tiles_per_chunk(a.L);
-    uint32_t* status = reinterpret_cast<uint32_t*>(ws_base + w.status);
+    const Shape u = shape_of(a);
+    uint32_t* ctl = reinterpret_cast<uint32_t*>(ws_base + w.status);
     uint32_t* gprefix = reinterpret_cast<uint32_t*>(ws_base + pw.prefix);
-    uint32_t* verd = reinterpret_cast<uint32_t*>(ws_base + pw.verd);
+    uint32_t* verdicts = reinterpret_cast<uint32_t*>(ws_base + pw.verd);
     if (npeers < 1 || npeers > kMaxPeers) return hipErrorInvalidValue;
-    if (a.C * (size_t)Tn > 0x7fffffffu || a.C * (size_t)npeers > 0x7fffffffu) return hipErrorInvalidValue;
+    const size_t count = a.C * (size_t)npeers;
+    if (a.C * (size_t)u.Tn > 0x7fffffffu || count > 0x7fffffffu || pw.verd / 4 > 0xffffffffu) return hipErrorInvalidValue;
     HeaderInfo h{1, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
-    FFTSP_LAUNCH("group_prefix", k_group_prefix_peers, dim3((unsigned)(a.C * (size_t)npeers)), dim3(RT), 0, s, streams,
-                 (uint32_t)a.C, a.S, W, a.k, h, gprefix, verd, status);
+    FFTSP_LAUNCH("group_prefix", k_group_prefix_peers, dim3((unsigned)count), dim3(RT), 0, s, streams, (uint32_t)a.C, a.S, u.W,
+                 a.k, h, gprefix, verdicts, ctl, StatusNote{(uint32_t)count, (uint32_t)(pw.verd / 4)});
     PeerList recs{};
     for (int i = 0; i < npeers; ++i) recs.p[i] = streams.p[i] + 64;  // records follow the 64-byte stream header
-    return launch_decode_kernel(recs, (uint32_t)npeers, a, spec, gprefix, verd, status, true, s);
+    return launch_decode_kernel(recs, (uint32_t)npeers, a, spec, gprefix, true, s);
 }
 
 }  // namespace fftsp

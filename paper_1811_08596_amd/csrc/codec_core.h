@@ -126,6 +126,18 @@ __device__ __forceinline__ uint32_t dequantize_field(uint32_t word, uint32_t at,
     return c ? v : 0u;
 }
 
+// The tensor of a LongTable that this workgroup belongs to and its number in that tensor's share: one load by all lanes
+// (a binary search would be six dependent ones).
+struct LongShare {
+    uint32_t tensor, blk;
+};
+__device__ __forceinline__ LongShare long_share(const LongStarts& at)
+{
+    const uint32_t lane = threadIdx.x & 63u, start = lane < at.count ? (uint32_t)at.at[lane] : ~0u;
+    const int i = (int)__popcll(__ballot(start <= blockIdx.x)) - 1;
+    return LongShare{at.first + (uint32_t)i, blockIdx.x - (uint32_t)__builtin_amdgcn_readlane((int)start, i)};
+}
+
 constexpr uint32_t kListCap = 256;  // keys of the threshold's bucket that are finished from a list
 
 // The `need`-th largest of `count` listed keys that share all bits above `low`: tau grows bit by bit, a ballot counts

@@ -21,7 +21,9 @@
 // an XOR swizzle that keeps both "b fastest" and "i fastest" wave accesses spread
 // over all banks without padding.
 #include "fft_core.h"
+#include "codec_core.h"
 #include <cmath>
+#include <type_traits>
 
 namespace fftsp {
 namespace {
@@ -43,6 +45,8 @@ constexpr size_t kWideTiles = 256;
 inline bool wide_tiles(size_t C, int logM) { return (C << (logM - 14)) >= kWideTiles; }
 constexpr int tile_lanes(int loge) { return 1 << (loge - 4); }
 constexpr int kLanePairs = 8;  // pairs of adjacent points a lane holds
+// a pass A tile is 2^(loge - LOGN1) columns of 8 bytes; the tiles of a 128-byte line (two at least) are walked in step
+constexpr int group_log(int loge, int logn1) { return loge - logn1 >= 3 ? 1 : 2; }
 
 // The next tile's loads are issued in at most this many portions: one before the LDS stages, one after each of the
 // first stages.  A wave that issues a whole tile's loads at once stands in the issue until the memory pipeline has
@@ -150,15 +154,17 @@ __device__ __forceinline__ void fwd_a_tile(uint32_t t, uint32_t tiles, int logM,
 }
 
 // Forward pass A: N1-point FFTs down the columns of the N1 x N2 view of z, for tiles of TA adjacent columns.
-// FAST: every tile of this workgroup's run lies in a chunk that is wholly inside the input, and the input is
-// 16-byte aligned: two columns per 16-byte load, no guards.  Otherwise every element is loaded under a guard
-// (ragged last chunk, unaligned tensors); the two variants are separate loops so that the guarded one does
-// not put branches between the fast one's loads and their use.
-template <int LOGN1, bool FAST, bool TABLE, bool HALF>
-__device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t n, int logM,
+// kWhole: every tile of this workgroup's run lies in a chunk that is wholly inside the input, and the input is
+// 16-byte aligned: two columns per 16-byte load, no guards.  kQuads: the input is aligned and ends on a multiple of four
+// samples: every 16-byte piece is inside or outside, and those outside read a valid address and count as zeros (tensors
+// that do not fill their chunk).  kGuarded: every element is loaded under a guard (other ragged ends, unaligned tensors).
+// The variants are separate loops so that no branches stand between the unguarded ones' loads and their use.
+enum Reads { kGuarded, kWhole, kQuads };
+template <int LOGN1, Reads MODE, bool HALF>
+__device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t first, size_t n, int logM,
                                           typename Cx<HALF>::One* __restrict__ mid, const Tables& tb, int aligned,
                                           uint32_t t, uint32_t tend, uint32_t tstep, float2* d, const float2* tw, int tid0,
-                                          const TableArg<TABLE>& tab, float in_scale)
+                                          float in_scale)
 {
     constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE), PER2 = kLanePairs;
     constexpr int N1 = 1 << LOGN1, LOGT = LOGE - LOGN1, TA = 1 << LOGT;
@@ -169,9 +175,21 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t n
     // part p of spread_parts(): loads q with q * parts / PER2 == p; prologue calls pass every part in turn
     auto load_tile = [&](float4 (&r)[PER2], uint32_t tile, int tid, bool live, int part) {
         // every tile lies in a real chunk, so the span needs no chunk count
-        const Span sp = chunk_span<TABLE>(tab, tile / tiles, ~(size_t)0, 2 * (size_t)M, n, aligned & 1);
+        const Span sp = chunk_span(first, n, tile / tiles, 2 * (size_t)M, aligned & 1);
         const uint32_t col0 = tile_in_chunk(tile, tiles) << LOGT;
-        if constexpr (FAST) {
+        if constexpr (MODE == kQuads) {
+            const float4* src = live ? reinterpret_cast<const float4*>(in + sp.first) : reinterpret_cast<const float4*>(tb.hi);
+            const size_t left = live && sp.limit > sp.first ? (sp.limit - sp.first) >> 2 : 0;  // pieces of this chunk that exist
+            const uint32_t quads = left < (size_t)(M >> 1) ? (uint32_t)left : M >> 1;
+#pragma unroll
+            for (int q = 0; q < PER2; ++q) {
+                if (q * spread_parts<LOGN1>() / PER2 != part) continue;
+                const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
+                const uint32_t i = (uint32_t)n1 * (N2 >> 1) + (col0 >> 1) + bp;
+                r[q] = src[i < quads ? i : 0u];
+                if (i >= quads) r[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        } else if constexpr (MODE == kWhole) {
             const float4* src = live ? reinterpret_cast<const float4*>(in + sp.first) + (col0 >> 1)
                                      : reinterpret_cast<const float4*>(tb.hi);
 #pragma unroll
@@ -214,41 +232,44 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t n
     }
 }
 
-// `aligned`: bit 0 = input is 8-byte aligned, bit 1 = 16-byte aligned.
-template <int LOGN1, bool TABLE, bool HALF>
-__global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __restrict__ in, size_t n, int logM,
-                                               typename Cx<HALF>::One* __restrict__ mid, Tables tb, int aligned,
-                                               uint32_t total, uint32_t per_wg, int glog, uint32_t* __restrict__ zero_ptr,
-                                               uint32_t zero_words, TableArg<TABLE> tab, float in_scale,
-                                               const uint32_t* __restrict__ only_if)
+// The tiles of workgroup blk of a pass A over the chunks of in[first .. first + n), in chunks of 2^(logM+1).
+// `aligned`: bit 0 = `in` is 8-byte aligned, bit 1 = 16-byte aligned.
+// LONG: one tensor, which may be much shorter than its chunk and start anywhere.
+template <int LOGN1, bool LONG, bool HALF>
+__device__ __forceinline__ void fwd_a_workgroup(uint32_t blk, const float* __restrict__ in, size_t first, size_t n, int logM,
+                                                typename Cx<HALF>::One* __restrict__ mid, const Tables& tb, int aligned,
+                                                uint32_t total, uint32_t per_wg, int glog, float in_scale)
 {
     constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE), ELEMS = 1 << LOGE;
-    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
-    // clears the status words and key histograms the next kernels of the sender accumulate into
-    for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < zero_words; i += gridDim.x * NT) zero_ptr[i] = 0u;
     extern __shared__ float2 smem[];
     float2* d = smem;
     float2* tw = smem + ELEMS;
     const int tid0 = threadIdx.x;
     uint32_t t, tend;
-    if (!grouped_run(total, per_wg, glog, t, tend)) return;
+    if (!grouped_run(blk, total, per_wg, glog, t, tend)) return;
     load_stage_twiddles<LOGN1, NT>(tw, tb, tid0);
     const uint32_t tiles = (1u << logM) >> LOGE;  // tiles per chunk
-    bool fast = (aligned & 2) != 0;
-    if constexpr (TABLE) {
-        // every tensor this run touches fills its chunk and starts on a 16-byte boundary
-        for (uint32_t c = t / tiles; c <= (tend - 1) / tiles; ++c)
-            fast = fast && (tab.t.goff[c] & 3u) == 0 && tab.t.glen[c] == (2u << logM);
-    } else {
-        const size_t last_chunk_end = ((size_t)((tend - 1) / tiles) + 1) << (logM + 1);
-        fast = fast && last_chunk_end <= n;
-    }
-    if (fast)
-        fwd_a_run<LOGN1, true, TABLE, HALF>(in, n, logM, mid, tb, aligned, t, tend, 1u << glog, d, tw, tid0, tab,
-                                            in_scale);
+    const size_t last_chunk_end = ((size_t)((tend - 1) / tiles) + 1) << (logM + 1);
+    const bool quads = (aligned & 2) && (first & 3u) == 0;
+    if (!LONG && quads && last_chunk_end <= n)
+        fwd_a_run<LOGN1, kWhole, HALF>(in, first, n, logM, mid, tb, aligned, t, tend, 1u << glog, d, tw, tid0, in_scale);
+    else if (LONG && quads && (n & 3u) == 0)
+        fwd_a_run<LOGN1, kQuads, HALF>(in, first, n, logM, mid, tb, aligned, t, tend, 1u << glog, d, tw, tid0, in_scale);
     else
-        fwd_a_run<LOGN1, false, TABLE, HALF>(in, n, logM, mid, tb, aligned, t, tend, 1u << glog, d, tw, tid0, tab,
-                                             in_scale);
+        fwd_a_run<LOGN1, kGuarded, HALF>(in, first, n, logM, mid, tb, aligned, t, tend, 1u << glog, d, tw, tid0, in_scale);
+}
+
+template <int LOGN1, bool HALF>
+__global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __restrict__ in, size_t n, int logM,
+                                               typename Cx<HALF>::One* __restrict__ mid, Tables tb, int aligned,
+                                               uint32_t total, uint32_t per_wg, int glog, uint32_t* __restrict__ zero_ptr,
+                                               uint32_t zero_words, float in_scale, const uint32_t* __restrict__ only_if)
+{
+    constexpr int NT = tile_lanes(kTileFA);
+    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
+    // clears the status words and key histograms the next kernels of the sender accumulate into
+    for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < zero_words; i += gridDim.x * NT) zero_ptr[i] = 0u;
+    fwd_a_workgroup<LOGN1, false, HALF>(blockIdx.x, in, 0, n, logM, mid, tb, aligned, total, per_wg, glog, in_scale);
 }
 
 
@@ -260,14 +281,14 @@ __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __re
 // selects) so that its LDS reads can be issued ahead in batches instead of one wait per read.
 // HALF (CODEC only): the intermediate is read and the spectrum written as binary16 pairs; the histogram counts
 // the keys of the values as stored, which are the ones the selection will see.
+// Workgroup blk of nblk does its share of the total tiles.
 template <int LOGN2, int LOGE, bool CODEC, bool HALF>
-__global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b(const typename Cx<HALF>::One* __restrict__ mid, int logM,
-                                               typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride, Tables tb,
-                                               uint32_t* __restrict__ hist, uint32_t total, uint32_t per_wg,
-                                               float mid_scale, const uint32_t* __restrict__ only_if)
+__device__ __forceinline__ void fwd_b_workgroup(uint32_t blk, uint32_t nblk, const typename Cx<HALF>::One* __restrict__ mid,
+                                                int logM, typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride,
+                                                const Tables& tb, uint32_t* __restrict__ hist, uint32_t total,
+                                                uint32_t per_wg, float mid_scale)
 {
     static_assert(CODEC || !HALF, "binary16 storage is the codec's own");
-    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
     using Two = typename Cx<HALF>::Two;
     constexpr int NT = tile_lanes(LOGE), PER2 = kLanePairs;
     constexpr int N2 = 1 << LOGN2, LOGT = LOGE - LOGN2, ELEMS = 1 << LOGE;
@@ -280,10 +301,10 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b(const typename Cx<HA
     const int tid0 = threadIdx.x;
     const int logN1 = logM - LOGN2;
     const uint32_t M = 1u << logM, N1 = 1u << logN1, tiles = N1 >> LOGT;
-    // runs differ by at most one tile: the first total - per_wg * gridDim.x workgroups take one more
-    const uint32_t extra = total - per_wg * gridDim.x;
-    uint32_t t = blockIdx.x * per_wg + (blockIdx.x < extra ? blockIdx.x : extra);
-    const uint32_t tend = t + per_wg + (blockIdx.x < extra ? 1u : 0u);
+    // runs differ by at most one tile: the first total - per_wg * nblk workgroups take one more
+    const uint32_t extra = total - per_wg * nblk;
+    uint32_t t = blk * per_wg + (blk < extra ? blk : extra);
+    const uint32_t tend = t + per_wg + (blk < extra ? 1u : 0u);
     if (t >= tend) return;
     load_stage_twiddles<LOGN2, NT>(tw, tb, tid0);
     if (CODEC)
@@ -409,16 +430,25 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b(const typename Cx<HA
     }
 }
 
+template <int LOGN2, int LOGE, bool CODEC, bool HALF>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b(const typename Cx<HALF>::One* __restrict__ mid, int logM,
+                                               typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride, Tables tb,
+                                               uint32_t* __restrict__ hist, uint32_t total, uint32_t per_wg,
+                                               float mid_scale, const uint32_t* __restrict__ only_if)
+{
+    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
+    fwd_b_workgroup<LOGN2, LOGE, CODEC, HALF>(blockIdx.x, gridDim.x, mid, logM, spec, sstride, tb, hist, total, per_wg, mid_scale);
+}
+
 // Inverse pass B: undo the split, inverse N2-point FFTs over k2, times conj W_M^(n2 k1).
 // PAIR: the spectrum is read in the paired order (the codec's own buffer), otherwise in natural bin order.
 // HALF (PAIR only): spectrum and intermediate are binary16 pairs.
 template <int LOGN2, int LOGE, bool PAIR, bool HALF>
-__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b(const typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride, int logM,
-                                               typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total,
-                                               uint32_t per_wg, float mid_scale, const uint32_t* __restrict__ only_if)
+__device__ __forceinline__ void inv_b_workgroup(uint32_t blk, uint32_t nblk, const typename Cx<HALF>::One* __restrict__ spec,
+                                                uint32_t sstride, int logM, typename Cx<HALF>::One* __restrict__ mid,
+                                                const Tables& tb, uint32_t total, uint32_t per_wg, float mid_scale)
 {
     static_assert(PAIR || !HALF, "binary16 storage is the codec's own");
-    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
     using One = typename Cx<HALF>::One;
     using Two = typename Cx<HALF>::Two;
     constexpr int NT = tile_lanes(LOGE), PER2 = kLanePairs;
@@ -431,10 +461,10 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b(const typename Cx<HA
     const int tid0 = threadIdx.x;
     const int logN1 = logM - LOGN2;
     const uint32_t M = 1u << logM, N1 = 1u << logN1, tiles = N1 >> LOGT;
-    // runs differ by at most one tile: the first total - per_wg * gridDim.x workgroups take one more
-    const uint32_t extra = total - per_wg * gridDim.x;
-    uint32_t t = blockIdx.x * per_wg + (blockIdx.x < extra ? blockIdx.x : extra);
-    const uint32_t tend = t + per_wg + (blockIdx.x < extra ? 1u : 0u);
+    // runs differ by at most one tile: the first total - per_wg * nblk workgroups take one more
+    const uint32_t extra = total - per_wg * nblk;
+    uint32_t t = blk * per_wg + (blk < extra ? blk : extra);
+    const uint32_t tend = t + per_wg + (blk < extra ? 1u : 0u);
     if (t >= tend) return;
     load_stage_twiddles<LOGN2, NT>(tw, tb, tid0);
     constexpr int DK = NT >> LOGP;
@@ -543,16 +573,23 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b(const typename Cx<HA
     }
 }
 
-// Inverse pass A: inverse N1-point FFTs over k1 for a tile of columns n2; writes the real samples.
-// `aligned`: bit 0 = output is 8-byte aligned, bit 1 = 16-byte aligned.
-template <int LOGN1, int LOGE, bool TABLE, bool HALF>
-__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HALF>::One* __restrict__ mid, int logM,
-                                               float* __restrict__ out, size_t n, Tables tb, int aligned, uint32_t total,
-                                               uint32_t per_wg, int glog, float gain, TableArg<TABLE> tab,
-                                               const uint32_t* __restrict__ only_if)
+template <int LOGN2, int LOGE, bool PAIR, bool HALF>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b(const typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride, int logM,
+                                               typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total,
+                                               uint32_t per_wg, float mid_scale, const uint32_t* __restrict__ only_if)
+{
+    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
+    inv_b_workgroup<LOGN2, LOGE, PAIR, HALF>(blockIdx.x, gridDim.x, spec, sstride, logM, mid, tb, total, per_wg, mid_scale);
+}
+
+// Inverse pass A: inverse N1-point FFTs over k1 for a tile of columns n2; writes the real samples to out[first .. first + n),
+// chunk by chunk.  `aligned`: bit 0 = `out` is 8-byte aligned, bit 1 = 16-byte aligned.
+template <int LOGN1, int LOGE, bool HALF>
+__device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<HALF>::One* __restrict__ mid, int logM,
+                                                float* __restrict__ out, size_t first, size_t n, const Tables& tb, int aligned,
+                                                uint32_t total, uint32_t per_wg, int glog, float gain)
 {
     using Two = typename Cx<HALF>::Two;
-    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
     constexpr int NT = tile_lanes(LOGE), PER2 = kLanePairs;
     constexpr int N1 = 1 << LOGN1, LOGT = LOGE - LOGN1, TA = 1 << LOGT, ELEMS = 1 << LOGE;
     constexpr int HP = N1 / 2, LOGHP = LOGN1 - 1;
@@ -563,7 +600,7 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HA
     const int tid0 = threadIdx.x;
     const uint32_t M = 1u << logM, N2 = M >> LOGN1, tiles = N2 >> LOGT;
     uint32_t t, tend;
-    if (!grouped_run(total, per_wg, glog, t, tend)) return;
+    if (!grouped_run(blk, total, per_wg, glog, t, tend)) return;
     const uint32_t tstep = 1u << glog;
     load_stage_twiddles<LOGN1, NT>(tw, tb, tid0);
 
@@ -600,17 +637,20 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HA
         run_fft_between<LOGN1, LOGT, NT, true, 0>(d, tw, tid, [&](int k) {
             if (k + 1 < PARTS) load_tile(more ? t + tstep : t, tid, more, k + 1);
         });
-        const Span sp = chunk_span<TABLE>(tab, t / tiles, ~(size_t)0, 2 * (size_t)M, n, aligned & 1);
+        const Span sp = chunk_span(first, n, t / tiles, 2 * (size_t)M, aligned & 1);
         const size_t cbase = sp.first;
         const uint32_t col0 = tile_in_chunk(t, tiles) << LOGT;
-        // whole chunk inside the output (per-tensor: the tensor fills its chunk, 16-byte aligned): no guards
-        if ((aligned & 2) && cbase + 2 * (size_t)M <= sp.limit && (!TABLE || (cbase & 3u) == 0)) {
-            float4* dst = reinterpret_cast<float4*>(out + cbase) + (col0 >> 1);
+        if ((aligned & 2) && (cbase & 3u) == 0 && (cbase + 2 * (size_t)M <= sp.limit || (sp.limit & 3u) == 0)) {
+            // 16-byte pieces, each inside the output or outside it
+            float4* dst = reinterpret_cast<float4*>(out + cbase);
+            const size_t left = sp.limit > cbase ? (sp.limit - cbase) >> 2 : 0;
+            const uint32_t quads = left < (size_t)(M >> 1) ? (uint32_t)left : M >> 1;
 #pragma unroll
             for (int q = 0; q < PER2; ++q) {
                 const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
+                const uint32_t i = (uint32_t)n1 * (N2 >> 1) + (col0 >> 1) + bp;
                 const float4 v = lds_load2<LOGT>(d, n1, 2 * bp);
-                dst[(uint32_t)n1 * (N2 >> 1) + bp] = make_float4(v.x * scale, v.y * scale, v.z * scale, v.w * scale);
+                if (i < quads) dst[i] = make_float4(v.x * scale, v.y * scale, v.z * scale, v.w * scale);
             }
         } else {
 #pragma unroll
@@ -628,6 +668,114 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HA
         fill(tid);
         __syncthreads();
     }
+}
+
+template <int LOGN1, int LOGE, bool HALF>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HALF>::One* __restrict__ mid, int logM,
+                                               float* __restrict__ out, size_t n, Tables tb, int aligned, uint32_t total,
+                                               uint32_t per_wg, int glog, float gain, const uint32_t* __restrict__ only_if)
+{
+    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
+    inv_a_workgroup<LOGN1, LOGE, HALF>(blockIdx.x, mid, logM, out, 0, n, tb, aligned, total, per_wg, glog, gain);
+}
+
+// ------------------------------------------------- tensors of different lengths ----
+// The four passes over the tensors of one LongTable: a workgroup finds the tensor it belongs to and does what a workgroup of
+// the uniform kernels does for a call with that tensor as its only chunk.  Rows and columns of any length share a launch
+// (the longest of either decides the LDS), so a call with tensors of seven lengths is four launches instead of 28, and short
+// tensors fill the compute units that the long ones leave.
+// Measured, ResNet-50's 161 tensors (49 of them long, of seven lengths), sender and receiver: seven launch sets on four
+// streams 579 us, one 467; the three long tensors of ResNet-20, all of 2^16, stay as they were.
+constexpr int log_columns(int logM) { return (logM + 1) / 2; }  // log2 N1
+constexpr int log_rows(int logM) { return logM / 2; }           // log2 N2
+constexpr int kLongMax = kMaxLogL - 1;                            // log2 M
+
+__device__ __forceinline__ uint32_t power_tiles(int logM, int loge) { return 1u << (logM - loge); }
+
+__global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a_long(const float* __restrict__ in, float2* __restrict__ mid, Tables tb,
+                                                   int aligned, uint32_t per_wg, uint32_t* __restrict__ zero_ptr,
+                                                   uint32_t zero_words, LongTable tab, LongStarts at)
+{
+    constexpr int NT = tile_lanes(kTileFA);
+    for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < zero_words; i += gridDim.x * NT) zero_ptr[i] = 0u;
+    const LongShare share = long_share(at);
+    const LongTensor& x = tab.t[share.tensor];
+    const int logM = x.logM;
+    auto run = [&](auto n1) __attribute__((always_inline)) {
+        constexpr int LOGN1 = decltype(n1)::value, GLOG = group_log(kTileFA, LOGN1);
+        fwd_a_workgroup<LOGN1, true, false>(share.blk, in, (size_t)x.goff, x.glen, logM, mid + long_mid(x), tb, aligned,
+                                            power_tiles(logM, kTileFA) >> GLOG, per_wg, GLOG, 1.0f);
+    };
+    switch (log_columns(logM)) {
+        case 8: return run(std::integral_constant<int, 8>{});
+        case 9: return run(std::integral_constant<int, 9>{});
+        case 10: return run(std::integral_constant<int, 10>{});
+        default: return run(std::integral_constant<int, 11>{});
+    }
+}
+
+template <int LOGE>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b_long(const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb,
+                                                uint32_t* __restrict__ hist, uint32_t per_wg, LongTable tab, LongStarts at)
+{
+    const LongShare share = long_share(at);
+    const LongTensor& x = tab.t[share.tensor];
+    const int logM = x.logM;
+    auto run = [&](auto n2) __attribute__((always_inline)) {
+        const uint32_t total = power_tiles(logM, LOGE), per = per_wg < total ? per_wg : total;
+        fwd_b_workgroup<decltype(n2)::value, LOGE, true, false>(share.blk, total / per, mid + long_mid(x), logM,
+                                                                spec + long_spec(x, share.tensor), 0u, tb,
+                                                                hist + (size_t)share.tensor * kHistBins, total, per, 1.0f);
+    };
+    const int rows = log_rows(logM);
+    if constexpr (LOGE == 13) {
+        if (rows == 7) return run(std::integral_constant<int, 7>{});
+        if (rows == 8) return run(std::integral_constant<int, 8>{});
+        if (rows == 9) return run(std::integral_constant<int, 9>{});
+    }
+    run(std::integral_constant<int, 10>{});
+}
+
+template <int LOGE>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b_long(const float2* __restrict__ spec, float2* __restrict__ mid, Tables tb,
+                                                uint32_t per_wg, LongTable tab, LongStarts at)
+{
+    const LongShare share = long_share(at);
+    const LongTensor& x = tab.t[share.tensor];
+    const int logM = x.logM;
+    auto run = [&](auto n2) __attribute__((always_inline)) {
+        const uint32_t total = power_tiles(logM, LOGE), per = per_wg < total ? per_wg : total;
+        inv_b_workgroup<decltype(n2)::value, LOGE, true, false>(share.blk, total / per, spec + long_spec(x, share.tensor), 0u, logM,
+                                                                mid + long_mid(x), tb, total, per, 1.0f);
+    };
+    const int rows = log_rows(logM);
+    if constexpr (LOGE == 13) {
+        if (rows == 7) return run(std::integral_constant<int, 7>{});
+        if (rows == 8) return run(std::integral_constant<int, 8>{});
+        if (rows == 9) return run(std::integral_constant<int, 9>{});
+    }
+    run(std::integral_constant<int, 10>{});
+}
+
+template <int LOGE>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a_long(const float2* __restrict__ mid, float* __restrict__ out, Tables tb,
+                                                int aligned, uint32_t per_wg, LongTable tab, LongStarts at)
+{
+    const LongShare share = long_share(at);
+    const LongTensor& x = tab.t[share.tensor];
+    const int logM = x.logM;
+    auto run = [&](auto n1) __attribute__((always_inline)) {
+        constexpr int LOGN1 = decltype(n1)::value, GLOG = group_log(LOGE, LOGN1);
+        inv_a_workgroup<LOGN1, LOGE, false>(share.blk, mid + long_mid(x), logM, out, (size_t)x.goff, x.glen, tb, aligned,
+                                            power_tiles(logM, LOGE) >> GLOG, per_wg, GLOG, 1.0f);
+    };
+    const int columns = log_columns(logM);
+    if constexpr (LOGE == 13) {
+        if (columns == 8) return run(std::integral_constant<int, 8>{});
+        if (columns == 9) return run(std::integral_constant<int, 9>{});
+    }
+    if (columns == 10) return run(std::integral_constant<int, 10>{});
+    run(std::integral_constant<int, 11>{});
 }
 
 // ---------------------------------------------------------------- launch ----
@@ -657,8 +805,6 @@ Grid persistent_grid(size_t total, uint32_t kMaxWgs = 512)
 
 // pass A: 2^glog workgroups (b, b+8, ...) share a run of aligned tile groups; per_wg counts tile groups and wgs
 // is a multiple of 8 * 2^glog
-// a pass A tile is 2^(loge - LOGN1) columns of 8 bytes; the tiles of a 128-byte line (two at least) are walked in step
-constexpr int group_log(int loge, int logn1) { return loge - logn1 >= 3 ? 1 : 2; }
 // most workgroups of a launch: the figures below are for two resident workgroups per compute unit
 constexpr uint32_t most_wgs(int loge, uint32_t with_two) { return loge == 13 ? with_two : with_two / 2; }
 constexpr uint32_t kPassAWgs = 2048;  // most workgroups the forward pass A is cut into
@@ -674,14 +820,14 @@ Grid grouped_grid(size_t groups, int glog, uint32_t kMaxWgs = 512)
 }
 
 // HALF launchers take the same buffer pointers; the kernels read them as binary16 pairs
-template <int LOGN1, bool TABLE, bool HALF>
+template <int LOGN1, bool HALF>
 hipError_t fwd_a(const float* in, size_t n, int logM, size_t C, float2* mid_f32, Tables t, int aligned,
-                 uint32_t* zero_ptr, uint32_t zero_words, const ChunkTable* tab, float in_scale, hipStream_t s,
+                 uint32_t* zero_ptr, uint32_t zero_words, float in_scale, hipStream_t s,
                  const uint32_t* only_if = nullptr)
 {
     constexpr int LOGE = kTileFA;
     const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN1)) * sizeof(float2);
-    auto kern = k_fwd_a<LOGN1, TABLE, HALF>;
+    auto kern = k_fwd_a<LOGN1, HALF>;
     auto* mid = reinterpret_cast<typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
@@ -690,8 +836,7 @@ hipError_t fwd_a(const float* in, size_t n, int logM, size_t C, float2* mid_f32,
     // measured: 143 us against 149 with 512; a stand-by launch (only_if) takes the small grid, which leaves sooner
     const Grid g = grouped_grid(total >> glog, glog, most_wgs(LOGE, only_if ? 512 : kPassAWgs));
     FFTSP_LAUNCH(only_if ? "rfft_pass_a_standby" : "rfft_pass_a", kern, dim3(g.wgs), dim3(tile_lanes(LOGE)), lds, s, in, n, logM, mid,
-                 t, aligned, (uint32_t)(total >> glog), g.per_wg, glog, zero_ptr, zero_words, table_arg<TABLE>(tab),
-                 in_scale, only_if);
+                 t, aligned, (uint32_t)(total >> glog), g.per_wg, glog, zero_ptr, zero_words, in_scale, only_if);
     return hipGetLastError();
 }
 
@@ -729,12 +874,12 @@ hipError_t inv_b_tiled(const float2* spec_f32, uint32_t sstride, int logM, size_
     return hipGetLastError();
 }
 
-template <int LOGN1, int LOGE, bool TABLE, bool HALF>
+template <int LOGN1, int LOGE, bool HALF>
 hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
-                 const ChunkTable* tab, hipStream_t s, const uint32_t* only_if)
+                 hipStream_t s, const uint32_t* only_if)
 {
     const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN1)) * sizeof(float2);
-    auto kern = k_inv_a<LOGN1, LOGE, TABLE, HALF>;
+    auto kern = k_inv_a<LOGN1, LOGE, HALF>;
     auto* mid = reinterpret_cast<const typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
@@ -742,7 +887,7 @@ hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, si
     constexpr int glog = group_log(LOGE, LOGN1);
     const Grid g = grouped_grid(total >> glog, glog, most_wgs(LOGE, 512));
     FFTSP_LAUNCH(only_if ? "irfft_pass_a_standby" : "irfft_pass_a", kern, dim3(g.wgs), dim3(tile_lanes(LOGE)), lds, s, mid, logM, out,
-                 n, t, aligned, (uint32_t)(total >> glog), g.per_wg, glog, gain, table_arg<TABLE>(tab), only_if);
+                 n, t, aligned, (uint32_t)(total >> glog), g.per_wg, glog, gain, only_if);
     return hipGetLastError();
 }
 
@@ -763,13 +908,70 @@ hipError_t inv_b(const float2* spec, uint32_t sstride, int logM, size_t C, float
         if (wide_tiles(C, logM)) return inv_b_tiled<LOGN2, 14, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
     return inv_b_tiled<LOGN2, 13, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
 }
-template <int LOGN1, bool TABLE, bool HALF>
+template <int LOGN1, bool HALF>
 hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
-                 const ChunkTable* tab, hipStream_t s, const uint32_t* only_if = nullptr)
+                 hipStream_t s, const uint32_t* only_if = nullptr)
 {
     if constexpr (LOGN1 >= kWideMin)
-        if (wide_tiles(C, logM)) return inv_a_tiled<LOGN1, 14, TABLE, HALF>(mid, logM, C, out, n, t, aligned, gain, tab, s, only_if);
-    return inv_a_tiled<LOGN1, 13, TABLE, HALF>(mid, logM, C, out, n, t, aligned, gain, tab, s, only_if);
+        if (wide_tiles(C, logM)) return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    return inv_a_tiled<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+}
+
+// Launches of the tensors i in [first, count) of a batch.  The tensors come shortest first, so those whose rows or columns
+// ask for the larger tile are the last ones; the rule for taking it is the one of the uniform calls.  They are then a launch
+// of their own, with two tails instead of one.  On ResNet-50's tensors (half of the samples in rows, four fifths in columns of
+// 2^10 and more) that pays in the forward second pass (92 -> 87 us) and the inverse first one (80 -> 70), not in the inverse
+// second one (72 -> 84), which takes it only when most of the samples ask for it.
+template <typename Logs>
+uint32_t first_wide(const LongBatch& b, Logs&& logs, bool most)
+{
+    uint32_t i = b.count;
+    size_t tiles = 0;
+    for (; i > 0 && logs(b.tab.t[i - 1].logM) >= kWideMin; --i) tiles += (size_t)1 << (b.tab.t[i - 1].logM - 14);
+    const bool enough = tiles >= kWideTiles && (!most || 8 * tiles >= 7 * ((size_t)b.units << (kLongUnitLog - 14)));
+    return enough ? i : b.count;
+}
+// starts of the workgroups' shares; wgs(tensor) workgroups each.  Returns the total.
+template <typename Wgs>
+uint32_t long_starts(const LongBatch& b, uint32_t first, uint32_t end, LongStarts* at, Wgs&& wgs)
+{
+    at->first = first;
+    at->count = end - first;
+    uint32_t sum = 0;
+    for (uint32_t i = first; i < end; ++i) {
+        at->at[i - first] = (uint16_t)sum;
+        sum += wgs(b.tab.t[i]);
+    }
+    return sum;
+}
+// tiles per workgroup (a power of two) that keep a launch over tensors [first, end) to about `most` workgroups
+uint32_t long_run(const LongBatch& b, uint32_t first, uint32_t end, int loge, uint32_t most)
+{
+    size_t tiles = 0;
+    for (uint32_t i = first; i < end; ++i) tiles += (size_t)1 << (b.tab.t[i].logM - loge);
+    uint32_t run = 1;
+    while (tiles / (2 * run) >= most) run *= 2;
+    return run;
+}
+// pass(tile size, first tensor, end): those with small tiles, then the others
+template <typename Logs, typename Pass>
+hipError_t by_tile_size(const LongBatch& b, Logs&& logs, bool most, Pass&& pass)
+{
+    const uint32_t wide = first_wide(b, logs, most);
+    hipError_t e = hipSuccess;
+    if (wide > 0) e = pass(std::integral_constant<int, 13>{}, 0u, wide);
+    if (e == hipSuccess && wide < b.count) e = pass(std::integral_constant<int, 14>{}, wide, b.count);
+    return e;
+}
+constexpr int kLongLogN = log_columns(kLongMax);  // the longest row or column
+// LDS of a pass: the tile and the stage twiddles
+constexpr size_t long_lds(int loge) { return ((size_t)(1 << loge) + (1 << kLongLogN)) * sizeof(float2); }
+// workgroups of a tensor in a pass A (see grouped_grid)
+uint32_t pass_a_wgs(const LongTensor& x, int loge, uint32_t per_wg)
+{
+    const int glog = group_log(loge, log_columns(x.logM));
+    const uint32_t groups = (1u << (x.logM - loge)) >> glog, used = (groups + per_wg - 1) / per_wg, unit = 8u << glog;
+    return (((used << glog) + unit - 1) / unit) * unit;
 }
 
 }  // namespace
@@ -782,10 +984,9 @@ int fft_pair_log(int logL)
 
 hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spec, uint32_t sstride, float2* mid,
                        Tables t, uint32_t* hist, uint32_t* zero_ptr, size_t zero_words, int pair_spec,
-                       int* pair_log, const ChunkTable* tab, hipStream_t s, const uint32_t* only_if)
+                       int* pair_log, hipStream_t s, const uint32_t* only_if)
 {
     if (pair_log) *pair_log = 0;
-    if (tab && C > (size_t)kMaxTableChunks) return hipErrorInvalidValue;
     if (zero_words > 0xffffffffu) return hipErrorInvalidValue;
     if (!hist) zero_words = 0;
     const int logM = logL - 1;
@@ -798,9 +999,7 @@ hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spe
     if ((hist != nullptr) != (pair_spec != 0)) return hipErrorInvalidValue;
     const int logN1 = (logM + 1) / 2, logN2 = logM / 2;
     hipError_t e;
-#define FWD_A(p)                                                                              \
-    (tab ? fwd_a<p, true, false>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, tab, 1.0f, s, only_if)      \
-         : fwd_a<p, false, false>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, nullptr, 1.0f, s, only_if))
+#define FWD_A(p) fwd_a<p, false>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, 1.0f, s, only_if)
     switch (logN1) {
         case 8: e = FWD_A(8); break;
         case 9: e = FWD_A(9); break;
@@ -830,9 +1029,8 @@ hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spe
 }
 
 hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL, size_t C, float* out, float2* mid,
-                        Tables t, int pair_spec, float gain, const ChunkTable* tab, hipStream_t s, const uint32_t* only_if)
+                        Tables t, int pair_spec, float gain, hipStream_t s, const uint32_t* only_if)
 {
-    if (tab && C > (size_t)kMaxTableChunks) return hipErrorInvalidValue;
     const int logM = logL - 1;
     const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
@@ -858,9 +1056,7 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
         }
     }
     if (e != hipSuccess) return e;
-#define INV_A(p)                                                          \
-    (tab ? inv_a<p, true, false>(mid, logM, C, out, n, t, aligned, gain, tab, s, only_if) \
-         : inv_a<p, false, false>(mid, logM, C, out, n, t, aligned, gain, nullptr, s, only_if))
+#define INV_A(p) inv_a<p, false>(mid, logM, C, out, n, t, aligned, gain, s, only_if)
     switch (logN1) {
         case 8: return INV_A(8);
         case 9: return INV_A(9);
@@ -869,6 +1065,65 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
         default: return hipErrorInvalidValue;
     }
 #undef INV_A
+}
+
+hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, float2* mid, Tables t, uint32_t* hist,
+                            uint32_t* zero_ptr, size_t zero_words, hipStream_t s)
+{
+    if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors || zero_words > 0xffffffffu) return hipErrorInvalidValue;
+    const uintptr_t addr = reinterpret_cast<uintptr_t>(in);
+    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    LongStarts at;
+    hipError_t e = set_lds(k_fwd_a_long, long_lds(kTileFA));
+    if (e != hipSuccess) return e;
+    const uint32_t run = long_run(b, 0, b.count, kTileFA, kPassAWgs);
+    const uint32_t wgs = long_starts(b, 0, b.count, &at, [&](const LongTensor& x) { return pass_a_wgs(x, kTileFA, run); });
+    FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long, dim3(wgs), dim3(tile_lanes(kTileFA)), long_lds(kTileFA), s, in, mid, t, aligned, run,
+                 zero_ptr, (uint32_t)zero_words, b.tab, at);
+    return by_tile_size(b, log_rows, false, [&](auto size, uint32_t first, uint32_t end) {
+        constexpr int LOGE = decltype(size)::value;
+        const size_t lds = long_lds(LOGE) + kHistLdsWords * sizeof(uint32_t);
+        const hipError_t err = set_lds(k_fwd_b_long<LOGE>, lds);
+        if (err != hipSuccess) return err;
+        const uint32_t per = long_run(b, first, end, LOGE, most_wgs(LOGE, 512));
+        const uint32_t g = long_starts(b, first, end, &at, [&](const LongTensor& x) {
+            const uint32_t tiles = 1u << (x.logM - LOGE);
+            return tiles > per ? tiles / per : 1u;
+        });
+        FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), lds, s, mid, spec, t, hist, per, b.tab, at);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out, float2* mid, Tables t, hipStream_t s)
+{
+    if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors) return hipErrorInvalidValue;
+    const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
+    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    LongStarts at;
+    const hipError_t e = by_tile_size(b, log_rows, true, [&](auto size, uint32_t first, uint32_t end) {
+        constexpr int LOGE = decltype(size)::value;
+        const hipError_t err = set_lds(k_inv_b_long<LOGE>, long_lds(LOGE));
+        if (err != hipSuccess) return err;
+        const uint32_t per = long_run(b, first, end, LOGE, most_wgs(LOGE, 1536));
+        const uint32_t g = long_starts(b, first, end, &at, [&](const LongTensor& x) {
+            const uint32_t tiles = 1u << (x.logM - LOGE);
+            return tiles > per ? tiles / per : 1u;
+        });
+        FFTSP_LAUNCH("irfft_pass_b", k_inv_b_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), long_lds(LOGE), s, spec, mid, t, per, b.tab, at);
+        return hipGetLastError();
+    });
+    if (e != hipSuccess) return e;
+    return by_tile_size(b, log_columns, false, [&](auto size, uint32_t first, uint32_t end) {
+        constexpr int LOGE = decltype(size)::value;
+        const hipError_t err = set_lds(k_inv_a_long<LOGE>, long_lds(LOGE));
+        if (err != hipSuccess) return err;
+        const uint32_t per = long_run(b, first, end, LOGE, most_wgs(LOGE, 512));
+        const uint32_t g = long_starts(b, first, end, &at, [&](const LongTensor& x) { return pass_a_wgs(x, LOGE, per); });
+        FFTSP_LAUNCH("irfft_pass_a", k_inv_a_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), long_lds(LOGE), s, mid, out, t, aligned, per,
+                     b.tab, at);
+        return hipGetLastError();
+    });
 }
 
 // Half-precision variant (two-pass sizes, the codec's own buffers): the same four kernels with the intermediate
@@ -892,7 +1147,7 @@ hipError_t launch_rfft_half(const float* in, size_t n, int logL, size_t C, void*
     // that it sits where the caller's scale put the spectrum.  Powers of two: exact.
     const float lift = std::ldexp(1.0f, logN2 / 2);
 #define FWD_A(p) \
-    fwd_a<p, false, true>(in, n, logM, C, md, t, aligned, zero_ptr, (uint32_t)zero_words, nullptr, in_scale * lift, s)
+    fwd_a<p, true>(in, n, logM, C, md, t, aligned, zero_ptr, (uint32_t)zero_words, in_scale * lift, s)
     switch (logN1) {
         case 7: e = FWD_A(7); break;
         case 8: e = FWD_A(8); break;
@@ -934,7 +1189,7 @@ hipError_t launch_irfft_half(const void* spec, uint32_t sstride, size_t n, int l
         default: return hipErrorInvalidValue;
     }
     if (e != hipSuccess) return e;
-#define INV_A(p) inv_a<p, false, true>(md, logM, C, out, n, t, aligned, gain * lift, nullptr, s)
+#define INV_A(p) inv_a<p, true>(md, logM, C, out, n, t, aligned, gain * lift, s)
     switch (logN1) {
         case 7: return INV_A(7);
         case 8: return INV_A(8);

@@ -274,27 +274,11 @@ struct Span {
     size_t first, limit;
     int pairs;
 };
-template <bool TABLE>
-__device__ __forceinline__ Span chunk_span(const TableArg<TABLE>& tab, size_t c, size_t C, size_t chunk_len, size_t n,
-                                           int aligned8)
+// what a launch covers: samples [first, first + count), cut into chunks
+__device__ __forceinline__ Span chunk_span(size_t first, size_t count, size_t c, size_t chunk_len, int aligned8)
 {
-    Span sp;
-    if constexpr (TABLE) {
-        if (c < C) {
-            sp.first = tab.t.goff[c];
-            sp.limit = sp.first + tab.t.glen[c];
-        } else {
-            sp.first = sp.limit = 0;
-        }
-        sp.pairs = aligned8 && !(sp.first & 1u);
-    } else {
-        sp.first = c * chunk_len;
-        sp.limit = n;
-        sp.pairs = aligned8;
-    }
-    return sp;
+    return Span{first + c * chunk_len, first + count, aligned8 && !(first & 1u)};
 }
-
 
 // X[k] from a = Z[k], b = Z[M-k], w = W_L^k   (0 < k < M)
 __device__ __forceinline__ float2 split_fwd(float2 a, float2 b, float2 w)
@@ -398,9 +382,9 @@ __device__ __forceinline__ uint32_t tile_in_chunk(uint32_t tile, uint32_t tiles)
 // b, b+8, ... share an L2: 2^glog of them walk the members of the same run of aligned tile groups in step, and
 // each line crosses the fabric once.  The workgroup's tiles are t, t+2^glog, ... < tend.  Returns false if this
 // workgroup has nothing to do.
-__device__ __forceinline__ bool grouped_run(uint32_t groups, uint32_t per_wg, int glog, uint32_t& t, uint32_t& tend)
+__device__ __forceinline__ bool grouped_run(uint32_t b, uint32_t groups, uint32_t per_wg, int glog, uint32_t& t, uint32_t& tend)
 {
-    const uint32_t b = blockIdx.x, x = b & 7u, y = b >> 3, h = y & ((1u << glog) - 1u);
+    const uint32_t x = b & 7u, y = b >> 3, h = y & ((1u << glog) - 1u);
     const uint32_t rho = ((y >> glog) << 3) + x;  // which group of workgroups
     const uint32_t p0 = rho * per_wg;
     if (p0 >= groups) return false;

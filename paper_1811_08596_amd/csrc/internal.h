@@ -98,15 +98,24 @@ static inline bool fused_shape(int logL, size_t C)
     return logM >= 15 && logM <= 19 && (C << logL) * 4 >= kFusedScratchBytes;
 }
 
+// The receiver's kernels store one verdict per record, and the call's first kernel leaves this note in words 2..4 of the
+// control block: how many there are, where (in words from the workspace's start), and a magic word.  So no earlier kernel has
+// to clear a status word before a record raises it.  fftsp_device_status looks at both.
+struct StatusNote {
+    uint32_t count, offset;
+};
+constexpr uint32_t kStatusNoteMagic = 0x46535653u;
+
 // Where everything lives inside the caller's workspace (byte offsets, 256-aligned).
 struct Workspace {
     size_t status;    // u32[1024] control block: word 0 = device status, word 1 = "the fused transform gave up",
-                      //           words 2..4 = where per-record verdicts are (chunk.h),
+                      //           words 2..4 = where per-record verdicts are,
                       //           from word 32 on the hand-over counters of the fused kernels (fused.hip)
     size_t hist;      // u32[C][kHistBins]         (directly after status: one fill zeroes both)
-    size_t sel;       // u32[C][8]  bstar, need, tau, quota, pbase, vmax, -, decode verdict
+    size_t sel;       // u32[C][8]  bstar, need, tau, quota, pbase, vmax, -, -
     size_t tinfo;     // u32[C][Tn][4]  n_def, vmax_def, n_cand, -
     size_t tscan;     // u32[C][Tn][2]  first rank of the tile, equal-key count before the tile
+                      //                (receiver: u32[C] verdicts)
     size_t cand;      // uint2[C][Tn*kTile]  (key, max component bits) of threshold-bucket bins, tile-ordered
                       //                     (shares its bytes with mid)
     size_t prefix;    // u32[C][ceil(W/16)]  set bits before each group of 16 bitmap words (decode)
@@ -117,28 +126,55 @@ struct Workspace {
 
 static inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Per-tensor mode: the chunks of one launch are separate tensors of the same (padded) length, so where a chunk's
-// samples and its record live is a table instead of c*L and c*S.  The table travels by value as a kernel argument
-// (no host-to-device copy to order against the stream); longer lists are cut into launches of kMaxTableChunks.
-constexpr int kMaxTableChunks = 64;
-struct ChunkTable {
-    uint64_t goff[kMaxTableChunks];  // element offset of the chunk's first sample in the gradient
-    uint64_t roff[kMaxTableChunks];  // byte offset of the chunk's record from the first record of the launch
-    uint32_t glen[kMaxTableChunks];  // samples present; the rest of the chunk is zero
+// Per-tensor mode, tensors longer than one workgroup takes: every launch covers up to kMaxLongTensors of them, each a
+// single chunk of its own length 2^(logM+1).  What the kernels need to know about them travels by value as a kernel
+// argument (no host-to-device copy to order against the stream).
+constexpr int kMaxLongTensors = 64;
+constexpr int kLongUnitLog = 15;  // the shortest has 2^15 complex values; their work areas are counted in these
+struct LongTensor {
+    uint64_t goff;    // element offset of its first sample in the gradient
+    uint64_t roff;    // byte offset of its record from the first record of the stream
+    uint32_t glen;    // samples present; the rest of the chunk is zero
+    uint32_t kept;    // kept bins
+    uint32_t stride;  // record bytes
+    uint16_t base;    // units of 2^kLongUnitLog complex values of the launch's tensors before it
+    uint8_t logM, pad;
 };
-// kernel parameter that is a ChunkTable in per-tensor launches and nothing otherwise
+// first workgroup of every tensor's share of a launch over tensors first .. first + count - 1
+struct LongStarts {
+    uint16_t at[kMaxLongTensors];
+    uint32_t first, count;
+};
+struct LongTable {
+    LongTensor t[kMaxLongTensors];
+    LongStarts tiles;  // the codec kernels' share: a workgroup per tile of bins
+};
+static_assert(sizeof(LongTable) + sizeof(LongStarts) + 256 <= 4096, "kernel arguments are at most 4 KiB");
+// a launch set of the long tensors (host)
+struct LongBatch {
+    LongTable tab;
+    uint32_t count, units;  // tensors, units of work area
+};
+// where tensor i of a launch finds its part of the work areas
+__host__ __device__ inline size_t long_mid(const LongTensor& t) { return (size_t)t.base << kLongUnitLog; }
+__host__ __device__ inline size_t long_spec(const LongTensor& t, uint32_t i) { return long_mid(t) + 16u * i; }
+__host__ __device__ inline uint32_t long_tile(const LongTensor& t, uint32_t i) { return ((uint32_t)t.base << (kLongUnitLog - 11)) + i; }
+__host__ __device__ inline uint32_t long_group(const LongTensor& t, uint32_t i) { return ((uint32_t)t.base << (kLongUnitLog - 9)) + i; }
+__host__ __device__ inline int long_pair_log(const LongTensor& t) { return (t.logM + 1) / 2; }
+static_assert(kTile == 1 << 11, "tiles of a tensor: M / 2^11 whole ones and one for the Nyquist bin");
+// kernel parameter that is a LongTable in per-tensor launches and nothing otherwise
 template <bool TABLE>
 struct TableArg {
 };
 template <>
 struct TableArg<true> {
-    ChunkTable t;
+    LongTable t;
 };
 template <bool TABLE>
-inline TableArg<TABLE> table_arg(const ChunkTable* tab)
+inline TableArg<TABLE> table_arg(const LongBatch* b)
 {
     TableArg<TABLE> a;
-    if constexpr (TABLE) a.t = *tab;
+    if constexpr (TABLE) a.t = b->tab;
     return a;
 }
 
@@ -187,6 +223,25 @@ static inline Workspace make_workspace(size_t C, uint32_t L, int time_domain = 0
     return w;
 }
 
+// the same for a launch set of long tensors
+static inline Workspace make_long_workspace(const LongBatch& b)
+{
+    Workspace w;
+    const size_t values = (size_t)b.units << kLongUnitLog, tiles = (values >> 11) + b.count, groups = (values >> 9) + b.count;
+    size_t off = 0;
+    w.status = off; off += kControlBytes;
+    w.hist = off;   off = align256(off + b.count * (size_t)kHistBins * 4);
+    w.sel = off;    off = align256(off + b.count * 8 * 4);
+    w.tinfo = off;  off = align256(off + tiles * 16);
+    w.tscan = off;  off = align256(off + tiles * 8);
+    w.cand = off;
+    w.mid = off;    off = align256(off + tiles * kTile * 8);
+    w.prefix = off; off = align256(off + groups * 4);
+    w.spec = off;   off = align256(off + (values + 16 * (size_t)b.count) * 8);
+    w.total = off;
+    return w;
+}
+
 // Where bin j of a chunk sits inside the chunk's spectrum.  pair_log = 0: natural order (the layout of the
 // stage-level entry points).  pair_log = log2(N1) > 0: the two-pass FFT's own "paired" order, in which each run
 // of N1 bins stores bin k1 next to bin N1-k1 (position 2*k1 / 2*k1+1; position 1 holds k1 = N1/2), so that the
@@ -226,17 +281,20 @@ hipError_t get_tables(Tables* out);
 // hist (optional): u32[C][kHistBins]; the kernels clear zero_words words at zero_ptr (covering hist and the status
 // words) and fill hist.  pair_spec != 0 (exactly when hist is given): the spectrum is written in paired order and
 // *pair_log receives log2(N1), otherwise 0.
-// tab != nullptr: per-tensor launch, chunk c is in[tab->goff[c] .. + tab->glen[c]) (n is not used)
 // only_if (optional, two-pass sizes): device word; the kernels return at once unless it is non-zero
 hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spec, uint32_t sstride, float2* mid,
                        Tables t, uint32_t* hist, uint32_t* zero_ptr, size_t zero_words, int pair_spec,
-                       int* pair_log, const ChunkTable* tab, hipStream_t s, const uint32_t* only_if = nullptr);
+                       int* pair_log, hipStream_t s, const uint32_t* only_if = nullptr);
 // log2(N1) of the two-pass factorisation for chunk length 2^logL (2^15 and up; 2^15 in the half-precision variant only)
 int fft_pair_log(int logL);
 // pair_spec != 0: the spectrum is in paired order; the output is gain/L times the plain sum
 hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL, size_t C, float* out, float2* mid,
-                        Tables t, int pair_spec, float gain, const ChunkTable* tab, hipStream_t s,
-                        const uint32_t* only_if = nullptr);
+                        Tables t, int pair_spec, float gain, hipStream_t s, const uint32_t* only_if = nullptr);
+// The same for a launch set of tensors of different lengths, paired order; spectra and intermediates lie as long_spec and
+// long_mid say.
+hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, float2* mid, Tables t, uint32_t* hist,
+                            uint32_t* zero_ptr, size_t zero_words, hipStream_t s);
+hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out, float2* mid, Tables t, hipStream_t s);
 
 // Fused two-pass transforms whose intermediate stays in the L2 caches (fused.hip).  They need the control block
 // zeroed beforehand (launch_zero_control) and the per-pass kernels enqueued behind them with only_if = the give-up
@@ -276,7 +334,8 @@ struct CodecArgs {
     uint32_t word3;     // 4th word of every record header
     uint32_t static_vmax;  // != 0: bit pattern of the caller's fixed range maximum (instead of the largest survivor)
     uint32_t sstride;   // distance between consecutive chunks' spectra, in complex bins
-    const ChunkTable* tab;  // per-tensor launches: where each chunk's record lives (host pointer); else nullptr
+    const LongBatch* tab;  // per-tensor launches: the tensors (host pointer), C of them; else nullptr.  C, L, k, S, word3
+                           // and sstride are then not used
     int time_domain;    // != 0: records describe the gradient's samples; `spec` of the launchers is the gradient
     size_t n;           // time domain: samples in the gradient (the last chunk may be short)
     int half;           // != 0: `spec` holds binary16 pairs (half-precision variant; two-pass chunk lengths only)
@@ -303,14 +362,13 @@ static inline PeerWorkspace make_peer_workspace(const Workspace& w, size_t C, ui
 hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_base, uint8_t* records,
                          uint8_t* ws_base, const Workspace& w, int hist_ready, hipStream_t s);
 
-// clears the device status word (for callers that decode a stream as several concurrent launch sets)
-hipError_t launch_clear_status(uint8_t* ws_base, const Workspace& w, hipStream_t s);
-
-// reset_status != 0: this call also clears the device status word (first record set of a stream)
+// verdicts: u32[C].  note (optional): this launch clears the control block and leaves the note there (the first one of a
+// call, or the only one).
 hipError_t launch_decode(const uint8_t* stream_base, const uint8_t* records, const CodecArgs& a, float* spec,
-                         uint8_t* ws_base, const Workspace& w, int check_header, int reset_status, hipStream_t s);
+                         uint8_t* ws_base, const Workspace& w, int check_header, uint32_t* verdicts, const StatusNote* note,
+                         hipStream_t s);
 
-// npeers streams (each: 64-byte header + records) summed bin by bin, in list order, into spec; clears the status word
+// npeers streams (each: 64-byte header + records) summed bin by bin, in list order, into spec
 hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecArgs& a, float* spec, uint8_t* ws_base,
                                const Workspace& w, const PeerWorkspace& pw, hipStream_t s);
 
