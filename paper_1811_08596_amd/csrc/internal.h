@@ -227,7 +227,7 @@ static inline Workspace make_workspace(size_t C, uint32_t L, int time_domain = 0
 static inline Workspace make_long_workspace(const LongBatch& b)
 {
     Workspace w;
-    const size_t values = (size_t)b.units << kLongUnitLog, tiles = (values >> 11) + b.count, groups = (values >> 9) + b.count;
+    const size_t values = (size_t)b.units << kLongUnitLog, tiles = (values >> 11) + b.count;
     size_t off = 0;
     w.status = off; off += kControlBytes;
     w.hist = off;   off = align256(off + b.count * (size_t)kHistBins * 4);
@@ -236,7 +236,7 @@ static inline Workspace make_long_workspace(const LongBatch& b)
     w.tscan = off;  off = align256(off + tiles * 8);
     w.cand = off;
     w.mid = off;    off = align256(off + tiles * kTile * 8);
-    w.prefix = off; off = align256(off + groups * 4);
+    w.prefix = off; off = align256(off + ((values >> 5) + b.count) * 4);  // as above: more than the groups take
     w.spec = off;   off = align256(off + (values + 16 * (size_t)b.count) * 8);
     w.total = off;
     return w;
