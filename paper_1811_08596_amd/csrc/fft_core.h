@@ -10,8 +10,9 @@ __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
 // Where two products meet, one of them ends up inside a fused multiply-add.  Left to the compiler, which one depends on
 // the kernel around it, and kernels that must agree bit for bit would not: chunk.hip, where several kernels compute the
-// same transform, asks for the fused operations to be written out (FFTSP_FMA_WRITTEN_OUT).  The two-pass kernels are the
-// only ones of their lengths and keep the compiler's choice, and with it the results they have always given.
+// same transform, asks for the fused operations to be written out (FFTSP_FMA_WRITTEN_OUT), as they came out in the kernels
+// of these lengths that it replaced.  The two-pass kernels are the only ones of their lengths and keep the compiler's
+// choice.  Either way spectra, and with them what is kept and how it is coded, are bit for bit what they have always been.
 #ifdef FFTSP_FMA_WRITTEN_OUT
 __device__ __forceinline__ float prod_sum(float a, float b, float c, float d) { return __fmaf_rn(a, b, c * d); }
 __device__ __forceinline__ float prod_diff(float a, float b, float c, float d) { return __fmaf_rn(a, b, -(c * d)); }
@@ -21,7 +22,11 @@ __device__ __forceinline__ float prod_diff(float a, float b, float c, float d) {
 #endif
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 {
+#ifdef FFTSP_FMA_WRITTEN_OUT
+    return make_float2(prod_diff(a.x, b.x, a.y, b.y), prod_sum(a.y, b.x, a.x, b.y));
+#else
     return make_float2(prod_diff(a.x, b.x, a.y, b.y), prod_sum(a.x, b.y, a.y, b.x));
+#endif
 }
 // a * conj(b)
 __device__ __forceinline__ float2 cmulc(float2 a, float2 b)
@@ -127,19 +132,34 @@ __device__ __forceinline__ void bf16(float2* v)
         for (int k0 = 0; k0 < 4; ++k0) y[n0][k0] = t[k0];
     }
     // W16^m = (cos(m pi/8), -sin(m pi/8)), conjugated for the inverse
-    auto rot = [](float2 a, float wr, float wi) {  // a * (wr + i wi) forward, a * (wr - i wi) inverse
-        return INV ? make_float2(prod_sum(a.x, wr, a.y, wi), prod_diff(a.y, wr, a.x, wi))
-                   : make_float2(prod_diff(a.x, wr, a.y, wi), prod_sum(a.y, wr, a.x, wi));
+#ifdef FFTSP_FMA_WRITTEN_OUT
+    auto rot = [&](int n0, int k0, float wr, float wi) __attribute__((always_inline)) {
+        const float x = y[n0][k0].x, z = y[n0][k0].y;
+        if (INV)
+            y[n0][k0] = make_float2(n0 == 1 || (n0 == 3 && k0 == 1) ? prod_sum(x, wr, z, wi) : prod_sum(z, wi, x, wr),
+                                    n0 == 1 && k0 == 2 ? prod_sum(x, -wi, z, wr) : prod_diff(z, wr, x, wi));
+        else if (wi < 0.f && !(n0 == 3 && k0 == 2))
+            y[n0][k0] = make_float2(prod_sum(z, -wi, x, wr), prod_sum(z, wr, x, wi));
+        else
+            y[n0][k0] = make_float2(prod_diff(x, wr, z, wi), prod_sum(x, wi, z, wr));
     };
-    y[1][1] = rot(y[1][1], c1, -s1);   // W^1
-    y[1][2] = rot(y[1][2], h, -h);     // W^2
-    y[1][3] = rot(y[1][3], s1, -c1);   // W^3
-    y[2][1] = rot(y[2][1], h, -h);     // W^2
+#else
+    auto rot = [&](int n0, int k0, float wr, float wi) __attribute__((always_inline)) {
+        const float2 a = y[n0][k0];
+        y[n0][k0] = INV ? make_float2(prod_sum(a.x, wr, a.y, wi), prod_diff(a.y, wr, a.x, wi))
+                        : make_float2(prod_diff(a.x, wr, a.y, wi), prod_sum(a.y, wr, a.x, wi));
+    };
+#endif
+    // y *= wr + i wi, forward; its conjugate, inverse
+    rot(1, 1, c1, -s1);                // W^1
+    rot(1, 2, h, -h);                  // W^2
+    rot(1, 3, s1, -c1);                // W^3
+    rot(2, 1, h, -h);                  // W^2
     y[2][2] = rot90<INV>(y[2][2]);     // W^4 = -i
-    y[2][3] = rot(y[2][3], -h, -h);    // W^6
-    y[3][1] = rot(y[3][1], s1, -c1);   // W^3
-    y[3][2] = rot(y[3][2], -h, -h);    // W^6
-    y[3][3] = rot(y[3][3], -c1, s1);   // W^9
+    rot(2, 3, -h, -h);                 // W^6
+    rot(3, 1, s1, -c1);                // W^3
+    rot(3, 2, -h, -h);                 // W^6
+    rot(3, 3, -c1, s1);                // W^9
 #pragma unroll
     for (int k0 = 0; k0 < 4; ++k0) {
         float2 t[4] = {y[0][k0], y[1][k0], y[2][k0], y[3][k0]};
