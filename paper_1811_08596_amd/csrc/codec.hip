@@ -196,20 +196,17 @@ __global__ __launch_bounds__(NT) void k_hist_samples(const float* __restrict__ i
     }
 }
 
-// inclusive scan over the 256 lanes of a workgroup; tmp has 4 entries
-__device__ __forceinline__ uint32_t block_scan_incl_256(uint32_t v, uint32_t* tmp)
+// inclusive scan over the NW waves of a workgroup; tmp has NW entries
+template <int NW>
+__device__ __forceinline__ uint32_t block_scan_incl(uint32_t v, uint32_t* tmp)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = __shfl_up(x, o, 64);
-        if (lane >= o) x += u;
-    }
+    const uint32_t x = wave_scan_incl(v);
     if (lane == 63) tmp[wave] = x;
     __syncthreads();
     uint32_t add = 0;
-    for (int w = 0; w < wave; ++w) add += tmp[w];
+#pragma unroll
+    for (int w = 0; w < NW - 1; ++w) add += w < wave ? tmp[w] : 0u;
     __syncthreads();
     return x + add;
 }
@@ -255,48 +252,54 @@ __device__ __forceinline__ Place place_of_tile(const Shape& u, const TableArg<TA
     }
 }
 
-// Per chunk: the bucket b* holding the k-th largest key, and how many of its bins are still needed.
+// The bucket b* holding the k-th largest key of a chunk, and how many of its bins are still needed; by a whole workgroup.
+struct Bucket {
+    uint32_t star, need;
+};
+__device__ __forceinline__ Bucket find_bucket(const uint32_t* __restrict__ hist, uint32_t k)
+{
+    __shared__ uint32_t tmp[NT / 64], found[2];
+    const int tid = threadIdx.x;
+    constexpr int PER = kHistBins / NT;  // 16 buckets per lane, lane t owns the buckets counted from the top
+    uint32_t loc[PER];
+    const uint32_t top = kHistBins - 1 - tid * PER;  // highest bucket of this lane
+#pragma unroll
+    for (int i = 0; i < PER; i += 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(hist + (top - i - 3));
+        loc[i] = v.w;
+        loc[i + 1] = v.z;
+        loc[i + 2] = v.y;
+        loc[i + 3] = v.x;
+    }
+    uint32_t s = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) s += loc[i];
+    // The histogram counts every bin of the chunk, so some bucket always qualifies unless k is 0 (then nothing is kept);
+    // should it ever not (fewer than k bins counted), the result is still defined.
+    if (tid == 0) {
+        found[0] = k == 0 ? (uint32_t)kHistBins : 0u;
+        found[1] = 0;
+    }
+    uint32_t run = block_scan_incl<NT / 64>(s, tmp) - s;  // bins in buckets above this lane's range
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (run < k && run + loc[i] >= k) {
+            found[0] = top - i;
+            found[1] = k - run;
+        }
+        run += loc[i];
+    }
+    __syncthreads();
+    return Bucket{found[0], found[1]};
+}
+
 template <bool TABLE>
 __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__ hist, Shape u, uint32_t* __restrict__ sel,
                                                     TableArg<TABLE> tab)
 {
-    __shared__ uint32_t tmp[4];
-    const int tid = threadIdx.x;
     const size_t c = blockIdx.x;
-    const uint32_t k = place_of<TABLE>(u, tab, blockIdx.x, 0u).k;
-    constexpr int PER = kHistBins / NT;  // 16 buckets per lane, lane t owns the buckets counted from the top
-    uint32_t loc[PER];
-    uint32_t s = 0;
-    const uint32_t top = kHistBins - 1 - tid * PER;  // highest bucket of this lane
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        loc[i] = hist[c * kHistBins + (top - i)];
-        s += loc[i];
-    }
-    const uint32_t incl = block_scan_incl_256(s, tmp);
-    uint32_t run = incl - s;  // bins in buckets above this lane's range
-    if (k == 0) {
-        if (tid == 0) {
-            sel[c * 8 + 0] = kHistBins;  // no bucket qualifies: nothing is kept
-            sel[c * 8 + 1] = 0;
-        }
-        return;
-    }
-    // The histogram counts every bin of the chunk, so some bucket always qualifies; should it ever not (fewer than
-    // k bins counted), the selection words still get defined values instead of the previous call's.
-    if (tid == 0) {
-        sel[c * 8 + 0] = 0;
-        sel[c * 8 + 1] = 0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        if (run < k && run + loc[i] >= k) {
-            sel[c * 8 + 0] = top - i;
-            sel[c * 8 + 1] = k - run;
-        }
-        run += loc[i];
-    }
+    const Bucket b = find_bucket(hist + c * kHistBins, place_of<TABLE>(u, tab, blockIdx.x, 0u).k);
+    if (threadIdx.x == 0) *reinterpret_cast<uint2*>(sel + c * 8) = make_uint2(b.star, b.need);
 }
 
 // --------------------------------------------------------------- collect ----
@@ -306,10 +309,13 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
 // run, and fetching each line for two waves was slower (62 M samples in chunks of 2^20: 52 against 44 us).  Samples
 // lie in order, and binary16 bins are half the bytes: those are read straight into registers, without the barrier
 // (62 M samples 51 -> 42, binary16 32 -> 29).
-template <bool TABLE, bool REAL, bool HALF>
+// FIND: every workgroup finds the threshold's bucket itself, from hist, instead of a launch before this one.  That is 16 KB more to
+// read per tile, from cache, so it is done where the launch weighs more: see find_in_collect.
+template <bool FIND, bool TABLE, bool REAL, bool HALF>
 __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u,
-                                                const uint32_t* __restrict__ sel, uint32_t* __restrict__ tinfo,
-                                                uint2* __restrict__ cand, TableArg<TABLE> tab, size_t n)
+                                                const uint32_t* __restrict__ hist, uint32_t* __restrict__ sel,
+                                                uint32_t* __restrict__ tinfo, uint2* __restrict__ cand, TableArg<TABLE> tab,
+                                                size_t n)
 {
     using E = typename Elem<REAL>::T;
     __shared__ uint32_t wcnt[4], wdef[4], wvmax[4];
@@ -318,7 +324,9 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
     const uint32_t B = at.B, tbase = at.tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
     const int pair_log = at.pair_log;
     const typename Stored<REAL, HALF>::T* X = spec + at.spec + tbase;
-    const uint32_t bstar = sel[at.chunk * 8 + 0], count = units_in_tile<REAL>(n, at.chunk, B, tbase);
+    const uint32_t count = units_in_tile<REAL>(n, at.chunk, B, tbase);
+    uint32_t bstar = 0;
+    if constexpr (!FIND) bstar = sel[(size_t)at.chunk * 8];
     E z[ROWS];
     if constexpr (REAL || HALF) {
         load_units(X, row0, count, lane, pair_log, z);
@@ -327,6 +335,11 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
         tile_to_lds(X, count, TABLE || (u.sstride & 1u) == 0, stage, tid);
         __syncthreads();
         load_units(stage, row0, count, lane, pair_log, z);
+    }
+    if constexpr (FIND) {
+        const Bucket b = find_bucket(hist + (size_t)at.chunk * kHistBins, at.k);
+        bstar = b.star;
+        if (at.tile == 0 && tid == 0) *reinterpret_cast<uint2*>(sel + (size_t)at.chunk * 8) = make_uint2(b.star, b.need);
     }
     uint32_t key[ROWS], vb[ROWS];
     uint64_t cm[ROWS];
@@ -380,21 +393,6 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
 constexpr int RT = 1024;           // lanes of the per-chunk workgroups of the decoder's prefix kernels
 constexpr int RW = RT / 64;        // 16 waves
 constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1025
-
-// inclusive scan over the NW waves of a workgroup; tmp has NW entries
-template <int NW>
-__device__ __forceinline__ uint32_t block_scan_incl(uint32_t v, uint32_t* tmp)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t x = wave_scan_incl(v);
-    if (lane == 63) tmp[wave] = x;
-    __syncthreads();
-    uint32_t add = 0;
-#pragma unroll
-    for (int w = 0; w < NW - 1; ++w) add += w < wave ? tmp[w] : 0u;
-    __syncthreads();
-    return x + add;
-}
 
 // One workgroup per chunk: finish the radix select on the candidates, break ties by bin order, scan the tiles, find the
 // survivors' largest component, write the record header and zero the code words that two tiles will share.
@@ -855,6 +853,17 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
 // ---------------------------------------------------------------- decode ----
 constexpr int GROUP_WORDS = 16;  // one wave of the decode kernel covers 512 bins = 16 bitmap words
 
+// 0, or 6 if a record (or the stream's header) is not what the call's arguments make it; kept: set bits of its bitmap
+__device__ __forceinline__ uint32_t record_verdict(const uint8_t* __restrict__ record, const uint8_t* __restrict__ stream,
+                                                   bool first_of_stream, uint32_t kept, uint32_t k, uint32_t word3,
+                                                   const HeaderInfo& hdr)
+{
+    const uint32_t* rec = reinterpret_cast<const uint32_t*>(record);
+    bool bad = kept != k || rec[2] != k || rec[3] != word3;
+    if (hdr.write && first_of_stream) bad = bad || header_bad(hdr, reinterpret_cast<const uint32_t*>(stream));
+    return bad ? 6u : 0u;
+}
+
 // Per chunk: number of set bits before each group of 16 bitmap words (the prefix sum of Sec. 3.2's status
 // vector, kept at the granularity a wave needs); checks the headers and leaves the verdict in *verdict.
 __device__ __forceinline__ void group_prefix_chunk(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ record,
@@ -901,11 +910,7 @@ __device__ __forceinline__ void group_prefix_chunk(const uint8_t* __restrict__ s
         if (tid == RT - 1) s_carry = carry + incl;
         __syncthreads();
     }
-    if (tid == 0) {
-        bool bad = s_carry != k || rec[2] != k || rec[3] != word3;
-        if (hdr.write && first_of_stream) bad = bad || header_bad(hdr, reinterpret_cast<const uint32_t*>(stream));
-        *verdict = bad ? 6u : 0u;
-    }
+    if (tid == 0) *verdict = record_verdict(record, stream, first_of_stream, s_carry, k, word3, hdr);
 }
 
 // what the first kernel of a receiver's call leaves in the control block
@@ -963,14 +968,12 @@ struct WaveCodes {
 // wide they are fetched as a window of NL * 1024 + 16 bytes from the 16-byte boundary below the first one (lanes past the
 // last code's 16 bytes repeat them), and picked out of LDS by rank; 32-bit codes (NL = 0) need no unpacking and are read by
 // rank from memory, a row's being adjacent.  The header, the bitmap words and the prefix are scalar loads.
-template <int NL, uint32_t CODES>
-__device__ __forceinline__ void fetch_codes(const uint8_t* __restrict__ record, size_t S, uint32_t W, uint32_t g, int bits,
-                                            const uint32_t* __restrict__ gprefix, int lane, WaveCodes<NL>& wc)
+template <int NL>
+__device__ __forceinline__ void fetch_flags(const uint8_t* __restrict__ record, uint32_t W, uint32_t g, int lane, WaveCodes<NL>& wc)
 {
     const uint32_t* rec = reinterpret_cast<const uint32_t*>(record);
     const uint32_t w0 = g * GROUP_WORDS;
     wc.pbase = scalar_load(rec);
-    wc.run = scalar_load(gprefix + (w0 < W ? g : 0u));
     if (w0 + GROUP_WORDS <= W) {
         const uint64_t* p = reinterpret_cast<const uint64_t*>(rec + 4 + w0);
 #pragma unroll
@@ -982,8 +985,14 @@ __device__ __forceinline__ void fetch_codes(const uint8_t* __restrict__ record, 
             wc.fm[r] = (uint32_t)__builtin_amdgcn_readlane((int)v, 2 * r) |
                        ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)v, 2 * r + 1) << 32);
     }
+}
+// The codes of the wave's units; run, kept: kept units before them and among them (or an upper bound).
+template <int NL, uint32_t CODES>
+__device__ __forceinline__ void fetch_codes(const uint8_t* __restrict__ record, size_t S, uint32_t W, int bits, uint32_t run,
+                                            uint32_t kept, int lane, WaveCodes<NL>& wc)
+{
+    wc.run = run;
     if constexpr (NL > 0) {
-        const uint32_t kept = w0 + GROUP_WORDS < W ? scalar_load(gprefix + g + 1u) - wc.run : (uint32_t)WAVE_BINS;
         const uint32_t width = CODES * (uint32_t)bits, last = (uint32_t)S - 16u;  // S is a multiple of 16, at least 32
         const uint32_t first = 8u * (16u + 4u * W) + width * wc.run;             // bit position in the record
         const uint32_t start = (first >> 3) & ~15u, end = (first + width * kept) >> 3 & ~15u;
@@ -997,6 +1006,14 @@ __device__ __forceinline__ void fetch_codes(const uint8_t* __restrict__ record, 
         const uint32_t off = start + (uint32_t)(NL * 1024);
         wc.tail = *reinterpret_cast<const u32x4*>(record + (off < lim ? off : lim));
     }
+}
+
+// Kept units before a wave's and among them (or an upper bound), from the chunk's group prefixes.
+__device__ __forceinline__ void group_run(const uint32_t* __restrict__ gprefix, uint32_t W, uint32_t g, uint32_t& run, uint32_t& kept)
+{
+    const uint32_t w0 = g * GROUP_WORDS;
+    run = scalar_load(gprefix + (w0 < W ? g : 0u));
+    kept = w0 + GROUP_WORDS < W ? scalar_load(gprefix + g + 1u) - run : (uint32_t)WAVE_BINS;
 }
 
 template <int NL>
@@ -1133,12 +1150,15 @@ __device__ __forceinline__ void tile_from_lds(T* __restrict__ X, const T* stage,
 // Bound by the stores of the decoded units, and by instruction issue: everything that is the same for a row's 64 lanes
 // (its flags as a mask, counts, addresses) is scalar.  Two dependent round trips (bitmap and prefix, then codes) are
 // covered by the seven workgroups that a compute unit holds.
+// COUNT: a workgroup counts the bits before its tile itself, leaves the record's verdict and the control block, and
+// there is no launch before this one: see prefix_in_decode.
 // Measured, 62 M samples in chunks of 2^20, against persistent workgroups with software-pipelined loads whose flags and
 // ranks were per lane: half of the bins kept as 8-bit codes 62 -> 54 us (298 MB of traffic), binary16 bins 52 -> 33, 15 % of
 // the samples kept at 32 bits 93 -> 62; chunks of 2^22 (138 M samples) 136 -> 112.
-template <int NL, bool TABLE, bool REAL, bool HALF>
-__global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ records, Shape u, int bits, int m,
-                                               const uint32_t* __restrict__ gprefix,
+template <int NL, bool COUNT, bool TABLE, bool REAL, bool HALF>
+__global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ records, Shape u,
+                                               int bits, int m, const uint32_t* __restrict__ gprefix, HeaderInfo hdr,
+                                               uint32_t* __restrict__ verdicts, uint32_t* __restrict__ ctl, StatusNote note,
                                                typename Stored<REAL, HALF>::T* __restrict__ spec, bool vec,
                                                TableArg<TABLE> tab, size_t n)
 {
@@ -1151,7 +1171,40 @@ __global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ recor
     const uint8_t* record = records + at.record;
     uint8_t* window = windows + (NL ? wave * kWindow<NL> : 0);
     WaveCodes<NL> wc;
-    fetch_codes<NL, Elem<REAL>::kCodes>(record, S, W, at.tile * (kTile / 32 / GROUP_WORDS) + wave, bits, gprefix + at.group0, lane, wc);
+    const uint32_t g = at.tile * (kTile / 32 / GROUP_WORDS) + wave;  // this wave's group of bitmap words
+    uint32_t run, kept;
+    if constexpr (!COUNT) group_run(gprefix + at.group0, W, g, run, kept);
+    fetch_flags<NL>(record, W, g, lane, wc);
+    if constexpr (COUNT) {
+        __shared__ uint32_t before[NT / 64], own[NT / 64];
+        kept = 0;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) kept += (uint32_t)__popcll(wc.fm[r]);
+        const uint4* words = reinterpret_cast<const uint4*>(record + 16);
+        uint32_t mine = 0;  // set bits of the tiles before this one
+        for (uint32_t i = (uint32_t)tid; i < at.tile * (kTile / 128u); i += NT) {
+            const uint4 v = words[i];
+            mine += (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w));
+        }
+        mine = wave_sum(mine);
+        if (lane == 0) {
+            before[wave] = mine;
+            own[wave] = kept;
+        }
+        __syncthreads();
+        uint32_t total = 0;
+        run = 0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) {
+            total += before[w] + own[w];
+            run += before[w] + (w < wave ? own[w] : 0u);
+        }
+        run = (uint32_t)__builtin_amdgcn_readfirstlane((int)run);
+        if (at.tile + 1u == at.Tn && tid == 0)  // the last tile has seen all of the bitmap
+            verdicts[at.chunk] = record_verdict(record, stream, at.chunk == 0, total, at.k, at.word3, hdr);
+        if (ctl && blockIdx.x == 0) write_control(ctl, note, tid, NT);
+    }
+    fetch_codes<NL, Elem<REAL>::kCodes>(record, S, W, bits, run, kept, lane, wc);
     T z[ROWS];
     unpack_codes<NL, REAL>(wc, record, S, W, bits, 23 - m, lane, window, [&](int r, const typename Elem<REAL>::T& v) {
         if constexpr (HALF)
@@ -1201,7 +1254,11 @@ __global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npe
     for (uint32_t p = 0; p < npeers; ++p) {
         const uint8_t* record = recs.p[p] + c * S;
         WaveCodes<NL> wc;
-        fetch_codes<NL, 2>(record, S, W, tile * (kTile / 32 / GROUP_WORDS) + wave, bits, gprefix + (p * C + c) * G, lane, wc);
+        const uint32_t g = tile * (kTile / 32 / GROUP_WORDS) + wave;
+        uint32_t run, kept;
+        fetch_flags<NL>(record, W, g, lane, wc);
+        group_run(gprefix + (p * C + c) * G, W, g, run, kept);
+        fetch_codes<NL, 2>(record, S, W, bits, run, kept, lane, wc);
         unpack_codes<NL, false>(wc, record, S, W, bits, 23 - m, lane, window, [&](int r, const float2& v) {
             acc[r] = make_float2(acc[r].x + v.x, acc[r].y + v.y);
         });
@@ -1249,6 +1306,16 @@ static Extent extent_of(const CodecArgs& a)
     return x;
 }
 
+// Short calls are bound by their launches, so the ones of one workgroup per chunk are left out there, and what they would
+// find is found by every workgroup of the kernel behind them.
+// In k_collect that is 16 KB more to read per tile.  Compress, chunks of 2^16: 16 tiles 30.5 -> 28.8 us, 512 39.7 -> 38.4,
+// 1088 no difference, 2176 58.0 -> 58.9.
+static bool find_in_collect(const Extent& x) { return x.tiles <= 1024; }
+// In k_decode it is the bitmap up to the tile, at most 256 bytes for each tile of the chunk, to read beside the tile's codes.
+// Decompress: one chunk of 2^16 21.7 -> 17.7 us, 2^23 samples in chunks of 2^20 (2056 tiles) 49.4 -> 48.8, 2^24 76.6 -> 77.8, one
+// chunk of 2^22 (1025 tiles) 50.3 -> 52.5.  Chunks of a few tiles always: Top-k of 2^24 samples in chunks of 2^12 32.8 -> 16.2.
+static bool prefix_in_decode(const Extent& x) { return x.most <= 8 || (x.most <= 257 && x.tiles <= 4096); }
+
 hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_base, uint8_t* records,
                          uint8_t* ws_base, const Workspace& w, int hist_ready, hipStream_t s)
 {
@@ -1286,16 +1353,24 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
     auto select = [&](auto table) {
         constexpr bool TABLE = decltype(table)::value;
         const TableArg<TABLE> tab = table_arg<TABLE>(a.tab);
-        FFTSP_LAUNCH("find_bucket", k_find_bucket<TABLE>, per_chunk, dim3(NT), 0, s, hist, u, sel, tab);
-        if constexpr (TABLE) {
-            FFTSP_LAUNCH("collect", (k_collect<true, false, false>), per_tile, dim3(NT), 0, s, X, u, sel, tinfo, cand, tab, a.n);
+        auto collect = [&](auto find) {
+            constexpr bool FIND = decltype(find)::value;
+            if constexpr (TABLE) {
+                FFTSP_LAUNCH("collect", (k_collect<FIND, true, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, cand, tab, a.n);
+            } else {
+                if (a.time_domain)
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, true, false>), per_tile, dim3(NT), 0, s, spec, u, hist, sel, tinfo, cand, tab, a.n);
+                else if (a.half)
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, true>), per_tile, dim3(NT), 0, s, Xh, u, hist, sel, tinfo, cand, tab, a.n);
+                else
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, cand, tab, a.n);
+            }
+        };
+        if (find_in_collect(x)) {
+            collect(std::true_type{});
         } else {
-            if (a.time_domain)
-                FFTSP_LAUNCH("collect", (k_collect<false, true, false>), per_tile, dim3(NT), 0, s, spec, u, sel, tinfo, cand, tab, a.n);
-            else if (a.half)
-                FFTSP_LAUNCH("collect", (k_collect<false, false, true>), per_tile, dim3(NT), 0, s, Xh, u, sel, tinfo, cand, tab, a.n);
-            else
-                FFTSP_LAUNCH("collect", (k_collect<false, false, false>), per_tile, dim3(NT), 0, s, X, u, sel, tinfo, cand, tab, a.n);
+            FFTSP_LAUNCH("find_bucket", k_find_bucket<TABLE>, per_chunk, dim3(NT), 0, s, hist, u, sel, tab);
+            collect(std::false_type{});
         }
         // few waves for few tiles: their barriers are cheaper than more hands
         auto resolve = [&](auto waves, auto keep) {
@@ -1332,67 +1407,64 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
     return hipGetLastError();
 }
 
-// the decode kernel proper, of one stream or of the peer list
-static hipError_t launch_decode_kernel(const PeerList& recs, uint32_t npeers, const CodecArgs& a, float* spec,
-                                       const uint32_t* gprefix, bool peers_layout, hipStream_t s)
-{
-    const Shape u = shape_of(a);
-    const dim3 grid((unsigned)extent_of(a).tiles);
-    if (a.half && (peers_layout || a.tab || a.time_domain)) return hipErrorInvalidValue;
-    if (a.time_domain && (peers_layout || a.tab || a.pair_log)) return hipErrorInvalidValue;
-    const bool vec = a.tab || (a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0);
-#define FFTSP_DECODE_AS(NL, TABLE, REAL, HALF, T)                                                                      \
-    FFTSP_LAUNCH("decode", (k_decode<NL, TABLE, REAL, HALF>), grid, dim3(NT), 0, s, recs.p[0], u, a.bits, a.m, gprefix, \
-                 reinterpret_cast<T*>(spec), vec, table_arg<TABLE>(a.tab), a.n)
-#define FFTSP_DECODE(NL)                                                                                               \
-    do {                                                                                                               \
-        if (peers_layout)                                                                                              \
-            FFTSP_LAUNCH("decode", k_decode_peers<NL>, grid, dim3(NT), 0, s, recs, npeers, a.S, u.B, u.W, a.bits, a.m, \
-                         u.Tn, a.C, gprefix, reinterpret_cast<float2*>(spec), a.sstride, vec, a.pair_log);             \
-        else if (a.tab)                                                                                                \
-            FFTSP_DECODE_AS(NL, true, false, false, float2);                                                           \
-        else if (a.half)                                                                                               \
-            FFTSP_DECODE_AS(NL, false, false, true, uint32_t);                                                         \
-        else                                                                                                           \
-            FFTSP_DECODE_AS(NL, false, false, false, float2);                                                          \
-    } while (0)
-    // code widths are 3..16 or 32 bits; the codes of a wave's 512 units are at most 1 KiB for 16 bits a unit, else 2 KiB
-    if (a.time_domain && a.bits <= 16)
-        FFTSP_DECODE_AS(1, false, true, false, float);
-    else if (a.time_domain)
-        FFTSP_DECODE_AS(0, false, true, false, float);
-    else if (a.bits <= 8)
-        FFTSP_DECODE(1);
-    else if (a.bits <= 16)
-        FFTSP_DECODE(2);
-    else
-        FFTSP_DECODE(0);
-#undef FFTSP_DECODE_AS
-#undef FFTSP_DECODE
-    return hipGetLastError();
-}
-
 hipError_t launch_decode(const uint8_t* stream_base, const uint8_t* records, const CodecArgs& a, float* spec,
-                         uint8_t* ws_base, const Workspace& w, int check_header, uint32_t* verdicts, const StatusNote* note,
+                         uint8_t* ws_base, const Workspace& w, int check_header, uint32_t* verdicts, const StatusNote* first,
                          hipStream_t s)
 {
     const Shape u = shape_of(a);
     const Extent x = extent_of(a);
-    uint32_t* ctl = note ? reinterpret_cast<uint32_t*>(ws_base + w.status) : nullptr;
-    uint32_t* gprefix = reinterpret_cast<uint32_t*>(ws_base + w.prefix);
+    uint32_t* ctl = first ? reinterpret_cast<uint32_t*>(ws_base + w.status) : nullptr;
+    const StatusNote note = first ? *first : StatusNote{0u, 0u};
     if (x.tiles > 0x7fffffffu) return hipErrorInvalidValue;
+    if (a.half && (a.tab || a.time_domain)) return hipErrorInvalidValue;
+    if (a.time_domain && (a.tab || a.pair_log)) return hipErrorInvalidValue;
     HeaderInfo h{check_header, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S,
                  a.hdr_theta, a.time_domain ? 1u : 0u, (uint32_t)a.hdr_scale};
-    const StatusNote none{0u, 0u};
-    if (a.tab)
-        FFTSP_LAUNCH("group_prefix", k_group_prefix<true>, dim3((unsigned)x.chunks), dim3(RT), 0, s, stream_base, records, u, h,
-                     gprefix, verdicts, ctl, note ? *note : none, table_arg<true>(a.tab));
-    else
-        FFTSP_LAUNCH("group_prefix", k_group_prefix<false>, dim3((unsigned)x.chunks), dim3(RT), 0, s, stream_base, records, u, h,
-                     gprefix, verdicts, ctl, note ? *note : none, table_arg<false>(a.tab));
-    PeerList recs{};
-    recs.p[0] = records;
-    return launch_decode_kernel(recs, 1u, a, spec, gprefix, false, s);
+    uint32_t* gprefix = nullptr;
+    if (!prefix_in_decode(x)) {
+        gprefix = reinterpret_cast<uint32_t*>(ws_base + w.prefix);
+        if (a.tab)
+            FFTSP_LAUNCH("group_prefix", k_group_prefix<true>, dim3((unsigned)x.chunks), dim3(RT), 0, s, stream_base, records, u, h,
+                         gprefix, verdicts, ctl, note, table_arg<true>(a.tab));
+        else
+            FFTSP_LAUNCH("group_prefix", k_group_prefix<false>, dim3((unsigned)x.chunks), dim3(RT), 0, s, stream_base, records, u, h,
+                         gprefix, verdicts, ctl, note, table_arg<false>(a.tab));
+    }
+    const bool vec = a.tab || (a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0);
+#define FFTSP_DECODE_AS(NL, TABLE, REAL, HALF, T)                                                                          \
+    if (gprefix)                                                                                                           \
+        FFTSP_DECODE_WITH(NL, false, TABLE, REAL, HALF, T);                                                                \
+    else                                                                                                                   \
+        FFTSP_DECODE_WITH(NL, true, TABLE, REAL, HALF, T)
+#define FFTSP_DECODE_WITH(NL, COUNT, TABLE, REAL, HALF, T)                                                                 \
+    FFTSP_LAUNCH("decode", (k_decode<NL, COUNT, TABLE, REAL, HALF>), dim3((unsigned)x.tiles), dim3(NT), 0, s, stream_base, records, u, \
+                 a.bits, a.m, gprefix, h, verdicts, ctl, note, reinterpret_cast<T*>(spec), vec, table_arg<TABLE>(a.tab), a.n)
+#define FFTSP_DECODE(NL)                                       \
+    do {                                                       \
+        if (a.tab) {                                           \
+            FFTSP_DECODE_AS(NL, true, false, false, float2);   \
+        } else if (a.half) {                                   \
+            FFTSP_DECODE_AS(NL, false, false, true, uint32_t); \
+        } else {                                               \
+            FFTSP_DECODE_AS(NL, false, false, false, float2);  \
+        }                                                      \
+    } while (0)
+    // code widths are 3..16 or 32 bits; the codes of a wave's 512 units are at most 1 KiB for 16 bits a unit, else 2 KiB
+    if (a.time_domain && a.bits <= 16) {
+        FFTSP_DECODE_AS(1, false, true, false, float);
+    } else if (a.time_domain) {
+        FFTSP_DECODE_AS(0, false, true, false, float);
+    } else if (a.bits <= 8) {
+        FFTSP_DECODE(1);
+    } else if (a.bits <= 16) {
+        FFTSP_DECODE(2);
+    } else {
+        FFTSP_DECODE(0);
+    }
+#undef FFTSP_DECODE_WITH
+#undef FFTSP_DECODE_AS
+#undef FFTSP_DECODE
+    return hipGetLastError();
 }
 
 hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecArgs& a, float* spec, uint8_t* ws_base,
@@ -1402,7 +1474,7 @@ hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecA
     uint32_t* ctl = reinterpret_cast<uint32_t*>(ws_base + w.status);
     uint32_t* gprefix = reinterpret_cast<uint32_t*>(ws_base + pw.prefix);
     uint32_t* verdicts = reinterpret_cast<uint32_t*>(ws_base + pw.verd);
-    if (npeers < 1 || npeers > kMaxPeers) return hipErrorInvalidValue;
+    if (npeers < 1 || npeers > kMaxPeers || a.half || a.tab || a.time_domain) return hipErrorInvalidValue;
     const size_t count = a.C * (size_t)npeers;
     if (a.C * (size_t)u.Tn > 0x7fffffffu || count > 0x7fffffffu || pw.verd / 4 > 0xffffffffu) return hipErrorInvalidValue;
     HeaderInfo h{1, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
@@ -1410,7 +1482,18 @@ hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecA
                  a.k, h, gprefix, verdicts, ctl, StatusNote{(uint32_t)count, (uint32_t)(pw.verd / 4)});
     PeerList recs{};
     for (int i = 0; i < npeers; ++i) recs.p[i] = streams.p[i] + 64;  // records follow the 64-byte stream header
-    return launch_decode_kernel(recs, (uint32_t)npeers, a, spec, gprefix, true, s);
+    const bool vec = a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0;
+#define FFTSP_DECODE_PEERS(NL)                                                                                             \
+    FFTSP_LAUNCH("decode", k_decode_peers<NL>, dim3((unsigned)(a.C * u.Tn)), dim3(NT), 0, s, recs, (uint32_t)npeers, a.S, u.B, \
+                 u.W, a.bits, a.m, u.Tn, a.C, gprefix, reinterpret_cast<float2*>(spec), a.sstride, vec, a.pair_log)
+    if (a.bits <= 8)
+        FFTSP_DECODE_PEERS(1);
+    else if (a.bits <= 16)
+        FFTSP_DECODE_PEERS(2);
+    else
+        FFTSP_DECODE_PEERS(0);
+#undef FFTSP_DECODE_PEERS
+    return hipGetLastError();
 }
 
 }  // namespace fftsp
