@@ -710,8 +710,11 @@ int fftsp_topk_compress(const float* d_grad, size_t n, uint32_t chunk_len, float
     uint8_t* ws = static_cast<uint8_t*>(d_workspace);
     uint8_t* out = static_cast<uint8_t*>(d_packed);
     const CodecArgs a = topk_args(p, theta);
-    return hip_status(launch_encode(d_grad, a, out, out + kStreamHeader, ws, p.ws, 0,
-                                    reinterpret_cast<hipStream_t>(stream)));
+    hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    if (p.logL <= kChunkMaxLogL)
+        return hip_status(launch_topk_compress(d_grad, p.n, p.logL, a, out, out + kStreamHeader,
+                                               reinterpret_cast<uint32_t*>(ws + p.ws.status), s));
+    return hip_status(launch_encode(d_grad, a, out, out + kStreamHeader, ws, p.ws, 0, s));
 }
 
 int fftsp_topk_decompress(const void* d_packed, size_t packed_bytes, float* d_grad_out, size_t n, uint32_t chunk_len,

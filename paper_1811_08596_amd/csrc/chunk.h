@@ -17,6 +17,9 @@ struct PackArgs {
 // Sender.  ctl: the workspace's control block.
 hipError_t launch_chunk_compress(const float* in, size_t n, int logL, const CodecArgs& a, uint8_t* stream, uint8_t* records,
                                  uint32_t* ctl, Tables t, hipStream_t s);
+// The same for time-domain Top-k.
+hipError_t launch_topk_compress(const float* in, size_t n, int logL, const CodecArgs& a, uint8_t* stream, uint8_t* records,
+                                uint32_t* ctl, hipStream_t s);
 // Receiver.  streams: whole packed streams (64-byte header first).  plain: one stream, taken as it is; otherwise the
 // streams are summed in list order, starting from zero.  verdicts: u32[npeers][C], announced by `note`.
 hipError_t launch_chunk_decompress(const PeerList& streams, int npeers, int plain, int logL, const CodecArgs& a, float* out,

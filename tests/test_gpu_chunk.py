@@ -58,3 +58,14 @@ def test_status_is_per_call_and_per_record(dev, ref):
     f.decompress(dev.to_dev(bad), packed.size, out, L, theta, bits, ws)
     f.compress(out, L, theta, bits, t.empty(packed.size, dtype=t.uint8, device=dev.dev), ws)
     assert f.device_status(ws) == 0                       # another call on the same workspace starts clean
+
+
+@pytest.mark.parametrize("logL", range(5, 16))
+def test_topk_sender_matches_the_oracle(dev, ref, logL):
+    L = 1 << logL
+    chunks = max(3, (1 << 13 >> logL) + 2)                # more than one workgroup, the last one not full
+    for name, g in signals(L, chunks, L // 3 + 1):
+        for theta, bits in ((0.3, 8), (0.15, 10), (1.0, 16), (0.5, 32), (0.02, 3), (0.0, 8)):
+            print(f"topk L=2^{logL} {name} theta={theta} bits={bits}", flush=True)
+            want = ref.topk_compress(g, L, theta, bits)
+            assert np.array_equal(dev.topk_compress(g, L, theta, bits), want)
