@@ -157,7 +157,8 @@ __device__ __forceinline__ void fwd_a_tile(uint32_t t, uint32_t tiles, int logM,
 // kWhole: every tile of this workgroup's run lies in a chunk that is wholly inside the input, and the input is
 // 16-byte aligned: two columns per 16-byte load, no guards.  kQuads: the input is aligned and ends on a multiple of four
 // samples: every 16-byte piece is inside or outside, and those outside read a valid address and count as zeros (tensors
-// that do not fill their chunk).  kGuarded: every element is loaded under a guard (other ragged ends, unaligned tensors).
+// that do not fill their chunk).  They become zeros on the way into LDS: choosing right behind the loads waits for them
+// before the stages they are to run beside (ResNet-50's long tensors 93 -> 79 us).  kGuarded: every element is loaded under a guard (other ragged ends, unaligned tensors).
 // The variants are separate loops so that no branches stand between the unguarded ones' loads and their use.
 enum Reads { kGuarded, kWhole, kQuads };
 template <int LOGN1, Reads MODE, bool HALF>
@@ -171,6 +172,11 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t f
     static_assert(LOGT >= 2 && (NT % (TA / 2)) == 0, "tile shape");
     const uint32_t M = 1u << logM, N2 = M >> LOGN1, tiles = N2 >> LOGT;
 
+    // 16-byte pieces of a chunk that exist
+    auto quads_of = [&](const Span& sp) __attribute__((always_inline)) {
+        const size_t left = sp.limit > sp.first ? (sp.limit - sp.first) >> 2 : 0;
+        return left < (size_t)(M >> 1) ? (uint32_t)left : M >> 1;
+    };
     // live = false: the tile does not exist; the fast loads are still issued, all to one valid address
     // part p of spread_parts(): loads q with q * parts / PER2 == p; prologue calls pass every part in turn
     auto load_tile = [&](float4 (&r)[PER2], uint32_t tile, int tid, bool live, int part) {
@@ -179,15 +185,13 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t f
         const uint32_t col0 = tile_in_chunk(tile, tiles) << LOGT;
         if constexpr (MODE == kQuads) {
             const float4* src = live ? reinterpret_cast<const float4*>(in + sp.first) : reinterpret_cast<const float4*>(tb.hi);
-            const size_t left = live && sp.limit > sp.first ? (sp.limit - sp.first) >> 2 : 0;  // pieces of this chunk that exist
-            const uint32_t quads = left < (size_t)(M >> 1) ? (uint32_t)left : M >> 1;
+            const uint32_t quads = quads_of(sp);
 #pragma unroll
             for (int q = 0; q < PER2; ++q) {
                 if (q * spread_parts<LOGN1>() / PER2 != part) continue;
                 const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
                 const uint32_t i = (uint32_t)n1 * (N2 >> 1) + (col0 >> 1) + bp;
-                r[q] = src[i < quads ? i : 0u];
-                if (i >= quads) r[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+                r[q] = src[live && i < quads ? i : 0u];
             }
         } else if constexpr (MODE == kWhole) {
             const float4* src = live ? reinterpret_cast<const float4*>(in + sp.first) + (col0 >> 1)
@@ -210,14 +214,23 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t f
     };
     // r[q] holds rows (tid >> (LOGT-1)) + q * N1/8 of one column pair: the first stage runs on the way into LDS
     static_assert(PER2 == 8 && (NT >> (LOGT - 1)) == N1 / 8, "a lane's loads are the inputs of two radix-8 butterflies");
-    auto fill = [&](const float4 (&r)[PER2], int tid) {
+    auto fill = [&](float4 (&r)[PER2], uint32_t tile, int tid) {
+        if constexpr (MODE == kQuads) {  // here, where the loads have to have arrived anyway
+            const uint32_t quads = quads_of(chunk_span(first, n, tile / tiles, 2 * (size_t)M, aligned & 1));
+            const uint32_t at = (tile_in_chunk(tile, tiles) << LOGT) >> 1;
+#pragma unroll
+            for (int q = 0; q < PER2; ++q) {
+                const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
+                if ((uint32_t)n1 * (N2 >> 1) + at + (uint32_t)bp >= quads) r[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
         first_stage_store<LOGT, false>(d, tid >> (LOGT - 1), 2 * (tid & (TA / 2 - 1)), r);
     };
     float4 r[PER2];
 #pragma unroll
     for (int part = 0; part < spread_parts<LOGN1>(); ++part) load_tile(r, t, tid0, true, part);
     const PassARatios<LOGN1> ratio = pass_a_ratios<LOGN1>(tb, logM, tid0);
-    fill(r, tid0);
+    fill(r, t, tid0);
     __syncthreads();
     for (;;) {
         const int tid = opaque_lane(tid0);
@@ -227,7 +240,7 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t f
         if (!more) break;
         t += tstep;
         __syncthreads();
-        fill(r, tid);
+        fill(r, t, tid);
         __syncthreads();
     }
 }
@@ -685,7 +698,7 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HA
 // (the longest of either decides the LDS), so a call with tensors of seven lengths is four launches instead of 28, and short
 // tensors fill the compute units that the long ones leave.
 // Measured, ResNet-50's 161 tensors (49 of them long, of seven lengths), sender and receiver: seven launch sets on four
-// streams 579 us, one 467; the three long tensors of ResNet-20, all of 2^16, stay as they were.
+// streams 579 us, one 451; the three long tensors of ResNet-20, all of 2^16, stay as they were.
 constexpr int log_columns(int logM) { return (logM + 1) / 2; }  // log2 N1
 constexpr int log_rows(int logM) { return logM / 2; }           // log2 N2
 constexpr int kLongMax = kMaxLogL - 1;                            // log2 M
