@@ -321,11 +321,12 @@ __device__ __forceinline__ float2 nyquist_bin(const float2* d, int base)
 // z[r]: bin (wave * R + r) * 64 + lane (lane < LR); zn (TAIL): the chunk's last bin, the same value in every lane.
 // lds: the group's own words (histogram, candidate list); image: its record image.  wg_most: a word of the workgroup,
 // zero on entry, through which several groups of several waves agree on the path they take together.
-// live = false groups (no such chunk) write nothing; groups of several waves call this together.
+// runs: many of the samples are zero.  live = false groups (no such chunk) write nothing; groups of several waves call this together.
 template <bool REAL, int R, bool TAIL, int LR, int WAVES, int GROUPS, int HB>
 __device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z)[R], typename Elem<REAL>::T zn, uint32_t* lds,
                                                 uint32_t* image, GroupScratch& gs, uint32_t* wg_most, int tid,
-                                                const PackArgs& a, uint32_t word3, uint8_t* __restrict__ record, bool live)
+                                                const PackArgs& a, uint32_t word3, uint8_t* __restrict__ record, bool live,
+                                                bool runs = false)
 {
     constexpr int NL = 64 * WAVES;
     constexpr bool SHARED = WAVES > 1 && GROUPS > 1;
@@ -388,13 +389,25 @@ __device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z
             group_sync<WAVES>();
             const int top = shift + NB;
             const uint32_t prefix = top >= 31 ? 0u : tau >> top;
-            auto add = [&](uint32_t k) __attribute__((always_inline)) {
-                if (top >= 31 || k >> top == prefix) atomicAdd(&lds[place((k >> shift) & (uint32_t)(BINS - 1))], 1u);
+            auto wanted = [&](uint32_t k) __attribute__((always_inline)) { return top >= 31 || k >> top == prefix; };
+            auto add = [&](uint32_t k, uint32_t many) __attribute__((always_inline)) {
+                atomicAdd(&lds[place((k >> shift) & (uint32_t)(BINS - 1))], many);
             };
+            if (REAL && runs) {
+                // the zeros past a gradient's end would queue for one counter: they are one addition a wave
+                uint32_t zeros = 0;
+                for (int r = 0; r < R; ++r) {
+                    const bool in = (LR == 64 || lane < LR) && wanted(key[r]);
+                    zeros += ones(__ballot(in && key[r] == 0u));
+                    if (in && key[r] != 0u) add(key[r], 1u);
+                }
+                if (zeros && lane == 0) add(0u, zeros);
+            } else {
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-                if (LR == 64 || lane < LR) add(key[r]);
-            if (tail && lane == 0) add(keyn);
+                for (int r = 0; r < R; ++r)
+                    if ((LR == 64 || lane < LR) && wanted(key[r])) add(key[r], 1u);
+            }
+            if (tail && lane == 0 && wanted(keyn)) add(keyn, 1u);
             group_sync<WAVES>();
             uint32_t cnt[PER], sum = 0;
             const bool mine = PER > 1 || tg < BINS;
@@ -838,7 +851,7 @@ __global__ __launch_bounds__(TopkGeo<LOGL>::NT) void k_topk_compress(const float
     }
     select_and_pack<true, G::R, false, G::LR, G::WAVES, G::GROUPS, G::HB>(z, 0.f, mine, mine + (G::HB ? kListCap : 0u), gs[group],
                                                                           reinterpret_cast<uint32_t*>(gs + G::GROUPS), tid, a,
-                                                                          a.word3, records + c * (size_t)a.S, true);
+                                                                          a.word3, records + c * (size_t)a.S, true, present < (uint32_t)G::L);
 }
 
 // ---------------------------------------------------------------- receiver ----

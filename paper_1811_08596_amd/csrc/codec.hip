@@ -178,8 +178,10 @@ __global__ __launch_bounds__(NT) void k_hist_samples(const float* __restrict__ i
             add(v.z);
             add(v.w);
         }
-    } else {  // the gradient ends inside this stretch: what lies past its end counts as zeros
-        for (uint32_t i = tid; i < count; i += NT) add(base + i < present ? X[base + i] : 0.f);
+    } else {  // the gradient ends inside this stretch or before it: what lies past its end counts as zeros
+        const uint32_t here = present > base ? present - base : 0u;
+        for (uint32_t i = tid; i < here; i += NT) add(X[base + i]);
+        if (tid == 0) atomicAdd(&mine[0], count - here);  // into the low half: fewer than 2^16
     }
     __syncthreads();
     uint32_t* g = hist + c * kHistBins;
@@ -309,6 +311,8 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
 // run, and fetching each line for two waves was slower (62 M samples in chunks of 2^20: 52 against 44 us).  Samples
 // lie in order, and binary16 bins are half the bytes: those are read straight into registers, without the barrier
 // (62 M samples 51 -> 42, binary16 32 -> 29).
+// A tile of more than kListCap candidates that are all the same value (the zeros past the end of a gradient, say) is marked,
+// so that k_resolve can take it as one.
 // FIND: every workgroup finds the threshold's bucket itself, from hist, instead of a launch before this one.  That is 16 KB more to
 // read per tile, from cache, so it is done where the launch weighs more: see find_in_collect.
 template <bool FIND, bool TABLE, bool REAL, bool HALF>
@@ -319,6 +323,8 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
 {
     using E = typename Elem<REAL>::T;
     __shared__ uint32_t wcnt[4], wdef[4], wvmax[4];
+    __shared__ uint2 wsame[4];  // the one candidate value of a wave, or kMixed
+    constexpr uint32_t kMixed = 0xFFFFFFFFu;  // no key
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const Place at = place_of_tile<TABLE>(u, tab);
     const uint32_t B = at.B, tbase = at.tile * kTile, row0 = (uint32_t)wave * WAVE_BINS;
@@ -362,7 +368,23 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
     }
     ndef = wave_sum(ndef);
     vmax = wave_max(vmax);
+    uint2 same = make_uint2(kMixed, 0u);
+    if (ncand > kListCap / 4) {
+        uint32_t most_key = 0, most_vb = 0, least_key = 0, least_vb = 0;  // least: of the complements
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const bool in = (mine >> r) & 1u;
+            most_key = in && key[r] > most_key ? key[r] : most_key;
+            most_vb = in && vb[r] > most_vb ? vb[r] : most_vb;
+            least_key = in && ~key[r] > least_key ? ~key[r] : least_key;
+            least_vb = in && ~vb[r] > least_vb ? ~vb[r] : least_vb;
+        }
+        most_key = wave_max(most_key);
+        most_vb = wave_max(most_vb);
+        if (most_key == ~wave_max(least_key) && most_vb == ~wave_max(least_vb)) same = make_uint2(most_key, most_vb);
+    }
     if (lane == 0) {
+        wsame[wave] = same;
         wcnt[wave] = ncand;
         wdef[wave] = ndef;
         wvmax[wave] = vmax;
@@ -384,8 +406,17 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
         m = wvmax[2] > m ? wvmax[2] : m;
         m = wvmax[3] > m ? wvmax[3] : m;
         ti[1] = m;
-        ti[2] = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
-        ti[3] = 0;
+        const uint32_t all = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+        uint2 one = make_uint2(kMixed, 0u);
+        bool alike = all > kListCap;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint2 v = wsame[w];
+            if (one.x == kMixed && wcnt[w]) one = v;
+            alike = alike && (wcnt[w] == 0 || (v.x != kMixed && v.x == one.x && v.y == one.y));
+        }
+        ti[2] = all;
+        ti[3] = alike ? 1u : 0u;
     }
 }
 
@@ -402,12 +433,15 @@ constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1
 // The second one counts per tile those above the two digits' common prefix, takes their range and lists the few that
 // share it (ten or so of a million bins).  The list settles the threshold, and its members are added to their tiles
 // afterwards.  More than kListCap of them (runs of equal keys) take a third digit and a third sweep.
+// A tile whose candidates are all the same value is one candidate of its weight: 10^6 samples in chunks of 2^18, the last
+// one nearly empty, Top-k sender and receiver 661 -> 72 us.
 // KEPT: the first sweep leaves the candidates in LDS, in slots of 64 per tile, for the second one.
 // Counting the second digit in k_collect instead saved a sweep here but cost that kernel more (43 -> 52 us: its atomics
 // meet in memory).
 // Measured, us per call, against three digits and three more sweeps by 16 waves: one chunk of 2^16 16 -> 9, sixty of
 // 2^20 24 -> 18, thirty-three of 2^22 87 -> 44.
 constexpr int kFetch = 8;  // tiles of a wave fetched in one round trip
+constexpr uint32_t kAlike = 0x80000000u;  // mark of a tile whose candidates are all the same
 constexpr uint32_t kKeptTiles = 270;  // 135 KiB beside the kernel's other 20
 template <bool TABLE, int NW, bool KEPT>
 __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, uint32_t static_vmax, uint32_t codes_per_bin,
@@ -438,19 +472,22 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
         const uint4 info = ti[t];
         tgt[t] = info.x;
         teq[t] = 0u;
-        tnc[t] = info.z;
+        tnc[t] = info.z | (info.w ? kAlike : 0u);
         vm = info.x && info.y > vm ? info.y : vm;
-        more = more || info.z > 64u;
+        more = more || (info.z > 64u && !info.w);
     }
     for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
     if (tid == 0) s_digit = s_need = s_count = s_listed = s_vmax = 0u;  // defined even if no digit qualifies
     const bool heavy = __syncthreads_or(more);
     const bool any = need > 0;  // else nothing is kept (k = 0), and there are no candidates
 
-    auto count_of = [&](uint32_t t) __attribute__((always_inline)) {
-        return t < Tn ? (uint32_t)__builtin_amdgcn_readfirstlane((int)tnc[t]) : 0u;
+    // candidates of a tile to look at, each standing for `weight` of them
+    auto count_of = [&](uint32_t t, uint32_t& weight) __attribute__((always_inline)) {
+        const uint32_t v = t < Tn ? (uint32_t)__builtin_amdgcn_readfirstlane((int)tnc[t]) : 0u;
+        weight = v & kAlike ? v & ~kAlike : 1u;
+        return v & kAlike ? 1u : v;
     };
-    // row(t, r, e, valid) for every row of 64 candidates of this wave's tiles
+    // row(t, r, e, valid, weight) for every row of 64 candidates of this wave's tiles
     auto sweep_as = [&](auto keep, auto first, auto&& row) __attribute__((always_inline)) {
         constexpr bool STORE = decltype(keep)::value && decltype(first)::value, LOAD = decltype(keep)::value && !decltype(first)::value;
         for (uint32_t t0 = (uint32_t)wave; t0 < Tn; t0 += NW * kFetch) {
@@ -463,13 +500,15 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
             }
 #pragma unroll
             for (int v = 0; v < kFetch; ++v) {
-                const uint32_t t = t0 + (uint32_t)(v * NW), nc = count_of(t);
+                const uint32_t t = t0 + (uint32_t)(v * NW);
+                uint32_t weight;
+                const uint32_t nc = count_of(t, weight);
                 if (STORE && t < Tn) kept[t * 64u + lane] = e[v];
-                row(t, 0u, e[v], (uint32_t)lane < nc);
+                row(t, 0u, e[v], (uint32_t)lane < nc, weight);
                 if (heavy)
                     for (uint32_t i0 = 64u; i0 < nc; i0 += 64u) {
                         const bool valid = i0 + (uint32_t)lane < nc;
-                        row(t, i0, cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)], valid);
+                        row(t, i0, cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)], valid, 1u);
                     }
             }
         }
@@ -481,22 +520,22 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
             sweep_as(std::bool_constant<KEPT>{}, first, row);
     };
     // candidates' next digit: d, counted for the lanes of `act` that want it
-    auto count_digit = [&](bool hit, uint32_t d, bool run_likely) __attribute__((always_inline)) {
+    auto count_digit = [&](bool hit, uint32_t d, bool run_likely, uint32_t weight) __attribute__((always_inline)) {
         if (run_likely) {
             const uint64_t act = __ballot(hit);
             if (!act) return;
             // a row whose keys share the digit (a run of equal values, e.g. zeros) is one atomic
             const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __ffsll((unsigned long long)act) - 1);
             if (__ballot(hit && d == d0) == act) {
-                if (lane == 0) atomicAdd(&h[d0], (uint32_t)__popcll(act));
+                if (lane == 0) atomicAdd(&h[d0], (uint32_t)__popcll(act) * weight);
                 return;
             }
         }
-        if (hit) atomicAdd(&h[d], 1u);
+        if (hit) atomicAdd(&h[d], weight);
     };
     if (any)
-        sweep(std::true_type(), [&](uint32_t, uint32_t i0, uint2 e, bool valid) {
-            count_digit(valid, (e.x >> kHist2Shift) & (uint32_t)(kHist2Bins - 1), i0 != 0);
+        sweep(std::true_type(), [&](uint32_t, uint32_t i0, uint2 e, bool valid, uint32_t weight) {
+            count_digit(valid, (e.x >> kHist2Shift) & (uint32_t)(kHist2Bins - 1), i0 != 0, weight);
         });
     __syncthreads();
     constexpr int PER = kHist2Bins / LANES;
@@ -527,11 +566,12 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
     uint32_t tau = any ? (uint32_t)prefix << kHist2Shift : 0xFFFFFFFFu, quota = 0;
     bool ties = false;
     if (any && few) {
-        sweep(std::false_type(), [&](uint32_t t, uint32_t i0, uint2 e, bool valid) {
+        sweep(std::false_type(), [&](uint32_t t, uint32_t i0, uint2 e, bool valid, uint32_t weight) {
             const int top = valid ? (int)(e.x >> kHist2Shift) : -1;
             const uint64_t above = __ballot(top > prefix), same = __ballot(top == prefix);
             vm = top > prefix && e.y > vm ? e.y : vm;
-            if (above && lane == 0) tgt[t] += (uint32_t)__popcll(above);
+            if (above && lane == 0) tgt[t] += (uint32_t)__popcll(above) * weight;
+            // a tile taken as one has more than kListCap candidates, so its digit is not the one with few
             if (same && top == prefix) {
                 const uint32_t at = atomicAdd(&s_listed, 1u);
                 if (at < kListCap) {
@@ -564,8 +604,8 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
     } else if (any) {
         for (int i = tid; i < 512; i += LANES) h[i] = 0u;
         __syncthreads();
-        sweep(std::false_type(), [&](uint32_t, uint32_t, uint2 e, bool valid) {
-            count_digit(valid && (int)(e.x >> kHist2Shift) == prefix, e.x & 511u, true);
+        sweep(std::false_type(), [&](uint32_t, uint32_t, uint2 e, bool valid, uint32_t weight) {
+            count_digit(valid && (int)(e.x >> kHist2Shift) == prefix, e.x & 511u, true, weight);
         });
         __syncthreads();
         if (tid == 0) {
@@ -581,11 +621,11 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
         quota = s_need;
         equal = s_count;
         ties = equal != quota;
-        sweep(std::false_type(), [&](uint32_t t, uint32_t, uint2 e, bool valid) {
+        sweep(std::false_type(), [&](uint32_t t, uint32_t, uint2 e, bool valid, uint32_t weight) {
             const uint64_t gm = __ballot(valid && e.x > tau), em = __ballot(valid && e.x == tau);
             if (lane == 0 && (gm | em)) {
-                tgt[t] += (uint32_t)__popcll(gm);
-                teq[t] += (uint32_t)__popcll(em);
+                tgt[t] += (uint32_t)__popcll(gm) * weight;
+                teq[t] += (uint32_t)__popcll(em) * weight;
             }
             vm = valid && (ties ? e.x > tau : e.x >= tau) && e.y > vm ? e.y : vm;
         });
@@ -641,7 +681,8 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
         if (count_equal && ties) {
             __syncthreads();
             for (uint32_t t = (uint32_t)wave; t < Tn; t += NW) {
-                const uint32_t nc = count_of(t), take = teq[t];
+                uint32_t weight;
+                const uint32_t nc = count_of(t, weight), take = teq[t];
                 uint32_t eqrun = 0;  // bins of the tile equal to tau seen so far
                 for (uint32_t i0 = 0; i0 < nc && eqrun < take; i0 += 64u) {
                     const bool valid = i0 + (uint32_t)lane < nc;

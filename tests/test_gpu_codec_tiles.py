@@ -34,3 +34,17 @@ def test_tiles_match_the_oracle(dev, ref, logL, bits):
         out, st = dev.decode_accumulate(streams, n, L, 0.4, bits)
         assert st == 0
         assert np.array_equal(out, ref.decode_accumulate_spectrum(streams, n, L, 0.4, bits, nthreads=4))
+
+
+@pytest.mark.parametrize("bits", (8, 32))
+@pytest.mark.parametrize("tail", (1, 786, 2048, 3000, 70000))
+def test_topk_chunk_of_nearly_only_zeros(dev, ref, tail, bits):
+    """tiles whose candidates are all one value count as one candidate, beside tiles where they are not"""
+    L = 1 << 17
+    n = L + tail
+    rng = np.random.default_rng(tail)
+    g = rng.standard_normal(n).astype(np.float32)
+    g[rng.random(n) < 0.01] = 0.0
+    for theta in (0.9, 0.6, 0.001):
+        print(f"tail={tail} bits={bits} theta={theta}", flush=True)
+        assert np.array_equal(dev.topk_compress(g, L, theta, bits), ref.topk_compress(g, L, theta, bits))
