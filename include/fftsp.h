@@ -219,15 +219,13 @@ int fftsp_topk_decompress(const void* d_packed, size_t packed_bytes, float* d_gr
  *      L_i = max(32, next power of two >= its size); seg_offsets (nseg+1 entries, ascending) is on the HOST
  *      and is consumed before the call returns.  Sizes above 2^22 are FFTSP_EUNSUPPORTED.
  *      Records follow tensor order in the stream.  Tensors of up to 2^15 samples, whatever their lengths, run as one
- *      launch per direction (up to 128 at a time).  Longer ones that pad to the same L_i run together as the chunks of
- *      shared launch sets (up to 64 at a time), so their cost grows with the number of distinct lengths rather
- *      than with the number of tensors.  These launch sets run on up to four streams at once (the caller's and
- *      streams of the library's own that fork from and join back into it, so the call is still one unit of work
- *      on the caller's stream and can be captured into a graph); the workspace holds one region per stream, each
- *      sized for the largest group.  The side streams belong to the device and are shared by all callers: calls
- *      from several host threads enqueue one after the other.  A captured call keeps the side streams inside its
- *      capture until that capture ends; a call made meanwhile on another stream, and a captured call made before
- *      the side streams exist, runs all its launch sets on the caller's stream alone (same bytes, less overlap). ---- */
+ *      launch per direction (up to 128 at a time).  All longer ones share one launch per kernel, whatever their lengths (up
+ *      to 64 of them and 2^26 padded samples at a time).  Where the longer ones take a while, the others run beside
+ *      them on a stream of the library's own that forks from and joins back into the caller's, so the call is still
+ *      one unit of work on the caller's stream and can be captured into a graph.  That stream belongs to the device
+ *      and is shared by all callers: calls from several host threads enqueue one after the other.  A captured call
+ *      keeps it inside its capture until that capture ends; a call made meanwhile on another stream, and a captured
+ *      call made before it exists, runs everything on the caller's stream alone (same bytes, less overlap). ---- */
 size_t fftsp_packed_bytes_segments(const size_t* seg_offsets, int nseg, float theta, int bits);
 size_t fftsp_workspace_bytes_segments(const size_t* seg_offsets, int nseg, int bits);
 int fftsp_compress_segments(const float* d_grad, const size_t* seg_offsets, int nseg, float theta, int bits,
