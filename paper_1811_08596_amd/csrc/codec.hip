@@ -304,6 +304,10 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
     if (threadIdx.x == 0) *reinterpret_cast<uint2*>(sel + c * 8) = make_uint2(b.star, b.need);
 }
 
+// Tiles of a chunk whose candidates k_resolve keeps in LDS: 135 KiB beside its other 20.  Longer chunks go through
+// k_count_digit and k_mark before it.
+constexpr uint32_t kKeptTiles = 270;
+
 // --------------------------------------------------------------- collect ----
 // Per tile: count and range of the bins kept outright, and the candidates in bin order.
 //
@@ -318,8 +322,8 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
 template <bool FIND, bool TABLE, bool REAL, bool HALF>
 __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u,
                                                 const uint32_t* __restrict__ hist, uint32_t* __restrict__ sel,
-                                                uint32_t* __restrict__ tinfo, uint2* __restrict__ cand, TableArg<TABLE> tab,
-                                                size_t n)
+                                                uint32_t* __restrict__ tinfo, uint32_t* __restrict__ tscan,
+                                                uint2* __restrict__ cand, TableArg<TABLE> tab, size_t n)
 {
     using E = typename Elem<REAL>::T;
     __shared__ uint32_t wcnt[4], wdef[4], wvmax[4];
@@ -398,6 +402,8 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
         if ((mine >> r) & 1u) out[off + prefix_popc(cm[r])] = make_uint2(key[r], vb[r]);
         off += (uint32_t)__popcll(cm[r]);
     }
+    if (tid == 64 && at.Tn > kKeptTiles)  // counters of k_count_digit
+        *reinterpret_cast<uint2*>(tscan + (size_t)blockIdx.x * 2) = make_uint2(0u, 0u);
     if (tid == 0) {
         uint32_t* ti = tinfo + (size_t)blockIdx.x * 4;
         ti[0] = wdef[0] + wdef[1] + wdef[2] + wdef[3];
@@ -425,6 +431,154 @@ constexpr int RT = 1024;           // lanes of the per-chunk workgroups of the d
 constexpr int RW = RT / 64;        // 16 waves
 constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1025
 
+// Chunks of more than kKeptTiles tiles: what k_resolve would do in its two sweeps over the candidates is done before it by
+// a workgroup per kPartTiles tiles, because a single one is bound by what a compute unit issues (a chunk of 2^22: 35 us).
+// k_count_digit counts the candidates' second digit into the first kHist2Bins words of the chunk's tscan, which k_collect
+// has cleared.  k_mark adds the candidates above the two digits' common prefix to their tiles' counts and maxima and moves
+// the ones that share it to the front of their tile's list, unless they are more than k_resolve lists.
+// Measured, a call of sender and receiver: a batch whose longest tensor has 2^22 samples 460 -> 452 us, thirty-three chunks
+// of 2^22 1550 -> 1537 us; sixty Top-k chunks of 512 tiles, the fewest there can be, break even with one workgroup (265 us).
+constexpr uint32_t kPartTiles = 64, kPartWave = kPartTiles / (NT / 64);
+inline uint32_t parts_of(uint32_t tiles) { return (tiles + kPartTiles - 1u) / kPartTiles; }
+static_assert(2 * kKeptTiles < (uint32_t)kHist2Bins && 2 * 512 >= kHist2Bins, "longer chunks have 512 tiles at least");
+template <bool TABLE>
+__device__ __forceinline__ Place part_of(const Shape& u, const TableArg<TABLE>& tab, const LongStarts& at, uint32_t& first)
+{
+    if constexpr (TABLE) {
+        const LongShare share = long_share(at);
+        first = share.blk * kPartTiles;
+        return place_of<TABLE>(u, tab, share.tensor, 0u);
+    } else {
+        const uint32_t parts = (u.Tn + kPartTiles - 1u) / kPartTiles;
+        first = blockIdx.x % parts * kPartTiles;
+        return place_of<TABLE>(u, tab, blockIdx.x / parts, 0u);
+    }
+}
+// The candidates of a wave's tiles [t0, t0 + kPartWave): tile(t, info, e) with a lane's candidate of the first row of 64.
+template <typename Tile>
+__device__ __forceinline__ void tiles_of_part(const uint4* ti, const uint2* cd, uint32_t t0, uint32_t Tn, int lane,
+                                              Tile&& tile)
+{
+    constexpr int AHEAD = 8;
+    static_assert(kPartWave % AHEAD == 0, "whole batches");
+    for (uint32_t b = t0; b < t0 + kPartWave && b < Tn; b += AHEAD) {
+        uint2 e[AHEAD];
+#pragma unroll
+        for (int v = 0; v < AHEAD; ++v)  // slots behind a tile's last candidate are allocated; what they hold is dropped
+            e[v] = cd[(size_t)(b + v < Tn ? b + v : b) * kTile + lane];
+#pragma unroll
+        for (int v = 0; v < AHEAD; ++v)
+            if (b + v < Tn) tile(b + v, ti[b + v], e[v]);
+    }
+}
+// candidates' next digit: d, counted for the lanes that want it
+__device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, bool run_likely, int lane, uint32_t weight)
+{
+    if (run_likely) {
+        const uint64_t act = __ballot(hit);
+        if (!act) return;
+        // a row whose keys share the digit (a run of equal values, e.g. zeros) is one atomic
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __ffsll((unsigned long long)act) - 1);
+        if (__ballot(hit && d == d0) == act) {
+            if (lane == 0) atomicAdd(&h[d0], (uint32_t)__popcll(act) * weight);
+            return;
+        }
+    }
+    if (hit) atomicAdd(&h[d], weight);
+}
+template <bool TABLE>
+__global__ __launch_bounds__(NT) void k_count_digit(Shape u, const uint32_t* __restrict__ tinfo, uint32_t* __restrict__ tscan,
+                                                    const uint2* __restrict__ cand, TableArg<TABLE> tab, LongStarts at)
+{
+    __shared__ uint32_t h[kHist2Bins];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t first;
+    const Place p = part_of<TABLE>(u, tab, at, first);
+    for (int i = tid; i < kHist2Bins; i += NT) h[i] = 0u;
+    __syncthreads();
+    const uint2* cd = cand + p.tile0 * (size_t)kTile;
+    tiles_of_part(reinterpret_cast<const uint4*>(tinfo) + p.tile0, cd, first + (uint32_t)wave * kPartWave, p.Tn, lane,
+                  [&](uint32_t t, uint4 info, uint2 e) __attribute__((always_inline)) {
+                      const uint32_t nc = info.w ? (info.z ? 1u : 0u) : info.z, weight = info.w ? info.z : 1u;
+                      for (uint32_t i0 = 0; i0 < nc; i0 += 64u) {
+                          const bool valid = i0 + (uint32_t)lane < nc;
+                          if (i0) e = cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)];
+                          count_digit(h, valid, (e.x >> kHist2Shift) & (uint32_t)(kHist2Bins - 1), i0 != 0, lane, weight);
+                      }
+                  });
+    __syncthreads();
+    uint32_t* g = tscan + (size_t)p.tile0 * 2;
+    for (int i = tid; i < kHist2Bins; i += NT)
+        if (h[i]) atomicAdd(&g[i], h[i]);
+}
+// the second digit of the threshold's key from its counts, by a whole workgroup of LANES lanes; need as k_find_bucket's
+template <int LANES>
+__device__ __forceinline__ void second_digit(const uint32_t* h, uint32_t need, uint32_t* tmp, uint32_t& s_digit, uint32_t& s_need,
+                                             uint32_t& s_count)
+{
+    constexpr int PER = kHist2Bins / LANES;
+    static_assert(PER >= 1, "a lane scans whole counters");
+    // scan from the top digit down
+    uint32_t cnt[PER], sum = 0;
+    const int base = kHist2Bins - PER - (int)threadIdx.x * PER;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        cnt[i] = h[base + i];
+        sum += cnt[i];
+    }
+    uint32_t run = block_scan_incl<LANES / 64>(sum, tmp) - sum;
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+        if (run < need && run + cnt[i] >= need) {
+            s_digit = (uint32_t)(base + i);
+            s_need = need - run;
+            s_count = cnt[i];
+        }
+        run += cnt[i];
+    }
+    __syncthreads();
+}
+template <bool TABLE>
+__global__ __launch_bounds__(NT) void k_mark(Shape u, const uint32_t* __restrict__ sel, uint32_t* __restrict__ tinfo,
+                                             const uint32_t* __restrict__ tscan, uint2* __restrict__ cand, TableArg<TABLE> tab,
+                                             LongStarts at)
+{
+    __shared__ uint32_t tmp[NT / 64], s_digit, s_need, s_count;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t first;
+    const Place p = part_of<TABLE>(u, tab, at, first);
+    const uint32_t bstar = sel[p.chunk * 8 + 0], need = sel[p.chunk * 8 + 1];
+    if (tid == 0) s_digit = s_need = s_count = 0u;
+    second_digit<NT>(tscan + (size_t)p.tile0 * 2, need, tmp, s_digit, s_need, s_count);
+    if (need == 0 || s_count > kListCap) return;
+    const int prefix = (int)((bstar << kHist2Bits) | s_digit);
+    uint4* ti = reinterpret_cast<uint4*>(tinfo) + p.tile0;
+    uint2* cd = cand + p.tile0 * (size_t)kTile;
+    const uint32_t t0 = first + (uint32_t)wave * kPartWave;
+    uint32_t vm = 0;
+    tiles_of_part(ti, cd, t0, p.Tn, lane, [&](uint32_t t, uint4 info, uint2 e) __attribute__((always_inline)) {
+        const uint32_t nc = info.w ? (info.z ? 1u : 0u) : info.z, weight = info.w ? info.z : 1u;
+        uint32_t more = 0, same = 0;
+        for (uint32_t i0 = 0; i0 < nc; i0 += 64u) {
+            const bool valid = i0 + (uint32_t)lane < nc;
+            if (i0) e = cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)];
+            const int top = valid ? (int)(e.x >> kHist2Shift) : -1;
+            more += (uint32_t)__popcll(__ballot(top > prefix)) * weight;
+            vm = top > prefix && e.y > vm ? e.y : vm;
+            // a tile taken as one has more than kListCap candidates, so its digit is not this one
+            const uint64_t m = __ballot(top == prefix);
+            if (top == prefix) cd[(size_t)t * kTile + same + prefix_popc(m)] = e;  // never past the row it comes from
+            same += (uint32_t)__popcll(m);
+        }
+        if (lane == 0) ti[t] = make_uint4(info.x + more, info.y, same, 0u);
+    });
+    vm = wave_max(vm);
+    if (lane == 0 && vm && t0 < p.Tn) {
+        uint32_t* y = &tinfo[((size_t)p.tile0 + t0) * 4 + 1];  // the maximum is the chunk's: any tile will do
+        *y = vm > *y ? vm : *y;
+    }
+}
+
 // One workgroup per chunk: finish the radix select on the candidates, break ties by bin order, scan the tiles, find the
 // survivors' largest component, write the record header and zero the code words that two tiles will share.
 //
@@ -442,7 +596,6 @@ constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1
 // 2^20 24 -> 18, thirty-three of 2^22 87 -> 44.
 constexpr int kFetch = 8;  // tiles of a wave fetched in one round trip
 constexpr uint32_t kAlike = 0x80000000u;  // mark of a tile whose candidates are all the same
-constexpr uint32_t kKeptTiles = 270;  // 135 KiB beside the kernel's other 20
 template <bool TABLE, int NW, bool KEPT>
 __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, uint32_t static_vmax, uint32_t codes_per_bin,
                                                      uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
@@ -473,7 +626,7 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
         tgt[t] = info.x;
         teq[t] = 0u;
         tnc[t] = info.z | (info.w ? kAlike : 0u);
-        vm = info.x && info.y > vm ? info.y : vm;
+        vm = info.y > vm ? info.y : vm;
         more = more || (info.z > 64u && !info.w);
     }
     for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
@@ -519,46 +672,15 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
         else
             sweep_as(std::bool_constant<KEPT>{}, first, row);
     };
-    // candidates' next digit: d, counted for the lanes of `act` that want it
-    auto count_digit = [&](bool hit, uint32_t d, bool run_likely, uint32_t weight) __attribute__((always_inline)) {
-        if (run_likely) {
-            const uint64_t act = __ballot(hit);
-            if (!act) return;
-            // a row whose keys share the digit (a run of equal values, e.g. zeros) is one atomic
-            const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __ffsll((unsigned long long)act) - 1);
-            if (__ballot(hit && d == d0) == act) {
-                if (lane == 0) atomicAdd(&h[d0], (uint32_t)__popcll(act) * weight);
-                return;
-            }
-        }
-        if (hit) atomicAdd(&h[d], weight);
-    };
-    if (any)
+    const bool counted = Tn > kKeptTiles;  // k_count_digit and k_mark have been here
+    if (any && counted)
+        for (int i = tid; i < kHist2Bins; i += LANES) h[i] = tscan[(size_t)at.tile0 * 2 + i];
+    else if (any)
         sweep(std::true_type(), [&](uint32_t, uint32_t i0, uint2 e, bool valid, uint32_t weight) {
-            count_digit(valid, (e.x >> kHist2Shift) & (uint32_t)(kHist2Bins - 1), i0 != 0, weight);
+            count_digit(h, valid, (e.x >> kHist2Shift) & (uint32_t)(kHist2Bins - 1), i0 != 0, lane, weight);
         });
     __syncthreads();
-    constexpr int PER = kHist2Bins / LANES;
-    static_assert(PER >= 1, "a lane scans whole counters");
-    // scan from the top digit down
-    uint32_t cnt[PER], sum = 0;
-    const int base = kHist2Bins - PER - tid * PER;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        cnt[i] = h[base + i];
-        sum += cnt[i];
-    }
-    uint32_t run = block_scan_incl<NW>(sum, tmp) - sum;
-#pragma unroll
-    for (int i = PER - 1; i >= 0; --i) {
-        if (run < need && run + cnt[i] >= need) {
-            s_digit = (uint32_t)(base + i);
-            s_need = need - run;
-            s_count = cnt[i];
-        }
-        run += cnt[i];
-    }
-    __syncthreads();
+    second_digit<LANES>(h, need, tmp, s_digit, s_need, s_count);
     need = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_need);
     uint32_t equal = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_count);
     const int prefix = (int)((bstar << kHist2Bits) | s_digit);  // the top bits of the threshold's key
@@ -566,21 +688,34 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
     uint32_t tau = any ? (uint32_t)prefix << kHist2Shift : 0xFFFFFFFFu, quota = 0;
     bool ties = false;
     if (any && few) {
-        sweep(std::false_type(), [&](uint32_t t, uint32_t i0, uint2 e, bool valid, uint32_t weight) {
-            const int top = valid ? (int)(e.x >> kHist2Shift) : -1;
-            const uint64_t above = __ballot(top > prefix), same = __ballot(top == prefix);
-            vm = top > prefix && e.y > vm ? e.y : vm;
-            if (above && lane == 0) tgt[t] += (uint32_t)__popcll(above) * weight;
-            // a tile taken as one has more than kListCap candidates, so its digit is not the one with few
-            if (same && top == prefix) {
-                const uint32_t at = atomicAdd(&s_listed, 1u);
-                if (at < kListCap) {
-                    list[at] = e.x;
-                    list_at[at] = t * (uint32_t)kTile + i0 + (uint32_t)lane;
-                    list_vb[at] = e.y;
+        if (counted) {
+            for (uint32_t t = tid; t < Tn; t += LANES)
+                for (uint32_t i = 0, n = tnc[t]; i < n; ++i) {
+                    const uint2 e = cd[(size_t)t * kTile + i];
+                    const uint32_t at_list = atomicAdd(&s_listed, 1u);
+                    if (at_list < kListCap) {
+                        list[at_list] = e.x;
+                        list_at[at_list] = t * (uint32_t)kTile + i;
+                        list_vb[at_list] = e.y;
+                    }
                 }
-            }
-        });
+        } else {
+            sweep(std::false_type(), [&](uint32_t t, uint32_t i0, uint2 e, bool valid, uint32_t weight) {
+                const int top = valid ? (int)(e.x >> kHist2Shift) : -1;
+                const uint64_t above = __ballot(top > prefix), same = __ballot(top == prefix);
+                vm = top > prefix && e.y > vm ? e.y : vm;
+                if (above && lane == 0) tgt[t] += (uint32_t)__popcll(above) * weight;
+                // a tile taken as one has more than kListCap candidates, so its digit is not the one with few
+                if (same && top == prefix) {
+                    const uint32_t at = atomicAdd(&s_listed, 1u);
+                    if (at < kListCap) {
+                        list[at] = e.x;
+                        list_at[at] = t * (uint32_t)kTile + i0 + (uint32_t)lane;
+                        list_vb[at] = e.y;
+                    }
+                }
+            });
+        }
         __syncthreads();
         const uint32_t listed = equal;
         search_list<4>(list, listed, kHist2Shift, lane, tau, need, equal);
@@ -605,7 +740,7 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
         for (int i = tid; i < 512; i += LANES) h[i] = 0u;
         __syncthreads();
         sweep(std::false_type(), [&](uint32_t, uint32_t, uint2 e, bool valid, uint32_t weight) {
-            count_digit(valid && (int)(e.x >> kHist2Shift) == prefix, e.x & 511u, true, weight);
+            count_digit(h, valid && (int)(e.x >> kHist2Shift) == prefix, e.x & 511u, true, lane, weight);
         });
         __syncthreads();
         if (tid == 0) {
@@ -1397,14 +1532,14 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
         auto collect = [&](auto find) {
             constexpr bool FIND = decltype(find)::value;
             if constexpr (TABLE) {
-                FFTSP_LAUNCH("collect", (k_collect<FIND, true, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, cand, tab, a.n);
+                FFTSP_LAUNCH("collect", (k_collect<FIND, true, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, tscan, cand, tab, a.n);
             } else {
                 if (a.time_domain)
-                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, true, false>), per_tile, dim3(NT), 0, s, spec, u, hist, sel, tinfo, cand, tab, a.n);
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, true, false>), per_tile, dim3(NT), 0, s, spec, u, hist, sel, tinfo, tscan, cand, tab, a.n);
                 else if (a.half)
-                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, true>), per_tile, dim3(NT), 0, s, Xh, u, hist, sel, tinfo, cand, tab, a.n);
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, true>), per_tile, dim3(NT), 0, s, Xh, u, hist, sel, tinfo, tscan, cand, tab, a.n);
                 else
-                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, cand, tab, a.n);
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, tscan, cand, tab, a.n);
             }
         };
         if (find_in_collect(x)) {
@@ -1412,6 +1547,22 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
         } else {
             FFTSP_LAUNCH("find_bucket", k_find_bucket<TABLE>, per_chunk, dim3(NT), 0, s, hist, u, sel, tab);
             collect(std::false_type{});
+        }
+        if (x.most > kKeptTiles) {
+            LongStarts at{};
+            uint32_t parts = (uint32_t)x.chunks * parts_of(x.most);
+            if constexpr (TABLE) {
+                // the longest tensors are the last ones
+                parts = 0;
+                at.first = a.tab->count;
+                while (at.first > 0 && (1u << a.tab->tab.t[at.first - 1].logM) / (uint32_t)kTile + 1u > kKeptTiles) --at.first;
+                for (uint32_t i = at.first; i < a.tab->count; ++i) {
+                    at.at[at.count++] = (uint16_t)parts;
+                    parts += parts_of((1u << a.tab->tab.t[i].logM) / (uint32_t)kTile + 1u);
+                }
+            }
+            FFTSP_LAUNCH("count_digit", k_count_digit<TABLE>, dim3(parts), dim3(NT), 0, s, u, tinfo, tscan, cand, tab, at);
+            FFTSP_LAUNCH("mark", k_mark<TABLE>, dim3(parts), dim3(NT), 0, s, u, sel, tinfo, tscan, cand, tab, at);
         }
         // few waves for few tiles: their barriers are cheaper than more hands
         auto resolve = [&](auto waves, auto keep) {

@@ -37,14 +37,27 @@ def test_tiles_match_the_oracle(dev, ref, logL, bits):
 
 
 @pytest.mark.parametrize("bits", (8, 32))
-@pytest.mark.parametrize("tail", (1, 786, 2048, 3000, 70000))
-def test_topk_chunk_of_nearly_only_zeros(dev, ref, tail, bits):
-    """tiles whose candidates are all one value count as one candidate, beside tiles where they are not"""
-    L = 1 << 17
+@pytest.mark.parametrize("logL, tail", ((17, 1), (17, 786), (17, 2048), (17, 3000), (17, 70000), (20, 786), (20, 70001)))
+def test_topk_chunk_of_nearly_only_zeros(dev, ref, logL, tail, bits):
+    """tiles whose candidates are all one value count as one candidate, beside tiles where they are not; in chunks that one
+    workgroup resolves alone and in longer ones"""
+    L = 1 << logL
     n = L + tail
     rng = np.random.default_rng(tail)
     g = rng.standard_normal(n).astype(np.float32)
     g[rng.random(n) < 0.01] = 0.0
     for theta in (0.9, 0.6, 0.001):
-        print(f"tail={tail} bits={bits} theta={theta}", flush=True)
-        assert np.array_equal(dev.topk_compress(g, L, theta, bits), ref.topk_compress(g, L, theta, bits))
+        print(f"L=2^{logL} tail={tail} bits={bits} theta={theta}", flush=True)
+        assert np.array_equal(dev.topk_compress(g, L, theta, bits), ref.topk_compress(g, L, theta, bits, nthreads=8))
+
+
+@pytest.mark.parametrize("logL, ties", ((21, False), (21, True), (22, False), (22, True)))
+def test_chunks_resolved_by_several_workgroups(dev, ref, logL, ties):
+    L = 1 << logL
+    spec = np.random.default_rng(logL).standard_normal(2 * (L + 2)).astype(np.float32)
+    if ties:
+        spec = (np.round(spec * 4.0) / 4.0).astype(np.float32)
+    for theta in (0.5, 0.001):
+        print(f"L=2^{logL} ties={ties} theta={theta}", flush=True)
+        want = ref.encode_spectrum(spec, 2 * L - 5, L, theta, 8, nthreads=8)
+        assert np.array_equal(dev.encode(spec, 2 * L - 5, L, theta, 8), want)
