@@ -232,8 +232,8 @@ int apply_quantizer(Plan* p, const fftsp_quantizer* q, uint32_t* static_vmax)
 // All chunks of one stream to units; verdicts go where the sender would keep its tile prefixes.
 hipError_t decode_stream(const Plan& p, const uint8_t* in, const CodecArgs& a, float* units, uint8_t* ws, hipStream_t s)
 {
-    if (p.C > 0xffffffffu || p.ws.tscan / 4 > 0xffffffffu) return hipErrorInvalidValue;
-    const StatusNote note{(uint32_t)p.C, (uint32_t)(p.ws.tscan / 4)};
+    if (p.C > 0xffffffffu) return hipErrorInvalidValue;
+    const StatusNote note{(uint32_t)p.C, p.ws.tscan};
     return launch_decode(in, in + kStreamHeader, a, units, ws, p.ws, 1, reinterpret_cast<uint32_t*>(ws + p.ws.tscan), &note, s);
 }
 
@@ -242,8 +242,8 @@ hipError_t decompress_chunks(const Plan& p, const PeerList& streams, int npeers,
                              float gain, uint8_t* ws, size_t verd, Tables t, hipStream_t s)
 {
     const size_t count = p.C * (size_t)npeers;
-    if (count > 0xffffffffu || verd / 4 > 0xffffffffu) return hipErrorInvalidValue;
-    const StatusNote note{(uint32_t)count, (uint32_t)(verd / 4)};
+    if (count > 0xffffffffu) return hipErrorInvalidValue;
+    const StatusNote note{(uint32_t)count, verd};
     return launch_chunk_decompress(streams, npeers, plain, p.logL, a, out, p.n, gain, reinterpret_cast<uint32_t*>(ws + p.ws.status),
                                    note, reinterpret_cast<uint32_t*>(ws + verd), t, s);
 }
@@ -1045,9 +1045,8 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const SegmentPlan plan = plan_segments(seg_offsets, nseg, theta, bits, true);
     const size_t verd = segment_verdicts(plan);
-    if (verd / 4 > 0xffffffffu) return FFTSP_EHIP;
     uint32_t* verdicts = reinterpret_cast<uint32_t*>(ws + verd);
-    const StatusNote note{(uint32_t)nseg, (uint32_t)(verd / 4)};
+    const StatusNote note{(uint32_t)nseg, verd};
     const hipError_t e = run_segments(
         plan, s,
         [&](hipStream_t st) {
@@ -1057,7 +1056,7 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
                 hdr.write_header = i == 0;
                 pe = launch_tensors_decompress(in, plan.shorts[i].tab, plan.shorts[i].pieces, plan.shorts[i].top_logL,
                                                QuantizerArgs{bits, m}, hdr, d_grad_out, reinterpret_cast<uint32_t*>(ws),
-                                               i == 0 ? note : StatusNote{0u, 0u}, 1, verdicts, t, st);
+                                               i == 0 ? note : StatusNote{}, 1, verdicts, t, st);
             }
             return pe;
         },
@@ -1084,12 +1083,13 @@ int fftsp_device_status(const void* d_workspace, int* status_out)
 {
     if (!d_workspace || !status_out) return FFTSP_EINVAL;
     if (hipDeviceSynchronize() != hipSuccess) return FFTSP_EHIP;
-    uint32_t v[5] = {};
+    uint32_t v[kNoteWord + kNoteWords] = {};
     if (hipMemcpy(v, d_workspace, sizeof(v), hipMemcpyDeviceToHost) != hipSuccess) return FFTSP_EHIP;
     uint32_t worst = v[0];
-    if (v[4] == kStatusNoteMagic && v[2] > 0) {  // one verdict per record
-        std::vector<uint32_t> verdicts(v[2]);
-        if (hipMemcpy(verdicts.data(), static_cast<const uint8_t*>(d_workspace) + (size_t)v[3] * 4, verdicts.size() * 4,
+    const StatusNote note{v[2], v[3] | (uint64_t)v[5] << 32};
+    if (v[4] == kStatusNoteMagic && note.count > 0) {  // one verdict per record
+        std::vector<uint32_t> verdicts(note.count);
+        if (hipMemcpy(verdicts.data(), static_cast<const uint8_t*>(d_workspace) + note.offset, verdicts.size() * 4,
                       hipMemcpyDeviceToHost) != hipSuccess)
             return FFTSP_EHIP;
         worst = std::max(worst, *std::max_element(verdicts.begin(), verdicts.end()));

@@ -666,9 +666,8 @@ __device__ __forceinline__ void write_control(uint32_t* __restrict__ ctl, const 
             ctl[0] = 0u;
             ctl[1] = 0u;
         }
-        ctl[2] = note.count;
-        ctl[3] = note.offset;
-        ctl[4] = note.count ? kStatusNoteMagic : 0u;
+#pragma unroll
+        for (int i = kNoteWord; i < kNoteWord + kNoteWords; ++i) ctl[i] = note_word(note, i);
     }
 }
 
@@ -749,7 +748,7 @@ __global__ __launch_bounds__(NT) void k_chunk_compress(const float* __restrict__
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x;
     if (blockIdx.x == 0) {
-        write_control(ctl, StatusNote{0u, 0u}, true, tid);
+        write_control(ctl, StatusNote{}, true, tid);
         if (tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
     }
     const UniformChunks where(n, C, G::T, 2u * G::M, a.S, aligned);
@@ -789,7 +788,7 @@ __global__ __launch_bounds__(tensor_threads<TOP>()) void k_tensors_compress(cons
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x;
     if (blockIdx.x == 0) {
-        if (ctl) write_control(ctl, StatusNote{0u, 0u}, true, tid);
+        if (ctl) write_control(ctl, StatusNote{}, true, tid);
         if (hdr.write && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
     }
     const TensorPiece piece = t.piece[blockIdx.x];
@@ -832,7 +831,7 @@ __global__ __launch_bounds__(TopkGeo<LOGL>::NT) void k_topk_compress(const float
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63, group = tid / G::NL, wig = (tid >> 6) % G::WAVES;
     if (blockIdx.x == 0) {
-        write_control(ctl, StatusNote{0u, 0u}, true, tid);
+        write_control(ctl, StatusNote{}, true, tid);
         if (tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
     }
     const size_t c = (size_t)blockIdx.x * G::GROUPS + (size_t)group;

@@ -1094,7 +1094,7 @@ __device__ __forceinline__ void write_control(uint32_t* __restrict__ ctl, const 
 {
     // cleared as a whole: also the hand-over words of the fused inverse transform that may follow
     for (int i = tid; i < (int)(kControlBytes / 4); i += lanes)
-        ctl[i] = i == 2 ? note.count : (i == 3 ? note.offset : (i == 4 ? kStatusNoteMagic : 0u));
+        ctl[i] = i >= kNoteWord && i < kNoteWord + kNoteWords ? note_word(note, i) : 0u;
 }
 
 template <bool TABLE>
@@ -1606,7 +1606,7 @@ hipError_t launch_decode(const uint8_t* stream_base, const uint8_t* records, con
     const Shape u = shape_of(a);
     const Extent x = extent_of(a);
     uint32_t* ctl = first ? reinterpret_cast<uint32_t*>(ws_base + w.status) : nullptr;
-    const StatusNote note = first ? *first : StatusNote{0u, 0u};
+    const StatusNote note = first ? *first : StatusNote{};
     if (x.tiles > 0x7fffffffu) return hipErrorInvalidValue;
     if (a.half && (a.tab || a.time_domain)) return hipErrorInvalidValue;
     if (a.time_domain && (a.tab || a.pair_log)) return hipErrorInvalidValue;
@@ -1668,10 +1668,10 @@ hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecA
     uint32_t* verdicts = reinterpret_cast<uint32_t*>(ws_base + pw.verd);
     if (npeers < 1 || npeers > kMaxPeers || a.half || a.tab || a.time_domain) return hipErrorInvalidValue;
     const size_t count = a.C * (size_t)npeers;
-    if (a.C * (size_t)u.Tn > 0x7fffffffu || count > 0x7fffffffu || pw.verd / 4 > 0xffffffffu) return hipErrorInvalidValue;
+    if (a.C * (size_t)u.Tn > 0x7fffffffu || count > 0x7fffffffu) return hipErrorInvalidValue;
     HeaderInfo h{1, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
     FFTSP_LAUNCH("group_prefix", k_group_prefix_peers, dim3((unsigned)count), dim3(RT), 0, s, streams, (uint32_t)a.C, a.S, u.W,
-                 a.k, h, gprefix, verdicts, ctl, StatusNote{(uint32_t)count, (uint32_t)(pw.verd / 4)});
+                 a.k, h, gprefix, verdicts, ctl, StatusNote{(uint32_t)count, pw.verd});
     PeerList recs{};
     for (int i = 0; i < npeers; ++i) recs.p[i] = streams.p[i] + 64;  // records follow the 64-byte stream header
     const bool vec = a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0;

@@ -98,18 +98,31 @@ static inline bool fused_shape(int logL, size_t C)
     return logM >= 15 && logM <= 19 && (C << logL) * 4 >= kFusedScratchBytes;
 }
 
-// The receiver's kernels store one verdict per record, and the call's first kernel leaves this note in words 2..4 of the
-// control block: how many there are, where (in words from the workspace's start), and a magic word.  So no earlier kernel has
-// to clear a status word before a record raises it.  fftsp_device_status looks at both.
+// The receiver's kernels store one verdict per record, and the call's first kernel leaves this note in words 2..5 of the
+// control block: how many there are, where (bytes from the workspace's start; calls with many short chunks have them
+// beyond 16 GiB), and a magic word.  So no earlier kernel has to clear a status word before a record raises it.
+// fftsp_device_status looks at both.
 struct StatusNote {
-    uint32_t count, offset;
+    uint32_t count;
+    uint64_t offset;
 };
 constexpr uint32_t kStatusNoteMagic = 0x46535653u;
+constexpr int kNoteWord = 2, kNoteWords = 4;  // of the control block
+// word i of it, for these four
+__host__ __device__ inline uint32_t note_word(const StatusNote& n, int i)
+{
+    switch (i - kNoteWord) {
+        case 0: return n.count;
+        case 1: return (uint32_t)n.offset;
+        case 2: return n.count ? kStatusNoteMagic : 0u;
+        default: return (uint32_t)(n.offset >> 32);
+    }
+}
 
 // Where everything lives inside the caller's workspace (byte offsets, 256-aligned).
 struct Workspace {
     size_t status;    // u32[1024] control block: word 0 = device status, word 1 = "the fused transform gave up",
-                      //           words 2..4 = where per-record verdicts are,
+                      //           words 2..5 = where per-record verdicts are,
                       //           from word 32 on the hand-over counters of the fused kernels (fused.hip)
     size_t hist;      // u32[C][kHistBins]         (directly after status: one fill zeroes both)
     size_t sel;       // u32[C][8]  bstar, need, tau, quota, pbase, vmax, -, -

@@ -1,0 +1,117 @@
+"""What the entry points enqueue, without a GPU: a recording stand-in for the HIP runtime is loaded in front of the
+library in a process of its own, so host-side decisions (which calls are taken, which launches they become) can be looked at
+for sizes no CPU test could compute.  Device addresses are made up; nothing dereferences them."""
+import json
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+RUNTIME = r"""
+#include <stddef.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+typedef struct { uint32_t x, y, z; } dim3;
+typedef int (*any)(void);
+static struct { const void* f; char name[200]; } known[4096];
+static int n_known;
+static FILE* out;
+static dim3 grid, block;
+static size_t lds;
+static void* stream;
+static const char* name_of(const void* f)
+{
+    for (int i = 0; i < n_known; ++i) if (known[i].f == f) return known[i].name;
+    return "?";
+}
+static void say(const char* what, const void* f, size_t a, size_t b)
+{
+    if (!out) out = fopen(getenv("LAUNCH_LOG"), "w");
+    fprintf(out, "%s %s %zu %zu\n", what, name_of(f), a, b);
+    fflush(out);
+}
+void** __hipRegisterFatBinary(const void* d) { static void* h; (void)d; return &h; }
+void __hipUnregisterFatBinary(void** m) { (void)m; }
+void __hipRegisterFunction(void** m, const void* f, char* df, const char* name, unsigned t, void* a, void* b, void* c, void* d, int* w)
+{
+    if (n_known < 4096) { known[n_known].f = f; strncpy(known[n_known++].name, name, 199); }
+}
+void __hipRegisterVar(void** m, void* v, char* h, char* d, int e, size_t s, int c, int g) {}
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t l, void* s) { grid = g; block = b; lds = l; stream = s; return 0; }
+int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* l, void** s) { *g = grid; *b = block; *l = lds; *s = stream; return 0; }
+int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t l, void* s) { say("launch", f, (size_t)g.x * b.x, l); return 0; }
+int hipFuncSetAttribute(const void* f, int attr, int value) { say("lds", f, (size_t)value, (size_t)attr); return 0; }
+int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipGetSymbolAddress(void** p, const void* s) { *p = (void*)(uintptr_t)0x10000; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipStreamGetCaptureInfo(void* s, int* st, unsigned long long* id) { *st = 0; *id = 0; return 0; }
+int hipStreamCreateWithFlags(void** s, unsigned f) { *s = (void*)(uintptr_t)0x20000; return 0; }
+int hipStreamDestroy(void* s) { return 0; }
+int hipStreamWaitEvent(void* s, void* e, unsigned f) { return 0; }
+int hipEventCreateWithFlags(void** e, unsigned f) { *e = (void*)(uintptr_t)0x30000; return 0; }
+int hipEventDestroy(void* e) { return 0; }
+int hipEventRecord(void* e, void* s) { return 0; }
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    d = tmp_path_factory.mktemp("runtime")
+    src, so = d / "runtime.c", d / "runtime.so"
+    src.write_text(RUNTIME)
+    subprocess.run(["gcc", "-O1", "-w", "-shared", "-fPIC", "-o", str(so), str(src)], check=True)
+    return str(so)
+
+
+def calls_made(runtime, tmp_path, calls):
+    """Runs the calls (entry point, arguments; "big" stands for a buffer that is large enough) in a process behind the
+    recording runtime.  Returns their statuses and what was recorded: (what, kernel, number, number)."""
+    log = tmp_path / "log"
+    program = textwrap.dedent("""
+        import ctypes, json, os, sys
+        ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+        from paper_1811_08596_amd import fftsp
+        lib, status = fftsp.load(), []
+        for name, args in json.load(sys.stdin):
+            f = getattr(lib, name)
+            given = []
+            for a, t in zip(args, f.argtypes):
+                if a == "big":
+                    a = 1 << 60 if t is ctypes.c_size_t else 1 << 40
+                elif isinstance(a, list):
+                    a = (t._type_ * len(a))(*a)
+                given.append(a)
+            status.append(f(*given))
+        print(json.dumps(status))
+    """)
+    r = subprocess.run([sys.executable, "-c", program, runtime], input=json.dumps(calls), capture_output=True, text=True,
+                       cwd=ROOT, env={**os.environ, "LAUNCH_LOG": str(log)}, timeout=120)
+    assert r.returncode == 0, r.stderr
+    rows = [line.split() for line in log.read_text().splitlines()] if log.exists() else []
+    return json.loads(r.stdout), [(a, b, int(c), int(d)) for a, b, c, d in rows]
+
+
+def decompress(n, L, theta=0.3, bits=8):
+    return ["fftsp_decompress", ["big", "big", "big", n, L, theta, bits, "big", "big", None]]
+
+
+def accumulate(n, L, peers=2):
+    return ["fftsp_decompress_accumulate", [[1 << 40] * peers, peers, "big", 0.5, "big", n, L, 0.3, 8, "big", "big", None]]
+
+
+def test_receivers_take_as_many_chunks_as_senders(runtime, tmp_path):
+    """Short chunks of long gradients: the verdicts lie beyond 2^32 words of the workspace (16 KiB of histogram a chunk)."""
+    n = 62378344
+    calls = [decompress(n, 32), decompress(138357544, 128), accumulate(n, 64), accumulate(n, 32, 8),
+             ["fftsp_topk_decompress", ["big", "big", "big", n, 32, 0.3, 8, "big", "big", None]],
+             ["fftsp_decode_spectrum", ["big", "big", n, 32, 0.3, 8, "big", "big", "big", None]],
+             ["fftsp_decode_accumulate_spectrum", [[1 << 40] * 2, 2, "big", n, 64, 0.3, 8, "big", "big", "big", None]],
+             ["fftsp_compress", ["big", n, 32, 0.3, 8, "big", "big", "big", "big", None]]]
+    status, _ = calls_made(runtime, tmp_path, calls)
+    assert status == [0] * len(calls)
