@@ -1154,6 +1154,8 @@ __global__ __launch_bounds__(NT) void k_chunk_irfft(const float2* __restrict__ s
 }
 
 // ---------------------------------------------------------------- launch ----
+// bytes: the most that any call of this kernel takes, not what this one does.  The attribute is the kernel's: another thread
+// may be between setting it and its launch.
 template <typename K>
 hipError_t allow_lds(K kernel, size_t bytes)
 {
@@ -1192,6 +1194,29 @@ constexpr size_t receiver_lds(size_t region)
     using G = Geo<LOGM, NT>;
     return G::RECEIVER_FRONT + G::GROUPS * region + (size_t)G::TW * sizeof(float2);
 }
+// the longest record of M + 1 bins: all of them kept, 32-bit codes
+constexpr size_t longest_record(size_t M) { return (16 + 4 * ((M + 32) / 32) + 8 * (M + 1) + 15) / 16 * 16; }
+template <int LOGM, int NT>
+constexpr size_t most_receiver_lds(size_t records)
+{
+    using G = Geo<LOGM, NT>;
+    const size_t need = records * (longest_record(G::M) + 16), data = G::DATA;
+    return receiver_lds<LOGM, NT>(need > data ? need : data);
+}
+// of a per-tensor launch whose longest tensor has 2^(LOGM+1) samples
+template <int LOGM>
+constexpr size_t most_tensors_lds(bool sender)
+{
+    constexpr int NT = tensor_threads<LOGM>();
+    const size_t own = sender ? sender_lds<LOGM, NT>() : most_receiver_lds<LOGM, NT>(1);
+    if constexpr (LOGM > 4) {
+        const size_t shorter = most_tensors_lds<LOGM - 1>(sender);
+        return own > shorter ? own : shorter;
+    }
+    return own;
+}
+constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit
+static_assert(most_tensors_lds<14>(true) <= kLdsBytes && most_tensors_lds<14>(false) <= kLdsBytes, "fits");
 
 template <int LOGM>
 hipError_t compress_as(const float* in, size_t n, const CodecArgs& a, uint8_t* stream, uint8_t* records, uint32_t* ctl,
@@ -1216,7 +1241,8 @@ hipError_t topk_compress_as(const float* in, size_t n, const CodecArgs& a, uint8
     // records are whole 16 bytes; of one with 32-bit codes only header and bitmap pass through LDS
     const size_t image = a.bits == 32 ? 16 + ((size_t)a.L / 8 + 15) / 16 * 16 : a.S;
     const size_t region = G::region(image), lds = G::SCRATCH + G::GROUPS * region;
-    const hipError_t e = allow_lds(k_topk_compress<LOGL>, lds);
+    constexpr size_t longest = (16 + 4 * ((G::L + 31) / 32) + 2 * (size_t)G::L + 15) / 16 * 16;  // all kept, 16-bit codes
+    const hipError_t e = allow_lds(k_topk_compress<LOGL>, G::SCRATCH + G::GROUPS * G::region(longest));
     if (e != hipSuccess) return e;
     FFTSP_LAUNCH("topk_compress", k_topk_compress<LOGL>, dim3((unsigned)((a.C + G::GROUPS - 1) / G::GROUPS)), dim3(G::NT), lds, s, in,
                  n, a.C, pack_args(a), stream, records, header_info(a, 1), ctl, (uint32_t)region);
@@ -1234,7 +1260,7 @@ hipError_t decompress_as(const PeerList& streams, int npeers, int plain, const C
     const size_t region = need > data ? need : data;  // both are multiples of 16
     const size_t lds = receiver_lds<LOGM, NT>(region);
     auto kern = k_chunk_decompress<LOGM, NT>;
-    const hipError_t e = allow_lds(kern, lds);
+    const hipError_t e = allow_lds(kern, most_receiver_lds<LOGM, NT>(G::CPW));
     if (e != hipSuccess) return e;
     FFTSP_LAUNCH("chunk_decompress", kern, dim3((unsigned)((a.C + G::T - 1) / G::T)), dim3(NT), lds, s, streams,
                  (uint32_t)npeers, plain, a.C, t, pack_args(a), header_info(a, 1), out, n, alignment(out), gain,
@@ -1349,7 +1375,8 @@ hipError_t launch_tensors_compress(const float* in, const TensorTable& t, uint32
 {
     const size_t lds = tensors_lds(t, pieces, true);
     const bool low = top_logL <= 12;
-    const hipError_t e = low ? allow_lds(k_tensors_compress<11>, lds) : allow_lds(k_tensors_compress<14>, lds);
+    const hipError_t e = low ? allow_lds(k_tensors_compress<11>, most_tensors_lds<11>(true))
+                             : allow_lds(k_tensors_compress<14>, most_tensors_lds<14>(true));
     if (e != hipSuccess) return e;
     if (low)
         FFTSP_LAUNCH("tensors_compress", k_tensors_compress<11>, dim3(pieces), dim3(tensor_threads<11>()), lds, s, in,
@@ -1366,7 +1393,8 @@ hipError_t launch_tensors_decompress(const uint8_t* stream, const TensorTable& t
 {
     const size_t lds = tensors_lds(t, pieces, false);
     const bool low = top_logL <= 12;
-    const hipError_t e = low ? allow_lds(k_tensors_decompress<11>, lds) : allow_lds(k_tensors_decompress<14>, lds);
+    const hipError_t e = low ? allow_lds(k_tensors_decompress<11>, most_tensors_lds<11>(false))
+                             : allow_lds(k_tensors_decompress<14>, most_tensors_lds<14>(false));
     if (e != hipSuccess) return e;
     PeerList one{};
     one.p[0] = stream;

@@ -1565,22 +1565,27 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
             FFTSP_LAUNCH("mark", k_mark<TABLE>, dim3(parts), dim3(NT), 0, s, u, sel, tinfo, tscan, cand, tab, at);
         }
         // few waves for few tiles: their barriers are cheaper than more hands
+        // KEEP: tiles there is room for in LDS (0: none are kept).  The attribute is the kernel's, not the call's: it is always
+        // set to the most any call takes, since another thread may be between setting it and its launch.
         auto resolve = [&](auto waves, auto keep) {
             constexpr int NW = decltype(waves)::value;
-            constexpr bool KEPT = decltype(keep)::value;
-            const size_t lds = KEPT ? (size_t)std::min(x.most, kKeptTiles) * 512u : 0u;
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_resolve<TABLE, NW, KEPT>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
+            constexpr uint32_t KEEP = decltype(keep)::value;
+            constexpr bool KEPT = KEEP != 0;
+            const size_t lds = std::min(x.most, KEEP) * 512u;
+            if constexpr (KEPT) {
+                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_resolve<TABLE, NW, KEPT>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)(KEEP * 512u));
+                if (e != hipSuccess) return e;
+            }
             FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW, KEPT>), per_chunk, dim3(NW * 64), lds, s, u, a.bits, a.m, a.static_vmax,
                          codes_per_bin, sel, tinfo, tscan, cand, records, stream_base, h, tab);
             return hipGetLastError();
         };
-        if (x.most <= 40u) return resolve(std::integral_constant<int, 4>{}, std::true_type{});
-        if (x.most <= 130u) return resolve(std::integral_constant<int, 8>{}, std::true_type{});
+        if (x.most <= 40u) return resolve(std::integral_constant<int, 4>{}, std::integral_constant<uint32_t, 40>{});
+        if (x.most <= 130u) return resolve(std::integral_constant<int, 8>{}, std::integral_constant<uint32_t, 130>{});
         if constexpr (!TABLE)
-            if (x.most > kKeptTiles) return resolve(std::integral_constant<int, 16>{}, std::false_type{});
-        return resolve(std::integral_constant<int, 16>{}, std::true_type{});
+            if (x.most > kKeptTiles) return resolve(std::integral_constant<int, 16>{}, std::integral_constant<uint32_t, 0>{});
+        return resolve(std::integral_constant<int, 16>{}, std::integral_constant<uint32_t, kKeptTiles>{});
     };
     const hipError_t e = a.tab ? select(std::true_type{}) : select(std::false_type{});
     if (e != hipSuccess) return e;

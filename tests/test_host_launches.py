@@ -105,6 +105,42 @@ def accumulate(n, L, peers=2):
     return ["fftsp_decompress_accumulate", [[1 << 40] * peers, peers, "big", 0.5, "big", n, L, 0.3, 8, "big", "big", None]]
 
 
+def compress(n, L, theta=0.3, bits=8):
+    return ["fftsp_compress", ["big", n, L, theta, bits, "big", "big", "big", "big", None]]
+
+
+def segments(sizes, theta, bits):
+    offs = [0]
+    for s in sizes:
+        offs.append(offs[-1] + s)
+    return [["fftsp_compress_segments", ["big", offs, len(sizes), theta, bits, "big", "big", "big", "big", None]],
+            ["fftsp_decompress_segments", ["big", "big", "big", offs, len(sizes), theta, bits, "big", "big", None]]]
+
+
+def test_lds_limit_of_a_kernel_does_not_depend_on_the_call(runtime, tmp_path):
+    """The limit belongs to the kernel on the device, so two threads' calls must set the same value, one that covers both."""
+    calls = []
+    for theta, bits in ((0.0, 8), (0.3, 8), (1.0, 16), (1.0, 32)):
+        for logL in range(5, 23):
+            L = 1 << logL
+            calls += [compress(3 * L, L, theta, bits), decompress(3 * L, L, theta, bits), accumulate(3 * L, L)]
+            if logL <= 21:
+                calls += [["fftsp_topk_compress", ["big", 3 * L, L, theta, bits, "big", "big", "big", "big", None]],
+                          ["fftsp_topk_decompress", ["big", "big", "big", 3 * L, L, theta, bits, "big", "big", None]]]
+        for top in (50, 4096, 1 << 15, 1 << 17, 1 << 22):
+            calls += segments([top // 2 + 1, top], theta, bits)
+    status, rows = calls_made(runtime, tmp_path, calls)
+    assert status == [0] * len(calls)
+    limits = {}
+    for what, kernel, a, b in rows:
+        if what == "lds":
+            limits.setdefault(kernel, set()).add(a)
+    assert {k: v for k, v in limits.items() if len(v) > 1} == {}
+    for what, kernel, threads, lds in rows:
+        if what == "launch" and lds > 48 * 1024:
+            assert lds <= min(limits[kernel]) <= 160 * 1024, kernel
+
+
 def test_receivers_take_as_many_chunks_as_senders(runtime, tmp_path):
     """Short chunks of long gradients: the verdicts lie beyond 2^32 words of the workspace (16 KiB of histogram a chunk)."""
     n = 62378344
