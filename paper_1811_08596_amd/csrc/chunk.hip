@@ -885,7 +885,7 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
         constexpr int MODE = decltype(mode)::value;
         rank = rank < last_rank ? rank : last_rank;  // a corrupt bitmap must not point outside the record
         if constexpr (MODE == 32) {
-            const uint2 v = *reinterpret_cast<const uint2*>(codes + 8u * rank);
+            const uint2 v = load_code_pair(reinterpret_cast<const uint32_t*>(codes) + 2u * rank);
             return make_float2(__uint_as_float(set ? v.x : 0u), __uint_as_float(set ? v.y : 0u));
         } else {
             uint32_t both;

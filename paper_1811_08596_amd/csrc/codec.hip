@@ -975,7 +975,7 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
             if constexpr (REAL)
                 dst[rk] = code(v, 0, 32);
             else
-                *reinterpret_cast<uint2*>(dst + 2u * rk) = make_uint2(code(v, 0, 32), code(v, 1, 32));
+                store_code_pair(dst + 2u * rk, code(v, 0, 32), code(v, 1, 32));
         });
         return;
     }

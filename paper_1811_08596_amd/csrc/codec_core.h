@@ -175,6 +175,20 @@ __device__ __forceinline__ void search_list(const uint32_t* list, uint32_t count
     need -= above;
 }
 
+// The two 32-bit codes of a kept bin.  They lie behind 16 bytes of header and W bitmap words, and W is odd for most chunk
+// lengths, so words are all the alignment there is.
+__device__ __forceinline__ uint2 load_code_pair(const uint32_t* p)
+{
+    uint2 v;
+    __builtin_memcpy(&v, p, sizeof(v));
+    return v;
+}
+__device__ __forceinline__ void store_code_pair(uint32_t* p, uint32_t re, uint32_t im)
+{
+    const uint2 v = make_uint2(re, im);
+    __builtin_memcpy(p, &v, sizeof(v));
+}
+
 struct HeaderInfo {
     int write;
     uint64_t n;
