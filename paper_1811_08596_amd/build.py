@@ -11,9 +11,10 @@ LIB = os.path.join(HERE, "libfftsp.so")
 SOURCES = ["fft.hip", "chunk.hip", "fused.hip", "codec.hip", "api.hip", "prof.hip"]
 HEADERS = [os.path.join(CSRC, "internal.h"), os.path.join(CSRC, "codec_core.h"), os.path.join(CSRC, "chunk.h"), os.path.join(CSRC, "fft_core.h"), os.path.join(CSRC, "twiddle_table.h"), os.path.join(os.path.dirname(HERE), "include", "fftsp.h")]
 
-# no fast-math: twiddles, keys and the split must round the same way on every launch
+# no fast-math, and no fused multiply-adds but those the sources write out: twiddles, keys and the split must round the same way
+# in every kernel that computes them
 HIPCC_FLAGS = [
-    "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
+    "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-fconstexpr-steps=50000000",
 ]

@@ -21,7 +21,6 @@
 // without a workgroup barrier.
 #include "chunk.h"
 #include "codec_core.h"
-#define FFTSP_FMA_WRITTEN_OUT
 #include "fft_core.h"
 
 #include <type_traits>
@@ -738,11 +737,12 @@ __device__ __forceinline__ void compress_workgroup(const float* __restrict__ in,
     }
 }
 
+// The longest chunks' workgroups have a compute unit to themselves: four waves a SIMD, and told so, or the compiler keeps
+// registers free for a fifth and holds the row masks in spilled scalars (2^15, 10-bit codes: 26 M samples 123 us against 110).
 template <int LOGM, int NT>
-__global__ __launch_bounds__(NT) void k_chunk_compress(const float* __restrict__ in, size_t n, size_t C, int aligned,
-                                                       Tables tb, PackArgs a, uint8_t* __restrict__ stream,
-                                                       uint8_t* __restrict__ records, HeaderInfo hdr,
-                                                       uint32_t* __restrict__ ctl)
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 256, NT == 1024 ? 4 : 8))) void k_chunk_compress(
+    const float* __restrict__ in, size_t n, size_t C, int aligned, Tables tb, PackArgs a, uint8_t* __restrict__ stream,
+    uint8_t* __restrict__ records, HeaderInfo hdr, uint32_t* __restrict__ ctl)
 {
     using G = Geo<LOGM, NT>;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];

@@ -347,13 +347,11 @@ __device__ __forceinline__ void fwd_b_workgroup(uint32_t blk, uint32_t nblk, con
         const int p = tid & (P - 1), kq0 = tid >> LOGP;
         float4 v[PER2];
 #pragma unroll
-        for (int q = 0; q < PER2; ++q) {
-            v[q] = cx_load(r[q]);
-            if constexpr (HALF)  // undo the factor that kept the intermediate inside binary16's range
-                v[q] = make_float4(v[q].x * mid_scale, v[q].y * mid_scale, v[q].z * mid_scale, v[q].w * mid_scale);
-        }
+        for (int q = 0; q < PER2; ++q) v[q] = cx_load(r[q]);
         first_stage_store<LOGT, false>(d, kq0, 2 * p, v);
     };
+    // the factor that kept the stored intermediate inside binary16's range is undone in the split (a power of two: exact)
+    const float unlift = HALF ? mid_scale : 1.f, half = 0.5f * unlift;
     // one key into the 16-bit LDS histogram (bucket b: word b/2, half b%2); on = false adds nothing
     auto count = [&](float2 x, bool on) {
         const uint32_t b = fft_key_of(x) >> kKeyShift;
@@ -398,13 +396,13 @@ __device__ __forceinline__ void fwd_b_workgroup(uint32_t blk, uint32_t nblk, con
             for (int u = 0; u < BATCH; ++u) {
                 const int q = q0 + u, k2 = kq0 + q * DK;
                 const float2 wq = make_float2(kW32re[2 * q * kSplitStep], kW32im[2 * q * kSplitStep]);
-                float2 xa = split_fwd(a0[u], pa[u], cmul(base_a, wq));
-                const float2 xb = split_fwd(a1[u], pb[u], cmul(base_b, wq));
+                float2 xa = split_fwd(a0[u], pa[u], cmul(base_a, wq), half);
+                const float2 xb = split_fwd(a1[u], pb[u], cmul(base_b, wq), half);
                 if (q == 0) {  // k2 = 0 only here: bin 0 and the Nyquist bin come from Z[0] alone
                     const bool dc = self && kq0 == 0;
-                    const typename Cx<HALF>::One xm_st = cx_store<HALF>(make_float2(a0[u].x - a0[u].y, 0.f));
+                    const typename Cx<HALF>::One xm_st = cx_store<HALF>(make_float2((a0[u].x - a0[u].y) * unlift, 0.f));
                     if (dc) {
-                        xa = make_float2(a0[u].x + a0[u].y, 0.f);
+                        xa = make_float2((a0[u].x + a0[u].y) * unlift, 0.f);
                         out[M] = xm_st;
                     }
                     if (CODEC) count(cx_load(xm_st), dc);

@@ -1,5 +1,5 @@
 // Device-side building blocks of the LDS-resident Stockham FFT passes (shared by the per-pass kernels in
-// fft.hip and the fused, cache-resident kernels in fused.hip).  Internal: nothing here is part of the C ABI.
+// fft.hip, the fused, cache-resident kernels in fused.hip and the chunk-resident codec in chunk.hip).  Internal: nothing here is part of the C ABI.
 #pragma once
 #include "internal.h"
 
@@ -8,25 +8,16 @@ namespace {
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-// Where two products meet, one of them ends up inside a fused multiply-add.  Left to the compiler, which one depends on
-// the kernel around it, and kernels that must agree bit for bit would not: chunk.hip, where several kernels compute the
-// same transform, asks for the fused operations to be written out (FFTSP_FMA_WRITTEN_OUT), as they came out in the kernels
-// of these lengths that it replaced.  The two-pass kernels are the only ones of their lengths and keep the compiler's
-// choice.  Either way spectra, and with them what is kept and how it is coded, are bit for bit what they have always been.
-#ifdef FFTSP_FMA_WRITTEN_OUT
+// Several kernels compute the same transform: with small tiles and large ones, for uniform chunks and for tensors, the codec's
+// own and the stage-level ones.  They have to agree bit for bit, so nothing is left to the compiler's choice of what becomes a
+// fused multiply-add (the sources are compiled with -ffp-contract=off): every fused operation is written out.
+// Of two products that meet, the second is rounded before the sum.  In a * b that is the one with the imaginary part of b: most
+// twiddles, and all entries of the fine table, lie nearer the real axis, so it is the smaller one.
 __device__ __forceinline__ float prod_sum(float a, float b, float c, float d) { return __fmaf_rn(a, b, c * d); }
 __device__ __forceinline__ float prod_diff(float a, float b, float c, float d) { return __fmaf_rn(a, b, -(c * d)); }
-#else
-__device__ __forceinline__ float prod_sum(float a, float b, float c, float d) { return a * b + c * d; }
-__device__ __forceinline__ float prod_diff(float a, float b, float c, float d) { return a * b - c * d; }
-#endif
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 {
-#ifdef FFTSP_FMA_WRITTEN_OUT
     return make_float2(prod_diff(a.x, b.x, a.y, b.y), prod_sum(a.y, b.x, a.x, b.y));
-#else
-    return make_float2(prod_diff(a.x, b.x, a.y, b.y), prod_sum(a.x, b.y, a.y, b.x));
-#endif
 }
 // a * conj(b)
 __device__ __forceinline__ float2 cmulc(float2 a, float2 b)
@@ -85,7 +76,6 @@ __device__ __forceinline__ void bf8(float2* v)
     float2 o[4] = {v[1], v[3], v[5], v[7]};
     bf4<INV>(e);
     bf4<INV>(o);
-#ifdef FFTSP_FMA_WRITTEN_OUT
     // v[k], v[k+4] = e[k] +- W8^k o[k]; the odd powers of W8 are (1 -+ i) / sqrt(2) times a real factor
     v[0] = cadd(e[0], o[0]);
     v[4] = csub(e[0], o[0]);
@@ -98,23 +88,6 @@ __device__ __forceinline__ void bf8(float2* v)
     v[5] = make_float2(__fmaf_rn(-c, o1.x, e[1].x), __fmaf_rn(-c, o1.y, e[1].y));
     v[3] = make_float2(__fmaf_rn(c, o3.x, e[3].x), __fmaf_rn(c, o3.y, e[3].y));
     v[7] = make_float2(__fmaf_rn(-c, o3.x, e[3].x), __fmaf_rn(-c, o3.y, e[3].y));
-#else
-    // o[k] *= W8^k
-    float2 o1 = o[1], o3 = o[3];
-    if (INV) {
-        o[1] = make_float2(c * (o1.x - o1.y), c * (o1.x + o1.y));
-        o[3] = make_float2(-c * (o3.x + o3.y), c * (o3.x - o3.y));
-    } else {
-        o[1] = make_float2(c * (o1.x + o1.y), c * (o1.y - o1.x));
-        o[3] = make_float2(c * (o3.y - o3.x), -c * (o3.x + o3.y));
-    }
-    o[2] = rot90<INV>(o[2]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        v[k] = cadd(e[k], o[k]);
-        v[k + 4] = csub(e[k], o[k]);
-    }
-#endif
 }
 
 // 16 points: four radix-4 butterflies over n1 (elements n0, n0+4, n0+8, n0+12), the inner twiddles W16^(n0 k0),
@@ -132,25 +105,14 @@ __device__ __forceinline__ void bf16(float2* v)
         for (int k0 = 0; k0 < 4; ++k0) y[n0][k0] = t[k0];
     }
     // W16^m = (cos(m pi/8), -sin(m pi/8)), conjugated for the inverse
-#ifdef FFTSP_FMA_WRITTEN_OUT
-    auto rot = [&](int n0, int k0, float wr, float wi) __attribute__((always_inline)) {
-        const float x = y[n0][k0].x, z = y[n0][k0].y;
-        if (INV)
-            y[n0][k0] = make_float2(n0 == 1 || (n0 == 3 && k0 == 1) ? prod_sum(x, wr, z, wi) : prod_sum(z, wi, x, wr),
-                                    n0 == 1 && k0 == 2 ? prod_sum(x, -wi, z, wr) : prod_diff(z, wr, x, wi));
-        else if (wi < 0.f && !(n0 == 3 && k0 == 2))
-            y[n0][k0] = make_float2(prod_sum(z, -wi, x, wr), prod_sum(z, wr, x, wi));
-        else
-            y[n0][k0] = make_float2(prod_diff(x, wr, z, wi), prod_sum(x, wi, z, wr));
-    };
-#else
+    // y *= wr + i wi, forward; its conjugate, inverse; where the imaginary part is the larger one, as i y times wi - i wr
     auto rot = [&](int n0, int k0, float wr, float wi) __attribute__((always_inline)) {
         const float2 a = y[n0][k0];
-        y[n0][k0] = INV ? make_float2(prod_sum(a.x, wr, a.y, wi), prod_diff(a.y, wr, a.x, wi))
-                        : make_float2(prod_diff(a.x, wr, a.y, wi), prod_sum(a.y, wr, a.x, wi));
+        if (wr * wr >= wi * wi)
+            y[n0][k0] = INV ? cmulc(a, make_float2(wr, wi)) : cmul(a, make_float2(wr, wi));
+        else
+            y[n0][k0] = INV ? cmulc(make_float2(a.y, -a.x), make_float2(wi, -wr)) : cmul(make_float2(-a.y, a.x), make_float2(wi, -wr));
     };
-#endif
-    // y *= wr + i wi, forward; its conjugate, inverse
     rot(1, 1, c1, -s1);                // W^1
     rot(1, 2, h, -h);                  // W^2
     rot(1, 3, s1, -c1);                // W^3
@@ -300,12 +262,12 @@ __device__ __forceinline__ Span chunk_span(size_t first, size_t count, size_t c,
     return Span{first + c * chunk_len, first + count, aligned8 && !(first & 1u)};
 }
 
-// X[k] from a = Z[k], b = Z[M-k], w = W_L^k   (0 < k < M)
-__device__ __forceinline__ float2 split_fwd(float2 a, float2 b, float2 w)
+// X[k] from a = Z[k], b = Z[M-k], w = W_L^k   (0 < k < M); times 2 half, a power of two
+__device__ __forceinline__ float2 split_fwd(float2 a, float2 b, float2 w, float half = 0.5f)
 {
-    const float er = 0.5f * (a.x + b.x), ei = 0.5f * (a.y - b.y);
-    const float dr = 0.5f * (a.x - b.x), di = 0.5f * (a.y + b.y);
-    return make_float2(er + prod_sum(w.x, di, w.y, dr), ei - prod_diff(w.x, dr, w.y, di));
+    const float dr = half * (a.x - b.x), di = half * (a.y + b.y);
+    return make_float2(__fmaf_rn(half, a.x + b.x, prod_sum(w.x, di, w.y, dr)),
+                       __fmaf_rn(half, a.y - b.y, -prod_diff(w.x, dr, w.y, di)));
 }
 
 // 2 Z[k] from a = X[k], b = X[M-k], w = W_L^k  (the factor 1/2 is folded into the final 1/L)

@@ -194,3 +194,12 @@ def test_product_does_not_import_the_oracle():
             text = open(os.path.join(ROOT, "oracle", f)).read()
             for needle in ("paper_1811_08596_amd", "libfftsp.so", "csrc", "hip_runtime"):
                 assert needle not in text, (f, needle)
+
+
+def test_no_fused_product_is_left_to_the_compiler():
+    """Kernels of one transform agree bit for bit because the sources write every fused multiply-add out."""
+    from paper_1811_08596_amd import build
+    assert "-ffp-contract=off" in build.HIPCC_FLAGS
+    for name in build.SOURCES:
+        text = open(os.path.join(build.CSRC, name)).read()
+        assert "fp contract" not in text and "fp-contract" not in text, name
