@@ -30,19 +30,24 @@ namespace {
 
 // Complex points of a tile (a power of two; 16 per lane).  A tile of 2^13 is 64 KiB of LDS, two workgroups of 512 lanes per
 // compute unit.  A tile of 2^14 has a workgroup of 1024 lanes and the compute unit to itself; it is taken where the smaller
-// one would touch memory in pieces of less than a 128-byte line:
-//   second pass, rows of 2^10 (64 -> 128 bytes): 138 M samples in chunks of 2^22, forward 313 -> 230 us, inverse 348 -> 268
-//     (with rows of 2^9, already a line wide: 101 -> 106 and 109 -> 127);
-//   inverse first pass, columns of 2^10 (stores of 64 -> 128 bytes): 62 M samples in chunks of 2^20, 116 -> 101 us, and
-//     the next call's forward first pass, which runs while those lines are written back, 135 -> 119; columns of 2^11
-//     (32 -> 64 bytes): 468 -> 300 us.
-// The forward first pass, which only reads in narrow pieces, was slower that way (columns of 2^10: 119 -> 124 us; of 2^11:
-// 340 us against 327 with four 2^13-point tiles of a line walked in step).
-// And only where there is such a tile for every compute unit: one to four chunks of 2^20 are 3 % faster in more, smaller tiles.
+// one would touch memory in pieces of less than a 128-byte line, and there are enough of them.  Whole calls in us, small / large
+// tiles in the pass, by number of the latter; nothing of a call in the caches when it starts (with everything there the lines of
+// the inverse passes lie higher):
+//   forward second pass, rows of 2^10 (64 -> 128 bytes), sender: 64 58.4 / 57.4, 128 67.0 / 66.1, 256 84.5 / 81.6, 1024 219 / 200,
+//     4224 (138 M samples in chunks of 2^22) 913 / 810;
+//   inverse second pass, the same rows, receiver: 384 80 / 84, 640 115 / 122, 1024 171 / 169 and (chunks of 2^22) 186 / 190, 1280
+//     222 / 202, 4224 780 / 694; four senders' streams 1216 242 / 221;
+//   inverse first pass, columns of 2^10 (stores of 64 -> 128 bytes), receiver: 256 51.9 / 53.2, 640 99 / 101, 768 129 / 118, 1920
+//     (62 M samples in chunks of 2^20) 310 / 280, and the next call's forward first pass, which runs while those lines are
+//     written back, 134 / 118; columns of 2^11 (32 -> 64 bytes): 128 52.1 / 52.7, 256 68.4 / 67.5, 768 157 / 146, 4224 926 / 780.
+// With rows of 2^9, already a line wide, the second passes lose (101 / 106 and 109 / 127 us).  The forward first pass, which only
+// reads in narrow pieces, was slower that way (columns of 2^10: 119 / 124 us; of 2^11: 340 us against 327 with four
+// 2^13-point tiles of a line walked in step).  Binary16 storage: the same lines within 3 us.
 constexpr int kTileFA = 13;
 constexpr int kWideMin = 10;  // columns (inverse first pass) or rows (second passes) of at least 2^kWideMin
-constexpr size_t kWideTiles = 256;
-inline bool wide_tiles(size_t C, int logM) { return (C << (logM - 14)) >= kWideTiles; }
+constexpr size_t kWideForward = 128, kWideInverseB = 1152;  // large tiles from which a pass takes them
+constexpr size_t wide_inverse_a(int logn1) { return logn1 == 10 ? 768 : 256; }
+inline size_t wide_tiles(size_t C, int logM) { return C << (logM - 14); }
 constexpr int tile_lanes(int loge) { return 1 << (loge - 4); }
 constexpr int kLanePairs = 8;  // pairs of adjacent points a lane holds
 // a pass A tile is 2^(loge - LOGN1) columns of 8 bytes; the tiles of a 128-byte line (two at least) are walked in step
@@ -908,7 +913,7 @@ hipError_t fwd_b(const float2* mid, int logM, size_t C, float2* spec, uint32_t s
                  float mid_scale, hipStream_t s, const uint32_t* only_if = nullptr)
 {
     if constexpr (LOGN2 >= kWideMin)
-        if (wide_tiles(C, logM)) return fwd_b_tiled<LOGN2, 14, CODEC, HALF>(mid, logM, C, spec, sstride, t, hist, mid_scale, s, only_if);
+        if (wide_tiles(C, logM) >= kWideForward) return fwd_b_tiled<LOGN2, 14, CODEC, HALF>(mid, logM, C, spec, sstride, t, hist, mid_scale, s, only_if);
     return fwd_b_tiled<LOGN2, 13, CODEC, HALF>(mid, logM, C, spec, sstride, t, hist, mid_scale, s, only_if);
 }
 template <int LOGN2, bool PAIR, bool HALF>
@@ -916,7 +921,7 @@ hipError_t inv_b(const float2* spec, uint32_t sstride, int logM, size_t C, float
                  hipStream_t s, const uint32_t* only_if = nullptr)
 {
     if constexpr (LOGN2 >= kWideMin)
-        if (wide_tiles(C, logM)) return inv_b_tiled<LOGN2, 14, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
+        if (wide_tiles(C, logM) >= kWideInverseB) return inv_b_tiled<LOGN2, 14, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
     return inv_b_tiled<LOGN2, 13, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
 }
 template <int LOGN1, bool HALF>
@@ -924,23 +929,30 @@ hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Ta
                  hipStream_t s, const uint32_t* only_if = nullptr)
 {
     if constexpr (LOGN1 >= kWideMin)
-        if (wide_tiles(C, logM)) return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+        if (wide_tiles(C, logM) >= wide_inverse_a(LOGN1)) return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
     return inv_a_tiled<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
 }
 
-// Launches of the tensors i in [first, count) of a batch.  The tensors come shortest first, so those whose rows or columns
-// ask for the larger tile are the last ones; the rule for taking it is the one of the uniform calls.  They are then a launch
-// of their own, with two tails instead of one.  On ResNet-50's tensors (half of the samples in rows, four fifths in columns of
-// 2^10 and more) that pays in the forward second pass (92 -> 87 us) and the inverse first one (80 -> 70), not in the inverse
-// second one (72 -> 84), which takes it only when most of the samples ask for it.
+// The tensors come shortest first, so those whose rows or columns ask for the larger tile are the last ones.  Beside shorter
+// tensors they are a launch of their own, with two tails instead of one, 8 to 15 us, so the lines lie higher than in uniform
+// calls.  Senders and receivers in us, small / large tiles, of sixty batches of 12 to 200 tensors of 10 to 2.4 M samples, not in
+// the caches, by number of large tiles (of what the launch would hold):
+//   forward second pass: 64 104 / 113, 192 158 / 162, 384 194 / 205, 448 236 / 243, 512 (of 778) 223 / 215, (of 900) 235 / 235,
+//     (of 1044, ResNet-50) 261 / 254, 640 236 / 243, 704 265 / 263 and 283 / 287, 768 313 / 317, 896 334 / 333, 1024 351 / 334,
+//     1280 445 / 428, 1536 438 / 411;
+//   inverse second pass: loses up to 1472 (of 2324) 458 / 476, 512 (of 1044) 206 / 210; 1536 (of 2048) 366 / 346;
+//   inverse first pass, by what the launch holds: 192 76 / 84, 498 130 / 145, 776 176 / 183, 892 195 / 200 and 197 / 196, 902 199 /
+//     205, 946 213 / 207 and 208 / 200, 1002 224 / 213, 1044 225 / 206, 1360 309 / 283, 2324 499 / 458.
+constexpr size_t kWideForwardBeside = 512, kWideInverseBBeside = 1536, kWideInverseALaunch = 940;
+// The first of them, or count; alone, beside: large tiles that are enough.  all: counted over the whole launch.
 template <typename Logs>
-uint32_t first_wide(const LongBatch& b, Logs&& logs, bool most)
+uint32_t first_wide(const LongBatch& b, Logs&& logs, size_t alone, size_t beside, bool all)
 {
     uint32_t i = b.count;
     size_t tiles = 0;
     for (; i > 0 && logs(b.tab.t[i - 1].logM) >= kWideMin; --i) tiles += (size_t)1 << (b.tab.t[i - 1].logM - 14);
-    const bool enough = tiles >= kWideTiles && (!most || 8 * tiles >= 7 * ((size_t)b.units << (kLongUnitLog - 14)));
-    return enough ? i : b.count;
+    if (all) tiles = (size_t)b.units << (kLongUnitLog - 14);
+    return tiles >= (i == 0 ? alone : beside) ? i : b.count;
 }
 // starts of the workgroups' shares; wgs(tensor) workgroups each.  Returns the total.
 template <typename Wgs>
@@ -964,11 +976,10 @@ uint32_t long_run(const LongBatch& b, uint32_t first, uint32_t end, int loge, ui
     while (tiles / (2 * run) >= most) run *= 2;
     return run;
 }
-// pass(tile size, first tensor, end): those with small tiles, then the others
-template <typename Logs, typename Pass>
-hipError_t by_tile_size(const LongBatch& b, Logs&& logs, bool most, Pass&& pass)
+// pass(tile size, first tensor, end): those with small tiles, then the ones from `wide` on
+template <typename Pass>
+hipError_t by_tile_size(const LongBatch& b, uint32_t wide, Pass&& pass)
 {
-    const uint32_t wide = first_wide(b, logs, most);
     hipError_t e = hipSuccess;
     if (wide > 0) e = pass(std::integral_constant<int, 13>{}, 0u, wide);
     if (e == hipSuccess && wide < b.count) e = pass(std::integral_constant<int, 14>{}, wide, b.count);
@@ -1091,7 +1102,8 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     const uint32_t wgs = long_starts(b, 0, b.count, &at, [&](const LongTensor& x) { return pass_a_wgs(x, kTileFA, run); });
     FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long, dim3(wgs), dim3(tile_lanes(kTileFA)), long_lds(kTileFA), s, in, mid, t, aligned, run,
                  zero_ptr, (uint32_t)zero_words, b.tab, at);
-    return by_tile_size(b, log_rows, false, [&](auto size, uint32_t first, uint32_t end) {
+    const uint32_t wide = first_wide(b, log_rows, kWideForward, kWideForwardBeside, false);
+    return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
         constexpr int LOGE = decltype(size)::value;
         const size_t lds = long_lds(LOGE) + kHistLdsWords * sizeof(uint32_t);
         const hipError_t err = set_lds(k_fwd_b_long<LOGE>, lds);
@@ -1112,7 +1124,8 @@ hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out,
     const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     LongStarts at;
-    const hipError_t e = by_tile_size(b, log_rows, true, [&](auto size, uint32_t first, uint32_t end) {
+    uint32_t wide = first_wide(b, log_rows, kWideInverseB, kWideInverseBBeside, false);
+    const hipError_t e = by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
         constexpr int LOGE = decltype(size)::value;
         const hipError_t err = set_lds(k_inv_b_long<LOGE>, long_lds(LOGE));
         if (err != hipSuccess) return err;
@@ -1125,7 +1138,8 @@ hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out,
         return hipGetLastError();
     });
     if (e != hipSuccess) return e;
-    return by_tile_size(b, log_columns, false, [&](auto size, uint32_t first, uint32_t end) {
+    wide = first_wide(b, log_columns, kWideInverseALaunch, kWideInverseALaunch, true);
+    return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
         constexpr int LOGE = decltype(size)::value;
         const hipError_t err = set_lds(k_inv_a_long<LOGE>, long_lds(LOGE));
         if (err != hipSuccess) return err;

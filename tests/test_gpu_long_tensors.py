@@ -13,6 +13,8 @@ SETS = {
     "more_than_a_table": [40000 + 361 * i for i in range(70)] + [65536, 40001, 9],
     "every_length": [50000, 1 << 16, 100004, 1 << 17, 200001, 1 << 18, 300000, 1 << 19, 700004, (1 << 20) - 3, 1 << 20, 1400000,
                      1 << 21, 3000000, 1 << 22, 12, 4096, 33],
+    "large_tiles": [(1 << 22) - 5 * i for i in range(13)] + [70000, 1 << 18, 12345],
+    "large_tiles_alone": [1 << 22, 3000004, (1 << 21) + 8],
     "large_and_short": [3000004, 2500000, 1 << 22, 3500000, 65540, 30000, 100, 7],
 }
 

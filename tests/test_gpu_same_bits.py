@@ -12,7 +12,7 @@ def dev():
     return Device()
 
 
-@pytest.mark.parametrize("logL,chunks", [(16, 40), (17, 40), (18, 24), (19, 24), (20, 9), (20, 60), (21, 5), (22, 3)])
+@pytest.mark.parametrize("logL,chunks", [(16, 40), (17, 40), (18, 24), (19, 24), (20, 9), (20, 60), (21, 5), (21, 20), (22, 3), (22, 11)])
 def test_a_chunk_alone_and_among_others(dev, logL, chunks):
     f, torch, L, theta, bits = dev.f, dev.torch, 1 << logL, 0.4, 12
     gen = torch.Generator(device="cuda").manual_seed(logL)
