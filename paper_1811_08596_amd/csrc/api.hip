@@ -233,7 +233,7 @@ int apply_quantizer(Plan* p, const fftsp_quantizer* q, uint32_t* static_vmax)
 hipError_t decode_stream(const Plan& p, const uint8_t* in, const CodecArgs& a, float* units, uint8_t* ws, hipStream_t s)
 {
     if (p.C > 0xffffffffu) return hipErrorInvalidValue;
-    const StatusNote note{(uint32_t)p.C, p.ws.tscan};
+    const StatusNote note = status_note(p.C, p.ws.tscan);
     return launch_decode(in, in + kStreamHeader, a, units, ws, p.ws, 1, reinterpret_cast<uint32_t*>(ws + p.ws.tscan), &note, s);
 }
 
@@ -243,7 +243,7 @@ hipError_t decompress_chunks(const Plan& p, const PeerList& streams, int npeers,
 {
     const size_t count = p.C * (size_t)npeers;
     if (count > 0xffffffffu) return hipErrorInvalidValue;
-    const StatusNote note{(uint32_t)count, verd};
+    const StatusNote note = status_note(count, verd);
     return launch_chunk_decompress(streams, npeers, plain, p.logL, a, out, p.n, gain, reinterpret_cast<uint32_t*>(ws + p.ws.status),
                                    note, reinterpret_cast<uint32_t*>(ws + verd), t, s);
 }
@@ -1046,7 +1046,7 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
     const SegmentPlan plan = plan_segments(seg_offsets, nseg, theta, bits, true);
     const size_t verd = segment_verdicts(plan);
     uint32_t* verdicts = reinterpret_cast<uint32_t*>(ws + verd);
-    const StatusNote note{(uint32_t)nseg, verd};
+    const StatusNote note = status_note((size_t)nseg, verd);
     const hipError_t e = run_segments(
         plan, s,
         [&](hipStream_t st) {
@@ -1086,10 +1086,10 @@ int fftsp_device_status(const void* d_workspace, int* status_out)
     uint32_t v[kNoteWord + kNoteWords] = {};
     if (hipMemcpy(v, d_workspace, sizeof(v), hipMemcpyDeviceToHost) != hipSuccess) return FFTSP_EHIP;
     uint32_t worst = v[0];
-    const StatusNote note{v[2], v[3] | (uint64_t)v[5] << 32};
-    if (v[4] == kStatusNoteMagic && note.count > 0) {  // one verdict per record
-        std::vector<uint32_t> verdicts(note.count);
-        if (hipMemcpy(verdicts.data(), static_cast<const uint8_t*>(d_workspace) + note.offset, verdicts.size() * 4,
+    if (v[4] == kStatusNoteMagic && v[2] > 0) {  // one verdict per record
+        std::vector<uint32_t> verdicts(v[2]);
+        const uint64_t offset = v[3] | (uint64_t)v[5] << 32;
+        if (hipMemcpy(verdicts.data(), static_cast<const uint8_t*>(d_workspace) + offset, verdicts.size() * 4,
                       hipMemcpyDeviceToHost) != hipSuccess)
             return FFTSP_EHIP;
         worst = std::max(worst, *std::max_element(verdicts.begin(), verdicts.end()));

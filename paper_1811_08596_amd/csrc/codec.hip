@@ -1676,7 +1676,7 @@ hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecA
     if (a.C * (size_t)u.Tn > 0x7fffffffu || count > 0x7fffffffu) return hipErrorInvalidValue;
     HeaderInfo h{1, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
     FFTSP_LAUNCH("group_prefix", k_group_prefix_peers, dim3((unsigned)count), dim3(RT), 0, s, streams, (uint32_t)a.C, a.S, u.W,
-                 a.k, h, gprefix, verdicts, ctl, StatusNote{(uint32_t)count, pw.verd});
+                 a.k, h, gprefix, verdicts, ctl, status_note(count, pw.verd));
     PeerList recs{};
     for (int i = 0; i < npeers; ++i) recs.p[i] = streams.p[i] + 64;  // records follow the 64-byte stream header
     const bool vec = a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0;

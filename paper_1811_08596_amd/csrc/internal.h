@@ -103,9 +103,12 @@ static inline bool fused_shape(int logL, size_t C)
 // beyond 16 GiB), and a magic word.  So no earlier kernel has to clear a status word before a record raises it.
 // fftsp_device_status looks at both.
 struct StatusNote {
-    uint32_t count;
-    uint64_t offset;
+    uint32_t count, low, high;  // low, high: the offset's halves
 };
+inline StatusNote status_note(size_t count, size_t offset)
+{
+    return StatusNote{(uint32_t)count, (uint32_t)offset, (uint32_t)((uint64_t)offset >> 32)};
+}
 constexpr uint32_t kStatusNoteMagic = 0x46535653u;
 constexpr int kNoteWord = 2, kNoteWords = 4;  // of the control block
 // word i of it, for these four
@@ -113,9 +116,9 @@ __host__ __device__ inline uint32_t note_word(const StatusNote& n, int i)
 {
     switch (i - kNoteWord) {
         case 0: return n.count;
-        case 1: return (uint32_t)n.offset;
+        case 1: return n.low;
         case 2: return n.count ? kStatusNoteMagic : 0u;
-        default: return (uint32_t)(n.offset >> 32);
+        default: return n.high;
     }
 }
 
