@@ -938,8 +938,12 @@ static hipError_t run_beside(hipStream_t user, S&& side, M&& main)
 }
 
 // Beside each other only where the longer tensors take a while: the event calls cost the host 46 us a call (sender and
-// receiver 92), which a short chain of kernels does not hide.  ResNet-50 (34 M padded samples in longer tensors): 512 -> 471
-// us; ResNet-20 (0.2 M): 111 -> 133.  Per-kernel timing wants one chain.
+// receiver 92), which a short chain of kernels does not hide.  Sender and receiver in us, beside / serial, by padded samples in
+// longer tensors, with 10 and 100 short ones; calls behind each other, and a call that is waited for:
+//   2^17 132 / 94 and 145 / 111;  2^21 135 / 119 and 158 / 133;  2^22 143 / 140 and 165 / 157, waited for 167 / 160 and 183 / 190;
+//   2^23 180 / 192 and 182 / 208, waited for 226 / 215 and 238 / 244;  2^24 278 / 290 and 280 / 301, waited for 307 / 310 and
+//   326 / 333;  2^26 1010 / 1028 and 1014 / 1039, waited for 1054 / 1056 and 1074 / 1081.
+// From 2^24 on both gain.  Per-kernel timing wants one chain.
 constexpr uint32_t kSideUnits = 1u << (23 - kLongUnitLog);
 template <typename S, typename M>
 static hipError_t run_segments(const SegmentPlan& plan, hipStream_t user, S&& side, M&& main)

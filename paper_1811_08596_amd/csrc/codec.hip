@@ -436,8 +436,9 @@ constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1
 // k_count_digit counts the candidates' second digit into the first kHist2Bins words of the chunk's tscan, which k_collect
 // has cleared.  k_mark adds the candidates above the two digits' common prefix to their tiles' counts and maxima and moves
 // the ones that share it to the front of their tile's list, unless they are more than k_resolve lists.
-// Measured, a call of sender and receiver: a batch whose longest tensor has 2^22 samples 460 -> 452 us, thirty-three chunks
-// of 2^22 1550 -> 1537 us; sixty Top-k chunks of 512 tiles, the fewest there can be, break even with one workgroup (265 us).
+// Senders in us, without / with: one chunk of 2^21 61.6 / 58.0, thirty-two 348 / 347; one of 2^22 90 / 70, thirty-three 801 / 785;
+// Top-k chunks of 2^20 (512 tiles, the fewest there can be) one 40.3 / 37.3, eight 59.5 / 56.1, thirty-two 115 / 113, sixty
+// 181 / 182, a hundred and twenty 378 / 383, where there is a k_resolve workgroup for every other compute unit anyway.
 constexpr uint32_t kPartTiles = 64, kPartWave = kPartTiles / (NT / 64);
 inline uint32_t parts_of(uint32_t tiles) { return (tiles + kPartTiles - 1u) / kPartTiles; }
 static_assert(2 * kKeptTiles < (uint32_t)kHist2Bins && 2 * 512 >= kHist2Bins, "longer chunks have 512 tiles at least");
