@@ -755,12 +755,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 256, NT
     compress_workgroup<LOGM, NT>(in, where, tb, a, records, lds, tid);
 }
 
-// lanes a tensor of 2^(LOGM+1) samples gets in a per-tensor launch
-template <int LOGM>
-constexpr int tensor_threads()
-{
-    return uniform_threads<LOGM>();
-}
 template <typename G>
 __device__ __forceinline__ ListedChunk listed(const TensorTable& t, const TensorPiece& piece, int aligned, int tid)
 {
@@ -771,7 +765,7 @@ __device__ __forceinline__ void compress_tensors(const float* __restrict__ in, c
                                                  int aligned, const Tables& tb, const PackArgs& a,
                                                  uint8_t* __restrict__ records, uint8_t* lds, int tid)
 {
-    constexpr int NT = tensor_threads<LOGM>();
+    constexpr int NT = uniform_threads<LOGM>();
     if (tid >= NT) return;
     compress_workgroup<LOGM, NT>(in, listed<Geo<LOGM, NT>>(t, piece, aligned, tid), tb, a, records, lds, tid);
 }
@@ -780,7 +774,7 @@ __device__ __forceinline__ void compress_tensors(const float* __restrict__ in, c
 // tensors of piece i.  Waves its length has no use for leave at once (an ended wave takes part in no barrier).
 // TOP: the longest a launch may hold, 2^(TOP+1) samples.
 template <int TOP>
-__global__ __launch_bounds__(tensor_threads<TOP>()) void k_tensors_compress(const float* __restrict__ in, int aligned, Tables tb,
+__global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_compress(const float* __restrict__ in, int aligned, Tables tb,
                                                                             QuantizerArgs q, uint8_t* __restrict__ stream,
                                                                             uint8_t* __restrict__ records, HeaderInfo hdr,
                                                                             uint32_t* __restrict__ ctl, TensorTable t)
@@ -1064,7 +1058,7 @@ __device__ __forceinline__ void decompress_tensors(const PeerList& streams, cons
                                                    int aligned, const Tables& tb, const PackArgs& a, const HeaderInfo& hdr,
                                                    float* __restrict__ out, uint32_t* __restrict__ verdicts, uint8_t* lds, int tid)
 {
-    constexpr int NT = tensor_threads<LOGM>();
+    constexpr int NT = uniform_threads<LOGM>();
     using G = Geo<LOGM, NT>;
     if (tid >= NT) return;
     decompress_workgroup<LOGM, NT>(streams, 1u, 1, listed<G>(t, piece, aligned, tid), tb, a, hdr, out, 1.0f,
@@ -1072,7 +1066,7 @@ __device__ __forceinline__ void decompress_tensors(const PeerList& streams, cons
 }
 
 template <int TOP>
-__global__ __launch_bounds__(tensor_threads<TOP>()) void k_tensors_decompress(PeerList streams, Tables tb, QuantizerArgs q,
+__global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_decompress(PeerList streams, Tables tb, QuantizerArgs q,
                                                                               HeaderInfo hdr, float* __restrict__ out, int aligned,
                                                                               uint32_t* __restrict__ ctl, StatusNote note,
                                                                               int clear, uint32_t* __restrict__ verdicts,
@@ -1207,7 +1201,7 @@ constexpr size_t most_receiver_lds(size_t records)
 template <int LOGM>
 constexpr size_t most_tensors_lds(bool sender)
 {
-    constexpr int NT = tensor_threads<LOGM>();
+    constexpr int NT = uniform_threads<LOGM>();
     const size_t own = sender ? sender_lds<LOGM, NT>() : most_receiver_lds<LOGM, NT>(1);
     if constexpr (LOGM > 4) {
         const size_t shorter = most_tensors_lds<LOGM - 1>(sender);
@@ -1341,7 +1335,7 @@ int tensors_per_workgroup(int logL)
 {
     switch (logL - 1) {
 #define X(p) \
-    case p: return Geo<p, tensor_threads<p>()>::GROUPS;
+    case p: return Geo<p, uniform_threads<p>()>::GROUPS;
         FFTSP_CHUNK_SIZES(X)
 #undef X
         default: return 1;
@@ -1357,8 +1351,8 @@ static size_t tensors_lds(const TensorTable& t, uint32_t pieces, bool sender)
         switch (t.piece[i].logm) {
 #define X(p)                                                                                                                 \
     case p:                                                                                                                  \
-        need = sender ? sender_lds<p, tensor_threads<p>()>()                                                                 \
-                      : receiver_lds<p, tensor_threads<p>()>(tensor_region(t.stride[p - 4], Geo<p, tensor_threads<p>()>::DATA)); \
+        need = sender ? sender_lds<p, uniform_threads<p>()>()                                                                 \
+                      : receiver_lds<p, uniform_threads<p>()>(tensor_region(t.stride[p - 4], Geo<p, uniform_threads<p>()>::DATA)); \
         break;
             FFTSP_CHUNK_SIZES(X)
 #undef X
@@ -1379,10 +1373,10 @@ hipError_t launch_tensors_compress(const float* in, const TensorTable& t, uint32
                              : allow_lds(k_tensors_compress<14>, most_tensors_lds<14>(true));
     if (e != hipSuccess) return e;
     if (low)
-        FFTSP_LAUNCH("tensors_compress", k_tensors_compress<11>, dim3(pieces), dim3(tensor_threads<11>()), lds, s, in,
+        FFTSP_LAUNCH("tensors_compress", k_tensors_compress<11>, dim3(pieces), dim3(uniform_threads<11>()), lds, s, in,
                      alignment(in), tb, q, stream, records, header_info(hdr, hdr.write_header), ctl, t);
     else
-        FFTSP_LAUNCH("tensors_compress", k_tensors_compress<14>, dim3(pieces), dim3(tensor_threads<14>()), lds, s, in,
+        FFTSP_LAUNCH("tensors_compress", k_tensors_compress<14>, dim3(pieces), dim3(uniform_threads<14>()), lds, s, in,
                      alignment(in), tb, q, stream, records, header_info(hdr, hdr.write_header), ctl, t);
     return hipGetLastError();
 }
@@ -1399,10 +1393,10 @@ hipError_t launch_tensors_decompress(const uint8_t* stream, const TensorTable& t
     PeerList one{};
     one.p[0] = stream;
     if (low)
-        FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<11>, dim3(pieces), dim3(tensor_threads<11>()), lds, s, one, tb, q,
+        FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<11>, dim3(pieces), dim3(uniform_threads<11>()), lds, s, one, tb, q,
                      header_info(hdr, hdr.write_header), out, alignment(out), ctl, note, clear, verdicts, t);
     else
-        FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<14>, dim3(pieces), dim3(tensor_threads<14>()), lds, s, one, tb, q,
+        FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<14>, dim3(pieces), dim3(uniform_threads<14>()), lds, s, one, tb, q,
                      header_info(hdr, hdr.write_header), out, alignment(out), ctl, note, clear, verdicts, t);
     return hipGetLastError();
 }

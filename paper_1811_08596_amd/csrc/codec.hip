@@ -1448,18 +1448,13 @@ __global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npe
 }  // namespace
 
 // control block and histograms are adjacent: one fill
-static hipError_t launch_zero_hist(uint8_t* ws_base, const Workspace& w, size_t C, hipStream_t s)
+hipError_t launch_zero_control(uint8_t* ws_base, const Workspace& w, size_t C, hipStream_t s)
 {
     uint32_t* status = reinterpret_cast<uint32_t*>(ws_base + w.status);
     const size_t zero_words = (w.hist - w.status) / 4 + C * kHistBins;
     FFTSP_LAUNCH("zero_fill", k_zero_u32, dim3((unsigned)((zero_words + 255) / 256)), dim3(256), 0, s, status,
                  zero_words);
     return hipGetLastError();
-}
-
-hipError_t launch_zero_control(uint8_t* ws_base, const Workspace& w, size_t C, hipStream_t s)
-{
-    return launch_zero_hist(ws_base, w, C, s);
 }
 
 static Shape shape_of(const CodecArgs& a)
@@ -1512,7 +1507,7 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
     if (a.tab && !hist_ready) return hipErrorInvalidValue;
 
     if (!hist_ready) {
-        hipError_t e = launch_zero_hist(ws_base, w, a.C, s);
+        hipError_t e = launch_zero_control(ws_base, w, a.C, s);
         if (e != hipSuccess) return e;
         const uint32_t groups = (u.Tn + HIST_TILES - 1) / HIST_TILES;
         const uint32_t sgroups = (u.Tn + kHistSampleTiles - 1) / kHistSampleTiles;
