@@ -304,9 +304,10 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
     if (threadIdx.x == 0) *reinterpret_cast<uint2*>(sel + c * 8) = make_uint2(b.star, b.need);
 }
 
-// Tiles of a chunk whose candidates k_resolve keeps in LDS: 135 KiB beside its other 20.  Longer chunks go through
-// k_count_digit and k_mark before it.
+// Tiles of a chunk whose candidates k_resolve keeps in registers.  Longer chunks go through k_count_digit and k_mark before it.
 constexpr uint32_t kKeptTiles = 270;
+// Tiles of a chunk up to which k_emit may do k_resolve's work.
+constexpr uint32_t kMergedTiles = 72;
 
 // --------------------------------------------------------------- collect ----
 // Per tile: count and range of the bins kept outright, and the candidates in bin order.
@@ -319,11 +320,12 @@ constexpr uint32_t kKeptTiles = 270;
 // so that k_resolve can take it as one.
 // FIND: every workgroup finds the threshold's bucket itself, from hist, instead of a launch before this one.  That is 16 KB more to
 // read per tile, from cache, so it is done where the launch weighs more: see find_in_collect.
+// clear (FIND only): the records, whose code words this kernel then clears, for a k_emit that finds the threshold itself.
 template <bool FIND, bool TABLE, bool REAL, bool HALF>
 __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u,
                                                 const uint32_t* __restrict__ hist, uint32_t* __restrict__ sel,
                                                 uint32_t* __restrict__ tinfo, uint32_t* __restrict__ tscan,
-                                                uint2* __restrict__ cand, TableArg<TABLE> tab, size_t n)
+                                                uint2* __restrict__ cand, uint8_t* __restrict__ clear, TableArg<TABLE> tab, size_t n)
 {
     using E = typename Elem<REAL>::T;
     __shared__ uint32_t wcnt[4], wdef[4], wvmax[4];
@@ -347,6 +349,12 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
         load_units(stage, row0, count, lane, pair_log, z);
     }
     if constexpr (FIND) {
+        if (clear) {  // the tile's share of the record behind the bitmap
+            uint32_t* codes = reinterpret_cast<uint32_t*>(clear + at.record) + 4 + at.W;
+            const uint32_t words = (uint32_t)(at.S / 4) - 4u - at.W, share = (words + at.Tn - 1u) / at.Tn;
+            const uint32_t from = at.tile * share, to = from + share < words ? from + share : words;
+            for (uint32_t i = from + (uint32_t)tid; i < to; i += NT) codes[i] = 0u;
+        }
         const Bucket b = find_bucket(hist + (size_t)at.chunk * kHistBins, at.k);
         bstar = b.star;
         if (at.tile == 0 && tid == 0) *reinterpret_cast<uint2*>(sel + (size_t)at.chunk * 8) = make_uint2(b.star, b.need);
@@ -583,139 +591,224 @@ __global__ __launch_bounds__(NT) void k_mark(Shape u, const uint32_t* __restrict
 // One workgroup per chunk: finish the radix select on the candidates, break ties by bin order, scan the tiles, find the
 // survivors' largest component, write the record header and zero the code words that two tiles will share.
 //
-// Bound by what one compute unit can issue and by memory round trips, so the candidates are looked at twice only.  The first
-// sweep (a wave per tile, kFetch tiles in flight, a lane per candidate: a tile has about 40) counts their second digit.
-// The second one counts per tile those above the two digits' common prefix, takes their range and lists the few that
-// share it (ten or so of a million bins).  The list settles the threshold, and its members are added to their tiles
-// afterwards.  More than kListCap of them (runs of equal keys) take a third digit and a third sweep.
+// Bound by latency: of memory once, then of LDS and of the barriers, since a wave has a few instructions for each of its
+// tiles.  So the candidates and the tiles' summaries are asked for together, before anything else, and stay in registers: a wave
+// holds its tiles' first rows of 64 candidates (a tile has about 40) and its lanes their summaries.  The first sweep counts the
+// candidates' second digit.  The second one counts per tile those above the two digits' common prefix, takes their range and
+// lists the few that share it (ten or so of a million bins).  The list settles the threshold, and its members are added to
+// their tiles afterwards.  More than kListCap of them (runs of equal keys) take a third digit and a third sweep.  Scans
+// over counters and tiles are short, so every wave does them for itself instead of waiting at a barrier.  What happens rarely
+// (more than 64 candidates in a tile, more than two listed by one lane) is kept out of the sweeps' straight code: jumping over it
+// there cost a fetch from memory per tile, about 550 cycles.
+// Measured, us per launch, against sweeps over LDS: one chunk of 2^16 6.2 -> 5.0, four of 2^18 9.3 -> 6.1, eight of 2^19 13.3 -> 7.2, four
+// of 2^20 14.8 -> 11.4, sixty 18.3 -> 14.1.
 // A tile whose candidates are all the same value is one candidate of its weight: 10^6 samples in chunks of 2^18, the last
 // one nearly empty, Top-k sender and receiver 661 -> 72 us.
-// KEPT: the first sweep leaves the candidates in LDS, in slots of 64 per tile, for the second one.
 // Counting the second digit in k_collect instead saved a sweep here but cost that kernel more (43 -> 52 us: its atomics
 // meet in memory).
-// Measured, us per call, against three digits and three more sweeps by 16 waves: one chunk of 2^16 16 -> 9, sixty of
-// 2^20 24 -> 18, thirty-three of 2^22 87 -> 44.
-constexpr int kFetch = 8;  // tiles of a wave fetched in one round trip
-constexpr uint32_t kAlike = 0x80000000u;  // mark of a tile whose candidates are all the same
-template <bool TABLE, int NW, bool KEPT>
-__global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, uint32_t static_vmax, uint32_t codes_per_bin,
-                                                     uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
-                                                     uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
-                                                     uint8_t* __restrict__ records, uint8_t* __restrict__ stream,
-                                                     HeaderInfo hdr, TableArg<TABLE> tab)
+//
+// MERGED: every workgroup of k_emit does this for its own tile, which saves the launch; see resolve_in_emit.  The code words are
+// clear already, and the tile of number 0 writes the headers.
+constexpr int kFetch = 9;  // tiles of a wave asked for at once; it holds twice as many
+template <int NW>
+constexpr uint32_t kHeldTiles = 2 * kFetch * NW;
+static_assert(kHeldTiles<16> >= kKeptTiles && kHeldTiles<NT / 64> >= kMergedTiles, "the candidates stay in registers");
+template <int MOST>
+struct ResolveScratch {
+    uint32_t h[kHist2Bins], list[kListCap], list_at[kListCap], list_vb[kListCap];
+    uint32_t tgt[MOST], teq[MOST], take[MOST];
+    uint32_t listed, vmax;
+};
+struct ResolveArgs {
+    int bits, m;
+    uint32_t static_vmax, codes_per_bin;
+};
+struct Threshold {
+    uint32_t tau, quota, pbase;  // quota: bins equal to tau that are kept, or ~0: all of them
+    uint32_t rank0, eq0;         // MERGED: survivors, and bins equal to tau, before the tile
+};
+// A digit's counters, so that the sixteen a lane scans are read without bank conflicts.
+__device__ __forceinline__ uint32_t digit_place(uint32_t d) { return ((d & 15u) << 6) | (d >> 4); }
+static_assert(kHist2Bins == 1024, "sixteen counters to a lane");
+struct Digit {
+    uint32_t digit, need, count;  // all zero if no digit qualifies
+};
+// The digit of the need-th largest from its counters, by a single wave.
+__device__ __forceinline__ Digit find_digit(const uint32_t* h, uint32_t need, int lane)
 {
-    constexpr int LANES = NW * 64;
-    extern __shared__ __attribute__((aligned(16))) uint2 kept[];
-    __shared__ uint32_t h[kHist2Bins], list[kListCap], list_at[kListCap], list_vb[kListCap];
-    __shared__ uint32_t tmp[NW], tgt[MAX_TILES], teq[MAX_TILES], tnc[MAX_TILES];
-    __shared__ uint32_t s_listed, s_digit, s_need, s_count, s_vmax;
+    uint32_t cnt[16], sum = 0;
+    const int l = 63 - lane;  // from the top down
+#pragma unroll
+    for (int i = 0; i < 16; ++i) cnt[i] = h[i * 64 + l];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sum += cnt[i];
+    uint32_t run = wave_scan_incl(sum) - sum;
+    const uint64_t mine = __ballot(run < need && run + sum >= need);
+    if (!mine) return Digit{0u, 0u, 0u};
+    Digit d{0u, 0u, 0u};
+#pragma unroll
+    for (int i = 15; i >= 0; --i) {
+        if (run < need && run + cnt[i] >= need) d = Digit{(uint32_t)(l * 16 + i), need - run, cnt[i]};
+        run += cnt[i];
+    }
+    const int who = __ffsll((unsigned long long)mine) - 1;
+    return Digit{(uint32_t)__builtin_amdgcn_readlane((int)d.digit, who), (uint32_t)__builtin_amdgcn_readlane((int)d.need, who),
+                 (uint32_t)__builtin_amdgcn_readlane((int)d.count, who)};
+}
+
+template <int NW, bool MERGED, int MOST>
+__device__ __forceinline__ Threshold resolve_chunk(const Place& at, const ResolveArgs& a, ResolveScratch<MOST>& lds,
+                                                   uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
+                                                   uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
+                                                   uint8_t* __restrict__ records, uint8_t* __restrict__ stream, const HeaderInfo& hdr)
+{
+    constexpr int LANES = NW * 64, HELD = 2 * kFetch;
+    uint32_t *const h = lds.h, *const list = lds.list, *const list_at = lds.list_at, *const list_vb = lds.list_vb;
+    uint32_t *const tgt = lds.tgt, *const teq = lds.teq;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const size_t c = blockIdx.x;
-    const Place at = place_of<TABLE>(u, tab, blockIdx.x, 0u);
-    const uint32_t Tn = at.Tn, k = at.k, W = at.W, word3 = at.word3;
-    const size_t S = at.S;
+    const size_t c = at.chunk;
+    const uint32_t Tn = at.Tn, k = at.k, W = at.W;
     const uint4* ti = reinterpret_cast<const uint4*>(tinfo + (size_t)at.tile0 * 4);
     const uint2* cd = cand + at.tile0 * (size_t)kTile;
     const uint32_t bstar = sel[c * 8 + 0];
     uint32_t need = sel[c * 8 + 1];
+    const bool counted = !MERGED && Tn > kKeptTiles;  // k_count_digit and k_mark have been here
 
-    // per-tile summaries: kept bins and their range, candidates
-    uint32_t vm = 0;  // per-lane maximum over survivors
-    bool more = false;
-    for (uint32_t t = tid; t < Tn; t += LANES) {
-        const uint4 info = ti[t];
-        tgt[t] = info.x;
-        teq[t] = 0u;
-        tnc[t] = info.z | (info.w ? kAlike : 0u);
-        vm = info.y > vm ? info.y : vm;
-        more = more || (info.z > 64u && !info.w);
+    // A wave's tiles are wave, wave + NW, ...; lane v has the summary of the v-th, e[v] its first candidates.  Slots behind
+    // a tile's last candidate are allocated; what they hold is dropped.
+    const uint32_t own = (uint32_t)wave + (uint32_t)(lane * NW);
+    const bool holds = !counted && lane < HELD && own < Tn, second = !counted && (uint32_t)(wave + kFetch * NW) < Tn;
+    uint4 info = make_uint4(0u, 0u, 0u, 0u);
+    uint2 e[HELD];
+#pragma unroll
+    for (int v = 0; v < HELD; ++v) e[v] = make_uint2(0u, 0u);
+    if (holds) info = ti[own];
+    if (!counted) {
+#pragma unroll
+        for (int v = 0; v < kFetch; ++v) {
+            const uint32_t t = (uint32_t)(wave + v * NW);
+            e[v] = cd[(size_t)(t < Tn ? t : 0u) * kTile + lane];
+        }
+    }
+    if (second) {
+#pragma unroll
+        for (int v = kFetch; v < HELD; ++v) {
+            const uint32_t t = (uint32_t)(wave + v * NW);
+            e[v] = cd[(size_t)(t < Tn ? t : 0u) * kTile + lane];
+        }
     }
     for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
-    if (tid == 0) s_digit = s_need = s_count = s_listed = s_vmax = 0u;  // defined even if no digit qualifies
-    const bool heavy = __syncthreads_or(more);
+    if (tid == 0) lds.listed = lds.vmax = 0u;
+    uint32_t vm = info.y;  // per-lane maximum over survivors
+    if (holds) {
+        tgt[own] = info.x;
+        teq[own] = 0u;
+    }
+    if (counted)
+        for (uint32_t t = tid; t < Tn; t += LANES) {
+            const uint4 v = ti[t];
+            tgt[t] = v.x;
+            teq[t] = 0u;
+            lds.take[t] = v.z;  // what k_mark has left
+            vm = v.y > vm ? v.y : vm;
+        }
+    __syncthreads();
     const bool any = need > 0;  // else nothing is kept (k = 0), and there are no candidates
+    // candidates of the lane's tile to look at, each standing for `weight` of them
+    const uint32_t ncand = info.w ? (info.z ? 1u : 0u) : info.z, nweight = info.w ? info.z : 1u;
+    const bool heavy = __any(ncand > 64u);
 
-    // candidates of a tile to look at, each standing for `weight` of them
-    auto count_of = [&](uint32_t t, uint32_t& weight) __attribute__((always_inline)) {
-        const uint32_t v = t < Tn ? (uint32_t)__builtin_amdgcn_readfirstlane((int)tnc[t]) : 0u;
-        weight = v & kAlike ? v & ~kAlike : 1u;
-        return v & kAlike ? 1u : v;
+    // f(v, t, nc, weight) for the first row of 64 candidates of each of this wave's tiles: straight code, and as little of it as
+    // can be, because it runs once and is fetched as it runs
+    auto first_rows = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < HELD; ++v) {
+            if (v == kFetch && !second) break;
+            f(v, (uint32_t)__builtin_amdgcn_readlane((int)ncand, v), (uint32_t)__builtin_amdgcn_readlane((int)nweight, v));
+        }
     };
-    // row(t, r, e, valid, weight) for every row of 64 candidates of this wave's tiles
-    auto sweep_as = [&](auto keep, auto first, auto&& row) __attribute__((always_inline)) {
-        constexpr bool STORE = decltype(keep)::value && decltype(first)::value, LOAD = decltype(keep)::value && !decltype(first)::value;
-        for (uint32_t t0 = (uint32_t)wave; t0 < Tn; t0 += NW * kFetch) {
-            uint2 e[kFetch];
-#pragma unroll
-            for (int v = 0; v < kFetch; ++v) {
-                // slots behind a tile's last candidate are allocated; what they hold is dropped
-                const uint32_t t = t0 + (uint32_t)(v * NW) < Tn ? t0 + (uint32_t)(v * NW) : 0u;
-                e[v] = LOAD ? kept[t * 64u + lane] : (cd + (size_t)t * kTile)[lane];
-            }
-#pragma unroll
-            for (int v = 0; v < kFetch; ++v) {
-                const uint32_t t = t0 + (uint32_t)(v * NW);
-                uint32_t weight;
-                const uint32_t nc = count_of(t, weight);
-                if (STORE && t < Tn) kept[t * 64u + lane] = e[v];
-                row(t, 0u, e[v], (uint32_t)lane < nc, weight);
-                if (heavy)
-                    for (uint32_t i0 = 64u; i0 < nc; i0 += 64u) {
-                        const bool valid = i0 + (uint32_t)lane < nc;
-                        row(t, i0, cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)], valid, 1u);
-                    }
+    // row(t, i0, e, valid, weight) for all rows of the wave's tiles from number `from` on, out of memory
+    auto rows_of_memory = [&](uint32_t from, auto&& row) __attribute__((always_inline)) {
+        for (uint32_t t = (uint32_t)wave; t < Tn; t += NW) {
+            const uint4 v = ti[t];
+            const uint32_t nc = v.w ? (v.z ? 1u : 0u) : v.z;
+            for (uint32_t i0 = from; i0 < nc; i0 += 64u) {
+                const bool valid = i0 + (uint32_t)lane < nc;
+                row(t, i0, cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)], valid, v.w ? v.z : 1u);
             }
         }
     };
-    auto sweep = [&](auto first, auto&& row) __attribute__((always_inline)) {
-        if (TABLE && KEPT && Tn > kKeptTiles)  // beside tensors whose candidates do fit
-            sweep_as(std::false_type{}, first, row);
-        else
-            sweep_as(std::bool_constant<KEPT>{}, first, row);
+    auto digit_of = [&](uint32_t key) __attribute__((always_inline)) {
+        return digit_place((key >> kHist2Shift) & (uint32_t)(kHist2Bins - 1));
     };
-    const bool counted = Tn > kKeptTiles;  // k_count_digit and k_mark have been here
-    if (any && counted)
-        for (int i = tid; i < kHist2Bins; i += LANES) h[i] = tscan[(size_t)at.tile0 * 2 + i];
-    else if (any)
-        sweep(std::true_type(), [&](uint32_t, uint32_t i0, uint2 e, bool valid, uint32_t weight) {
-            count_digit(h, valid, (e.x >> kHist2Shift) & (uint32_t)(kHist2Bins - 1), i0 != 0, lane, weight);
+    if (any && counted) {
+        for (int i = tid; i < kHist2Bins; i += LANES) h[digit_place((uint32_t)i)] = tscan[(size_t)at.tile0 * 2 + i];
+    } else if (any) {
+        first_rows([&](int v, uint32_t nc, uint32_t weight) __attribute__((always_inline)) {
+            if ((uint32_t)lane < nc) atomicAdd(&h[digit_of(e[v].x)], weight);
         });
+        if (heavy)
+            rows_of_memory(64u, [&](uint32_t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+                count_digit(h, valid, digit_of(x.x), true, lane, weight);
+            });
+    }
     __syncthreads();
-    second_digit<LANES>(h, need, tmp, s_digit, s_need, s_count);
-    need = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_need);
-    uint32_t equal = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_count);
-    const int prefix = (int)((bstar << kHist2Bits) | s_digit);  // the top bits of the threshold's key
+    Digit found = any ? find_digit(h, need, lane) : Digit{0u, 0u, 0u};
+    need = found.need;
+    uint32_t equal = found.count;
+    const int prefix = (int)((bstar << kHist2Bits) | found.digit);  // the top bits of the threshold's key
     const bool few = equal <= kListCap;
     uint32_t tau = any ? (uint32_t)prefix << kHist2Shift : 0xFFFFFFFFu, quota = 0;
     bool ties = false;
     if (any && few) {
+        auto list_one = [&](uint32_t place, uint2 x) __attribute__((always_inline)) {
+            const uint32_t slot = atomicAdd(&lds.listed, 1u);
+            if (slot < kListCap) {
+                list[slot] = x.x;
+                list_at[slot] = place;
+                list_vb[slot] = x.y;
+            }
+        };
         if (counted) {
             for (uint32_t t = tid; t < Tn; t += LANES)
-                for (uint32_t i = 0, n = tnc[t]; i < n; ++i) {
-                    const uint2 e = cd[(size_t)t * kTile + i];
-                    const uint32_t at_list = atomicAdd(&s_listed, 1u);
-                    if (at_list < kListCap) {
-                        list[at_list] = e.x;
-                        list_at[at_list] = t * (uint32_t)kTile + i;
-                        list_vb[at_list] = e.y;
-                    }
-                }
+                for (uint32_t i = 0, n = lds.take[t]; i < n; ++i) list_one(t * (uint32_t)kTile + i, cd[(size_t)t * kTile + i]);
         } else {
-            sweep(std::false_type(), [&](uint32_t t, uint32_t i0, uint2 e, bool valid, uint32_t weight) {
-                const int top = valid ? (int)(e.x >> kHist2Shift) : -1;
-                const uint64_t above = __ballot(top > prefix), same = __ballot(top == prefix);
-                vm = top > prefix && e.y > vm ? e.y : vm;
-                if (above && lane == 0) tgt[t] += (uint32_t)__popcll(above) * weight;
-                // a tile taken as one has more than kListCap candidates, so its digit is not the one with few
-                if (same && top == prefix) {
-                    const uint32_t at = atomicAdd(&s_listed, 1u);
-                    if (at < kListCap) {
-                        list[at] = e.x;
-                        list_at[at] = t * (uint32_t)kTile + i0 + (uint32_t)lane;
-                        list_vb[at] = e.y;
-                    }
-                }
+            // a tile taken as one has more than kListCap candidates, so its digit is not the one with few
+            uint32_t above = 0, hits = 0;  // lane v: of the wave's v-th tile; each lane: what it has to list, the last two of it
+            uint32_t hit_at[2] = {0u, 0u};
+            uint2 hit[2] = {make_uint2(0u, 0u), make_uint2(0u, 0u)};
+            first_rows([&](int v, uint32_t nc, uint32_t weight) __attribute__((always_inline)) {
+                const int top = (uint32_t)lane < nc ? (int)(e[v].x >> kHist2Shift) : -1;
+                const uint32_t many = (uint32_t)__popcll(__ballot(top > prefix)) * weight;
+                above = lane == v ? many : above;
+                vm = top > prefix && e[v].y > vm ? e[v].y : vm;
+                const bool is = top == prefix;
+                hits += is ? 1u : 0u;
+                hit_at[1] = is ? hit_at[0] : hit_at[1];
+                hit[1].x = is ? hit[0].x : hit[1].x;
+                hit[1].y = is ? hit[0].y : hit[1].y;
+                hit_at[0] = is ? (uint32_t)v : hit_at[0];
+                hit[0].x = is ? e[v].x : hit[0].x;
+                hit[0].y = is ? e[v].y : hit[0].y;
             });
+            if (holds) atomicAdd(&tgt[own], above);
+            if (!__any(hits > 2u)) {
+#pragma unroll
+                for (uint32_t i = 0; i < 2u; ++i)
+                    if (hits > i) list_one(((uint32_t)wave + hit_at[i] * NW) * (uint32_t)kTile + (uint32_t)lane, hit[i]);
+            } else {
+                rows_of_memory(0u, [&](uint32_t t, uint32_t i0, uint2 x, bool valid, uint32_t) __attribute__((always_inline)) {
+                    if (i0 == 0u && valid && (int)(x.x >> kHist2Shift) == prefix) list_one(t * (uint32_t)kTile + (uint32_t)lane, x);
+                });
+            }
+            if (heavy)
+                rows_of_memory(64u, [&](uint32_t t, uint32_t i0, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+                    const int top = valid ? (int)(x.x >> kHist2Shift) : -1;
+                    const uint64_t more = __ballot(top > prefix);
+                    vm = top > prefix && x.y > vm ? x.y : vm;
+                    if (more && lane == 0) atomicAdd(&tgt[t], (uint32_t)__popcll(more) * weight);
+                    if (top == prefix) list_one(t * (uint32_t)kTile + i0 + (uint32_t)lane, x);
+                });
         }
         __syncthreads();
         const uint32_t listed = equal;
@@ -723,132 +816,140 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
         quota = need;
         ties = equal != quota;
         for (uint32_t i = tid; i < listed; i += LANES) {
-            const uint32_t x = list[i], at = list_at[i];
+            const uint32_t x = list[i], place = list_at[i];
             bool kept = x >= tau;
             if (ties && x == tau) {  // the first of them, in bin order
                 uint32_t before = 0;
-                for (uint32_t j = 0; j < listed; ++j) before += list[j] == tau && list_at[j] < at;
+                for (uint32_t j = 0; j < listed; ++j) before += list[j] == tau && list_at[j] < place;
                 kept = before < quota;
-                atomicAdd(&teq[at / (uint32_t)kTile], 1u);
+                atomicAdd(&teq[place / (uint32_t)kTile], 1u);
             }
             if (kept) {
-                atomicAdd(&tgt[at / (uint32_t)kTile], 1u);
+                atomicAdd(&tgt[place / (uint32_t)kTile], 1u);
                 vm = list_vb[i] > vm ? list_vb[i] : vm;
             }
         }
         __syncthreads();
     } else if (any) {
-        for (int i = tid; i < 512; i += LANES) h[i] = 0u;
         __syncthreads();
-        sweep(std::false_type(), [&](uint32_t, uint32_t, uint2 e, bool valid, uint32_t weight) {
-            count_digit(h, valid && (int)(e.x >> kHist2Shift) == prefix, e.x & 511u, true, lane, weight);
+        for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
+        __syncthreads();
+        rows_of_memory(0u, [&](uint32_t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+            count_digit(h, valid && (int)(x.x >> kHist2Shift) == prefix, digit_place(x.x & 511u), true, lane, weight);
         });
         __syncthreads();
-        if (tid == 0) {
-            uint32_t above = 0;
-            int d = 511;
-            while (d > 0 && above + h[d] < need) above += h[d--];
-            s_digit = (uint32_t)d;
-            s_need = need - above;
-            s_count = h[d];
-        }
-        __syncthreads();
-        tau |= s_digit;
-        quota = s_need;
-        equal = s_count;
+        found = find_digit(h, need, lane);
+        tau |= found.digit;
+        quota = found.need;
+        equal = found.count;
         ties = equal != quota;
-        sweep(std::false_type(), [&](uint32_t t, uint32_t, uint2 e, bool valid, uint32_t weight) {
-            const uint64_t gm = __ballot(valid && e.x > tau), em = __ballot(valid && e.x == tau);
-            if (lane == 0 && (gm | em)) {
-                tgt[t] += (uint32_t)__popcll(gm) * weight;
-                teq[t] += (uint32_t)__popcll(em) * weight;
-            }
-            vm = valid && (ties ? e.x > tau : e.x >= tau) && e.y > vm ? e.y : vm;
+        rows_of_memory(0u, [&](uint32_t t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+            const uint64_t gm = __ballot(valid && x.x > tau), em = __ballot(valid && x.x == tau);
+            if (gm && lane == 0) atomicAdd(&tgt[t], (uint32_t)__popcll(gm) * weight);
+            if (em && lane == 0) atomicAdd(&teq[t], (uint32_t)__popcll(em) * weight);
+            vm = valid && (ties ? x.x > tau : x.x >= tau) && x.y > vm ? x.y : vm;
         });
         __syncthreads();
     }
     const bool count_equal = any && !few;  // tgt does not hold the kept ones of the bins equal to tau yet
 
-    // scan over tiles: equal-key prefix decides who gets the tie quota, survivor prefix gives the ranks
+    // Scan over tiles: the equal keys before a tile decide who gets the tie quota, the survivors before it give the ranks.  Every
+    // wave runs through all of them, 64 at a time, and sees to its share.
     uint32_t* rec = reinterpret_cast<uint32_t*>(records + at.record);
     uint32_t* codes = rec + 4 + W;
-    const uint32_t twoN = codes_per_bin * (uint32_t)bits;  // code bits per kept bin
-    uint32_t eqcarry = 0, rankcarry = 0;
-    for (uint32_t b0 = 0; b0 < Tn; b0 += LANES) {
-        const uint32_t t = b0 + tid;
-        uint32_t surv = t < Tn ? tgt[t] : 0u, eq = t < Tn ? teq[t] : 0u, eqpre = 0;
-        if (ties) {
-            const uint32_t incl = block_scan_incl<NW>(eq, tmp);
-            eqpre = eqcarry + incl - eq;
-            eq = eqpre >= quota ? 0u : (eq < quota - eqpre ? eq : quota - eqpre);
-            if (tid == LANES - 1) s_count = incl;
+    const uint32_t twoN = a.codes_per_bin * (uint32_t)a.bits;  // code bits per kept bin
+    uint32_t eqcarry = 0, rankcarry = 0, my_rank = 0, my_eq = 0;
+    for (uint32_t t0 = 0; t0 < Tn; t0 += 64u) {
+        const uint32_t t = t0 + (uint32_t)lane;
+        const bool share = (t0 >> 6) % NW == (uint32_t)wave;
+        uint32_t surv = t < Tn ? tgt[t] : 0u, eqpre = 0;
+        if (ties || count_equal) {
+            uint32_t eq = t < Tn ? teq[t] : 0u;
+            if (ties) {
+                const uint32_t incl = wave_scan_incl(eq);
+                eqpre = eqcarry + incl - eq;
+                eq = eqpre >= quota ? 0u : (eq < quota - eqpre ? eq : quota - eqpre);
+                eqcarry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            }
+            if (count_equal) {
+                surv += eq;
+                if (share && t < Tn) lds.take[t] = eq;
+            }
         }
-        if (count_equal) {
-            surv += eq;
-            if (t < Tn) teq[t] = eq;
-        }
-        const uint32_t incl = block_scan_incl<NW>(surv, tmp);
-        const uint32_t before = rankcarry + incl - surv;
+        const uint32_t incl = wave_scan_incl(surv), before = rankcarry + incl - surv;
+        rankcarry += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         // ranks never leave [0, k]: whatever the counts say, the code words of a tile stay inside the record
         const uint32_t rank = before < k ? before : k;
-        surv = surv < k - rank ? surv : k - rank;
-        if (t < Tn) {
+        if constexpr (MERGED) {
+            if (at.tile >> 6 == t0 >> 6) {
+                my_rank = (uint32_t)__builtin_amdgcn_readlane((int)rank, (int)(at.tile & 63u));
+                my_eq = (uint32_t)__builtin_amdgcn_readlane((int)eqpre, (int)(at.tile & 63u));
+            }
+        } else if (share && t < Tn) {
             // where all bins equal to tau are taken, a prefix of zero (and an endless quota) says so
             *reinterpret_cast<uint2*>(tscan + (size_t)(at.tile0 + t) * 2) = make_uint2(rank, eqpre);
+            surv = surv < k - rank ? surv : k - rank;
             if (surv) {
                 codes[(twoN * rank) >> 5] = 0u;
                 codes[(twoN * (rank + surv) - 1u) >> 5] = 0u;
             }
         }
-        if (b0 + LANES < Tn) {
-            if (tid == LANES - 1) s_digit = incl;
-            __syncthreads();
-            rankcarry += s_digit;
-            if (ties) eqcarry += s_count;
-            __syncthreads();
-        }
     }
-    const uint32_t code_words = (twoN * k + 31u) >> 5;
-    const uint32_t rec_words = (uint32_t)(S / 4) - 4u - W;
-    for (uint32_t w = code_words + tid; w < rec_words; w += LANES) codes[w] = 0u;
+    if constexpr (!MERGED) {
+        const uint32_t code_words = (twoN * k + 31u) >> 5, rec_words = (uint32_t)(at.S / 4) - 4u - W;
+        for (uint32_t w = code_words + tid; w < rec_words; w += LANES) codes[w] = 0u;
+    }
 
     // largest component over the survivors (not needed when the caller fixed the range: Sec. 3.2.1, static max)
-    if (!static_vmax) {
+    uint32_t vmax = a.static_vmax;
+    if (!vmax) {
         if (count_equal && ties) {
             __syncthreads();
             for (uint32_t t = (uint32_t)wave; t < Tn; t += NW) {
-                uint32_t weight;
-                const uint32_t nc = count_of(t, weight), take = teq[t];
-                uint32_t eqrun = 0;  // bins of the tile equal to tau seen so far
-                for (uint32_t i0 = 0; i0 < nc && eqrun < take; i0 += 64u) {
+                const uint4 v = ti[t];
+                const uint32_t nc = v.w ? (v.z ? 1u : 0u) : v.z, take = lds.take[t];
+                uint32_t eqseen = 0;  // bins of the tile equal to tau seen so far
+                for (uint32_t i0 = 0; i0 < nc && eqseen < take; i0 += 64u) {
                     const bool valid = i0 + (uint32_t)lane < nc;
-                    const uint2 e = cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)];
-                    const bool iseq = valid && e.x == tau;
+                    const uint2 x = cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)];
+                    const bool iseq = valid && x.x == tau;
                     const uint64_t em = __ballot(iseq);
-                    vm = iseq && eqrun + prefix_popc(em) < take && e.y > vm ? e.y : vm;
-                    eqrun += (uint32_t)__popcll(em);
+                    vm = iseq && eqseen + prefix_popc(em) < take && x.y > vm ? x.y : vm;
+                    eqseen += (uint32_t)__popcll(em);
                 }
             }
         }
         vm = wave_max(vm);
-        if (lane == 0 && vm) atomicMax(&s_vmax, vm);
+        if (lane == 0 && vm) atomicMax(&lds.vmax, vm);
         __syncthreads();
+        vmax = lds.vmax;
     }
-    if (tid == 0) {
-        const uint32_t vmax = static_vmax ? static_vmax : s_vmax;
-        uint32_t pbase = 0;
-        if (bits != 32) {
-            const int shift = 23 - m;
-            const int64_t pb = (int64_t)(vmax >> shift) - (int64_t)((1u << (bits - 1)) - 2u);
-            pbase = pb < 1 ? 1u : (uint32_t)pb;
-        }
-        sel[c * 8 + 2] = tau;
-        sel[c * 8 + 3] = ties ? quota : 0xFFFFFFFFu;
-        sel[c * 8 + 4] = pbase;
+    Threshold th{tau, ties ? quota : 0xFFFFFFFFu, 0u, 0u, 0u};
+    if (a.bits != 32) {
+        const int64_t pb = (int64_t)(vmax >> (23 - a.m)) - (int64_t)((1u << (a.bits - 1)) - 2u);
+        th.pbase = pb < 1 ? 1u : (uint32_t)pb;
+    }
+    if constexpr (MERGED) {
+        th.rank0 = my_rank;
+        th.eq0 = my_eq;
+    } else if (tid == 0) {
+        sel[c * 8 + 2] = th.tau;
+        sel[c * 8 + 3] = th.quota;
+        sel[c * 8 + 4] = th.pbase;
         sel[c * 8 + 5] = vmax;
-        *reinterpret_cast<uint4*>(rec) = make_uint4(pbase, vmax, k, word3);
     }
-    if (hdr.write && c == 0 && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
+    if ((!MERGED || at.tile == 0) && tid == 0) *reinterpret_cast<uint4*>(rec) = make_uint4(th.pbase, vmax, k, at.word3);
+    if (hdr.write && c == 0 && (!MERGED || at.tile == 0) && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
+    return th;
+}
+template <bool TABLE, int NW>
+__global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, ResolveArgs a, uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
+                                                     uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
+                                                     uint8_t* __restrict__ records, uint8_t* __restrict__ stream,
+                                                     HeaderInfo hdr, TableArg<TABLE> tab)
+{
+    __shared__ ResolveScratch<MAX_TILES> lds;
+    resolve_chunk<NW, false>(place_of<TABLE>(u, tab, blockIdx.x, 0u), a, lds, sel, tinfo, tscan, cand, records, stream, hdr);
 }
 
 // ------------------------------------------------------------------ emit ----
@@ -860,10 +961,12 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, int bits, int m, u
 // do pass through LDS, in 16-byte loads (50 us for 55).
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against shuffles and vector masks: 70 -> 67 us,
 // binary16 bins 60 -> 45, 15 % of the samples kept at 32 bits 98 -> 50; one chunk of 2^16 8 -> 7.
-template <bool TABLE, bool REAL, bool HALF>
-__global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u, int bits, int m,
-                                             const uint32_t* __restrict__ sel, const uint32_t* __restrict__ tscan,
-                                             uint8_t* __restrict__ records, TableArg<TABLE> tab, size_t n)
+template <bool TABLE, bool REAL, bool HALF, bool MERGED>
+__global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u, ResolveArgs a,
+                                             uint32_t* __restrict__ sel, uint32_t* __restrict__ tscan,
+                                             const uint32_t* __restrict__ tinfo, const uint2* __restrict__ cand,
+                                             uint8_t* __restrict__ records, uint8_t* __restrict__ stream, HeaderInfo hdr,
+                                             TableArg<TABLE> tab, size_t n)
 {
     using E = typename Elem<REAL>::T;
     constexpr uint32_t CODES = Elem<REAL>::kCodes;
@@ -876,8 +979,11 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
     const uint32_t c = at.chunk, tile = at.tile, B = at.B, W = at.W;
     const size_t S = at.S;
     const int pair_log = at.pair_log;
-    const uint32_t tau = sel[c * 8 + 2], quota = sel[c * 8 + 3], pbase = sel[c * 8 + 4];
-    const uint32_t rank0 = tscan[(size_t)blockIdx.x * 2 + 0], eq0 = tscan[(size_t)blockIdx.x * 2 + 1];
+    const int bits = a.bits, m = a.m;
+    Threshold found;
+    if constexpr (!MERGED)
+        found = Threshold{sel[c * 8 + 2], sel[c * 8 + 3], sel[c * 8 + 4], tscan[(size_t)blockIdx.x * 2 + 0],
+                          tscan[(size_t)blockIdx.x * 2 + 1]};
     const uint32_t twoN = CODES * (uint32_t)bits;  // code bits per kept unit
     const int shift = 23 - m;
 
@@ -893,6 +999,11 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
     } else {
         load_units(X, row0, count, lane, pair_log, z);
     }
+    if constexpr (MERGED) {
+        __shared__ ResolveScratch<kMergedTiles> lds;
+        found = resolve_chunk<NT / 64, true>(at, a, lds, sel, tinfo, tscan, cand, records, stream, hdr);
+    }
+    const uint32_t tau = found.tau, quota = found.quota, pbase = found.pbase, rank0 = found.rank0, eq0 = found.eq0;
     if (bits != 32)  // 32-bit codes go straight to memory
         for (uint32_t i = 4u * tid; i < (uint32_t)kTile * twoN / 32u + 8u; i += 4u * NT)
             *reinterpret_cast<uint4*>(cw + i) = make_uint4(0u, 0u, 0u, 0u);
@@ -1030,17 +1141,6 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
 // ---------------------------------------------------------------- decode ----
 constexpr int GROUP_WORDS = 16;  // one wave of the decode kernel covers 512 bins = 16 bitmap words
 
-// 0, or 6 if a record (or the stream's header) is not what the call's arguments make it; kept: set bits of its bitmap
-__device__ __forceinline__ uint32_t record_verdict(const uint8_t* __restrict__ record, const uint8_t* __restrict__ stream,
-                                                   bool first_of_stream, uint32_t kept, uint32_t k, uint32_t word3,
-                                                   const HeaderInfo& hdr)
-{
-    const uint32_t* rec = reinterpret_cast<const uint32_t*>(record);
-    bool bad = kept != k || rec[2] != k || rec[3] != word3;
-    if (hdr.write && first_of_stream) bad = bad || header_bad(hdr, reinterpret_cast<const uint32_t*>(stream));
-    return bad ? 6u : 0u;
-}
-
 // Per chunk: number of set bits before each group of 16 bitmap words (the prefix sum of Sec. 3.2's status
 // vector, kept at the granularity a wave needs); checks the headers and leaves the verdict in *verdict.
 __device__ __forceinline__ void group_prefix_chunk(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ record,
@@ -1090,14 +1190,6 @@ __device__ __forceinline__ void group_prefix_chunk(const uint8_t* __restrict__ s
     if (tid == 0) *verdict = record_verdict(record, stream, first_of_stream, s_carry, k, word3, hdr);
 }
 
-// what the first kernel of a receiver's call leaves in the control block
-__device__ __forceinline__ void write_control(uint32_t* __restrict__ ctl, const StatusNote& note, int tid, int lanes)
-{
-    // cleared as a whole: also the hand-over words of the fused inverse transform that may follow
-    for (int i = tid; i < (int)(kControlBytes / 4); i += lanes)
-        ctl[i] = i >= kNoteWord && i < kNoteWord + kNoteWords ? note_word(note, i) : 0u;
-}
-
 template <bool TABLE>
 __global__ __launch_bounds__(RT) void k_group_prefix(const uint8_t* __restrict__ stream,
                                                      const uint8_t* __restrict__ records, Shape u, HeaderInfo hdr,
@@ -1107,7 +1199,7 @@ __global__ __launch_bounds__(RT) void k_group_prefix(const uint8_t* __restrict__
     const Place at = place_of<TABLE>(u, tab, blockIdx.x, 0u);
     group_prefix_chunk(stream, records + at.record, blockIdx.x == 0, at.W, at.k, at.word3, hdr, gprefix + at.group0,
                        verdicts + blockIdx.x);
-    if (ctl && blockIdx.x == 0) write_control(ctl, note, threadIdx.x, RT);
+    if (ctl && blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, RT);
 }
 
 // The same for several peers' streams: workgroup (peer, chunk).
@@ -1121,7 +1213,7 @@ __global__ __launch_bounds__(RT) void k_group_prefix_peers(PeerList streams, uin
     const uint8_t* stream = streams.p[peer];
     group_prefix_chunk(stream, stream + 64 + (size_t)c * S, c == 0, W, k, 0u, hdr,
                        gprefix + ((size_t)peer * C + c) * G, verdicts + (size_t)peer * C + c);
-    if (blockIdx.x == 0) write_control(ctl, note, threadIdx.x, RT);
+    if (blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, RT);
 }
 
 // A word every lane reads: by a scalar load, from memory that this kernel does not write.
@@ -1379,7 +1471,7 @@ __global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ strea
         run = (uint32_t)__builtin_amdgcn_readfirstlane((int)run);
         if (at.tile + 1u == at.Tn && tid == 0)  // the last tile has seen all of the bitmap
             verdicts[at.chunk] = record_verdict(record, stream, at.chunk == 0, total, at.k, at.word3, hdr);
-        if (ctl && blockIdx.x == 0) write_control(ctl, note, tid, NT);
+        if (ctl && blockIdx.x == 0) clear_control(ctl, note, tid, NT);
     }
     fetch_codes<NL, Elem<REAL>::kCodes>(record, S, W, bits, run, kept, lane, wc);
     T z[ROWS];
@@ -1483,6 +1575,10 @@ static Extent extent_of(const CodecArgs& a)
 // In k_collect that is 16 KB more to read per tile.  Compress, chunks of 2^16: 16 tiles 30.5 -> 28.8 us, 512 39.7 -> 38.4,
 // 1088 no difference, 2176 58.0 -> 58.9.
 static bool find_in_collect(const Extent& x) { return x.tiles <= 1024; }
+// k_emit finds the threshold itself, every workgroup all of it, where the launch saved weighs more.  Senders in us, k_resolve /
+// without: chunks of 2^16 (17 tiles) 68 tiles 24.3 / 22.7, 374 34.0 / 32.5, 782 40.7 / 40.5, 1088 47.7 / 47.9;  2^17 (33) 66 23.8 / 22.3,
+// 528 34.4 / 33.9, 1056 46.7 / 47.2;  2^18 (65) 65 25.4 / 24.3, 390 34.4 / 34.1, 520 36.4 / 37.2.
+static bool resolve_in_emit(const Extent& x) { return x.most <= kMergedTiles && x.tiles <= 512; }
 // In k_decode it is the bitmap up to the tile, at most 256 bytes for each tile of the chunk, to read beside the tile's codes.
 // Decompress: one chunk of 2^16 21.7 -> 17.7 us, 2^23 samples in chunks of 2^20 (2056 tiles) 49.4 -> 48.8, 2^24 76.6 -> 77.8, one
 // chunk of 2^22 (1025 tiles) 50.3 -> 52.5.  Chunks of a few tiles always: Top-k of 2^24 samples in chunks of 2^12 32.8 -> 16.2.
@@ -1522,20 +1618,23 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
                  a.hdr_theta, a.time_domain ? 1u : 0u, (uint32_t)a.hdr_scale};
     const uint32_t codes_per_bin = a.time_domain ? 1u : 2u;
     const dim3 per_tile((unsigned)x.tiles), per_chunk((unsigned)x.chunks);
+    const bool merged = resolve_in_emit(x);
+    uint8_t* clear = merged ? records : nullptr;
+    const ResolveArgs ra{a.bits, a.m, a.static_vmax, codes_per_bin};
     auto select = [&](auto table) {
         constexpr bool TABLE = decltype(table)::value;
         const TableArg<TABLE> tab = table_arg<TABLE>(a.tab);
         auto collect = [&](auto find) {
             constexpr bool FIND = decltype(find)::value;
             if constexpr (TABLE) {
-                FFTSP_LAUNCH("collect", (k_collect<FIND, true, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, tscan, cand, tab, a.n);
+                FFTSP_LAUNCH("collect", (k_collect<FIND, true, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, tscan, cand, clear, tab, a.n);
             } else {
                 if (a.time_domain)
-                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, true, false>), per_tile, dim3(NT), 0, s, spec, u, hist, sel, tinfo, tscan, cand, tab, a.n);
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, true, false>), per_tile, dim3(NT), 0, s, spec, u, hist, sel, tinfo, tscan, cand, clear, tab, a.n);
                 else if (a.half)
-                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, true>), per_tile, dim3(NT), 0, s, Xh, u, hist, sel, tinfo, tscan, cand, tab, a.n);
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, true>), per_tile, dim3(NT), 0, s, Xh, u, hist, sel, tinfo, tscan, cand, clear, tab, a.n);
                 else
-                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, tscan, cand, tab, a.n);
+                    FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, tscan, cand, clear, tab, a.n);
             }
         };
         if (find_in_collect(x)) {
@@ -1544,6 +1643,7 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
             FFTSP_LAUNCH("find_bucket", k_find_bucket<TABLE>, per_chunk, dim3(NT), 0, s, hist, u, sel, tab);
             collect(std::false_type{});
         }
+        if (merged) return hipGetLastError();
         if (x.most > kKeptTiles) {
             LongStarts at{};
             uint32_t parts = (uint32_t)x.chunks * parts_of(x.most);
@@ -1560,43 +1660,38 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
             FFTSP_LAUNCH("count_digit", k_count_digit<TABLE>, dim3(parts), dim3(NT), 0, s, u, tinfo, tscan, cand, tab, at);
             FFTSP_LAUNCH("mark", k_mark<TABLE>, dim3(parts), dim3(NT), 0, s, u, sel, tinfo, tscan, cand, tab, at);
         }
-        // few waves for few tiles: their barriers are cheaper than more hands
-        // KEEP: tiles there is room for in LDS (0: none are kept).  The attribute is the kernel's, not the call's: it is always
-        // set to the most any call takes, since another thread may be between setting it and its launch.
-        auto resolve = [&](auto waves, auto keep) {
+        auto resolve = [&](auto waves) {
             constexpr int NW = decltype(waves)::value;
-            constexpr uint32_t KEEP = decltype(keep)::value;
-            constexpr bool KEPT = KEEP != 0;
-            const size_t lds = std::min(x.most, KEEP) * 512u;
-            if constexpr (KEPT) {
-                const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_resolve<TABLE, NW, KEPT>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)(KEEP * 512u));
-                if (e != hipSuccess) return e;
-            }
-            FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW, KEPT>), per_chunk, dim3(NW * 64), lds, s, u, a.bits, a.m, a.static_vmax,
-                         codes_per_bin, sel, tinfo, tscan, cand, records, stream_base, h, tab);
+            FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW>), per_chunk, dim3(NW * 64), 0, s, u, ra, sel, tinfo, tscan, cand, records, stream_base,
+                         h, tab);
             return hipGetLastError();
         };
-        if (x.most <= 40u) return resolve(std::integral_constant<int, 4>{}, std::integral_constant<uint32_t, 40>{});
-        if (x.most <= 130u) return resolve(std::integral_constant<int, 8>{}, std::integral_constant<uint32_t, 130>{});
-        if constexpr (!TABLE)
-            if (x.most > kKeptTiles) return resolve(std::integral_constant<int, 16>{}, std::integral_constant<uint32_t, 0>{});
-        return resolve(std::integral_constant<int, 16>{}, std::integral_constant<uint32_t, kKeptTiles>{});
+        // few waves for few tiles: their barriers are cheaper than more hands
+        if (x.most <= 40u) return resolve(std::integral_constant<int, 4>{});
+        if (x.most <= kHeldTiles<8>) return resolve(std::integral_constant<int, 8>{});
+        return resolve(std::integral_constant<int, 16>{});
     };
     const hipError_t e = a.tab ? select(std::true_type{}) : select(std::false_type{});
     if (e != hipSuccess) return e;
-#define FFTSP_EMIT(TABLE, REAL, HALF, src)                                                                             \
-    FFTSP_LAUNCH("emit", (k_emit<TABLE, REAL, HALF>), per_tile, dim3(NT), 0, s, src, u, a.bits, a.m, sel, tscan, records, \
-                 table_arg<TABLE>(a.tab), a.n)
-    if (a.tab)
+#define FFTSP_EMIT_AS(TABLE, REAL, HALF, MERGED, src, lds)                                                                          \
+    FFTSP_LAUNCH("emit", (k_emit<TABLE, REAL, HALF, MERGED>), per_tile, dim3(NT), lds, s, src, u, ra, sel, tscan, tinfo, cand, records, \
+                 stream_base, h, table_arg<TABLE>(a.tab), a.n)
+#define FFTSP_EMIT(TABLE, REAL, HALF, src)                              \
+    if (merged)                                                         \
+        FFTSP_EMIT_AS(TABLE, REAL, HALF, true, src, 0);     \
+    else                                                                \
+        FFTSP_EMIT_AS(TABLE, REAL, HALF, false, src, 0)
+    if (a.tab) {
         FFTSP_EMIT(true, false, false, X);
-    else if (a.time_domain)
+    } else if (a.time_domain) {
         FFTSP_EMIT(false, true, false, spec);
-    else if (a.half)
+    } else if (a.half) {
         FFTSP_EMIT(false, false, true, Xh);
-    else
+    } else {
         FFTSP_EMIT(false, false, false, X);
+    }
 #undef FFTSP_EMIT
+#undef FFTSP_EMIT_AS
     return hipGetLastError();
 }
 

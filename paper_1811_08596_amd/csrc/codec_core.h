@@ -227,5 +227,24 @@ __device__ __forceinline__ bool header_bad(const HeaderInfo& hdr, const uint32_t
     return bad;
 }
 
+// 0, or 6 if a record (or the stream's header) is not what the call's arguments make it; kept: set bits of its bitmap
+__device__ __forceinline__ uint32_t record_verdict(const uint8_t* __restrict__ record, const uint8_t* __restrict__ stream,
+                                                   bool first_of_stream, uint32_t kept, uint32_t k, uint32_t word3,
+                                                   const HeaderInfo& hdr)
+{
+    const uint32_t* rec = reinterpret_cast<const uint32_t*>(record);
+    bool bad = kept != k || rec[2] != k || rec[3] != word3;
+    if (hdr.write && first_of_stream) bad = bad || header_bad(hdr, reinterpret_cast<const uint32_t*>(stream));
+    return bad ? 6u : 0u;
+}
+
+// what the first kernel of a receiver's call leaves in the control block
+__device__ __forceinline__ void clear_control(uint32_t* __restrict__ ctl, const StatusNote& note, int tid, int lanes)
+{
+    // cleared as a whole: also the hand-over words of the fused inverse transform that may follow
+    for (int i = tid; i < (int)(kControlBytes / 4); i += lanes)
+        ctl[i] = i >= kNoteWord && i < kNoteWord + kNoteWords ? note_word(note, i) : 0u;
+}
+
 }  // namespace
 }  // namespace fftsp
