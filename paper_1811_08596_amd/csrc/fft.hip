@@ -22,7 +22,7 @@
 // over all banks without padding.
 #include "fft_core.h"
 #include "codec_core.h"
-#include <cmath>
+#include "short.h"
 #include <type_traits>
 
 namespace fftsp {
@@ -1020,6 +1020,10 @@ hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spe
     // wants neither
     if ((hist != nullptr) != (pair_spec != 0)) return hipErrorInvalidValue;
     const int logN1 = (logM + 1) / 2, logN2 = logM / 2;
+    if (!only_if && short_forward(logM, C)) {
+        if (pair_log && pair_spec) *pair_log = logN1;
+        return launch_short_rfft(in, n, logM, C, sp, sstride, mid, t, hist, zero_ptr, (uint32_t)zero_words, s);
+    }
     hipError_t e;
 #define FWD_A(p) fwd_a<p, false>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, 1.0f, s, only_if)
     switch (logN1) {
@@ -1054,14 +1058,13 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
                         Tables t, int pair_spec, float gain, hipStream_t s, const uint32_t* only_if)
 {
     const int logM = logL - 1;
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     const float2* sp = reinterpret_cast<const float2*>(spec);
     if (logM < 15 || C * ((size_t)1 << (logM - 13)) > 0x7fffffffu) return hipErrorInvalidValue;
-    const int logN1 = (logM + 1) / 2, logN2 = logM / 2;
     hipError_t e;
-    if (pair_spec) {
-        switch (logN2) {
+    if (!only_if && short_inverse(logM, C)) {
+        e = launch_short_inverse_b(sp, sstride, logM, C, mid, t, pair_spec, s);
+    } else if (pair_spec) {
+        switch (logM / 2) {
             case 7: e = inv_b<7, true, false>(sp, sstride, logM, C, mid, t, 1.0f, s, only_if); break;
             case 8: e = inv_b<8, true, false>(sp, sstride, logM, C, mid, t, 1.0f, s, only_if); break;
             case 9: e = inv_b<9, true, false>(sp, sstride, logM, C, mid, t, 1.0f, s, only_if); break;
@@ -1069,7 +1072,7 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
             default: return hipErrorInvalidValue;
         }
     } else {
-        switch (logN2) {
+        switch (logM / 2) {
             case 7: e = inv_b<7, false, false>(sp, sstride, logM, C, mid, t, 1.0f, s); break;
             case 8: e = inv_b<8, false, false>(sp, sstride, logM, C, mid, t, 1.0f, s); break;
             case 9: e = inv_b<9, false, false>(sp, sstride, logM, C, mid, t, 1.0f, s); break;
@@ -1077,22 +1080,36 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
             default: return hipErrorInvalidValue;
         }
     }
-    if (e != hipSuccess) return e;
-#define INV_A(p) inv_a<p, false>(mid, logM, C, out, n, t, aligned, gain, s, only_if)
-    switch (logN1) {
-        case 8: return INV_A(8);
-        case 9: return INV_A(9);
-        case 10: return INV_A(10);
-        case 11: return INV_A(11);
+    return e == hipSuccess ? launch_inverse_a(mid, logM, C, out, n, t, gain, 0, s, only_if) : e;
+}
+
+hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, hipStream_t s,
+                            const uint32_t* only_if)
+{
+    if (half) gain *= half_lift(logM);
+    if (!only_if && short_inverse(logM, C)) return launch_short_inverse_a(mid, logM, C, out, n, t, gain, half, s);
+    const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
+    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    auto run = [&](auto columns) {
+        constexpr int LOGN1 = decltype(columns)::value;
+        return half ? inv_a<LOGN1, true>(mid, logM, C, out, n, t, aligned, gain, s, only_if)
+                    : inv_a<LOGN1, false>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    };
+    switch ((logM + 1) / 2) {
+        case 7: return half ? inv_a<7, true>(mid, logM, C, out, n, t, aligned, gain, s) : hipErrorInvalidValue;
+        case 8: return run(std::integral_constant<int, 8>{});
+        case 9: return run(std::integral_constant<int, 9>{});
+        case 10: return run(std::integral_constant<int, 10>{});
+        case 11: return run(std::integral_constant<int, 11>{});
         default: return hipErrorInvalidValue;
     }
-#undef INV_A
 }
 
 hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, float2* mid, Tables t, uint32_t* hist,
                             uint32_t* zero_ptr, size_t zero_words, hipStream_t s)
 {
     if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors || zero_words > 0xffffffffu) return hipErrorInvalidValue;
+    if (short_forward(b)) return launch_short_rfft_long(in, b, spec, mid, t, hist, zero_ptr, (uint32_t)zero_words, s);
     const uintptr_t addr = reinterpret_cast<uintptr_t>(in);
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     LongStarts at;
@@ -1121,24 +1138,36 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
 hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out, float2* mid, Tables t, hipStream_t s)
 {
     if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors) return hipErrorInvalidValue;
+    hipError_t e;
+    if (short_inverse(b)) {
+        e = launch_short_inverse_b_long(spec, b, mid, t, s);
+    } else {
+        LongStarts at;
+        const uint32_t wide = first_wide(b, log_rows, kWideInverseB, kWideInverseBBeside, false);
+        e = by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
+            constexpr int LOGE = decltype(size)::value;
+            const hipError_t err = set_lds(k_inv_b_long<LOGE>, long_lds(LOGE));
+            if (err != hipSuccess) return err;
+            const uint32_t per = long_run(b, first, end, LOGE, most_wgs(LOGE, 1536));
+            const uint32_t g = long_starts(b, first, end, &at, [&](const LongTensor& x) {
+                const uint32_t tiles = 1u << (x.logM - LOGE);
+                return tiles > per ? tiles / per : 1u;
+            });
+            FFTSP_LAUNCH("irfft_pass_b", k_inv_b_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), long_lds(LOGE), s, spec, mid, t, per, b.tab, at);
+            return hipGetLastError();
+        });
+    }
+    return e == hipSuccess ? launch_inverse_a_long(mid, b, out, t, s) : e;
+}
+
+hipError_t launch_inverse_a_long(const float2* mid, const LongBatch& b, float* out, Tables t, hipStream_t s)
+{
+    if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors) return hipErrorInvalidValue;
+    if (short_inverse(b)) return launch_short_inverse_a_long(b, out, mid, t, s);
     const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     LongStarts at;
-    uint32_t wide = first_wide(b, log_rows, kWideInverseB, kWideInverseBBeside, false);
-    const hipError_t e = by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
-        constexpr int LOGE = decltype(size)::value;
-        const hipError_t err = set_lds(k_inv_b_long<LOGE>, long_lds(LOGE));
-        if (err != hipSuccess) return err;
-        const uint32_t per = long_run(b, first, end, LOGE, most_wgs(LOGE, 1536));
-        const uint32_t g = long_starts(b, first, end, &at, [&](const LongTensor& x) {
-            const uint32_t tiles = 1u << (x.logM - LOGE);
-            return tiles > per ? tiles / per : 1u;
-        });
-        FFTSP_LAUNCH("irfft_pass_b", k_inv_b_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), long_lds(LOGE), s, spec, mid, t, per, b.tab, at);
-        return hipGetLastError();
-    });
-    if (e != hipSuccess) return e;
-    wide = first_wide(b, log_columns, kWideInverseALaunch, kWideInverseALaunch, true);
+    const uint32_t wide = first_wide(b, log_columns, kWideInverseALaunch, kWideInverseALaunch, true);
     return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
         constexpr int LOGE = decltype(size)::value;
         const hipError_t err = set_lds(k_inv_a_long<LOGE>, long_lds(LOGE));
@@ -1167,10 +1196,11 @@ hipError_t launch_rfft_half(const float* in, size_t n, int logL, size_t C, void*
     float2* md = static_cast<float2*>(mid);
     const int logN1 = (logM + 1) / 2, logN2 = logM / 2;
     hipError_t e;
-    // A first-pass sum of N1 terms is about sqrt(N2) times smaller than a spectrum value, an unnormalised inverse
-    // second-pass sum about sqrt(N2) times larger: the stored intermediate is lifted (lowered) by 2^(logN2 / 2) so
-    // that it sits where the caller's scale put the spectrum.  Powers of two: exact.
-    const float lift = std::ldexp(1.0f, logN2 / 2);
+    const float lift = half_lift(logM);
+    if (short_forward(logM, C)) {
+        *pair_log = logN1;
+        return launch_short_rfft_half(in, n, logM, C, sp, sstride, md, t, hist, zero_ptr, (uint32_t)zero_words, in_scale * lift, 1.0f / lift, s);
+    }
 #define FWD_A(p) \
     fwd_a<p, true>(in, n, logM, C, md, t, aligned, zero_ptr, (uint32_t)zero_words, in_scale * lift, s)
     switch (logN1) {
@@ -1199,31 +1229,22 @@ hipError_t launch_irfft_half(const void* spec, uint32_t sstride, size_t n, int l
     const int logM = logL - 1;
     if (logM < 14) return hipErrorInvalidValue;
     if (C * ((size_t)1 << (logM - 13)) > 0x7fffffffu) return hipErrorInvalidValue;
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     const float2* sp = static_cast<const float2*>(spec);
     float2* md = static_cast<float2*>(mid);
-    const int logN1 = (logM + 1) / 2, logN2 = logM / 2;
+    const float lower = 1.0f / half_lift(logM);
     hipError_t e;
-    const float lift = std::ldexp(1.0f, logN2 / 2);  // see launch_rfft_half
-    switch (logN2) {
-        case 7: e = inv_b<7, true, true>(sp, sstride, logM, C, md, t, 1.0f / lift, s); break;
-        case 8: e = inv_b<8, true, true>(sp, sstride, logM, C, md, t, 1.0f / lift, s); break;
-        case 9: e = inv_b<9, true, true>(sp, sstride, logM, C, md, t, 1.0f / lift, s); break;
-        case 10: e = inv_b<10, true, true>(sp, sstride, logM, C, md, t, 1.0f / lift, s); break;
-        default: return hipErrorInvalidValue;
+    if (short_inverse(logM, C)) {
+        e = launch_short_inverse_b_half(sp, sstride, logM, C, md, t, lower, s);
+    } else {
+        switch (logM / 2) {
+            case 7: e = inv_b<7, true, true>(sp, sstride, logM, C, md, t, lower, s); break;
+            case 8: e = inv_b<8, true, true>(sp, sstride, logM, C, md, t, lower, s); break;
+            case 9: e = inv_b<9, true, true>(sp, sstride, logM, C, md, t, lower, s); break;
+            case 10: e = inv_b<10, true, true>(sp, sstride, logM, C, md, t, lower, s); break;
+            default: return hipErrorInvalidValue;
+        }
     }
-    if (e != hipSuccess) return e;
-#define INV_A(p) inv_a<p, true>(md, logM, C, out, n, t, aligned, gain * lift, s)
-    switch (logN1) {
-        case 7: return INV_A(7);
-        case 8: return INV_A(8);
-        case 9: return INV_A(9);
-        case 10: return INV_A(10);
-        case 11: return INV_A(11);
-        default: return hipErrorInvalidValue;
-    }
-#undef INV_A
+    return e == hipSuccess ? launch_inverse_a(md, logM, C, out, n, t, gain, 1, s) : e;
 }
 
 }  // namespace fftsp

@@ -149,36 +149,42 @@ __host__ __device__ constexpr int stage_radix_log(int rem)
 
 // One Stockham stage of radix 2^RL on T = 2^LOGT interleaved R-point transforms.
 // NS = product of the radices already applied.  tw[e] = exp(-2 pi i e / R).
+// With fewer butterflies than lanes the last lanes have none.
 template <int LOGR, int LOGT, int NT, bool INV, int NS_LOG, int RL>
 __device__ __forceinline__ void fft_stage(float2* d, const float2* tw, int tid)
 {
     constexpr int R = 1 << LOGR, T = 1 << LOGT, RHO = 1 << RL, NS = 1 << NS_LOG;
     constexpr int NBF = (R / RHO) * T;
-    static_assert(NBF % NT == 0, "butterflies must divide evenly over the workgroup");
-    constexpr int PER = NBF / NT;
+    static_assert(NBF % NT == 0 || (NBF < NT && NBF % 64 == 0), "butterflies must divide evenly over the workgroup, or over some of its waves");
+    constexpr int PER = NBF < NT ? 1 : NBF / NT;
+    const bool on = NBF >= NT || tid < NBF;
     float2 v[PER][RHO];
+    if (on) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int w = tid + q * NT, b = w & (T - 1), j = w >> LOGT;
+        for (int q = 0; q < PER; ++q) {
+            const int w = tid + q * NT, b = w & (T - 1), j = w >> LOGT;
 #pragma unroll
-        for (int t = 0; t < RHO; ++t) v[q][t] = d[sw_idx<LOGT>(j + t * (R / RHO), b)];
+            for (int t = 0; t < RHO; ++t) v[q][t] = d[sw_idx<LOGT>(j + t * (R / RHO), b)];
+        }
     }
     __syncthreads();
+    if (on) {
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int w = tid + q * NT, b = w & (T - 1), j = w >> LOGT;
-        const int k = j & (NS - 1);
-        if constexpr (NS > 1) {
+        for (int q = 0; q < PER; ++q) {
+            const int w = tid + q * NT, b = w & (T - 1), j = w >> LOGT;
+            const int k = j & (NS - 1);
+            if constexpr (NS > 1) {
 #pragma unroll
-            for (int t = 1; t < RHO; ++t) {
-                const float2 c = tw[(t * k) << (LOGR - NS_LOG - RL)];
-                v[q][t] = INV ? cmulc(v[q][t], c) : cmul(v[q][t], c);
+                for (int t = 1; t < RHO; ++t) {
+                    const float2 c = tw[(t * k) << (LOGR - NS_LOG - RL)];
+                    v[q][t] = INV ? cmulc(v[q][t], c) : cmul(v[q][t], c);
+                }
             }
-        }
-        butterfly<RL, INV>(v[q]);
-        const int base = ((j >> NS_LOG) << (NS_LOG + RL)) + k;
+            butterfly<RL, INV>(v[q]);
+            const int base = ((j >> NS_LOG) << (NS_LOG + RL)) + k;
 #pragma unroll
-        for (int t = 0; t < RHO; ++t) d[sw_idx<LOGT>(base + t * NS, b)] = v[q][t];
+            for (int t = 0; t < RHO; ++t) d[sw_idx<LOGT>(base + t * NS, b)] = v[q][t];
+        }
     }
     __syncthreads();
 }

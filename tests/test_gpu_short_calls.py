@@ -1,4 +1,6 @@
-"""Short calls of two-pass chunk lengths: the sender's last kernel finds the threshold (csrc/codec.hip)."""
+"""Short calls of two-pass chunk lengths go through kernels of their own (csrc/short.hip): small tiles, the sender's last
+kernel finding the threshold.  What they compute is what the long calls' kernels compute, bit
+for bit."""
 import numpy as np
 import pytest
 
@@ -10,6 +12,37 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(scope="module")
 def dev():
     return Device()
+
+
+@pytest.mark.parametrize("logL", (16, 17, 18, 19, 20, 21))
+@pytest.mark.parametrize("chunks, tail", ((1, 1), (1, 40003), (2, 6), (3, 65534)))
+def test_ragged_short_call_and_the_same_chunks_in_a_long_one(dev, logL, chunks, tail):
+    """the last chunk ends in it, after an odd or an even number of samples; the long call holds the zeros that follow"""
+    torch, f, L, theta, bits = dev.torch, dev.f, 1 << logL, 0.4, 9
+    n, many = (chunks - 1) * L + tail, chunks + (1 << 23) // L + 1
+    gen = torch.Generator(device="cuda").manual_seed(logL * 8 + chunks)
+    long = torch.randn(many * L, device="cuda", generator=gen) * 1e-3
+    long[n:chunks * L] = 0.0
+
+    def all_of(x, count):
+        ws, c = dev.ws_for(count, L, bits), -(-count // L)
+        spec, out, hout, back = torch.empty(c * (L + 2), device="cuda"), torch.empty_like(x), torch.empty_like(x), torch.empty_like(x)
+        f.rfft(x, L, spec, ws)
+        f.irfft(spec, count, L, back, ws)
+        packed = torch.empty(f.packed_bytes(count, L, theta, bits), dtype=torch.uint8, device="cuda")
+        half = torch.empty_like(packed)
+        f.compress(x, L, theta, bits, packed, ws)
+        f.decompress(packed, packed.numel(), out, L, theta, bits, ws)
+        f.compress_h(x, L, theta, bits, 8, half, ws)
+        f.decompress_h(half, half.numel(), hout, L, theta, bits, 8, ws)
+        assert f.device_status(ws) == 0
+        return (spec.view(torch.int32).view(c, -1), packed[64:].view(c, -1), half[64:].view(c, -1), back.view(torch.int32),
+                out.view(torch.int32), hout.view(torch.int32))
+
+    short, want = all_of(long[:n].clone(), n), all_of(long, many * L)
+    for i, (what, a, b) in enumerate(zip(("spectra", "records", "half records", "inverse", "samples", "half samples"), short, want)):
+        print(f"L=2^{logL} n={n}: {what}", flush=True)
+        assert torch.equal(a, b[:chunks if i < 3 else n])
 
 
 @pytest.mark.parametrize("chunks", (1, 12))
