@@ -2,6 +2,7 @@
 #include "../../include/fftsp.h"
 #include "chunk.h"
 #include "internal.h"
+#include "short.h"
 #include "twiddle_table.h"
 
 #include <algorithm>
@@ -235,6 +236,18 @@ hipError_t decode_stream(const Plan& p, const uint8_t* in, const CodecArgs& a, f
     if (p.C > 0xffffffffu) return hipErrorInvalidValue;
     const StatusNote note = status_note(p.C, p.ws.tscan);
     return launch_decode(in, in + kStreamHeader, a, units, ws, p.ws, 1, reinterpret_cast<uint32_t*>(ws + p.ws.tscan), &note, s);
+}
+
+// The same without a spectrum, transform included, where the call is short enough (short.h).
+bool decompress_without_spectrum(const Plan& p, const uint8_t* in, const CodecArgs& a, float* out, float gain, uint8_t* ws, Tables t,
+                                 hipStream_t s, hipError_t* e)
+{
+    if (!short_decode(p.logL - 1, p.C)) return false;
+    float2* mid = reinterpret_cast<float2*>(ws + p.ws.mid);
+    *e = launch_short_decode(in, a, p.logL - 1, mid, t, reinterpret_cast<uint32_t*>(ws + p.ws.tscan),
+                             reinterpret_cast<uint32_t*>(ws + p.ws.status), status_note(p.C, p.ws.tscan), s);
+    if (*e == hipSuccess) *e = launch_inverse_a(mid, p.logL - 1, p.C, out, p.n, t, gain, a.half, s);
+    return true;
 }
 
 // The receiver for chunks that fit one workgroup; its per-record verdicts go to the workspace at byte offset `verd`.
@@ -521,7 +534,9 @@ int fftsp_decompress_q(const void* d_packed, size_t packed_bytes, float* d_grad_
     }
     a.sstride = padded_bins(p.L);
     a.pair_log = fft_pair_log(p.logL);
-    hipError_t e = decode_stream(p, in, a, spec, ws, s);
+    hipError_t e;
+    if (decompress_without_spectrum(p, in, a, d_grad_out, 1.0f, ws, t, s, &e)) return hip_status(e);
+    e = decode_stream(p, in, a, spec, ws, s);
     if (e == hipSuccess) e = inverse_of_decoded(p, spec, a.sstride, a.pair_log, d_grad_out, ws, t, 1.0f, s);
     return hip_status(e);
 }
@@ -665,10 +680,11 @@ int fftsp_decompress_h(const void* d_packed, size_t packed_bytes, float* d_grad_
     a.pair_log = fft_pair_log(p.logL);
     a.half = 1;
     a.hdr_scale = scale_log2;
-    hipError_t e = decode_stream(p, in, a, reinterpret_cast<float*>(ws + p.ws.spec), ws, s);
-    if (e == hipSuccess)
-        e = launch_irfft_half(ws + p.ws.spec, a.sstride, n, p.logL, p.C, d_grad_out, ws + p.ws.mid, t,
-                              std::ldexp(1.0f, -scale_log2), s);
+    const float gain = std::ldexp(1.0f, -scale_log2);
+    hipError_t e;
+    if (decompress_without_spectrum(p, in, a, d_grad_out, gain, ws, t, s, &e)) return hip_status(e);
+    e = decode_stream(p, in, a, reinterpret_cast<float*>(ws + p.ws.spec), ws, s);
+    if (e == hipSuccess) e = launch_irfft_half(ws + p.ws.spec, a.sstride, n, p.logL, p.C, d_grad_out, ws + p.ws.mid, t, gain, s);
     return hip_status(e);
 }
 
@@ -1073,9 +1089,15 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
                 const bool leads = i == 0 && plan.shorts.empty();
                 const CodecArgs a = segment_args(b, seg_offsets, nseg, theta, bits, m);
                 float* spec = reinterpret_cast<float*>(ws + w.spec);
-                pe = launch_decode(in, in + kStreamHeader, a, spec, ws, w, leads, verdicts + done, leads ? &note : nullptr, st);
-                if (pe == hipSuccess)
-                    pe = launch_irfft_long(reinterpret_cast<float2*>(spec), b, d_grad_out, reinterpret_cast<float2*>(ws + w.mid), t, st);
+                float2* mid = reinterpret_cast<float2*>(ws + w.mid);
+                if (short_decode(b)) {
+                    pe = launch_short_decode_long(in, a, mid, t, leads, verdicts + done, reinterpret_cast<uint32_t*>(ws + w.status),
+                                                  leads ? &note : nullptr, st);
+                    if (pe == hipSuccess) pe = launch_inverse_a_long(mid, b, d_grad_out, t, st);
+                } else {
+                    pe = launch_decode(in, in + kStreamHeader, a, spec, ws, w, leads, verdicts + done, leads ? &note : nullptr, st);
+                    if (pe == hipSuccess) pe = launch_irfft_long(reinterpret_cast<float2*>(spec), b, d_grad_out, mid, t, st);
+                }
                 done += b.count;
             }
             return pe;

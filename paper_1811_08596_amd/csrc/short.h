@@ -26,4 +26,13 @@ hipError_t launch_short_inverse_b_long(const float2* spec, const LongBatch& b, f
 hipError_t launch_short_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, hipStream_t s);
 hipError_t launch_short_inverse_a_long(const LongBatch& b, float* out, const float2* mid, Tables t, hipStream_t s);
 
+// The inverse pass B with the bins taken from the records: no launch that decodes, and no spectrum.
+// verdicts, ctl, note: as launch_decode.
+bool short_decode(int logM, size_t C);
+bool short_decode(const LongBatch& b);
+hipError_t launch_short_decode(const uint8_t* stream, const CodecArgs& a, int logM, float2* mid, Tables t, uint32_t* verdicts,
+                               uint32_t* ctl, const StatusNote& note, hipStream_t s);
+hipError_t launch_short_decode_long(const uint8_t* stream, const CodecArgs& a, float2* mid, Tables t, int check_header,
+                                    uint32_t* verdicts, uint32_t* ctl, const StatusNote* first, hipStream_t s);
+
 }  // namespace fftsp

@@ -270,6 +270,106 @@ struct SpectrumBins {
         for (int q = 0; q < 8; ++q) x[q] = cx_load(raw[q]);
     }
 };
+// Record: the codes of the bins themselves, so that there is no launch that decodes before this one, and no spectrum.  Every
+// workgroup counts the chunk's bitmap into a table of its words and the set bits before them (in the LDS that the transform
+// will use), and a lane picks the codes of its bins out of memory.
+struct RecordArgs {
+    uint32_t k, W, S, word3;
+    int bits, m;
+};
+template <bool HALF>
+struct RecordBins {
+    const uint8_t* record;
+    const uint8_t* stream;
+    RecordArgs a;
+    uint32_t* verdict;  // not null: this workgroup leaves the record's verdict
+    bool first;         // the record is its stream's first
+    const HeaderInfo& hdr;
+    // entry i of the table; one in nine is left out so that lanes eight entries apart use different banks
+    static __device__ __forceinline__ uint32_t place_of(uint32_t i) { return i + (i >> 3); }
+    template <int LOGN2>
+    __device__ __forceinline__ void load(float2 (&x)[8], float2& last, uint32_t, uint32_t k, int kq0, int logM, float2* lds, int tid) const
+    {
+        constexpr int NT = 1 << LOGN2, DK = NT / 8, QUADS = 8;  // N1 is 1024 at most
+        __shared__ uint32_t before[NT / 64];
+        uint2* table = reinterpret_cast<uint2*>(lds);
+        const uint32_t* rec = reinterpret_cast<const uint32_t*>(record);
+        const int logN1 = logM - LOGN2, quads = 1 << (logN1 - 7);  // a lane's words, in fours
+        const uint4* words = reinterpret_cast<const uint4*>(rec + 4) + (uint32_t)tid * (uint32_t)quads;
+        uint4 w[QUADS];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i) w[i] = i < quads ? words[i] : make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t end = rec[4 + (1u << (logM - 5))] & 1u;  // the Nyquist bin has the last word to itself
+        const uint32_t pbase = rec[0];
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i) sum += (uint32_t)(__popc(w[i].x) + __popc(w[i].y) + __popc(w[i].z) + __popc(w[i].w));
+        const uint32_t incl = wave_scan_incl(sum);
+        if ((tid & 63) == 63) before[tid >> 6] = incl;
+        __syncthreads();
+        uint32_t run = incl - sum, all = 0;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) {
+            run += i < (tid >> 6) ? before[i] : 0u;
+            all += before[i];
+        }
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i) {
+            if (i >= quads) break;
+            const uint32_t at = 4u * ((uint32_t)tid * (uint32_t)quads + (uint32_t)i), v[4] = {w[i].x, w[i].y, w[i].z, w[i].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                table[place_of(at + (uint32_t)j)] = make_uint2(v[j], run);
+                run += (uint32_t)__popc(v[j]);
+            }
+        }
+        if (verdict && tid == 0) *verdict = record_verdict(record, stream, first, all + (uint32_t)__popc(rec[4 + (1u << (logM - 5))]), a.k, a.word3, hdr);
+        __syncthreads();
+        const uint32_t* codes = rec + 4 + a.W;
+        const uint32_t final = a.S / 4u - 5u - a.W;  // last code word (a record has one, if only padding: see fetch)
+        const uint32_t width = 2u * (uint32_t)a.bits;
+        const uint32_t base = (pbase - 1u) << (23 - a.m);
+        uint32_t rank[9], c0[9], c1[9];
+        bool on[9];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t bin = k + ((uint32_t)(kq0 + q * DK) << logN1);
+            const uint2 e = table[place_of(bin >> 5)];
+            on[q] = (e.x >> (bin & 31u)) & 1u;
+            rank[q] = e.y + (uint32_t)__popc(e.x & ((1u << (bin & 31u)) - 1u));
+        }
+        on[8] = end != 0;
+        rank[8] = all;
+        // a record without kept bins has no code words; a corrupt bitmap's ranks must not point outside the record
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            const uint64_t bit = (uint64_t)width * rank[q];
+            const uint32_t i = on[q] && a.k ? (uint32_t)(bit >> 5 < final ? bit >> 5 : final) : 0u;
+            const uint32_t* p = a.k ? codes : rec;
+            c0[q] = p[i];
+            c1[q] = p[i < final && a.k ? i + 1u : i];
+        }
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            uint32_t re, im;
+            if (a.bits == 32) {
+                re = on[q] ? c0[q] : 0u;
+                im = on[q] ? c1[q] : 0u;
+            } else {
+                const uint32_t raw = on[q] ? __builtin_amdgcn_alignbit(c1[q], c0[q], width * rank[q]) : 0u;
+                re = dequantize_field(raw, 0u, (uint32_t)a.bits, base, 23 - a.m);
+                im = dequantize_field(raw, (uint32_t)a.bits, (uint32_t)a.bits, base, 23 - a.m);
+            }
+            const float2 z = cx_load(cx_store<HALF>(make_float2(__uint_as_float(re), __uint_as_float(im))));
+            if (q < 8)
+                x[q] = z;
+            else
+                last = z;
+        }
+        __syncthreads();
+    }
+};
+
 template <int LOGN2, bool HALF, typename Bins>
 __device__ __forceinline__ void inv_b_short(uint32_t tile, const Bins& bins, int logM, typename Cx<HALF>::One* __restrict__ mid,
                                             const Tables& tb, float mid_scale)
@@ -375,6 +475,18 @@ __global__ __launch_bounds__(1 << LOGN2) void k_inv_b_short(const typename Cx<HA
     inv_b_short<LOGN2, HALF>(blockIdx.x & ((1u << log_tiles) - 1u), SpectrumBins<PAIR, HALF>{spec + c * (size_t)sstride}, logM,
                              mid + ((size_t)c << logM), tb, mid_scale);
 }
+template <int LOGN2, bool HALF>
+__global__ __launch_bounds__(1 << LOGN2) void k_decode_inv_b(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ records,
+                                                             RecordArgs a, HeaderInfo hdr, uint32_t* __restrict__ verdicts,
+                                                             uint32_t* __restrict__ ctl, StatusNote note, int logM,
+                                                             typename Cx<HALF>::One* __restrict__ mid, Tables tb, float mid_scale)
+{
+    const int log_tiles = logM - LOGN2 - kShortLogSlots;
+    const uint32_t c = blockIdx.x >> log_tiles, tile = blockIdx.x & ((1u << log_tiles) - 1u);
+    if (blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, 1 << LOGN2);
+    const RecordBins<HALF> bins{records + (size_t)c * a.S, stream, a, tile == 0 ? verdicts + c : nullptr, c == 0, hdr};
+    inv_b_short<LOGN2, HALF>(tile, bins, logM, mid + ((size_t)c << logM), tb, mid_scale);
+}
 
 // tensors of a LongTable, every workgroup looking up the one it belongs to
 constexpr int short_columns(int logM) { return (logM + 1) / 2; }
@@ -456,6 +568,31 @@ __global__ __launch_bounds__(1 << TOP) void k_inv_b_long_short(const float2* __r
         if (rows == 10) return run(std::integral_constant<int, 10>{});
 }
 
+template <int TOP>
+__global__ __launch_bounds__(1 << TOP) void k_decode_inv_b_long(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ records,
+                                                                int bits, int m, HeaderInfo hdr, uint32_t* __restrict__ verdicts,
+                                                                uint32_t* __restrict__ ctl, StatusNote note,
+                                                                float2* __restrict__ mid, Tables tb, LongTable tab, LongStarts at)
+{
+    if (ctl && blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, 1 << TOP);
+    const LongShare share = long_share(at);
+    const LongTensor& x = tab.t[share.tensor];
+    const RecordArgs a{x.kept, (1u << x.logM) / 32u + 1u, x.stride, 2u << x.logM, bits, m};
+    const RecordBins<false> bins{records + x.roff, stream, a, share.blk == 0 ? verdicts + share.tensor : nullptr, share.tensor == 0, hdr};
+    auto run = [&](auto n2) __attribute__((always_inline)) {
+        constexpr int LOGN2 = decltype(n2)::value;
+        if (threadIdx.x < (1u << LOGN2)) inv_b_short<LOGN2, false>(share.blk, bins, x.logM, mid + long_mid(x), tb, 1.0f);
+    };
+    const int rows = short_rows(x.logM);
+    if (rows == 7) return run(std::integral_constant<int, 7>{});
+    if constexpr (TOP >= 8)
+        if (rows == 8) return run(std::integral_constant<int, 8>{});
+    if constexpr (TOP >= 9)
+        if (rows == 9) return run(std::integral_constant<int, 9>{});
+    if constexpr (TOP >= 10)
+        if (rows == 10) return run(std::integral_constant<int, 10>{});
+}
+
 // ------------------------------------------------------------------ launch ----
 template <typename K>
 hipError_t short_lds(K kernel, size_t bytes)
@@ -510,6 +647,27 @@ hipError_t launch_b_inv(const float2* spec, uint32_t sstride, int logM, size_t C
     return hipGetLastError();
 }
 
+// LDS of the inverse pass B from records: the table of bitmap words (RecordBins), or the tile and its twiddles
+constexpr size_t lds_decode(int logM, int logn2)
+{
+    const size_t words = (size_t)1 << (logM - 5), table = (words + words / 8) * sizeof(uint2);
+    return table > lds_b(logn2, false) ? table : lds_b(logn2, false);
+}
+constexpr int kDecodeMost = 18;  // log2 of the longest half chunk whose table is built in every workgroup
+
+template <int LOGN2, bool HALF>
+hipError_t launch_b_decode(const uint8_t* stream, const CodecArgs& a, int logM, float2* mid, Tables t, const HeaderInfo& hdr,
+                           uint32_t* verdicts, uint32_t* ctl, const StatusNote& note, float mid_scale, hipStream_t s)
+{
+    auto kern = k_decode_inv_b<LOGN2, HALF>;
+    const hipError_t e = short_lds(kern, lds_decode(2 * LOGN2 + 1 < kDecodeMost ? 2 * LOGN2 + 1 : kDecodeMost, LOGN2));
+    if (e != hipSuccess) return e;
+    const RecordArgs r{a.k, (1u << logM) / 32u + 1u, (uint32_t)a.S, a.word3, a.bits, a.m};
+    FFTSP_LAUNCH("irfft_pass_b", kern, dim3((unsigned)(a.C << (logM - LOGN2 - kShortLogSlots))), dim3(1 << LOGN2), lds_decode(logM, LOGN2), s,
+                 stream, stream + 64, r, hdr, verdicts, ctl, note, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, mid_scale);
+    return hipGetLastError();
+}
+
 template <bool CODEC, bool HALF>
 hipError_t rfft_short(const float* in, size_t n, int logM, size_t C, float2* spec, uint32_t sstride, float2* mid, Tables t, int aligned,
                       uint32_t* hist, uint32_t* zero_ptr, uint32_t zero_words, float in_scale, float mid_scale, hipStream_t s)
@@ -561,6 +719,20 @@ hipError_t inv_b_any(const float2* spec, uint32_t sstride, int logM, size_t C, f
     }
 #undef INV_B
 }
+template <bool HALF>
+hipError_t decode_b_any(const uint8_t* stream, const CodecArgs& a, int logM, float2* mid, Tables t, float mid_scale, uint32_t* verdicts,
+                        uint32_t* ctl, const StatusNote& note, hipStream_t s)
+{
+    const HeaderInfo hdr{1, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, (uint32_t)a.hdr_scale};
+#define DECODE_B(p) launch_b_decode<p, HALF>(stream, a, logM, mid, t, hdr, verdicts, ctl, note, mid_scale, s)
+    switch (short_rows(logM)) {
+        case 7: return DECODE_B(7);
+        case 8: return DECODE_B(8);
+        case 9: return DECODE_B(9);
+        default: return hipErrorInvalidValue;
+    }
+#undef DECODE_B
+}
 // workgroups of every tensor's share: 2^log(logM) each
 template <typename Log>
 uint32_t starts_of(const LongBatch& b, LongStarts* at, Log&& log)
@@ -584,6 +756,10 @@ uint32_t starts_of(const LongBatch& b, LongStarts* at, Log&& log)
 //     512 82.9 / 96.2
 //   receiver, transform alone: 2^20 64 24.3 / 20.1, 256 35.9 / 33.8, 384 44.7 / 41.6, 512 51.5 / 51.5;  2^21 128 34.1 / 31.4, 384 51.9 / 53.0
 constexpr size_t kShortForward = 192, kShortInverse = 320;
+// The inverse pass B from records (decode, with a launch that counts the bitmaps where there is one, and pass B / this one), in whole
+// receivers: 2^16 16 17.9 / 11.0, 128 23.1 / 15.2, 512 43.0 / 37.6, 1024 68.6 / 56.4;  2^17 512 45.0 / 37.9, 1024 71.3 / 55.9;  2^18 16
+// 20.2 / 11.6, 512 46.5 / 43.8, 724 63.8 / 60.2;  2^19 32 21.4 / 13.9, 512 48.9 / 46.6, 724 67.4 / 64.6.
+constexpr size_t kShortDecode = 512;
 constexpr int kShortMostLogM = 20;
 static size_t tiles_of(int logM, size_t C) { return C << (logM - 13); }
 static size_t tiles_of(const LongBatch& b) { return (size_t)b.units << (kLongUnitLog - 13); }
@@ -594,6 +770,9 @@ bool short_forward(int logM, size_t C) { return short_length(logM) && tiles_of(l
 bool short_forward(const LongBatch& b) { return short_length(longest(b)) && tiles_of(b) <= kShortForward; }
 bool short_inverse(int logM, size_t C) { return short_length(logM) && tiles_of(logM, C) <= kShortInverse; }
 bool short_inverse(const LongBatch& b) { return short_length(longest(b)) && tiles_of(b) <= kShortInverse; }
+bool short_decode(int logM, size_t C) { return logM >= 15 && logM <= kDecodeMost && tiles_of(logM, C) <= kShortDecode; }
+bool short_decode(const LongBatch& b) { return longest(b) <= kDecodeMost && tiles_of(b) <= kShortDecode; }
+
 hipError_t launch_short_rfft(const float* in, size_t n, int logM, size_t C, float2* spec, uint32_t sstride, float2* mid, Tables t,
                              uint32_t* hist, uint32_t* zero_ptr, uint32_t zero_words, hipStream_t s)
 {
@@ -620,6 +799,37 @@ hipError_t launch_short_rfft_half(const float* in, size_t n, int logM, size_t C,
 {
     return rfft_short<true, true>(in, n, logM, C, spec, sstride, mid, t, alignment(in), hist, zero_ptr, zero_words, in_scale, mid_scale, s);
 }
+hipError_t launch_short_decode(const uint8_t* stream, const CodecArgs& a, int logM, float2* mid, Tables t, uint32_t* verdicts,
+                               uint32_t* ctl, const StatusNote& note, hipStream_t s)
+{
+    if (!a.half) return decode_b_any<false>(stream, a, logM, mid, t, 1.0f, verdicts, ctl, note, s);
+    return decode_b_any<true>(stream, a, logM, mid, t, 1.0f / half_lift(logM), verdicts, ctl, note, s);
+}
+hipError_t launch_short_decode_long(const uint8_t* stream, const CodecArgs& a, float2* mid, Tables t, int check_header,
+                                    uint32_t* verdicts, uint32_t* ctl, const StatusNote* first, hipStream_t s)
+{
+    const LongBatch& b = *a.tab;
+    const HeaderInfo hdr{check_header, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
+    const StatusNote note = first ? *first : StatusNote{};
+    const int logM = longest(b);
+    LongStarts at;
+    const uint32_t wgs = starts_of(b, &at, [](int log) { return log - short_rows(log) - kShortLogSlots; });
+    auto pass_b = [&](auto top) {
+        constexpr int TOP = decltype(top)::value;
+        auto kern = k_decode_inv_b_long<TOP>;
+        const hipError_t e = short_lds(kern, lds_decode(2 * TOP + 1 < kDecodeMost ? 2 * TOP + 1 : kDecodeMost, TOP));
+        if (e != hipSuccess) return e;
+        FFTSP_LAUNCH("irfft_pass_b", kern, dim3(wgs), dim3(1 << TOP), lds_decode(logM, TOP), s, stream, stream + 64, a.bits, a.m, hdr,
+                     verdicts, first ? ctl : nullptr, note, mid, t, b.tab, at);
+        return hipGetLastError();
+    };
+    switch (short_rows(logM)) {
+        case 7: return pass_b(std::integral_constant<int, 7>{});
+        case 8: return pass_b(std::integral_constant<int, 8>{});
+        default: return pass_b(std::integral_constant<int, 9>{});
+    }
+}
+
 hipError_t launch_short_rfft_long(const float* in, const LongBatch& b, float2* spec, float2* mid, Tables t, uint32_t* hist,
                                   uint32_t* zero_ptr, uint32_t zero_words, hipStream_t s)
 {

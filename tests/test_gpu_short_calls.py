@@ -1,5 +1,5 @@
-"""Short calls of two-pass chunk lengths go through kernels of their own (csrc/short.hip): small tiles, the sender's last
-kernel finding the threshold.  What they compute is what the long calls' kernels compute, bit
+"""Short calls of two-pass chunk lengths go through kernels of their own (csrc/short.hip): small tiles, the receiver's first pass
+reading the records, the sender's last kernel finding the threshold.  What they compute is what the long calls' kernels compute, bit
 for bit."""
 import numpy as np
 import pytest
@@ -43,6 +43,31 @@ def test_ragged_short_call_and_the_same_chunks_in_a_long_one(dev, logL, chunks, 
     for i, (what, a, b) in enumerate(zip(("spectra", "records", "half records", "inverse", "samples", "half samples"), short, want)):
         print(f"L=2^{logL} n={n}: {what}", flush=True)
         assert torch.equal(a, b[:chunks if i < 3 else n])
+
+
+@pytest.mark.parametrize("bits", (3, 8, 9, 16, 32))
+@pytest.mark.parametrize("logL", (16, 17, 18, 19))
+def test_receiver_without_a_spectrum(dev, logL, bits):
+    """decompress takes the bins from the records; decode_spectrum and irfft go through a spectrum"""
+    torch, f, L = dev.torch, dev.f, 1 << logL
+    n = 2 * L - 4099
+    g = torch.randn(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(bits)) * 1e-2
+    ws = dev.ws_for(n, L, bits)
+    for theta in (1.0, 0.5, 0.003, 0.0):
+        print(f"L=2^{logL} bits={bits} theta={theta}", flush=True)
+        packed = torch.empty(f.packed_bytes(n, L, theta, bits), dtype=torch.uint8, device="cuda")
+        f.compress(g, L, theta, bits, packed, ws)
+        out, want, spec = torch.empty_like(g), torch.empty_like(g), torch.empty(2 * (L + 2), device="cuda")
+        f.decompress(packed, packed.numel(), out, L, theta, bits, ws)
+        assert f.device_status(ws) == 0
+        f.decode_spectrum(packed, packed.numel(), n, L, theta, bits, spec, ws)
+        f.irfft(spec, n, L, want, ws)
+        assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+        # a bitmap that claims every bin: reads stay inside the record, and the record is reported
+        if theta < 1.0:
+            packed[64 + 16:64 + 16 + L // 16] = 255
+            f.decompress(packed, packed.numel(), out, L, theta, bits, ws)
+            assert f.device_status(ws) != 0
 
 
 @pytest.mark.parametrize("chunks", (1, 12))
