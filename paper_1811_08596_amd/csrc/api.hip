@@ -2,6 +2,7 @@
 #include "../../include/fftsp.h"
 #include "chunk.h"
 #include "internal.h"
+#include "receive.h"
 #include "short.h"
 #include "twiddle_table.h"
 
@@ -238,15 +239,23 @@ hipError_t decode_stream(const Plan& p, const uint8_t* in, const CodecArgs& a, f
     return launch_decode(in, in + kStreamHeader, a, units, ws, p.ws, 1, reinterpret_cast<uint32_t*>(ws + p.ws.tscan), &note, s);
 }
 
-// The same without a spectrum, transform included, where the call is short enough (short.h).
-bool decompress_without_spectrum(const Plan& p, const uint8_t* in, const CodecArgs& a, float* out, float gain, uint8_t* ws, Tables t,
-                                 hipStream_t s, hipError_t* e)
+// The whole receiver of one stream without a spectrum, where there are kernels for it (short.h, receive.h); false: there are none.
+bool receive_without_spectrum(const Plan& p, const uint8_t* in, const CodecArgs& a, float* out, float gain, uint8_t* ws, size_t verd, Tables t,
+                              hipStream_t s, hipError_t* e)
 {
-    if (!short_decode(p.logL - 1, p.C)) return false;
+    const int logM = p.logL - 1;
+    const FusedKnobs knobs = fused_knobs();
+    if (p.C > 0xffffffffu || (knobs.enabled && fused_applies(p.logL, p.C))) return false;
+    uint32_t *ctl = reinterpret_cast<uint32_t*>(ws + p.ws.status), *verdicts = reinterpret_cast<uint32_t*>(ws + verd);
     float2* mid = reinterpret_cast<float2*>(ws + p.ws.mid);
-    *e = launch_short_decode(in, a, p.logL - 1, mid, t, reinterpret_cast<uint32_t*>(ws + p.ws.tscan),
-                             reinterpret_cast<uint32_t*>(ws + p.ws.status), status_note(p.C, p.ws.tscan), s);
-    if (*e == hipSuccess) *e = launch_inverse_a(mid, p.logL - 1, p.C, out, p.n, t, gain, a.half, s);
+    const StatusNote note = status_note(p.C, verd);
+    if (short_decode(logM, p.C))
+        *e = launch_short_decode(in, a, logM, mid, t, verdicts, ctl, note, s);
+    else if (receive_applies(logM, p.C, p.bits))
+        *e = launch_receive(in, a, logM, ws + p.ws.spec, mid, t, verdicts, ctl, note, s);
+    else
+        return false;
+    if (*e == hipSuccess) *e = launch_inverse_a(mid, logM, p.C, out, p.n, t, gain, a.half, s);
     return true;
 }
 
@@ -535,7 +544,7 @@ int fftsp_decompress_q(const void* d_packed, size_t packed_bytes, float* d_grad_
     a.sstride = padded_bins(p.L);
     a.pair_log = fft_pair_log(p.logL);
     hipError_t e;
-    if (decompress_without_spectrum(p, in, a, d_grad_out, 1.0f, ws, t, s, &e)) return hip_status(e);
+    if (receive_without_spectrum(p, in, a, d_grad_out, 1.0f, ws, p.ws.tscan, t, s, &e)) return hip_status(e);
     e = decode_stream(p, in, a, spec, ws, s);
     if (e == hipSuccess) e = inverse_of_decoded(p, spec, a.sstride, a.pair_log, d_grad_out, ws, t, 1.0f, s);
     return hip_status(e);
@@ -612,7 +621,10 @@ int fftsp_decompress_accumulate(const void* const* d_packed, int npeers, size_t 
         return hip_status(decompress_chunks(p, peers, npeers, 0, a, d_grad_out, scale, ws, pw.verd, t, s));
     a.sstride = padded_bins(p.L);
     a.pair_log = fft_pair_log(p.logL);
-    hipError_t e = launch_decode_peers(peers, npeers, a, spec, ws, p.ws, pw, s);
+    hipError_t e;
+    // a sum of one: adding to zero changes nothing, there are no negative zeros among decoded values
+    if (npeers == 1 && receive_without_spectrum(p, peers.p[0], a, d_grad_out, scale, ws, pw.verd, t, s, &e)) return hip_status(e);
+    e = launch_decode_peers(peers, npeers, a, spec, ws, p.ws, pw, s);
     if (e == hipSuccess) e = inverse_of_decoded(p, spec, a.sstride, a.pair_log, d_grad_out, ws, t, scale, s);
     return hip_status(e);
 }
@@ -682,7 +694,7 @@ int fftsp_decompress_h(const void* d_packed, size_t packed_bytes, float* d_grad_
     a.hdr_scale = scale_log2;
     const float gain = std::ldexp(1.0f, -scale_log2);
     hipError_t e;
-    if (decompress_without_spectrum(p, in, a, d_grad_out, gain, ws, t, s, &e)) return hip_status(e);
+    if (receive_without_spectrum(p, in, a, d_grad_out, gain, ws, p.ws.tscan, t, s, &e)) return hip_status(e);
     e = decode_stream(p, in, a, reinterpret_cast<float*>(ws + p.ws.spec), ws, s);
     if (e == hipSuccess) e = launch_irfft_half(ws + p.ws.spec, a.sstride, n, p.logL, p.C, d_grad_out, ws + p.ws.mid, t, gain, s);
     return hip_status(e);

@@ -1216,13 +1216,6 @@ __global__ __launch_bounds__(RT) void k_group_prefix_peers(PeerList streams, uin
     if (blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, RT);
 }
 
-// A word every lane reads: by a scalar load, from memory that this kernel does not write.
-template <typename T>
-__device__ __forceinline__ T scalar_load(const T* p)
-{
-    return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
-}
-
 // What a wave needs of one record to decode its 512 units (16 bitmap words, group g of the chunk).
 template <int NL>
 struct WaveCodes {

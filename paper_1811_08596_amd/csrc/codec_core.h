@@ -246,5 +246,12 @@ __device__ __forceinline__ void clear_control(uint32_t* __restrict__ ctl, const 
         ctl[i] = i >= kNoteWord && i < kNoteWord + kNoteWords ? note_word(note, i) : 0u;
 }
 
+// A word every lane reads: by a scalar load, from memory that this kernel does not write.
+template <typename T>
+__device__ __forceinline__ T scalar_load(const T* p)
+{
+    return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+
 }  // namespace
 }  // namespace fftsp

@@ -756,10 +756,9 @@ uint32_t starts_of(const LongBatch& b, LongStarts* at, Log&& log)
 //     512 82.9 / 96.2
 //   receiver, transform alone: 2^20 64 24.3 / 20.1, 256 35.9 / 33.8, 384 44.7 / 41.6, 512 51.5 / 51.5;  2^21 128 34.1 / 31.4, 384 51.9 / 53.0
 constexpr size_t kShortForward = 192, kShortInverse = 320;
-// The inverse pass B from records (decode, with a launch that counts the bitmaps where there is one, and pass B / this one), in whole
-// receivers: 2^16 16 17.9 / 11.0, 128 23.1 / 15.2, 512 43.0 / 37.6, 1024 68.6 / 56.4;  2^17 512 45.0 / 37.9, 1024 71.3 / 55.9;  2^18 16
-// 20.2 / 11.6, 512 46.5 / 43.8, 724 63.8 / 60.2;  2^19 32 21.4 / 13.9, 512 48.9 / 46.6, 724 67.4 / 64.6.
-constexpr size_t kShortDecode = 512;
+// The inverse pass B from records, against receive.hip's two kernels, in whole receivers: 2^16 128 15.0 / 18.2, 256 22.0 / 25.4, 362 29.8 /
+// 32.6, 512 40.3 / 37.4;  2^18 128 17.0 / 19.0, 256 25.9 / 27.3, 362 35.8 / 33.7;  2^19 128 17.6 / 23.2, 362 38.7 / 39.3, 512 47.6 / 41.9.
+constexpr size_t kShortDecode = 320;
 constexpr int kShortMostLogM = 20;
 static size_t tiles_of(int logM, size_t C) { return C << (logM - 13); }
 static size_t tiles_of(const LongBatch& b) { return (size_t)b.units << (kLongUnitLog - 13); }
