@@ -37,6 +37,18 @@ struct GroupScratch {
 };
 static_assert(sizeof(GroupScratch) % 16 == 0, "the LDS regions behind it stay aligned");
 
+// Coarse twiddles (steps of 1/2048 of a turn, or of 1/R for R < 2048) that the stages of an R-point transform look up: those
+// of the last part of the turn are never wanted, and what they would take decides how many workgroups a compute unit holds.
+constexpr int coarse_twiddles(int logr)
+{
+    int most = 0;
+    for (int ns = 0; ns < logr;) {
+        const int rl = stage_radix_log(logr - ns), at = ((1 << rl) - 1) * ((1 << ns) - 1) << (logr - ns - rl);
+        most = at > most ? at : most;
+        ns += rl;
+    }
+    return ((most >> (logr > 11 ? logr - 11 : 0)) + 2) & ~1;  // whole 16 bytes
+}
 template <int LOGM, int NTHREADS>
 struct Geo {
     static constexpr int M = 1 << LOGM;
@@ -52,13 +64,18 @@ struct Geo {
     static constexpr int LR = M < 64 ? M : 64;                 // bins of a row that exist
     static constexpr int HB = M <= 256 ? 0 : (M <= 2048 ? 11 : 12);  // first radix digit; 0: bisection
     static constexpr int WC = M >= 32 ? M / 32 : 1;            // bitmap words of a chunk without the Nyquist bin's
-    static constexpr int TABLE_WORDS = T * WC;
-    static constexpr int TW = LOGM <= 11 ? M : 2048 + (1 << (LOGM - 11));  // entries of the stage twiddle table
+    static constexpr int GROUP_WORDS = CPW * WC;                 // bitmap words of a group
+    static constexpr int TW = coarse_twiddles(LOGM) + (LOGM <= 11 ? 0 : 1 << (LOGM - 11));  // entries of the stage twiddle table
     // LDS bytes of a group: its complex values, later its histogram, candidate list and record image
     static constexpr int DATA = E / GROUPS * 8, REGION = DATA > (4 << HB) ? DATA : (4 << HB);
-    static constexpr int RECEIVER_FRONT_RAW = TABLE_WORDS * 8 + T * 8;  // bitmap words with their prefixes, Nyquist bins
     static constexpr int SCRATCH = GROUPS * (int)sizeof(GroupScratch) + 16;  // and the word the groups agree through
-    static constexpr int RECEIVER_FRONT = SCRATCH + (RECEIVER_FRONT_RAW + 15) / 16 * 16;
+    static constexpr int RECEIVER_FRONT = SCRATCH + (T * 8 + 15) / 16 * 16;  // and the Nyquist bins
+    // of a receiver's group: its record images and behind them the bitmap's words with their prefixes, later its complex values
+    __host__ __device__ static constexpr size_t receiver_region(size_t images)
+    {
+        const size_t need = (images + GROUP_WORDS * 8 + 15) / 16 * 16;
+        return need > (size_t)DATA ? need : (size_t)DATA;
+    }
     // record image of one chunk of up to 16-bit codes, in words; short chunks keep theirs beside the data
     static constexpr int IMAGE = HB ? 0 : ((16 + 4 * (M / 32 + 1) + 4 * (M + 1) + 16) / 4 + 3) & ~3;
 };
@@ -93,27 +110,34 @@ __device__ __forceinline__ constexpr int flat(int g) { return g ^ ((g >> 4) & 15
 __device__ __forceinline__ int flat_plus(int flat_g, int o) { return (flat_g ^ (flat(o) & 15)) + (o & ~15); }
 
 // ------------------------------------------------------------------- FFT ----
-// Stage twiddles exp(-2 pi i e / R): the whole table up to R = 2048; above it the 2048 coarse entries and the
-// R / 2048 fine ones behind them, multiplied where a stage needs the fine part (the last one).
+// Stage twiddles exp(-2 pi i e / R): what there are of R of them up to R = 2048; above it the coarse entries and the R / 2048
+// fine ones behind them, multiplied where a stage needs the fine part (the last one).
 template <int LOGR, int NT>
 __device__ __forceinline__ void load_chunk_twiddles(float2* tw, const Tables& tb, int tid)
 {
-    if constexpr (LOGR <= 11) {
-        for (int e = tid; e < (1 << LOGR); e += NT) tw[e] = tb.hi[e << (11 - LOGR)];
-    } else {
-        for (int e = tid; e < 2048; e += NT) tw[e] = tb.hi[e];
-        if (tid < (1 << (LOGR - 11))) tw[2048 + tid] = tb.lo[tid << (22 - LOGR)];
+    constexpr int COUNT = coarse_twiddles(LOGR), ITERS = (COUNT + NT - 1) / NT;
+    float2 v[ITERS];  // all loads before the first wait
+#pragma unroll
+    for (int i = 0; i < ITERS; ++i) {
+        const int e = tid + i * NT < COUNT ? tid + i * NT : 0;
+        v[i] = tb.hi[LOGR <= 11 ? e << (LOGR <= 11 ? 11 - LOGR : 0) : e];
     }
+    if constexpr (LOGR > 11)
+        if (tid < (1 << (LOGR - 11))) tw[COUNT + tid] = tb.lo[tid << (22 - LOGR)];
+#pragma unroll
+    for (int i = 0; i < ITERS; ++i)
+        if (tid + i * NT < COUNT) tw[tid + i * NT] = v[i];
 }
 template <int LOGR, int SHIFT>
 __device__ __forceinline__ float2 stage_twiddle(const float2* tw, int idx)
 {
+    constexpr int COARSE = coarse_twiddles(LOGR);
     if constexpr (LOGR <= 11)
         return tw[idx << SHIFT];
     else if constexpr (SHIFT >= LOGR - 11)
         return tw[idx << (SHIFT - (LOGR - 11))];
     else
-        return cmul(tw[idx >> (LOGR - 11 - SHIFT)], tw[2048 + ((idx << SHIFT) & ((1 << (LOGR - 11)) - 1))]);
+        return cmul(tw[idx >> (LOGR - 11 - SHIFT)], tw[COARSE + ((idx << SHIFT) & ((1 << (LOGR - 11)) - 1))]);
 }
 
 // Butterfly q of a lane: transform b, index j.  A wave's butterflies are consecutive, so its points are too.
@@ -849,8 +873,7 @@ __global__ __launch_bounds__(TopkGeo<LOGL>::NT) void k_topk_compress(const float
 
 // ---------------------------------------------------------------- receiver ----
 // Receiver of one workgroup; several peers' streams are summed bin by bin in list order.
-// region: LDS bytes of a group for its complex values or its record images, whichever is larger (single-wave groups run
-// without barriers, so no group may touch another's bytes).
+// region: LDS bytes of a group (receiver_region; single-wave groups run without barriers, so no group may touch another's bytes).
 template <int LOGM, int NT, typename Where>
 __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, uint32_t npeers, int plain, const Where& where,
                                                      const Tables& tb, const PackArgs& a, const HeaderInfo& hdr,
@@ -863,10 +886,10 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
     using B = Butterflies<LOGM, G::LOGE, NT, RL>;
     const int lane = tid & 63, group = tid / G::NL, tg = tid & (G::NL - 1), wig = tg >> 6;
     GroupScratch* gs = reinterpret_cast<GroupScratch*>(lds);
-    uint2* words = reinterpret_cast<uint2*>(lds + G::SCRATCH);
-    float2* nyquist = reinterpret_cast<float2*>(words + G::TABLE_WORDS);
+    float2* nyquist = reinterpret_cast<float2*>(lds + G::SCRATCH);
     uint8_t* regions = lds + G::RECEIVER_FRONT;
     uint8_t* images = regions + (size_t)group * region;
+    uint2* words = reinterpret_cast<uint2*>(images + region) - G::GROUP_WORDS;
     float2* tw = reinterpret_cast<float2*>(regions + (size_t)G::GROUPS * region);
     // the workgroup's point g lies at d[flat(g)]; a group's points are a multiple of 256, so its base moves freely
     float2* d = reinterpret_cast<float2*>(images) - group * (G::E / G::GROUPS);
@@ -912,8 +935,7 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
         group_sync<G::WAVES>();
         // bitmap words with the number of set bits before each; the total tells a corrupt record
         {
-            constexpr int WORDS = G::CPW * G::WC;  // of this group
-            const bool has = tg < WORDS;
+            const bool has = tg < G::GROUP_WORDS;
             const int i = has ? tg / G::WC : 0, wi = has ? tg % G::WC : 0, b = group * G::CPW + i;
             const bool live = where.exists(b);
             const uint32_t* rec = reinterpret_cast<const uint32_t*>(images + (uint32_t)i * image_stride);
@@ -940,7 +962,7 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
                 for (int w = 0; w < G::WC / 64 - 1; ++w) incl += w < wig ? gs[group].a[w] : 0u;
             }
             if (has) {
-                words[group * WORDS + tg] = make_uint2(word, incl - count);
+                words[tg] = make_uint2(word, incl - count);
                 if (wi == G::WC - 1) {  // this lane knows the chunk's total: the last bin and the verdict are its
                     const uint32_t total = incl;
                     float2 v = make_float2(0.f, 0.f);
@@ -965,7 +987,7 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
                 const int w = B::index(tid, q), j = B::j(w), b = B::b(w);
                 const uint8_t* image = images + (uint32_t)(b - group * G::CPW) * image_stride;
                 const uint32_t pbase = *reinterpret_cast<const uint32_t*>(image);
-                const uint2* row = words + b * G::WC;
+                const uint2* row = words + (b - group * G::CPW) * G::WC;
 #pragma unroll
                 for (int t = 0; t < B::RHO; ++t) {
                     const int i = j + t * B::STEP;
@@ -1049,9 +1071,10 @@ __global__ __launch_bounds__(NT) void k_chunk_decompress(PeerList streams, uint3
 }
 
 // LDS bytes of a receiver group in a per-tensor launch: one record image
-__host__ __device__ constexpr uint32_t tensor_region(uint32_t stride, uint32_t data)
+template <typename G>
+__host__ __device__ constexpr uint32_t tensor_region(uint32_t stride)
 {
-    return stride + 16u > data ? stride + 16u : data;
+    return (uint32_t)G::receiver_region(stride + 16u);
 }
 template <int LOGM>
 __device__ __forceinline__ void decompress_tensors(const PeerList& streams, const TensorTable& t, const TensorPiece& piece,
@@ -1062,7 +1085,7 @@ __device__ __forceinline__ void decompress_tensors(const PeerList& streams, cons
     using G = Geo<LOGM, NT>;
     if (tid >= NT) return;
     decompress_workgroup<LOGM, NT>(streams, 1u, 1, listed<G>(t, piece, aligned, tid), tb, a, hdr, out, 1.0f,
-                                   tensor_region(a.S, G::DATA), a.S + 16u, 0, verdicts, lds, tid);
+                                   tensor_region<G>(a.S), a.S + 16u, 0, verdicts, lds, tid);
 }
 
 template <int TOP>
@@ -1194,8 +1217,7 @@ template <int LOGM, int NT>
 constexpr size_t most_receiver_lds(size_t records)
 {
     using G = Geo<LOGM, NT>;
-    const size_t need = records * (longest_record(G::M) + 16), data = G::DATA;
-    return receiver_lds<LOGM, NT>(need > data ? need : data);
+    return receiver_lds<LOGM, NT>(G::receiver_region(records * (longest_record(G::M) + 16)));
 }
 // of a per-tensor launch whose longest tensor has 2^(LOGM+1) samples
 template <int LOGM>
@@ -1211,6 +1233,12 @@ constexpr size_t most_tensors_lds(bool sender)
 }
 constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit
 static_assert(most_tensors_lds<14>(true) <= kLdsBytes && most_tensors_lds<14>(false) <= kLdsBytes, "fits");
+// What leaving out the twiddles that no stage wants, and keeping a receiver's bitmap table where its data will be, is for: two
+// workgroups of 2^13 points to a compute unit and four senders of 2^10, where one and three fitted.  33 M
+// samples in chunks of 2^14: sender 129 -> 83 us, receiver 104 -> 68; of 2^11 72 -> 64 and 61 -> 54.  For 2^11 points the same four
+// waves a SIMD by way of 512 lanes and four chunks a workgroup gained and lost: sender 78 -> 83, receiver 52 -> 56 (26 M samples).
+static_assert(2 * sender_lds<13, 512>() <= kLdsBytes && 2 * receiver_lds<13, 512>(Geo<13, 512>::DATA) <= kLdsBytes, "two a compute unit");
+static_assert(4 * sender_lds<10, 256>() <= kLdsBytes && 4 * receiver_lds<10, 256>(Geo<10, 256>::DATA) <= kLdsBytes, "four a compute unit");
 
 template <int LOGM>
 hipError_t compress_as(const float* in, size_t n, const CodecArgs& a, uint8_t* stream, uint8_t* records, uint32_t* ctl,
@@ -1250,8 +1278,7 @@ hipError_t decompress_as(const PeerList& streams, int npeers, int plain, const C
     constexpr int NT = uniform_threads<LOGM>();
     using G = Geo<LOGM, NT>;
     const uint32_t stride = (uint32_t)a.S + 16u;  // slack: a code is fetched as two words
-    const size_t need = (size_t)G::CPW * stride, data = G::DATA;
-    const size_t region = need > data ? need : data;  // both are multiples of 16
+    const size_t region = G::receiver_region((size_t)G::CPW * stride);
     const size_t lds = receiver_lds<LOGM, NT>(region);
     auto kern = k_chunk_decompress<LOGM, NT>;
     const hipError_t e = allow_lds(kern, most_receiver_lds<LOGM, NT>(G::CPW));
@@ -1352,7 +1379,7 @@ static size_t tensors_lds(const TensorTable& t, uint32_t pieces, bool sender)
 #define X(p)                                                                                                                 \
     case p:                                                                                                                  \
         need = sender ? sender_lds<p, uniform_threads<p>()>()                                                                 \
-                      : receiver_lds<p, uniform_threads<p>()>(tensor_region(t.stride[p - 4], Geo<p, uniform_threads<p>()>::DATA)); \
+                      : receiver_lds<p, uniform_threads<p>()>(tensor_region<Geo<p, uniform_threads<p>()>>(t.stride[p - 4])); \
         break;
             FFTSP_CHUNK_SIZES(X)
 #undef X
