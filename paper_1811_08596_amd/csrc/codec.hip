@@ -1141,79 +1141,91 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
 // ---------------------------------------------------------------- decode ----
 constexpr int GROUP_WORDS = 16;  // one wave of the decode kernel covers 512 bins = 16 bitmap words
 
-// Per chunk: number of set bits before each group of 16 bitmap words (the prefix sum of Sec. 3.2's status
-// vector, kept at the granularity a wave needs); checks the headers and leaves the verdict in *verdict.
-__device__ __forceinline__ void group_prefix_chunk(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ record,
-                                                   bool first_of_stream, uint32_t W, uint32_t k, uint32_t word3,
-                                                   const HeaderInfo& hdr, uint32_t* __restrict__ gprefix,
-                                                   uint32_t* __restrict__ verdict)
+// Number of set bits before each group of 16 bitmap words of a record (the prefix sum of Sec. 3.2's status vector, kept at the
+// granularity a wave needs), for the part-th kPrefixWords words; the words before them are counted again, eight loads in flight.
+// The last part checks the headers and leaves the verdict in *verdict.  A workgroup per record took, us: sixty of 2^20 bins (Top-k)
+// 9.1 -> 7.6, ResNet-50's tensors 11.7 -> 7.7, eight peers' sixty of 2^19 15.6 -> 16.6.
+constexpr int kPrefixQuads = 4;  // four words each: what a lane has in flight
+constexpr uint32_t kPrefixWords = 4u * kPrefixQuads * RT;
+__device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ record,
+                                                  bool first_of_stream, uint32_t W, uint32_t k, uint32_t word3,
+                                                  const HeaderInfo& hdr, uint32_t part, uint32_t* __restrict__ gprefix,
+                                                  uint32_t* __restrict__ verdict)
 {
-    __shared__ uint32_t tmp[RW];
-    __shared__ uint32_t s_carry;
-    const int tid = threadIdx.x;
-    const uint32_t* rec = reinterpret_cast<const uint32_t*>(record);
-    const uint32_t* bitmap = rec + 4;
-    const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
-    if (tid == 0) s_carry = 0;
-    __syncthreads();
-    // set bits of one group of 16 words
-    auto group_count = [&](uint32_t g) {
-        uint32_t cnt = 0;
-        if (g < G) {
-            const uint32_t w0 = g * GROUP_WORDS;
-            if (w0 + GROUP_WORDS <= W) {
-                const uint4* p = reinterpret_cast<const uint4*>(bitmap + w0);  // records and bitmaps are 16-byte aligned
+    __shared__ uint32_t own[kPrefixQuads][RW], earlier[RW];
+    static_assert(GROUP_WORDS == 16, "a group is four lanes");
+    if (part * kPrefixWords >= W) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t* bitmap = reinterpret_cast<const uint32_t*>(record) + 4;
+    const uint4* quads = reinterpret_cast<const uint4*>(bitmap);  // records and bitmaps are 16-byte aligned
+    const uint32_t whole = W / 4u, from = part * kPrefixQuads * RT;
+    auto ones = [](uint4 v) __attribute__((always_inline)) { return (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w)); };
+    uint32_t before = 0;
+#pragma unroll 8
+    for (uint32_t i = 0; i < part * kPrefixQuads; ++i) before += ones(quads[i * RT + (uint32_t)tid]);
+    uint4 v[kPrefixQuads];
 #pragma unroll
-                for (int i = 0; i < GROUP_WORDS / 4; ++i) {
-                    const uint4 v = p[i];
-                    cnt += (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w));
-                }
-            } else {
-                for (uint32_t w = w0; w < W; ++w) cnt += (uint32_t)__popc(bitmap[w]);
-            }
-        }
-        return cnt;
-    };
-    // two adjacent groups per lane, so that the longest chunk (1025 groups) is one scan, not two
-    for (uint32_t base = 0; base < G; base += 2 * RT) {
-        const uint32_t g = base + 2 * (uint32_t)tid;
-        const uint32_t cnt0 = group_count(g), cnt1 = group_count(g + 1);
-        const uint32_t carry = s_carry;
-        const uint32_t incl = block_scan_incl<RW>(cnt0 + cnt1, tmp);
-        const uint32_t before = carry + incl - cnt0 - cnt1;
-        if (g < G) gprefix[g] = before;
-        if (g + 1 < G) gprefix[g + 1] = before + cnt0;
-        __syncthreads();
-        if (tid == RT - 1) s_carry = carry + incl;
-        __syncthreads();
+    for (int i = 0; i < kPrefixQuads; ++i) {
+        const uint32_t q = from + (uint32_t)(i * RT + tid);
+        v[i] = quads[q < whole ? q : 0u];
     }
-    if (tid == 0) *verdict = record_verdict(record, stream, first_of_stream, s_carry, k, word3, hdr);
+    uint32_t incl[kPrefixQuads], sum[kPrefixQuads];
+#pragma unroll
+    for (int i = 0; i < kPrefixQuads; ++i) {
+        const uint32_t q = from + (uint32_t)(i * RT + tid);
+        sum[i] = q < whole ? ones(v[i]) : 0u;
+        if (q == whole)
+            for (uint32_t w = 4u * q; w < W; ++w) sum[i] += (uint32_t)__popc(bitmap[w]);
+    }
+#pragma unroll
+    for (int i = 0; i < kPrefixQuads; ++i) {
+        incl[i] = wave_scan_incl(sum[i]);
+        if (lane == 63) own[i][wave] = incl[i];
+    }
+    before = wave_sum(before);
+    if (lane == 63) earlier[wave] = before;
+    __syncthreads();
+    uint32_t run = 0;
+#pragma unroll
+    for (int i = 0; i < RW; ++i) run += earlier[i];
+#pragma unroll
+    for (int i = 0; i < kPrefixQuads; ++i) {
+        uint32_t here = run + incl[i] - sum[i];
+#pragma unroll
+        for (int j = 0; j < RW; ++j) {
+            if (j < wave) here += own[i][j];
+            run += own[i][j];
+        }
+        const uint32_t q = from + (uint32_t)(i * RT + tid);
+        if ((q & 3u) == 0u && 4u * q < W) gprefix[q >> 2] = here;
+    }
+    if ((part + 1u) * kPrefixWords >= W && tid == 0) *verdict = record_verdict(record, stream, first_of_stream, run, k, word3, hdr);
 }
+inline uint32_t prefix_parts(uint32_t W) { return (W + kPrefixWords - 1u) / kPrefixWords; }
 
 template <bool TABLE>
 __global__ __launch_bounds__(RT) void k_group_prefix(const uint8_t* __restrict__ stream,
-                                                     const uint8_t* __restrict__ records, Shape u, HeaderInfo hdr,
+                                                     const uint8_t* __restrict__ records, Shape u, HeaderInfo hdr, uint32_t parts,
                                                      uint32_t* __restrict__ gprefix, uint32_t* __restrict__ verdicts,
                                                      uint32_t* __restrict__ ctl, StatusNote note, TableArg<TABLE> tab)
 {
-    const Place at = place_of<TABLE>(u, tab, blockIdx.x, 0u);
-    group_prefix_chunk(stream, records + at.record, blockIdx.x == 0, at.W, at.k, at.word3, hdr, gprefix + at.group0,
-                       verdicts + blockIdx.x);
     if (ctl && blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, RT);
+    const uint32_t c = blockIdx.x / parts;
+    const Place at = place_of<TABLE>(u, tab, c, 0u);
+    group_prefix_part(stream, records + at.record, c == 0, at.W, at.k, at.word3, hdr, blockIdx.x % parts, gprefix + at.group0, verdicts + c);
 }
 
-// The same for several peers' streams: workgroup (peer, chunk).
+// The same for several peers' streams.
 __global__ __launch_bounds__(RT) void k_group_prefix_peers(PeerList streams, uint32_t C, size_t S, uint32_t W, uint32_t k,
-                                                           HeaderInfo hdr, uint32_t* __restrict__ gprefix,
+                                                           HeaderInfo hdr, uint32_t parts, uint32_t* __restrict__ gprefix,
                                                            uint32_t* __restrict__ verdicts, uint32_t* __restrict__ ctl,
                                                            StatusNote note)
 {
-    const uint32_t peer = blockIdx.x / C, c = blockIdx.x % C;
+    if (blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, RT);
+    const uint32_t r = blockIdx.x / parts, peer = r / C, c = r % C;
     const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS;
     const uint8_t* stream = streams.p[peer];
-    group_prefix_chunk(stream, stream + 64 + (size_t)c * S, c == 0, W, k, 0u, hdr,
-                       gprefix + ((size_t)peer * C + c) * G, verdicts + (size_t)peer * C + c);
-    if (blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, RT);
+    group_prefix_part(stream, stream + 64 + (size_t)c * S, c == 0, W, k, 0u, hdr, blockIdx.x % parts, gprefix + (size_t)r * G, verdicts + r);
 }
 
 // What a wave needs of one record to decode its 512 units (16 bitmap words, group g of the chunk).
@@ -1704,12 +1716,13 @@ hipError_t launch_decode(const uint8_t* stream_base, const uint8_t* records, con
     uint32_t* gprefix = nullptr;
     if (!prefix_in_decode(x)) {
         gprefix = reinterpret_cast<uint32_t*>(ws_base + w.prefix);
+        const uint32_t parts = prefix_parts(x.most * (uint32_t)(kTile / 32));  // of the longest chunk
         if (a.tab)
-            FFTSP_LAUNCH("group_prefix", k_group_prefix<true>, dim3((unsigned)x.chunks), dim3(RT), 0, s, stream_base, records, u, h,
-                         gprefix, verdicts, ctl, note, table_arg<true>(a.tab));
+            FFTSP_LAUNCH("group_prefix", k_group_prefix<true>, dim3((unsigned)x.chunks * parts), dim3(RT), 0, s, stream_base, records, u, h,
+                         parts, gprefix, verdicts, ctl, note, table_arg<true>(a.tab));
         else
-            FFTSP_LAUNCH("group_prefix", k_group_prefix<false>, dim3((unsigned)x.chunks), dim3(RT), 0, s, stream_base, records, u, h,
-                         gprefix, verdicts, ctl, note, table_arg<false>(a.tab));
+            FFTSP_LAUNCH("group_prefix", k_group_prefix<false>, dim3((unsigned)x.chunks * parts), dim3(RT), 0, s, stream_base, records, u, h,
+                         parts, gprefix, verdicts, ctl, note, table_arg<false>(a.tab));
     }
     const bool vec = a.tab || (a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0);
 #define FFTSP_DECODE_AS(NL, TABLE, REAL, HALF, T)                                                                          \
@@ -1759,8 +1772,10 @@ hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecA
     const size_t count = a.C * (size_t)npeers;
     if (a.C * (size_t)u.Tn > 0x7fffffffu || count > 0x7fffffffu) return hipErrorInvalidValue;
     HeaderInfo h{1, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
-    FFTSP_LAUNCH("group_prefix", k_group_prefix_peers, dim3((unsigned)count), dim3(RT), 0, s, streams, (uint32_t)a.C, a.S, u.W,
-                 a.k, h, gprefix, verdicts, ctl, status_note(count, pw.verd));
+    const uint32_t parts = prefix_parts(u.W);
+    if (count * parts > 0x7fffffffu) return hipErrorInvalidValue;
+    FFTSP_LAUNCH("group_prefix", k_group_prefix_peers, dim3((unsigned)(count * parts)), dim3(RT), 0, s, streams, (uint32_t)a.C, a.S, u.W,
+                 a.k, h, parts, gprefix, verdicts, ctl, status_note(count, pw.verd));
     PeerList recs{};
     for (int i = 0; i < npeers; ++i) recs.p[i] = streams.p[i] + 64;  // records follow the 64-byte stream header
     const bool vec = a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0;
