@@ -1506,12 +1506,88 @@ __global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ strea
     }
 }
 
-// Several peers' streams (receiver under an allgather: Sec. 4, implementation): the same, the units summed over the
-// peers in list order in registers, starting from zero, and stored once.
-// Bound by instruction issue (two thirds of the vector slots).  Fetching the next peer's codes before unpacking this
-// one's changed nothing.  Measured, eight peers of 62 M samples, half of the bins kept as 8-bit codes: 354 -> 181 us.
+// Several peers' streams (receiver under an allgather: Sec. 4, implementation): the units summed over the peers in list order in
+// registers, starting from zero, and stored once.  Bound by instruction issue.
+//
+// Codes of up to 15 bits: a lane has eight neighbouring bins.  Their codes are neighbours in the record, so it fetches one window
+// and shifts them out of registers (Stretch): no LDS, and nothing scalar for each row of 64 bins.  While one peer's are
+// unpacked the next one's window and the byte of the bitmap after that are on their way.
+// Measured, eight peers of 62 M samples, half of the bins kept as 8-bit codes, against 64 neighbouring lanes a row and codes picked out
+// of LDS by rank (k_decode_peers_wide, still there for the widest codes): 178 -> 155 us.
+template <int WIDEST>
+__global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npeers, size_t S, uint32_t B, uint32_t W, int bits, int m,
+                                                     uint32_t Tn, size_t C, const uint32_t* __restrict__ gprefix, float2* __restrict__ spec,
+                                                     uint32_t sstride, bool vec, int pair_log)
+{
+    // sixteen slots and a gap, so that lanes sixteen slots apart use different banks
+    constexpr int GAP = 2;
+    __shared__ __align__(16) float2 stage[kTile + kTile / 16 * GAP];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const size_t c = blockIdx.x / Tn;
+    const uint32_t tile = blockIdx.x % Tn, tbase = tile * kTile, j0 = (uint32_t)tid * 8u;  // j0: this lane's first bin in the tile
+    const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS, g = tile * (kTile / 32 / GROUP_WORDS) + wave;
+    const uint32_t byte = (tbase + j0) >> 3, twoN = 2u * (uint32_t)bits;
+    const int shift = 23 - m, final = (int)(S / 4u) - 5 - (int)W;
+    const bool in = byte < 4u * W;
+    auto record_of = [&](uint32_t p) __attribute__((always_inline)) { return recs.p[p] + c * S; };
+    auto flags_of = [&](uint32_t p) __attribute__((always_inline)) { return (uint32_t)record_of(p)[16u + (in ? byte : 0u)]; };
+    auto run_of = [&](uint32_t p) __attribute__((always_inline)) { return scalar_load(gprefix + (p * C + c) * G + (g < G ? g : 0u)); };
+    auto window = [&](Stretch<8, WIDEST>& o, uint32_t p, uint32_t flags, uint32_t run) __attribute__((always_inline)) {
+        o.mask = in ? flags : 0u;
+        const uint32_t n = (uint32_t)__popc(o.mask);
+        o.fetch(reinterpret_cast<const uint32_t*>(record_of(p)) + 4 + W, final, (run + wave_scan_incl(n) - n) * twoN);
+    };
+    float2 acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = make_float2(0.f, 0.f);
+    Stretch<8, WIDEST> o;
+    uint32_t flags = flags_of(0u), run = run_of(0u);
+    window(o, 0u, flags, run);
+    if (npeers > 1u) {
+        flags = flags_of(1u);
+        run = run_of(1u);
+    }
+    for (uint32_t p = 0; p < npeers; ++p) {
+        Stretch<8, WIDEST> next = o;
+        if (p + 1u < npeers) {
+            window(next, p + 1u, flags, run);
+            const uint32_t after = p + 2u < npeers ? p + 2u : p + 1u;
+            flags = flags_of(after);
+            run = run_of(after);
+        }
+        const uint32_t base = (scalar_load(reinterpret_cast<const uint32_t*>(record_of(p))) - 1u) << shift;
+        o.unpack(twoN, (uint32_t)bits, shift, base, [&](int j, float2 z) __attribute__((always_inline)) {
+            acc[j] = make_float2(acc[j].x + z.x, acc[j].y + z.y);
+        });
+        o = next;
+    }
+    // a tile is whole runs, and eight bins lie in one half of one of them: upwards two slots apart, or downwards
+    auto gapped = [](uint32_t slot) __attribute__((always_inline)) { return slot + (slot >> 4) * GAP; };
+    const uint32_t N1 = 1u << pair_log, half = N1 / 2, k1 = j0 & (N1 - 1u), start = j0 - k1;
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) {
+        uint32_t slot = j0 + j;
+        if (pair_log) slot = start + (k1 < half ? 2u * (k1 + j) : (k1 + j == half ? 1u : 2u * (N1 - k1 - j) + 1u));
+        stage[gapped(slot)] = acc[j];
+    }
+    __syncthreads();
+    float2* X = spec + c * (size_t)sstride + tbase;
+    const uint32_t count = units_in_tile<false>(0, c, B, tbase);
+    if (vec) {
+        float4* dst = reinterpret_cast<float4*>(X);  // the last one may reach past the chunk's last bin into the padding
+#pragma unroll
+        for (int i = 0; i < kTile / 2 / NT; ++i) {
+            const uint32_t idx = (uint32_t)(tid + i * NT);
+            if (2u * idx < count) dst[idx] = *reinterpret_cast<const float4*>(stage + gapped(2u * idx));
+        }
+    } else {
+        for (uint32_t i = tid; i < count; i += NT) X[i] = stage[gapped(i)];
+    }
+}
+
+// The widest codes, 16 bits and 32.
 template <int NL>
-__global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npeers, size_t S, uint32_t B, uint32_t W, int bits,
+__global__ __launch_bounds__(NT) void k_decode_peers_wide(PeerList recs, uint32_t npeers, size_t S, uint32_t B, uint32_t W, int bits,
                                                      int m, uint32_t Tn, size_t C, const uint32_t* __restrict__ gprefix,
                                                      float2* __restrict__ spec, uint32_t sstride, bool vec, int pair_log)
 {
@@ -1779,15 +1855,17 @@ hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecA
     PeerList recs{};
     for (int i = 0; i < npeers; ++i) recs.p[i] = streams.p[i] + 64;  // records follow the 64-byte stream header
     const bool vec = a.sstride == padded_bins(a.L) && (reinterpret_cast<uintptr_t>(spec) & 15u) == 0;
-#define FFTSP_DECODE_PEERS(NL)                                                                                             \
-    FFTSP_LAUNCH("decode", k_decode_peers<NL>, dim3((unsigned)(a.C * u.Tn)), dim3(NT), 0, s, recs, (uint32_t)npeers, a.S, u.B, \
-                 u.W, a.bits, a.m, u.Tn, a.C, gprefix, reinterpret_cast<float2*>(spec), a.sstride, vec, a.pair_log)
+#define FFTSP_DECODE_PEERS(kern)                                                                                       \
+    FFTSP_LAUNCH("decode", kern, dim3((unsigned)(a.C * u.Tn)), dim3(NT), 0, s, recs, (uint32_t)npeers, a.S, u.B, u.W, a.bits, a.m, u.Tn, a.C, \
+                 gprefix, reinterpret_cast<float2*>(spec), a.sstride, vec, a.pair_log)
     if (a.bits <= 8)
-        FFTSP_DECODE_PEERS(1);
+        FFTSP_DECODE_PEERS(k_decode_peers<16>);
+    else if (a.bits <= 15)
+        FFTSP_DECODE_PEERS(k_decode_peers<30>);
     else if (a.bits <= 16)
-        FFTSP_DECODE_PEERS(2);
+        FFTSP_DECODE_PEERS(k_decode_peers_wide<2>);
     else
-        FFTSP_DECODE_PEERS(0);
+        FFTSP_DECODE_PEERS(k_decode_peers_wide<0>);
 #undef FFTSP_DECODE_PEERS
     return hipGetLastError();
 }

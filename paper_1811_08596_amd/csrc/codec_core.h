@@ -253,5 +253,45 @@ __device__ __forceinline__ T scalar_load(const T* p)
     return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
 }
 
+// BINS neighbouring bins of one record: which of them are kept, and the stretch of the record their codes are in.
+// WIDEST: bits of a bin at most (16: codes of up to 8, 30: of up to 15).
+template <int BINS, int WIDEST>
+struct Stretch {
+    static constexpr int WORDS = (BINS * WIDEST + 31 + 31) / 32;
+    uint32_t mask, rel;  // rel: bit position of the first code inside the window
+    uint32_t w[WORDS];
+    __device__ __forceinline__ void fetch(const uint32_t* codes, int final, uint32_t bit)
+    {
+        // the window stays inside the record, also for a corrupt bitmap; what lies before the codes is the bitmap
+        const int first = (int)(bit >> 5) < final - (WORDS - 1) ? (int)(bit >> 5) : final - (WORDS - 1);
+        rel = bit - 32u * (uint32_t)first;
+        __builtin_memcpy(w, codes + first, sizeof(w));
+    }
+    // put(j, value) for all bins, zero where one is not kept
+    template <typename Put>
+    __device__ __forceinline__ void unpack(uint32_t twoN, uint32_t bits, int shift, uint32_t base, Put&& put)
+    {
+        while (__any(rel >= 32u)) {  // windows moved back from a record's end
+            const bool on = rel >= 32u;
+#pragma unroll
+            for (int i = 0; i + 1 < WORDS; ++i) w[i] = on ? w[i + 1] : w[i];
+            w[WORDS - 1] = on ? 0u : w[WORDS - 1];
+            rel = on ? (rel < 32u * WORDS ? rel - 32u : 0u) : rel;
+        }
+#pragma unroll
+        for (int i = 0; i + 1 < WORDS; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], rel);
+        asm("" : "+v"(base));  // in a vector register, so that it is the addend of a shift-and-add
+#pragma unroll
+        for (int j = 0; j < BINS; ++j) {
+            const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)mask, j, 1), raw = w[0] & m, by = m & twoN;
+#pragma unroll
+            for (int i = 0; i + 1 < WORDS; ++i)
+                if (32 * i < (BINS - 1 - j) * WIDEST) w[i] = i + 2 < WORDS ? __builtin_amdgcn_alignbit(w[i + 1], w[i], by) : w[i] >> by;
+            put(j, make_float2(__uint_as_float(dequantize_field(raw, 0u, bits, base, shift)),
+                               __uint_as_float(dequantize_field(raw, bits, bits, base, shift))));
+        }
+    }
+};
+
 }  // namespace
 }  // namespace fftsp
