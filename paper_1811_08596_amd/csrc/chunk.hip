@@ -340,14 +340,27 @@ __device__ __forceinline__ float2 nyquist_bin(const float2* d, int base)
 }
 
 // --------------------------------------------------------- select and pack ----
+// Packing a row of bins costs the same however few of them survive.  Where at most this many do, and the region has room behind
+// the image, the survivors first move there, next to each other.
+// Senders of 25 M normal samples, row by row -> next to each other, us, at 15 %, 30 %, 50 % kept.  Transforms, 10-bit codes: L = 2^11
+// 51.5 -> 49.3, 51.6 -> 50.6, 52.8 -> 52.8;  2^12 62.9 -> 56.0, 63.5 -> 60.0, 65.0 -> 63.4;  2^13 58.8 -> 56.1, 61.3 -> 59.1, 61.2 -> 61.0;
+// 2^15 90.3 -> 81.4, 90.6 -> 83.8, 92.2 -> 88.3; at 75 % none gains.  Top-k, 10 bits: 2^10 57.8 -> 52.6, 58.7 -> 55.4, 58.8 -> 59.1;
+// 2^12 43.9 -> 38.5, 44.7 -> 41.0, 44.9 -> 45.6;  8-bit codes, which are stores and no atomics: 38.0 -> 37.7, 38.2 -> 38.8, 38.2 -> 38.7.
+template <bool REAL, int WAVES>
+__host__ __device__ constexpr uint32_t most_packed(uint32_t units, int bits)
+{
+    return bits == 32 ? 0u : units / (!REAL && WAVES > 1 ? 2u : (bits == 8 ? 5u : 3u));
+}
+
 // Steps 2-4 of the sender for one chunk whose bins (samples) lie in the registers of a group of WAVES waves:
 // z[r]: bin (wave * R + r) * 64 + lane (lane < LR); zn (TAIL): the chunk's last bin, the same value in every lane.
-// lds: the group's own words (histogram, candidate list); image: its record image.  wg_most: a word of the workgroup,
-// zero on entry, through which several groups of several waves agree on the path they take together.
+// lds: the group's own words (histogram, candidate list, survivors), room of them; image: its record image, among them but for
+// the shortest chunks.  wg_most: a word of the workgroup, zero on entry, through which several groups of several waves agree on
+// the path they take together.
 // runs: many of the samples are zero.  live = false groups (no such chunk) write nothing; groups of several waves call this together.
 template <bool REAL, int R, bool TAIL, int LR, int WAVES, int GROUPS, int HB>
 __device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z)[R], typename Elem<REAL>::T zn, uint32_t* lds,
-                                                uint32_t* image, GroupScratch& gs, uint32_t* wg_most, int tid,
+                                                uint32_t room, uint32_t* image, GroupScratch& gs, uint32_t* wg_most, int tid,
                                                 const PackArgs& a, uint32_t word3, uint8_t* __restrict__ record, bool live,
                                                 bool runs = false)
 {
@@ -525,26 +538,27 @@ __device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z
     uint32_t nfl = 0, vmax = 0;
     // usually all bins equal to tau are wanted; in the other case their order across the group counts
     const bool ties = need != equal;
-    if (ties || SHARED) {
-        uint32_t eqrun = 0;
-        if constexpr (WAVES > 1) {
+    uint32_t eqrun = 0;
+    if (WAVES > 1 && (ties || SHARED)) {
+        if (ties) {
             uint32_t neq = 0;
 #pragma unroll
             for (int r = 0; r < R; ++r) neq += ones(among(key[r] == tau));
             if (lane == 0) gs.a[wig] = neq;
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < WAVES - 1; ++w) eqrun += w < wig ? gs.a[w] : 0u;
-            eqrun = (uint32_t)__builtin_amdgcn_readfirstlane((int)eqrun);
         }
-        const uint32_t take = ties ? need : 0xFFFFFFFFu;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WAVES - 1; ++w) eqrun += w < wig ? gs.a[w] : 0u;
+        eqrun = (uint32_t)__builtin_amdgcn_readfirstlane((int)eqrun);
+    }
+    if (ties) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const uint64_t em = among(key[r] == tau);
-            fm[r] = among(key[r] > tau || (key[r] == tau && eqrun + prefix_popc(em) < take));
+            fm[r] = among(key[r] > tau || (key[r] == tau && eqrun + prefix_popc(em) < need));
             eqrun += ones(em);
         }
-        fn = tail && (keyn > tau || (keyn == tau && eqrun < take));
+        fn = tail && (keyn > tau || (keyn == tau && eqrun < need));
     } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) fm[r] = among(key[r] >= tau);
@@ -648,12 +662,37 @@ __device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z
         }
         if (fn && lane == 0) put(mode, zn, run);
     };
-    if (bits == 8)
-        all(std::integral_constant<int, 8>());
-    else if (bits == 32)
-        all(std::integral_constant<int, 32>());
-    else
-        all(std::integral_constant<int, 0>());
+    bool packed = false;
+    if constexpr (HB != 0) {
+        const uint32_t from = (room - CODES * a.k) & ~1u;
+        packed = a.k <= most_packed<REAL, WAVES>((uint32_t)(R * NL), bits) && (uint32_t)(image - lds) + image_words + CODES * a.k < room;
+        if (packed) {
+            typename Elem<REAL>::T* kept = reinterpret_cast<typename Elem<REAL>::T*>(lds + from);
+            uint32_t run = rank;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (__builtin_amdgcn_inverse_ballot_w64(fm[r])) kept[run + prefix_popc(fm[r])] = z[r];
+                run += ones(fm[r]);
+            }
+            if (fn && lane == 0) kept[run] = zn;
+            group_sync<WAVES>();
+            auto each = [&](auto mode) __attribute__((always_inline)) {
+                for (uint32_t i = (uint32_t)tg; i < a.k; i += NL) put(mode, kept[i], i);
+            };
+            if (bits == 8)
+                each(std::integral_constant<int, 8>());
+            else
+                each(std::integral_constant<int, 0>());
+        }
+    }
+    if (!packed) {
+        if (bits == 8)
+            all(std::integral_constant<int, 8>());
+        else if (bits == 32)
+            all(std::integral_constant<int, 32>());
+        else
+            all(std::integral_constant<int, 0>());
+    }
     group_sync<WAVES>();
     if (live) {
         const uint32_t whole = image_words / 4u;
@@ -737,11 +776,12 @@ __device__ __forceinline__ void compress_workgroup(const float* __restrict__ in,
         }
         zn = nyquist_bin<LOGM>(d, base);
     };
+    static_assert(G::REGION % 8 == 0, "survivors are aligned");
     auto pack = [&](int i, const float2 (&z)[G::R], float2 zn, uint32_t* image) __attribute__((always_inline)) {
         const int b = group * G::CPW + i;
         const bool live = where.exists(b);
         select_and_pack<false, G::R, true, G::LR, G::WAVES, G::GROUPS, G::HB>(
-            z, zn, mine, image, gs[group], wg_most, tid, a, a.word3, records + (live ? where.record(b) : 0), live);
+            z, zn, mine, (uint32_t)G::REGION / 4u, image, gs[group], wg_most, tid, a, a.word3, records + (live ? where.record(b) : 0), live);
     };
     if constexpr (G::HB == 0) {
         for (int i = 0; i < G::CPW; ++i) {  // the bins stay in LDS until their turn comes
@@ -833,10 +873,11 @@ struct TopkGeo {
     static constexpr int R = L / NL > 1 ? L / NL : 1, LR = L < 64 ? L : 64;
     static constexpr int HB = L <= 512 ? 0 : (L <= 4096 ? 11 : 12);
     static constexpr int SCRATCH = GROUPS * (int)sizeof(GroupScratch) + 16;
-    // LDS bytes of a group: histogram, then candidate list and record image
-    static constexpr size_t region(size_t record)
+    static constexpr uint32_t most_moved(int bits) { return HB ? most_packed<true, WAVES>((uint32_t)L, bits) : 0u; }
+    // LDS bytes of a group: histogram, then candidate list, record image and survivors
+    static constexpr size_t region(size_t record, size_t moved)
     {
-        const size_t image = (HB ? 4 * (size_t)kListCap : 0) + record + 16, hist = HB ? (size_t)4 << HB : 0;
+        const size_t image = ((HB ? 4 * (size_t)kListCap : 0) + record + 16 + 4 * moved + 15) / 16 * 16, hist = HB ? (size_t)4 << HB : 0;
         return image > hist ? image : hist;
     }
 };
@@ -866,7 +907,7 @@ __global__ __launch_bounds__(TopkGeo<LOGL>::NT) void k_topk_compress(const float
         z[r] = 0.f;
         if (i < present) z[r] = src[i];
     }
-    select_and_pack<true, G::R, false, G::LR, G::WAVES, G::GROUPS, G::HB>(z, 0.f, mine, mine + (G::HB ? kListCap : 0u), gs[group],
+    select_and_pack<true, G::R, false, G::LR, G::WAVES, G::GROUPS, G::HB>(z, 0.f, mine, region / 4u, mine + (G::HB ? kListCap : 0u), gs[group],
                                                                           reinterpret_cast<uint32_t*>(gs + G::GROUPS), tid, a,
                                                                           a.word3, records + c * (size_t)a.S, true, present < (uint32_t)G::L);
 }
@@ -1262,9 +1303,9 @@ hipError_t topk_compress_as(const float* in, size_t n, const CodecArgs& a, uint8
     using G = TopkGeo<LOGL>;
     // records are whole 16 bytes; of one with 32-bit codes only header and bitmap pass through LDS
     const size_t image = a.bits == 32 ? 16 + ((size_t)a.L / 8 + 15) / 16 * 16 : a.S;
-    const size_t region = G::region(image), lds = G::SCRATCH + G::GROUPS * region;
+    const size_t region = G::region(image, a.k <= G::most_moved(a.bits) ? a.k : 0u), lds = G::SCRATCH + G::GROUPS * region;
     constexpr size_t longest = (16 + 4 * ((G::L + 31) / 32) + 2 * (size_t)G::L + 15) / 16 * 16;  // all kept, 16-bit codes
-    const hipError_t e = allow_lds(k_topk_compress<LOGL>, G::SCRATCH + G::GROUPS * G::region(longest));
+    const hipError_t e = allow_lds(k_topk_compress<LOGL>, G::SCRATCH + G::GROUPS * G::region(longest, G::most_moved(16)));
     if (e != hipSuccess) return e;
     FFTSP_LAUNCH("topk_compress", k_topk_compress<LOGL>, dim3((unsigned)((a.C + G::GROUPS - 1) / G::GROUPS)), dim3(G::NT), lds, s, in,
                  n, a.C, pack_args(a), stream, records, header_info(a, 1), ctl, (uint32_t)region);
