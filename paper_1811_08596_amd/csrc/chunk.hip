@@ -39,8 +39,12 @@ static_assert(sizeof(GroupScratch) % 16 == 0, "the LDS regions behind it stay al
 
 // Coarse twiddles (steps of 1/2048 of a turn, or of 1/R for R < 2048) that the stages of an R-point transform look up: those
 // of the last part of the turn are never wanted, and what they would take decides how many workgroups a compute unit holds.
+// At R = 2048 they are half a turn, the other half their negatives: 1024 entries beside 32 KB of data are a quarter of a compute
+// unit's LDS to the byte.  25 M samples in chunks of 2^12, three workgroups a compute unit -> four: sender 66 -> 58 us, receiver 53 -> 47.
+constexpr bool half_turn(int logr) { return logr == 11; }
 constexpr int coarse_twiddles(int logr)
 {
+    if (half_turn(logr)) return 1 << (logr - 1);
     int most = 0;
     for (int ns = 0; ns < logr;) {
         const int rl = stage_radix_log(logr - ns), at = ((1 << rl) - 1) * ((1 << ns) - 1) << (logr - ns - rl);
@@ -69,7 +73,10 @@ struct Geo {
     // LDS bytes of a group: its complex values, later its histogram, candidate list and record image
     static constexpr int DATA = E / GROUPS * 8, REGION = DATA > (4 << HB) ? DATA : (4 << HB);
     static constexpr int SCRATCH = GROUPS * (int)sizeof(GroupScratch) + 16;  // and the word the groups agree through
-    static constexpr int RECEIVER_FRONT = SCRATCH + (T * 8 + 15) / 16 * 16;  // and the Nyquist bins
+    // A sender's lies at the end of its groups' regions where histogram, list and image leave room.
+    static constexpr int INSIDE = LOGM >= 11 ? (int)sizeof(GroupScratch) + 16 : 0;
+    static constexpr int SENDER_FRONT = INSIDE ? 0 : SCRATCH;
+    static constexpr int RECEIVER_FRONT = WC > 64 ? SCRATCH : 0;  // one wave counts a short bitmap
     // of a receiver's group: its record images and behind them the bitmap's words with their prefixes, later its complex values
     __host__ __device__ static constexpr size_t receiver_region(size_t images)
     {
@@ -128,11 +135,17 @@ __device__ __forceinline__ void load_chunk_twiddles(float2* tw, const Tables& tb
     for (int i = 0; i < ITERS; ++i)
         if (tid + i * NT < COUNT) tw[tid + i * NT] = v[i];
 }
+// most: the largest idx of any lane
 template <int LOGR, int SHIFT>
-__device__ __forceinline__ float2 stage_twiddle(const float2* tw, int idx)
+__device__ __forceinline__ float2 stage_twiddle(const float2* tw, int idx, int most)
 {
     constexpr int COARSE = coarse_twiddles(LOGR);
-    if constexpr (LOGR <= 11)
+    if constexpr (half_turn(LOGR)) {
+        if (most << SHIFT < COARSE) return tw[idx << SHIFT];
+        const float2 c = tw[(idx << SHIFT) & (COARSE - 1)];
+        const uint32_t sign = ((uint32_t)idx << (SHIFT + 32 - LOGR)) & 0x80000000u;
+        return make_float2(__uint_as_float(__float_as_uint(c.x) ^ sign), __uint_as_float(__float_as_uint(c.y) ^ sign));
+    } else if constexpr (LOGR <= 11)
         return tw[idx << SHIFT];
     else if constexpr (SHIFT >= LOGR - 11)
         return tw[idx << (SHIFT - (LOGR - 11))];
@@ -163,7 +176,7 @@ __device__ __forceinline__ void stage_compute(float2 (&v)[(1 << (LOGE - RL)) / N
             const int k = B::j(B::index(tid, q)) & ((1 << NS_LOG) - 1);
 #pragma unroll
             for (int t = 1; t < B::RHO; ++t) {
-                const float2 c = stage_twiddle<LOGR, LOGR - NS_LOG - RL>(tw, t * k);
+                const float2 c = stage_twiddle<LOGR, LOGR - NS_LOG - RL>(tw, t * k, t * ((1 << NS_LOG) - 1));
                 v[q][t] = INV ? cmulc(v[q][t], c) : cmul(v[q][t], c);
             }
         }
@@ -740,15 +753,17 @@ __device__ __forceinline__ void compress_workgroup(const float* __restrict__ in,
 {
     using G = Geo<LOGM, NT>;
     const int lane = tid & 63, group = tid / G::NL, wig = (tid >> 6) % G::WAVES;
-    GroupScratch* gs = reinterpret_cast<GroupScratch*>(lds);
-    uint32_t* wg_most = reinterpret_cast<uint32_t*>(gs + G::GROUPS);
-    uint8_t* regions = lds + G::SCRATCH;
+    uint8_t* regions = lds + G::SENDER_FRONT;
     uint8_t* region = regions + group * G::REGION;
+    constexpr int ROOM = G::REGION - G::INSIDE;
+    static_assert(!G::INSIDE || ROOM >= 4 * kListCap + 16 + 4 * (G::WC + 1) + 4 * (G::M + 1) + 16, "list and image of 16-bit codes");
+    static_assert(ROOM >= (G::HB ? 4 << G::HB : 0) && ROOM % 16 == 0, "histogram");
+    GroupScratch& gs = *reinterpret_cast<GroupScratch*>(G::INSIDE ? region + ROOM : lds + group * (int)sizeof(GroupScratch));
+    uint32_t* wg_most = reinterpret_cast<uint32_t*>((G::INSIDE ? regions + ROOM : lds) + (G::INSIDE ? 1 : G::GROUPS) * (int)sizeof(GroupScratch));
     // the workgroup's point g lies at d[flat(g)]; a group's points are a multiple of 256, so its base moves freely
     float2* d = reinterpret_cast<float2*>(region) - group * (G::E / G::GROUPS);
     float2* tw = reinterpret_cast<float2*>(regions + G::GROUPS * G::REGION);
     uint32_t* images = reinterpret_cast<uint32_t*>(tw + G::TW);  // short chunks only
-    if (tid == 0) *wg_most = 0u;
     load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
     forward_tile<G, LOGM>(in, where, d, tw, tid);
     uint32_t* mine = reinterpret_cast<uint32_t*>(region);
@@ -781,7 +796,7 @@ __device__ __forceinline__ void compress_workgroup(const float* __restrict__ in,
         const int b = group * G::CPW + i;
         const bool live = where.exists(b);
         select_and_pack<false, G::R, true, G::LR, G::WAVES, G::GROUPS, G::HB>(
-            z, zn, mine, (uint32_t)G::REGION / 4u, image, gs[group], wg_most, tid, a, a.word3, records + (live ? where.record(b) : 0), live);
+            z, zn, mine, (uint32_t)ROOM / 4u, image, gs, wg_most, tid, a, a.word3, records + (live ? where.record(b) : 0), live);
     };
     if constexpr (G::HB == 0) {
         for (int i = 0; i < G::CPW; ++i) {  // the bins stay in LDS until their turn comes
@@ -797,6 +812,7 @@ __device__ __forceinline__ void compress_workgroup(const float* __restrict__ in,
         float2 z[G::R], zn;
         bins_of(group, z, zn);
         group_sync<G::WAVES>();
+        if (G::WAVES > 1 && tid == 0) *wg_most = 0u;  // ordered by the barrier behind the histogram's zeros
         pack(0, z, zn, mine + kListCap);
     }
 }
@@ -927,7 +943,6 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
     using B = Butterflies<LOGM, G::LOGE, NT, RL>;
     const int lane = tid & 63, group = tid / G::NL, tg = tid & (G::NL - 1), wig = tg >> 6;
     GroupScratch* gs = reinterpret_cast<GroupScratch*>(lds);
-    float2* nyquist = reinterpret_cast<float2*>(lds + G::SCRATCH);
     uint8_t* regions = lds + G::RECEIVER_FRONT;
     uint8_t* images = regions + (size_t)group * region;
     uint2* words = reinterpret_cast<uint2*>(images + region) - G::GROUP_WORDS;
@@ -1058,9 +1073,12 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
     for (int q = 0; q < B::PER; ++q) {
         const int w = B::index(tid, q), f = flat((B::b(w) << LOGM) + B::j(w));
 #pragma unroll
-        for (int t = 0; t < B::RHO; ++t) d[flat_plus(f, t * B::STEP)] = x[q][t];
+        for (int t = 1; t < B::RHO; ++t) d[flat_plus(f, t * B::STEP)] = x[q][t];
+        d[f].x = x[q][0].x;
+        if (B::j(w) != 0) d[f].y = x[q][0].y;
     }
-    if (tg < G::CPW * G::WC && tg % G::WC == G::WC - 1) nyquist[group * G::CPW + tg / G::WC] = xn;
+    // imaginary parts of the DC and Nyquist bins are ignored: the Nyquist bin takes the place of one
+    if (tg < G::CPW * G::WC && tg % G::WC == G::WC - 1) d[flat((group * G::CPW + tg / G::WC) << LOGM)].y = xn.x;
     if constexpr (G::WAVES == 1) __syncthreads();  // the twiddle table
     group_sync<G::WAVES>();
 #pragma unroll
@@ -1073,8 +1091,8 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
             const int mirror = j == 0 ? flat((b << LOGM) + ((G::M - t * B::STEP) & (G::M - 1)))
                                       : flat_plus(flat((b << LOGM) + B::STEP - j), (B::RHO - 1 - t) * B::STEP);
             float2 p = d[mirror], s = x[q][t];
-            if (t == 0 && k == 0) {  // imaginary parts of the DC and Nyquist bins are ignored
-                p = make_float2(nyquist[b].x, 0.f);
+            if (t == 0 && k == 0) {
+                p = make_float2(p.y, 0.f);
                 s.y = 0.f;
             }
             x[q][t] = split_inv(s, p, split_twiddle<LOGM>(tb, k));
@@ -1244,7 +1262,7 @@ template <int LOGM, int NT>
 constexpr size_t sender_lds()
 {
     using G = Geo<LOGM, NT>;
-    return G::SCRATCH + (size_t)G::GROUPS * (G::REGION + 4 * G::IMAGE) + (size_t)G::TW * sizeof(float2);
+    return G::SENDER_FRONT + (size_t)G::GROUPS * (G::REGION + 4 * G::IMAGE) + (size_t)G::TW * sizeof(float2);
 }
 template <int LOGM, int NT>
 constexpr size_t receiver_lds(size_t region)
@@ -1276,9 +1294,11 @@ constexpr size_t kLdsBytes = 160 * 1024;  // of a compute unit
 static_assert(most_tensors_lds<14>(true) <= kLdsBytes && most_tensors_lds<14>(false) <= kLdsBytes, "fits");
 // What leaving out the twiddles that no stage wants, and keeping a receiver's bitmap table where its data will be, is for: two
 // workgroups of 2^13 points to a compute unit and four senders of 2^10, where one and three fitted.  33 M
-// samples in chunks of 2^14: sender 129 -> 83 us, receiver 104 -> 68; of 2^11 72 -> 64 and 61 -> 54.  For 2^11 points the same four
-// waves a SIMD by way of 512 lanes and four chunks a workgroup gained and lost: sender 78 -> 83, receiver 52 -> 56 (26 M samples).
+// samples in chunks of 2^14: sender 129 -> 83 us, receiver 104 -> 68; of 2^11 72 -> 64 and 61 -> 54.  With 2^11 points four
+// fit since their table is half a turn and the scratch lies in the regions; 512 lanes and eight points a lane instead: 78 -> 83 and
+// 52 -> 56 us.
 static_assert(2 * sender_lds<13, 512>() <= kLdsBytes && 2 * receiver_lds<13, 512>(Geo<13, 512>::DATA) <= kLdsBytes, "two a compute unit");
+static_assert(4 * sender_lds<11, 256>() <= kLdsBytes && 4 * receiver_lds<11, 256>(Geo<11, 256>::DATA) <= kLdsBytes, "four a compute unit");
 static_assert(4 * sender_lds<10, 256>() <= kLdsBytes && 4 * receiver_lds<10, 256>(Geo<10, 256>::DATA) <= kLdsBytes, "four a compute unit");
 
 template <int LOGM>
