@@ -1106,6 +1106,10 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
                     pe = launch_short_decode_long(in, a, mid, t, leads, verdicts + done, reinterpret_cast<uint32_t*>(ws + w.status),
                                                   leads ? &note : nullptr, st);
                     if (pe == hipSuccess) pe = launch_inverse_a_long(mid, b, d_grad_out, t, st);
+                } else if (receive_applies(b, bits)) {
+                    pe = launch_receive_long(in, a, spec, mid, t, leads, verdicts + done, reinterpret_cast<uint32_t*>(ws + w.status),
+                                             leads ? &note : nullptr, st);
+                    if (pe == hipSuccess) pe = launch_inverse_a_long(mid, b, d_grad_out, t, st);
                 } else {
                     pe = launch_decode(in, in + kStreamHeader, a, spec, ws, w, leads, verdicts + done, leads ? &note : nullptr, st);
                     if (pe == hipSuccess) pe = launch_irfft_long(reinterpret_cast<float2*>(spec), b, d_grad_out, mid, t, st);

@@ -11,4 +11,9 @@ bool receive_applies(int logM, size_t C, int bits);
 hipError_t launch_receive(const uint8_t* stream, const CodecArgs& a, int logM, void* table, float2* mid, Tables t, uint32_t* verdicts,
                           uint32_t* ctl, const StatusNote& note, hipStream_t s);
 
+// The same for the tensors of a per-tensor launch (a.tab); first, if not null: the launch clears the control block and leaves it there.
+bool receive_applies(const LongBatch& b, int bits);
+hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* table, float2* mid, Tables t, int check_header, uint32_t* verdicts,
+                               uint32_t* ctl, const StatusNote* first, hipStream_t s);
+
 }  // namespace fftsp

@@ -15,7 +15,8 @@
 // is kept for a next tile: a workgroup does one.  (Persistent workgroups of sixteen points a lane that fetched the next tile's entries and
 // codes during the transform took 124 to 134 us; a lane that looked up each of its bins alone 187.)
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against counting, decoding and the pass: 6 + 54 + 110
-// -> 6 + 116 us; 138 M in chunks of 2^22 15 + 118 + 275 -> 12 + 354; binary16 5 + 33 + 95 -> 6 + 96.
+// -> 6 + 116 us; 138 M in chunks of 2^22 15 + 118 + 275 -> 12 + 341; binary16 5 + 33 + 95 -> 6 + 96.
+// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 6 + 38 + 40.
 // Several senders' streams are decoded into a spectrum first (codec.hip): eight of them took 444 us this way against 285, since every
 // stretch of eight bins is two and a half lines out of L2.
 #include "fft_core.h"
@@ -35,17 +36,14 @@ __host__ __device__ constexpr uint32_t table_stride(int logM) { return (1u << (l
 // and counts the words before its own itself, four loads in flight; the last one of a record leaves the record's verdict.
 // (A workgroup per record: sixty records of 2^20 samples 10.8 -> 6.1 us, thirty-three of 2^22 39 -> 12.)
 constexpr uint32_t kTableWords = 4 * kTableLanes;
-__global__ __launch_bounds__(kTableLanes) void k_bitmap_table(const uint8_t* __restrict__ stream, uint32_t C, size_t S, uint32_t k, HeaderInfo hdr, int logM,
-                                                             uint32_t parts, uint2* __restrict__ table, uint32_t* __restrict__ verdicts,
-                                                             uint32_t* __restrict__ ctl, StatusNote note)
+__host__ __device__ constexpr uint32_t table_parts(int logM) { return ((1u << (logM - 5)) + kTableWords - 1u) / kTableWords; }
+__device__ __forceinline__ void bitmap_part(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ record, bool first_of_stream, uint32_t k,
+                                            uint32_t word3, const HeaderInfo& hdr, int logM, uint32_t part, uint2* __restrict__ out,
+                                            uint32_t* __restrict__ verdict)
 {
     __shared__ uint32_t own[kTableWaves], earlier[kTableWaves];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // the parts of a record share an XCD, and with it the words before theirs (workgroups are dealt out round-robin over the eight)
-    const uint32_t y = blockIdx.x >> 3, c = y / parts * 8u + (blockIdx.x & 7u), part = y % parts;
-    if (blockIdx.x == 0) clear_control(ctl, note, tid, kTableLanes);
-    if (c >= C) return;
-    const uint8_t* record = stream + 64 + (size_t)c * S;
+    const uint32_t parts = table_parts(logM);
     const uint4* quads = reinterpret_cast<const uint4*>(record + 16);
     const uint32_t words = 1u << (logM - 5), at = part * kTableLanes + (uint32_t)tid;  // this lane's four
     auto ones = [](uint4 v) __attribute__((always_inline)) { return (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w)); };
@@ -67,7 +65,6 @@ __global__ __launch_bounds__(kTableLanes) void k_bitmap_table(const uint8_t* __r
         run += earlier[i] + (i < wave ? own[i] : 0u);
         all += earlier[i] + own[i];
     }
-    uint2* out = table + (size_t)c * table_stride(logM);
     if (in) {
         const uint32_t r1 = run + (uint32_t)__popc(w.x), r2 = r1 + (uint32_t)__popc(w.y), r3 = r2 + (uint32_t)__popc(w.z);
         uint4* p = reinterpret_cast<uint4*>(out + 4u * at);  // the stride is even
@@ -77,15 +74,33 @@ __global__ __launch_bounds__(kTableLanes) void k_bitmap_table(const uint8_t* __r
     if (part + 1u == parts && tid == 0) {
         const uint32_t last = reinterpret_cast<const uint32_t*>(quads)[words];  // the Nyquist bin has a word to itself
         *reinterpret_cast<uint4*>(out + words) = make_uint4(last, all, 0u, 0u);
-        verdicts[c] = record_verdict(record, stream, c == 0, all + (uint32_t)__popc(last), k, 0u, hdr);
+        *verdict = record_verdict(record, stream, first_of_stream, all + (uint32_t)__popc(last), k, word3, hdr);
     }
+}
+__global__ __launch_bounds__(kTableLanes) void k_bitmap_table(const uint8_t* __restrict__ stream, uint32_t C, size_t S, uint32_t k, HeaderInfo hdr, int logM,
+                                                             uint2* __restrict__ table, uint32_t* __restrict__ verdicts,
+                                                             uint32_t* __restrict__ ctl, StatusNote note)
+{
+    // the parts of a record share an XCD, and with it the words before theirs (workgroups are dealt out round-robin over the eight)
+    const uint32_t parts = table_parts(logM), y = blockIdx.x >> 3, c = y / parts * 8u + (blockIdx.x & 7u);
+    if (blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, kTableLanes);
+    if (c >= C) return;
+    bitmap_part(stream, stream + 64 + (size_t)c * S, c == 0, k, 0u, hdr, logM, y % parts, table + (size_t)c * table_stride(logM), verdicts + c);
+}
+// where tensor i of a launch has its entries, in the spectrum's region
+__device__ __forceinline__ size_t long_entries(const LongTensor& x, uint32_t i) { return (long_mid(x) >> 5) + 2u * i; }
+__global__ __launch_bounds__(kTableLanes) void k_bitmap_table_long(const uint8_t* __restrict__ stream, HeaderInfo hdr, uint2* __restrict__ table,
+                                                                  uint32_t* __restrict__ verdicts, uint32_t* __restrict__ ctl, StatusNote note,
+                                                                  LongTable tab, LongStarts at)
+{
+    if (ctl && blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, kTableLanes);
+    const LongShare share = long_share(at);
+    const LongTensor& x = tab.t[share.tensor];
+    bitmap_part(stream, stream + 64 + x.roff, share.tensor == 0, x.kept, 2u << x.logM, hdr, x.logM, share.blk, table + long_entries(x, share.tensor),
+                verdicts + share.tensor);
 }
 
 // ---------------------------------------------------------- inverse pass B ----
-struct RecordShape {
-    uint32_t W, S;
-    int bits, m;
-};
 // Eight points a lane and eight waves a SIMD where the tile allows it: what this kernel waits for are its two dependent trips to
 // memory and the barriers between the transform's stages, and it moves half the bytes of a transform pass.
 template <int LOGN2>
@@ -95,30 +110,23 @@ struct Receive {
     static constexpr int BINS = SLOTS / 2;                         // neighbouring bins of either side of a run
     static constexpr size_t kLds = ((size_t)(SLOTS + 1) << LOGN2) * sizeof(float2);
 };
+// A tile of rows and mirrors from pp0 on, by G::NT lanes; mid: the chunk's.  Several tiles of a workgroup run beside each other, each
+// in LDS of its own; first: whether row 0 is in one of them.
 template <int LOGN2, bool HALF, int WIDEST>
-__global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(8 / Receive<LOGN2>::U, 8 / Receive<LOGN2>::U))) void k_receive_b(
-    const uint8_t* __restrict__ records, RecordShape rs, const uint2* __restrict__ table, int logM, typename Cx<HALF>::One* __restrict__ mid,
-    Tables tb, uint32_t total, float mid_scale)
+__device__ __forceinline__ void receive_tile(const uint8_t* __restrict__ record, uint32_t W, uint32_t S, int code_bits, int m,
+                                             const uint2* __restrict__ entries, int logM, typename Cx<HALF>::One* __restrict__ mid, Tables tb,
+                                             uint32_t pp0, bool first, float2* d, int tid, float mid_scale)
 {
     using G = Receive<LOGN2>;
     constexpr int N2 = G::N2, NT = G::NT, U = G::U, DK = N2 / 8, LOGT = G::LOGT, SLOTS = G::SLOTS, BINS = G::BINS;
-    extern __shared__ float2 smem[];
-    float2* d = smem;
-    float2* tw = smem + (N2 << LOGT);
-    const int tid = threadIdx.x, logN1 = logM - LOGN2, log_tiles = logN1 - LOGT;
+    float2* tw = d + (N2 << LOGT);
+    const int logN1 = logM - LOGN2;
     const uint32_t M = 1u << logM, N1 = 1u << logN1;
-    // every XCD has a stretch of tiles of its own
-    const uint32_t xcd = blockIdx.x & 7u, lo = (uint32_t)((uint64_t)total * xcd >> 3), hi = (uint32_t)((uint64_t)total * (xcd + 1u) >> 3);
-    const uint32_t t = lo + (blockIdx.x >> 3);
-    if (t >= hi) return;
-    const uint32_t c = t >> log_tiles, pp0 = (t & ((1u << log_tiles) - 1u)) * (SLOTS / 2);
 
-    const uint32_t bits = (uint32_t)rs.bits, twoN = 2u * bits;
-    const int shift = 23 - rs.m;
-    const int final = (int)(rs.S / 4u) - 5 - (int)rs.W;  // a record's last code word
-    const uint8_t* record = records + (size_t)c * rs.S;
-    const uint32_t* words = reinterpret_cast<const uint32_t*>(record) + 4 + rs.W;
-    const uint2* entries = table + (size_t)c * table_stride(logM);
+    const uint32_t bits = (uint32_t)code_bits, twoN = 2u * bits;
+    const int shift = 23 - m;
+    const int final = (int)(S / 4u) - 5 - (int)W;  // a record's last code word
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(record) + 4 + W;
     const uint32_t vbase = (scalar_load(reinterpret_cast<const uint32_t*>(record)) - 1u) << shift;
     auto stored = [](float2 z) __attribute__((always_inline)) { return cx_load(cx_store<HALF>(z)); };  // as a spectrum would hold it
 
@@ -131,7 +139,7 @@ __global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per
     };
     u32x4 entry[U];
 #pragma unroll
-    for (int i = 0; i < U; ++i) __builtin_memcpy(&entry[i], entries + (first_of(i) >> 5), sizeof(u32x4));
+    for (int i = 0; i < U; ++i) __builtin_memcpy(&entry[i], reinterpret_cast<const uint8_t*>(entries) + (first_of(i) >> 5) * 8u, sizeof(u32x4));
     load_stage_twiddles<LOGN2, NT>(tw, tb, tid);
     Stretch<BINS, WIDEST> o[U];
 #pragma unroll
@@ -147,21 +155,27 @@ __global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per
     const bool self = pp == 0;
     const int sh = 22 - logM;
     auto kq_of = [&](int u) __attribute__((always_inline)) { return (tid >> LOGT) + u * (NT / SLOTS); };
-    float2 base[U], cur[U];
+    float2 base[U], cur[U], ratio;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        base[u] = twiddle(tb, (k + ((uint32_t)kq_of(u) << logN1)) << (21 - logM));
-        cur[u] = twiddle(tb, ((uint32_t)kq_of(u) * k) << sh);
-        if constexpr (HALF) cur[u] = make_float2(cur[u].x * mid_scale, cur[u].y * mid_scale);
-    }
-    const float2 ratio = twiddle(tb, ((uint32_t)DK * k) << sh);
+    for (int u = 0; u < U; ++u) base[u] = twiddle(tb, (k + ((uint32_t)kq_of(u) << logN1)) << (21 - logM));
+    auto outer_twiddles = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            cur[u] = twiddle(tb, ((uint32_t)kq_of(u) * k) << sh);
+            if constexpr (HALF) cur[u] = make_float2(cur[u].x * mid_scale, cur[u].y * mid_scale);
+        }
+        ratio = twiddle(tb, ((uint32_t)DK * k) << sh);
+    };
+    // with sixteen points a lane the split wants their registers: 138 M samples in chunks of 2^22 354 -> 340 us
+    if constexpr (U == 1) outer_twiddles();
 #pragma unroll
     for (int i = 0; i < U; ++i)
         o[i].unpack(twoN, bits, shift, vbase, [&](int j, float2 z) __attribute__((always_inline)) {
             d[sw_idx<LOGT>(k2, 2 * (side_of(i) ? BINS - 1 - j : j) + side_of(i))] = stored(z);
         });
     float2 last = make_float2(0.f, 0.f);  // the Nyquist bin
-    if (pp0 == 0) {
+    if (first) {
+        if constexpr (U == 1) __syncthreads();  // the upper lanes have left a zero where row N1/2 goes
         // one bin on its own: those outside the stretches
         auto single = [&](uint32_t bin) __attribute__((always_inline)) {
             const uint2 e = entries[bin >> 5];
@@ -171,9 +185,10 @@ __global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per
             return stored(make_float2(__uint_as_float(dequantize_field(raw, 0u, bits, vbase, shift)),
                                       __uint_as_float(dequantize_field(raw, bits, bits, vbase, shift))));
         };
-        if constexpr (U == 1) __syncthreads();  // the upper lanes have left a zero where row N1/2 goes
-        if (tid < N2) d[sw_idx<LOGT>(k2, 1)] = single(((uint32_t)k2 << logN1) + N1 / 2);  // it is its own mirror
-        last = single(M);
+        if (pp0 == 0) {
+            if (tid < N2) d[sw_idx<LOGT>(k2, 1)] = single(((uint32_t)k2 << logN1) + N1 / 2);  // it is its own mirror
+            last = single(M);
+        }
     }
     __syncthreads();
     // from here on as in fft.hip's inverse pass B
@@ -203,17 +218,73 @@ __global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int i = 0; i < 8; ++i) d[sw_idx<LOGT>(8 * kq_of(u) + i, slot)] = x[u][i];
     }
+    if constexpr (U > 1) outer_twiddles();
     __syncthreads();
     run_fft<LOGN2, LOGT, NT, true, 3>(d, tw, tid);
-    typename Cx<HALF>::One* dst = mid + ((size_t)c << logM) + 2u * pp0 + (uint32_t)slot;
+    // one base for all lanes and 32-bit offsets: a chunk is 16 MB at most
+    auto store = [&](uint32_t i, typename Cx<HALF>::One z) __attribute__((always_inline)) {
+        *reinterpret_cast<typename Cx<HALF>::One*>(reinterpret_cast<uint8_t*>(mid) + i * (uint32_t)sizeof(z)) = z;
+    };
+    const uint32_t column = 2u * pp0 + (uint32_t)slot;
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int n2 = kq_of(u) + q * DK;
-            dst[(uint32_t)n2 << logN1] = cx_store<HALF>(cmulc(d[sw_idx<LOGT>(n2, slot)], cur[u]));
+            store(((uint32_t)n2 << logN1) + column, cx_store<HALF>(cmulc(d[sw_idx<LOGT>(n2, slot)], cur[u])));
             cur[u] = cmul(cur[u], ratio);
         }
+}
+
+// every XCD has a stretch of the launch's workgroups of its own; at or above `total`: none
+__device__ __forceinline__ uint32_t in_stretches(uint32_t total)
+{
+    const uint32_t xcd = blockIdx.x & 7u, lo = (uint32_t)((uint64_t)total * xcd >> 3), hi = (uint32_t)((uint64_t)total * (xcd + 1u) >> 3);
+    const uint32_t t = lo + (blockIdx.x >> 3);
+    return t < hi ? t : total;
+}
+template <int LOGN2, bool HALF, int WIDEST>
+__global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(8 / Receive<LOGN2>::U, 8 / Receive<LOGN2>::U))) void k_receive_b(
+    const uint8_t* __restrict__ records, uint32_t W, uint32_t S, int bits, int m, const uint2* __restrict__ table, int logM,
+    typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total, float mid_scale)
+{
+    using G = Receive<LOGN2>;
+    extern __shared__ float2 smem[];
+    const int log_tiles = logM - LOGN2 - G::LOGT;
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const uint32_t c = t >> log_tiles, pp0 = (t & ((1u << log_tiles) - 1u)) * (G::SLOTS / 2);
+    receive_tile<LOGN2, HALF, WIDEST>(records + (size_t)c * S, W, S, bits, m, table + (size_t)c * table_stride(logM), logM, mid + ((size_t)c << logM), tb,
+                                      pp0, pp0 == 0, smem, threadIdx.x, mid_scale);
+}
+// Tensors of different lengths: those with rows of up to 2^9 are one launch, a workgroup of 1024 lanes does one tile of rows of 2^9,
+// two of 2^8 or four of 2^7; those with rows of 2^10 are another (TOP 10).
+template <int TOP, int WIDEST>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8 / Receive<TOP>::U, 8 / Receive<TOP>::U))) void k_receive_b_long(
+    const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total,
+    LongTable tab, LongStarts at)
+{
+    static_assert(Receive<TOP>::NT == 1024, "one tile of the longest rows");
+    extern __shared__ float2 smem[];
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const LongShare share = long_share(at, t);
+    const LongTensor& x = tab.t[share.tensor];
+    auto run = [&](auto n2) __attribute__((always_inline)) {
+        constexpr int LOGN2 = decltype(n2)::value, LOGSUB = LOGN2 < TOP ? TOP - LOGN2 : 0;
+        using G = Receive<LOGN2>;
+        static_assert(G::NT << LOGSUB == 1024, "tiles beside each other");
+        const uint32_t sub = LOGSUB ? (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / G::NT) : 0u, pp0 = ((share.blk << LOGSUB) + sub) * (G::SLOTS / 2);
+        receive_tile<LOGN2, false, WIDEST>(records + x.roff, (1u << x.logM) / 32u + 1u, x.stride, bits, m, table + long_entries(x, share.tensor), x.logM,
+                                           mid + long_mid(x), tb, pp0, share.blk == 0, smem + (size_t)sub * (G::kLds / sizeof(float2)),
+                                           threadIdx.x & (G::NT - 1), 1.0f);
+    };
+    if constexpr (TOP == 9) {
+        const int rows = x.logM / 2;
+        if (rows == 7) return run(std::integral_constant<int, 7>{});
+        if (rows == 8) return run(std::integral_constant<int, 8>{});
+    }
+    run(std::integral_constant<int, TOP>{});
 }
 
 // ------------------------------------------------------------------ launch ----
@@ -225,9 +296,8 @@ hipError_t receive_b(const uint8_t* records, const CodecArgs& a, int logM, const
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::kLds);
     if (e != hipSuccess) return e;
     const size_t total = a.C << (logM - LOGN2 - G::LOGT);
-    const RecordShape rs{(1u << logM) / 32u + 1u, (uint32_t)a.S, a.bits, a.m};
-    FFTSP_LAUNCH("irfft_pass_b", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(G::NT), G::kLds, s, records, rs, table, logM,
-                 reinterpret_cast<typename Cx<HALF>::One*>(mid), t, (uint32_t)total, HALF ? 1.0f / half_lift(logM) : 1.0f);
+    FFTSP_LAUNCH("irfft_pass_b", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(G::NT), G::kLds, s, records, (1u << logM) / 32u + 1u, (uint32_t)a.S,
+                 a.bits, a.m, table, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, (uint32_t)total, HALF ? 1.0f / half_lift(logM) : 1.0f);
     return hipGetLastError();
 }
 template <int LOGN2>
@@ -259,9 +329,8 @@ hipError_t launch_receive(const uint8_t* stream, const CodecArgs& a, int logM, v
     if (!receive_applies(logM, a.C, a.bits)) return hipErrorInvalidValue;
     const HeaderInfo h{1, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, (uint32_t)a.hdr_scale};
     uint2* entries = static_cast<uint2*>(table);
-    const uint32_t parts = ((1u << (logM - 5)) + kTableWords - 1u) / kTableWords;
-    FFTSP_LAUNCH("bitmap_table", k_bitmap_table, dim3((unsigned)((a.C + 7) / 8 * 8 * parts)), dim3(kTableLanes), 0, s, stream, (uint32_t)a.C, a.S, a.k, h, logM, parts, entries,
-                 verdicts, ctl, note);
+    FFTSP_LAUNCH("bitmap_table", k_bitmap_table, dim3((unsigned)((a.C + 7) / 8 * 8 * table_parts(logM))), dim3(kTableLanes), 0, s, stream, (uint32_t)a.C, a.S,
+                 a.k, h, logM, entries, verdicts, ctl, note);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     switch (logM / 2) {
@@ -271,6 +340,58 @@ hipError_t launch_receive(const uint8_t* stream, const CodecArgs& a, int logM, v
         case 10: return receive_rows<10>(stream + 64, a, logM, entries, mid, t, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+// Tensors with rows of 2^10 are a launch of their own, a workgroup a compute unit: beside others it costs a tail more, and few of its
+// workgroups leave compute units idle.  Whole receivers of per-tensor calls in us, by tiles, decode and inverse pass B / these
+// kernels, half of the bins as 8-bit codes:
+//   rows of up to 2^9 alone 128 26.8 / 26.1, 192 31.4 / 29.0, 480 52.7 / 45.2 and 47.5 / 40.7;  of 2^10 alone 128 31.2 / 34.5, 256
+//   43.5 / 41.8, 512 62.3 / 50.7;  both 252 41.7 / 50.8, 420 74.4 / 76.8, 650 95.1 / 95.2, 700 99.3 / 105.5, 1190 130.5 / 120.1, 1400 154.6 / 147.7
+//   and 152.7 / 141.3, 2760 295.5 / 250.0, 3320 346.0 / 284.4.
+constexpr size_t kReceiveTallFrom = 192, kReceiveBothFrom = 1024;
+bool receive_applies(const LongBatch& b, int bits)
+{
+    auto tall = [&](uint32_t i) { return b.tab.t[i].logM / 2 >= 10; };  // the longest come last
+    const size_t tiles = (size_t)b.units << (kLongUnitLog - 13);
+    return bits <= 15 && tiles >= (tall(0) ? kReceiveTallFrom : (tall(b.count - 1) ? kReceiveBothFrom : kReceiveFrom));
+}
+
+hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* table, float2* mid, Tables t, int check_header, uint32_t* verdicts,
+                               uint32_t* ctl, const StatusNote* first, hipStream_t s)
+{
+    const LongBatch& b = *a.tab;
+    if (!receive_applies(b, a.bits)) return hipErrorInvalidValue;
+    const HeaderInfo h{check_header, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
+    uint2* entries = static_cast<uint2*>(table);
+    LongStarts at;
+    auto starts = [&](uint32_t from, uint32_t end, auto wgs) {
+        uint32_t sum = 0;
+        at.first = from;
+        at.count = end - from;
+        for (uint32_t i = from; i < end; ++i) {
+            at.at[i - from] = (uint16_t)sum;
+            sum += wgs((int)b.tab.t[i].logM);
+        }
+        return sum;
+    };
+    const uint32_t parts = starts(0, b.count, [](int logM) { return table_parts(logM); });
+    FFTSP_LAUNCH("bitmap_table", k_bitmap_table_long, dim3(parts), dim3(kTableLanes), 0, s, stream, h, entries, verdicts, first ? ctl : nullptr,
+                 first ? *first : StatusNote{}, b.tab, at);
+    hipError_t e = hipGetLastError();
+    uint32_t split = b.count;  // the longest come last
+    while (split > 0 && b.tab.t[split - 1].logM / 2 >= 10) --split;
+    auto pass = [&](auto kern, size_t lds, uint32_t from, uint32_t end, int log_points) {
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (err != hipSuccess) return err;
+        const uint32_t total = starts(from, end, [&](int logM) { return 1u << (logM - log_points); });
+        FFTSP_LAUNCH("irfft_pass_b", kern, dim3((total + 7) / 8 * 8), dim3(1024), lds, s, stream + 64, a.bits, a.m, entries, mid, t, total, b.tab, at);
+        return hipGetLastError();
+    };
+    if (e == hipSuccess && split > 0)
+        e = pass(a.bits <= 8 ? k_receive_b_long<9, 16> : k_receive_b_long<9, 30>, Receive<9>::kLds, 0, split, 9 + Receive<9>::LOGT);
+    if (e == hipSuccess && split < b.count)
+        e = pass(a.bits <= 8 ? k_receive_b_long<10, 16> : k_receive_b_long<10, 30>, Receive<10>::kLds, split, b.count, 10 + Receive<10>::LOGT);
+    return e;
 }
 
 }  // namespace fftsp
