@@ -326,7 +326,7 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
 }
 
 // Tiles of a chunk whose candidates k_resolve keeps in registers.  Longer chunks go through k_count_digit and k_mark before it.
-constexpr uint32_t kKeptTiles = 270;
+constexpr uint32_t kKeptTiles = 513;
 // Tiles of a chunk up to which k_emit may do k_resolve's work.
 constexpr uint32_t kMergedTiles = 72;
 
@@ -465,12 +465,12 @@ constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1
 // k_count_digit counts the candidates' second digit into the first kHist2Bins words of the chunk's tscan, which k_collect
 // has cleared.  k_mark adds the candidates above the two digits' common prefix to their tiles' counts and maxima and moves
 // the ones that share it to the front of their tile's list, unless they are more than k_resolve lists.
-// Senders in us, without / with: one chunk of 2^21 61.6 / 58.0, thirty-two 348 / 347; one of 2^22 90 / 70, thirty-three 801 / 785;
-// Top-k chunks of 2^20 (512 tiles, the fewest there can be) one 40.3 / 37.3, eight 59.5 / 56.1, thirty-two 115 / 113, sixty
-// 181 / 182, a hundred and twenty 378 / 383, where there is a k_resolve workgroup for every other compute unit anyway.
+// Senders in us, without / with: one chunk of 2^22 90 / 70, thirty-three 801 / 785.  Chunks of 512 and 513 tiles no longer come
+// here, since k_resolve holds as many candidates in registers: with / held there, chunks of 2^21 one 50.8 / 48.4, eight 119 / 115,
+// thirty-two 355 / 351; Top-k chunks of 2^20 one 37.0 / 31.0, eight 59.2 / 49.6, thirty-two 117 / 109, sixty 193 / 182.
 constexpr uint32_t kPartTiles = 64, kPartWave = kPartTiles / (NT / 64);
 inline uint32_t parts_of(uint32_t tiles) { return (tiles + kPartTiles - 1u) / kPartTiles; }
-static_assert(2 * kKeptTiles < (uint32_t)kHist2Bins && 2 * 512 >= kHist2Bins, "longer chunks have 512 tiles at least");
+static_assert(2 * (kKeptTiles + 1) >= (uint32_t)kHist2Bins, "their part of tscan holds the counters");
 template <bool TABLE>
 __device__ __forceinline__ Place part_of(const Shape& u, const TableArg<TABLE>& tab, const LongStarts& at, uint32_t& first)
 {
@@ -630,10 +630,11 @@ __global__ __launch_bounds__(NT) void k_mark(Shape u, const uint32_t* __restrict
 //
 // MERGED: every workgroup of k_emit does this for its own tile, which saves the launch; see resolve_in_emit.  The code words are
 // clear already, and the tile of number 0 writes the headers.
-constexpr int kFetch = 9;  // tiles of a wave asked for at once; it holds twice as many
-template <int NW>
-constexpr uint32_t kHeldTiles = 2 * kFetch * NW;
-static_assert(kHeldTiles<16> >= kKeptTiles && kHeldTiles<NT / 64> >= kMergedTiles, "the candidates stay in registers");
+// FETCH: tiles of a wave asked for at once; it holds twice as many.
+constexpr int kFetch = 9, kFetchMost = 17;
+template <int NW, int FETCH>
+constexpr uint32_t kHeldTiles = 2 * FETCH * NW;
+static_assert(kHeldTiles<16, kFetchMost> >= kKeptTiles && kHeldTiles<NT / 64, kFetch> >= kMergedTiles, "the candidates stay in registers");
 template <int MOST>
 struct ResolveScratch {
     uint32_t h[kHist2Bins], list[kListCap], list_at[kListCap], list_vb[kListCap];
@@ -677,13 +678,13 @@ __device__ __forceinline__ Digit find_digit(const uint32_t* h, uint32_t need, in
                  (uint32_t)__builtin_amdgcn_readlane((int)d.count, who)};
 }
 
-template <int NW, bool MERGED, int MOST>
+template <int NW, int FETCH, bool MERGED, int MOST>
 __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const ResolveArgs& a, ResolveScratch<MOST>& lds,
                                                    uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
                                                    uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
                                                    uint8_t* __restrict__ records, uint8_t* __restrict__ stream, const HeaderInfo& hdr)
 {
-    constexpr int LANES = NW * 64, HELD = 2 * kFetch;
+    constexpr int LANES = NW * 64, HELD = 2 * FETCH;
     uint32_t *const h = lds.h, *const list = lds.list, *const list_at = lds.list_at, *const list_vb = lds.list_vb;
     uint32_t *const tgt = lds.tgt, *const teq = lds.teq;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -698,7 +699,7 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
     // A wave's tiles are wave, wave + NW, ...; lane v has the summary of the v-th, e[v] its first candidates.  Slots behind
     // a tile's last candidate are allocated; what they hold is dropped.
     const uint32_t own = (uint32_t)wave + (uint32_t)(lane * NW);
-    const bool holds = !counted && lane < HELD && own < Tn, second = !counted && (uint32_t)(wave + kFetch * NW) < Tn;
+    const bool holds = !counted && lane < HELD && own < Tn, second = !counted && (uint32_t)(wave + FETCH * NW) < Tn;
     uint4 info = make_uint4(0u, 0u, 0u, 0u);
     uint2 e[HELD];
 #pragma unroll
@@ -706,14 +707,14 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
     if (holds) info = ti[own];
     if (!counted) {
 #pragma unroll
-        for (int v = 0; v < kFetch; ++v) {
+        for (int v = 0; v < FETCH; ++v) {
             const uint32_t t = (uint32_t)(wave + v * NW);
             e[v] = cd[(size_t)(t < Tn ? t : 0u) * kTile + lane];
         }
     }
     if (second) {
 #pragma unroll
-        for (int v = kFetch; v < HELD; ++v) {
+        for (int v = FETCH; v < HELD; ++v) {
             const uint32_t t = (uint32_t)(wave + v * NW);
             e[v] = cd[(size_t)(t < Tn ? t : 0u) * kTile + lane];
         }
@@ -744,7 +745,7 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
     auto first_rows = [&](auto&& f) __attribute__((always_inline)) {
 #pragma unroll
         for (int v = 0; v < HELD; ++v) {
-            if (v == kFetch && !second) break;
+            if (v == FETCH && !second) break;
             f(v, (uint32_t)__builtin_amdgcn_readlane((int)ncand, v), (uint32_t)__builtin_amdgcn_readlane((int)nweight, v));
         }
     };
@@ -963,14 +964,14 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
     if (hdr.write && c == 0 && (!MERGED || at.tile == 0) && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
     return th;
 }
-template <bool TABLE, int NW>
+template <bool TABLE, int NW, int FETCH>
 __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, ResolveArgs a, uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
                                                      uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
                                                      uint8_t* __restrict__ records, uint8_t* __restrict__ stream,
                                                      HeaderInfo hdr, TableArg<TABLE> tab)
 {
     __shared__ ResolveScratch<MAX_TILES> lds;
-    resolve_chunk<NW, false>(place_of<TABLE>(u, tab, blockIdx.x, 0u), a, lds, sel, tinfo, tscan, cand, records, stream, hdr);
+    resolve_chunk<NW, FETCH, false>(place_of<TABLE>(u, tab, blockIdx.x, 0u), a, lds, sel, tinfo, tscan, cand, records, stream, hdr);
 }
 
 // ------------------------------------------------------------------ emit ----
@@ -1022,7 +1023,7 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
     }
     if constexpr (MERGED) {
         __shared__ ResolveScratch<kMergedTiles> lds;
-        found = resolve_chunk<NT / 64, true>(at, a, lds, sel, tinfo, tscan, cand, records, stream, hdr);
+        found = resolve_chunk<NT / 64, kFetch, true>(at, a, lds, sel, tinfo, tscan, cand, records, stream, hdr);
     }
     const uint32_t tau = found.tau, quota = found.quota, pbase = found.pbase, rank0 = found.rank0, eq0 = found.eq0;
     if (bits != 32)  // 32-bit codes go straight to memory
@@ -1762,16 +1763,18 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
             FFTSP_LAUNCH("count_digit", k_count_digit<TABLE>, dim3(parts), dim3(NT), 0, s, u, tinfo, tscan, cand, tab, at);
             FFTSP_LAUNCH("mark", k_mark<TABLE>, dim3(parts), dim3(NT), 0, s, u, sel, tinfo, tscan, cand, tab, at);
         }
-        auto resolve = [&](auto waves) {
-            constexpr int NW = decltype(waves)::value;
-            FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW>), per_chunk, dim3(NW * 64), 0, s, u, ra, sel, tinfo, tscan, cand, records, stream_base,
+        auto resolve = [&](auto waves, auto fetch) {
+            constexpr int NW = decltype(waves)::value, FETCH = decltype(fetch)::value;
+            FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW, FETCH>), per_chunk, dim3(NW * 64), 0, s, u, ra, sel, tinfo, tscan, cand, records, stream_base,
                          h, tab);
             return hipGetLastError();
         };
         // few waves for few tiles: their barriers are cheaper than more hands
-        if (x.most <= 40u) return resolve(std::integral_constant<int, 4>{});
-        if (x.most <= kHeldTiles<8>) return resolve(std::integral_constant<int, 8>{});
-        return resolve(std::integral_constant<int, 16>{});
+        constexpr std::integral_constant<int, kFetch> some{};
+        if (x.most <= 40u) return resolve(std::integral_constant<int, 4>{}, some);
+        if (x.most <= kHeldTiles<8, kFetch>) return resolve(std::integral_constant<int, 8>{}, some);
+        if (x.most <= kHeldTiles<16, kFetch>) return resolve(std::integral_constant<int, 16>{}, some);
+        return resolve(std::integral_constant<int, 16>{}, std::integral_constant<int, kFetchMost>{});
     };
     const hipError_t e = a.tab ? select(std::true_type{}) : select(std::false_type{});
     if (e != hipSuccess) return e;
