@@ -21,14 +21,16 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 
 
-def kernel_algorithmic_bytes(name: str, n: int, L: int, theta: float, bits: int) -> float:
+def kernel_algorithmic_bytes(name: str, n: int, L: int, theta: float, bits: int, launched=("decode",)) -> float:
     """Bytes a kernel has to read plus write once for the n-element gradient, per launch: its inputs and
-    outputs at their stored width (fp32 gradient, float2 bins, float2 intermediate, packed bitmap + codes)."""
+    outputs at their stored width (fp32 gradient, float2 bins, float2 intermediate, packed bitmap + codes).
+    launched: the kernels of the step; without a "decode" among them the inverse's first pass reads the records."""
     C = (n + L - 1) // L
     bins = C * (L // 2 + 1)
     spec = 8.0 * bins                       # one pass over the spectrum
     k = C * round(theta * (L // 2 + 1))
     payload = bins / 8.0 + 2.0 * k * bits / 8.0   # bitmap + codes
+    index = 8.0 * bins / 32.0                     # a bitmap word and the bits before it
     table = {
         "rfft_pass_a": 4.0 * n + 4.0 * C * L,     # gradient in, intermediate out
         "rfft_pass_b": 4.0 * C * L + spec,        # intermediate in, spectrum out
@@ -39,8 +41,9 @@ def kernel_algorithmic_bytes(name: str, n: int, L: int, theta: float, bits: int)
         "collect": spec,
         "emit": spec + payload,
         "group_prefix": bins / 8.0 + bins / (8.0 * 16),
+        "bitmap_table": bins / 8.0 + index,
         "decode": payload + spec,
-        "irfft_pass_b": spec + 4.0 * C * L,
+        "irfft_pass_b": (spec if "decode" in launched else payload - bins / 8.0 + index) + 4.0 * C * L,
         "irfft_pass_a": 4.0 * C * L + 4.0 * n,
         "irfft_small": spec + 4.0 * n,
     }
@@ -110,15 +113,16 @@ def measure_topk(fftsp, torch, gd, out, n, L, theta, bits, steps, stream):
                     "here; tests/test_oracle_topk.py pins the ordering of the paper's figure on a signal with a trend"}
 
 
-def half_kernel_bytes(name: str, n: int, L: int, theta: float, bits: int) -> float:
+def half_kernel_bytes(name: str, n: int, L: int, theta: float, bits: int, launched) -> float:
     """The same for the half-precision variant: intermediate and spectrum are binary16 pairs (4 bytes per value)."""
     C = (n + L - 1) // L
     bins = C * (L // 2 + 1)
     spec, mid = 4.0 * bins, 2.0 * C * L
     payload = bins / 8.0 + 2.0 * C * round(theta * (L // 2 + 1)) * bits / 8.0
+    index = 8.0 * bins / 32.0
     table = {"rfft_pass_a": 4.0 * n + mid, "rfft_pass_b": mid + spec, "collect": spec, "emit": spec + payload,
-             "group_prefix": bins / 8.0 + bins / (8.0 * 16), "decode": payload + spec, "irfft_pass_b": spec + mid,
-             "irfft_pass_a": mid + 4.0 * n}
+             "group_prefix": bins / 8.0 + bins / (8.0 * 16), "decode": payload + spec, "bitmap_table": bins / 8.0 + index,
+             "irfft_pass_b": (spec if "decode" in launched else payload - bins / 8.0 + index) + mid, "irfft_pass_a": mid + 4.0 * n}
     return table.get(name, 0.0)
 
 
@@ -153,7 +157,7 @@ def measure_half(fftsp, torch, gd, out, n, L, theta, bits, scale_log2, steps, st
     fftsp.profile_enable(False)
     us = {k: v[1] * 1e3 / v[0] for k, v in kern.items()}
     dom = max(us, key=us.get)
-    dom_bytes = half_kernel_bytes(dom, n, L, theta, bits)
+    dom_bytes = half_kernel_bytes(dom, n, L, theta, bits, us)
     s = (steps - 1) % len(gd)
     src = gd[s].cpu().numpy().astype(np.float64)
     alpha = float(np.linalg.norm(out[s].cpu().numpy() - src) / np.linalg.norm(src))
@@ -173,9 +177,9 @@ def measured_traffic(kernel: str):
     """(HBM bytes per launch, name of the summary) of `kernel` from the committed rocprofv3 --pmc summary
     (FETCH_SIZE + WRITE_SIZE, each scaled by the plain-copy calibration stated in that file), or (None, None) if the
     summary does not cover it.  The figure belongs to the build the summary was taken from, not to this run."""
-    names = {"rfft_pass_a": "k_fwd_a", "rfft_pass_b": "k_fwd_b", "irfft_pass_b": "k_inv_b", "irfft_pass_a": "k_inv_a",
+    names = {"rfft_pass_a": "k_fwd_a", "rfft_pass_b": "k_fwd_b", "irfft_pass_b": "k_receive_b", "irfft_pass_a": "k_inv_a",
              "rfft_fused": "k_fused_fwd", "irfft_fused": "k_fused_inv", "collect": "k_collect", "emit": "k_emit",
-             "decode": "k_decode"}
+             "decode": "k_decode", "bitmap_table": "k_bitmap_table"}
     rel = os.path.join("profiles", "codec_config3_hbm_traffic.txt")
     try:
         for line in open(os.path.join(ROOT, rel)):
@@ -336,15 +340,17 @@ def main() -> int:
     dom = max(kern.items(), key=lambda kv: kv[1][1])
     dom_name, (dom_calls, dom_ms) = dom
     dom_avg_s = dom_ms * 1e-3 / dom_calls
-    dom_io = kernel_algorithmic_bytes(dom_name, n, L, args.theta, bits)
+    dom_io = kernel_algorithmic_bytes(dom_name, n, L, args.theta, bits, kern)
     kernels_us = {k: round(v[1] * 1e3 / v[0], 2) for k, v in kern.items()}
-    kernels_gbs = {k: round(kernel_algorithmic_bytes(k, n, L, args.theta, bits) / (v[1] * 1e-3 / v[0]) / 1e9, 1)
+    kernels_gbs = {k: round(kernel_algorithmic_bytes(k, n, L, args.theta, bits, kern) / (v[1] * 1e-3 / v[0]) / 1e9, 1)
                    for k, v in kern.items() if kernel_algorithmic_bytes(k, n, L, args.theta, bits) > 0}
     # The roofline figure is the path's own: algorithmic bytes of the method per gradient element (gradient in and
     # out, packed bytes out and in; not a transform's intermediate) times the elements one step processes, over the
     # step's duration.  The dominant kernel's share of it: the bytes of that definition that this kernel moves.
     share = {"rfft_fused": 4.0 * n, "rfft_pass_a": 4.0 * n, "irfft_fused": 4.0 * n, "irfft_pass_a": 4.0 * n,
              "emit": p * n, "decode": p * n}
+    if "decode" not in kern:
+        share["irfft_pass_b"] = p * n
     dom_algo = share.get(dom_name, 0.0)
     traffic, traffic_src = measured_traffic(dom_name)
 

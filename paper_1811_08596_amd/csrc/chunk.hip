@@ -11,10 +11,10 @@
 // Between the two ends nothing leaves the workgroup: no spectrum, no histogram and no candidate list in memory, and one
 // launch where the per-tile kernels (codec.hip) take ten.  The transform's arithmetic is that of fft_core.h.
 //
-// What bounds it: vector instruction issue (chunks of 2^12, 10-bit codes: 145 instructions per bin sending, about half of them
-// transform and split, 98 receiving; the vector units are busy 58 and 56 % of the time) and, for the longest chunks, the few
-// waves one workgroup per compute unit leaves.  Measured on 25.6 M samples, compress + decompress, against the per-tile kernels
-// with their ten sweeps and 16 KiB of histogram per chunk: L = 2^12 636 -> 123 us, one chunk of 2^10 91 -> 22 us.
+// What bounds it: vector instruction issue (chunks of 2^12, 10-bit codes of 15 % of the bins: 114 instructions per bin sending, more than
+// half of them transform and split, 101 receiving; the vector units are busy 59 and 65 % of the time) and, for the longest chunks, the
+// few waves one workgroup per compute unit leaves.  Measured on 25.6 M samples, compress + decompress, against the per-tile kernels
+// with their ten sweeps and 16 KiB of histogram per chunk: L = 2^12 636 -> 98 us, one chunk of 2^10 91 -> 22 us.
 //
 // A workgroup holds 2^LOGE complex points, i.e. one chunk, or several when they are short.  Every chunk belongs to a
 // group of WAVES waves.  Up to M = 1024 that is a single wave: waves then share nothing but the twiddle table and run

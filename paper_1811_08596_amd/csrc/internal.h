@@ -136,6 +136,7 @@ struct Workspace {
                       //                     (shares its bytes with mid)
     size_t prefix;    // u32[C][ceil(W/16)]  set bits before each group of 16 bitmap words (decode)
     size_t spec;      // float2[C][padded_bins(L)]  spectrum, each chunk on a 128-byte boundary
+                      //                        (receivers that make none: the bitmaps' table, uint2[C][M/32 + 2])
     size_t mid;       // float2[C][L/2] intermediate of the two-pass FFT
     size_t total;
 };
