@@ -1166,7 +1166,7 @@ constexpr int GROUP_WORDS = 16;  // one wave of the decode kernel covers 512 bin
 // Number of set bits before each group of 16 bitmap words of a record (the prefix sum of Sec. 3.2's status vector, kept at the
 // granularity a wave needs), for the part-th kPrefixWords words; the words before them are counted again, eight loads in flight.
 // The last part checks the headers and leaves the verdict in *verdict.  A workgroup per record took, us: sixty of 2^20 bins (Top-k)
-// 9.1 -> 7.6, ResNet-50's tensors 11.7 -> 7.7, eight peers' sixty of 2^19 15.6 -> 16.6.
+// 9.1 -> 6.7, ResNet-50's tensors 11.7 -> 7.7, eight peers' sixty of 2^19 15.6 -> 16.0.
 constexpr int kPrefixQuads = 4;  // four words each: what a lane has in flight
 constexpr uint32_t kPrefixWords = 4u * kPrefixQuads * RT;
 __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ record,
@@ -1174,7 +1174,8 @@ __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ st
                                                   const HeaderInfo& hdr, uint32_t part, uint32_t* __restrict__ gprefix,
                                                   uint32_t* __restrict__ verdict)
 {
-    __shared__ uint32_t own[kPrefixQuads][RW], earlier[RW];
+    __shared__ uint32_t own[kPrefixQuads * RW], earlier[RW];
+    static_assert(kPrefixQuads * RW == 64, "a lane to each of a part's sums");
     static_assert(GROUP_WORDS == 16, "a group is four lanes");
     if (part * kPrefixWords >= W) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1202,25 +1203,24 @@ __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ st
 #pragma unroll
     for (int i = 0; i < kPrefixQuads; ++i) {
         incl[i] = wave_scan_incl(sum[i]);
-        if (lane == 63) own[i][wave] = incl[i];
+        if (lane == 63) own[i * RW + wave] = incl[i];
     }
-    before = wave_sum(before);
-    if (lane == 63) earlier[wave] = before;
+    if (part) {
+        before = wave_sum(before);
+        if (lane == 63) earlier[wave] = before;
+    }
     __syncthreads();
+    // every wave scans the sums for itself: read one by one they were 64 LDS reads a wave
     uint32_t run = 0;
-#pragma unroll
-    for (int i = 0; i < RW; ++i) run += earlier[i];
+    if (part) run = wave_sum(lane < RW ? earlier[lane] : 0u);
+    const uint32_t one = own[lane], upto = wave_scan_incl(one);
 #pragma unroll
     for (int i = 0; i < kPrefixQuads; ++i) {
-        uint32_t here = run + incl[i] - sum[i];
-#pragma unroll
-        for (int j = 0; j < RW; ++j) {
-            if (j < wave) here += own[i][j];
-            run += own[i][j];
-        }
+        const uint32_t here = run + (uint32_t)__builtin_amdgcn_readlane((int)(upto - one), i * RW + wave) + incl[i] - sum[i];
         const uint32_t q = from + (uint32_t)(i * RT + tid);
         if ((q & 3u) == 0u && 4u * q < W) gprefix[q >> 2] = here;
     }
+    run += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
     if ((part + 1u) * kPrefixWords >= W && tid == 0) *verdict = record_verdict(record, stream, first_of_stream, run, k, word3, hdr);
 }
 inline uint32_t prefix_parts(uint32_t W) { return (W + kPrefixWords - 1u) / kPrefixWords; }

@@ -42,7 +42,7 @@ __device__ __forceinline__ void bitmap_part(const uint8_t* __restrict__ stream, 
                                             uint32_t* __restrict__ verdict)
 {
     __shared__ uint32_t own[kTableWaves], earlier[kTableWaves];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t parts = table_parts(logM);
     const uint4* quads = reinterpret_cast<const uint4*>(record + 16);
     const uint32_t words = 1u << (logM - 5), at = part * kTableLanes + (uint32_t)tid;  // this lane's four
@@ -59,12 +59,10 @@ __device__ __forceinline__ void bitmap_part(const uint8_t* __restrict__ stream, 
         earlier[wave] = before;
     }
     __syncthreads();
-    uint32_t run = incl - sum, all = 0;
-#pragma unroll
-    for (int i = 0; i < kTableWaves; ++i) {
-        run += earlier[i] + (i < wave ? own[i] : 0u);
-        all += earlier[i] + own[i];
-    }
+    // every wave sums for itself, a lane to each of the others' sums
+    const uint32_t one = lane < kTableWaves ? own[lane] : 0u, upto = wave_scan_incl(one), base = wave_sum(lane < kTableWaves ? earlier[lane] : 0u);
+    const uint32_t all = base + (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    const uint32_t run = base + (uint32_t)__builtin_amdgcn_readlane((int)(upto - one), wave) + incl - sum;
     if (in) {
         const uint32_t r1 = run + (uint32_t)__popc(w.x), r2 = r1 + (uint32_t)__popc(w.y), r3 = r2 + (uint32_t)__popc(w.z);
         uint4* p = reinterpret_cast<uint4*>(out + 4u * at);  // the stride is even
