@@ -622,8 +622,9 @@ int fftsp_decompress_accumulate(const void* const* d_packed, int npeers, size_t 
     a.sstride = padded_bins(p.L);
     a.pair_log = fft_pair_log(p.logL);
     hipError_t e;
-    // a sum of one: adding to zero changes nothing, there are no negative zeros among decoded values
-    if (npeers == 1 && receive_without_spectrum(p, peers.p[0], a, d_grad_out, scale, ws, pw.verd, t, s, &e)) return hip_status(e);
+    // a sum of one: adding to zero changes nothing, there are no negative zeros among decoded values but the raw ones
+    if (npeers == 1 && p.bits != 32 && receive_without_spectrum(p, peers.p[0], a, d_grad_out, scale, ws, pw.verd, t, s, &e))
+        return hip_status(e);
     e = launch_decode_peers(peers, npeers, a, spec, ws, p.ws, pw, s);
     if (e == hipSuccess) e = inverse_of_decoded(p, spec, a.sstride, a.pair_log, d_grad_out, ws, t, scale, s);
     return hip_status(e);

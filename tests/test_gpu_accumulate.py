@@ -65,6 +65,26 @@ def test_single_peer_equals_decompress(dev, ref):
     assert st == 0 and np.array_equal(a.view(np.uint32), b.view(np.uint32))
 
 
+@pytest.mark.parametrize("n,L", [(300, 256), (32768 + 9, 32768), (65536, 65536), (3 * 131072 - 7, 131072), (1 << 19, 1 << 19), (1 << 20, 1 << 20)])
+def test_single_peer_with_raw_codes_is_added_to_zero(dev, ref, n, L):
+    """raw codes carry the sign of a zero, and 0 + -0 is 0: the samples are those of the summed spectrum, bit for bit"""
+    torch, f, C = dev.torch, dev.f, -(-n // L)
+    rng = np.random.default_rng(L)
+    for name, signs in (("re", (1, 0)), ("both", (1, 1)), ("random", None)):
+        neg = rng.integers(0, 2, (C, L // 2 + 1, 2)) if signs is None else np.broadcast_to(signs, (C, L // 2 + 1, 2))
+        spec = np.where(neg, np.float32(-0.0), np.float32(0.0)).astype(np.float32).reshape(-1)
+        assert np.signbit(spec).any() and not spec.any()
+        packed = dev.to_dev(ref.encode_spectrum(spec, n, L, 1.0, 32))
+        ws = dev.workspace(f.workspace_bytes_accumulate(n, L, 32, 1))
+        out, want, total = torch.empty(n, device="cuda"), torch.empty(n, device="cuda"), torch.empty(C * (L + 2), device="cuda")
+        f.decompress_accumulate([packed], packed.numel(), 1.0, out, L, 1.0, 32, ws)
+        f.decode_accumulate_spectrum([packed], packed.numel(), n, L, 1.0, 32, total, ws)
+        assert not total.view(torch.int32).any()
+        f.irfft(total, n, L, want, ws)
+        print(f"n={n} L={L} signs {name}: {int((out.view(torch.int32) != want.view(torch.int32)).sum())} samples differ", flush=True)
+        assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+
+
 def test_sum_order_is_the_list_order(dev, ref):
     L, n = 32, 32
     B = L // 2 + 1
