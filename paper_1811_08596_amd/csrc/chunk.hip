@@ -364,6 +364,12 @@ __host__ __device__ constexpr uint32_t most_packed(uint32_t units, int bits)
 {
     return bits == 32 ? 0u : units / (!REAL && WAVES > 1 ? 2u : (bits == 8 ? 5u : 3u));
 }
+// Whether a kernel's survivors move.  Top-k has a kernel for each way: one that holds both is slower on either.
+// Senders of 8-bit codes in us, no survivor moved anywhere -> one kernel -> two.  80 % kept: 8 chunks of 2^10
+// 6.61 -> 6.67 -> 6.63, 256 of 2^14 14.4 -> 14.6 -> 14.4, 25 M samples in chunks of 2^12 39.9 -> 40.6 -> 40.0, of 2^15 67.6 -> 68.5 -> 67.6;  10 %
+// kept, moved: 7.07 -> 6.70 -> 6.66, 14.2 -> 14.05 -> 13.8, 38.0 -> 37.0 -> 36.7, 66.1 -> 65.0 -> 64.0.  Transforms are longer and gain
+// nothing (2^14 64.3 -> 65.2, 2^15 85.5 -> 87.1, 80 % kept), and the tensors of one launch differ: those decide as they run.
+enum Packing { kByRow, kMoved, kEither };
 
 // Steps 2-4 of the sender for one chunk whose bins (samples) lie in the registers of a group of WAVES waves:
 // z[r]: bin (wave * R + r) * 64 + lane (lane < LR); zn (TAIL): the chunk's last bin, the same value in every lane.
@@ -371,7 +377,7 @@ __host__ __device__ constexpr uint32_t most_packed(uint32_t units, int bits)
 // the shortest chunks.  wg_most: a word of the workgroup, zero on entry, through which several groups of several waves agree on
 // the path they take together.
 // runs: many of the samples are zero.  live = false groups (no such chunk) write nothing; groups of several waves call this together.
-template <bool REAL, int R, bool TAIL, int LR, int WAVES, int GROUPS, int HB>
+template <bool REAL, int R, bool TAIL, int LR, int WAVES, int GROUPS, int HB, Packing PACKING>
 __device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z)[R], typename Elem<REAL>::T zn, uint32_t* lds,
                                                 uint32_t room, uint32_t* image, GroupScratch& gs, uint32_t* wg_most, int tid,
                                                 const PackArgs& a, uint32_t word3, uint8_t* __restrict__ record, bool live,
@@ -675,10 +681,11 @@ __device__ __forceinline__ void select_and_pack(const typename Elem<REAL>::T (&z
         }
         if (fn && lane == 0) put(mode, zn, run);
     };
-    bool packed = false;
-    if constexpr (HB != 0) {
+    bool packed = PACKING == kMoved;
+    if constexpr (PACKING != kByRow) {
         const uint32_t from = (room - CODES * a.k) & ~1u;
-        packed = a.k <= most_packed<REAL, WAVES>((uint32_t)(R * NL), bits) && (uint32_t)(image - lds) + image_words + CODES * a.k < room;
+        if (PACKING == kEither)
+            packed = a.k <= most_packed<REAL, WAVES>((uint32_t)(R * NL), bits) && (uint32_t)(image - lds) + image_words + CODES * a.k < room;
         if (packed) {
             typename Elem<REAL>::T* kept = reinterpret_cast<typename Elem<REAL>::T*>(lds + from);
             uint32_t run = rank;
@@ -795,7 +802,7 @@ __device__ __forceinline__ void compress_workgroup(const float* __restrict__ in,
     auto pack = [&](int i, const float2 (&z)[G::R], float2 zn, uint32_t* image) __attribute__((always_inline)) {
         const int b = group * G::CPW + i;
         const bool live = where.exists(b);
-        select_and_pack<false, G::R, true, G::LR, G::WAVES, G::GROUPS, G::HB>(
+        select_and_pack<false, G::R, true, G::LR, G::WAVES, G::GROUPS, G::HB, G::HB ? kEither : kByRow>(
             z, zn, mine, (uint32_t)ROOM / 4u, image, gs, wg_most, tid, a, a.word3, records + (live ? where.record(b) : 0), live);
     };
     if constexpr (G::HB == 0) {
@@ -897,7 +904,7 @@ struct TopkGeo {
         return image > hist ? image : hist;
     }
 };
-template <int LOGL>
+template <int LOGL, Packing PACKING>
 __global__ __launch_bounds__(TopkGeo<LOGL>::NT) void k_topk_compress(const float* __restrict__ in, size_t n, size_t C, PackArgs a,
                                                                      uint8_t* __restrict__ stream, uint8_t* __restrict__ records,
                                                                      HeaderInfo hdr, uint32_t* __restrict__ ctl, uint32_t region)
@@ -923,9 +930,9 @@ __global__ __launch_bounds__(TopkGeo<LOGL>::NT) void k_topk_compress(const float
         z[r] = 0.f;
         if (i < present) z[r] = src[i];
     }
-    select_and_pack<true, G::R, false, G::LR, G::WAVES, G::GROUPS, G::HB>(z, 0.f, mine, region / 4u, mine + (G::HB ? kListCap : 0u), gs[group],
-                                                                          reinterpret_cast<uint32_t*>(gs + G::GROUPS), tid, a,
-                                                                          a.word3, records + c * (size_t)a.S, true, present < (uint32_t)G::L);
+    select_and_pack<true, G::R, false, G::LR, G::WAVES, G::GROUPS, G::HB, PACKING>(
+        z, 0.f, mine, region / 4u, mine + (G::HB ? kListCap : 0u), gs[group], reinterpret_cast<uint32_t*>(gs + G::GROUPS), tid, a, a.word3,
+        records + c * (size_t)a.S, true, present < (uint32_t)G::L);
 }
 
 // ---------------------------------------------------------------- receiver ----
@@ -1323,11 +1330,13 @@ hipError_t topk_compress_as(const float* in, size_t n, const CodecArgs& a, uint8
     using G = TopkGeo<LOGL>;
     // records are whole 16 bytes; of one with 32-bit codes only header and bitmap pass through LDS
     const size_t image = a.bits == 32 ? 16 + ((size_t)a.L / 8 + 15) / 16 * 16 : a.S;
-    const size_t region = G::region(image, a.k <= G::most_moved(a.bits) ? a.k : 0u), lds = G::SCRATCH + G::GROUPS * region;
+    const bool moved = G::HB && a.k <= G::most_moved(a.bits);  // and the region is made to hold them
+    const size_t region = G::region(image, moved ? a.k : 0u), lds = G::SCRATCH + G::GROUPS * region;
     constexpr size_t longest = (16 + 4 * ((G::L + 31) / 32) + 2 * (size_t)G::L + 15) / 16 * 16;  // all kept, 16-bit codes
-    const hipError_t e = allow_lds(k_topk_compress<LOGL>, G::SCRATCH + G::GROUPS * G::region(longest, G::most_moved(16)));
+    auto kern = moved ? k_topk_compress<LOGL, G::HB ? kMoved : kByRow> : k_topk_compress<LOGL, kByRow>;
+    const hipError_t e = allow_lds(kern, G::SCRATCH + G::GROUPS * G::region(longest, G::most_moved(16)));
     if (e != hipSuccess) return e;
-    FFTSP_LAUNCH("topk_compress", k_topk_compress<LOGL>, dim3((unsigned)((a.C + G::GROUPS - 1) / G::GROUPS)), dim3(G::NT), lds, s, in,
+    FFTSP_LAUNCH("topk_compress", kern, dim3((unsigned)((a.C + G::GROUPS - 1) / G::GROUPS)), dim3(G::NT), lds, s, in,
                  n, a.C, pack_args(a), stream, records, header_info(a, 1), ctl, (uint32_t)region);
     return hipGetLastError();
 }
