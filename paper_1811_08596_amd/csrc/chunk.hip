@@ -356,13 +356,19 @@ __device__ __forceinline__ float2 nyquist_bin(const float2* d, int base)
 // Packing a row of bins costs the same however few of them survive.  Where at most this many do, and the region has room behind
 // the image, the survivors first move there, next to each other.
 // Senders of 25 M normal samples, row by row -> next to each other, us, at 15 %, 30 %, 50 % kept.  Transforms, 10-bit codes: L = 2^11
-// 51.5 -> 49.3, 51.6 -> 50.6, 52.8 -> 52.8;  2^12 62.9 -> 56.0, 63.5 -> 60.0, 65.0 -> 63.4;  2^13 58.8 -> 56.1, 61.3 -> 59.1, 61.2 -> 61.0;
-// 2^15 90.3 -> 81.4, 90.6 -> 83.8, 92.2 -> 88.3; at 75 % none gains.  Top-k, 10 bits: 2^10 57.8 -> 52.6, 58.7 -> 55.4, 58.8 -> 59.1;
-// 2^12 43.9 -> 38.5, 44.7 -> 41.0, 44.9 -> 45.6;  8-bit codes, which are stores and no atomics: 38.0 -> 37.7, 38.2 -> 38.8, 38.2 -> 38.7.
+// 51.8 -> 48.5, 52.5 -> 50.4, 53.3 -> 53.3;  2^12 55.5 -> 51.7, 56.3 -> 53.7, 57.0 -> 56.7;  2^13 61.1 -> 57.9, 63.0 -> 60.8, 64.0 -> 63.5;
+// 2^15 86.7 -> 80.2, 87.6 -> 83.1, 89.9 -> 87.8; at 75 % none gains.  8-bit codes are stores and no atomics; at 15 %, 30 %, 40 %, 50 %: 2^11
+// 48.0 -> 47.6, 48.9 -> 48.4, 48.6 -> 49.3, 49.3 -> 50.4;  2^12 51.3 -> 49.5, 51.4 -> 50.7, 51.2 -> 51.3, 52.4 -> 52.9;  2^13 57.7 -> 56.9, 58.7 ->
+// 57.8, 58.7 -> 58.5, 58.1 -> 58.5;  2^15 81.5 -> 79.3, 82.1 -> 81.6, 83.3 -> 83.0, 83.2 -> 84.1.  Top-k, 10 bits, 15 %, 30 %, 50 %: 2^10 57.8 ->
+// 52.6, 58.7 -> 55.4, 58.8 -> 59.1;  2^12 43.9 -> 38.5, 44.7 -> 41.0, 44.9 -> 45.6;  8-bit codes, 10 %, 20 %, 30 %: 2^10 51.3 -> 50.9, 51.6 -> 52.3,
+// 52.8 -> 53.6;  2^12 38.6 -> 37.5, 38.6 -> 38.1, 39.4 -> 39.4;  2^15 66.4 -> 64.3, 66.5 -> 65.4, 67.2 -> 67.0.
 template <bool REAL, int WAVES>
 __host__ __device__ constexpr uint32_t most_packed(uint32_t units, int bits)
 {
-    return bits == 32 ? 0u : units / (!REAL && WAVES > 1 ? 2u : (bits == 8 ? 5u : 3u));
+    if (bits == 32) return 0u;
+    const bool several = !REAL && WAVES > 1;
+    if (bits == 8) return several ? units * 2u / 5u : units / (REAL ? 5u : 3u);
+    return units / (several ? 2u : 3u);
 }
 // Whether a kernel's survivors move.  Top-k has a kernel for each way: one that holds both is slower on either.
 // Senders of 8-bit codes in us, no survivor moved anywhere -> one kernel -> two.  80 % kept: 8 chunks of 2^10
