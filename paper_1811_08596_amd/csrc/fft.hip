@@ -1021,7 +1021,7 @@ hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spe
     // wants neither
     if ((hist != nullptr) != (pair_spec != 0)) return hipErrorInvalidValue;
     const int logN1 = (logM + 1) / 2, logN2 = logM / 2;
-    if (!only_if && short_forward(logM, C)) {
+    if (!only_if && short_forward(logM, C, 0)) {
         if (pair_log && pair_spec) *pair_log = logN1;
         return launch_short_rfft(in, n, logM, C, sp, sstride, mid, t, hist, zero_ptr, (uint32_t)zero_words, s);
     }
@@ -1198,7 +1198,7 @@ hipError_t launch_rfft_half(const float* in, size_t n, int logL, size_t C, void*
     const int logN1 = (logM + 1) / 2, logN2 = logM / 2;
     hipError_t e;
     const float lift = half_lift(logM);
-    if (short_forward(logM, C)) {
+    if (short_forward(logM, C, 1)) {
         *pair_log = logN1;
         return launch_short_rfft_half(in, n, logM, C, sp, sstride, md, t, hist, zero_ptr, (uint32_t)zero_words, in_scale * lift, 1.0f / lift, s);
     }

@@ -5,7 +5,7 @@
 namespace fftsp {
 
 // whether a call of C chunks of 2^(logM+1) samples, or a launch set of tensors, takes these kernels
-bool short_forward(int logM, size_t C);
+bool short_forward(int logM, size_t C, int half);
 bool short_forward(const LongBatch& b);
 bool short_inverse(int logM, size_t C);
 bool short_inverse(const LongBatch& b);

@@ -151,3 +151,35 @@ def test_receivers_take_as_many_chunks_as_senders(runtime, tmp_path):
              ["fftsp_compress", ["big", n, 32, 0.3, 8, "big", "big", "big", "big", None]]]
     status, _ = calls_made(runtime, tmp_path, calls)
     assert status == [0] * len(calls)
+
+
+def kernels(runtime, tmp_path, calls):
+    """names of the kernels each call launches"""
+    made = []
+    for i, call in enumerate(calls):
+        d = tmp_path / str(i)
+        d.mkdir()
+        status, rows = calls_made(runtime, d, [call])
+        assert status == [0]
+        made.append([kernel for what, kernel, _, _ in rows if what == "launch"])
+    return made
+
+
+@pytest.mark.parametrize("logL, half, most", [(16, 0, 32), (17, 0, 24), (18, 0, 12), (19, 0, 6), (20, 0, 2), (21, 0, 1), (16, 1, 32), (18, 1, 8)])
+def test_senders_leave_the_small_tiles_where_they_stop_paying(runtime, tmp_path, logL, half, most):
+    L = 1 << logL
+    calls = [["fftsp_compress_h", ["big", C * L, L, 0.5, 8, 0, "big", "big", "big", "big", None]] if half else compress(C * L, L, 0.5)
+             for C in (most, most + 1)]
+    small, large = kernels(runtime, tmp_path, calls)
+    assert any("k_fwd_a_short" in k for k in small) and not any("short" in k for k in large)
+
+
+@pytest.mark.parametrize("sizes, send, receive_a", [
+    ([1 << 18] * 8, True, True), ([1 << 18] * 9, False, False), ([1 << 17] * 24, True, True), ([1 << 17] * 25, False, True),
+    ([1 << 20] * 2, True, True), ([1 << 20] * 3, False, False), ([1 << 16] * 30 + [1 << 20], True, True),
+    ([1 << 17] * 8 + [1 << 18] * 6, False, True), ([1 << 16] * 20 + [1 << 18] * 6, True, True), ([1 << 16] * 4 + [1 << 21], True, True),
+    ([1 << 16] * 5 + [1 << 21], False, True), ([1 << 16] * 20 + [1 << 18] * 10, False, False), ([1 << 16] * 21 + [1 << 18] * 10, False, True)])
+def test_tensors_leave_the_small_tiles_where_they_stop_paying(runtime, tmp_path, sizes, send, receive_a):
+    sender, receiver = kernels(runtime, tmp_path, segments(sizes, 0.5, 8))
+    assert any("k_fwd_a_long_short" in k for k in sender) == send
+    assert any("k_inv_a_long_short" in k for k in receiver) == receive_a
