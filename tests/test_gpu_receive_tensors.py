@@ -22,10 +22,29 @@ def dev():
     return Device()
 
 
+# launch sets of few tiles, which go through csrc/short.hip wholly or in one pass
+SHORT_SETS = {
+    "one_of_2^21": [(1 << 21) - 9, 77],                                    # the tallest rows there
+    "2^18_and_2^19": [(1 << 18) - 3] * 7 + [(1 << 19) - 8, 1 << 19],       # more than 128 tiles of tall tensors: pass A of the others
+    "2^21_and_short_ones": [1 << 21] + [(1 << 16) - 1] * 5,                # more than 144 tiles, most of them tall: the others' forward passes
+    "2^16_and_a_tall_one": [1 << 16] * 20 + [(1 << 18) - 1],
+}
+
+
 @pytest.mark.parametrize("bits", (3, 8, 9, 15))
 @pytest.mark.parametrize("name", SETS)
 def test_tensors_and_the_spectra_they_leave_out(dev, ref, name, bits):
-    torch, f, sizes = dev.torch, dev.f, SETS[name]
+    check(dev, ref, name, SETS[name], bits)
+
+
+@pytest.mark.parametrize("bits", (8, 16, 32))
+@pytest.mark.parametrize("name", SHORT_SETS)
+def test_short_launch_sets(dev, ref, name, bits):
+    check(dev, ref, name, SHORT_SETS[name], bits)
+
+
+def check(dev, ref, name, sizes, bits):
+    torch, f = dev.torch, dev.f
     offs = [int(v) for v in np.concatenate([[0], np.cumsum(sizes)])]
     g = torch.randn(offs[-1], device="cuda", generator=torch.Generator(device="cuda").manual_seed(bits)) * 1e-2
     ws = dev.workspace(f.workspace_bytes_segments(offs, bits))
