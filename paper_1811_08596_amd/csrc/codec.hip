@@ -1680,8 +1680,15 @@ static Extent extent_of(const CodecArgs& a)
 static bool find_in_collect(const Extent& x) { return x.tiles <= 1024; }
 // k_emit finds the threshold itself, every workgroup all of it, where the launch saved weighs more.  Senders in us, k_resolve /
 // without: chunks of 2^16 (17 tiles) 68 tiles 24.3 / 22.7, 374 34.0 / 32.5, 782 40.7 / 40.5, 1088 47.7 / 47.9;  2^17 (33) 66 23.8 / 22.3,
-// 528 34.4 / 33.9, 1056 46.7 / 47.2;  2^18 (65) 65 25.4 / 24.3, 390 34.4 / 34.1, 520 36.4 / 37.2.
-static bool resolve_in_emit(const Extent& x) { return x.most <= kMergedTiles && x.tiles <= 512; }
+// 528 34.4 / 33.9, 1056 46.7 / 47.2;  2^18 (65) 65 25.4 / 24.3, 390 34.4 / 34.1, 520 36.4 / 37.2.  Binary16: 2^15 (9 tiles) 63 29.7 / 28.2, 495 33.8 / 32.1;
+// 2^16 493 35.5 / 34.1;  2^18 260 30.0 / 29.5, 455 34.1 / 34.4.  Tensors: 2^16 493 38.9 / 37.5;  2^17 495 38.9 / 37.6;  2^18 65 28.3 / 27.1, 455 41.2 / 40.9.
+// Top-k: 2^16 (32) 64 34.5 / 32.8, 512 36.1 / 35.2;  2^17 (64) 64 35.1 / 33.9, 256 35.5 / 34.3, 384 36.4 / 36.4, 512 37.0 / 36.9; but where the threshold's
+// bucket is crowded and tiles have more candidates than are held (30 % of normal samples), 2^16 64 37.7 / 35.9, 512 39.8 / 39.1;  2^17 64 38.4 /
+// 39.2, 256 39.5 / 40.9, 384 40.2 / 42.6, 512 40.2 / 42.9.  So long chunks of samples leave off earlier.
+static bool resolve_in_emit(const Extent& x, int time_domain)
+{
+    return x.most <= kMergedTiles && x.tiles <= (time_domain && x.most > 32 ? 256 : 512);
+}
 // In k_decode it is the bitmap up to the tile, at most 256 bytes for each tile of the chunk, to read beside the tile's codes.
 // Decompress: one chunk of 2^16 21.7 -> 17.7 us, 2^23 samples in chunks of 2^20 (2056 tiles) 49.4 -> 48.8, 2^24 76.6 -> 77.8, one
 // chunk of 2^22 (1025 tiles) 50.3 -> 52.5.  Chunks of a few tiles always: Top-k of 2^24 samples in chunks of 2^12 32.8 -> 16.2.
@@ -1721,7 +1728,7 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
                  a.hdr_theta, a.time_domain ? 1u : 0u, (uint32_t)a.hdr_scale};
     const uint32_t codes_per_bin = a.time_domain ? 1u : 2u;
     const dim3 per_tile((unsigned)x.tiles), per_chunk((unsigned)x.chunks);
-    const bool merged = resolve_in_emit(x);
+    const bool merged = resolve_in_emit(x, a.time_domain);
     uint8_t* clear = merged ? records : nullptr;
     const ResolveArgs ra{a.bits, a.m, a.static_vmax, codes_per_bin};
     auto select = [&](auto table) {

@@ -183,3 +183,10 @@ def test_tensors_leave_the_small_tiles_where_they_stop_paying(runtime, tmp_path,
     sender, receiver = kernels(runtime, tmp_path, segments(sizes, 0.5, 8))
     assert any("k_fwd_a_long_short" in k for k in sender) == send
     assert any("k_inv_a_long_short" in k for k in receiver) == receive_a
+
+
+@pytest.mark.parametrize("L, most", [(1 << 16, 16), (1 << 17, 4)])
+def test_topk_finds_its_threshold_beside_the_codes_in_short_calls(runtime, tmp_path, L, most):
+    calls = [["fftsp_topk_compress", ["big", C * L, L, 0.3, 8, "big", "big", "big", "big", None]] for C in (most, most + 1)]
+    within, beyond = kernels(runtime, tmp_path, calls)
+    assert not any("k_resolve" in k for k in within) and any("k_resolve" in k for k in beyond)
