@@ -325,8 +325,9 @@ __global__ __launch_bounds__(NT) void k_find_bucket(const uint32_t* __restrict__
     if (threadIdx.x == 0) *reinterpret_cast<uint2*>(sel + c * 8) = make_uint2(b.star, b.need);
 }
 
-// Tiles of a chunk whose candidates k_resolve keeps in registers.  Longer chunks go through k_count_digit and k_mark before it.
-constexpr uint32_t kKeptTiles = 513;
+// Tiles of a chunk whose candidates k_resolve keeps in registers.  Longer chunks go through k_count_digit and k_mark before it, and
+// where some of a launch do, so do those of more than kFewTiles beside them.
+constexpr uint32_t kKeptTiles = 513, kFewTiles = 288;
 // Tiles of a chunk up to which k_emit may do k_resolve's work.
 constexpr uint32_t kMergedTiles = 72;
 
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
         if ((mine >> r) & 1u) out[off + prefix_popc(cm[r])] = make_uint2(key[r], vb[r]);
         off += (uint32_t)__popcll(cm[r]);
     }
-    if (tid == 64 && at.Tn > kKeptTiles)  // counters of k_count_digit
+    if (tid == 64 && at.Tn > kFewTiles)  // counters of k_count_digit
         *reinterpret_cast<uint2*>(tscan + (size_t)blockIdx.x * 2) = make_uint2(0u, 0u);
     if (tid == 0) {
         uint32_t* ti = tinfo + (size_t)blockIdx.x * 4;
@@ -460,7 +461,7 @@ constexpr int RT = 1024;           // lanes of the per-chunk workgroups of the d
 constexpr int RW = RT / 64;        // 16 waves
 constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1025
 
-// Chunks of more than kKeptTiles tiles: what k_resolve would do in its two sweeps over the candidates is done before it by
+// Launches with chunks of more than kKeptTiles tiles: what k_resolve would do in its two sweeps over the candidates is done before it by
 // a workgroup per kPartTiles tiles, because a single one is bound by what a compute unit issues (a chunk of 2^22: 35 us).
 // k_count_digit counts the candidates' second digit into the first kHist2Bins words of the chunk's tscan, which k_collect
 // has cleared.  k_mark adds the candidates above the two digits' common prefix to their tiles' counts and maxima and moves
@@ -468,9 +469,11 @@ constexpr int MAX_TILES = ((1 << (kMaxLogL - 1)) + 1 + kTile - 1) / kTile;  // 1
 // Senders in us, without / with: one chunk of 2^22 90 / 70, thirty-three 801 / 785.  Chunks of 512 and 513 tiles no longer come
 // here, since k_resolve holds as many candidates in registers: with / held there, chunks of 2^21 one 50.8 / 48.4, eight 119 / 115,
 // thirty-two 355 / 351; Top-k chunks of 2^20 one 37.0 / 31.0, eight 59.2 / 49.6, thirty-two 117 / 109, sixty 193 / 182.
+// Beside longer chunks, for which the two kernels run anyway, they do better here too: senders of tensors of 2^21 and 2^22 held / here 91.5 /
+// 83.6, of six and one 142 / 132.
 constexpr uint32_t kPartTiles = 64, kPartWave = kPartTiles / (NT / 64);
 inline uint32_t parts_of(uint32_t tiles) { return (tiles + kPartTiles - 1u) / kPartTiles; }
-static_assert(2 * (kKeptTiles + 1) >= (uint32_t)kHist2Bins, "their part of tscan holds the counters");
+static_assert(2 * (kFewTiles + 1) <= (uint32_t)kHist2Bins && 2 * 512 >= kHist2Bins, "a chunk of 512 tiles, the next length, holds the counters");
 template <bool TABLE>
 __device__ __forceinline__ Place part_of(const Shape& u, const TableArg<TABLE>& tab, const LongStarts& at, uint32_t& first)
 {
@@ -634,7 +637,8 @@ __global__ __launch_bounds__(NT) void k_mark(Shape u, const uint32_t* __restrict
 constexpr int kFetch = 9, kFetchMost = 17;
 template <int NW, int FETCH>
 constexpr uint32_t kHeldTiles = 2 * FETCH * NW;
-static_assert(kHeldTiles<16, kFetchMost> >= kKeptTiles && kHeldTiles<NT / 64, kFetch> >= kMergedTiles, "the candidates stay in registers");
+static_assert(kHeldTiles<16, kFetchMost> >= kKeptTiles && kHeldTiles<16, kFetch> == kFewTiles && kHeldTiles<NT / 64, kFetch> >= kMergedTiles,
+              "the candidates stay in registers");
 template <int MOST>
 struct ResolveScratch {
     uint32_t h[kHist2Bins], list[kListCap], list_at[kListCap], list_vb[kListCap];
@@ -694,7 +698,7 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
     const uint2* cd = cand + at.tile0 * (size_t)kTile;
     const uint32_t bstar = sel[c * 8 + 0];
     uint32_t need = sel[c * 8 + 1];
-    const bool counted = !MERGED && Tn > kKeptTiles;  // k_count_digit and k_mark have been here
+    const bool counted = !MERGED && Tn > kHeldTiles<NW, FETCH>;  // k_count_digit and k_mark have been here
 
     // A wave's tiles are wave, wave + NW, ...; lane v has the summary of the v-th, e[v] its first candidates.  Slots behind
     // a tile's last candidate are allocated; what they hold is dropped.
@@ -1754,14 +1758,15 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
             collect(std::false_type{});
         }
         if (merged) return hipGetLastError();
-        if (x.most > kKeptTiles) {
+        const bool counted = x.most > kKeptTiles;
+        if (counted) {
             LongStarts at{};
             uint32_t parts = (uint32_t)x.chunks * parts_of(x.most);
             if constexpr (TABLE) {
                 // the longest tensors are the last ones
                 parts = 0;
                 at.first = a.tab->count;
-                while (at.first > 0 && (1u << a.tab->tab.t[at.first - 1].logM) / (uint32_t)kTile + 1u > kKeptTiles) --at.first;
+                while (at.first > 0 && (1u << a.tab->tab.t[at.first - 1].logM) / (uint32_t)kTile + 1u > kFewTiles) --at.first;
                 for (uint32_t i = at.first; i < a.tab->count; ++i) {
                     at.at[at.count++] = (uint16_t)parts;
                     parts += parts_of((1u << a.tab->tab.t[i].logM) / (uint32_t)kTile + 1u);
@@ -1780,7 +1785,7 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
         constexpr std::integral_constant<int, kFetch> some{};
         if (x.most <= 40u) return resolve(std::integral_constant<int, 4>{}, some);
         if (x.most <= kHeldTiles<8, kFetch>) return resolve(std::integral_constant<int, 8>{}, some);
-        if (x.most <= kHeldTiles<16, kFetch>) return resolve(std::integral_constant<int, 16>{}, some);
+        if (x.most <= kFewTiles || counted) return resolve(std::integral_constant<int, 16>{}, some);
         return resolve(std::integral_constant<int, 16>{}, std::integral_constant<int, kFetchMost>{});
     };
     const hipError_t e = a.tab ? select(std::true_type{}) : select(std::false_type{});
