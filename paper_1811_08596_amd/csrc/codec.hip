@@ -1169,10 +1169,12 @@ constexpr int GROUP_WORDS = 16;  // one wave of the decode kernel covers 512 bin
 
 // Number of set bits before each group of 16 bitmap words of a record (the prefix sum of Sec. 3.2's status vector, kept at the
 // granularity a wave needs), for the part-th kPrefixWords words; the words before them are counted again, eight loads in flight.
+// The word that the Nyquist bin has to itself makes no part of its own: the one before takes it along.
 // The last part checks the headers and leaves the verdict in *verdict.  A workgroup per record took, us: sixty of 2^20 bins (Top-k)
-// 9.1 -> 6.7, ResNet-50's tensors 11.7 -> 7.7, eight peers' sixty of 2^19 15.6 -> 16.0.
+// 9.1 -> 6.7, ResNet-50's tensors 11.7 -> 7.7, eight peers' sixty of 2^19 15.6 -> 14.1 (16.1 with parts of one word).
 constexpr int kPrefixQuads = 4;  // four words each: what a lane has in flight
 constexpr uint32_t kPrefixWords = 4u * kPrefixQuads * RT;
+__host__ __device__ constexpr uint32_t prefix_parts(uint32_t W) { return W < 2u ? 1u : (W + kPrefixWords - 2u) / kPrefixWords; }
 __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ record,
                                                   bool first_of_stream, uint32_t W, uint32_t k, uint32_t word3,
                                                   const HeaderInfo& hdr, uint32_t part, uint32_t* __restrict__ gprefix,
@@ -1181,12 +1183,15 @@ __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ st
     __shared__ uint32_t own[kPrefixQuads * RW], earlier[RW];
     static_assert(kPrefixQuads * RW == 64, "a lane to each of a part's sums");
     static_assert(GROUP_WORDS == 16, "a group is four lanes");
-    if (part * kPrefixWords >= W) return;
+    const uint32_t parts = prefix_parts(W);
+    if (part >= parts) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t* bitmap = reinterpret_cast<const uint32_t*>(record) + 4;
     const uint4* quads = reinterpret_cast<const uint4*>(bitmap);  // records and bitmaps are 16-byte aligned
     const uint32_t whole = W / 4u, from = part * kPrefixQuads * RT;
     auto ones = [](uint4 v) __attribute__((always_inline)) { return (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w)); };
+    const bool last = part + 1u == parts, along = last && W > parts * kPrefixWords;
+    const uint32_t nyquist = along ? scalar_load(bitmap + (W - 1u)) : 0u;
     uint32_t before = 0;
 #pragma unroll 8
     for (uint32_t i = 0; i < part * kPrefixQuads; ++i) before += ones(quads[i * RT + (uint32_t)tid]);
@@ -1225,9 +1230,11 @@ __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ st
         if ((q & 3u) == 0u && 4u * q < W) gprefix[q >> 2] = here;
     }
     run += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-    if ((part + 1u) * kPrefixWords >= W && tid == 0) *verdict = record_verdict(record, stream, first_of_stream, run, k, word3, hdr);
+    if (last && tid == 0) {
+        if (along) gprefix[(W - 1u) / GROUP_WORDS] = run;
+        *verdict = record_verdict(record, stream, first_of_stream, run + (uint32_t)__popc(nyquist), k, word3, hdr);
+    }
 }
-inline uint32_t prefix_parts(uint32_t W) { return (W + kPrefixWords - 1u) / kPrefixWords; }
 
 template <bool TABLE>
 __global__ __launch_bounds__(RT) void k_group_prefix(const uint8_t* __restrict__ stream,
@@ -1828,7 +1835,7 @@ hipError_t launch_decode(const uint8_t* stream_base, const uint8_t* records, con
     uint32_t* gprefix = nullptr;
     if (!prefix_in_decode(x)) {
         gprefix = reinterpret_cast<uint32_t*>(ws_base + w.prefix);
-        const uint32_t parts = prefix_parts(x.most * (uint32_t)(kTile / 32));  // of the longest chunk
+        const uint32_t parts = prefix_parts(a.tab ? (1u << a.tab->tab.t[a.tab->count - 1].logM) / 32u + 1u : u.W);  // of the longest chunk
         if (a.tab)
             FFTSP_LAUNCH("group_prefix", k_group_prefix<true>, dim3((unsigned)x.chunks * parts), dim3(RT), 0, s, stream_base, records, u, h,
                          parts, gprefix, verdicts, ctl, note, table_arg<true>(a.tab));
