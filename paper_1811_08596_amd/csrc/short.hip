@@ -752,34 +752,21 @@ uint32_t starts_of(const LongBatch& b, LongStarts* at, Log&& log)
 // In tiles of 2^13 points, by length: whole calls in us, the kernels of fft.hip / these, 8-bit codes of half of the bins, buffers in turn:
 //   sender:    2^16 64 30.9 / 28.1, 128 37.5 / 35.9, 144 38.6 / 39.2, 192 41.6 / 43.0;  2^17 128 38.3 / 35.6, 192 43.0 / 41.3, 208 44.2 / 44.8;
 //     2^18 128 40.0 / 38.4, 192 44.7 / 44.3, 208 46.1 / 49.3;  2^19 128 41.6 / 38.9, 192 46.4 / 45.5, 224 48.9 / 50.3;  2^20 128 45.7 / 42.4,
-//     192 51.8 / 52.3;  2^21 128 54.5 / 49.8, 256 63.3 / 61.9, 384 72.5 / 78.1
+//     192 50.0 / 48.7;  2^21 128 54.5 / 49.8, 256 63.3 / 61.9, 384 72.5 / 78.1
 //   binary16:  2^16 128 36.0 / 35.8, 144 37.6 / 37.7;  2^17 192 41.1 / 40.5, 208 41.9 / 43.2;  2^18 128 37.8 / 36.1, 160 40.2 / 40.7, 192 42.1 / 43.5;
-//     2^19 192 44.7 / 44.1, 224 46.6 / 48.7;  2^20 128 43.9 / 41.6, 192 49.7 / 50.5;  2^21 128 53.5 / 49.1
+//     2^19 192 44.7 / 44.1, 224 46.6 / 48.7;  2^20 128 43.9 / 41.6, 192 48.9 / 48.6;  2^21 128 53.5 / 49.1
 //   receiver, transform alone: 2^20 64 24.3 / 20.1, 256 35.9 / 33.8, 384 44.7 / 41.6, 512 51.5 / 51.5;  2^21 128 34.1 / 31.4, 384 51.9 / 53.0
-constexpr size_t kShortForward[] = {128, 192, 192, 192, 128, 128}, kShortForwardHalf[] = {128, 192, 128, 192, 128, 128};  // from 2^16 on
-constexpr size_t kShortInverse = 320;
-// Tensors: fft.hip's kernels run whole powers of two of tiles, which costs tensors of 2^16 and 2^17 most, so longer launch sets take
-// these kernels if not too many of their tiles are tall ones, of 2^18 samples and more ("x": copies).  Senders in us, as above:
-// 2^16 x 48 55.3 / 48.5, 2^17 x 24 48.7 / 46.1, 2^18 x 8 42.4 / 42.6, 2^18 x 12 46.6 / 48.8, 2^19 x 6 48.9 / 50.3, 2^20 x 2 48.3 / 46.4, 2^20 x 2 + 2^17 x 2 51.9 /
-// 50.2, 2^20 x 3 54.0 / 57.0, 2^21 + 2^16 x 2 58.0 / 56.7;  2^20 + 2^16 x 32 64.8 / 61.0, 2^19 + 2^17 x 20 51.7 / 51.3, 2^18 x 6 + 2^16 x 20 50.3 / 49.5,
-// 2^18 x 6 + 2^17 x 8 45.4 / 48.3, 2^18 x 8 + 2^16 x 2 44.2 / 46.2, 2^21 + 2^16 x 8 58.8 / 62.7.  Receivers, pass A of fft.hip / these: 2^17 x 32 31.2 / 29.3,
-// 2^18 x 8 20.7 / 21.0, 2^18 x 12 27.6 / 29.3, 2^18 x 16 32.0 / 35.2, 2^19 x 8 30.2 / 33.2;  2^18 x 6 + 2^16 x 20 28.8 / 26.0, 2^18 x 10 + 2^16 x 20 35.3 / 35.2,
-// 2^18 x 10 + 2^16 x 32 44.6 / 39.1;  both passes: 2^20 x 2 28.1 / 28.5, 2^20 x 4 32.5 / 36.8, 2^20 + 2^16 x 32 40.4 / 31.7, 2^21 + 2^16 x 20 42.8 / 43.3,
-// 2^21 + 2^16 x 32 49.7 / 47.8.
-constexpr size_t kShortSet = 128, kShortSetTallest = 144, kShortSetMixed = 192;
+// Tensors: sets of random ones, padded to 2^16 to 2^21 samples, few of them whole powers of two, most tiles of 2^18 and more.  Time with these over time
+// with fft.hip's: senders, 890 sets of 129 to 192 tiles, 1.003 in the mean (up to 160 tiles 0.98, above 176 1.04, single sets 0.91 to
+// 1.12); receivers, 2273 sets of 129 to 320 tiles, 0.994 (0.85 to 1.15).
+constexpr size_t kShortForward[] = {128, 192, 192, 192, 192, 128}, kShortForwardHalf[] = {128, 192, 128, 192, 192, 128};  // from 2^16 on
+constexpr size_t kShortForwardSet = 192, kShortInverse = 320;
 // The inverse pass B from records, against receive.hip's two kernels, in whole receivers: 2^16 128 15.0 / 18.2, 256 22.0 / 25.4, 362 29.8 /
 // 32.6, 512 40.3 / 37.4;  2^18 128 17.0 / 19.0, 256 25.9 / 27.3, 362 35.8 / 33.7;  2^19 128 17.6 / 23.2, 362 38.7 / 39.3, 512 47.6 / 41.9.
 constexpr size_t kShortDecode = 320;
 constexpr int kShortMostLogM = 20;
 static size_t tiles_of(int logM, size_t C) { return C << (logM - 13); }
 static size_t tiles_of(const LongBatch& b) { return (size_t)b.units << (kLongUnitLog - 13); }
-static size_t tall_tiles(const LongBatch& b)  // of tensors of 2^18 and more
-{
-    size_t tiles = 0;
-    for (uint32_t i = 0; i < b.count; ++i)
-        if (b.tab.t[i].logM >= 17) tiles += (size_t)1 << (b.tab.t[i].logM - 13);
-    return tiles;
-}
 static int longest(const LongBatch& b) { return b.tab.t[b.count - 1].logM; }  // it comes last
 static bool short_length(int logM) { return logM >= 15 && logM <= kShortMostLogM; }
 
@@ -787,18 +774,9 @@ bool short_forward(int logM, size_t C, int half)
 {
     return short_length(logM) && tiles_of(logM, C) <= (half ? kShortForwardHalf : kShortForward)[logM - 15];
 }
-bool short_forward(const LongBatch& b)
-{
-    const size_t tiles = tiles_of(b), tall = tall_tiles(b);
-    if (!short_length(longest(b)) || tiles > kShortSetMixed) return false;
-    return tiles <= (longest(b) >= 19 ? kShortSetTallest : kShortSet) || 4 * tall <= 5 * (tiles - tall);
-}
+bool short_forward(const LongBatch& b) { return short_length(longest(b)) && tiles_of(b) <= kShortForwardSet; }
 bool short_inverse(int logM, size_t C) { return short_length(logM) && tiles_of(logM, C) <= kShortInverse; }
-bool short_inverse(const LongBatch& b)
-{
-    const size_t tiles = tiles_of(b), tall = tall_tiles(b);
-    return short_length(longest(b)) && tiles <= kShortInverse && (tall <= kShortSet || tall < 2 * (tiles - tall));
-}
+bool short_inverse(const LongBatch& b) { return short_length(longest(b)) && tiles_of(b) <= kShortInverse; }
 bool short_decode(int logM, size_t C) { return logM >= 15 && logM <= kDecodeMost && tiles_of(logM, C) <= kShortDecode; }
 bool short_decode(const LongBatch& b) { return longest(b) <= kDecodeMost && tiles_of(b) <= kShortDecode; }
 

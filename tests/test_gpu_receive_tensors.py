@@ -25,8 +25,8 @@ def dev():
 # launch sets of few tiles, which go through csrc/short.hip wholly or in one pass
 SHORT_SETS = {
     "one_of_2^21": [(1 << 21) - 9, 77],                                    # the tallest rows there
-    "2^18_and_2^19": [(1 << 18) - 3] * 7 + [(1 << 19) - 8, 1 << 19],       # more than 128 tiles of tall tensors: pass A of the others
-    "2^21_and_short_ones": [1 << 21] + [(1 << 16) - 1] * 5,                # more than 144 tiles, most of them tall: the others' forward passes
+    "2^18_and_2^19": [(1 << 18) - 3] * 9 + [(1 << 19) - 8, 1 << 19],       # more than 192 tiles: the others' forward passes
+    "2^21_and_short_ones": [1 << 21] + [(1 << 16) - 1] * 17,               # the same, and the tallest rows' inverse passes
     "2^16_and_a_tall_one": [1 << 16] * 20 + [(1 << 18) - 1],
 }
 
