@@ -1168,10 +1168,11 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
 constexpr int GROUP_WORDS = 16;  // one wave of the decode kernel covers 512 bins = 16 bitmap words
 
 // Number of set bits before each group of 16 bitmap words of a record (the prefix sum of Sec. 3.2's status vector, kept at the
-// granularity a wave needs), for the part-th kPrefixWords words; the words before them are counted again, eight loads in flight.
-// The word that the Nyquist bin has to itself makes no part of its own: the one before takes it along.
+// granularity a wave needs), for the part-th kPrefixWords words; the words before them are counted again, a lane's own loads and
+// then eight of them in flight.  The word that the Nyquist bin has to itself makes no part of its own: the one before takes it along.
 // The last part checks the headers and leaves the verdict in *verdict.  A workgroup per record took, us: sixty of 2^20 bins (Top-k)
 // 9.1 -> 6.7, ResNet-50's tensors 11.7 -> 7.7, eight peers' sixty of 2^19 15.6 -> 14.1 (16.1 with parts of one word).
+// Receivers of five peers' single chunk of 2^21 samples 43.2 -> 36.4, of 2^22 57.0 -> 51.3 (37.4 and 52.2 with those before asked for one by one).
 constexpr int kPrefixQuads = 4;  // four words each: what a lane has in flight
 constexpr uint32_t kPrefixWords = 4u * kPrefixQuads * RT;
 __host__ __device__ constexpr uint32_t prefix_parts(uint32_t W) { return W < 2u ? 1u : (W + kPrefixWords - 2u) / kPrefixWords; }
@@ -1191,16 +1192,17 @@ __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ st
     const uint32_t whole = W / 4u, from = part * kPrefixQuads * RT;
     auto ones = [](uint4 v) __attribute__((always_inline)) { return (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w)); };
     const bool last = part + 1u == parts, along = last && W > parts * kPrefixWords;
-    const uint32_t nyquist = along ? scalar_load(bitmap + (W - 1u)) : 0u;
-    uint32_t before = 0;
-#pragma unroll 8
-    for (uint32_t i = 0; i < part * kPrefixQuads; ++i) before += ones(quads[i * RT + (uint32_t)tid]);
+    uint32_t nyquist = scalar_load(bitmap + (W - 1u)), before = 0;
     uint4 v[kPrefixQuads];
 #pragma unroll
     for (int i = 0; i < kPrefixQuads; ++i) {
         const uint32_t q = from + (uint32_t)(i * RT + tid);
         v[i] = quads[q < whole ? q : 0u];
     }
+#pragma unroll 2
+    for (uint32_t p = 0; p < part; ++p)
+#pragma unroll
+        for (uint32_t i = 0; i < kPrefixQuads; ++i) before += ones(quads[(p * kPrefixQuads + i) * RT + (uint32_t)tid]);
     uint32_t incl[kPrefixQuads], sum[kPrefixQuads];
 #pragma unroll
     for (int i = 0; i < kPrefixQuads; ++i) {
@@ -1218,6 +1220,7 @@ __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ st
         before = wave_sum(before);
         if (lane == 63) earlier[wave] = before;
     }
+    asm volatile("" : "+s"(nyquist));  // beside the other loads and not, as the last thing wanted, after them
     __syncthreads();
     // every wave scans the sums for itself: read one by one they were 64 LDS reads a wave
     uint32_t run = 0;
@@ -1232,7 +1235,7 @@ __device__ __forceinline__ void group_prefix_part(const uint8_t* __restrict__ st
     run += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
     if (last && tid == 0) {
         if (along) gprefix[(W - 1u) / GROUP_WORDS] = run;
-        *verdict = record_verdict(record, stream, first_of_stream, run + (uint32_t)__popc(nyquist), k, word3, hdr);
+        *verdict = record_verdict(record, stream, first_of_stream, run + (along ? (uint32_t)__popc(nyquist) : 0u), k, word3, hdr);
     }
 }
 
