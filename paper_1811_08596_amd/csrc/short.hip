@@ -426,12 +426,14 @@ __device__ __forceinline__ void clear_words(uint32_t* __restrict__ p, uint32_t w
     for (uint32_t i = blockIdx.x * lanes + threadIdx.x; i < words; i += gridDim.x * lanes) p[i] = 0u;
 }
 // Work item of a workgroup: runs of 2^LOG consecutive items, whose tiles share lines of memory, go to workgroups of one XCD
-// (they are dealt out round-robin over the eight).  Forward pass A of 2^22 samples in chunks of 2^16 15.8 -> 11.4 us.
+// (they are dealt out round-robin over the eight).  Forward pass A of 2^22 samples in chunks of 2^16 15.8 -> 11.4 us.  Those that make no
+// whole round of runs stay where they are: where then none moved, odd numbers of chunks of 2^16 lost, 37 sent and received 58.6 -> 56.3
+// us, 45 61.0 -> 58.2, 27 51.1 -> 48.5 (though 27 sent again and again without anything between 33.2 -> 34.7).
 template <int LOG>
 __device__ __forceinline__ uint32_t beside()
 {
     const uint32_t b = blockIdx.x;
-    if (gridDim.x & ((8u << LOG) - 1u)) return b;
+    if (b >= (gridDim.x & ~((8u << LOG) - 1u))) return b;
     const uint32_t xcd = b & 7u, y = b >> 3;
     return (((y >> LOG) * 8u + xcd) << LOG) + (y & ((1u << LOG) - 1u));
 }
@@ -750,17 +752,20 @@ uint32_t starts_of(const LongBatch& b, LongStarts* at, Log&& log)
 }  // namespace
 
 // In tiles of 2^13 points, by length: whole calls in us, the kernels of fft.hip / these, 8-bit codes of half of the bins, buffers in turn:
-//   sender:    2^16 64 30.9 / 28.1, 128 37.5 / 35.9, 144 38.6 / 39.2, 192 41.6 / 43.0;  2^17 128 38.3 / 35.6, 192 43.0 / 41.3, 208 44.2 / 44.8;
+//   sender:    2^16 64 30.9 / 28.1, 128 37.5 / 35.9, 160 37.4 / 39.6, 192 39.2 / 40.1;  2^17 128 38.3 / 35.6, 192 43.0 / 41.3, 208 44.2 / 44.8;
 //     2^18 128 40.0 / 38.4, 192 44.7 / 44.3, 208 46.1 / 49.3;  2^19 128 41.6 / 38.9, 192 46.4 / 45.5, 224 48.9 / 50.3;  2^20 128 45.7 / 42.4,
 //     192 50.0 / 48.7;  2^21 128 54.5 / 49.8, 256 63.3 / 61.9, 384 72.5 / 78.1
-//   binary16:  2^16 128 36.0 / 35.8, 144 37.6 / 37.7;  2^17 192 41.1 / 40.5, 208 41.9 / 43.2;  2^18 128 37.8 / 36.1, 160 40.2 / 40.7, 192 42.1 / 43.5;
-//     2^19 192 44.7 / 44.1, 224 46.6 / 48.7;  2^20 128 43.9 / 41.6, 192 48.9 / 48.6;  2^21 128 53.5 / 49.1
+//     Sent and received in turn, 2^16 132 57.0 / 54.4, 160 57.4 / 56.8, 176 58.8 / 57.8, 192 59.7 / 58.9; sent after other kernels and 600 MB of
+//     other memory 136 52.5 / 50.1, 156 52.8 / 51.0, 164 54.6 / 53.0, 192 54.6 / 55.0.  That is nearer to a training step.
+//   binary16:  2^16 128 36.0 / 35.8, 144 37.6 / 37.7, 192 39.8 / 40.5, after other kernels 144 50.2 / 50.9, 192 52.4 / 53.8;  2^17 192 41.1 / 40.5, 208 41.9 /
+//     43.2;  2^18 128 37.8 / 36.1, 160 40.2 / 40.7, 192 42.1 / 43.5;  2^19 192 44.7 / 44.1, 224 46.6 / 48.7;  2^20 128 43.9 / 41.6, 192 48.9 / 48.6;
+//     2^21 128 53.5 / 49.1
 //   receiver, transform alone: 2^20 64 24.3 / 20.1, 256 35.9 / 33.8, 384 44.7 / 41.6, 512 51.5 / 51.5;  2^21 128 34.1 / 31.4, 384 51.9 / 53.0
 // Tensors: sets of random ones, padded to 2^16 to 2^21 samples, few of them whole powers of two, most tiles of 2^18 and more.  Time with these over time
 // with fft.hip's: senders, 890 sets of 129 to 192 tiles, 1.003 in the mean (up to 160 tiles 0.98, above 176 1.04, single sets 0.91 to
 // 1.12); receivers, 2273 sets of 129 to 320 tiles, 0.994 (0.85 to 1.15).
-constexpr size_t kShortForward[] = {128, 192, 192, 192, 192, 128}, kShortForwardHalf[] = {128, 192, 128, 192, 192, 128};  // from 2^16 on
-constexpr size_t kShortForwardSet = 192, kShortInverse = 320;
+constexpr size_t kShortForward = 192, kShortForwardHalf[] = {128, 192, 128, 192, 192, 192};  // the latter from 2^16 on
+constexpr size_t kShortInverse = 320;
 // The inverse pass B from records, against receive.hip's two kernels, in whole receivers: 2^16 128 15.0 / 18.2, 256 22.0 / 25.4, 362 29.8 /
 // 32.6, 512 40.3 / 37.4;  2^18 128 17.0 / 19.0, 256 25.9 / 27.3, 362 35.8 / 33.7;  2^19 128 17.6 / 23.2, 362 38.7 / 39.3, 512 47.6 / 41.9.
 constexpr size_t kShortDecode = 320;
@@ -772,9 +777,9 @@ static bool short_length(int logM) { return logM >= 15 && logM <= kShortMostLogM
 
 bool short_forward(int logM, size_t C, int half)
 {
-    return short_length(logM) && tiles_of(logM, C) <= (half ? kShortForwardHalf : kShortForward)[logM - 15];
+    return short_length(logM) && tiles_of(logM, C) <= (half ? kShortForwardHalf[logM - 15] : kShortForward);
 }
-bool short_forward(const LongBatch& b) { return short_length(longest(b)) && tiles_of(b) <= kShortForwardSet; }
+bool short_forward(const LongBatch& b) { return short_length(longest(b)) && tiles_of(b) <= kShortForward; }
 bool short_inverse(int logM, size_t C) { return short_length(logM) && tiles_of(logM, C) <= kShortInverse; }
 bool short_inverse(const LongBatch& b) { return short_length(longest(b)) && tiles_of(b) <= kShortInverse; }
 bool short_decode(int logM, size_t C) { return logM >= 15 && logM <= kDecodeMost && tiles_of(logM, C) <= kShortDecode; }

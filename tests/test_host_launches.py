@@ -165,7 +165,7 @@ def kernels(runtime, tmp_path, calls):
     return made
 
 
-@pytest.mark.parametrize("logL, half, most", [(16, 0, 32), (17, 0, 24), (18, 0, 12), (19, 0, 6), (20, 0, 3), (21, 0, 1), (16, 1, 32), (18, 1, 8)])
+@pytest.mark.parametrize("logL, half, most", [(16, 0, 48), (17, 0, 24), (18, 0, 12), (19, 0, 6), (20, 0, 3), (21, 0, 1), (16, 1, 32), (18, 1, 8)])
 def test_senders_leave_the_small_tiles_where_they_stop_paying(runtime, tmp_path, logL, half, most):
     L = 1 << logL
     calls = [["fftsp_compress_h", ["big", C * L, L, 0.5, 8, 0, "big", "big", "big", "big", None]] if half else compress(C * L, L, 0.5)
