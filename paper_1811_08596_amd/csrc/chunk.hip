@@ -822,6 +822,9 @@ __device__ __forceinline__ void compress_workgroup(const float* __restrict__ in,
     } else {
         // the bins move into registers and their LDS becomes histogram, candidate list and record image
         static_assert(G::CPW == 1, "one chunk per group");
+        // A group of one wave without a chunk is done: no barrier follows.  Its zeros would all queue for one counter, and the call
+        // wait for it: one chunk of 2^10 12.8 -> 7.3 us, of 2^11 19.8 -> 10.4.
+        if (G::WAVES == 1 && !where.exists(group)) return;
         float2 z[G::R], zn;
         bins_of(group, z, zn);
         group_sync<G::WAVES>();
