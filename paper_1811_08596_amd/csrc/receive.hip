@@ -11,7 +11,7 @@
 // over the fabric once and then out of that XCD's L2.
 //
 // What bounds it: about 100 vector instructions a point (60 of the 116 us below), the two dependent trips to memory before a
-// tile's transform, and the barriers in it.  So a lane has eight points and a SIMD eight waves where the tile allows it, and nothing
+// tile's transform, and the barriers in it.  So a lane has eight points and a SIMD six or eight waves where the tile allows it, and nothing
 // is kept for a next tile: a workgroup does one.  (Persistent workgroups of sixteen points a lane that fetched the next tile's entries and
 // codes during the transform took 124 to 134 us; a lane that looked up each of its bins alone 187.)
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against counting, decoding and the pass: 6 + 54 + 110
@@ -99,12 +99,17 @@ __global__ __launch_bounds__(kTableLanes) void k_bitmap_table_long(const uint8_t
 }
 
 // ---------------------------------------------------------- inverse pass B ----
-// Eight points a lane and eight waves a SIMD where the tile allows it: what this kernel waits for are its two dependent trips to
+// Eight points a lane and six or eight waves a SIMD where the tile allows it: what this kernel waits for are its two dependent trips to
 // memory and the barriers between the transform's stages, and it moves half the bytes of a transform pass.
 template <int LOGN2>
 struct Receive {
     static constexpr int N2 = 1 << LOGN2, LOGT = 4, SLOTS = 1 << LOGT;
     static constexpr int U = LOGN2 >= 10 ? 2 : 1, NT = 2 * N2 / U;  // eights of points of a lane
+    // Waves a SIMD in long launches.  Workgroups of 256 lanes do better with six and 80 registers than with eight, for which three to seven are
+    // spilled: chunks of 2^16, half kept, 8 bits, 181 46.5 / 45.5 us, 724 168 / 151, 10 bits 48.5 / 45.6 and 183 / 154, binary16 133 / 122; seven 160
+    // and 165, five 153 and 156.  512 lanes spill none: 2^17, 362 chunks 148.8, with six 148.1, with four 159.  With 1024 there is only four
+    // beside eight, which spill three at most.
+    static constexpr int WAVES = LOGN2 == 7 ? 6 : 8 / U;
     static constexpr int BINS = SLOTS / 2;                         // neighbouring bins of either side of a run
     static constexpr size_t kLds = ((size_t)(SLOTS + 1) << LOGN2) * sizeof(float2);
 };
@@ -241,8 +246,8 @@ __device__ __forceinline__ uint32_t in_stretches(uint32_t total)
     const uint32_t t = lo + (blockIdx.x >> 3);
     return t < hi ? t : total;
 }
-template <int LOGN2, bool HALF, int WIDEST>
-__global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(8 / Receive<LOGN2>::U, 8 / Receive<LOGN2>::U))) void k_receive_b(
+template <int LOGN2, bool HALF, int WIDEST, int WAVES>
+__global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) void k_receive_b(
     const uint8_t* __restrict__ records, uint32_t W, uint32_t S, int bits, int m, const uint2* __restrict__ table, int logM,
     typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total, float mid_scale)
 {
@@ -258,7 +263,7 @@ __global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per
 // Tensors of different lengths: those with rows of up to 2^9 are one launch, a workgroup of 1024 lanes does one tile of rows of 2^9,
 // two of 2^8 or four of 2^7; those with rows of 2^10 are another (TOP 10).
 template <int TOP, int WIDEST>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8 / Receive<TOP>::U, 8 / Receive<TOP>::U))) void k_receive_b_long(
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(Receive<TOP>::WAVES, Receive<TOP>::WAVES))) void k_receive_b_long(
     const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total,
     LongTable tab, LongStarts at)
 {
@@ -290,10 +295,13 @@ template <int LOGN2, bool HALF, int WIDEST>
 hipError_t receive_b(const uint8_t* records, const CodecArgs& a, int logM, const uint2* table, float2* mid, Tables t, hipStream_t s)
 {
     using G = Receive<LOGN2>;
-    auto kern = k_receive_b<LOGN2, HALF, WIDEST>;
+    const size_t total = a.C << (logM - LOGN2 - G::LOGT);
+    constexpr size_t one_wave = 256 * 4 * 64 / G::NT;  // workgroups that are a wave on every SIMD
+    // As many waves as there can be while most workgroups run at once: chunks of 2^16, 10 bits, 10 % kept, eight waves / six, 96 34.6 / 35.2, 128 37.8 /
+    // 39.5, 129 43.8 / 46.1, 160 44.7 / 44.9, 181 47.0 / 46.2.
+    const auto kern = total <= 10 * one_wave ? k_receive_b<LOGN2, HALF, WIDEST, 8 / G::U> : k_receive_b<LOGN2, HALF, WIDEST, G::WAVES>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::kLds);
     if (e != hipSuccess) return e;
-    const size_t total = a.C << (logM - LOGN2 - G::LOGT);
     FFTSP_LAUNCH("irfft_pass_b", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(G::NT), G::kLds, s, records, (1u << logM) / 32u + 1u, (uint32_t)a.S,
                  a.bits, a.m, table, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, (uint32_t)total, HALF ? 1.0f / half_lift(logM) : 1.0f);
     return hipGetLastError();
@@ -312,7 +320,7 @@ hipError_t receive_rows(const uint8_t* records, const CodecArgs& a, int logM, co
 
 // In tiles of 2^13 points.  Whole receivers in us, decode and inverse pass B / these kernels, nothing of a call in the caches when it
 // starts, 8-bit codes of half of the bins (chunks of up to 2^19: short.hip's kernels up to 320 tiles).
-//   2^16 724 59.6 / 50.4, 4096 285 / 235;  2^17 4096 284 / 212;  2^18 724 64.6 / 50.6, 4096 288 / 220;  2^19 4096 300 / 238;
+//   2^16 724 59.6 / 50.4, 4096 284 / 220;  2^17 4096 284 / 212;  2^18 724 64.6 / 50.6, 4096 288 / 220;  2^19 4096 300 / 238;
 //   2^20 64 20.5 / 21.4, 128 25.4 / 23.9, 256 33.8 / 29.7, 1024 85.0 / 67.9, 4096 293 / 235;
 //   2^21 128 31.3 / 30.2, 1024 96.0 / 75.8, 4096 308 / 279;  2^22 256 47.6 / 38.0, 1024 106 / 83, 4096 347 / 314
 constexpr size_t kReceiveFrom = 65;

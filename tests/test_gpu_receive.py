@@ -42,3 +42,25 @@ def test_receiver_and_the_spectrum_it_leaves_out(dev, logL, bits):
             packed[-(nb - 64) // chunks + 16:][:L // 16] = 255  # and in the last one, at the end of the stream
             f.decompress(packed, nb, out, L, theta, bits, ws)
             assert f.device_status(ws) != 0
+
+
+@pytest.mark.parametrize("half", (0, 1))
+@pytest.mark.parametrize("bits", (8, 15))
+def test_chunks_of_2_to_the_16_on_either_side_of_the_wave_count(dev, bits, half):
+    """161 chunks take the kernel with six waves a SIMD, their first 160 by themselves the one with eight."""
+    torch, f, L = dev.torch, dev.f, 1 << 16
+    g = torch.randn(161 * L, device="cuda", generator=torch.Generator(device="cuda").manual_seed(bits)) * 1e-2
+    outs = []
+    for chunks in (161, 160):
+        n = chunks * L
+        packed, out = torch.empty(f.packed_bytes(n, L, 0.4, bits), dtype=torch.uint8, device="cuda"), torch.empty(n, device="cuda")
+        ws = dev.ws_for(n, L, bits)
+        if half:
+            f.compress_h(g[:n], L, 0.4, bits, 10, packed, ws)
+            f.decompress_h(packed, packed.numel(), out, L, 0.4, bits, 10, ws)
+        else:
+            f.compress(g[:n], L, 0.4, bits, packed, ws)
+            f.decompress(packed, packed.numel(), out, L, 0.4, bits, ws)
+        assert f.device_status(ws) == 0
+        outs.append(out)
+    assert torch.equal(outs[0][:160 * L].view(torch.int32), outs[1].view(torch.int32))
