@@ -6,9 +6,9 @@
 // lane decodes eight of them at a time: it looks up the word of the bitmap and the number of bits before it (one table entry
 // for 32 bins, made by k_bitmap_table), fetches a window of the record with two loads, and shifts the codes out of registers.
 //
-// All tiles of a chunk read the same lines of its record and table, 1.3 MB for a chunk of 2^20.  Workgroups are dealt out to
-// the XCDs round-robin, so each XCD gets a stretch of chunks of its own and its workgroups neighbouring tiles of it: the lines come
-// over the fabric once and then out of that XCD's L2.
+// All tiles of a chunk read the same lines of its record and table: 0.66 MB for a chunk of 2^20 samples, half of its bins kept as 8-bit
+// codes.  Workgroups are dealt out to the XCDs round-robin, so each XCD gets a stretch of chunks of its own and its workgroups neighbouring
+// tiles of it: the lines come over the fabric once and then out of that XCD's L2.
 //
 // What bounds it: about 100 vector instructions a point (60 of the 116 us below), the two dependent trips to memory before a
 // tile's transform, and the barriers in it.  So a lane has eight points and a SIMD six or eight waves where the tile allows it, and nothing
