@@ -562,10 +562,8 @@ __global__ __launch_bounds__(1 << TOP) void k_inv_b_long_short(const float2* __r
     };
     const int rows = short_rows(x.logM);
     if (rows == 7) return run(std::integral_constant<int, 7>{});
-    if constexpr (TOP >= 8)
-        if (rows == 8) return run(std::integral_constant<int, 8>{});
-    if constexpr (TOP >= 9)
-        if (rows == 9) return run(std::integral_constant<int, 9>{});
+    if (rows == 8) return run(std::integral_constant<int, 8>{});
+    if (rows == 9) return run(std::integral_constant<int, 9>{});
     if constexpr (TOP >= 10)
         if (rows == 10) return run(std::integral_constant<int, 10>{});
 }
@@ -713,12 +711,14 @@ template <bool PAIR, bool HALF>
 hipError_t inv_b_any(const float2* spec, uint32_t sstride, int logM, size_t C, float2* mid, Tables t, float mid_scale, hipStream_t s)
 {
 #define INV_B(p) launch_b_inv<p, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s)
-    switch (short_rows(logM)) {
-        case 7: return INV_B(7);
-        case 8: return INV_B(8);
-        case 9: return INV_B(9);
-        default: return INV_B(10);
+    const int rows = short_rows(logM);
+    if constexpr (!HALF) {
+        if (rows == 7) return INV_B(7);
+        if (rows == 8) return INV_B(8);
     }
+    // shorter binary16 spectra are not made: see kShortDecode
+    if (rows < 9) return hipErrorInvalidValue;
+    return rows == 9 ? INV_B(9) : INV_B(10);
 #undef INV_B
 }
 template <bool HALF>
@@ -769,6 +769,7 @@ constexpr size_t kShortInverse = 320;
 // The inverse pass B from records, against receive.hip's two kernels, in whole receivers: 2^16 128 15.0 / 18.2, 256 22.0 / 25.4, 362 29.8 /
 // 32.6, 512 40.3 / 37.4;  2^18 128 17.0 / 19.0, 256 25.9 / 27.3, 362 35.8 / 33.7;  2^19 128 17.6 / 23.2, 362 38.7 / 39.3, 512 47.6 / 41.9.
 constexpr size_t kShortDecode = 320;
+static_assert(kShortDecode >= kShortInverse && kDecodeMost / 2 == 9, "receivers of short calls have a spectrum from rows of 2^9 on");
 constexpr int kShortMostLogM = 20;
 static size_t tiles_of(int logM, size_t C) { return C << (logM - 13); }
 static size_t tiles_of(const LongBatch& b) { return (size_t)b.units << (kLongUnitLog - 13); }
@@ -878,12 +879,9 @@ hipError_t launch_short_inverse_b_long(const float2* spec, const LongBatch& b, f
         FFTSP_LAUNCH("irfft_pass_b", kern, dim3(wgs), dim3(1 << TOP), lds_b(TOP, false), s, spec, mid, t, b.tab, at);
         return hipGetLastError();
     };
-    switch (short_rows(longest(b))) {
-        case 7: return pass_b(std::integral_constant<int, 7>{});
-        case 8: return pass_b(std::integral_constant<int, 8>{});
-        case 9: return pass_b(std::integral_constant<int, 9>{});
-        default: return pass_b(std::integral_constant<int, 10>{});
-    }
+    // sets whose longest has shorter rows have no spectrum: see kShortDecode
+    if (short_rows(longest(b)) < 9) return hipErrorInvalidValue;
+    return short_rows(longest(b)) == 9 ? pass_b(std::integral_constant<int, 9>{}) : pass_b(std::integral_constant<int, 10>{});
 }
 
 hipError_t launch_short_inverse_a_long(const LongBatch& b, float* out, const float2* mid, Tables t, hipStream_t s)
