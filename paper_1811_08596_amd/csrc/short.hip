@@ -24,6 +24,7 @@ constexpr int short_log_a(int logn1) { return logn1 <= 9 ? 11 : logn1 + 2; }
 constexpr int short_lanes_a(int logn1) { return 1 << (short_log_a(logn1) - 3); }
 constexpr int kShortSlots = 8;                // rows and mirrors of a pass B tile, side by side: 64 bytes of a run
 constexpr int kShortLogSlots = 3;
+constexpr int kDecodeMost = 18;  // log2 of the longest half chunk whose bitmap every workgroup counts for itself (RecordBins)
 
 // ------------------------------------------------------------------ pass A ----
 // fft.hip multiplies column c of a group of 8 DC by an anchor looked up for column c mod DC and c / DC further factors, one
@@ -290,7 +291,8 @@ struct RecordBins {
     template <int LOGN2>
     __device__ __forceinline__ void load(float2 (&x)[8], float2& last, uint32_t, uint32_t k, int kq0, int logM, float2* lds, int tid) const
     {
-        constexpr int NT = 1 << LOGN2, DK = NT / 8, QUADS = 8;  // N1 is 1024 at most
+        constexpr int NT = 1 << LOGN2, DK = NT / 8, MOST = 2 * LOGN2 + 1 < kDecodeMost ? 2 * LOGN2 + 1 : kDecodeMost;
+        constexpr int QUADS = 1 << (MOST - LOGN2 - 7);  // of the longest such half chunk
         __shared__ uint32_t before[NT / 64];
         uint2* table = reinterpret_cast<uint2*>(lds);
         const uint32_t* rec = reinterpret_cast<const uint32_t*>(record);
@@ -653,7 +655,6 @@ constexpr size_t lds_decode(int logM, int logn2)
     const size_t words = (size_t)1 << (logM - 5), table = (words + words / 8) * sizeof(uint2);
     return table > lds_b(logn2, false) ? table : lds_b(logn2, false);
 }
-constexpr int kDecodeMost = 18;  // log2 of the longest half chunk whose table is built in every workgroup
 
 template <int LOGN2, bool HALF>
 hipError_t launch_b_decode(const uint8_t* stream, const CodecArgs& a, int logM, float2* mid, Tables t, const HeaderInfo& hdr,
