@@ -1563,7 +1563,7 @@ __global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npe
     const uint32_t tile = blockIdx.x % Tn, tbase = tile * kTile, j0 = (uint32_t)tid * 8u;  // j0: this lane's first bin in the tile
     const uint32_t G = (W + GROUP_WORDS - 1) / GROUP_WORDS, g = tile * (kTile / 32 / GROUP_WORDS) + wave;
     const uint32_t byte = (tbase + j0) >> 3, twoN = 2u * (uint32_t)bits;
-    const int shift = 23 - m, final = (int)(S / 4u) - 5 - (int)W;
+    const int shift = 23 - m, final = last_code_word((uint32_t)S, W);
     const bool in = byte < 4u * W;
     auto record_of = [&](uint32_t p) __attribute__((always_inline)) { return recs.p[p] + c * S; };
     auto flags_of = [&](uint32_t p) __attribute__((always_inline)) { return (uint32_t)record_of(p)[16u + (in ? byte : 0u)]; };

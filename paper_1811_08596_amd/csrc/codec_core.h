@@ -2,6 +2,7 @@
 // the chunk-resident kernels in chunk.hip).  Internal: nothing here is part of the C ABI.
 #pragma once
 #include "internal.h"
+#include "record_bounds.h"
 
 namespace fftsp {
 namespace {
@@ -263,8 +264,7 @@ struct Stretch {
     uint32_t w[WORDS];
     __device__ __forceinline__ void fetch(const uint32_t* codes, int final, uint32_t bit)
     {
-        // the window stays inside the record, also for a corrupt bitmap; what lies before the codes is the bitmap
-        const int first = (int)(bit >> 5) < final - (WORDS - 1) ? (int)(bit >> 5) : final - (WORDS - 1);
+        const int first = window_first(bit, final, WORDS);
         rel = bit - 32u * (uint32_t)first;
         __builtin_memcpy(w, codes + first, sizeof(w));
     }

@@ -128,7 +128,7 @@ __device__ __forceinline__ void receive_tile(const uint8_t* __restrict__ record,
 
     const uint32_t bits = (uint32_t)code_bits, twoN = 2u * bits;
     const int shift = 23 - m;
-    const int final = (int)(S / 4u) - 5 - (int)W;  // a record's last code word
+    const int final = last_code_word(S, W);
     const uint32_t* words = reinterpret_cast<const uint32_t*>(record) + 4 + W;
     const uint32_t vbase = (scalar_load(reinterpret_cast<const uint32_t*>(record)) - 1u) << shift;
     auto stored = [](float2 z) __attribute__((always_inline)) { return cx_load(cx_store<HALF>(z)); };  // as a spectrum would hold it
@@ -183,7 +183,7 @@ __device__ __forceinline__ void receive_tile(const uint8_t* __restrict__ record,
         auto single = [&](uint32_t bin) __attribute__((always_inline)) {
             const uint2 e = entries[bin >> 5];
             const uint32_t bit = (e.y + (uint32_t)__popc(e.x & ((1u << (bin & 31u)) - 1u))) * twoN;
-            const int i = (int)(bit >> 5) < final ? (int)(bit >> 5) : final, i1 = i < final ? i + 1 : i;
+            const int i = code_word(bit, final), i1 = word_after(i, final);
             const uint32_t raw = (e.x >> (bin & 31u)) & 1u ? __builtin_amdgcn_alignbit(words[i1], words[i], bit) : 0u;
             return stored(make_float2(__uint_as_float(dequantize_field(raw, 0u, bits, vbase, shift)),
                                       __uint_as_float(dequantize_field(raw, bits, bits, vbase, shift))));

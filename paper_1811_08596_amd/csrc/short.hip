@@ -328,7 +328,7 @@ struct RecordBins {
         if (verdict && tid == 0) *verdict = record_verdict(record, stream, first, all + (uint32_t)__popc(rec[4 + (1u << (logM - 5))]), a.k, a.word3, hdr);
         __syncthreads();
         const uint32_t* codes = rec + 4 + a.W;
-        const uint32_t final = a.S / 4u - 5u - a.W;  // last code word (a record has one, if only padding: see fetch)
+        const int final = a.k ? last_code_word(a.S, a.W) : 0;  // a record with a kept bin has one
         const uint32_t width = 2u * (uint32_t)a.bits;
         const uint32_t base = (pbase - 1u) << (23 - a.m);
         uint32_t rank[9], c0[9], c1[9];
@@ -345,11 +345,10 @@ struct RecordBins {
         // a record without kept bins has no code words; a corrupt bitmap's ranks must not point outside the record
 #pragma unroll
         for (int q = 0; q < 9; ++q) {
-            const uint64_t bit = (uint64_t)width * rank[q];
-            const uint32_t i = on[q] && a.k ? (uint32_t)(bit >> 5 < final ? bit >> 5 : final) : 0u;
+            const int i = on[q] ? code_word(width * rank[q], final) : 0;
             const uint32_t* p = a.k ? codes : rec;
             c0[q] = p[i];
-            c1[q] = p[i < final && a.k ? i + 1u : i];
+            c1[q] = p[word_after(i, final)];
         }
 #pragma unroll
         for (int q = 0; q < 9; ++q) {

@@ -1,6 +1,6 @@
 """Long receivers take the inverse's first pass straight from the records (csrc/receive.hip).  They give the bits that a decoded
 spectrum (decode_spectrum) and its inverse give, at every chunk length, for windows of the record at its end and across bitmap words,
-and reads stay inside the stream whatever the bitmap claims."""
+and a bitmap that claims more bins than there are is reported (test_record_bounds.py: what is read then)."""
 import pytest
 
 from tests.gpu_harness import Device

@@ -1,6 +1,6 @@
 """Per-tensor receivers take the inverse's first pass straight from the records as well (csrc/receive.hip): every row length, each
 alone in its launch or beside others, at the narrowest and widest codes.  Every tensor comes back with the bits that its decoded
-spectrum (decode_spectrum) and its inverse give, and reads stay inside the stream whatever a bitmap claims."""
+spectrum (decode_spectrum) and its inverse give, and a bitmap that claims too many bins is reported."""
 import numpy as np
 import pytest
 

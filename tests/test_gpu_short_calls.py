@@ -63,7 +63,7 @@ def test_receiver_without_a_spectrum(dev, logL, bits):
         f.decode_spectrum(packed, packed.numel(), n, L, theta, bits, spec, ws)
         f.irfft(spec, n, L, want, ws)
         assert torch.equal(out.view(torch.int32), want.view(torch.int32))
-        # a bitmap that claims every bin: reads stay inside the record, and the record is reported
+        # a bitmap that claims every bin is reported (test_record_bounds.py: what is read then)
         if theta < 1.0:
             packed[64 + 16:64 + 16 + L // 16] = 255
             f.decompress(packed, packed.numel(), out, L, theta, bits, ws)
