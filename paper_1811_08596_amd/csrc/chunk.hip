@@ -12,7 +12,8 @@
 // launch where the per-tile kernels (codec.hip) take ten.  The transform's arithmetic is that of fft_core.h.
 //
 // What bounds it: vector instruction issue (chunks of 2^12, 10-bit codes of 15 % of the bins: 114 instructions per bin sending, more than
-// half of them transform and split, 101 receiving; the vector units are busy 59 and 65 % of the time) and, for the longest chunks, the
+// half of them transform and split, 101 receiving; the vector units are busy 30 to 59 and 33 to 65 % of the time, at two to four
+// cycles an instruction), the barriers between its stages and, for the longest chunks, the
 // few waves one workgroup per compute unit leaves.  Measured on 25.6 M samples, compress + decompress, against the per-tile kernels
 // with their ten sweeps and 16 KiB of histogram per chunk: L = 2^12 636 -> 98 us, one chunk of 2^10 91 -> 22 us.
 //

@@ -10,7 +10,7 @@
 // codes.  Workgroups are dealt out to the XCDs round-robin, so each XCD gets a stretch of chunks of its own and its workgroups neighbouring
 // tiles of it: the lines come over the fabric once and then out of that XCD's L2.
 //
-// What bounds it: about 100 vector instructions a point (60 of the 116 us below), the two dependent trips to memory before a
+// What bounds it: about 100 vector instructions a point (44 to 87 of the 116 us below, at two to four cycles each), the two dependent trips to memory before a
 // tile's transform, and the barriers in it.  So a lane has eight points and a SIMD six or eight waves where the tile allows it, and nothing
 // is kept for a next tile: a workgroup does one.  (Persistent workgroups of sixteen points a lane that fetched the next tile's entries and
 // codes during the transform took 124 to 134 us; a lane that looked up each of its bins alone 187.)
