@@ -1557,17 +1557,123 @@ __global__ __launch_bounds__(NT) void k_decode(const uint8_t* __restrict__ strea
 }
 
 // Several peers' streams (receiver under an allgather: Sec. 4, implementation): the units summed over the peers in list order in
-// registers, starting from zero, and stored once.  Bound by instruction issue: 26 vector instructions a bin and peer, which is 53 to 106 % of the
-// time at two to four cycles each; shifts across two registers and bit-field extracts are the ones of four.
+// registers, starting from zero, and stored once.
 //
 // Codes of up to 15 bits: a lane has eight neighbouring bins.  Their codes are neighbours in the record, so it fetches one window
-// and shifts them out of registers (Stretch): no LDS, and nothing scalar for each row of 64 bins.  While one peer's are
-// unpacked the next one's window and the byte of the bitmap after that are on their way.
+// and shifts them out of registers (Stretch; ByteWindow for 8-bit codes): no LDS, and nothing scalar for each row of 64 bins.  While one peer's
+// are unpacked the next one's window and the byte of the bitmap after that are on their way.
 // Measured, eight peers of 62 M samples, half of the bins kept as 8-bit codes, against 64 neighbouring lanes a row and codes picked out
-// of LDS by rank (k_decode_peers_wide, still there for the widest codes): 178 -> 155 us, with 27 % more vector instructions but a seventh of the
-// LDS ones and no chain through LDS.
+// of LDS by rank (k_decode_peers_wide, still there for the widest codes): 178 -> 155 us with Stretch, 131 with ByteWindow.
+//
+// What bounds it: with Stretch instruction issue (26 a bin and peer), with ByteWindow the trips to memory of 551 MB (106 us for a copy of
+// as much), of which a wave has one window and one byte a lane of flags on the way.  What counts there is eight waves a SIMD: two windows ahead and
+// seven waves took 136, three sets of registers in turn and four waves 178, workgroups that go on to another tile with its first
+// window fetched before 203.
+// A load of more than four bytes a lane, or of lanes that are not neighbours, takes the vector memory's return path 17 cycles; one whose lanes
+// start inside a word 33 for eight bytes and 66 for sixteen.  Adds, logic of up to three operands, binary32 arithmetic and shifts by a
+// constant hold a SIMD for two cycles, nearly everything else for four: permutes, bit-field and bit-select operations, shifts by a
+// register, counts, minima, comparisons and selections by one.
+
+// Eight neighbouring bins of a record of 8-bit codes: a kept bin is two bytes, so those of eight are in the four words from the first one's on, or,
+// where it starts inside a word and all are kept, the first byte pair of the next lane's window too.  Two byte permutes deal the bytes of
+// four bins out, by selectors looked up for the set of them that is kept.
+// For three bits of mantissa a code with its sign in the top bit goes to its place by one arithmetic shift and a mask that drops the copies
+// of the sign, and the base is added where the bin is kept, by a mask looked up with the selectors.  Kept bins with a zero code, which comparisons
+// and selections would sort out one by one, are looked for in the four words first: waves that have one, 1 in 20 or so, and other codes take
+// dequantize_field.
+struct ByteTable {
+    uint4 pick[16];  // entry i, for four bins of which those of i's set bits are kept: selectors of the first two and of the last two, and to
+                     // get to the bytes behind theirs: bits to shift by once whole words have been left out, ~0 if one has to be
+    uint4 keep[16];  // ~0 where the bin is kept
+    // Each wave writes all of it, the same values, before it reads them: no barrier is needed.
+    __device__ __forceinline__ void fill(int lane)
+    {
+        const uint32_t i = (uint32_t)lane & 15u, b0 = i & 1u, b1 = (i >> 1) & 1u, b2 = (i >> 2) & 1u, b3 = i >> 3, r2 = b0 + b1, r3 = r2 + b2, n = r3 + b3;
+        auto half = [](uint32_t kept, uint32_t rank) __attribute__((always_inline)) { return kept ? 0x0100u + rank * 0x0202u : 0x0C0Cu; };  // 12: zero
+        if (lane < 16) {
+            pick[i] = make_uint4(half(b0, 0u) | half(b1, b0) << 16, half(b2, r2) | half(b3, r3) << 16, 16u * (n < 2u ? n : n - 2u), n < 2u ? 0u : ~0u);
+            keep[i] = make_uint4(0u - b0, 0u - b1, 0u - b2, 0u - b3);
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+};
+struct ByteWindow {
+    uint32_t mask, rel, after;  // rel: bit position of the first code inside the window; after: the word behind the wave's last window
+    uint32_t w[4];
+    // run: kept bins of the record before these.  All lanes call this, with neighbouring stretches.
+    __device__ __forceinline__ void fetch(const uint8_t* record, uint32_t W, int final, uint32_t run, uint32_t)
+    {
+        const int first = window_first(16u * run, final, 4);
+        rel = 16u * run - 32u * (uint32_t)first;
+        __builtin_memcpy(w, record + (uint32_t)(4 * (first + 4 + (int)W)), sizeof(w));
+        const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)(run + (uint32_t)__popc(mask)), 63);
+        const int word = code_word(16u * end, final > 0 ? final : 0);
+        after = scalar_load(reinterpret_cast<const uint32_t*>(record) + (final < 0 ? 0 : 4 + (int)W + word));
+    }
+    template <typename Put>
+    __device__ __forceinline__ void unpack(uint32_t, uint32_t, int shift, uint32_t base, const ByteTable* table, Put&& put)
+    {
+        while (__any(rel >= 32u)) {  // windows moved back from a record's end
+            const bool on = rel >= 32u;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) w[i] = on ? w[i + 1] : w[i];
+            w[3] = on ? 0u : w[3];
+            rel = on ? (rel < 128u ? rel - 32u : 0u) : rel;
+        }
+        const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)after, (int)w[0], 0x130, 0xF, 0xF, false);  // the next lane's first word
+        uint32_t v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_alignbit(i < 3 ? w[i + 1] : next, w[i], rel);
+        uint32_t zeros = 0;  // top bits of the bytes whose other seven are all zero
+#pragma unroll
+        for (int i = 0; i < 4; ++i) zeros |= ~((v[i] & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) & 0x80808080u;
+        const uint4 pick = table->pick[mask & 15u], pick2 = table->pick[(mask >> 4) & 15u];
+        uint32_t u[3];  // the words that the second four bins' bytes start in
+#pragma unroll
+        for (int i = 0; i < 3; ++i) u[i] = (v[i] & ~pick.w) | (v[i + 1] & pick.w);
+        const uint32_t u0 = (uint32_t)(((uint64_t)u[1] << 32 | u[0]) >> pick.z), u1 = (uint32_t)(((uint64_t)u[2] << 32 | u[1]) >> pick.z);
+        const uint32_t two[4] = {__builtin_amdgcn_perm(v[1], v[0], pick.x), __builtin_amdgcn_perm(v[1], v[0], pick.y),
+                                 __builtin_amdgcn_perm(u1, u0, pick2.x), __builtin_amdgcn_perm(u1, u0, pick2.y)};
+        constexpr uint32_t kMost = 0x7Fu << 20;  // the largest code's place
+        if (shift == 20 && base < 0x80000000u - kMost && !__any(zeros)) {
+            const uint4 keep = table->keep[mask & 15u], keep2 = table->keep[(mask >> 4) & 15u];
+            const uint32_t bases[8] = {base & keep.x,  base & keep.y,  base & keep.z,  base & keep.w,
+                                       base & keep2.x, base & keep2.y, base & keep2.z, base & keep2.w};
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                auto value = [&](uint32_t top) __attribute__((always_inline)) {
+                    return __uint_as_float(((uint32_t)((int)top >> 4) & (0x80000000u | kMost)) + bases[j]);
+                };
+                put(j, make_float2(value(two[j >> 1] << (24 - 16 * (j & 1))), value(two[j >> 1] << (16 - 16 * (j & 1)))));
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                put(j, make_float2(__uint_as_float(dequantize_field(two[j >> 1], 16u * (j & 1), 8u, base, shift)),
+                                   __uint_as_float(dequantize_field(two[j >> 1], 16u * (j & 1) + 8u, 8u, base, shift))));
+        }
+    }
+};
+// WIDEST: bits of a bin at most (16: codes of up to 8, 30: of up to 15); kByteCodes: the codes are bytes
+constexpr int kByteCodes = 8;
 template <int WIDEST>
-__global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npeers, size_t S, uint32_t B, uint32_t W, int bits, int m,
+struct PeerWindow : Stretch<8, WIDEST> {
+    using Base = Stretch<8, WIDEST>;
+    __device__ __forceinline__ void fetch(const uint8_t* record, uint32_t W, int final, uint32_t run, uint32_t twoN)
+    {
+        Base::fetch(reinterpret_cast<const uint32_t*>(record) + 4 + W, final, run * twoN);
+    }
+    template <typename Put>
+    __device__ __forceinline__ void unpack(uint32_t twoN, uint32_t bits, int shift, uint32_t base, const ByteTable*, Put&& put)
+    {
+        Base::unpack(twoN, bits, shift, base, put);
+    }
+};
+template <>
+struct PeerWindow<kByteCodes> : ByteWindow {
+};
+template <int WIDEST>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_decode_peers(PeerList recs, uint32_t npeers, size_t S, uint32_t B, uint32_t W, int bits, int m,
                                                      uint32_t Tn, size_t C, const uint32_t* __restrict__ gprefix, float2* __restrict__ spec,
                                                      uint32_t sstride, bool vec, int pair_log)
 {
@@ -1584,35 +1690,38 @@ __global__ __launch_bounds__(NT) void k_decode_peers(PeerList recs, uint32_t npe
     auto record_of = [&](uint32_t p) __attribute__((always_inline)) { return recs.p[p] + c * S; };
     auto flags_of = [&](uint32_t p) __attribute__((always_inline)) { return (uint32_t)record_of(p)[16u + (in ? byte : 0u)]; };
     auto run_of = [&](uint32_t p) __attribute__((always_inline)) { return scalar_load(gprefix + (p * C + c) * G + (g < G ? g : 0u)); };
-    auto window = [&](Stretch<8, WIDEST>& o, uint32_t p, uint32_t flags, uint32_t run) __attribute__((always_inline)) {
+    auto window = [&](PeerWindow<WIDEST>& o, uint32_t p, uint32_t flags, uint32_t run) __attribute__((always_inline)) {
         o.mask = in ? flags : 0u;
         const uint32_t n = (uint32_t)__popc(o.mask);
-        o.fetch(reinterpret_cast<const uint32_t*>(record_of(p)) + 4 + W, final, (run + wave_scan_incl(n) - n) * twoN);
+        o.fetch(record_of(p), W, final, run + wave_scan_incl(n) - n, twoN);
     };
+    __shared__ __align__(16) ByteTable table;
+    if constexpr (WIDEST == kByteCodes) table.fill(tid & 63);
     float2 acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = make_float2(0.f, 0.f);
-    Stretch<8, WIDEST> o;
+    PeerWindow<WIDEST> o;
     uint32_t flags = flags_of(0u), run = run_of(0u);
     window(o, 0u, flags, run);
-    if (npeers > 1u) {
-        flags = flags_of(1u);
-        run = run_of(1u);
-    }
-    for (uint32_t p = 0; p < npeers; ++p) {
-        Stretch<8, WIDEST> next = o;
-        if (p + 1u < npeers) {
-            window(next, p + 1u, flags, run);
-            const uint32_t after = p + 2u < npeers ? p + 2u : p + 1u;
-            flags = flags_of(after);
-            run = run_of(after);
-        }
+    const uint32_t last = npeers - 1u;
+    flags = flags_of(last ? 1u : 0u);
+    run = run_of(last ? 1u : 0u);
+    auto add = [&](uint32_t p) __attribute__((always_inline)) {
         const uint32_t base = (scalar_load(reinterpret_cast<const uint32_t*>(record_of(p))) - 1u) << shift;
-        o.unpack(twoN, (uint32_t)bits, shift, base, [&](int j, float2 z) __attribute__((always_inline)) {
+        o.unpack(twoN, (uint32_t)bits, shift, base, &table, [&](int j, float2 z) __attribute__((always_inline)) {
             acc[j] = make_float2(acc[j].x + z.x, acc[j].y + z.y);
         });
+    };
+    for (uint32_t p = 0; p < last; ++p) {
+        PeerWindow<WIDEST> next;
+        window(next, p + 1u, flags, run);
+        const uint32_t after = p + 1u < last ? p + 2u : last;
+        flags = flags_of(after);
+        run = run_of(after);
+        add(p);
         o = next;
     }
+    add(last);
     // a tile is whole runs, and eight bins lie in one half of one of them: upwards two slots apart, or downwards
     auto gapped = [](uint32_t slot) __attribute__((always_inline)) { return slot + (slot >> 4) * GAP; };
     const uint32_t N1 = 1u << pair_log, half = N1 / 2, k1 = j0 & (N1 - 1u), start = j0 - k1;
@@ -1920,7 +2029,9 @@ hipError_t launch_decode_peers(const PeerList& streams, int npeers, const CodecA
 #define FFTSP_DECODE_PEERS(kern)                                                                                       \
     FFTSP_LAUNCH("decode", kern, dim3((unsigned)(a.C * u.Tn)), dim3(NT), 0, s, recs, (uint32_t)npeers, a.S, u.B, u.W, a.bits, a.m, u.Tn, a.C, \
                  gprefix, reinterpret_cast<float2*>(spec), a.sstride, vec, a.pair_log)
-    if (a.bits <= 8)
+    if (a.bits == 8)
+        FFTSP_DECODE_PEERS(k_decode_peers<kByteCodes>);
+    else if (a.bits < 8)
         FFTSP_DECODE_PEERS(k_decode_peers<16>);
     else if (a.bits <= 15)
         FFTSP_DECODE_PEERS(k_decode_peers<30>);
