@@ -331,6 +331,177 @@ constexpr uint32_t kKeptTiles = 513, kFewTiles = 288;
 // Tiles of a chunk up to which k_emit may do k_resolve's work.
 constexpr uint32_t kMergedTiles = 72;
 
+// a digit d, counted for the lanes that want it
+__device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, bool run_likely, int lane, uint32_t weight)
+{
+    if (run_likely) {
+        const uint64_t act = __ballot(hit);
+        if (!act) return;
+        // a row whose keys share the digit (a run of equal values, e.g. zeros) is one atomic
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __ffsll((unsigned long long)act) - 1);
+        if (__ballot(hit && d == d0) == act) {
+            if (lane == 0) atomicAdd(&h[d0], (uint32_t)__popcll(act) * weight);
+            return;
+        }
+    }
+    if (hit) atomicAdd(&h[d], weight);
+}
+// ---------------------------------------------------------------- sample ----
+// Time domain, chunks of up to kKeptTiles tiles: the samples are not counted.  A workgroup per chunk looks at 2^15 of them and says between which
+// two keys the k-th largest lies, so widely that it all but always does; k_collect then takes those above as kept and those between as
+// candidates, and k_resolve, which knows how many are above, sees whether the k-th largest is among the candidates.  Where it is not, it selects
+// from the samples themselves (select_samples): the result is exact whatever was sampled.
+//
+// The sample: 2^11 stretches of sixteen neighbours, one from each 2^11-th of the chunk, at a place in it that a hash of its number says,
+// so that no period of the gradient's layout is met again and again.  Neighbours are alike in a gradient, so how far the sample's ranks are off
+// is taken from the stretches: half the squared differences between one's count above the estimate and the next one's, which is what independent
+// samples' ranks vary by too where there is no likeness.  Five and a half of these standard deviations either side: 46 candidates to a tile of 2048
+// at 15 % kept, where a bucket of the histogram has 10 to 40.
+//
+// Zeros are never candidates: a gradient can be half zeros (a rectifier's), and a window that reached them would have k_collect write most of
+// the chunk.  Where the window's lower end is the smallest key above zero and the candidates do not have the threshold, it is zero.
+//
+// Bound by latency: one trip to memory, behind what the call before has left to write, and the barriers of three scans.  Sixty chunks of 2^20:
+// 16 us, where clearing the histograms, counting 62 M samples and finding the buckets took 83; k_collect, which then is the first to read the
+// gradient, 42 -> 64, k_resolve 21 -> 27.
+constexpr int kSampleLanes = 1024, kSampleLoads = 8, kSampleStretches = kSampleLanes / 4 * kSampleLoads;
+constexpr uint32_t kSamples = 16u * kSampleStretches;
+// where stretch g lies among the `slots` (a power of two) of its part
+__host__ __device__ constexpr uint32_t sample_slot(uint32_t g, uint32_t slots) { return (g * 2654435761u >> 15) & (slots - 1u); }
+__global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict__ in, uint32_t L, uint32_t k, size_t n, uint32_t* __restrict__ sel,
+                                                        uint32_t* __restrict__ ctl)
+{
+    constexpr int NW = kSampleLanes / 64;
+    __shared__ __align__(16) uint32_t h[kHistBins];
+    __shared__ uint32_t fine[kHist2Bins], sums[3][NW], edge[6];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const size_t c = blockIdx.x;
+    if (c == 0 && tid < (int)(kControlBytes / 4)) ctl[tid] = 0u;
+    if (k == 0) {  // nothing is kept, and nothing is a candidate
+        if (tid == 0) *reinterpret_cast<uint2*>(sel + c * 8) = make_uint2(0xFFFFFFFFu, 0xFFFFFFFFu);
+        return;
+    }
+    const float* X = in + c * (size_t)L;
+    const uint32_t present = present_of<true>(n, c, L), slots = L / kSamples;
+    uint32_t key[4 * kSampleLoads];
+#pragma unroll
+    for (int j = 0; j < kSampleLoads; ++j) {
+        const uint32_t g = (uint32_t)(j * (kSampleLanes / 4) + (tid >> 2)), at = 16u * (g * slots + sample_slot(g, slots)) + 4u * ((uint32_t)tid & 3u);
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (at + 4u <= present) {
+            v = *reinterpret_cast<const float4*>(X + at);
+        } else if (at < present) {
+            v.x = X[at];
+            if (at + 1u < present) v.y = X[at + 1u];
+            if (at + 2u < present) v.z = X[at + 2u];
+        }
+        key[4 * j] = key_of(v.x);
+        key[4 * j + 1] = key_of(v.y);
+        key[4 * j + 2] = key_of(v.z);
+        key[4 * j + 3] = key_of(v.w);
+    }
+    reinterpret_cast<uint4*>(h)[tid] = make_uint4(0u, 0u, 0u, 0u);
+    static_assert(kHistBins == 4 * kSampleLanes && kHist2Bins == kSampleLanes, "four counters to a lane, then one");
+    fine[tid] = 0u;
+    if (tid < 6) edge[tid] = 0u;
+    __syncthreads();
+    // A quarter of the samples, by their top digit: between which buckets the rest is worth counting.  Of four neighbours a different one
+    // each time: where a layout's period is a multiple of four, the first ones are a biased quarter.  Twenty standard deviations of
+    // independent samples' ranks, because these are no more independent than the rest: too few cost a window without an end, too many
+    // only a coarser digit.
+    constexpr uint32_t kFew = kSamples / 4;
+#pragma unroll
+    for (int j = 0; j < kSampleLoads; ++j) count_digit(h, true, key[4 * j + (j & 3)] >> kKeyShift, true, lane, 1u);
+    __syncthreads();
+    // counts before a lane's `sum`
+    auto before = [&](uint32_t sum, uint32_t* tmp) __attribute__((always_inline)) {
+        const uint32_t incl = wave_scan_incl(sum);
+        if (lane == 63) tmp[wave] = incl;
+        __syncthreads();
+        const uint32_t one = lane < NW ? tmp[lane] : 0u, upto = wave_scan_incl(one);
+        return (uint32_t)__builtin_amdgcn_readlane((int)(upto - one), wave) + incl - sum;
+    };
+    auto clamped = [](float r, uint32_t most) __attribute__((always_inline)) { return r < 1.f ? 1u : (r > (float)most ? most : (uint32_t)r); };
+    const float share = (float)k / (float)L;
+    {
+        const uint4 v = reinterpret_cast<const uint4*>(h)[kHistBins / 4 - 1 - tid];
+        const uint32_t cnt[4] = {v.w, v.z, v.y, v.x};  // from the top down
+        uint32_t run = before(v.x + v.y + v.z + v.w, sums[0]);
+        const float at = share * kFew, wide = 20.f * sqrtf(share * (1.f - share) * kFew) + 20.f;
+        const uint32_t r0 = clamped(at - wide, kFew), r1 = clamped(at + wide, kFew), r2 = clamped(at, kFew);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t b = (uint32_t)(kHistBins - 1 - 4 * tid - i), end = run + cnt[i];
+            if (run < r0 && end >= r0) {
+                edge[0] = b;
+                edge[3] = run;
+            }
+            if (run < r1 && end >= r1) {
+                edge[1] = b;
+                edge[4] = end;
+            }
+            if (run < r2 && end >= r2) edge[2] = b;
+            run = end;
+        }
+        __syncthreads();
+    }
+    const uint32_t top = edge[0], bottom = edge[1], middle = edge[2] << kKeyShift;  // top >= bottom
+    const bool crowded = edge[4] - edge[3] > kFew / 2;                              // many of them may be the same
+    // All that lie between, by 2^10 digits of what there is between; how many are above; the differences.
+    const uint32_t base = bottom << kKeyShift, range = ((top - bottom + 1u) << kKeyShift) - 1u;
+    const int shift = 32 - __clz((int)range) - kHist2Bits;  // at least 9
+    uint32_t above = 0, off = 0;
+#pragma unroll
+    for (int j = 0; j < kSampleLoads; ++j) {
+        int in = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t x = key[4 * j + i], d = x - base;
+            above += x > base + range ? 1u : 0u;
+            in += x >= middle ? 1 : 0;
+            if (crowded)
+                count_digit(fine, d <= range, d >> shift, true, lane, 1u);
+            else if (d <= range)
+                atomicAdd(&fine[d >> shift], 1u);
+        }
+        in += __builtin_amdgcn_mov_dpp(in, 0xB1, 0xF, 0xF, false);  // of the four lanes of a stretch
+        in += __builtin_amdgcn_mov_dpp(in, 0x4E, 0xF, 0xF, false);
+        const int next = __builtin_amdgcn_update_dpp(in, in, 0x104, 0xF, 0xF, false);  // four lanes on; itself in a row's last four
+        off += (uint32_t)((next - in) * (next - in));
+    }
+    above = wave_sum(above);
+    off = wave_sum(off);
+    if (lane == 0) {
+        sums[1][wave] = above;
+        sums[2][wave] = off;
+    }
+    __syncthreads();
+    above = wave_sum(lane < NW ? sums[1][lane] : 0u);
+    off = wave_sum(lane < NW ? sums[2][lane] : 0u);
+    // half of the differences, each seen by four lanes, and three of them to four stretches
+    const float likely = sqrtf(fmaxf((float)off * (0.5f / 4.f * 4.f / 3.f), share * (1.f - share) * kSamples)), wide = 5.5f * likely + 4.f;
+    const float at = share * kSamples;
+    const uint32_t r0 = clamped(at - wide, kSamples), r1 = clamped(at + wide, kSamples), digit = (uint32_t)(kHist2Bins - 1 - tid);
+    const uint32_t cnt = fine[digit], run = above + before(cnt, sums[0]), end = run + cnt;
+    // where a rank lies outside what was counted there is no bound on that side; a zero is never a candidate
+    auto atleast1 = [](uint32_t lo) __attribute__((always_inline)) { return lo ? lo : 1u; };
+    if (tid == 0) {
+        if (at - wide < 1.f || above >= r0) sel[c * 8 + 1] = 0x7FFFFFFFu;
+        if (at + wide > (float)kSamples) sel[c * 8] = 1u;
+    }
+    if (at - wide >= 1.f && run < r0 && end >= r0) {
+        const uint32_t hi = base + (digit << shift) + ((1u << shift) - 1u);
+        sel[c * 8 + 1] = hi < 0x7FFFFFFFu ? hi : 0x7FFFFFFFu;
+    }
+    if (at + wide <= (float)kSamples) {
+        if (run < r1 && end >= r1) sel[c * 8] = atleast1(base + (digit << shift));
+        if (tid == kSampleLanes - 1 && end < r1) sel[c * 8] = 1u;
+    }
+    // (above < r0 <= end of the last digit, unless fewer are counted than r0)
+    if (tid == kSampleLanes - 1 && end < r0) sel[c * 8 + 1] = 0x7FFFFFFFu;
+    if (tid == 0 && above >= r1 && at + wide <= (float)kSamples) sel[c * 8] = atleast1(base);
+}
+
 // --------------------------------------------------------------- collect ----
 // Per tile: count and range of the bins kept outright, and the candidates in bin order.
 //
@@ -342,8 +513,10 @@ constexpr uint32_t kMergedTiles = 72;
 // so that k_resolve can take it as one.
 // FIND: every workgroup finds the threshold's bucket itself, from hist, instead of a launch before this one.  That is 16 KB more to
 // read per tile, from cache, so it is done where the launch weighs more: see find_in_collect.
+// WINDOW: sel holds the two keys between which candidates lie (k_sample) instead of the bucket; a candidate is its key, which is a sample's
+// component too.
 // clear (FIND only): the records, whose code words this kernel then clears, for a k_emit that finds the threshold itself.
-template <bool FIND, bool TABLE, bool REAL, bool HALF>
+template <bool FIND, bool TABLE, bool REAL, bool HALF, bool WINDOW = false>
 __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u,
                                                 const uint32_t* __restrict__ hist, uint32_t* __restrict__ sel,
                                                 uint32_t* __restrict__ tinfo, uint32_t* __restrict__ tscan,
@@ -359,8 +532,13 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
     const int pair_log = at.pair_log;
     const typename Stored<REAL, HALF>::T* X = spec + at.spec + tbase;
     const uint32_t count = units_in_tile<REAL>(n, at.chunk, B, tbase);
-    uint32_t bstar = 0;
-    if constexpr (!FIND) bstar = sel[(size_t)at.chunk * 8];
+    uint32_t bstar = 0, lowest = 0, highest = 0;
+    if constexpr (WINDOW) {
+        lowest = sel[(size_t)at.chunk * 8];
+        highest = sel[(size_t)at.chunk * 8 + 1];
+    } else if constexpr (!FIND) {
+        bstar = sel[(size_t)at.chunk * 8];
+    }
     E z[ROWS];
     if constexpr (REAL || HALF) {
         load_units(X, row0, count, lane, pair_log, z);
@@ -377,6 +555,8 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
             const uint32_t from = at.tile * share, to = from + share < words ? from + share : words;
             for (uint32_t i = from + (uint32_t)tid; i < to; i += NT) codes[i] = 0u;
         }
+    }
+    if constexpr (FIND) {
         const Bucket b = find_bucket(hist + (size_t)at.chunk * kHistBins, at.k);
         bstar = b.star;
         if (at.tile == 0 && tid == 0) *reinterpret_cast<uint2*>(sel + (size_t)at.chunk * 8) = make_uint2(b.star, b.need);
@@ -390,8 +570,8 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
         key[r] = key_of(z[r]);
         vb[r] = vbits_of(z[r]);
         const uint32_t bucket = key[r] >> kKeyShift;
-        const bool isdef = valid && bucket > bstar;
-        const bool iscand = valid && bucket == bstar;
+        const bool isdef = valid && (WINDOW ? key[r] > highest : bucket > bstar);
+        const bool iscand = valid && (WINDOW ? key[r] - lowest <= highest - lowest : bucket == bstar);
         if (isdef) {
             ++ndef;
             vmax = vb[r] > vmax ? vb[r] : vmax;
@@ -429,7 +609,12 @@ __global__ __launch_bounds__(NT) void k_collect(const typename Stored<REAL, HALF
     uint2* out = cand + blockIdx.x * (size_t)kTile;
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
-        if ((mine >> r) & 1u) out[off + prefix_popc(cm[r])] = make_uint2(key[r], vb[r]);
+        if ((mine >> r) & 1u) {
+            if constexpr (WINDOW)
+                reinterpret_cast<uint32_t*>(cand)[blockIdx.x * (size_t)kTile + off + prefix_popc(cm[r])] = key[r];
+            else
+                out[off + prefix_popc(cm[r])] = make_uint2(key[r], vb[r]);
+        }
         off += (uint32_t)__popcll(cm[r]);
     }
     if (tid == 64 && at.Tn > kFewTiles)  // counters of k_count_digit
@@ -503,21 +688,6 @@ __device__ __forceinline__ void tiles_of_part(const uint4* ti, const uint2* cd, 
         for (int v = 0; v < AHEAD; ++v)
             if (b + v < Tn) tile(b + v, ti[b + v], e[v]);
     }
-}
-// candidates' next digit: d, counted for the lanes that want it
-__device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, bool run_likely, int lane, uint32_t weight)
-{
-    if (run_likely) {
-        const uint64_t act = __ballot(hit);
-        if (!act) return;
-        // a row whose keys share the digit (a run of equal values, e.g. zeros) is one atomic
-        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, __ffsll((unsigned long long)act) - 1);
-        if (__ballot(hit && d == d0) == act) {
-            if (lane == 0) atomicAdd(&h[d0], (uint32_t)__popcll(act) * weight);
-            return;
-        }
-    }
-    if (hit) atomicAdd(&h[d], weight);
 }
 template <bool TABLE>
 __global__ __launch_bounds__(NT) void k_count_digit(Shape u, const uint32_t* __restrict__ tinfo, uint32_t* __restrict__ tscan,
@@ -643,6 +813,7 @@ template <int MOST>
 struct ResolveScratch {
     uint32_t h[kHist2Bins], list[kListCap], list_at[kListCap], list_vb[kListCap];
     uint32_t tgt[MOST], teq[MOST], take[MOST];
+    uint2 sums[RW];  // of a wave's tiles: bins above the candidates, and candidates
     uint32_t listed, vmax;
 };
 struct ResolveArgs {
@@ -682,11 +853,94 @@ __device__ __forceinline__ Digit find_digit(const uint32_t* h, uint32_t need, in
                  (uint32_t)__builtin_amdgcn_readlane((int)d.count, who)};
 }
 
-template <int NW, int FETCH, bool MERGED, int MOST>
+// The threshold of a chunk of samples from the samples themselves, where the candidates do not have it: ten bits at a time, then every tile's
+// samples above it and equal to it.  Slow, and all but never needed: see k_sample.
+template <int LANES>
+__device__ __forceinline__ Digit select_samples(const float* __restrict__ X, uint32_t present, uint32_t L, uint32_t Tn, uint32_t need,
+                                                          uint32_t* h, uint32_t* tgt, uint32_t* teq, uint32_t& vm)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int AHEAD = 4;
+    static_assert((1 << 18) % (4 * AHEAD * LANES) == 0 && kTile % (4 * AHEAD * 64) == 0, "whole batches");
+    // keys i .. i + 3 of the chunk, with nothing but zeros past the gradient's end
+    auto four = [&](uint32_t i) __attribute__((always_inline)) {
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (i + 4u <= present) {
+            v = *reinterpret_cast<const float4*>(X + i);
+        } else if (i < present) {
+            v.x = X[i];
+            if (i + 1u < present) v.y = X[i + 1u];
+            if (i + 2u < present) v.z = X[i + 2u];
+        }
+        return make_uint4(key_of(v.x), key_of(v.y), key_of(v.z), key_of(v.w));
+    };
+    Digit found{0u, need, 0u};
+    uint32_t tau = 0;
+    for (int top = 31; top > 0;) {
+        const int shift = top > 10 ? top - 10 : 0;
+        __syncthreads();
+        for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t i = 0; i < L; i += 4 * AHEAD * LANES) {
+            uint4 v[AHEAD];
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) v[q] = four(i + 4u * (uint32_t)(q * LANES + tid));
+            auto count = [&](uint32_t key) __attribute__((always_inline)) {
+                count_digit(h, key >> top == tau, digit_place((key >> shift) & ((1u << (top - shift)) - 1u)), true, lane, 1u);
+            };
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) {
+                count(v[q].x);
+                count(v[q].y);
+                count(v[q].z);
+                count(v[q].w);
+            }
+        }
+        __syncthreads();
+        found = find_digit(h, found.need, lane);
+        tau = tau << (top - shift) | found.digit;
+        top = shift;
+    }
+    __syncthreads();
+    uint32_t most = 0;
+    for (uint32_t t = (uint32_t)wave; t < Tn; t += LANES / 64) {
+        uint32_t above = 0, same = 0;
+#pragma unroll 1
+        for (uint32_t i = 0; i < (uint32_t)kTile; i += 4 * AHEAD * 64) {
+            uint4 v[AHEAD];
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) v[q] = four(t * kTile + i + 4u * (uint32_t)(q * 64 + lane));
+            auto count = [&](uint32_t key) __attribute__((always_inline)) {
+                above += (uint32_t)__popcll(__ballot(key > tau));
+                same += (uint32_t)__popcll(__ballot(key == tau));
+                most = key > most ? key : most;
+            };
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) {
+                count(v[q].x);
+                count(v[q].y);
+                count(v[q].z);
+                count(v[q].w);
+            }
+        }
+        if (lane == 0) {
+            tgt[t] = above;
+            teq[t] = same;
+        }
+    }
+    vm = most;  // the largest sample is a survivor
+    __syncthreads();
+    return Digit{tau, found.need, found.count};
+}
+
+// WINDOW: samples (time domain); the candidates lie between two keys, and X has them all, `present` of them in the chunk.
+template <int NW, int FETCH, bool MERGED, bool WINDOW, int MOST>
 __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const ResolveArgs& a, ResolveScratch<MOST>& lds,
                                                    uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
                                                    uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
-                                                   uint8_t* __restrict__ records, uint8_t* __restrict__ stream, const HeaderInfo& hdr)
+                                                   uint8_t* __restrict__ records, uint8_t* __restrict__ stream, const HeaderInfo& hdr,
+                                                   const float* __restrict__ X, uint32_t present)
 {
     constexpr int LANES = NW * 64, HELD = 2 * FETCH;
     uint32_t *const h = lds.h, *const list = lds.list, *const list_at = lds.list_at, *const list_vb = lds.list_vb;
@@ -696,12 +950,24 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
     const uint32_t Tn = at.Tn, k = at.k, W = at.W;
     const uint4* ti = reinterpret_cast<const uint4*>(tinfo + (size_t)at.tile0 * 4);
     const uint2* cd = cand + at.tile0 * (size_t)kTile;
+    // WINDOW: the lowest candidate's key and the highest one's; a key's digits are those of what it lies above the lowest
     const uint32_t bstar = sel[c * 8 + 0];
     uint32_t need = sel[c * 8 + 1];
-    const bool counted = !MERGED && Tn > kHeldTiles<NW, FETCH>;  // k_count_digit and k_mark have been here
+    const uint32_t lowest = WINDOW ? bstar : 0u, range = WINDOW ? need - bstar : 0u;
+    const int low = WINDOW ? (range >> kHist2Bits ? 32 - __clz((int)range) - kHist2Bits : 0) : kHist2Shift;  // bits below the first digit
+    auto rel = [&](uint32_t key) __attribute__((always_inline)) { return WINDOW ? key - lowest : key; };
+    const bool counted = !MERGED && !WINDOW && Tn > kHeldTiles<NW, FETCH>;  // k_count_digit and k_mark have been here
 
-    // A wave's tiles are wave, wave + NW, ...; lane v has the summary of the v-th, e[v] its first candidates.  Slots behind
-    // a tile's last candidate are allocated; what they hold is dropped.
+    // A wave's tiles are wave, wave + NW, ...; lane v has the summary of the v-th, e[v] its first candidates: of a sample the key is all there
+    // is, and a lane has two of them.  Slots behind a tile's last candidate are allocated; what they hold is dropped.
+    constexpr uint32_t ROW = WINDOW ? 128u : 64u;
+    const uint32_t* ck = reinterpret_cast<const uint32_t*>(cand) + at.tile0 * (size_t)kTile;
+    auto first_of = [&](uint32_t t) __attribute__((always_inline)) {
+        return WINDOW ? *reinterpret_cast<const uint2*>(ck + (size_t)t * kTile + 2 * lane) : cd[(size_t)t * kTile + lane];
+    };
+    auto one_of = [&](uint32_t t, uint32_t i) __attribute__((always_inline)) {
+        return WINDOW ? make_uint2(ck[(size_t)t * kTile + i], ck[(size_t)t * kTile + i]) : cd[(size_t)t * kTile + i];
+    };
     const uint32_t own = (uint32_t)wave + (uint32_t)(lane * NW);
     const bool holds = !counted && lane < HELD && own < Tn, second = !counted && (uint32_t)(wave + FETCH * NW) < Tn;
     uint4 info = make_uint4(0u, 0u, 0u, 0u);
@@ -709,18 +975,18 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
 #pragma unroll
     for (int v = 0; v < HELD; ++v) e[v] = make_uint2(0u, 0u);
     if (holds) info = ti[own];
-    if (!counted) {
+    if (!counted && !WINDOW) {
 #pragma unroll
         for (int v = 0; v < FETCH; ++v) {
             const uint32_t t = (uint32_t)(wave + v * NW);
-            e[v] = cd[(size_t)(t < Tn ? t : 0u) * kTile + lane];
+            e[v] = first_of(t < Tn ? t : 0u);
         }
     }
-    if (second) {
+    if (second && !WINDOW) {
 #pragma unroll
         for (int v = FETCH; v < HELD; ++v) {
             const uint32_t t = (uint32_t)(wave + v * NW);
-            e[v] = cd[(size_t)(t < Tn ? t : 0u) * kTile + lane];
+            e[v] = first_of(t < Tn ? t : 0u);
         }
     }
     for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
@@ -738,21 +1004,64 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
             lds.take[t] = v.z;  // what k_mark has left
             vm = v.y > vm ? v.y : vm;
         }
+    if constexpr (WINDOW) {
+        const uint32_t defs = wave_sum(info.x), cands = wave_sum(info.z);
+        if (lane == 0) lds.sums[wave] = make_uint2(defs, cands);
+    }
     __syncthreads();
-    const bool any = need > 0;  // else nothing is kept (k = 0), and there are no candidates
+    bool missed = false, zero = false;  // the threshold is not among the candidates; it is zero
+    bool unkept = false;                // all that is kept are candidates
+    if constexpr (WINDOW) {
+        const uint2 v = lane < NW ? lds.sums[lane] : make_uint2(0u, 0u);
+        const uint32_t defs = wave_sum(v.x), cands = wave_sum(v.y);
+        need = k - defs;
+        missed = k != 0 && (defs >= k || need > cands);
+        zero = missed && defs < k && lowest == 1u;
+        unkept = defs == 0u;
+        if (zero) need -= cands;
+    }
+    const bool any = need > 0 || missed;  // else nothing is kept (k = 0), and there are no candidates
     // candidates of the lane's tile to look at, each standing for `weight` of them
     const uint32_t ncand = info.w ? (info.z ? 1u : 0u) : info.z, nweight = info.w ? info.z : 1u;
-    const bool heavy = __any(ncand > 64u);
+    const bool heavy = __any(ncand > ROW);
 
-    // f(v, t, nc, weight) for the first row of 64 candidates of each of this wave's tiles: straight code, and as little of it as
+    // f(v, nc, weight) for the first row of candidates of each of this wave's tiles: straight code, and as little of it as
     // can be, because it runs once and is fetched as it runs
     auto first_rows = [&](auto&& f) __attribute__((always_inline)) {
+        auto one = [&](int v, uint2 x) __attribute__((always_inline)) {
+            f(v, x, (uint32_t)__builtin_amdgcn_readlane((int)ncand, v), (uint32_t)__builtin_amdgcn_readlane((int)nweight, v));
+        };
+        if constexpr (WINDOW) {
+            // a loop, with the next tiles' rows on their way, that goes through memory both times: it takes as long as rows held in registers,
+            // and a fourth of the code
+            constexpr int AHEAD = 4;
+            uint2 a[AHEAD], b[AHEAD];
+            auto ask = [&](uint2 (&x)[AHEAD], int v) __attribute__((always_inline)) {
 #pragma unroll
-        for (int v = 0; v < HELD; ++v) {
-            if (v == FETCH && !second) break;
-            f(v, (uint32_t)__builtin_amdgcn_readlane((int)ncand, v), (uint32_t)__builtin_amdgcn_readlane((int)nweight, v));
+                for (int q = 0; q < AHEAD; ++q) {
+                    const uint32_t t = (uint32_t)(wave + (v + q) * NW);
+                    x[q] = first_of(t < Tn ? t : 0u);
+                }
+            };
+            ask(a, 0);
+#pragma unroll 1
+            for (int v = 0; (uint32_t)(wave + v * NW) < Tn; v += 2 * AHEAD) {
+                ask(b, v + AHEAD);
+#pragma unroll
+                for (int q = 0; q < AHEAD; ++q) one(v + q, a[q]);
+                ask(a, v + 2 * AHEAD);
+#pragma unroll
+                for (int q = 0; q < AHEAD; ++q) one(v + AHEAD + q, b[q]);
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < HELD; ++v) {
+                if (v == FETCH && !second) break;
+                one(v, e[v]);
+            }
         }
     };
+    static_assert(HELD + 8 <= 64, "a lane to every tile that is asked for");
     // row(t, i0, e, valid, weight) for all rows of the wave's tiles from number `from` on, out of memory
     auto rows_of_memory = [&](uint32_t from, auto&& row) __attribute__((always_inline)) {
         for (uint32_t t = (uint32_t)wave; t < Tn; t += NW) {
@@ -760,37 +1069,99 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
             const uint32_t nc = v.w ? (v.z ? 1u : 0u) : v.z;
             for (uint32_t i0 = from; i0 < nc; i0 += 64u) {
                 const bool valid = i0 + (uint32_t)lane < nc;
-                row(t, i0, cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)], valid, v.w ? v.z : 1u);
+                row(t, i0, one_of(t, valid ? i0 + (uint32_t)lane : 0u), valid, v.w ? v.z : 1u);
             }
         }
     };
-    auto digit_of = [&](uint32_t key) __attribute__((always_inline)) {
-        return digit_place((key >> kHist2Shift) & (uint32_t)(kHist2Bins - 1));
+    // row(t, i0, e, valid, weight) for the rows behind the first of those of the wave's tiles that have any (a tile taken as one has none);
+    // of samples several tiles' second rows asked for at a time
+    auto more_rows = [&](auto&& row) __attribute__((always_inline)) {
+        if constexpr (!WINDOW) {
+            rows_of_memory(ROW, row);
+            return;
+        }
+        constexpr int AHEAD = 8;
+        for (uint64_t left = __ballot(ncand > ROW); left;) {
+            uint2 x[AHEAD];
+            uint32_t tiles[AHEAD], counts[AHEAD];
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q) {
+                const int v = left ? __ffsll((unsigned long long)left) - 1 : 0;
+                tiles[q] = (uint32_t)(wave + v * NW);
+                counts[q] = left ? (uint32_t)__builtin_amdgcn_readlane((int)ncand, v) : 0u;
+                x[q] = one_of(tiles[q], ROW + (uint32_t)lane);
+                left &= left - 1u;
+            }
+#pragma unroll
+            for (int q = 0; q < AHEAD; ++q)
+                if (counts[q]) row(tiles[q], ROW, x[q], ROW + (uint32_t)lane < counts[q], 1u);
+#pragma unroll 1
+            for (int q = 0; q < AHEAD; ++q)
+                for (uint32_t i0 = ROW + 64u; i0 < counts[q]; i0 += 64u) {
+                    const bool valid = i0 + (uint32_t)lane < counts[q];
+                    row(tiles[q], i0, one_of(tiles[q], valid ? i0 + (uint32_t)lane : 0u), valid, 1u);
+                }
+        }
     };
-    if (any && counted) {
-        for (int i = tid; i < kHist2Bins; i += LANES) h[digit_place((uint32_t)i)] = tscan[(size_t)at.tile0 * 2 + i];
-    } else if (any) {
-        first_rows([&](int v, uint32_t nc, uint32_t weight) __attribute__((always_inline)) {
-            if ((uint32_t)lane < nc) atomicAdd(&h[digit_of(e[v].x)], weight);
+    // row(t, key, valid, weight) for all rows of samples
+    auto every_row = [&](auto&& row) __attribute__((always_inline)) {
+        first_rows([&](int v, uint2 x, uint32_t nc, uint32_t weight) __attribute__((always_inline)) {
+            row((uint32_t)(wave + v * NW), x.x, 2u * (uint32_t)lane < nc, weight);
+            row((uint32_t)(wave + v * NW), x.y, 2u * (uint32_t)lane + 1u < nc, weight);
         });
         if (heavy)
-            rows_of_memory(64u, [&](uint32_t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+            more_rows([&](uint32_t t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) { row(t, x.x, valid, weight); });
+    };
+    auto digit_of = [&](uint32_t key) __attribute__((always_inline)) {
+        return digit_place((rel(key) >> low) & (uint32_t)(kHist2Bins - 1));
+    };
+    if (missed) {
+    } else if (any && counted) {
+        for (int i = tid; i < kHist2Bins; i += LANES) h[digit_place((uint32_t)i)] = tscan[(size_t)at.tile0 * 2 + i];
+    } else if (any) {
+        first_rows([&](int v, uint2 x, uint32_t nc, uint32_t weight) __attribute__((always_inline)) {
+            if constexpr (WINDOW) {
+                if (2u * (uint32_t)lane < nc) atomicAdd(&h[digit_of(x.x)], weight);
+                if (2u * (uint32_t)lane + 1u < nc) atomicAdd(&h[digit_of(x.y)], weight);
+            } else {
+                if ((uint32_t)lane < nc) atomicAdd(&h[digit_of(x.x)], weight);
+            }
+        });
+        if (heavy)
+            more_rows([&](uint32_t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
                 count_digit(h, valid, digit_of(x.x), true, lane, weight);
             });
     }
     __syncthreads();
-    Digit found = any ? find_digit(h, need, lane) : Digit{0u, 0u, 0u};
+    Digit found = any && !missed ? find_digit(h, need, lane) : Digit{0u, need, 0u};
     need = found.need;
     uint32_t equal = found.count;
-    const int prefix = (int)((bstar << kHist2Bits) | found.digit);  // the top bits of the threshold's key
-    const bool few = equal <= kListCap;
-    uint32_t tau = any ? (uint32_t)prefix << kHist2Shift : 0xFFFFFFFFu, quota = 0;
+    const int prefix = (int)(WINDOW ? found.digit : (bstar << kHist2Bits) | found.digit);  // the top bits of the threshold's key
+    const bool few = equal <= kListCap && !missed;
+    uint32_t tau = any ? (uint32_t)prefix << low : 0xFFFFFFFFu, quota = 0;  // WINDOW: above the lowest, until it is known
     bool ties = false;
-    if (any && few) {
+    if (WINDOW && zero) {  // all that are not zero are kept, and the first zeros
+        if (holds) {
+            tgt[own] += info.z;
+            teq[own] = (uint32_t)kTile - info.x - info.z;
+        }
+        if (unkept)
+            every_row([&](uint32_t, uint32_t x, bool valid, uint32_t) __attribute__((always_inline)) { vm = valid && x > vm ? x : vm; });
+        tau = 0u;
+        quota = need;
+        ties = true;  // a quota of all of them is one, too
+        __syncthreads();
+    } else if (WINDOW && missed) {
+        const Digit d = select_samples<LANES>(X, present, Tn * (uint32_t)kTile, Tn, k, h, tgt, teq, vm);
+        tau = d.digit;
+        quota = d.need;
+        equal = d.count;
+        ties = equal != quota;
+    } else if (any && few) {
         auto list_one = [&](uint32_t place, uint2 x) __attribute__((always_inline)) {
             const uint32_t slot = atomicAdd(&lds.listed, 1u);
             if (slot < kListCap) {
-                list[slot] = x.x;
+                list[slot] = rel(x.x);
                 list_at[slot] = place;
                 list_vb[slot] = x.y;
             }
@@ -803,33 +1174,48 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
             uint32_t above = 0, hits = 0;  // lane v: of the wave's v-th tile; each lane: what it has to list, the last two of it
             uint32_t hit_at[2] = {0u, 0u};
             uint2 hit[2] = {make_uint2(0u, 0u), make_uint2(0u, 0u)};
-            first_rows([&](int v, uint32_t nc, uint32_t weight) __attribute__((always_inline)) {
-                const int top = (uint32_t)lane < nc ? (int)(e[v].x >> kHist2Shift) : -1;
-                const uint32_t many = (uint32_t)__popcll(__ballot(top > prefix)) * weight;
-                above = lane == v ? many : above;
-                vm = top > prefix && e[v].y > vm ? e[v].y : vm;
-                const bool is = top == prefix;
-                hits += is ? 1u : 0u;
-                hit_at[1] = is ? hit_at[0] : hit_at[1];
-                hit[1].x = is ? hit[0].x : hit[1].x;
-                hit[1].y = is ? hit[0].y : hit[1].y;
-                hit_at[0] = is ? (uint32_t)v : hit_at[0];
-                hit[0].x = is ? e[v].x : hit[0].x;
-                hit[0].y = is ? e[v].y : hit[0].y;
+            first_rows([&](int v, uint2 x, uint32_t nc, uint32_t weight) __attribute__((always_inline)) {
+                auto hit_one = [&](bool is, uint32_t place, uint32_t key, uint32_t vb) __attribute__((always_inline)) {
+                    hits += is ? 1u : 0u;
+                    hit_at[1] = is ? hit_at[0] : hit_at[1];
+                    hit[1].x = is ? hit[0].x : hit[1].x;
+                    hit[1].y = is ? hit[0].y : hit[1].y;
+                    hit_at[0] = is ? place : hit_at[0];
+                    hit[0].x = is ? key : hit[0].x;
+                    hit[0].y = is ? vb : hit[0].y;
+                };
+                if constexpr (WINDOW) {
+                    const int top = 2u * (uint32_t)lane < nc ? (int)(rel(x.x) >> low) : -1;
+                    const int next = 2u * (uint32_t)lane + 1u < nc ? (int)(rel(x.y) >> low) : -1;
+                    const uint32_t many = (uint32_t)(__popcll(__ballot(top > prefix)) + __popcll(__ballot(next > prefix))) * weight;
+                    above = lane == v ? many : above;
+                    vm = top > prefix && x.x > vm ? x.x : vm;
+                    vm = next > prefix && x.y > vm ? x.y : vm;
+                    const uint32_t place = (uint32_t)(wave + v * NW) * (uint32_t)kTile + 2u * (uint32_t)lane;
+                    if (top == prefix) list_one(place, make_uint2(x.x, x.x));
+                    if (next == prefix) list_one(place + 1u, make_uint2(x.y, x.y));
+                } else {
+                    const int top = (uint32_t)lane < nc ? (int)(rel(x.x) >> low) : -1;
+                    const uint32_t many = (uint32_t)__popcll(__ballot(top > prefix)) * weight;
+                    above = lane == v ? many : above;
+                    vm = top > prefix && x.y > vm ? x.y : vm;
+                    hit_one(top == prefix, (uint32_t)v, x.x, x.y);
+                }
             });
             if (holds) atomicAdd(&tgt[own], above);
-            if (!__any(hits > 2u)) {
+            if (WINDOW) {
+            } else if (!__any(hits > 2u)) {
 #pragma unroll
                 for (uint32_t i = 0; i < 2u; ++i)
                     if (hits > i) list_one(((uint32_t)wave + hit_at[i] * NW) * (uint32_t)kTile + (uint32_t)lane, hit[i]);
             } else {
                 rows_of_memory(0u, [&](uint32_t t, uint32_t i0, uint2 x, bool valid, uint32_t) __attribute__((always_inline)) {
-                    if (i0 == 0u && valid && (int)(x.x >> kHist2Shift) == prefix) list_one(t * (uint32_t)kTile + (uint32_t)lane, x);
+                    if (i0 == 0u && valid && (int)(x.x >> low) == prefix) list_one(t * (uint32_t)kTile + (uint32_t)lane, x);
                 });
             }
             if (heavy)
-                rows_of_memory(64u, [&](uint32_t t, uint32_t i0, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
-                    const int top = valid ? (int)(x.x >> kHist2Shift) : -1;
+                more_rows([&](uint32_t t, uint32_t i0, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+                    const int top = valid ? (int)(rel(x.x) >> low) : -1;
                     const uint64_t more = __ballot(top > prefix);
                     vm = top > prefix && x.y > vm ? x.y : vm;
                     if (more && lane == 0) atomicAdd(&tgt[t], (uint32_t)__popcll(more) * weight);
@@ -838,7 +1224,7 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
         }
         __syncthreads();
         const uint32_t listed = equal;
-        search_list<4>(list, listed, kHist2Shift, lane, tau, need, equal);
+        search_list<4>(list, listed, low, lane, tau, need, equal);
         quota = need;
         ties = equal != quota;
         for (uint32_t i = tid; i < listed; i += LANES) {
@@ -855,26 +1241,51 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
                 vm = list_vb[i] > vm ? list_vb[i] : vm;
             }
         }
+        if constexpr (WINDOW) tau += lowest;
         __syncthreads();
     } else if (any) {
-        __syncthreads();
-        for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
-        __syncthreads();
-        rows_of_memory(0u, [&](uint32_t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
-            count_digit(h, valid && (int)(x.x >> kHist2Shift) == prefix, digit_place(x.x & 511u), true, lane, weight);
-        });
-        __syncthreads();
-        found = find_digit(h, need, lane);
-        tau |= found.digit;
-        quota = found.need;
-        equal = found.count;
+        if constexpr (WINDOW) {
+            for (int top = low; top > 0;) {  // the rest of the bits, ten at a time
+                const int shift = top > kHist2Bits ? top - kHist2Bits : 0;
+                __syncthreads();
+                for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
+                __syncthreads();
+                every_row([&](uint32_t, uint32_t x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+                    count_digit(h, valid && rel(x) >> top == tau >> top, digit_place((rel(x) >> shift) & ((1u << (top - shift)) - 1u)), true, lane, weight);
+                });
+                __syncthreads();
+                found = find_digit(h, need, lane);
+                tau |= found.digit << shift;
+                need = found.need;
+                equal = found.count;
+                top = shift;
+            }
+        } else {
+            __syncthreads();
+            for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;
+            __syncthreads();
+            rows_of_memory(0u, [&](uint32_t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+                count_digit(h, valid && (int)(x.x >> kHist2Shift) == prefix, digit_place(x.x & 511u), true, lane, weight);
+            });
+            __syncthreads();
+            found = find_digit(h, need, lane);
+            tau |= found.digit;
+            need = found.need;
+            equal = found.count;
+        }
+        quota = need;
         ties = equal != quota;
-        rows_of_memory(0u, [&](uint32_t t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
+        if constexpr (WINDOW) tau += lowest;
+        auto weigh = [&](uint32_t t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) {
             const uint64_t gm = __ballot(valid && x.x > tau), em = __ballot(valid && x.x == tau);
             if (gm && lane == 0) atomicAdd(&tgt[t], (uint32_t)__popcll(gm) * weight);
             if (em && lane == 0) atomicAdd(&teq[t], (uint32_t)__popcll(em) * weight);
             vm = valid && (ties ? x.x > tau : x.x >= tau) && x.y > vm ? x.y : vm;
-        });
+        };
+        if constexpr (WINDOW)
+            every_row([&](uint32_t t, uint32_t x, bool valid, uint32_t weight) __attribute__((always_inline)) { weigh(t, make_uint2(x, x), valid, weight); });
+        else
+            rows_of_memory(0u, [&](uint32_t t, uint32_t, uint2 x, bool valid, uint32_t weight) __attribute__((always_inline)) { weigh(t, x, valid, weight); });
         __syncthreads();
     }
     const bool count_equal = any && !few;  // tgt does not hold the kept ones of the bins equal to tau yet
@@ -929,7 +1340,7 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
     // largest component over the survivors (not needed when the caller fixed the range: Sec. 3.2.1, static max)
     uint32_t vmax = a.static_vmax;
     if (!vmax) {
-        if (count_equal && ties) {
+        if (count_equal && ties && !missed) {
             __syncthreads();
             for (uint32_t t = (uint32_t)wave; t < Tn; t += NW) {
                 const uint4 v = ti[t];
@@ -937,7 +1348,7 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
                 uint32_t eqseen = 0;  // bins of the tile equal to tau seen so far
                 for (uint32_t i0 = 0; i0 < nc && eqseen < take; i0 += 64u) {
                     const bool valid = i0 + (uint32_t)lane < nc;
-                    const uint2 x = cd[(size_t)t * kTile + (valid ? i0 + (uint32_t)lane : 0u)];
+                    const uint2 x = one_of(t, valid ? i0 + (uint32_t)lane : 0u);
                     const bool iseq = valid && x.x == tau;
                     const uint64_t em = __ballot(iseq);
                     vm = iseq && eqseen + prefix_popc(em) < take && x.y > vm ? x.y : vm;
@@ -968,14 +1379,16 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
     if (hdr.write && c == 0 && (!MERGED || at.tile == 0) && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
     return th;
 }
-template <bool TABLE, int NW, int FETCH>
+template <bool TABLE, bool WINDOW, int NW, int FETCH>
 __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, ResolveArgs a, uint32_t* __restrict__ sel, const uint32_t* __restrict__ tinfo,
                                                      uint32_t* __restrict__ tscan, const uint2* __restrict__ cand,
                                                      uint8_t* __restrict__ records, uint8_t* __restrict__ stream,
-                                                     HeaderInfo hdr, TableArg<TABLE> tab)
+                                                     HeaderInfo hdr, TableArg<TABLE> tab, const float* __restrict__ samples, size_t n)
 {
     __shared__ ResolveScratch<MAX_TILES> lds;
-    resolve_chunk<NW, FETCH, false>(place_of<TABLE>(u, tab, blockIdx.x, 0u), a, lds, sel, tinfo, tscan, cand, records, stream, hdr);
+    const Place at = place_of<TABLE>(u, tab, blockIdx.x, 0u);
+    resolve_chunk<NW, FETCH, false, WINDOW>(at, a, lds, sel, tinfo, tscan, cand, records, stream, hdr, WINDOW ? samples + at.spec : nullptr,
+                                            WINDOW ? present_of<true>(n, at.chunk, at.B) : 0u);
 }
 
 // ------------------------------------------------------------------ emit ----
@@ -1027,7 +1440,7 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
     }
     if constexpr (MERGED) {
         __shared__ ResolveScratch<kMergedTiles> lds;
-        found = resolve_chunk<NT / 64, kFetch, true>(at, a, lds, sel, tinfo, tscan, cand, records, stream, hdr);
+        found = resolve_chunk<NT / 64, kFetch, true, false>(at, a, lds, sel, tinfo, tscan, cand, records, stream, hdr, nullptr, 0u);
     }
     const uint32_t tau = found.tau, quota = found.quota, pbase = found.pbase, rank0 = found.rank0, eq0 = found.eq0;
     if (bits != 32)  // 32-bit codes go straight to memory
@@ -1828,6 +2241,11 @@ static bool resolve_in_emit(const Extent& x, int time_domain)
 {
     return x.most <= kMergedTiles && x.tiles <= (time_domain && x.most > 32 ? 256 : 512);
 }
+// k_sample instead of the histogram.  Shorter chunks would have half or a quarter of their samples looked at, longer ones have more tiles than
+// k_resolve holds the summaries of.  Sender and receiver in us, 8-bit codes of 20 %, histogram / sample:  2^18 6 M samples 47.7 / 49.3, 8 M 53.9 /
+// 53.8, 10 M 76.7 / 67.7, 18 M 104 / 84;  2^19 6 M 54.3 / 56.3, 8 M 61.3 / 67.3, 10 M 85.9 / 74.0, 18 M 107 / 94;  2^20 6 M 59.3 / 62.2, 8 M 67.5 / 66.4, 10 M
+// 76.7 / 74.6, 18 M 147 / 127;  62 M, 15 % kept at 32 bits 2^20 253 / 219, 85 % at 8 bits 2^18 276 / 239;  2^16, 30 % at 32 bits 251 / 258.
+static bool sampled(uint32_t chunk_tiles, size_t tiles) { return chunk_tiles >= 128 && chunk_tiles <= kKeptTiles && tiles > 4096; }
 // In k_decode it is the bitmap up to the tile, at most 256 bytes for each tile of the chunk, to read beside the tile's codes.
 // Decompress: one chunk of 2^16 21.7 -> 17.7 us, 2^23 samples in chunks of 2^20 (2056 tiles) 49.4 -> 48.8, 2^24 76.6 -> 77.8, one
 // chunk of 2^22 (1025 tiles) 50.3 -> 52.5.  Chunks of a few tiles always: Top-k of 2^24 samples in chunks of 2^12 32.8 -> 16.2.
@@ -1851,7 +2269,11 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
     if (a.half && (a.tab || a.time_domain || !a.pair_log || !hist_ready)) return hipErrorInvalidValue;
     if (a.tab && !hist_ready) return hipErrorInvalidValue;
 
-    if (!hist_ready) {
+    const bool window = a.time_domain && sampled(u.Tn, x.tiles);
+    if (window) {
+        FFTSP_LAUNCH("sample", k_sample, dim3((unsigned)a.C), dim3(kSampleLanes), 0, s, spec, a.L, a.k, a.n, sel,
+                     reinterpret_cast<uint32_t*>(ws_base + w.status));
+    } else if (!hist_ready) {
         hipError_t e = launch_zero_control(ws_base, w, a.C, s);
         if (e != hipSuccess) return e;
         const uint32_t groups = (u.Tn + HIST_TILES - 1) / HIST_TILES;
@@ -1886,7 +2308,11 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
                     FFTSP_LAUNCH("collect", (k_collect<FIND, false, false, false>), per_tile, dim3(NT), 0, s, X, u, hist, sel, tinfo, tscan, cand, clear, tab, a.n);
             }
         };
-        if (find_in_collect(x)) {
+        if (window) {
+            if constexpr (!TABLE)
+                FFTSP_LAUNCH("collect", (k_collect<false, false, true, false, true>), per_tile, dim3(NT), 0, s, spec, u, hist, sel, tinfo, tscan, cand, clear, tab,
+                             a.n);
+        } else if (find_in_collect(x)) {
             collect(std::true_type{});
         } else {
             FFTSP_LAUNCH("find_bucket", k_find_bucket<TABLE>, per_chunk, dim3(NT), 0, s, hist, u, sel, tab);
@@ -1912,8 +2338,15 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
         }
         auto resolve = [&](auto waves, auto fetch) {
             constexpr int NW = decltype(waves)::value, FETCH = decltype(fetch)::value;
-            FFTSP_LAUNCH("resolve", (k_resolve<TABLE, NW, FETCH>), per_chunk, dim3(NW * 64), 0, s, u, ra, sel, tinfo, tscan, cand, records, stream_base,
-                         h, tab);
+            if constexpr (!TABLE) {
+                if (window) {
+                    FFTSP_LAUNCH("resolve", (k_resolve<false, true, NW, FETCH>), per_chunk, dim3(NW * 64), 0, s, u, ra, sel, tinfo, tscan, cand, records,
+                                 stream_base, h, tab, spec, a.n);
+                    return hipGetLastError();
+                }
+            }
+            FFTSP_LAUNCH("resolve", (k_resolve<TABLE, false, NW, FETCH>), per_chunk, dim3(NW * 64), 0, s, u, ra, sel, tinfo, tscan, cand, records, stream_base,
+                         h, tab, nullptr, a.n);
             return hipGetLastError();
         };
         // few waves for few tiles: their barriers are cheaper than more hands
