@@ -199,6 +199,36 @@ __device__ __forceinline__ void run_fft(float2* d, const float2* tw, int tid)
     }
 }
 
+// The same, but the last stage leaves its outputs in registers: put(q, t, value) of row j + t * R / 2^RL, j = (tid + q * NT) / T, slot tid % T.
+template <int LOGR, int LOGT, int NT, bool INV, int NS_LOG, typename Put>
+__device__ __forceinline__ void run_fft_put(float2* d, const float2* tw, int tid, Put&& put)
+{
+    constexpr int RL = stage_radix_log(LOGR - NS_LOG);
+    if constexpr (NS_LOG + RL < LOGR) {
+        fft_stage<LOGR, LOGT, NT, INV, NS_LOG, RL>(d, tw, tid);
+        run_fft_put<LOGR, LOGT, NT, INV, NS_LOG + RL>(d, tw, tid, static_cast<Put&&>(put));
+    } else {
+        constexpr int R = 1 << LOGR, T = 1 << LOGT, RHO = 1 << RL, PER = (R / RHO) * T / NT;
+        static_assert(PER * NT == (R / RHO) * T, "butterflies for all lanes");
+        float2 v[PER][RHO];
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+#pragma unroll
+            for (int t = 0; t < RHO; ++t) v[q][t] = d[sw_idx<LOGT>(((tid + q * NT) >> LOGT) + t * (R / RHO), tid & (T - 1))];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+#pragma unroll
+            for (int t = 1; t < RHO; ++t) {
+                const float2 c = tw[t * ((tid + q * NT) >> LOGT)];
+                v[q][t] = INV ? cmulc(v[q][t], c) : cmul(v[q][t], c);
+            }
+            butterfly<RL, INV>(v[q]);
+#pragma unroll
+            for (int t = 0; t < RHO; ++t) put(q, t, v[q][t]);
+        }
+    }
+}
+
 // LDS stages run_fft takes for `rem` remaining levels
 constexpr int lds_stages(int rem)
 {

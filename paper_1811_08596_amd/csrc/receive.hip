@@ -223,20 +223,26 @@ __device__ __forceinline__ void receive_tile(const uint8_t* __restrict__ record,
     }
     if constexpr (U > 1) outer_twiddles();
     __syncthreads();
-    run_fft<LOGN2, LOGT, NT, true, 3>(d, tw, tid);
     // one base for all lanes and 32-bit offsets: a chunk is 16 MB at most
     auto store = [&](uint32_t i, typename Cx<HALF>::One z) __attribute__((always_inline)) {
         *reinterpret_cast<typename Cx<HALF>::One*>(reinterpret_cast<uint8_t*>(mid) + i * (uint32_t)sizeof(z)) = z;
     };
     const uint32_t column = 2u * pp0 + (uint32_t)slot;
+    auto out = [&](int u, int q, float2 z) __attribute__((always_inline)) {
+        store(((uint32_t)(kq_of(u) + q * DK) << logN1) + column, cx_store<HALF>(cmulc(z, cur[u])));
+        cur[u] = cmul(cur[u], ratio);
+    };
+    if constexpr (LOGN2 > 7) {
+        // A last stage of radix 8 leaves every lane what it stores, so a trip through LDS and two barriers are saved: chunks of 2^22 344 -> 317 us, of 2^20
+        // in binary16 101 -> 94.
+        run_fft_put<LOGN2, LOGT, NT, true, 3>(d, tw, tid, out);
+    } else {
+        run_fft<LOGN2, LOGT, NT, true, 3>(d, tw, tid);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int n2 = kq_of(u) + q * DK;
-            store(((uint32_t)n2 << logN1) + column, cx_store<HALF>(cmulc(d[sw_idx<LOGT>(n2, slot)], cur[u])));
-            cur[u] = cmul(cur[u], ratio);
-        }
+            for (int q = 0; q < 8; ++q) out(u, q, d[sw_idx<LOGT>(kq_of(u) + q * DK, slot)]);
+    }
 }
 
 // every XCD has a stretch of the launch's workgroups of its own; at or above `total`: none
