@@ -268,9 +268,9 @@ struct Stretch {
         rel = bit - 32u * (uint32_t)first;
         __builtin_memcpy(w, codes + first, sizeof(w));
     }
-    // put(j, value) for all bins, zero where one is not kept
+    // put(j, word) for all bins: the code's two fields and what is above them, zero where one is not kept
     template <typename Put>
-    __device__ __forceinline__ void unpack(uint32_t twoN, uint32_t bits, int shift, uint32_t base, Put&& put)
+    __device__ __forceinline__ void unpack_codes(uint32_t twoN, Put&& put)
     {
         while (__any(rel >= 32u)) {  // windows moved back from a record's end
             const bool on = rel >= 32u;
@@ -281,16 +281,24 @@ struct Stretch {
         }
 #pragma unroll
         for (int i = 0; i + 1 < WORDS; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], rel);
-        asm("" : "+v"(base));  // in a vector register, so that it is the addend of a shift-and-add
 #pragma unroll
         for (int j = 0; j < BINS; ++j) {
             const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)mask, j, 1), raw = w[0] & m, by = m & twoN;
 #pragma unroll
             for (int i = 0; i + 1 < WORDS; ++i)
                 if (32 * i < (BINS - 1 - j) * WIDEST) w[i] = i + 2 < WORDS ? __builtin_amdgcn_alignbit(w[i + 1], w[i], by) : w[i] >> by;
+            put(j, raw);
+        }
+    }
+    // put(j, value) for all bins, zero where one is not kept
+    template <typename Put>
+    __device__ __forceinline__ void unpack(uint32_t twoN, uint32_t bits, int shift, uint32_t base, Put&& put)
+    {
+        asm("" : "+v"(base));  // in a vector register, so that it is the addend of a shift-and-add
+        unpack_codes(twoN, [&](int j, uint32_t raw) __attribute__((always_inline)) {
             put(j, make_float2(__uint_as_float(dequantize_field(raw, 0u, bits, base, shift)),
                                __uint_as_float(dequantize_field(raw, bits, bits, base, shift))));
-        }
+        });
     }
 };
 

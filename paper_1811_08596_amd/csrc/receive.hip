@@ -10,13 +10,15 @@
 // codes.  Workgroups are dealt out to the XCDs round-robin, so each XCD gets a stretch of chunks of its own and its workgroups neighbouring
 // tiles of it: the lines come over the fabric once and then out of that XCD's L2.
 //
-// What bounds it: about 100 vector instructions a point (44 to 87 of the 116 us below, at two to four cycles each), the two dependent trips to memory before a
-// tile's transform, and the barriers in it.  So a lane has eight points and a SIMD six or eight waves where the tile allows it, and nothing
-// is kept for a next tile: a workgroup does one.  (Persistent workgroups of sixteen points a lane that fetched the next tile's entries and
-// codes during the transform took 124 to 134 us; a lane that looked up each of its bins alone 187.)
+// What bounds it: the two dependent trips to memory before a tile's transform, the barriers in it, and about 90 vector instructions a point
+// (40 to 80 of the 104 us below).  None of them alone: what helps is tiles beside each other in a compute unit, whose waits another
+// one's work fills.  Launches with enough tiles keep a tile in half of the LDS (receive_pairs), which makes it four tiles a compute unit
+// for rows of 2^9 and two for 2^10; in shorter ones, a tile or two a compute unit anyhow, the fewer barriers of receive_tile do better.
+// (Persistent workgroups of sixteen points a lane that fetched the next tile's entries and codes during the transform took 124 to 134 us where
+// receive_tile took 116; a lane that looked up each of its bins alone 187.)
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against counting, decoding and the pass: 6 + 54 + 110
-// -> 6 + 116 us; 138 M in chunks of 2^22 15 + 118 + 275 -> 12 + 341; binary16 5 + 33 + 95 -> 6 + 96.
-// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 6 + 38 + 40.
+// -> 6 + 104 us; 138 M in chunks of 2^22 15 + 118 + 275 -> 12 + 254; binary16 5 + 33 + 95 -> 6 + 82.
+// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 6 + 36 + 33.
 // Several senders' streams are decoded into a spectrum first (codec.hip): eight of them took 444 us this way against 285, since every
 // stretch of eight bins is two and a half lines out of L2.
 #include "fft_core.h"
@@ -99,17 +101,12 @@ __global__ __launch_bounds__(kTableLanes) void k_bitmap_table_long(const uint8_t
 }
 
 // ---------------------------------------------------------- inverse pass B ----
-// Eight points a lane and six or eight waves a SIMD where the tile allows it: what this kernel waits for are its two dependent trips to
-// memory and the barriers between the transform's stages, and it moves half the bytes of a transform pass.
+// The kernel of short launches: eight points a lane where the tile allows it.
 template <int LOGN2>
 struct Receive {
     static constexpr int N2 = 1 << LOGN2, LOGT = 4, SLOTS = 1 << LOGT;
     static constexpr int U = LOGN2 >= 10 ? 2 : 1, NT = 2 * N2 / U;  // eights of points of a lane
-    // Waves a SIMD in long launches.  Workgroups of 256 lanes do better with six and 80 registers than with eight, for which three to seven are
-    // spilled: chunks of 2^16, half kept, 8 bits, 181 46.5 / 45.5 us, 724 168 / 151, 10 bits 48.5 / 45.6 and 183 / 154, binary16 133 / 122; seven 160
-    // and 165, five 153 and 156.  512 lanes spill none: 2^17, 362 chunks 148.8, with six 148.1, with four 159.  With 1024 there is only four
-    // beside eight, which spill three at most: 62 M samples in chunks of 2^20 270 / 221 us, ResNet-50's tensors 430 / 417 (whole calls).
-    static constexpr int WAVES = LOGN2 == 7 ? 6 : 8 / U;
+    static constexpr int WAVES = 8 / U;  // a SIMD: as many as the LDS leaves
     static constexpr int BINS = SLOTS / 2;                         // neighbouring bins of either side of a run
     static constexpr size_t kLds = ((size_t)(SLOTS + 1) << LOGN2) * sizeof(float2);
 };
@@ -233,8 +230,8 @@ __device__ __forceinline__ void receive_tile(const uint8_t* __restrict__ record,
         cur[u] = cmul(cur[u], ratio);
     };
     if constexpr (LOGN2 > 7) {
-        // A last stage of radix 8 leaves every lane what it stores, so a trip through LDS and two barriers are saved: chunks of 2^22 344 -> 317 us, of 2^20
-        // in binary16 101 -> 94.
+        // A last stage of radix 8 leaves every lane what it stores, so a trip through LDS and two barriers are saved: long launches of it, chunks of
+        // 2^22 344 -> 317 us, of 2^20 in binary16 101 -> 94.
         run_fft_put<LOGN2, LOGT, NT, true, 3>(d, tw, tid, out);
     } else {
         run_fft<LOGN2, LOGT, NT, true, 3>(d, tw, tid);
@@ -245,6 +242,208 @@ __device__ __forceinline__ void receive_tile(const uint8_t* __restrict__ record,
     }
 }
 
+// The kernel of long launches: a tile in half of the LDS and half of the lanes, sixteen points each.
+//
+// What goes through LDS before the split are the codes, a word to a bin, [side][run][pair]: a lane writes the eight of a stretch as they lie
+// and reads, of a pair of slots, rows that are each other's mirrors, so that every bin is read once and a lane has both of a split's
+// inputs.  Those rows are also the inputs of two radix-8 butterflies.  Between the stages real and imaginary parts go through LDS one after
+// the other.  The last stage goes to memory from registers.  Same arithmetic as receive_tile, bit for bit.
+//
+// Eight waves a SIMD (64 registers, none spilled): with six, 62 M samples in chunks of 2^20 104 -> 110 us, binary16 82 -> 86, 40 M in chunks
+// of 2^16 58 -> 60.  Outer twiddles fetched before the stages: 104 -> 106, 82 -> 84.
+template <int LOGN2>
+struct ReceivePairs {
+    static constexpr int N2 = 1 << LOGN2, SLOTS = 16, BINS = 8, NT = N2;
+    static constexpr size_t kLds = (size_t)N2 * (SLOTS * sizeof(uint32_t) + sizeof(float2));
+};
+template <int LOGN2, bool HALF, int WIDEST>
+__device__ __forceinline__ void receive_pairs(const uint8_t* __restrict__ record, uint32_t W, uint32_t S, int code_bits, int m,
+                                              const uint2* __restrict__ entries, int logM, typename Cx<HALF>::One* __restrict__ mid, Tables tb,
+                                              uint32_t pp0, bool first, uint32_t* lds, int tid, float mid_scale)
+{
+    using G = ReceivePairs<LOGN2>;
+    constexpr int N2 = G::N2, NT = G::NT, DK = N2 / 8, BINS = G::BINS;
+    float* const d = reinterpret_cast<float*>(lds);
+    float2* const tw = reinterpret_cast<float2*>(lds + N2 * G::SLOTS);
+    const int logN1 = logM - LOGN2;
+    const uint32_t M = 1u << logM, N1 = 1u << logN1;
+
+    const uint32_t bits = (uint32_t)code_bits, twoN = 2u * bits;
+    const int shift = 23 - m;
+    const int final = last_code_word(S, W);
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(record) + 4 + W;
+    uint32_t vbase = (scalar_load(reinterpret_cast<const uint32_t*>(record)) - 1u) << shift;
+
+    // A lane's two stretches of bins: run tid, its lower rows and the mirrors.  The latter start at one more than a multiple of
+    // eight, so the last bin may be in the bitmap's next word.
+    auto first_of = [&](int i) __attribute__((always_inline)) {  // the stretch's first bin
+        return ((uint32_t)tid << logN1) + (i ? N1 - pp0 - (BINS - 1u) : pp0);
+    };
+    u32x4 entry[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) __builtin_memcpy(&entry[i], reinterpret_cast<const uint8_t*>(entries) + (first_of(i) >> 5) * 8u, sizeof(u32x4));
+    load_stage_twiddles<LOGN2, NT>(tw, tb, tid);
+    Stretch<BINS, WIDEST> o[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t at = first_of(i) & 31u, all = (1u << BINS) - 1u;
+        // row N1 is the next run's
+        o[i].mask = __builtin_amdgcn_alignbit(entry[i][2], entry[i][0], at) & (i && pp0 == 0 ? all >> 1 : all);
+        o[i].fetch(words, final, (entry[i][1] + (uint32_t)__popc(entry[i][0] & ((1u << at) - 1u))) * twoN);
+    }
+    // What the lane has of the first stage: rows at[0] + q * DK of one slot and at[1] + q * DK of another, whose mirrors they are (q and 7 - q):
+    // a pair's lower slot and its upper one.  Rows 0 and N1/2 are their own mirrors: of those the lane has both from the same slot, and the
+    // last lane, row 0's points 0 and DK / 2, each with itself.
+    const int j = tid & (BINS - 1), r = tid >> 3;
+    const bool self = pp0 == 0 && j == 0, lower = r >= DK / 2, alone = self && r == DK / 2;
+    const int at[2] = {self && lower ? r - DK / 2 : r, self && lower ? (alone ? DK / 2 : DK + DK / 2 - r) : DK - 1 - r};
+    const int upper[2] = {self && !lower ? 1 : 0, self && lower ? 0 : 1};
+    float2 base[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t pp = pp0 + (uint32_t)j, k = upper[i] ? mirror_row(pp, N1) : pp;
+        base[i] = twiddle(tb, (k + ((uint32_t)at[i] << logN1)) << (21 - logM));
+    }
+    // codes[side][run][pair]
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        uint32_t code[BINS];
+        o[i].unpack_codes(twoN, [&](int b, uint32_t raw) __attribute__((always_inline)) { code[i ? BINS - 1 - b : b] = raw; });
+        uint4* to = reinterpret_cast<uint4*>(lds + (i * N2 + tid) * BINS);
+        to[0] = make_uint4(code[0], code[1], code[2], code[3]);
+        to[1] = make_uint4(code[4], code[5], code[6], code[7]);
+    }
+    asm("" : "+v"(vbase));  // in a vector register, so that it is the addend of a shift-and-add
+    auto value = [&](uint32_t raw) __attribute__((always_inline)) {  // as a spectrum would hold it
+        return cx_load(cx_store<HALF>(make_float2(__uint_as_float(dequantize_field(raw, 0u, bits, vbase, shift)),
+                                                  __uint_as_float(dequantize_field(raw, bits, bits, vbase, shift)))));
+    };
+    float last = 0.f;  // the Nyquist bin
+    if (first) {
+        // one bin on its own: those outside the stretches
+        auto single = [&](uint32_t bin) __attribute__((always_inline)) {
+            const uint2 e = entries[bin >> 5];
+            const uint32_t bit = (e.y + (uint32_t)__popc(e.x & ((1u << (bin & 31u)) - 1u))) * twoN;
+            const int i = code_word(bit, final), i1 = word_after(i, final);
+            return (e.x >> (bin & 31u)) & 1u ? __builtin_amdgcn_alignbit(words[i1], words[i], bit) : 0u;
+        };
+        if (pp0 == 0) {
+            lds[(N2 + tid) * BINS] = single(((uint32_t)tid << logN1) + N1 / 2);  // it is its own mirror
+            last = value(single(M)).x;
+        }
+    }
+    __syncthreads();
+    float2 v[16];
+    {
+        const uint32_t *a = lds + (upper[0] * N2 + at[0]) * BINS + j, *b = lds + (upper[1] * N2 + at[1]) * BINS + j;
+        auto turned = [&](int i, int q) __attribute__((always_inline)) { return cmul(base[i], make_float2(kW32re[2 * q], kW32im[2 * q])); };
+        if (first) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                asm volatile("" ::: "memory");  // one after the other: all at once take more registers than there are
+                float2 x = value(a[q * DK * BINS]), y = value((alone ? a : b)[(alone ? (8 - q) & 7 : 7 - q) * DK * BINS]);
+                if (q == 0 && alone) {  // imaginary parts of the DC and Nyquist bins are ignored
+                    x.y = 0.f;
+                    y = make_float2(last, 0.f);
+                }
+                v[q] = split_inv(x, y, turned(0, q));
+                v[15 - q] = split_inv(value(b[(7 - q) * DK * BINS]), value((alone ? b : a)[q * DK * BINS]), turned(1, 7 - q));
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const float2 x = value(a[q * DK * BINS]), y = value(b[(7 - q) * DK * BINS]);
+                v[q] = split_inv(x, y, turned(0, q));
+                v[15 - q] = split_inv(y, x, turned(1, 7 - q));
+            }
+        }
+    }
+    bf8<true>(v);
+    bf8<true>(v + 8);
+    // Row i, slot s of a component (slots: eight lower rows, then their mirrors), so that 64 lanes of either kind have two words of every bank.
+    auto swizzled = [](int word, int x) __attribute__((always_inline)) { return word ^ (x & 3) << 3; };
+    auto exchange = [&](auto&& to, auto&& from) __attribute__((always_inline)) {
+        float x[16];
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) d[to(n)] = v[n].x;
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) x[n] = d[from(n)];
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) d[to(n)] = v[n].y;
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) v[n] = make_float2(x[n], d[from(n)]);
+    };
+    const int slot = tid & 15, s = (slot & 1) * BINS + (slot >> 1);
+    auto row_of = [&](int q) __attribute__((always_inline)) { return (tid >> 4) + q * (N2 / 16); };
+    // inputs of a stage of radix 2^RL, and the stage
+    auto input = [&](auto rl, int n) __attribute__((always_inline)) {
+        constexpr int RL = decltype(rl)::value, RHO = 1 << RL, STEP = N2 / RHO;
+        const int i = row_of(n / RHO), t = n % RHO;
+        return swizzled(i * 16 + s, STEP >= 32 ? i >> 3 : (i >> 3) + t * (STEP / 8)) + t * STEP * 16;
+    };
+    auto stage = [&](auto rl, auto ns) __attribute__((always_inline)) {
+        constexpr int RL = decltype(rl)::value, RHO = 1 << RL, NS_LOG = decltype(ns)::value;
+#pragma unroll
+        for (int q = 0; q < 16 / RHO; ++q) {
+            const int k = row_of(q) & ((1 << NS_LOG) - 1);
+#pragma unroll
+            for (int t = 1; t < RHO; ++t) v[q * RHO + t] = cmulc(v[q * RHO + t], tw[(t * k) << (LOGN2 - NS_LOG - RL)]);
+            butterfly<RL, true>(v + q * RHO);
+        }
+    };
+    constexpr int RL2 = stage_radix_log(LOGN2 - 3), RL3 = LOGN2 - 3 - RL2, LAST = RL3 ? RL3 : RL2;
+    static_assert(RL3 == 0 || stage_radix_log(RL3) == RL3, "three stages at most");
+    using Second = std::integral_constant<int, RL2>;
+    using Third = std::integral_constant<int, LAST>;
+    // What the lane stores: two chains of eight rows of its slot, an eighth of the rows apart, with their twiddles.
+    constexpr int RHO = 1 << LAST, CHAINS = RHO / 8;
+    const uint32_t column = 2u * pp0 + (uint32_t)slot, k = slot & 1 ? mirror_row(pp0 + (uint32_t)(slot >> 1), N1) : pp0 + (uint32_t)(slot >> 1);
+    auto first_row = [&](int g) __attribute__((always_inline)) { return row_of(g / CHAINS) + g % CHAINS * (N2 / RHO); };
+    const int sh = 22 - logM;
+    float2 cur[2], ratio;
+    auto outer_twiddles = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            cur[g] = twiddle(tb, ((uint32_t)first_row(g) * k) << sh);
+            if constexpr (HALF) cur[g] = make_float2(cur[g].x * mid_scale, cur[g].y * mid_scale);
+        }
+        ratio = twiddle(tb, ((uint32_t)DK * k) << sh);
+    };
+    exchange(
+        [&](int n) __attribute__((always_inline)) {
+            const int i = at[n >> 3], t = n & 7;
+            return i * 128 + (t >> 1) * 32 + swizzled((t & 1) * 16 + upper[n >> 3] * BINS + j, i);
+        },
+        [&](int n) __attribute__((always_inline)) { return input(Second{}, n); });
+    stage(Second{}, std::integral_constant<int, 3>{});
+    if constexpr (RL3 > 0) {
+        exchange(
+            [&](int n) __attribute__((always_inline)) {
+                const int i = row_of(n >> RL2), t = n & ((1 << RL2) - 1);
+                return swizzled((((i >> 3) << (3 + RL2)) + (i & 7)) * 16 + s, t) + t * 128;
+            },
+            [&](int n) __attribute__((always_inline)) { return input(Third{}, n); });
+        stage(Third{}, std::integral_constant<int, 3 + RL2>{});
+    }
+    outer_twiddles();
+    // one base for all lanes and 32-bit offsets: a chunk is 16 MB at most
+#pragma unroll
+    for (int g = 0; g < 2; ++g) {
+        float2 z = cur[g];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const uint32_t i = ((uint32_t)(first_row(g) + u * DK) << logN1) + column;
+            *reinterpret_cast<typename Cx<HALF>::One*>(reinterpret_cast<uint8_t*>(mid) + i * (uint32_t)sizeof(typename Cx<HALF>::One)) =
+                cx_store<HALF>(cmulc(v[g / CHAINS * RHO + g % CHAINS + u * CHAINS], z));
+            z = cmul(z, ratio);
+        }
+    }
+}
+
 // every XCD has a stretch of the launch's workgroups of its own; at or above `total`: none
 __device__ __forceinline__ uint32_t in_stretches(uint32_t total)
 {
@@ -252,8 +451,8 @@ __device__ __forceinline__ uint32_t in_stretches(uint32_t total)
     const uint32_t t = lo + (blockIdx.x >> 3);
     return t < hi ? t : total;
 }
-template <int LOGN2, bool HALF, int WIDEST, int WAVES>
-__global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) void k_receive_b(
+template <int LOGN2, bool HALF, int WIDEST>
+__global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(Receive<LOGN2>::WAVES, Receive<LOGN2>::WAVES))) void k_receive_b(
     const uint8_t* __restrict__ records, uint32_t W, uint32_t S, int bits, int m, const uint2* __restrict__ table, int logM,
     typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total, float mid_scale)
 {
@@ -265,6 +464,19 @@ __global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per
     const uint32_t c = t >> log_tiles, pp0 = (t & ((1u << log_tiles) - 1u)) * (G::SLOTS / 2);
     receive_tile<LOGN2, HALF, WIDEST>(records + (size_t)c * S, W, S, bits, m, table + (size_t)c * table_stride(logM), logM, mid + ((size_t)c << logM), tb,
                                       pp0, pp0 == 0, smem, threadIdx.x, mid_scale);
+}
+template <int LOGN2, bool HALF, int WIDEST>
+__global__ __launch_bounds__(ReceivePairs<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_receive_pairs(
+    const uint8_t* __restrict__ records, uint32_t W, uint32_t S, int bits, int m, const uint2* __restrict__ table, int logM,
+    typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total, float mid_scale)
+{
+    extern __shared__ float2 smem[];
+    const int log_tiles = logM - LOGN2 - 4;
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const uint32_t c = t >> log_tiles, pp0 = (t & ((1u << log_tiles) - 1u)) * 8u;
+    receive_pairs<LOGN2, HALF, WIDEST>(records + (size_t)c * S, W, S, bits, m, table + (size_t)c * table_stride(logM), logM, mid + ((size_t)c << logM), tb,
+                                       pp0, pp0 == 0, reinterpret_cast<uint32_t*>(smem), threadIdx.x, mid_scale);
 }
 // Tensors of different lengths: those with rows of up to 2^9 are one launch, a workgroup of 1024 lanes does one tile of rows of 2^9,
 // two of 2^8 or four of 2^7; those with rows of 2^10 are another (TOP 10).
@@ -296,21 +508,52 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(Receive<TO
     run(std::integral_constant<int, TOP>{});
 }
 
+template <int TOP, int WIDEST>
+__global__ __launch_bounds__(ReceivePairs<TOP>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_receive_pairs_long(
+    const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total,
+    LongTable tab, LongStarts at)
+{
+    extern __shared__ float2 smem[];
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const LongShare share = long_share(at, t);
+    const LongTensor& x = tab.t[share.tensor];
+    auto run = [&](auto n2) __attribute__((always_inline)) {
+        constexpr int LOGN2 = decltype(n2)::value, LOGSUB = LOGN2 < TOP ? TOP - LOGN2 : 0;
+        using G = ReceivePairs<LOGN2>;
+        const uint32_t sub = LOGSUB ? (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / G::NT) : 0u, pp0 = ((share.blk << LOGSUB) + sub) * 8u;
+        receive_pairs<LOGN2, false, WIDEST>(records + x.roff, (1u << x.logM) / 32u + 1u, x.stride, bits, m, table + long_entries(x, share.tensor), x.logM,
+                                            mid + long_mid(x), tb, pp0, share.blk == 0, reinterpret_cast<uint32_t*>(smem) + sub * (G::kLds / 4),
+                                            threadIdx.x & (G::NT - 1), 1.0f);
+    };
+    if constexpr (TOP == 9) {
+        const int rows = x.logM / 2;
+        if (rows == 7) return run(std::integral_constant<int, 7>{});
+        if (rows == 8) return run(std::integral_constant<int, 8>{});
+    }
+    run(std::integral_constant<int, TOP>{});
+}
+
 // ------------------------------------------------------------------ launch ----
 template <int LOGN2, bool HALF, int WIDEST>
 hipError_t receive_b(const uint8_t* records, const CodecArgs& a, int logM, const uint2* table, float2* mid, Tables t, hipStream_t s)
 {
-    using G = Receive<LOGN2>;
-    const size_t total = a.C << (logM - LOGN2 - G::LOGT);
-    constexpr size_t one_wave = 256 * 4 * 64 / G::NT;  // workgroups that are a wave on every SIMD
-    // As many waves as there can be while most workgroups run at once: chunks of 2^16, 10 bits, 10 % kept, eight waves / six, 96 34.6 / 35.2, 128 37.8 /
-    // 39.5, 129 43.8 / 46.1, 160 44.7 / 44.9, 181 47.0 / 46.2.
-    const auto kern = total <= 10 * one_wave ? k_receive_b<LOGN2, HALF, WIDEST, 8 / G::U> : k_receive_b<LOGN2, HALF, WIDEST, G::WAVES>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::kLds);
-    if (e != hipSuccess) return e;
-    FFTSP_LAUNCH("irfft_pass_b", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(G::NT), G::kLds, s, records, (1u << logM) / 32u + 1u, (uint32_t)a.S,
-                 a.bits, a.m, table, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, (uint32_t)total, HALF ? 1.0f / half_lift(logM) : 1.0f);
-    return hipGetLastError();
+    const size_t total = a.C << (logM - LOGN2 - 4);
+    // Where there is more than a tile to a compute unit (rows of 2^9 and 2^10), or more than its SIMDs hold of receive_tile's.  Whole receivers in
+    // us, receive_tile / receive_pairs, 8-bit codes of half of the bins, by tiles:  2^21 192 38.3 / 41.0, 384 64.9 / 61.2, 1920 255 / 225;  2^22 128 40.0
+    // / 42.5, 256 45.2 / 47.5, 512 78.0 / 72.6, 2048 300 / 277;  2^20 128 22.3 / 22.7, 320 33.3 / 32.7, 640 52.4 / 51.1, 3840 225 / 210;  2^18 1280 46.1 / 47.1 and 45.8
+    // / 45.5, 2560 75.2 / 72.9;  2^17 1280 42.7 / 43.4, 2560 69.5 / 68.8;  2^16 1600 31.6 / 30.8 and 33.9 / 34.5, 2560 47.3 / 44.2 and 43.3 / 46.5,
+    // 4800 67.8 / 64.6, 11200 150 / 144.
+    constexpr size_t kPairsFrom = LOGN2 >= 9 ? 257 : 10 * 256 * 4 * 64 / Receive<LOGN2>::NT + 1;
+    auto launch = [&](auto kern, unsigned lanes, size_t lds) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        FFTSP_LAUNCH("irfft_pass_b", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(lanes), lds, s, records, (1u << logM) / 32u + 1u, (uint32_t)a.S,
+                     a.bits, a.m, table, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, (uint32_t)total, HALF ? 1.0f / half_lift(logM) : 1.0f);
+        return hipGetLastError();
+    };
+    return total >= kPairsFrom ? launch(k_receive_pairs<LOGN2, HALF, WIDEST>, ReceivePairs<LOGN2>::NT, ReceivePairs<LOGN2>::kLds)
+                               : launch(k_receive_b<LOGN2, HALF, WIDEST>, Receive<LOGN2>::NT, Receive<LOGN2>::kLds);
 }
 template <int LOGN2>
 hipError_t receive_rows(const uint8_t* records, const CodecArgs& a, int logM, const uint2* table, float2* mid, Tables t, hipStream_t s)
@@ -392,17 +635,29 @@ hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* 
     hipError_t e = hipGetLastError();
     uint32_t split = b.count;  // the longest come last
     while (split > 0 && b.tab.t[split - 1].logM / 2 >= 10) --split;
-    auto pass = [&](auto kern, size_t lds, uint32_t from, uint32_t end, int log_points) {
+    // receive_pairs from four tiles of 2^13 points a compute unit on, or one of 2^14.  Whole calls (sender too) in us, receive_tile / receive_pairs:
+    // 2^13 points 256 73.6 / 74.3, 512 119 / 119.5, 768 164.6 / 166.6;  ResNet-50-like 344 / 334, 606 / 588;  2^14 192 114 / 117.5, 256 142.7 / 145.1, 320 166.8 / 164.7,
+    // 384 197.9 / 194.5, 512 197.3 / 193.1.
+    auto pass = [&](auto kern, auto pairs, uint32_t pairs_from, unsigned lanes, size_t lds, size_t pairs_lds, uint32_t from, uint32_t end, int log_points) {
+        const uint32_t total = starts(from, end, [&](int logM) { return 1u << (logM - log_points); });
+        const bool long_one = total >= pairs_from;
+        if (long_one) {
+            kern = pairs;
+            lds = pairs_lds;
+        }
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err != hipSuccess) return err;
-        const uint32_t total = starts(from, end, [&](int logM) { return 1u << (logM - log_points); });
-        FFTSP_LAUNCH("irfft_pass_b", kern, dim3((total + 7) / 8 * 8), dim3(1024), lds, s, stream + 64, a.bits, a.m, entries, mid, t, total, b.tab, at);
+        FFTSP_LAUNCH("irfft_pass_b", kern, dim3((total + 7) / 8 * 8), dim3(long_one ? lanes : 1024u), lds, s, stream + 64, a.bits, a.m, entries, mid, t,
+                     total, b.tab, at);
         return hipGetLastError();
     };
+    const bool narrow = a.bits <= 8;
     if (e == hipSuccess && split > 0)
-        e = pass(a.bits <= 8 ? k_receive_b_long<9, 16> : k_receive_b_long<9, 30>, Receive<9>::kLds, 0, split, 9 + Receive<9>::LOGT);
+        e = pass(narrow ? k_receive_b_long<9, 16> : k_receive_b_long<9, 30>, narrow ? k_receive_pairs_long<9, 16> : k_receive_pairs_long<9, 30>, 1025u,
+                 ReceivePairs<9>::NT, Receive<9>::kLds, ReceivePairs<9>::kLds, 0, split, 13);
     if (e == hipSuccess && split < b.count)
-        e = pass(a.bits <= 8 ? k_receive_b_long<10, 16> : k_receive_b_long<10, 30>, Receive<10>::kLds, split, b.count, 10 + Receive<10>::LOGT);
+        e = pass(narrow ? k_receive_b_long<10, 16> : k_receive_b_long<10, 30>, narrow ? k_receive_pairs_long<10, 16> : k_receive_pairs_long<10, 30>, 257u,
+                 ReceivePairs<10>::NT, Receive<10>::kLds, ReceivePairs<10>::kLds, split, b.count, 14);
     return e;
 }
 
