@@ -457,6 +457,174 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b(const typename Cx<HA
     fwd_b_workgroup<LOGN2, LOGE, CODEC, HALF>(blockIdx.x, gridDim.x, mid, logM, spec, sstride, tb, hist, total, per_wg, mid_scale);
 }
 
+// The same for the codec with a tile in half of the LDS (HalfTile), one to a workgroup: eight pairs of rows from pp0 on.
+//
+// The last stage leaves a lane rows that are each other's mirrors, so the split needs no trip through LDS; lanes 32 apart have each
+// other's mirrored rows, and swap, so that a lane stores pairs.
+//
+// Bound by the two trips to memory that nothing hides but the other workgroups of the compute unit, and by the stages.  Binary16, 62 M samples in
+// chunks of 2^20: 80 us for 50 of traffic (99 as fwd_b_workgroup).  Six waves a SIMD: eight spill twenty registers (125 us), and the
+// histogram in the tile's place, which they would need, costs two barriers and 11 us with six.  Runs of tiles that share a
+// histogram spill, too (115).
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b)  // lanes 32 .. 63 of a with lanes 0 .. 31 of b
+{
+    const auto v = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = v[0];
+    b = v[1];
+}
+__device__ __forceinline__ void swap_halves(float2& a, float2& b)
+{
+    uint32_t ax = __float_as_uint(a.x), ay = __float_as_uint(a.y), bx = __float_as_uint(b.x), by = __float_as_uint(b.y);
+    swap_halves(ax, bx);
+    swap_halves(ay, by);
+    a = make_float2(__uint_as_float(ax), __uint_as_float(ay));
+    b = make_float2(__uint_as_float(bx), __uint_as_float(by));
+}
+__device__ __forceinline__ float4 two_of(float2 a, float2 b) { return join(a, b); }
+__device__ __forceinline__ uint2 two_of(uint32_t a, uint32_t b) { return make_uint2(a, b); }
+template <int LOGN2, bool HALF, int TOP = LOGN2>
+__device__ __forceinline__ void fwd_b_pairs(const typename Cx<HALF>::One* __restrict__ mid, int logM, typename Cx<HALF>::One* __restrict__ spec,
+                                            const Tables& tb, uint32_t* __restrict__ hist, uint32_t pp0, bool first, uint32_t* lds, int lane,
+                                            float mid_scale)
+{
+    using G = HalfTile<LOGN2>;
+    using One = typename Cx<HALF>::One;
+    using Two = typename Cx<HALF>::Two;
+    constexpr int N2 = G::N2, NT = G::NT, DK = G::DK, P = G::PAIRS;
+    // 2^(TOP - LOGN2) tiles beside each other, each with LDS of its own, share the histogram behind them
+    constexpr int LANES = NT << (TOP - LOGN2);
+    const int tid = lane & (NT - 1), sub = __builtin_amdgcn_readfirstlane(lane / NT);
+    float* const d = reinterpret_cast<float*>(lds + sub * (int)(G::kLds / 4));
+    float2* const tw = reinterpret_cast<float2*>(d + N2 * G::SLOTS);
+    uint32_t* const h16 = lds + (G::kLds / 4 << (TOP - LOGN2));  // 16-bit counters: there are 2^14 + 1 keys at most
+    const int logN1 = logM - LOGN2, p = tid & (P - 1), kq = tid >> 3;
+    const uint32_t M = 1u << logM, N1 = 1u << logN1, pp = pp0 + (uint32_t)p;
+    Two raw[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) raw[q] = reinterpret_cast<const Two*>(mid)[((uint32_t)(kq + q * DK) << (logN1 - 1)) + pp];
+    load_stage_twiddles<LOGN2, NT>(tw, tb, tid);
+    for (int i = 4 * lane; i < kHistLdsWords; i += 4 * LANES) *reinterpret_cast<uint4*>(h16 + i) = make_uint4(0u, 0u, 0u, 0u);
+    // a wave has four rows of a pair in its lower lanes and their mirrors in the upper ones
+    const int hi = (tid >> 5) & 1, low_row = 4 * (tid >> 6) + ((tid >> 3) & 3);
+    const MirroredRows<LOGN2> rows(pp, hi ? DK - 1 - low_row : low_row);
+    // W_L^(k1 + N1*k2): k2 advances by N2/8 per step, i.e. by a sixteenth of a turn
+    float2 base[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        base[i] = twiddle(tb, ((rows.upper(i) ? mirror_row(pp, N1) : pp) + ((uint32_t)rows.at(i) << logN1)) << (21 - logM));
+    float2 v[16];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const float4 z = cx_load(raw[q]);
+        v[q] = lo2(z);
+        v[8 + q] = hi2(z);
+    }
+    bf8<false>(v);
+    bf8<false>(v + 8);
+    auto row_of = [&](int q) __attribute__((always_inline)) { return G::row_of(tid, q); };
+    auto mirrored = [&](int n) __attribute__((always_inline)) {
+        return G::template at_row<DK>(rows.at(n >> 3), n & 7, rows.upper(n >> 3) * P + p);
+    };
+    G::exchange(
+        d, v, [&](int n) __attribute__((always_inline)) { return G::first_output(kq, n & 7, n < 8 ? p : P + p); },
+        [&](int n) __attribute__((always_inline)) { return G::template input<G::RL2>(tid, n); });
+    G::template stage<false, 3, G::RL2>(v, tw, row_of);
+    G::exchange(d, v, [&](int n) __attribute__((always_inline)) { return G::second_output(tid, n); }, mirrored);
+    if constexpr (G::RL3 > 0) {
+        static_assert(G::RL3 == 0 || G::LAST == 3, "two butterflies of eight rows");
+        G::template stage<false, 3 + G::RL2, G::LAST>(v, tw, [&](int q) __attribute__((always_inline)) { return rows.at(q); });
+    }
+    const float unlift = HALF ? mid_scale : 1.f, half = 0.5f * unlift;
+    auto turned = [&](int i, int q) __attribute__((always_inline)) { return cmul(base[i], make_float2(kW32re[2 * q], kW32im[2 * q])); };
+    auto count = [&](One st) __attribute__((always_inline)) {  // what the selection will read back
+        const uint32_t b = fft_key_of(cx_load(st)) >> kKeyShift;
+        atomicAdd(&h16[b >> 1], 1u << ((b & 1u) * 16u));
+    };
+    if (first) {
+        auto either = [](bool which, float2 a, float2 b) __attribute__((always_inline)) { return make_float2(which ? a.x : b.x, which ? a.y : b.y); };
+        auto put = [&](int i, int q, float2 x) __attribute__((always_inline)) {
+            const One st = cx_store<HALF>(x);
+            spec[((uint32_t)(rows.at(i) + q * DK) << logN1) + 2u * pp + (uint32_t)rows.upper(i)] = st;
+            count(st);
+        };
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            __builtin_amdgcn_sched_barrier(0);
+            const float2 pa = either(rows.alone, v[(8 - q) & 7], v[15 - q]), pb = either(rows.alone, v[15 - q], v[7 - q]);
+            float2 x = split_fwd(v[q], pa, turned(0, q), half);
+            if (q == 0 && rows.alone) {  // bin 0 and the Nyquist bin come from Z[0] alone
+                x = make_float2((v[0].x + v[0].y) * unlift, 0.f);
+                const One last = cx_store<HALF>(make_float2((v[0].x - v[0].y) * unlift, 0.f));
+                spec[M] = last;
+                count(last);
+            }
+            put(0, q, x);
+            put(1, q, split_fwd(v[8 + q], pb, turned(1, q), half));
+        }
+    } else {
+        Two* const out = reinterpret_cast<Two*>(spec);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            __builtin_amdgcn_sched_barrier(0);
+            const int u = 7 - t;
+            One xt = cx_store<HALF>(split_fwd(v[t], v[15 - t], turned(0, t), half)), xu = cx_store<HALF>(split_fwd(v[u], v[15 - u], turned(0, u), half));
+            One yt = cx_store<HALF>(split_fwd(v[8 + t], v[u], turned(1, t), half)), yu = cx_store<HALF>(split_fwd(v[8 + u], v[t], turned(1, u), half));
+            count(xt);
+            count(xu);
+            count(yt);
+            count(yu);
+            swap_halves(xt, xu);
+            swap_halves(yt, yu);
+            const uint32_t q = (uint32_t)(hi ? u : t) * DK;
+            out[(((uint32_t)low_row + q) << (logN1 - 1)) + pp] = two_of(xt, yu);
+            out[(((uint32_t)(DK - 1 - low_row) + q) << (logN1 - 1)) + pp] = two_of(xu, yt);
+        }
+    }
+    __syncthreads();
+    // two counters at a time: neither carries into the other
+    for (int i = lane; i < kHistLdsWords; i += LANES) {
+        const uint32_t n = h16[i];
+        if (n) atomicAdd(reinterpret_cast<unsigned long long*>(hist) + i, (unsigned long long)(n >> 16) << 32 | (n & 0xFFFFu));
+    }
+}
+template <int LOGN2, bool HALF>  // (rows of 2^10: a workgroup of sixteen waves)
+__global__ __launch_bounds__(HalfTile<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(LOGN2 == 10 ? 8 : 6, LOGN2 == 10 ? 8 : 6))) void k_fwd_b_pairs(
+    const typename Cx<HALF>::One* __restrict__ mid, int logM, typename Cx<HALF>::One* __restrict__ spec, uint32_t sstride, Tables tb,
+    uint32_t* __restrict__ hist, uint32_t total, float mid_scale)
+{
+    extern __shared__ float2 smem[];
+    const int log_tiles = logM - LOGN2 - 4;
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const uint32_t c = t >> log_tiles, pp0 = (t & ((1u << log_tiles) - 1u)) * HalfTile<LOGN2>::PAIRS;
+    fwd_b_pairs<LOGN2, HALF>(mid + ((size_t)c << logM), logM, spec + c * (size_t)sstride, tb, hist + (size_t)c * kHistBins, pp0, pp0 == 0,
+                             reinterpret_cast<uint32_t*>(smem), threadIdx.x, mid_scale);
+}
+
+// Tensors of different lengths: those with rows of up to 2^9, a workgroup does one tile of rows of 2^9, two of 2^8 or four of 2^7.
+constexpr int kPairsTop = 9;
+constexpr size_t kPairsLds = HalfTile<kPairsTop>::kLds + kHistLdsWords * sizeof(uint32_t);
+__global__ __launch_bounds__(HalfTile<kPairsTop>::NT) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_fwd_b_pairs_long(
+    const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb, uint32_t* __restrict__ hist, uint32_t total, LongTable tab, LongStarts at)
+{
+    extern __shared__ float2 smem[];
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const LongShare share = long_share(at, t);
+    const LongTensor& x = tab.t[share.tensor];
+    auto run = [&](auto n2) __attribute__((always_inline)) {
+        constexpr int LOGN2 = decltype(n2)::value, LOGSUB = kPairsTop - LOGN2;
+        using G = HalfTile<LOGN2>;
+        const uint32_t sub = LOGSUB ? (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / G::NT) : 0u, pp0 = ((share.blk << LOGSUB) + sub) * G::PAIRS;
+        fwd_b_pairs<LOGN2, false, kPairsTop>(mid + long_mid(x), x.logM, spec + long_spec(x, share.tensor), tb, hist + (size_t)share.tensor * kHistBins, pp0,
+                                  share.blk == 0, reinterpret_cast<uint32_t*>(smem), threadIdx.x, 1.0f);
+    };
+    const int rows = x.logM / 2;
+    if (rows == 7) return run(std::integral_constant<int, 7>{});
+    if (rows == 8) return run(std::integral_constant<int, 8>{});
+    run(std::integral_constant<int, 9>{});
+}
+
 // Inverse pass B: undo the split, inverse N2-point FFTs over k2, times conj W_M^(n2 k1).
 // PAIR: the spectrum is read in the paired order (the codec's own buffer), otherwise in natural bin order.
 // HALF (PAIR only): spectrum and intermediate are binary16 pairs.
@@ -707,7 +875,7 @@ constexpr int log_columns(int logM) { return (logM + 1) / 2; }  // log2 N1
 constexpr int log_rows(int logM) { return logM / 2; }           // log2 N2
 constexpr int kLongMax = kMaxLogL - 1;                            // log2 M
 
-__device__ __forceinline__ uint32_t power_tiles(int logM, int loge) { return 1u << (logM - loge); }
+__host__ __device__ __forceinline__ uint32_t power_tiles(int logM, int loge) { return 1u << (logM - loge); }
 
 __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a_long(const float* __restrict__ in, float2* __restrict__ mid, Tables tb,
                                                    int aligned, uint32_t per_wg, uint32_t* __restrict__ zero_ptr,
@@ -908,6 +1076,23 @@ hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, si
     return hipGetLastError();
 }
 
+// Binary16 storage, rows of 2^8 and more: half the LDS per tile and a workgroup for each.  Whole calls in us, theta 0.3, 8 bits, fwd_b_tiled / this:
+//   2^17 10 M samples 112 / 108.6, 42 M 287 / 278;  2^18 118.8 / 115.3, 275 / 264;  2^19 129 / 126, 303 / 294;  2^20 134 / 131, 62 M 442.5 / 434.5 (this
+//   kernel 99 / 80);  2^21 25 M 227.5 / 227, 62 M 482.7 / 467.8;  2^22 33 M 302 / 297.6, 138 M 1119 / 1081;  2^16 45 M 306.7 / 311.8.
+// Binary32 bins keep their persistent workgroups, which have a tile's loads on their way while they work on another: 2^16 45 M 364 / 381, 2^20 42 M
+// 357 / 362.7, 2^22 67 M 661 / 674.
+template <int LOGN2>
+hipError_t fwd_b_half(const float2* mid, int logM, size_t C, float2* spec, uint32_t sstride, Tables t, uint32_t* hist, float mid_scale, hipStream_t s)
+{
+    constexpr size_t lds = HalfTile<LOGN2>::kLds + kHistLdsWords * sizeof(uint32_t);
+    const auto kern = k_fwd_b_pairs<LOGN2, true>;
+    const hipError_t e = set_lds(kern, lds);
+    if (e != hipSuccess) return e;
+    const size_t total = C << (logM - LOGN2 - 4);
+    FFTSP_LAUNCH("rfft_pass_b", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(HalfTile<LOGN2>::NT), lds, s, reinterpret_cast<const uint32_t*>(mid), logM,
+                 reinterpret_cast<uint32_t*>(spec), sstride, t, hist, (uint32_t)total, mid_scale);
+    return hipGetLastError();
+}
 // the tile size by the rule at the top of the file
 template <int LOGN2, bool CODEC, bool HALF>
 hipError_t fwd_b(const float2* mid, int logM, size_t C, float2* spec, uint32_t sstride, Tables t, uint32_t* hist,
@@ -1123,6 +1308,16 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     const uint32_t wide = first_wide(b, log_rows, kWideForward, kWideForwardBeside, false);
     return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
         constexpr int LOGE = decltype(size)::value;
+        // Sender and receiver in us, k_fwd_b_long / this: sets of 2^20 6 111 / 105, 12 163.5 / 152;  16 of 2^19 118.4 / 114.2;  two each of 2^16 .. 2^20 83.5 / 81.5;
+        // ResNet-50-like 150 tensors 586 / 575, 60 338.4 / 338.9, 200 819 / 820.
+        if (LOGE == 13 && log_rows(b.tab.t[end - 1].logM) <= kPairsTop) {
+            const hipError_t err = set_lds(k_fwd_b_pairs_long, kPairsLds);
+            if (err != hipSuccess) return err;
+            const uint32_t total = long_starts(b, first, end, &at, [](const LongTensor& x) { return power_tiles(x.logM, 13); });
+            FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_pairs_long, dim3((total + 7) / 8 * 8), dim3(HalfTile<kPairsTop>::NT), kPairsLds, s, mid, spec, t, hist, total,
+                         b.tab, at);
+            return hipGetLastError();
+        }
         const size_t lds = long_lds(LOGE) + kHistLdsWords * sizeof(uint32_t);
         const hipError_t err = set_lds(k_fwd_b_long<LOGE>, lds);
         if (err != hipSuccess) return err;
@@ -1217,9 +1412,9 @@ hipError_t launch_rfft_half(const float* in, size_t n, int logL, size_t C, void*
     *pair_log = logN1;
     switch (logN2) {
         case 7: return fwd_b<7, true, true>(md, logM, C, sp, sstride, t, hist, 1.0f / lift, s);
-        case 8: return fwd_b<8, true, true>(md, logM, C, sp, sstride, t, hist, 1.0f / lift, s);
-        case 9: return fwd_b<9, true, true>(md, logM, C, sp, sstride, t, hist, 1.0f / lift, s);
-        case 10: return fwd_b<10, true, true>(md, logM, C, sp, sstride, t, hist, 1.0f / lift, s);
+        case 8: return fwd_b_half<8>(md, logM, C, sp, sstride, t, hist, 1.0f / lift, s);
+        case 9: return fwd_b_half<9>(md, logM, C, sp, sstride, t, hist, 1.0f / lift, s);
+        case 10: return fwd_b_half<10>(md, logM, C, sp, sstride, t, hist, 1.0f / lift, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -229,6 +229,103 @@ __device__ __forceinline__ void run_fft_put(float2* d, const float2* tw, int tid
     }
 }
 
+// Sixteen transforms of N2 = 2^LOGN2 points, sixteen points a lane, in half of the LDS they would take as complex values: between
+// the stages real and imaginary parts go through it one after the other.  The slots are eight pairs (rows k1 and their mirrors).
+template <int LOGN2>
+struct HalfTile {
+    static constexpr int N2 = 1 << LOGN2, SLOTS = 16, PAIRS = 8, NT = N2, DK = N2 / 8;
+    static constexpr size_t kLds = (size_t)N2 * (SLOTS * sizeof(uint32_t) + sizeof(float2));  // and the stage twiddles
+    static constexpr int RL2 = stage_radix_log(LOGN2 - 3), RL3 = LOGN2 - 3 - RL2, LAST = RL3 ? RL3 : RL2;  // after a first stage of radix 8
+    static_assert(RL3 == 0 || stage_radix_log(RL3) == RL3, "three stages at most");
+
+    // Row i, place s of a component (places: the pairs' lower slots, then the upper ones) is word i * 16 + s with i >> 3 swizzled in, so that
+    // 64 lanes have two words of every bank whether they hold neighbouring rows or rows eight apart.
+    static __device__ __forceinline__ int swizzled(int word, int x) { return word ^ (x & 3) << 3; }
+    static __device__ __forceinline__ int place(int slot) { return (slot & 1) * PAIRS + (slot >> 1); }
+    // the first stage's output n of a butterfly of rows i + q * DK
+    static __device__ __forceinline__ int first_output(int i, int t, int place) { return i * 128 + (t >> 1) * 32 + swizzled((t & 1) * 16 + place, i); }
+    // Inputs n = q * RHO + t of a stage of radix RHO = 2^RL, and outputs of the second stage: slot tid % 16.
+    static __device__ __forceinline__ int row_of(int tid, int q) { return (tid >> 4) + q * (N2 / 16); }
+    template <int RL>
+    static __device__ __forceinline__ int input(int tid, int n)
+    {
+        constexpr int RHO = 1 << RL;
+        return at_row<N2 / RHO>(row_of(tid, n / RHO), n % RHO, place(tid & 15));
+    }
+    static __device__ __forceinline__ int second_output(int tid, int n)
+    {
+        const int i = row_of(tid, n >> RL2), t = n & ((1 << RL2) - 1);
+        return swizzled((((i >> 3) << (3 + RL2)) + (i & 7)) * 16 + place(tid & 15), t) + t * 128;
+    }
+    // row i + t * STEP
+    template <int STEP>
+    static __device__ __forceinline__ int at_row(int i, int t, int place)
+    {
+        return swizzled(i * 16 + place, STEP >= 32 ? i >> 3 : (i >> 3) + t * (STEP / 8)) + t * STEP * 16;
+    }
+    template <typename To, typename From>
+    static __device__ __forceinline__ void exchange(float* d, float2 (&v)[16], To&& to, From&& from)
+    {
+        float x[16];
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) d[to(n)] = v[n].x;
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) x[n] = d[from(n)];
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) d[to(n)] = v[n].y;
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) v[n] = make_float2(x[n], d[from(n)]);
+    }
+    // row(q): that of the q-th butterfly's first input
+    template <bool INV, int NS_LOG, int RL, typename Row>
+    static __device__ __forceinline__ void stage(float2 (&v)[16], const float2* tw, Row&& row)
+    {
+        constexpr int RHO = 1 << RL;
+#pragma unroll
+        for (int q = 0; q < 16 / RHO; ++q) {
+            const int k = row(q) & ((1 << NS_LOG) - 1);
+#pragma unroll
+            for (int t = 1; t < RHO; ++t) {
+                const float2 c = tw[(t * k) << (LOGN2 - NS_LOG - RL)];
+                v[q * RHO + t] = INV ? cmulc(v[q * RHO + t], c) : cmul(v[q * RHO + t], c);
+            }
+            butterfly<RL, INV>(v + q * RHO);
+        }
+    }
+};
+// Which rows of a tile of mirrored rows a lane has: at(0) + q * N2/8 of one slot and at(1) + q * N2/8 of another, q and 7 - q of which are
+// each other's mirrors: pair j's lower slot and its upper one, rows r and N2/8 - 1 - r.  Rows k1 = 0 and N1/2 (pair 0 of a chunk's first
+// tile) are their own mirrors: of those a lane has both from the same slot, and the lane `alone` row 0's points 0 and N2/16, each with itself.
+template <int LOGN2>
+struct MirroredRows {
+    static constexpr int DK = (1 << LOGN2) / 8;
+    int at0, at1, upper0, upper1;
+    bool alone;
+    __device__ __forceinline__ MirroredRows(uint32_t pp, int r)
+    {
+        const bool self = pp == 0, lower = r >= DK / 2;
+        alone = self && r == DK / 2;
+        at0 = self && lower ? r - DK / 2 : r;
+        at1 = self && lower ? (alone ? DK / 2 : DK + DK / 2 - r) : DK - 1 - r;
+        upper0 = self && !lower ? 1 : 0;
+        upper1 = self && lower ? 0 : 1;
+    }
+    __device__ __forceinline__ int at(int i) const { return i ? at1 : at0; }
+    __device__ __forceinline__ int upper(int i) const { return i ? upper1 : upper0; }
+};
+
+// every XCD has a stretch of the launch's workgroups of its own; at or above `total`: none
+__device__ __forceinline__ uint32_t in_stretches(uint32_t total)
+{
+    const uint32_t xcd = blockIdx.x & 7u, lo = (uint32_t)((uint64_t)total * xcd >> 3), hi = (uint32_t)((uint64_t)total * (xcd + 1u) >> 3);
+    const uint32_t t = lo + (blockIdx.x >> 3);
+    return t < hi ? t : total;
+}
+
 // LDS stages run_fft takes for `rem` remaining levels
 constexpr int lds_stages(int rem)
 {

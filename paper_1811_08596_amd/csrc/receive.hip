@@ -251,18 +251,13 @@ __device__ __forceinline__ void receive_tile(const uint8_t* __restrict__ record,
 //
 // Eight waves a SIMD (64 registers, none spilled): with six, 62 M samples in chunks of 2^20 104 -> 110 us, binary16 82 -> 86, 40 M in chunks
 // of 2^16 58 -> 60.  Outer twiddles fetched before the stages: 104 -> 106, 82 -> 84.
-template <int LOGN2>
-struct ReceivePairs {
-    static constexpr int N2 = 1 << LOGN2, SLOTS = 16, BINS = 8, NT = N2;
-    static constexpr size_t kLds = (size_t)N2 * (SLOTS * sizeof(uint32_t) + sizeof(float2));
-};
 template <int LOGN2, bool HALF, int WIDEST>
 __device__ __forceinline__ void receive_pairs(const uint8_t* __restrict__ record, uint32_t W, uint32_t S, int code_bits, int m,
                                               const uint2* __restrict__ entries, int logM, typename Cx<HALF>::One* __restrict__ mid, Tables tb,
                                               uint32_t pp0, bool first, uint32_t* lds, int tid, float mid_scale)
 {
-    using G = ReceivePairs<LOGN2>;
-    constexpr int N2 = G::N2, NT = G::NT, DK = N2 / 8, BINS = G::BINS;
+    using G = HalfTile<LOGN2>;
+    constexpr int N2 = G::N2, NT = G::NT, DK = G::DK, BINS = G::PAIRS;
     float* const d = reinterpret_cast<float*>(lds);
     float2* const tw = reinterpret_cast<float2*>(lds + N2 * G::SLOTS);
     const int logN1 = logM - LOGN2;
@@ -291,18 +286,13 @@ __device__ __forceinline__ void receive_pairs(const uint8_t* __restrict__ record
         o[i].mask = __builtin_amdgcn_alignbit(entry[i][2], entry[i][0], at) & (i && pp0 == 0 ? all >> 1 : all);
         o[i].fetch(words, final, (entry[i][1] + (uint32_t)__popc(entry[i][0] & ((1u << at) - 1u))) * twoN);
     }
-    // What the lane has of the first stage: rows at[0] + q * DK of one slot and at[1] + q * DK of another, whose mirrors they are (q and 7 - q):
-    // a pair's lower slot and its upper one.  Rows 0 and N1/2 are their own mirrors: of those the lane has both from the same slot, and the
-    // last lane, row 0's points 0 and DK / 2, each with itself.
-    const int j = tid & (BINS - 1), r = tid >> 3;
-    const bool self = pp0 == 0 && j == 0, lower = r >= DK / 2, alone = self && r == DK / 2;
-    const int at[2] = {self && lower ? r - DK / 2 : r, self && lower ? (alone ? DK / 2 : DK + DK / 2 - r) : DK - 1 - r};
-    const int upper[2] = {self && !lower ? 1 : 0, self && lower ? 0 : 1};
+    const int j = tid & (BINS - 1);
+    const MirroredRows<LOGN2> rows(pp0 + (uint32_t)j, tid >> 3);
     float2 base[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const uint32_t pp = pp0 + (uint32_t)j, k = upper[i] ? mirror_row(pp, N1) : pp;
-        base[i] = twiddle(tb, (k + ((uint32_t)at[i] << logN1)) << (21 - logM));
+        const uint32_t pp = pp0 + (uint32_t)j, k = rows.upper(i) ? mirror_row(pp, N1) : pp;
+        base[i] = twiddle(tb, (k + ((uint32_t)rows.at(i) << logN1)) << (21 - logM));
     }
     // codes[side][run][pair]
 #pragma unroll
@@ -335,7 +325,8 @@ __device__ __forceinline__ void receive_pairs(const uint8_t* __restrict__ record
     __syncthreads();
     float2 v[16];
     {
-        const uint32_t *a = lds + (upper[0] * N2 + at[0]) * BINS + j, *b = lds + (upper[1] * N2 + at[1]) * BINS + j;
+        const uint32_t *a = lds + (rows.upper(0) * N2 + rows.at(0)) * BINS + j, *b = lds + (rows.upper(1) * N2 + rows.at(1)) * BINS + j;
+        const bool alone = rows.alone;
         auto turned = [&](int i, int q) __attribute__((always_inline)) { return cmul(base[i], make_float2(kW32re[2 * q], kW32im[2 * q])); };
         if (first) {
 #pragma unroll
@@ -360,49 +351,11 @@ __device__ __forceinline__ void receive_pairs(const uint8_t* __restrict__ record
     }
     bf8<true>(v);
     bf8<true>(v + 8);
-    // Row i, slot s of a component (slots: eight lower rows, then their mirrors), so that 64 lanes of either kind have two words of every bank.
-    auto swizzled = [](int word, int x) __attribute__((always_inline)) { return word ^ (x & 3) << 3; };
-    auto exchange = [&](auto&& to, auto&& from) __attribute__((always_inline)) {
-        float x[16];
-        __syncthreads();
-#pragma unroll
-        for (int n = 0; n < 16; ++n) d[to(n)] = v[n].x;
-        __syncthreads();
-#pragma unroll
-        for (int n = 0; n < 16; ++n) x[n] = d[from(n)];
-        __syncthreads();
-#pragma unroll
-        for (int n = 0; n < 16; ++n) d[to(n)] = v[n].y;
-        __syncthreads();
-#pragma unroll
-        for (int n = 0; n < 16; ++n) v[n] = make_float2(x[n], d[from(n)]);
-    };
-    const int slot = tid & 15, s = (slot & 1) * BINS + (slot >> 1);
-    auto row_of = [&](int q) __attribute__((always_inline)) { return (tid >> 4) + q * (N2 / 16); };
-    // inputs of a stage of radix 2^RL, and the stage
-    auto input = [&](auto rl, int n) __attribute__((always_inline)) {
-        constexpr int RL = decltype(rl)::value, RHO = 1 << RL, STEP = N2 / RHO;
-        const int i = row_of(n / RHO), t = n % RHO;
-        return swizzled(i * 16 + s, STEP >= 32 ? i >> 3 : (i >> 3) + t * (STEP / 8)) + t * STEP * 16;
-    };
-    auto stage = [&](auto rl, auto ns) __attribute__((always_inline)) {
-        constexpr int RL = decltype(rl)::value, RHO = 1 << RL, NS_LOG = decltype(ns)::value;
-#pragma unroll
-        for (int q = 0; q < 16 / RHO; ++q) {
-            const int k = row_of(q) & ((1 << NS_LOG) - 1);
-#pragma unroll
-            for (int t = 1; t < RHO; ++t) v[q * RHO + t] = cmulc(v[q * RHO + t], tw[(t * k) << (LOGN2 - NS_LOG - RL)]);
-            butterfly<RL, true>(v + q * RHO);
-        }
-    };
-    constexpr int RL2 = stage_radix_log(LOGN2 - 3), RL3 = LOGN2 - 3 - RL2, LAST = RL3 ? RL3 : RL2;
-    static_assert(RL3 == 0 || stage_radix_log(RL3) == RL3, "three stages at most");
-    using Second = std::integral_constant<int, RL2>;
-    using Third = std::integral_constant<int, LAST>;
+    const int slot = tid & 15;
     // What the lane stores: two chains of eight rows of its slot, an eighth of the rows apart, with their twiddles.
-    constexpr int RHO = 1 << LAST, CHAINS = RHO / 8;
+    constexpr int RHO = 1 << G::LAST, CHAINS = RHO / 8;
     const uint32_t column = 2u * pp0 + (uint32_t)slot, k = slot & 1 ? mirror_row(pp0 + (uint32_t)(slot >> 1), N1) : pp0 + (uint32_t)(slot >> 1);
-    auto first_row = [&](int g) __attribute__((always_inline)) { return row_of(g / CHAINS) + g % CHAINS * (N2 / RHO); };
+    auto first_row = [&](int g) __attribute__((always_inline)) { return G::row_of(tid, g / CHAINS) + g % CHAINS * (N2 / RHO); };
     const int sh = 22 - logM;
     float2 cur[2], ratio;
     auto outer_twiddles = [&]() __attribute__((always_inline)) {
@@ -413,21 +366,16 @@ __device__ __forceinline__ void receive_pairs(const uint8_t* __restrict__ record
         }
         ratio = twiddle(tb, ((uint32_t)DK * k) << sh);
     };
-    exchange(
-        [&](int n) __attribute__((always_inline)) {
-            const int i = at[n >> 3], t = n & 7;
-            return i * 128 + (t >> 1) * 32 + swizzled((t & 1) * 16 + upper[n >> 3] * BINS + j, i);
-        },
-        [&](int n) __attribute__((always_inline)) { return input(Second{}, n); });
-    stage(Second{}, std::integral_constant<int, 3>{});
-    if constexpr (RL3 > 0) {
-        exchange(
-            [&](int n) __attribute__((always_inline)) {
-                const int i = row_of(n >> RL2), t = n & ((1 << RL2) - 1);
-                return swizzled((((i >> 3) << (3 + RL2)) + (i & 7)) * 16 + s, t) + t * 128;
-            },
-            [&](int n) __attribute__((always_inline)) { return input(Third{}, n); });
-        stage(Third{}, std::integral_constant<int, 3 + RL2>{});
+    auto row_of = [&](int q) __attribute__((always_inline)) { return G::row_of(tid, q); };
+    G::exchange(
+        d, v, [&](int n) __attribute__((always_inline)) { return G::first_output(rows.at(n >> 3), n & 7, rows.upper(n >> 3) * BINS + j); },
+        [&](int n) __attribute__((always_inline)) { return G::template input<G::RL2>(tid, n); });
+    G::template stage<true, 3, G::RL2>(v, tw, row_of);
+    if constexpr (G::RL3 > 0) {
+        G::exchange(
+            d, v, [&](int n) __attribute__((always_inline)) { return G::second_output(tid, n); },
+            [&](int n) __attribute__((always_inline)) { return G::template input<G::LAST>(tid, n); });
+        G::template stage<true, 3 + G::RL2, G::LAST>(v, tw, row_of);
     }
     outer_twiddles();
     // one base for all lanes and 32-bit offsets: a chunk is 16 MB at most
@@ -444,13 +392,6 @@ __device__ __forceinline__ void receive_pairs(const uint8_t* __restrict__ record
     }
 }
 
-// every XCD has a stretch of the launch's workgroups of its own; at or above `total`: none
-__device__ __forceinline__ uint32_t in_stretches(uint32_t total)
-{
-    const uint32_t xcd = blockIdx.x & 7u, lo = (uint32_t)((uint64_t)total * xcd >> 3), hi = (uint32_t)((uint64_t)total * (xcd + 1u) >> 3);
-    const uint32_t t = lo + (blockIdx.x >> 3);
-    return t < hi ? t : total;
-}
 template <int LOGN2, bool HALF, int WIDEST>
 __global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(Receive<LOGN2>::WAVES, Receive<LOGN2>::WAVES))) void k_receive_b(
     const uint8_t* __restrict__ records, uint32_t W, uint32_t S, int bits, int m, const uint2* __restrict__ table, int logM,
@@ -466,7 +407,7 @@ __global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per
                                       pp0, pp0 == 0, smem, threadIdx.x, mid_scale);
 }
 template <int LOGN2, bool HALF, int WIDEST>
-__global__ __launch_bounds__(ReceivePairs<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_receive_pairs(
+__global__ __launch_bounds__(HalfTile<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_receive_pairs(
     const uint8_t* __restrict__ records, uint32_t W, uint32_t S, int bits, int m, const uint2* __restrict__ table, int logM,
     typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total, float mid_scale)
 {
@@ -509,7 +450,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(Receive<TO
 }
 
 template <int TOP, int WIDEST>
-__global__ __launch_bounds__(ReceivePairs<TOP>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_receive_pairs_long(
+__global__ __launch_bounds__(HalfTile<TOP>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_receive_pairs_long(
     const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total,
     LongTable tab, LongStarts at)
 {
@@ -520,7 +461,7 @@ __global__ __launch_bounds__(ReceivePairs<TOP>::NT) __attribute__((amdgpu_waves_
     const LongTensor& x = tab.t[share.tensor];
     auto run = [&](auto n2) __attribute__((always_inline)) {
         constexpr int LOGN2 = decltype(n2)::value, LOGSUB = LOGN2 < TOP ? TOP - LOGN2 : 0;
-        using G = ReceivePairs<LOGN2>;
+        using G = HalfTile<LOGN2>;
         const uint32_t sub = LOGSUB ? (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / G::NT) : 0u, pp0 = ((share.blk << LOGSUB) + sub) * 8u;
         receive_pairs<LOGN2, false, WIDEST>(records + x.roff, (1u << x.logM) / 32u + 1u, x.stride, bits, m, table + long_entries(x, share.tensor), x.logM,
                                             mid + long_mid(x), tb, pp0, share.blk == 0, reinterpret_cast<uint32_t*>(smem) + sub * (G::kLds / 4),
@@ -552,7 +493,7 @@ hipError_t receive_b(const uint8_t* records, const CodecArgs& a, int logM, const
                      a.bits, a.m, table, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, (uint32_t)total, HALF ? 1.0f / half_lift(logM) : 1.0f);
         return hipGetLastError();
     };
-    return total >= kPairsFrom ? launch(k_receive_pairs<LOGN2, HALF, WIDEST>, ReceivePairs<LOGN2>::NT, ReceivePairs<LOGN2>::kLds)
+    return total >= kPairsFrom ? launch(k_receive_pairs<LOGN2, HALF, WIDEST>, HalfTile<LOGN2>::NT, HalfTile<LOGN2>::kLds)
                                : launch(k_receive_b<LOGN2, HALF, WIDEST>, Receive<LOGN2>::NT, Receive<LOGN2>::kLds);
 }
 template <int LOGN2>
@@ -654,10 +595,10 @@ hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* 
     const bool narrow = a.bits <= 8;
     if (e == hipSuccess && split > 0)
         e = pass(narrow ? k_receive_b_long<9, 16> : k_receive_b_long<9, 30>, narrow ? k_receive_pairs_long<9, 16> : k_receive_pairs_long<9, 30>, 1025u,
-                 ReceivePairs<9>::NT, Receive<9>::kLds, ReceivePairs<9>::kLds, 0, split, 13);
+                 HalfTile<9>::NT, Receive<9>::kLds, HalfTile<9>::kLds, 0, split, 13);
     if (e == hipSuccess && split < b.count)
         e = pass(narrow ? k_receive_b_long<10, 16> : k_receive_b_long<10, 30>, narrow ? k_receive_pairs_long<10, 16> : k_receive_pairs_long<10, 30>, 257u,
-                 ReceivePairs<10>::NT, Receive<10>::kLds, ReceivePairs<10>::kLds, split, b.count, 14);
+                 HalfTile<10>::NT, Receive<10>::kLds, HalfTile<10>::kLds, split, b.count, 14);
     return e;
 }
 
