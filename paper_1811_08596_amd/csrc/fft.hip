@@ -37,16 +37,16 @@ namespace {
 //     4224 (138 M samples in chunks of 2^22) 913 / 810;
 //   inverse second pass, the same rows, receiver: 384 80 / 84, 640 115 / 122, 1024 171 / 169 and (chunks of 2^22) 186 / 190, 1280
 //     222 / 202, 4224 780 / 694; four senders' streams 1216 242 / 221;
-//   inverse first pass, columns of 2^10 (stores of 64 -> 128 bytes), receiver: 256 51.9 / 53.2, 640 99 / 101, 768 129 / 118, 1920
-//     (62 M samples in chunks of 2^20) 310 / 280, and the next call's forward first pass, which runs while those lines are
-//     written back, 134 / 118; columns of 2^11 (32 -> 64 bytes): 128 52.1 / 52.7, 256 68.4 / 67.5, 768 157 / 146, 4224 926 / 780.
+//   inverse first pass, columns of 2^10 (stores of 64 -> 128 bytes), receiver: 768 129 / 118, 1920 (62 M samples in chunks of 2^20)
+//     310 / 280, and the next call's forward first pass, which runs while those lines are written back, 134 / 118; columns of 2^11
+//     (32 -> 64 bytes): 128 52.1 / 52.7, 256 68.4 / 67.5, 768 157 / 146, 4224 926 / 780.  (Tiles in half of the LDS: below.)
 // With rows of 2^9, already a line wide, the second passes lose (101 / 106 and 109 / 127 us).  The forward first pass, which only
 // reads in narrow pieces, was slower that way (columns of 2^10: 119 / 124 us; of 2^11: 340 us against 327 with four
 // 2^13-point tiles of a line walked in step).  Binary16 storage: the same lines within 3 us.
 constexpr int kTileFA = 13;
 constexpr int kWideMin = 10;  // columns (inverse first pass) or rows (second passes) of at least 2^kWideMin
 constexpr size_t kWideForward = 128, kWideInverseB = 1152;  // large tiles from which a pass takes them
-constexpr size_t wide_inverse_a(int logn1) { return logn1 == 10 ? 768 : 256; }
+constexpr size_t kWideInverseA = 256;  // columns of 2^11
 inline size_t wide_tiles(size_t C, int logM) { return C << (logM - 14); }
 constexpr int tile_lanes(int loge) { return 1 << (loge - 4); }
 constexpr int kLanePairs = 8;  // pairs of adjacent points a lane holds
@@ -290,6 +290,184 @@ __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __re
     fwd_a_workgroup<LOGN1, false, HALF>(blockIdx.x, in, 0, n, logM, mid, tb, aligned, total, per_wg, glog, in_scale);
 }
 
+
+// Forward pass A with a tile in half of the LDS: 16 points a lane stay in registers, and between the stages real and imaginary parts go
+// through LDS one after the other.  Two tiles of 2^14 points or four of 2^13 are on a compute unit, all 32 waves of it, so columns of 2^11
+// are read 64 bytes wide instead of 32.  What it costs is LDS instructions of four bytes instead of eight, and the persistent kernel's loads ahead.
+// The same radices, twiddles and order of operations as fwd_a_run and fwd_a_tile: the bits are the same.
+// Calls in us, persistent / this, 2^22 by number of tiles of 2^14: binary32 512 120.7 / 119.7, 1024 208 / 222, 1280 242.6 / 241.8, 1536 281 / 284,
+//   1920 354.8 / 348.1, 3072 582 / 578, 4224 (138 M samples) 817.7 / 759.5, kernel 330 / 264;  binary16 1024 176 / 187, 1280 209 / 205, 1536 246 / 242.5,
+//   1920 302 / 289.  Columns of 2^10, tiles of 2^13, binary16: 512 93.7 / 97.4, 640 120.5 / 121.1, 1024 146.4 / 144.7, 1280 173.5 / 172.7, 1920 261.1 / 253.2 and
+//   (2^21) 272.7 / 265.9; binary32 1920 313.7 / 317.1, and with tiles of 2^14 326.  Shorter columns: equal at best.
+template <bool HALF>
+constexpr size_t kSplitForward = HALF ? 1280 : 1792;  // tiles of 2^14, columns of 2^11
+template <int LOGN1, int LOGE>
+struct SplitTile {
+    static constexpr int N1 = 1 << LOGN1, LOGT = LOGE - LOGN1, T = 1 << LOGT, NT = tile_lanes(LOGE);
+    static constexpr int HP = N1 / 2, LOGHP = LOGN1 - 1;
+    static constexpr size_t kLds = ((size_t)sizeof(float) << LOGE) + N1 * sizeof(float2);  // a component of the tile, and the stage twiddles
+    static constexpr int RL2 = stage_radix_log(LOGN1 - 3), RL3 = LOGN1 - 3 - RL2;
+    static_assert(RL3 > 0 && stage_radix_log(RL3) == RL3, "three stages");
+    static_assert(NT >= HP && T >= 8 && T <= 32, "a lane stores one pair of rows, of eight columns");
+    // columns of a lane's stores: first(lane) + j * STEP, with the twiddles anchored every ANCHOR of them; as fwd_a_tile has them
+    static constexpr int OLD = tile_lanes(kTileFA), STEP = HP >= OLD ? 1 : OLD / HP, ANCHOR = HP > OLD ? 8 * OLD / HP : 8;
+    static __device__ __forceinline__ int first_column(int tid) { return (tid >> LOGHP) * (STEP > 1 ? 1 : 8); }
+    // Row i, column b between two stages.  64 lanes have all columns of 64 / T neighbouring rows, or half as many lanes with column pairs have
+    // them of rows eight apart: every bank once.
+    static __device__ __forceinline__ int staged(int i, int b) { return ((i ^ ((i >> 3) & (64 / T - 1))) << LOGT) + b; }
+    // and on the way to the stores: 64 lanes have one column of 64 neighbouring rows
+    static __device__ __forceinline__ int stored(int i, int b) { return (i << LOGT) + (b ^ ((i >> (6 - LOGT)) & (T - 1))); }
+    static __device__ __forceinline__ int butterfly_of(int tid, int q) { return (tid >> LOGT) + q * (NT >> LOGT); }
+    template <int RL>
+    static __device__ __forceinline__ int input(int tid, int n)
+    {
+        return staged(butterfly_of(tid, n >> RL) + (n & ((1 << RL) - 1)) * (N1 >> RL), tid & (T - 1));
+    }
+    template <int NS_LOG, int RL>
+    static __device__ __forceinline__ int output_row(int tid, int n)
+    {
+        const int j = butterfly_of(tid, n >> RL);
+        return ((j >> NS_LOG) << (NS_LOG + RL)) + (j & ((1 << NS_LOG) - 1)) + ((n & ((1 << RL) - 1)) << NS_LOG);
+    }
+    template <int NS_LOG, int RL>
+    static __device__ __forceinline__ void stage(float2 (&v)[16], const float2* tw, int tid)
+    {
+        constexpr int RHO = 1 << RL;
+#pragma unroll
+        for (int q = 0; q < 16 / RHO; ++q) {
+            const int k = butterfly_of(tid, q) & ((1 << NS_LOG) - 1);
+#pragma unroll
+            for (int t = 1; t < RHO; ++t) v[q * RHO + t] = cmul(v[q * RHO + t], tw[(t * k) << (LOGN1 - NS_LOG - RL)]);
+            butterfly<RL, false>(v + q * RHO);
+        }
+    }
+    // put(component of point n) then, behind a barrier, from(n)
+    template <typename Put, typename From>
+    static __device__ __forceinline__ void exchange(const float* d, float2 (&v)[16], int tid, Put&& put, From&& from)
+    {
+        float x[16];
+        put([&](int n) __attribute__((always_inline)) { return v[n].x; }, tid);
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) x[n] = d[from(n, tid)];
+        __syncthreads();
+        const int again = opaque_lane(tid);  // addresses are computed again for the second component: kept, they spill
+        put([&](int n) __attribute__((always_inline)) { return v[n].y; }, again);
+        __syncthreads();
+#pragma unroll
+        for (int n = 0; n < 16; ++n) v[n] = make_float2(x[n], d[from(n, again)]);
+    }
+};
+
+// One tile, columns col0 .. of a chunk whose samples are `sp` and whose intermediate is `mid`; d: 2^LOGE words; tw: the stage twiddles, which
+// other lanes may still be writing.  quads: every 16-byte piece is inside the input or outside it.
+template <int LOGN1, int LOGE, bool HALF>
+__device__ __forceinline__ void fwd_a_split(const float* __restrict__ in, const Span& sp, bool quads, int logM, typename Cx<HALF>::One* __restrict__ mid,
+                                            const Tables& tb, uint32_t col0, float* d, const float2* tw, int tid, float in_scale)
+{
+    using G = SplitTile<LOGN1, LOGE>;
+    constexpr int N1 = G::N1, HP = G::HP, T = G::T;
+    const uint32_t M = 1u << logM, N2 = M >> LOGN1;
+    const int bp = tid & (T / 2 - 1), j0 = tid >> (G::LOGT - 1);
+    float2 v[16];
+    if (quads) {
+        const size_t left = sp.limit > sp.first ? (sp.limit - sp.first) >> 2 : 0;
+        const uint32_t end = left < (size_t)(M >> 1) ? (uint32_t)left : M >> 1;
+        const float4* src = end ? reinterpret_cast<const float4*>(in + sp.first) : reinterpret_cast<const float4*>(tb.hi);
+        float4 r[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t i = (uint32_t)(j0 + q * (N1 / 8)) * (N2 >> 1) + (col0 >> 1) + (uint32_t)bp;
+            r[q] = src[i < end ? i : 0u];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const bool there = (uint32_t)(j0 + q * (N1 / 8)) * (N2 >> 1) + (col0 >> 1) + (uint32_t)bp < end;
+            v[q] = there ? lo2(r[q]) : make_float2(0.f, 0.f);
+            v[8 + q] = there ? hi2(r[q]) : make_float2(0.f, 0.f);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const size_t gi = sp.first + 2 * ((size_t)(j0 + q * (N1 / 8)) * N2 + col0 + 2 * bp);
+            v[q] = load_pair(in, gi, sp.limit, sp.pairs);
+            v[8 + q] = load_pair(in, gi + 2, sp.limit, sp.pairs);
+        }
+    }
+    bf8<false>(v);
+    bf8<false>(v + 8);
+    G::exchange(
+        d, v, tid,
+        [&](auto part, int tid) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) *reinterpret_cast<float2*>(d + G::staged(8 * (tid >> (G::LOGT - 1)) + t, 2 * (tid & (T / 2 - 1)))) = make_float2(part(t), part(8 + t));
+        },
+        [&](int n, int tid) __attribute__((always_inline)) { return G::template input<G::RL2>(tid, n); });
+    G::template stage<3, G::RL2>(v, tw, tid);
+    __syncthreads();
+    G::exchange(
+        d, v, tid,
+        [&](auto part, int tid) __attribute__((always_inline)) {
+#pragma unroll
+            for (int n = 0; n < 16; ++n) d[G::staged(G::template output_row<3, G::RL2>(tid, n), tid & (T - 1))] = part(n);
+        },
+        [&](int n, int tid) __attribute__((always_inline)) { return G::template input<G::RL3>(tid, n); });
+    G::template stage<3 + G::RL2, G::RL3>(v, tw, tid);
+    __syncthreads();
+    const uint32_t kp = (uint32_t)tid & (HP - 1);  // pair of paired positions (2kp, 2kp+1)
+    const int ka = (int)kp, kb = (int)mirror_row(kp, N1), c0 = G::first_column(tid);
+    G::exchange(
+        d, v, tid,
+        [&](auto part, int tid) __attribute__((always_inline)) {
+#pragma unroll
+            for (int n = 0; n < 16; ++n) d[G::stored(G::template output_row<3 + G::RL2, G::RL3>(tid, n), tid & (T - 1))] = part(n);
+        },
+        [&](int n, int tid) __attribute__((always_inline)) {
+            const uint32_t kp = (uint32_t)tid & (HP - 1);
+            return G::stored(n & 1 ? (int)mirror_row(kp, N1) : (int)kp, G::first_column(tid) + (n >> 1) * G::STEP);
+        });
+    const int sh = 22 - logM;
+    const float2 ratio_a = twiddle(tb, (uint32_t)(G::STEP * ka) << sh), ratio_b = twiddle(tb, (uint32_t)(G::STEP * kb) << sh);
+    typename Cx<HALF>::Two* out = reinterpret_cast<typename Cx<HALF>::Two*>(mid);
+    float2 cur_a, cur_b;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const uint32_t n2 = col0 + (uint32_t)(c0 + j * G::STEP);
+        if (j % G::ANCHOR == 0) {
+            cur_a = twiddle(tb, (n2 * (uint32_t)ka) << sh);
+            cur_b = twiddle(tb, (n2 * (uint32_t)kb) << sh);
+            if constexpr (HALF) {  // the variant's power-of-two factors ride on the twiddles (exact)
+                cur_a = make_float2(cur_a.x * in_scale, cur_a.y * in_scale);
+                cur_b = make_float2(cur_b.x * in_scale, cur_b.y * in_scale);
+            }
+        }
+        out[n2 * (uint32_t)HP + kp] = cx_store<HALF>(join(cmul(v[2 * j], cur_a), cmul(v[2 * j + 1], cur_b)));
+        cur_a = cmul(cur_a, ratio_a);
+        cur_b = cmul(cur_b, ratio_b);
+    }
+}
+
+template <int LOGN1, int LOGE, bool HALF>
+__global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fwd_a_split(
+    const float* __restrict__ in, size_t n, int logM, typename Cx<HALF>::One* __restrict__ mid, Tables tb, int aligned, uint32_t total,
+    uint32_t* __restrict__ zero_ptr, uint32_t zero_words, float in_scale)
+{
+    using G = SplitTile<LOGN1, LOGE>;
+    extern __shared__ float2 smem[];
+    float* const d = reinterpret_cast<float*>(smem);
+    float2* const tw = smem + (1 << LOGE) / 2;
+    const int tid = threadIdx.x;
+    // clears the status words and key histograms the next kernels of the sender accumulate into
+    for (uint32_t i = blockIdx.x * G::NT + tid; i < zero_words; i += gridDim.x * G::NT) zero_ptr[i] = 0u;
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const int log_tiles = logM - LOGE;
+    const uint32_t c = t >> log_tiles;
+    const Span sp = chunk_span(0, n, c, (size_t)2 << logM, aligned & 1);
+    const bool quads = (aligned & 2) && (sp.first + ((size_t)2 << logM) <= n || (n & 3u) == 0);
+    load_stage_twiddles<LOGN1, G::NT>(tw, tb, tid);
+    fwd_a_split<LOGN1, LOGE, HALF>(in, sp, quads, logM, mid + ((size_t)c << logM), tb, (t & ((1u << log_tiles) - 1u)) << G::LOGT, d, tw, tid, in_scale);
+}
 
 // Forward pass B: N2-point FFTs along n2 for a tile of rows and their mirrors, then the real-FFT split.
 // A lane owns one pair of slots (row ka and its mirror kb), i.e. 16 bytes of every run it touches.
@@ -771,7 +949,7 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b(const typename Cx<HA
 // chunk by chunk.  `aligned`: bit 0 = `out` is 8-byte aligned, bit 1 = 16-byte aligned.
 template <int LOGN1, int LOGE, bool HALF>
 __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<HALF>::One* __restrict__ mid, int logM,
-                                                float* __restrict__ out, size_t first, size_t n, const Tables& tb, int aligned,
+                                                float* __restrict__ out, size_t n, const Tables& tb, int aligned,
                                                 uint32_t total, uint32_t per_wg, int glog, float gain)
 {
     using Two = typename Cx<HALF>::Two;
@@ -822,7 +1000,7 @@ __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<
         run_fft_between<LOGN1, LOGT, NT, true, 0>(d, tw, tid, [&](int k) {
             if (k + 1 < PARTS) load_tile(more ? t + tstep : t, tid, more, k + 1);
         });
-        const Span sp = chunk_span(first, n, t / tiles, 2 * (size_t)M, aligned & 1);
+        const Span sp = chunk_span(0, n, t / tiles, 2 * (size_t)M, aligned & 1);
         const size_t cbase = sp.first;
         const uint32_t col0 = tile_in_chunk(t, tiles) << LOGT;
         if ((aligned & 2) && (cbase & 3u) == 0 && (cbase + 2 * (size_t)M <= sp.limit || (sp.limit & 3u) == 0)) {
@@ -861,7 +1039,173 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HA
                                                uint32_t per_wg, int glog, float gain, const uint32_t* __restrict__ only_if)
 {
     if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
-    inv_a_workgroup<LOGN1, LOGE, HALF>(blockIdx.x, mid, logM, out, 0, n, tb, aligned, total, per_wg, glog, gain);
+    inv_a_workgroup<LOGN1, LOGE, HALF>(blockIdx.x, mid, logM, out, n, tb, aligned, total, per_wg, glog, gain);
+}
+
+// Inverse pass A with a tile in half of the LDS, as fwd_a_split: the same radices, twiddles and order of operations as inv_a_workgroup.  The last
+// stage's butterflies are dealt out so that a lane has both of two adjacent columns and stores 16 bytes from its registers.
+// Four tiles of 2^13 points to a compute unit where the persistent kernel has two, and no rounds of runs of equal length that end together.
+// Receivers in us, persistent / this: columns of 2^9, chunks of 2^19, 8.4 M samples 43.5 / 39.5, 25.6 M 81.5 / 75.1, 62 M 208 / 200, binary16 169.7 / 155.8; 2^18
+//   20 M 63.0 / 59.1.  Columns of 2^10 by number of tiles of 2^14, persistent / this with 2^14 / with 2^13: 256 43.7 / 40.6 / 40.1, 512 60.6 / 59.0 / 57.0, 640
+//   80.5 / 81.0 / 74.6, 768 79.2 / 79.5 / 78.1, 1024 108.2 / 107.2 / 110.5, 1280 132.6 / 132.6 / 151, 1920 208 / 211 / 246; binary16 512 60.6 / 57.2 / 57.0, 1024
+//   94.0 / 91.2 / 93.2, 1920 167.1 / 164.0 / 181 and (2^21) 184.0 / 179.6 / 201.7.  Of 2^11: 256 51.1 / 48.6, 384 64.2 / 60.7, 512 70.5 / 69.1, 768 92.9 / 94.7, 1024
+//   119.3 / 125.7, 1280 161.7 / 159.2, 1536 196 / 203.8, 1920 266.9 / 268.0, 2560 358.3 / 358.7, 3072 418.8 / 411.6, 4224 584.9 / 564.5; binary16 256 46.0 / 46.5, 512
+//   70.5 / 65.3, 768 90.5 / 88.1, 1024 111.1 / 114.3, 1920 205.5 / 208.  Columns of 2^8, two stages: 10 M 44.0 / 44.0, 45 M 134 / 150.
+constexpr size_t kSplitInverse10 = 1024;  // fewer tiles: of 2^13; from here on binary32 keeps the persistent kernel, binary16 takes 2^14
+template <bool HALF>
+constexpr size_t kSplitInverse11 = HALF ? 896 : 640;
+constexpr size_t kSplitInverse11Many = 2816;
+template <int LOGN1, int LOGE>
+struct SplitInverse {
+    static constexpr int N1 = 1 << LOGN1, LOGT = LOGE - LOGN1, T = 1 << LOGT, NT = tile_lanes(LOGE), HP = N1 / 2, LOGHP = LOGN1 - 1;
+    static constexpr size_t kLds = ((size_t)sizeof(float) << LOGE) + N1 * sizeof(float2);
+    static constexpr int RL1 = stage_radix_log(LOGN1), RL2 = stage_radix_log(LOGN1 - RL1), RL3 = LOGN1 - RL1 - RL2;
+    static_assert(T >= 8 && T <= 32 && RL1 >= 3 && (RL3 == 3 || (RL3 == 0 && RL2 == 4)), "three stages, the last of radix 8, or two (columns of 2^8, in tensors' launches)");
+    // Rows and columns as loaded: 64 lanes have one column of 64 neighbouring rows, and then all columns of 64 / T of them
+    static __device__ __forceinline__ int loaded(int i, int b) { return (i << LOGT) + (b ^ ((i >> (6 - LOGT)) & (T - 1))); }
+    // between the first two stages: rows a radix apart, then neighbouring ones
+    static __device__ __forceinline__ int staged(int i, int b) { return ((i ^ ((i >> RL1) & (64 / T - 1))) << LOGT) + b; }
+    static __device__ __forceinline__ int butterfly_of(int tid, int q) { return (tid >> LOGT) + q * (NT >> LOGT); }
+    // row(q) = the butterfly's number; points q * RHO + t
+    template <int NS_LOG, int RL, typename Row>
+    static __device__ __forceinline__ void stage(float2 (&v)[16], const float2* tw, Row&& row)
+    {
+        constexpr int RHO = 1 << RL;
+#pragma unroll
+        for (int q = 0; q < 16 / RHO; ++q) {
+            if constexpr (NS_LOG > 0) {
+                const int k = row(q) & ((1 << NS_LOG) - 1);
+#pragma unroll
+                for (int t = 1; t < RHO; ++t) v[q * RHO + t] = cmulc(v[q * RHO + t], tw[(t * k) << (LOGN1 - NS_LOG - RL)]);
+            }
+            butterfly<RL, true>(v + q * RHO);
+        }
+    }
+};
+// TOP: 2^(TOP - LOGE) tiles beside each other, each with words d of its own, share the stage twiddles
+template <int LOGN1, int LOGE, bool HALF, int TOP = LOGE>
+__device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __restrict__ mid, int logM, float* __restrict__ out, const Span& sp, bool quads,
+                                            const Tables& tb, uint32_t col0, float* d, float2* tw, int lane, float gain)
+{
+    using G = SplitInverse<LOGN1, LOGE>;
+    using Two = typename Cx<HALF>::Two;
+    constexpr int N1 = G::N1, HP = G::HP, T = G::T, LOGT = G::LOGT, NT = G::NT, RHO1 = 1 << G::RL1, RHO2 = 1 << G::RL2;
+    const uint32_t M = 1u << logM, N2 = M >> LOGN1;
+    const int tid = lane & (NT - 1), b = tid & (T - 1), bp = tid & (T / 2 - 1), j2 = tid >> (LOGT - 1);
+    float2 v[16];
+    {
+        Two raw[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int w = tid + q * NT, kp = w & (HP - 1), col = w >> G::LOGHP;
+            raw[q] = reinterpret_cast<const Two*>(mid)[(col0 + (uint32_t)col) * (uint32_t)HP + (uint32_t)kp];
+        }
+        load_stage_twiddles<LOGN1, tile_lanes(TOP)>(tw, tb, lane);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float4 z = cx_load(raw[q]);
+            v[2 * q] = lo2(z);
+            v[2 * q + 1] = hi2(z);
+        }
+    }
+    float x[16];
+    // component by component: to(n) <- v[n], then v[n] <- from(n)
+    // (addresses are computed again for the second component: kept, they spill)
+    auto exchange = [&](auto to, auto get) __attribute__((always_inline)) {
+#pragma unroll
+        for (int n = 0; n < 16; ++n) d[to(n, tid)] = v[n].x;
+        __syncthreads();
+        get(x, tid);
+        __syncthreads();
+        const int again = opaque_lane(tid);
+#pragma unroll
+        for (int n = 0; n < 16; ++n) d[to(n, again)] = v[n].y;
+        __syncthreads();
+        float y[16];
+        get(y, again);
+#pragma unroll
+        for (int n = 0; n < 16; ++n) v[n] = make_float2(x[n], y[n]);
+    };
+    exchange(
+        [&](int n, int tid) __attribute__((always_inline)) {
+            const int w = tid + (n >> 1) * NT, kp = w & (HP - 1);
+            return G::loaded(n & 1 ? (int)mirror_row((uint32_t)kp, N1) : kp, w >> G::LOGHP);
+        },
+        [&](float (&to)[16], int tid) __attribute__((always_inline)) {
+#pragma unroll
+            for (int n = 0; n < 16; ++n) to[n] = d[G::loaded(G::butterfly_of(tid, n >> G::RL1) + (n & (RHO1 - 1)) * (N1 / RHO1), tid & (T - 1))];
+        });
+    G::template stage<0, G::RL1>(v, tw, [](int) { return 0; });
+    __syncthreads();
+    exchange([&](int n, int tid) __attribute__((always_inline)) { return G::staged(G::butterfly_of(tid, n >> G::RL1) * RHO1 + (n & (RHO1 - 1)), tid & (T - 1)); },
+             [&](float (&to)[16], int tid) __attribute__((always_inline)) {
+#pragma unroll
+                 for (int n = 0; n < 16; ++n) to[n] = d[G::staged(G::butterfly_of(tid, n >> G::RL2) + (n & (RHO2 - 1)) * (N1 / RHO2), tid & (T - 1))];
+             });
+    G::template stage<G::RL1, G::RL2>(v, tw, [&](int q) __attribute__((always_inline)) { return G::butterfly_of(tid, q); });
+    const float scale = gain * (1.0f / (float)(2u * M));
+    const size_t left = sp.limit > sp.first ? (sp.limit - sp.first) >> 2 : 0;
+    const uint32_t end = left < (size_t)(M >> 1) ? (uint32_t)left : M >> 1;  // 16-byte pieces that exist
+    if constexpr (G::RL3 == 0) {
+        float2* dst = reinterpret_cast<float2*>(out + sp.first);
+#pragma unroll
+        for (int n = 0; n < 16; ++n) {
+            const uint32_t i = (uint32_t)((tid >> LOGT) + n * (N1 / 16)) * N2 + col0 + (uint32_t)b;
+            const float2 z = make_float2(v[n].x * scale, v[n].y * scale);
+            if (!quads)
+                store_pair(out, sp.first + 2 * (size_t)i, sp.limit, sp.pairs, z);
+            else if (i < 2 * end)
+                dst[i] = z;
+        }
+        return;
+    }
+    __syncthreads();
+    exchange(
+        [&](int n, int tid) __attribute__((always_inline)) {
+            const int j = G::butterfly_of(tid, n >> G::RL2);
+            return ((((j >> G::RL1) << (G::RL1 + G::RL2)) + (j & (RHO1 - 1)) + ((n & (RHO2 - 1)) << G::RL1)) << LOGT) + (tid & (T - 1));
+        },
+        [&](float (&to)[16], int tid) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const float2 two = *reinterpret_cast<const float2*>(d + (((tid >> (LOGT - 1)) + t * (N1 / 8)) << LOGT) + 2 * (tid & (T / 2 - 1)));
+                to[t] = two.x;
+                to[8 + t] = two.y;
+            }
+        });
+    G::template stage<LOGN1 - 3, 3>(v, tw, [&](int) __attribute__((always_inline)) { return j2; });
+    if (quads) {
+        float4* dst = reinterpret_cast<float4*>(out + sp.first);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const uint32_t i = (uint32_t)(j2 + t * (N1 / 8)) * (N2 >> 1) + (col0 >> 1) + (uint32_t)bp;
+            if (i < end) dst[i] = make_float4(v[t].x * scale, v[t].y * scale, v[8 + t].x * scale, v[8 + t].y * scale);
+        }
+    } else {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const size_t gi = sp.first + 2 * ((size_t)(j2 + t * (N1 / 8)) * N2 + col0 + 2 * bp);
+            store_pair(out, gi, sp.limit, sp.pairs, make_float2(v[t].x * scale, v[t].y * scale));
+            store_pair(out, gi + 2, sp.limit, sp.pairs, make_float2(v[8 + t].x * scale, v[8 + t].y * scale));
+        }
+    }
+}
+template <int LOGN1, int LOGE, bool HALF>
+__global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_inv_a_split(
+    const typename Cx<HALF>::One* __restrict__ mid, int logM, float* __restrict__ out, size_t n, Tables tb, int aligned, uint32_t total, float gain,
+    const uint32_t* __restrict__ only_if)
+{
+    using G = SplitInverse<LOGN1, LOGE>;
+    if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
+    extern __shared__ float2 smem[];
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const int log_tiles = logM - LOGE;
+    const uint32_t c = t >> log_tiles;
+    const Span sp = chunk_span(0, n, c, (size_t)2 << logM, aligned & 1);
+    const bool quads = (aligned & 2) && (sp.first + ((size_t)2 << logM) <= n || (n & 3u) == 0);
+    inv_a_split<LOGN1, LOGE, HALF>(mid + ((size_t)c << logM), logM, out, sp, quads, tb, (t & ((1u << log_tiles) - 1u)) << G::LOGT,
+                                   reinterpret_cast<float*>(smem), smem + (1 << LOGE) / 2, threadIdx.x, gain);
 }
 
 // ------------------------------------------------- tensors of different lengths ----
@@ -942,25 +1286,31 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b_long(const float2* _
     run(std::integral_constant<int, 10>{});
 }
 
-template <int LOGE>
-__global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a_long(const float2* __restrict__ mid, float* __restrict__ out, Tables tb,
-                                                int aligned, uint32_t per_wg, LongTable tab, LongStarts at)
+// A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of less than 2^10
+template <int TOP>
+__global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_inv_a_split_long(
+    const float2* __restrict__ mid, float* __restrict__ out, Tables tb, int aligned, uint32_t total, LongTable tab, LongStarts at)
 {
-    const LongShare share = long_share(at);
+    extern __shared__ float2 smem[];
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const LongShare share = long_share(at, t);
     const LongTensor& x = tab.t[share.tensor];
     const int logM = x.logM;
+    const Span sp{(size_t)x.goff, (size_t)x.goff + x.glen, (aligned & 1) && !(x.goff & 1u)};
+    const bool quads = (aligned & 2) && (x.goff & 3u) == 0 && (x.glen & 3u) == 0;
     auto run = [&](auto n1) __attribute__((always_inline)) {
-        constexpr int LOGN1 = decltype(n1)::value, GLOG = group_log(LOGE, LOGN1);
-        inv_a_workgroup<LOGN1, LOGE, false>(share.blk, mid + long_mid(x), logM, out, (size_t)x.goff, x.glen, tb, aligned,
-                                            power_tiles(logM, LOGE) >> GLOG, per_wg, GLOG, 1.0f);
+        constexpr int LOGN1 = decltype(n1)::value, LOGE = LOGN1 >= 10 ? TOP : 13;
+        using G = SplitInverse<LOGN1, LOGE>;
+        const uint32_t sub = LOGE < TOP ? (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / G::NT) : 0u, tile = (share.blk << (TOP - LOGE)) + sub;
+        inv_a_split<LOGN1, LOGE, false, TOP>(mid + long_mid(x), logM, out, sp, quads, tb, tile << G::LOGT, reinterpret_cast<float*>(smem) + (sub << LOGE),
+                                            smem + (1 << TOP) / 2, (int)threadIdx.x, 1.0f);
     };
     const int columns = log_columns(logM);
-    if constexpr (LOGE == 13) {
-        if (columns == 8) return run(std::integral_constant<int, 8>{});
-        if (columns == 9) return run(std::integral_constant<int, 9>{});
-    }
-    if (columns == 10) return run(std::integral_constant<int, 10>{});
-    run(std::integral_constant<int, 11>{});
+    if (columns == 8) return run(std::integral_constant<int, 8>{});
+    if (columns == 9) return run(std::integral_constant<int, 9>{});
+    if (TOP == 13 || columns == 10) return run(std::integral_constant<int, 10>{});
+    if constexpr (TOP == 14) run(std::integral_constant<int, 11>{});
 }
 
 // ---------------------------------------------------------------- launch ----
@@ -1004,6 +1354,19 @@ Grid grouped_grid(size_t groups, int glog, uint32_t kMaxWgs = 512)
     return g;
 }
 
+template <int LOGN1, int LOGE, bool HALF>
+hipError_t fwd_a_halved(const float* in, size_t n, int logM, size_t C, typename Cx<HALF>::One* mid, Tables t, int aligned, uint32_t* zero_ptr,
+                        uint32_t zero_words, float in_scale, hipStream_t s)
+{
+    using G = SplitTile<LOGN1, LOGE>;
+    const auto kern = k_fwd_a_split<LOGN1, LOGE, HALF>;
+    const hipError_t e = set_lds(kern, G::kLds);
+    if (e != hipSuccess) return e;
+    const size_t total = C << (logM - LOGE);
+    FFTSP_LAUNCH("rfft_pass_a", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(G::NT), G::kLds, s, in, n, logM, mid, t, aligned, (uint32_t)total,
+                 zero_ptr, zero_words, in_scale);
+    return hipGetLastError();
+}
 // HALF launchers take the same buffer pointers; the kernels read them as binary16 pairs
 template <int LOGN1, bool HALF>
 hipError_t fwd_a(const float* in, size_t n, int logM, size_t C, float2* mid_f32, Tables t, int aligned,
@@ -1016,6 +1379,10 @@ hipError_t fwd_a(const float* in, size_t n, int logM, size_t C, float2* mid_f32,
     auto* mid = reinterpret_cast<typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
+    if constexpr (LOGN1 == 11)
+        if (!only_if && wide_tiles(C, logM) >= kSplitForward<HALF>) return fwd_a_halved<LOGN1, 14, HALF>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, in_scale, s);
+    if constexpr (LOGN1 == 10 && HALF)
+        if (!only_if && wide_tiles(C, logM) >= 1024) return fwd_a_halved<LOGN1, 13, HALF>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, in_scale, s);
     const size_t total = C * (((size_t)1 << (logM - LOGN1)) >> (LOGE - LOGN1));
     constexpr int glog = group_log(LOGE, LOGN1);  // a chunk has at least that many tiles
     // measured: 143 us against 149 with 512; a stand-by launch (only_if) takes the small grid, which leaves sooner
@@ -1110,13 +1477,34 @@ hipError_t inv_b(const float2* spec, uint32_t sstride, int logM, size_t C, float
         if (wide_tiles(C, logM) >= kWideInverseB) return inv_b_tiled<LOGN2, 14, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
     return inv_b_tiled<LOGN2, 13, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
 }
+template <int LOGN1, int LOGE, bool HALF>
+hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, hipStream_t s, const uint32_t* only_if)
+{
+    using G = SplitInverse<LOGN1, LOGE>;
+    const auto kern = k_inv_a_split<LOGN1, LOGE, HALF>;
+    const hipError_t e = set_lds(kern, G::kLds);
+    if (e != hipSuccess) return e;
+    const size_t total = C << (logM - LOGE);
+    FFTSP_LAUNCH(only_if ? "irfft_pass_a_standby" : "irfft_pass_a", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(G::NT), G::kLds, s,
+                 reinterpret_cast<const typename Cx<HALF>::One*>(mid), logM, out, n, t, aligned, (uint32_t)total, gain, only_if);
+    return hipGetLastError();
+}
 template <int LOGN1, bool HALF>
 hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
                  hipStream_t s, const uint32_t* only_if = nullptr)
 {
-    if constexpr (LOGN1 >= kWideMin)
-        if (wide_tiles(C, logM) >= wide_inverse_a(LOGN1)) return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
-    return inv_a_tiled<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    const size_t wide = wide_tiles(C, logM);
+    if constexpr (LOGN1 == 9) return inv_a_halved<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    if constexpr (LOGN1 == 10) {
+        if (wide < kSplitInverse10) return inv_a_halved<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+        if constexpr (HALF) return inv_a_halved<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+        else return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    }
+    if constexpr (LOGN1 == 11) {
+        if (wide >= kWideInverseA && (wide < kSplitInverse11<HALF> || (!HALF && wide >= kSplitInverse11Many))) return inv_a_halved<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+        if (wide >= kWideInverseA) return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    }
+    if constexpr (LOGN1 < 9 || LOGN1 == 11) return inv_a_tiled<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
 }
 
 // The tensors come shortest first, so those whose rows or columns ask for the larger tile are the last ones.  Beside shorter
@@ -1126,18 +1514,16 @@ hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Ta
 //   forward second pass: 64 104 / 113, 192 158 / 162, 384 194 / 205, 448 236 / 243, 512 (of 778) 223 / 215, (of 900) 235 / 235,
 //     (of 1044, ResNet-50) 261 / 254, 640 236 / 243, 704 265 / 263 and 283 / 287, 768 313 / 317, 896 334 / 333, 1024 351 / 334,
 //     1280 445 / 428, 1536 438 / 411;
-//   inverse second pass: loses up to 1472 (of 2324) 458 / 476, 512 (of 1044) 206 / 210; 1536 (of 2048) 366 / 346;
-//   inverse first pass, by what the launch holds: 192 76 / 84, 498 130 / 145, 776 176 / 183, 892 195 / 200 and 197 / 196, 902 199 /
-//     205, 946 213 / 207 and 208 / 200, 1002 224 / 213, 1044 225 / 206, 1360 309 / 283, 2324 499 / 458.
-constexpr size_t kWideForwardBeside = 512, kWideInverseBBeside = 1536, kWideInverseALaunch = 940;
-// The first of them, or count; alone, beside: large tiles that are enough.  all: counted over the whole launch.
+//   inverse second pass: loses up to 1472 (of 2324) 458 / 476, 512 (of 1044) 206 / 210; 1536 (of 2048) 366 / 346.
+constexpr size_t kWideForwardBeside = 512, kWideInverseBBeside = 1536;
+size_t launch_tiles(const LongBatch& b) { return (size_t)b.units << (kLongUnitLog - 14); }  // of 2^14 points
+// The first of them, or count; alone, beside: large tiles that are enough.
 template <typename Logs>
-uint32_t first_wide(const LongBatch& b, Logs&& logs, size_t alone, size_t beside, bool all)
+uint32_t first_wide(const LongBatch& b, Logs&& logs, size_t alone, size_t beside)
 {
     uint32_t i = b.count;
     size_t tiles = 0;
     for (; i > 0 && logs(b.tab.t[i - 1].logM) >= kWideMin; --i) tiles += (size_t)1 << (b.tab.t[i - 1].logM - 14);
-    if (all) tiles = (size_t)b.units << (kLongUnitLog - 14);
     return tiles >= (i == 0 ? alone : beside) ? i : b.count;
 }
 // starts of the workgroups' shares; wgs(tensor) workgroups each.  Returns the total.
@@ -1305,7 +1691,7 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     const uint32_t wgs = long_starts(b, 0, b.count, &at, [&](const LongTensor& x) { return pass_a_wgs(x, kTileFA, run); });
     FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long, dim3(wgs), dim3(tile_lanes(kTileFA)), long_lds(kTileFA), s, in, mid, t, aligned, run,
                  zero_ptr, (uint32_t)zero_words, b.tab, at);
-    const uint32_t wide = first_wide(b, log_rows, kWideForward, kWideForwardBeside, false);
+    const uint32_t wide = first_wide(b, log_rows, kWideForward, kWideForwardBeside);
     return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
         constexpr int LOGE = decltype(size)::value;
         // Sender and receiver in us, k_fwd_b_long / this: sets of 2^20 6 111 / 105, 12 163.5 / 152;  16 of 2^19 118.4 / 114.2;  two each of 2^16 .. 2^20 83.5 / 81.5;
@@ -1339,7 +1725,7 @@ hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out,
         e = launch_short_inverse_b_long(spec, b, mid, t, s);
     } else {
         LongStarts at;
-        const uint32_t wide = first_wide(b, log_rows, kWideInverseB, kWideInverseBBeside, false);
+        const uint32_t wide = first_wide(b, log_rows, kWideInverseB, kWideInverseBBeside);
         e = by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
             constexpr int LOGE = decltype(size)::value;
             const hipError_t err = set_lds(k_inv_b_long<LOGE>, long_lds(LOGE));
@@ -1363,17 +1749,20 @@ hipError_t launch_inverse_a_long(const float2* mid, const LongBatch& b, float* o
     const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     LongStarts at;
-    const uint32_t wide = first_wide(b, log_columns, kWideInverseALaunch, kWideInverseALaunch, true);
-    return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
-        constexpr int LOGE = decltype(size)::value;
-        const hipError_t err = set_lds(k_inv_a_long<LOGE>, long_lds(LOGE));
+    // Tiles of 2^13 as in uniform calls; launches with columns of 2^11 have them beside tiles of 2^14, two to a workgroup.  Receivers in us,
+    // persistent (a launch for each tile size) / this: ResNet-50's 161 tensors 144 / 134, 150 of 10 to 2.4 M samples 275.5 / 241, 60 144 / 137, 48 of 2^19 95 / 80
+    // (two tiles to a workgroup 100), 18 of 2^20 72 / 66, 30 107.5 / 107.8, 60 (tiles of 2^14) 224 / 214, 120 of 2^18 124 / 115, 5 of 3 M 93 / 86, 180 of 2^16 67 / 67.
+    const bool small = log_columns(b.tab.t[b.count - 1].logM) <= (launch_tiles(b) < kSplitInverse10 ? 10 : 9);
+    auto run = [&](auto size) {
+        constexpr int TOP = decltype(size)::value;
+        constexpr size_t lds = SplitInverse<TOP == 14 ? 11 : 10, TOP>::kLds;
+        const hipError_t err = set_lds(k_inv_a_split_long<TOP>, lds);
         if (err != hipSuccess) return err;
-        const uint32_t per = long_run(b, first, end, LOGE, most_wgs(LOGE, 512));
-        const uint32_t g = long_starts(b, first, end, &at, [&](const LongTensor& x) { return pass_a_wgs(x, LOGE, per); });
-        FFTSP_LAUNCH("irfft_pass_a", k_inv_a_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), long_lds(LOGE), s, mid, out, t, aligned, per,
-                     b.tab, at);
+        const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, TOP); });
+        FFTSP_LAUNCH("irfft_pass_a", k_inv_a_split_long<TOP>, dim3((total + 7) / 8 * 8), dim3(tile_lanes(TOP)), lds, s, mid, out, t, aligned, total, b.tab, at);
         return hipGetLastError();
-    });
+    };
+    return small ? run(std::integral_constant<int, 13>{}) : run(std::integral_constant<int, 14>{});
 }
 
 // Half-precision variant (two-pass sizes, the codec's own buffers): the same four kernels with the intermediate

@@ -184,6 +184,24 @@ def test_tensors_leave_the_small_tiles_where_they_stop_paying(runtime, tmp_path,
     assert any("k_inv_a_long_short" in k for k in receiver) == receive_a
 
 
+# chunks of 2^20 and 2^22 hold 32 and 128 tiles of 2^14 points
+@pytest.mark.parametrize("logL, half, C, forward, inverse", [
+    (19, 0, 16, False, True), (19, 1, 120, False, True), (20, 0, 31, False, True), (20, 0, 32, False, False), (20, 1, 31, False, True), (20, 1, 32, True, True),
+    (22, 0, 1, False, False), (22, 0, 2, False, True), (22, 0, 4, False, True), (22, 0, 5, False, False), (22, 0, 13, False, False), (22, 0, 14, True, False),
+    (22, 0, 21, True, False), (22, 0, 22, True, True), (22, 1, 6, False, True), (22, 1, 7, False, False), (22, 1, 9, False, False), (22, 1, 10, True, False)])
+def test_first_passes_with_half_of_the_lds(runtime, tmp_path, logL, half, C, forward, inverse):
+    L = 1 << logL
+    n = C * L
+    if half:
+        calls = [["fftsp_compress_h", ["big", n, L, 0.5, 8, 0, "big", "big", "big", "big", None]],
+                 ["fftsp_decompress_h", ["big", "big", "big", n, L, 0.5, 8, 0, "big", "big", None]]]
+    else:
+        calls = [compress(n, L, 0.5), ["fftsp_decompress", ["big", "big", "big", n, L, 0.5, 8, "big", "big", None]]]
+    sender, receiver = kernels(runtime, tmp_path, calls)
+    assert any("k_fwd_a_split" in k for k in sender) == forward
+    assert any("k_inv_a_split" in k for k in receiver) == inverse
+
+
 @pytest.mark.parametrize("L, most", [(1 << 16, 16), (1 << 17, 4)])
 def test_topk_finds_its_threshold_beside_the_codes_in_short_calls(runtime, tmp_path, L, most):
     calls = [["fftsp_topk_compress", ["big", C * L, L, 0.3, 8, "big", "big", "big", "big", None]] for C in (most, most + 1)]
