@@ -265,13 +265,13 @@ __device__ __forceinline__ Place place_of(const Shape& u, const TableArg<TABLE>&
 }
 // a workgroup per tile
 template <bool TABLE>
-__device__ __forceinline__ Place place_of_tile(const Shape& u, const TableArg<TABLE>& tab)
+__device__ __forceinline__ Place place_of_tile(const Shape& u, const TableArg<TABLE>& tab, uint32_t tile = blockIdx.x)
 {
     if constexpr (TABLE) {
-        const LongShare share = long_share(tab.t.tiles);
+        const LongShare share = long_share(tab.t.tiles, tile);
         return place_of<TABLE>(u, tab, share.tensor, share.blk);
     } else {
-        return place_of<TABLE>(u, tab, blockIdx.x / u.Tn, blockIdx.x % u.Tn);
+        return place_of<TABLE>(u, tab, tile / u.Tn, tile % u.Tn);
     }
 }
 
@@ -1400,6 +1400,9 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, ResolveArgs a, uin
 // do pass through LDS, in 16-byte loads (50 us for 55).
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against shuffles and vector masks: 70 -> 67 us,
 // binary16 bins 60 -> 45, 15 % of the samples kept at 32 bits 98 -> 50; one chunk of 2^16 8 -> 7.
+// The last tiles come first: k_collect has just read them, and of what does not fit the 256 MB cache the first ones are gone
+// (62 M samples in chunks of 2^20 67 -> 61 us, the step 537 -> 532; 138 M in 2^22 150 -> 138, 1320 -> 1306; top-k 223 -> 218.5).  After a kernel that
+// wrote the bins instead of reading them the order makes no difference.
 template <bool TABLE, bool REAL, bool HALF, bool MERGED>
 __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u, ResolveArgs a,
                                              uint32_t* __restrict__ sel, uint32_t* __restrict__ tscan,
@@ -1414,15 +1417,16 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
     __shared__ __align__(16) uint64_t bmw[kTile / 64];
     __shared__ uint32_t weq[4], wfl[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Place at = place_of_tile<TABLE>(u, tab);
+    const uint32_t nth = MERGED ? blockIdx.x : gridDim.x - 1u - blockIdx.x;  // which tile of the launch
+    const Place at = place_of_tile<TABLE>(u, tab, nth);
     const uint32_t c = at.chunk, tile = at.tile, B = at.B, W = at.W;
     const size_t S = at.S;
     const int pair_log = at.pair_log;
     const int bits = a.bits, m = a.m;
     Threshold found;
     if constexpr (!MERGED)
-        found = Threshold{sel[c * 8 + 2], sel[c * 8 + 3], sel[c * 8 + 4], tscan[(size_t)blockIdx.x * 2 + 0],
-                          tscan[(size_t)blockIdx.x * 2 + 1]};
+        found = Threshold{sel[c * 8 + 2], sel[c * 8 + 3], sel[c * 8 + 4], tscan[(size_t)nth * 2 + 0],
+                          tscan[(size_t)nth * 2 + 1]};
     const uint32_t twoN = CODES * (uint32_t)bits;  // code bits per kept unit
     const int shift = 23 - m;
 
