@@ -1402,7 +1402,10 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, ResolveArgs a, uin
 // binary16 bins 60 -> 45, 15 % of the samples kept at 32 bits 98 -> 50; one chunk of 2^16 8 -> 7.
 // The last tiles come first: k_collect has just read them, and of what does not fit the 256 MB cache the first ones are gone
 // (62 M samples in chunks of 2^20 67 -> 61 us, the step 537 -> 532; 138 M in 2^22 150 -> 138, 1320 -> 1306; top-k 223 -> 218.5).  After a kernel that
-// wrote the bins instead of reading them the order makes no difference.
+// wrote the bins instead of reading them the order makes no difference.  Eight by eight, so that a tile stays on the XCD whose L2 may have it from
+// k_collect: one by one, calls of 100 to 450 tiles of 2^14 points lost 3 to 12 us (13 tensors 183 -> 195, so 186; 29 186 -> 196, so 187; 42 275 -> 281,
+// so 270).  Below kEmitBackwards tiles of 16 KB the first ones are still there, and the order stays.
+constexpr uint32_t kEmitBackwards = 4096;
 template <bool TABLE, bool REAL, bool HALF, bool MERGED>
 __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u, ResolveArgs a,
                                              uint32_t* __restrict__ sel, uint32_t* __restrict__ tscan,
@@ -1417,7 +1420,9 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
     __shared__ __align__(16) uint64_t bmw[kTile / 64];
     __shared__ uint32_t weq[4], wfl[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t nth = MERGED ? blockIdx.x : gridDim.x - 1u - blockIdx.x;  // which tile of the launch
+    const uint32_t whole = gridDim.x & ~7u;
+    const bool backwards = !MERGED && gridDim.x >= kEmitBackwards && blockIdx.x < whole;
+    const uint32_t nth = backwards ? whole - 8u - (blockIdx.x & ~7u) + (blockIdx.x & 7u) : blockIdx.x;  // which tile of the launch
     const Place at = place_of_tile<TABLE>(u, tab, nth);
     const uint32_t c = at.chunk, tile = at.tile, B = at.B, W = at.W;
     const size_t S = at.S;
