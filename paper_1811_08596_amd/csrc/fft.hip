@@ -947,7 +947,8 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b(const typename Cx<HA
 
 // Inverse pass A: inverse N1-point FFTs over k1 for a tile of columns n2; writes the real samples to out[first .. first + n),
 // chunk by chunk.  `aligned`: bit 0 = `out` is 8-byte aligned, bit 1 = 16-byte aligned.
-template <int LOGN1, int LOGE, bool HALF>
+// ONCE: what it reads and writes passes the caches by.
+template <int LOGN1, int LOGE, bool HALF, bool ONCE>
 __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<HALF>::One* __restrict__ mid, int logM,
                                                 float* __restrict__ out, size_t n, const Tables& tb, int aligned,
                                                 uint32_t total, uint32_t per_wg, int glog, float gain)
@@ -977,7 +978,7 @@ __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<
         for (int q = 0; q < PER2; ++q) {
             if (!(part < 0 || q * PARTS / PER2 == part)) continue;
             const int w = tid + q * NT, kp = w & (HP - 1), col = w >> LOGHP;
-            r[q] = src[live ? (uint32_t)(col0 + col) * HP + kp : 0u];
+            r[q] = load_maybe_once<ONCE>(src + (live ? (uint32_t)(col0 + col) * HP + kp : 0u));
         }
     };
     auto fill = [&](int tid) {
@@ -1013,7 +1014,7 @@ __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<
                 const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
                 const uint32_t i = (uint32_t)n1 * (N2 >> 1) + (col0 >> 1) + bp;
                 const float4 v = lds_load2<LOGT>(d, n1, 2 * bp);
-                if (i < quads) dst[i] = make_float4(v.x * scale, v.y * scale, v.z * scale, v.w * scale);
+                if (i < quads) store_maybe_once<ONCE>(dst + i, make_float4(v.x * scale, v.y * scale, v.z * scale, v.w * scale));
             }
         } else {
 #pragma unroll
@@ -1033,13 +1034,13 @@ __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<
     }
 }
 
-template <int LOGN1, int LOGE, bool HALF>
+template <int LOGN1, int LOGE, bool HALF, bool ONCE>
 __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HALF>::One* __restrict__ mid, int logM,
                                                float* __restrict__ out, size_t n, Tables tb, int aligned, uint32_t total,
                                                uint32_t per_wg, int glog, float gain, const uint32_t* __restrict__ only_if)
 {
     if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
-    inv_a_workgroup<LOGN1, LOGE, HALF>(blockIdx.x, mid, logM, out, n, tb, aligned, total, per_wg, glog, gain);
+    inv_a_workgroup<LOGN1, LOGE, HALF, ONCE>(blockIdx.x, mid, logM, out, n, tb, aligned, total, per_wg, glog, gain);
 }
 
 // Inverse pass A with a tile in half of the LDS, as fwd_a_split: the same radices, twiddles and order of operations as inv_a_workgroup.  The last
@@ -1083,7 +1084,7 @@ struct SplitInverse {
     }
 };
 // TOP: 2^(TOP - LOGE) tiles beside each other, each with words d of its own, share the stage twiddles
-template <int LOGN1, int LOGE, bool HALF, int TOP = LOGE>
+template <int LOGN1, int LOGE, bool HALF, bool ONCE, int TOP = LOGE>
 __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __restrict__ mid, int logM, float* __restrict__ out, const Span& sp, bool quads,
                                             const Tables& tb, uint32_t col0, float* d, float2* tw, int lane, float gain)
 {
@@ -1098,7 +1099,7 @@ __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __rest
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int w = tid + q * NT, kp = w & (HP - 1), col = w >> G::LOGHP;
-            raw[q] = reinterpret_cast<const Two*>(mid)[(col0 + (uint32_t)col) * (uint32_t)HP + (uint32_t)kp];
+            raw[q] = load_maybe_once<ONCE>(reinterpret_cast<const Two*>(mid) + ((col0 + (uint32_t)col) * (uint32_t)HP + (uint32_t)kp));
         }
         load_stage_twiddles<LOGN1, tile_lanes(TOP)>(tw, tb, lane);
 #pragma unroll
@@ -1179,7 +1180,7 @@ __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __rest
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const uint32_t i = (uint32_t)(j2 + t * (N1 / 8)) * (N2 >> 1) + (col0 >> 1) + (uint32_t)bp;
-            if (i < end) dst[i] = make_float4(v[t].x * scale, v[t].y * scale, v[8 + t].x * scale, v[8 + t].y * scale);
+            if (i < end) store_maybe_once<ONCE>(dst + i, make_float4(v[t].x * scale, v[t].y * scale, v[8 + t].x * scale, v[8 + t].y * scale));
         }
     } else {
 #pragma unroll
@@ -1190,7 +1191,7 @@ __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __rest
         }
     }
 }
-template <int LOGN1, int LOGE, bool HALF>
+template <int LOGN1, int LOGE, bool HALF, bool ONCE>
 __global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_inv_a_split(
     const typename Cx<HALF>::One* __restrict__ mid, int logM, float* __restrict__ out, size_t n, Tables tb, int aligned, uint32_t total, float gain,
     const uint32_t* __restrict__ only_if)
@@ -1204,7 +1205,7 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_e
     const uint32_t c = t >> log_tiles;
     const Span sp = chunk_span(0, n, c, (size_t)2 << logM, aligned & 1);
     const bool quads = (aligned & 2) && (sp.first + ((size_t)2 << logM) <= n || (n & 3u) == 0);
-    inv_a_split<LOGN1, LOGE, HALF>(mid + ((size_t)c << logM), logM, out, sp, quads, tb, (t & ((1u << log_tiles) - 1u)) << G::LOGT,
+    inv_a_split<LOGN1, LOGE, HALF, ONCE>(mid + ((size_t)c << logM), logM, out, sp, quads, tb, (t & ((1u << log_tiles) - 1u)) << G::LOGT,
                                    reinterpret_cast<float*>(smem), smem + (1 << LOGE) / 2, threadIdx.x, gain);
 }
 
@@ -1303,7 +1304,7 @@ __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu
         constexpr int LOGN1 = decltype(n1)::value, LOGE = LOGN1 >= 10 ? TOP : 13;
         using G = SplitInverse<LOGN1, LOGE>;
         const uint32_t sub = LOGE < TOP ? (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / G::NT) : 0u, tile = (share.blk << (TOP - LOGE)) + sub;
-        inv_a_split<LOGN1, LOGE, false, TOP>(mid + long_mid(x), logM, out, sp, quads, tb, tile << G::LOGT, reinterpret_cast<float*>(smem) + (sub << LOGE),
+        inv_a_split<LOGN1, LOGE, false, false, TOP>(mid + long_mid(x), logM, out, sp, quads, tb, tile << G::LOGT, reinterpret_cast<float*>(smem) + (sub << LOGE),
                                             smem + (1 << TOP) / 2, (int)threadIdx.x, 1.0f);
     };
     const int columns = log_columns(logM);
@@ -1426,12 +1427,18 @@ hipError_t inv_b_tiled(const float2* spec_f32, uint32_t sstride, int logM, size_
     return hipGetLastError();
 }
 
+// Outputs of this size pass the caches by, and so do the last reads of the intermediate: the two do not fit the 256 MB cache together, and what
+// is kept of them there has to be written back, or made room for, under the kernels that come next.  A consumer finds no less of such an output
+// in the cache than its last part.  Calls in us, all through the caches / this, samples in millions: 2^20 62 step 531 / 511, receiver 190 / 172,
+// binary16 step 428 / 404, 45 384 / 381;  2^22 138 step 1308 / 1249;  2^21 34 343 / 327;  2^16 40 327 / 321.  Smaller ones lose: 2^20 17 167 / 171, 2^19 26
+// 224 / 228, binary16 2^18 30 209 / 211, 60 tensors 288 / 297.  Stores alone: 62 515, 181, 412, 138 1287.  The gradient read this way: 62 535 -> 551.
+constexpr size_t kOnceBytes = (size_t)1 << 27;
 template <int LOGN1, int LOGE, bool HALF>
 hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
                  hipStream_t s, const uint32_t* only_if)
 {
     const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN1)) * sizeof(float2);
-    auto kern = k_inv_a<LOGN1, LOGE, HALF>;
+    auto kern = 4 * n >= kOnceBytes ? k_inv_a<LOGN1, LOGE, HALF, true> : k_inv_a<LOGN1, LOGE, HALF, false>;
     auto* mid = reinterpret_cast<const typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
@@ -1481,7 +1488,7 @@ template <int LOGN1, int LOGE, bool HALF>
 hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, hipStream_t s, const uint32_t* only_if)
 {
     using G = SplitInverse<LOGN1, LOGE>;
-    const auto kern = k_inv_a_split<LOGN1, LOGE, HALF>;
+    const auto kern = 4 * n >= kOnceBytes ? k_inv_a_split<LOGN1, LOGE, HALF, true> : k_inv_a_split<LOGN1, LOGE, HALF, false>;
     const hipError_t e = set_lds(kern, G::kLds);
     if (e != hipSuccess) return e;
     const size_t total = C << (logM - LOGE);

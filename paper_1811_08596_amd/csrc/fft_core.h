@@ -326,6 +326,39 @@ __device__ __forceinline__ uint32_t in_stretches(uint32_t total)
     return t < hi ? t : total;
 }
 
+// Accesses that leave the caches to others (ONCE), for what the call does not touch again: whole calls choose, see kOnceBytes.
+template <bool ONCE>
+__device__ __forceinline__ void store_maybe_once(float4* p, float4 v)
+{
+    using F4 = float __attribute__((ext_vector_type(4)));
+    if constexpr (ONCE)
+        __builtin_nontemporal_store(F4{v.x, v.y, v.z, v.w}, reinterpret_cast<F4*>(p));
+    else
+        *p = v;
+}
+template <bool ONCE>
+__device__ __forceinline__ float4 load_maybe_once(const float4* p)
+{
+    using F4 = float __attribute__((ext_vector_type(4)));
+    if constexpr (ONCE) {
+        const F4 v = __builtin_nontemporal_load(reinterpret_cast<const F4*>(p));
+        return make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+        return *p;
+    }
+}
+template <bool ONCE>
+__device__ __forceinline__ uint2 load_maybe_once(const uint2* p)
+{
+    using U2 = uint32_t __attribute__((ext_vector_type(2)));
+    if constexpr (ONCE) {
+        const U2 v = __builtin_nontemporal_load(reinterpret_cast<const U2*>(p));
+        return make_uint2(v[0], v[1]);
+    } else {
+        return *p;
+    }
+}
+
 // LDS stages run_fft takes for `rem` remaining levels
 constexpr int lds_stages(int rem)
 {
