@@ -14,7 +14,7 @@ def dev():
 
 # chunks of a call that takes the kernel in question; test_host_launches.py pins which one that is
 @pytest.mark.parametrize("half,log_l,chunks", [
-    (0, 18, 70), (0, 19, 40), (0, 20, 31), (0, 21, 10), (0, 22, 4), (0, 22, 14), (0, 22, 22),
+    (0, 16, 512), (0, 18, 70), (0, 19, 40), (0, 20, 31), (0, 20, 32), (0, 21, 10), (0, 22, 4), (0, 22, 14), (0, 22, 22),
     (1, 18, 70), (1, 19, 40), (1, 20, 31), (1, 20, 33), (1, 21, 17), (1, 22, 4), (1, 22, 10),
 ])
 @pytest.mark.parametrize("short", (0, 8, 1, 6))
