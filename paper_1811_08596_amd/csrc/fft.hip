@@ -1427,18 +1427,31 @@ hipError_t inv_b_tiled(const float2* spec_f32, uint32_t sstride, int logM, size_
     return hipGetLastError();
 }
 
-// Outputs of this size pass the caches by, and so do the last reads of the intermediate: the two do not fit the 256 MB cache together, and what
-// is kept of them there has to be written back, or made room for, under the kernels that come next.  A consumer finds no less of such an output
-// in the cache than its last part.  Calls in us, all through the caches / this, samples in millions: 2^20 62 step 531 / 511, receiver 190 / 172,
-// binary16 step 428 / 404, 45 384 / 381;  2^22 138 step 1308 / 1249;  2^21 34 343 / 327;  2^16 40 327 / 321.  Smaller ones lose: 2^20 17 167 / 171, 2^19 26
-// 224 / 228, binary16 2^18 30 209 / 211, 60 tensors 288 / 297.  Stores alone: 62 515, 181, 412, 138 1287.  The gradient read this way: 62 535 -> 551.
-constexpr size_t kOnceBytes = (size_t)1 << 27;
+// Large outputs pass the caches by, and so do the last reads of the intermediate: the two do not fit the 256 MB cache together, and what
+// is kept of them there has to be written back, or made room for, under the kernels that come next, a caller's that reads the output among them.
+// Calls in us, all through the caches / this, alone and with a kernel behind each call that reads the output and updates as many weights:
+//   2^20 34 M samples receiver 118.6 / 99.5 and 187.9 / 178.1, 45 M 146.4 / 130.2 and 239.8 / 232.1, 62 M 208.8 / 193.6 and 334.4 / 328.8, step 531.6 / 511.5
+//   and 658.9 / 640.3, binary16 step 424.4 / 402.6 and 558.4 / 534.6;  2^22 100 M receiver 409.9 / 350.6 and 642.6 / 550.9, 138 M step 1309.9 / 1247.2 and
+//   1622.4 / 1529.1;  2^16 40 M receiver 122.9 / 103.5 and 209.1 / 199.8.  A kernel that reads and writes elsewhere: 62 M step 611.3 / 597.5.
+// Smaller ones lose alone: 2^20 17 M 167 / 171, 2^19 26 M 224 / 228, 60 tensors 288 / 297.  Stores alone, with that reader: 62 M step 645.7, 138 M 1577.6;
+// loads alone 653.0, 1635.5.  The gradient read this way: 62 M step 535 / 551.
+// Columns of 2^8 behind a spectrum in memory (several senders' streams; codes of 16 and 32 bits) have a higher line, below which the reader pays more
+// than the call gains: 2^16 four streams 34 M 167.0 / 160.0 and 228.7 / 240.4, 2^17 40 M 188.6 / 184.4 and 266.6 / 275.1, 2^16 eight streams 48 M 275.1 / 278.2 and
+// 372.7 / 375.3, 54 M 309.1 / 313.0 and 420.3 / 419.7, 60 M 345.5 / 344.4 and 467.8 / 463.0, 72 M 418.0 / 417.7 and 569.6 / 556.0.  Longer columns there: 2^18 four
+// streams 34 M 166.8 / 160.2 and 233.8 / 233.7.  Binary16 right above the line gives with a reader what it takes alone, and gains from 38 M on: 2^16 33.6 M 89.3 / 84.2
+// and 155.4 / 160.2, 2^22 126.6 / 122.8 and 195.8 / 199.8, 2^20 94.6 / 85.1 and 158.9 / 160.2;  2^16 42 M 101.2 / 98.2 and 197.6 / 189.6.
+constexpr size_t kOnceBytes = (size_t)1 << 27, kOnceBytesSpectrum8 = (size_t)7 << 25;
+template <int LOGN1, bool HALF>
+bool passes_by(size_t n, int from_spectrum)
+{
+    return 4 * n >= (!HALF && LOGN1 == 8 && from_spectrum ? kOnceBytesSpectrum8 : kOnceBytes);
+}
 template <int LOGN1, int LOGE, bool HALF>
-hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
-                 hipStream_t s, const uint32_t* only_if)
+hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, bool once,
+                  hipStream_t s, const uint32_t* only_if)
 {
     const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN1)) * sizeof(float2);
-    auto kern = 4 * n >= kOnceBytes ? k_inv_a<LOGN1, LOGE, HALF, true> : k_inv_a<LOGN1, LOGE, HALF, false>;
+    auto kern = once ? k_inv_a<LOGN1, LOGE, HALF, true> : k_inv_a<LOGN1, LOGE, HALF, false>;
     auto* mid = reinterpret_cast<const typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
@@ -1485,10 +1498,11 @@ hipError_t inv_b(const float2* spec, uint32_t sstride, int logM, size_t C, float
     return inv_b_tiled<LOGN2, 13, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
 }
 template <int LOGN1, int LOGE, bool HALF>
-hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, hipStream_t s, const uint32_t* only_if)
+hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, bool once, hipStream_t s,
+                        const uint32_t* only_if)
 {
     using G = SplitInverse<LOGN1, LOGE>;
-    const auto kern = 4 * n >= kOnceBytes ? k_inv_a_split<LOGN1, LOGE, HALF, true> : k_inv_a_split<LOGN1, LOGE, HALF, false>;
+    const auto kern = once ? k_inv_a_split<LOGN1, LOGE, HALF, true> : k_inv_a_split<LOGN1, LOGE, HALF, false>;
     const hipError_t e = set_lds(kern, G::kLds);
     if (e != hipSuccess) return e;
     const size_t total = C << (logM - LOGE);
@@ -1497,21 +1511,22 @@ hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_
     return hipGetLastError();
 }
 template <int LOGN1, bool HALF>
-hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
+hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, int from_spectrum,
                  hipStream_t s, const uint32_t* only_if = nullptr)
 {
     const size_t wide = wide_tiles(C, logM);
-    if constexpr (LOGN1 == 9) return inv_a_halved<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    const bool once = passes_by<LOGN1, HALF>(n, from_spectrum);
+    if constexpr (LOGN1 == 9) return inv_a_halved<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
     if constexpr (LOGN1 == 10) {
-        if (wide < kSplitInverse10) return inv_a_halved<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
-        if constexpr (HALF) return inv_a_halved<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
-        else return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+        if (wide < kSplitInverse10) return inv_a_halved<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
+        if constexpr (HALF) return inv_a_halved<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
+        else return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
     }
     if constexpr (LOGN1 == 11) {
-        if (wide >= kWideInverseA && (wide < kSplitInverse11<HALF> || (!HALF && wide >= kSplitInverse11Many))) return inv_a_halved<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
-        if (wide >= kWideInverseA) return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+        if (wide >= kWideInverseA && (wide < kSplitInverse11<HALF> || (!HALF && wide >= kSplitInverse11Many))) return inv_a_halved<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
+        if (wide >= kWideInverseA) return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
     }
-    if constexpr (LOGN1 < 9 || LOGN1 == 11) return inv_a_tiled<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    if constexpr (LOGN1 < 9 || LOGN1 == 11) return inv_a_tiled<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
 }
 
 // The tensors come shortest first, so those whose rows or columns ask for the larger tile are the last ones.  Beside shorter
@@ -1659,11 +1674,11 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
             default: return hipErrorInvalidValue;
         }
     }
-    return e == hipSuccess ? launch_inverse_a(mid, logM, C, out, n, t, gain, 0, s, only_if) : e;
+    return e == hipSuccess ? launch_inverse_a(mid, logM, C, out, n, t, gain, 0, 1, s, only_if) : e;
 }
 
-hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, hipStream_t s,
-                            const uint32_t* only_if)
+hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, int from_spectrum,
+                            hipStream_t s, const uint32_t* only_if)
 {
     if (half) gain *= half_lift(logM);
     if (!only_if && short_inverse(logM, C)) return launch_short_inverse_a(mid, logM, C, out, n, t, gain, half, s);
@@ -1671,11 +1686,11 @@ hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, s
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     auto run = [&](auto columns) {
         constexpr int LOGN1 = decltype(columns)::value;
-        return half ? inv_a<LOGN1, true>(mid, logM, C, out, n, t, aligned, gain, s, only_if)
-                    : inv_a<LOGN1, false>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+        return half ? inv_a<LOGN1, true>(mid, logM, C, out, n, t, aligned, gain, from_spectrum, s, only_if)
+                    : inv_a<LOGN1, false>(mid, logM, C, out, n, t, aligned, gain, from_spectrum, s, only_if);
     };
     switch ((logM + 1) / 2) {
-        case 7: return half ? inv_a<7, true>(mid, logM, C, out, n, t, aligned, gain, s) : hipErrorInvalidValue;
+        case 7: return half ? inv_a<7, true>(mid, logM, C, out, n, t, aligned, gain, from_spectrum, s) : hipErrorInvalidValue;
         case 8: return run(std::integral_constant<int, 8>{});
         case 9: return run(std::integral_constant<int, 9>{});
         case 10: return run(std::integral_constant<int, 10>{});
@@ -1836,7 +1851,7 @@ hipError_t launch_irfft_half(const void* spec, uint32_t sstride, size_t n, int l
             default: return hipErrorInvalidValue;
         }
     }
-    return e == hipSuccess ? launch_inverse_a(md, logM, C, out, n, t, gain, 1, s) : e;
+    return e == hipSuccess ? launch_inverse_a(md, logM, C, out, n, t, gain, 1, 1, s) : e;
 }
 
 }  // namespace fftsp

@@ -3,6 +3,7 @@ library in a process of its own, so host-side decisions (which calls are taken, 
 for sizes no CPU test could compute.  Device addresses are made up; nothing dereferences them."""
 import json
 import os
+import re
 import subprocess
 import sys
 import textwrap
@@ -200,6 +201,21 @@ def test_first_passes_with_half_of_the_lds(runtime, tmp_path, logL, half, C, for
     sender, receiver = kernels(runtime, tmp_path, calls)
     assert any("k_fwd_a_split" in k for k in sender) == forward
     assert any("k_inv_a_split" in k for k in receiver) == inverse
+
+
+# samples of a receiver from which its output passes the caches by: below, a call and a reader of its output take longer together
+@pytest.mark.parametrize("call, logL, n, by", [
+    ("one", 16, (1 << 25) - 1, False), ("one", 16, 1 << 25, True), ("one", 20, 1 << 25, True), ("one", 22, 1 << 25, True),
+    ("peers", 16, 1 << 25, False), ("peers", 17, (7 << 23) - 1, False), ("peers", 16, 7 << 23, True), ("peers", 18, 1 << 25, True), ("peers", 20, 1 << 25, True),
+    ("raw", 16, 1 << 25, False), ("raw", 19, 1 << 25, True),
+    ("half", 15, 1 << 25, True), ("half", 17, (1 << 25) - 1, False), ("half", 17, 1 << 25, True), ("half", 22, 1 << 25, True)])
+def test_outputs_that_pass_the_caches_by(runtime, tmp_path, call, logL, n, by):
+    L = 1 << logL
+    made, = kernels(runtime, tmp_path, [
+        {"one": decompress(n, L), "peers": accumulate(n, L, 8), "raw": decompress(n, L, bits=32),
+         "half": ["fftsp_decompress_h", ["big", "big", "big", n, L, 0.5, 8, 0, "big", "big", None]]}[call]])
+    last, = [re.search(r"k_inv_a(?:_split)?ILi\d+ELi\d+ELb(\d)ELb(\d)E", k) for k in made if "k_inv_a" in k]
+    assert (last[1] == "1") == (call == "half") and (last[2] == "1") == by
 
 
 @pytest.mark.parametrize("L, most", [(1 << 16, 16), (1 << 17, 4)])
