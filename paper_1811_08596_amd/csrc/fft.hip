@@ -37,9 +37,8 @@ namespace {
 //     4224 (138 M samples in chunks of 2^22) 913 / 810;
 //   inverse second pass, the same rows, receiver: 384 80 / 84, 640 115 / 122, 1024 171 / 169 and (chunks of 2^22) 186 / 190, 1280
 //     222 / 202, 4224 780 / 694; four senders' streams 1216 242 / 221;
-//   inverse first pass, columns of 2^10 (stores of 64 -> 128 bytes), receiver: 768 129 / 118, 1920 (62 M samples in chunks of 2^20)
-//     310 / 280, and the next call's forward first pass, which runs while those lines are written back, 134 / 118; columns of 2^11
-//     (32 -> 64 bytes): 128 52.1 / 52.7, 256 68.4 / 67.5, 768 157 / 146, 4224 926 / 780.  (Tiles in half of the LDS: below.)
+//   inverse first pass, columns of 2^11 (stores of 32 -> 64 bytes): 128 52.1 / 52.7, 256 68.4 / 67.5, 768 157 / 146.  (Tiles in half of the
+//     LDS: below.)
 // With rows of 2^9, already a line wide, the second passes lose (101 / 106 and 109 / 127 us).  The forward first pass, which only
 // reads in narrow pieces, was slower that way (columns of 2^10: 119 / 124 us; of 2^11: 340 us against 327 with four
 // 2^13-point tiles of a line walked in step).  Binary16 storage: the same lines within 3 us.
@@ -1046,16 +1045,20 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HA
 // Inverse pass A with a tile in half of the LDS, as fwd_a_split: the same radices, twiddles and order of operations as inv_a_workgroup.  The last
 // stage's butterflies are dealt out so that a lane has both of two adjacent columns and stores 16 bytes from its registers.
 // Four tiles of 2^13 points to a compute unit where the persistent kernel has two, and no rounds of runs of equal length that end together.
-// Receivers in us, persistent / this: columns of 2^9, chunks of 2^19, 8.4 M samples 43.5 / 39.5, 25.6 M 81.5 / 75.1, 62 M 208 / 200, binary16 169.7 / 155.8; 2^18
-//   20 M 63.0 / 59.1.  Columns of 2^10 by number of tiles of 2^14, persistent / this with 2^14 / with 2^13: 256 43.7 / 40.6 / 40.1, 512 60.6 / 59.0 / 57.0, 640
-//   80.5 / 81.0 / 74.6, 768 79.2 / 79.5 / 78.1, 1024 108.2 / 107.2 / 110.5, 1280 132.6 / 132.6 / 151, 1920 208 / 211 / 246; binary16 512 60.6 / 57.2 / 57.0, 1024
-//   94.0 / 91.2 / 93.2, 1920 167.1 / 164.0 / 181 and (2^21) 184.0 / 179.6 / 201.7.  Of 2^11: 256 51.1 / 48.6, 384 64.2 / 60.7, 512 70.5 / 69.1, 768 92.9 / 94.7, 1024
-//   119.3 / 125.7, 1280 161.7 / 159.2, 1536 196 / 203.8, 1920 266.9 / 268.0, 2560 358.3 / 358.7, 3072 418.8 / 411.6, 4224 584.9 / 564.5; binary16 256 46.0 / 46.5, 512
-//   70.5 / 65.3, 768 90.5 / 88.1, 1024 111.1 / 114.3, 1920 205.5 / 208.  Columns of 2^8, two stages: 10 M 44.0 / 44.0, 45 M 134 / 150.
-constexpr size_t kSplitInverse10 = 1024;  // fewer tiles: of 2^13; from here on binary32 keeps the persistent kernel, binary16 takes 2^14
-template <bool HALF>
-constexpr size_t kSplitInverse11 = HALF ? 896 : 640;
-constexpr size_t kSplitInverse11Many = 2816;
+// Receivers in us, persistent / this, by number of tiles of 2^14; behind a semicolon with a kernel after each call that reads the output:
+//   columns of 2^9, through the caches: 2^19 8.4 M samples 43.5 / 39.5, 25.6 M 81.5 / 75.1; 2^18 20 M 63.0 / 59.1; past them: 2^19 1024 97.5 / 90.8; 171.4 / 166.4, 1920
+//     192.1 / 174.7; 330.4 / 296.7, binary16 1920 156.5 / 134.6; 291.0 / 268.1, 2^18 1600 157.3 / 148.6;
+//   columns of 2^10, through the caches, persistent / this with tiles of 2^14 / of 2^13: 256 43.7 / 40.6 / 40.1, 512 60.6 / 59.0 / 57.0, 640 80.5 / 81.0 / 74.6, 768
+//     79.2 / 79.5 / 78.1; past them, persistent / this with 2^14: 2^20 1024 95.1 / 93.1; 173.2 / 171.1, 1280 114.8 / 113.0; 206.7 / 203.4, 1536 134.4 / 135.3; 256.4 / 240.4,
+//     1920 191.9 / 184.9; 329.9 / 304.7, 3840 380.7 / 357.8; 637.0 / 608.7; 2^21 1024 103.6 / 105.2; 178.7 / 179.6, 1280 127.7 / 126.7; 223.8 / 216.7, 1920 207.9 /
+//     201.1; 346.8 / 327.9; binary16 2^20 1024 89.7 / 85.5; 164.0 / 159.2, 1920 151.9 / 147.0; 281.5 / 276.3;
+//   columns of 2^11, through the caches: 256 51.1 / 48.6, 384 64.2 / 60.7, 512 70.5 / 69.1, 640 91.1 / 90.9; 127.6 / 129.5, 768 97.8 / 98.5; 147.7 / 149.8, 896 114.2 / 114.1;
+//     187.2 / 184.9, 1024 120.5 / 127.2; 208.5 / 211.3; past them: 1024 117.8 / 118.6; 194.7 / 194.1, 1152 135.8 / 131.7; 222.6 / 213.8, 1920 231.3 / 221.2; 371.7 / 352.0,
+//     4224 537.7 / 492.0; 832.3 / 785.9; binary16 through the caches 640 85.8 / 81.6; 131.6 / 127.0, 768 91.2 / 88.3; 132.4 / 130.5, 896 108.6 / 102.7; 162.0 / 158.2, past
+//     them 1024 113.8 / 114.3; 189.5 / 191.9, 1280 136.2 / 134.6; 229.3 / 224.3, 4224 428.8 / 394.0; 733.9 / 689.9;
+//   columns of 2^8, two stages: 10 M 44.0 / 44.0, 45 M 134 / 150.
+constexpr size_t kSplitInverse10 = 1024;  // fewer tiles: of 2^13; else of 2^14
+constexpr size_t kSplitInverse11 = 640;   // binary32 through the caches: from here on the persistent kernel
 template <int LOGN1, int LOGE>
 struct SplitInverse {
     static constexpr int N1 = 1 << LOGN1, LOGT = LOGE - LOGN1, T = 1 << LOGT, NT = tile_lanes(LOGE), HP = N1 / 2, LOGHP = LOGN1 - 1;
@@ -1446,12 +1449,12 @@ bool passes_by(size_t n, int from_spectrum)
 {
     return 4 * n >= (!HALF && LOGN1 == 8 && from_spectrum ? kOnceBytesSpectrum8 : kOnceBytes);
 }
-template <int LOGN1, int LOGE, bool HALF>
-hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, bool once,
+template <int LOGN1, int LOGE, bool HALF, bool ONCE>
+hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
                   hipStream_t s, const uint32_t* only_if)
 {
     const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN1)) * sizeof(float2);
-    auto kern = once ? k_inv_a<LOGN1, LOGE, HALF, true> : k_inv_a<LOGN1, LOGE, HALF, false>;
+    auto kern = k_inv_a<LOGN1, LOGE, HALF, ONCE>;
     auto* mid = reinterpret_cast<const typename Cx<HALF>::One*>(mid_f32);
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
@@ -1497,12 +1500,11 @@ hipError_t inv_b(const float2* spec, uint32_t sstride, int logM, size_t C, float
         if (wide_tiles(C, logM) >= kWideInverseB) return inv_b_tiled<LOGN2, 14, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
     return inv_b_tiled<LOGN2, 13, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
 }
-template <int LOGN1, int LOGE, bool HALF>
-hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, bool once, hipStream_t s,
-                        const uint32_t* only_if)
+template <int LOGN1, int LOGE, bool HALF, bool ONCE>
+hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, hipStream_t s, const uint32_t* only_if)
 {
     using G = SplitInverse<LOGN1, LOGE>;
-    const auto kern = once ? k_inv_a_split<LOGN1, LOGE, HALF, true> : k_inv_a_split<LOGN1, LOGE, HALF, false>;
+    const auto kern = k_inv_a_split<LOGN1, LOGE, HALF, ONCE>;
     const hipError_t e = set_lds(kern, G::kLds);
     if (e != hipSuccess) return e;
     const size_t total = C << (logM - LOGE);
@@ -1516,17 +1518,31 @@ hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Ta
 {
     const size_t wide = wide_tiles(C, logM);
     const bool once = passes_by<LOGN1, HALF>(n, from_spectrum);
-    if constexpr (LOGN1 == 9) return inv_a_halved<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
-    if constexpr (LOGN1 == 10) {
-        if (wide < kSplitInverse10) return inv_a_halved<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
-        if constexpr (HALF) return inv_a_halved<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
-        else return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
+    auto persistent = [&](auto size, auto by) {
+        return inv_a_tiled<LOGN1, decltype(size)::value, HALF, decltype(by)::value>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    };
+    auto split = [&](auto size, auto by) {
+        return inv_a_halved<LOGN1, decltype(size)::value, HALF, decltype(by)::value>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
+    };
+    constexpr std::integral_constant<int, 13> small{};
+    constexpr std::integral_constant<int, 14> large{};
+    constexpr std::true_type by{};  // the caches: outputs with at least 2^10 large tiles
+    constexpr std::false_type through{};
+    static_assert(kOnceBytes >> 17 >= kSplitInverse10 && kOnceBytes >> 17 >= kSplitInverse11, "outputs that pass the caches by have large tiles");
+    if constexpr (LOGN1 <= 8) {
+        return once ? persistent(small, by) : persistent(small, through);
+    } else if constexpr (LOGN1 == 9) {
+        return once ? split(small, by) : split(small, through);
+    } else if constexpr (LOGN1 == 10) {
+        if (wide < kSplitInverse10) return split(small, through);
+        return once ? split(large, by) : split(large, through);
+    } else {
+        if (once) return split(large, by);
+        if (wide < kWideInverseA) return persistent(small, through);
+        if constexpr (!HALF)
+            if (wide >= kSplitInverse11) return persistent(large, through);
+        return split(large, through);
     }
-    if constexpr (LOGN1 == 11) {
-        if (wide >= kWideInverseA && (wide < kSplitInverse11<HALF> || (!HALF && wide >= kSplitInverse11Many))) return inv_a_halved<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
-        if (wide >= kWideInverseA) return inv_a_tiled<LOGN1, 14, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
-    }
-    if constexpr (LOGN1 < 9 || LOGN1 == 11) return inv_a_tiled<LOGN1, 13, HALF>(mid, logM, C, out, n, t, aligned, gain, once, s, only_if);
 }
 
 // The tensors come shortest first, so those whose rows or columns ask for the larger tile are the last ones.  Beside shorter

@@ -12,10 +12,12 @@ def dev():
     return Device()
 
 
-# chunks of a call that takes the kernel in question; test_host_launches.py pins which one that is
+# chunks of a call that takes the kernel in question; test_host_launches.py pins which one that is.  The last lines are receivers whose output
+# passes the caches by, against chunks on their own, whose output does not
 @pytest.mark.parametrize("half,log_l,chunks", [
     (0, 16, 512), (0, 18, 70), (0, 19, 40), (0, 20, 31), (0, 20, 32), (0, 21, 10), (0, 22, 4), (0, 22, 14), (0, 22, 22),
     (1, 18, 70), (1, 19, 40), (1, 20, 31), (1, 20, 33), (1, 21, 17), (1, 22, 4), (1, 22, 10),
+    (0, 16, 513), (0, 18, 129), (0, 19, 65), (0, 20, 33), (0, 22, 9), (1, 15, 1025), (1, 16, 513), (1, 18, 129), (1, 19, 65), (1, 22, 9),
 ])
 @pytest.mark.parametrize("short", (0, 8, 1, 6))
 def test_chunks(dev, half, log_l, chunks, short):
