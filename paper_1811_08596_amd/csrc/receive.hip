@@ -106,7 +106,7 @@ template <int LOGN2>
 struct Receive {
     static constexpr int N2 = 1 << LOGN2, LOGT = 4, SLOTS = 1 << LOGT;
     static constexpr int U = LOGN2 >= 10 ? 2 : 1, NT = 2 * N2 / U;  // eights of points of a lane
-    static constexpr int WAVES = 8 / U;  // a SIMD: as many as the LDS leaves
+    static constexpr int WAVES = 8 / U;  // a SIMD: as many as the LDS leaves (rows of 2^7: see receive_b)
     static constexpr int BINS = SLOTS / 2;                         // neighbouring bins of either side of a run
     static constexpr size_t kLds = ((size_t)(SLOTS + 1) << LOGN2) * sizeof(float2);
 };
@@ -392,8 +392,8 @@ __device__ __forceinline__ void receive_pairs(const uint8_t* __restrict__ record
     }
 }
 
-template <int LOGN2, bool HALF, int WIDEST>
-__global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(Receive<LOGN2>::WAVES, Receive<LOGN2>::WAVES))) void k_receive_b(
+template <int LOGN2, bool HALF, int WIDEST, int WAVES>
+__global__ __launch_bounds__(Receive<LOGN2>::NT) __attribute__((amdgpu_waves_per_eu(WAVES, WAVES))) void k_receive_b(
     const uint8_t* __restrict__ records, uint32_t W, uint32_t S, int bits, int m, const uint2* __restrict__ table, int logM,
     typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total, float mid_scale)
 {
@@ -480,12 +480,18 @@ template <int LOGN2, bool HALF, int WIDEST>
 hipError_t receive_b(const uint8_t* records, const CodecArgs& a, int logM, const uint2* table, float2* mid, Tables t, hipStream_t s)
 {
     const size_t total = a.C << (logM - LOGN2 - 4);
-    // Where there is more than a tile to a compute unit (rows of 2^9 and 2^10), or more than its SIMDs hold of receive_tile's.  Whole receivers in
-    // us, receive_tile / receive_pairs, 8-bit codes of half of the bins, by tiles:  2^21 192 38.3 / 41.0, 384 64.9 / 61.2, 1920 255 / 225;  2^22 128 40.0
-    // / 42.5, 256 45.2 / 47.5, 512 78.0 / 72.6, 2048 300 / 277;  2^20 128 22.3 / 22.7, 320 33.3 / 32.7, 640 52.4 / 51.1, 3840 225 / 210;  2^18 1280 46.1 / 47.1 and 45.8
-    // / 45.5, 2560 75.2 / 72.9;  2^17 1280 42.7 / 43.4, 2560 69.5 / 68.8;  2^16 1600 31.6 / 30.8 and 33.9 / 34.5, 2560 47.3 / 44.2 and 43.3 / 46.5,
-    // 4800 67.8 / 64.6, 11200 150 / 144.
-    constexpr size_t kPairsFrom = LOGN2 >= 9 ? 257 : 10 * 256 * 4 * 64 / Receive<LOGN2>::NT + 1;
+    // Whole receivers in us, receive_tile / receive_pairs, 8-bit codes of 40 %, by tiles; binary16 behind a semicolon:
+    //   rows of 2^7 (2^16), receive_tile with eight waves a SIMD, four registers spilled / with six / receive_pairs: 1536 34.6 / 35.2, 2048 36.4 / 37.1 / 37.1; 34.7 / 34.9 /
+    //     36.8, 2560 42.2 / 42.5 / 46.0; 41.6 / 42.4 / 45.5, 3072 45.1 / 45.9 / 46.5; 43.7 / 44.8 / 46.9, 3328 48.7 / 45.5 / 47.0; 44.4 / 45.3 / 47.4, 3584 53.0 / 48.9 / 48.3; 45.7 /
+    //     46.4 / 48.9, 4096 60.6 / 56.6 / 54.7; 51.2 / 50.1 / 51.4, 4352 65.8 / 61.2 / 58.3; 58.2 / 55.7 / 55.5, 6400 90.7 / 83.8 / 80.1; 76.7 / 72.7 / 70.3;
+    //   rows of 2^8 (2^17): 1280 43.6 / 44.9; 42.5 / 45.6, 1920 52.5 / 54.3; 48.5 / 51.9, 2176 59.9 / 59.9; 55.7 / 56.8, 2304 62.1 / 61.0; 56.8 / 57.1, 2560 66.4 / 66.1; 59.9 / 59.3;
+    //     (2^18) 1920 52.3 / 54.8; 46.9 / 49.6, 2176 59.4 / 59.5; 52.6 / 53.6, 2304 61.5 / 60.4; 53.9 / 54.0, 2560 65.8 / 65.4; 58.4 / 57.1;
+    //   rows of 2^9 (2^19): 256 27.0 / 27.0, 384 36.6 / 35.2; 34.2 / 35.0, 640 43.1 / 43.5; 41.2 / 44.1, 1024 58.0 / 55.3; 51.6 / 53.8, 1088 57.3 / 56.5 (binary16), 1536
+    //     82.5 / 77.7; 70.3 / 67.6;  (2^20) 320 36.0 / 35.2; 34.0 / 33.4, 640 45.0 / 44.7; 42.9 / 44.4, 1024 60.0 / 55.7; 55.1 / 55.0, 3840 225 / 210;
+    //   rows of 2^10 (2^21): 256 41.2 / 43.6; 39.7 / 42.2, 320 55.8 / 52.8; 54.1 / 52.8, 1024 115.9 / 103.5; 108.3 / 97.8;  (2^22) 256 46.9 / 48.2; 44.1 / 45.3, 384 63.2 / 59.1;
+    //     59.8 / 58.2.
+    constexpr size_t kPairsFrom = LOGN2 == 7 ? (HALF ? 4224 : 3584) : LOGN2 == 8 ? (HALF ? 2305 : 2177) : LOGN2 == 9 && HALF ? 1025 : 257;
+    constexpr size_t kSixWavesFrom = HALF ? 3840 : 2561;  // rows of 2^7
     auto launch = [&](auto kern, unsigned lanes, size_t lds) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -493,8 +499,11 @@ hipError_t receive_b(const uint8_t* records, const CodecArgs& a, int logM, const
                      a.bits, a.m, table, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, (uint32_t)total, HALF ? 1.0f / half_lift(logM) : 1.0f);
         return hipGetLastError();
     };
-    return total >= kPairsFrom ? launch(k_receive_pairs<LOGN2, HALF, WIDEST>, HalfTile<LOGN2>::NT, HalfTile<LOGN2>::kLds)
-                               : launch(k_receive_b<LOGN2, HALF, WIDEST>, Receive<LOGN2>::NT, Receive<LOGN2>::kLds);
+    using G = Receive<LOGN2>;
+    if (total >= kPairsFrom) return launch(k_receive_pairs<LOGN2, HALF, WIDEST>, HalfTile<LOGN2>::NT, HalfTile<LOGN2>::kLds);
+    if constexpr (LOGN2 == 7)
+        if (total >= kSixWavesFrom) return launch(k_receive_b<LOGN2, HALF, WIDEST, 6>, G::NT, G::kLds);
+    return launch(k_receive_b<LOGN2, HALF, WIDEST, G::WAVES>, G::NT, G::kLds);
 }
 template <int LOGN2>
 hipError_t receive_rows(const uint8_t* records, const CodecArgs& a, int logM, const uint2* table, float2* mid, Tables t, hipStream_t s)

@@ -47,7 +47,7 @@ def test_receiver_and_the_spectrum_it_leaves_out(dev, logL, bits):
 @pytest.mark.parametrize("half", (0, 1))
 @pytest.mark.parametrize("bits", (8, 15))
 def test_chunks_of_2_to_the_16_on_either_side_of_the_wave_count(dev, bits, half):
-    """161 chunks take the kernel of long launches, their first 160 by themselves the one of short ones."""
+    """161 chunks of binary32 take the kernel with six waves a SIMD, their first 160 by themselves the one with eight."""
     torch, f, L = dev.torch, dev.f, 1 << 16
     g = torch.randn(161 * L, device="cuda", generator=torch.Generator(device="cuda").manual_seed(bits)) * 1e-2
     outs = []

@@ -12,9 +12,9 @@ def dev():
     return Device()
 
 
-def first_long(log_l):
+def first_long(log_l, half):
     rows = (log_l - 1) // 2
-    tiles = {7: 2561, 8: 1281}.get(rows, 257)
+    tiles = {7: (3584, 4224), 8: (2177, 2305), 9: (257, 1025), 10: (257, 257)}[rows][half]
     return -(-tiles // (1 << (log_l - 1 - rows - 4)))
 
 
@@ -23,7 +23,7 @@ def first_long(log_l):
 @pytest.mark.parametrize("log_l", (16, 17, 18, 19, 20, 21, 22))
 def test_chunks(dev, log_l, theta, bits, half):
     torch, f, L = dev.torch, dev.f, 1 << log_l
-    most = first_long(log_l)
+    most = first_long(log_l, half)
     print(f"2^{log_l} theta={theta} bits={bits} half={half} chunks={most}", flush=True)
     g = torch.randn(most * L, device="cuda", generator=torch.Generator(device="cuda").manual_seed(log_l)) * 1e-2
     outs = []

@@ -203,6 +203,19 @@ def test_first_passes_with_half_of_the_lds(runtime, tmp_path, logL, half, C, for
     assert any("k_inv_a_split" in k for k in receiver) == inverse
 
 
+# tiles of a receiver's second pass: chunks of 2^16 hold 16 of them (rows of 2^7), of 2^17 and 2^18 16 and 32 (2^8), of 2^19 and 2^20 32 and 64 (2^9)
+@pytest.mark.parametrize("logL, half, C, kernel", [
+    (16, 0, 160, "b"), (16, 0, 161, "six"), (16, 0, 223, "six"), (16, 0, 224, "pairs"), (16, 1, 239, "b"), (16, 1, 240, "six"), (16, 1, 263, "six"), (16, 1, 264, "pairs"),
+    (17, 0, 136, "b"), (17, 0, 137, "pairs"), (18, 0, 68, "b"), (18, 0, 69, "pairs"), (17, 1, 144, "b"), (17, 1, 145, "pairs"), (18, 1, 72, "b"), (18, 1, 73, "pairs"),
+    (19, 0, 20, "pairs"), (19, 1, 32, "b"), (19, 1, 33, "pairs"), (20, 0, 5, "pairs"), (20, 1, 16, "b"), (20, 1, 17, "pairs"),
+    (21, 0, 4, "b"), (21, 0, 5, "pairs"), (21, 1, 5, "pairs"), (22, 1, 3, "pairs")])
+def test_receivers_take_half_of_the_lds_where_it_pays(runtime, tmp_path, logL, half, C, kernel):
+    n, L = C << logL, 1 << logL
+    made, = kernels(runtime, tmp_path, [["fftsp_decompress_h", ["big", "big", "big", n, L, 0.5, 8, 0, "big", "big", None]] if half else decompress(n, L)])
+    second, = [k for k in made if "k_receive" in k]
+    assert kernel == ("pairs" if "k_receive_pairs" in second else "six" if "ELi6EE" in second else "b")
+
+
 def test_every_form_of_the_inverse_first_pass_is_reached(runtime, tmp_path):
     """The forms that the library has are those that receivers of all lengths launch."""
     calls = []
