@@ -1406,8 +1406,10 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, ResolveArgs a, uin
 // k_collect: one by one, calls of 100 to 450 tiles of 2^14 points lost 3 to 12 us (13 tensors 183 -> 195, so 186; 29 186 -> 196, so 187; 42 275 -> 281,
 // so 270).  Below kEmitBackwards tiles of 16 KB the first ones are still there, and the order stays.
 constexpr uint32_t kEmitBackwards = 4096;
+// tiles from the first on whose order is reversed, a multiple of eight; an argument, since asking for the launch's size cost every launch 0.5 us
+inline uint32_t emit_reversed(uint32_t tiles) { return tiles >= kEmitBackwards ? tiles & ~7u : 0u; }
 template <bool TABLE, bool REAL, bool HALF, bool MERGED>
-__global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u, ResolveArgs a,
+__global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::T* __restrict__ spec, Shape u, uint32_t reversed, ResolveArgs a,
                                              uint32_t* __restrict__ sel, uint32_t* __restrict__ tscan,
                                              const uint32_t* __restrict__ tinfo, const uint2* __restrict__ cand,
                                              uint8_t* __restrict__ records, uint8_t* __restrict__ stream, HeaderInfo hdr,
@@ -1420,9 +1422,7 @@ __global__ __launch_bounds__(NT) void k_emit(const typename Stored<REAL, HALF>::
     __shared__ __align__(16) uint64_t bmw[kTile / 64];
     __shared__ uint32_t weq[4], wfl[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t whole = gridDim.x & ~7u;
-    const bool backwards = !MERGED && gridDim.x >= kEmitBackwards && blockIdx.x < whole;
-    const uint32_t nth = backwards ? whole - 8u - (blockIdx.x & ~7u) + (blockIdx.x & 7u) : blockIdx.x;  // which tile of the launch
+    const uint32_t nth = !MERGED && blockIdx.x < reversed ? reversed - 8u - (blockIdx.x & ~7u) + (blockIdx.x & 7u) : blockIdx.x;  // which tile of the launch
     const Place at = place_of_tile<TABLE>(u, tab, nth);
     const uint32_t c = at.chunk, tile = at.tile, B = at.B, W = at.W;
     const size_t S = at.S;
@@ -2368,7 +2368,7 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
     const hipError_t e = a.tab ? select(std::true_type{}) : select(std::false_type{});
     if (e != hipSuccess) return e;
 #define FFTSP_EMIT_AS(TABLE, REAL, HALF, MERGED, src, lds)                                                                          \
-    FFTSP_LAUNCH("emit", (k_emit<TABLE, REAL, HALF, MERGED>), per_tile, dim3(NT), lds, s, src, u, ra, sel, tscan, tinfo, cand, records, \
+    FFTSP_LAUNCH("emit", (k_emit<TABLE, REAL, HALF, MERGED>), per_tile, dim3(NT), lds, s, src, u, emit_reversed(per_tile.x), ra, sel, tscan, tinfo, cand, records, \
                  stream_base, h, table_arg<TABLE>(a.tab), a.n)
 #define FFTSP_EMIT(TABLE, REAL, HALF, src)                              \
     if (merged)                                                         \
