@@ -1468,12 +1468,18 @@ hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, si
 
 // Binary16 storage, rows of 2^8 and more: half the LDS per tile and a workgroup for each.  Whole calls in us, theta 0.3, 8 bits, fwd_b_tiled / this:
 //   2^17 10 M samples 112 / 108.6, 42 M 287 / 278;  2^18 118.8 / 115.3, 275 / 264;  2^19 129 / 126, 303 / 294;  2^20 134 / 131, 62 M 442.5 / 434.5 (this
-//   kernel 99 / 80);  2^21 25 M 227.5 / 227, 62 M 482.7 / 467.8;  2^22 33 M 302 / 297.6, 138 M 1119 / 1081;  2^16 45 M 306.7 / 311.8.
+//   kernel 99 / 80);  2^21 25 M 227.5 / 227, 62 M 482.7 / 467.8;  2^22 33 M 302 / 297.6, 138 M 1119 / 1081;  2^16 45 M 306.7 / 311.8.  Senders, by tiles of 2^14: rows of
+//   2^10, a workgroup a compute unit either way up to 256 of them, 128 (2^21) 54.9 / 57.1 and (2^22) 63.7 / 65.7, 192 65.0 / 65.1, 256 66.7 / 66.3 and 78.3 / 78.1, 384 86.3 /
+//   83.5;  shorter rows from the first launches on that are not the short kernels': 2^17 128 42.4 / 41.0, 2^18 72 38.2 / 36.2, 2^19 128 45.0 / 44.5, 2^20 128 48.4 / 48.7, 192 55.9 /
+//   54.7.
 // Binary32 bins keep their persistent workgroups, which have a tile's loads on their way while they work on another: 2^16 45 M 364 / 381, 2^20 42 M
 // 357 / 362.7, 2^22 67 M 661 / 674.
+constexpr size_t kPairsForward10 = 192;  // tiles of 2^14 from which rows of 2^10 take it
 template <int LOGN2>
 hipError_t fwd_b_half(const float2* mid, int logM, size_t C, float2* spec, uint32_t sstride, Tables t, uint32_t* hist, float mid_scale, hipStream_t s)
 {
+    if constexpr (LOGN2 == 10)
+        if (wide_tiles(C, logM) < kPairsForward10) return fwd_b_tiled<LOGN2, 14, true, true>(mid, logM, C, spec, sstride, t, hist, mid_scale, s, nullptr);
     constexpr size_t lds = HalfTile<LOGN2>::kLds + kHistLdsWords * sizeof(uint32_t);
     const auto kern = k_fwd_b_pairs<LOGN2, true>;
     const hipError_t e = set_lds(kern, lds);

@@ -203,6 +203,14 @@ def test_first_passes_with_half_of_the_lds(runtime, tmp_path, logL, half, C, for
     assert any("k_inv_a_split" in k for k in receiver) == inverse
 
 
+@pytest.mark.parametrize("logL, C, kernel", [(17, 24, "short"), (17, 32, "pairs"), (20, 4, "pairs"), (21, 1, "short"), (21, 2, "k_fwd_bI"), (21, 3, "pairs"),
+                                             (22, 1, "k_fwd_bI"), (22, 2, "pairs"), (16, 64, "k_fwd_bI")])
+def test_binary16_senders_take_half_of_the_lds_where_it_pays(runtime, tmp_path, logL, C, kernel):
+    made, = kernels(runtime, tmp_path, [["fftsp_compress_h", ["big", C << logL, 1 << logL, 0.5, 8, 0, "big", "big", "big", "big", None]]])
+    second, = [k for k in made if "k_fwd_b" in k]
+    assert kernel in second
+
+
 # tiles of a receiver's second pass: chunks of 2^16 hold 16 of them (rows of 2^7), of 2^17 and 2^18 16 and 32 (2^8), of 2^19 and 2^20 32 and 64 (2^9)
 @pytest.mark.parametrize("logL, half, C, kernel", [
     (16, 0, 160, "b"), (16, 0, 161, "six"), (16, 0, 223, "six"), (16, 0, 224, "pairs"), (16, 1, 239, "b"), (16, 1, 240, "six"), (16, 1, 263, "six"), (16, 1, 264, "pairs"),
