@@ -1086,6 +1086,28 @@ struct SplitInverse {
         }
     }
 };
+// Four, or two, neighbouring samples wherever they start, those that are there: most tensors start at any multiple of four bytes.  One instruction, since
+// lanes that store a float at a time touch every line many times (receivers: 37 tensors of up to 4 M samples 101.5 -> 90.9 us, 33 of up to 1.7 M 71.3 -> 67.3,
+// 66 of up to 2.4 M 105.7 -> 101.4).
+__device__ __forceinline__ void store_floats(float* __restrict__ out, size_t gi, size_t limit, float4 z)
+{
+    using F4 = float __attribute__((ext_vector_type(4), aligned(4)));
+    if (gi + 4 <= limit) {
+        *reinterpret_cast<F4*>(out + gi) = F4{z.x, z.y, z.z, z.w};
+    } else {
+        if (gi < limit) out[gi] = z.x;
+        if (gi + 1 < limit) out[gi + 1] = z.y;
+        if (gi + 2 < limit) out[gi + 2] = z.z;
+    }
+}
+__device__ __forceinline__ void store_floats(float* __restrict__ out, size_t gi, size_t limit, float2 z)
+{
+    using F2 = float __attribute__((ext_vector_type(2), aligned(4)));
+    if (gi + 2 <= limit)
+        *reinterpret_cast<F2*>(out + gi) = F2{z.x, z.y};
+    else if (gi < limit)
+        out[gi] = z.x;
+}
 // TOP: 2^(TOP - LOGE) tiles beside each other, each with words d of its own, share the stage twiddles
 template <int LOGN1, int LOGE, bool HALF, bool ONCE, int TOP = LOGE>
 __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __restrict__ mid, int logM, float* __restrict__ out, const Span& sp, bool quads,
@@ -1157,7 +1179,7 @@ __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __rest
             const uint32_t i = (uint32_t)((tid >> LOGT) + n * (N1 / 16)) * N2 + col0 + (uint32_t)b;
             const float2 z = make_float2(v[n].x * scale, v[n].y * scale);
             if (!quads)
-                store_pair(out, sp.first + 2 * (size_t)i, sp.limit, sp.pairs, z);
+                store_floats(out, sp.first + 2 * (size_t)i, sp.limit, z);
             else if (i < 2 * end)
                 dst[i] = z;
         }
@@ -1189,8 +1211,7 @@ __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __rest
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const size_t gi = sp.first + 2 * ((size_t)(j2 + t * (N1 / 8)) * N2 + col0 + 2 * bp);
-            store_pair(out, gi, sp.limit, sp.pairs, make_float2(v[t].x * scale, v[t].y * scale));
-            store_pair(out, gi + 2, sp.limit, sp.pairs, make_float2(v[8 + t].x * scale, v[8 + t].y * scale));
+            store_floats(out, gi, sp.limit, make_float4(v[t].x * scale, v[t].y * scale, v[8 + t].x * scale, v[8 + t].y * scale));
         }
     }
 }
