@@ -15,6 +15,7 @@
 // (pbase) of Algorithm 1.  A last pass flags, ranks (wave ballots + popcounts),
 // quantizes and bit-packs.
 #include "codec_core.h"
+#include "sample.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -355,8 +356,8 @@ __device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, b
 // The sample: 2^11 stretches of sixteen neighbours, one from each 2^11-th of the chunk, at a place in it that a hash of its number says,
 // so that no period of the gradient's layout is met again and again.  Neighbours are alike in a gradient, so how far the sample's ranks are off
 // is taken from the stretches: half the squared differences between one's count above the estimate and the next one's, which is what independent
-// samples' ranks vary by too where there is no likeness.  Five and a half of these standard deviations either side: 46 candidates to a tile of 2048
-// at 15 % kept, where a bucket of the histogram has 10 to 40.
+// samples' ranks vary by too where there is no likeness (sample_variance).  Five and a half of these standard deviations either side: 46 candidates to a
+// tile of 2048 at 15 % kept, where a bucket of the histogram has 10 to 40.
 //
 // Zeros are never candidates: a gradient can be half zeros (a rectifier's), and a window that reached them would have k_collect write most of
 // the chunk.  Where the window's lower end is the smallest key above zero and the candidates do not have the threshold, it is zero.
@@ -364,10 +365,8 @@ __device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, b
 // Bound by latency: one trip to memory, behind what the call before has left to write, and the barriers of three scans.  Sixty chunks of 2^20:
 // 16 us, where clearing the histograms, counting 62 M samples and finding the buckets took 83; k_collect, which then is the first to read the
 // gradient, 42 -> 64, k_resolve 21 -> 27.
-constexpr int kSampleLanes = 1024, kSampleLoads = 8, kSampleStretches = kSampleLanes / 4 * kSampleLoads;
-constexpr uint32_t kSamples = 16u * kSampleStretches;
-// where stretch g lies among the `slots` (a power of two) of its part
-__host__ __device__ constexpr uint32_t sample_slot(uint32_t g, uint32_t slots) { return (g * 2654435761u >> 15) & (slots - 1u); }
+constexpr int kSampleLanes = 1024, kSampleLoads = 8;
+static_assert(kSampleLanes / 4 * kSampleLoads == kSampleStretches, "a load is a quarter of a stretch");
 __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict__ in, uint32_t L, uint32_t k, size_t n, uint32_t* __restrict__ sel,
                                                         uint32_t* __restrict__ ctl)
 {
@@ -479,7 +478,7 @@ __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict
     above = wave_sum(lane < NW ? sums[1][lane] : 0u);
     off = wave_sum(lane < NW ? sums[2][lane] : 0u);
     // half of the differences, each seen by four lanes, and three of them to four stretches
-    const float likely = sqrtf(fmaxf((float)off * (0.5f / 4.f * 4.f / 3.f), share * (1.f - share) * kSamples)), wide = 5.5f * likely + 4.f;
+    const float wide = 5.5f * sqrtf(sample_variance((float)off * (0.5f / 4.f * 4.f / 3.f), k, L, present)) + sample_margin(L, present);
     const float at = share * kSamples;
     const uint32_t r0 = clamped(at - wide, kSamples), r1 = clamped(at + wide, kSamples), digit = (uint32_t)(kHist2Bins - 1 - tid);
     const uint32_t cnt = fine[digit], run = above + before(cnt, sums[0]), end = run + cnt;
@@ -854,7 +853,8 @@ __device__ __forceinline__ Digit find_digit(const uint32_t* h, uint32_t need, in
 }
 
 // The threshold of a chunk of samples from the samples themselves, where the candidates do not have it: ten bits at a time, then every tile's
-// samples above it and equal to it.  Slow, and all but never needed: see k_sample.
+// samples above it and equal to it.  All but never needed (see k_sample), and slow, one workgroup reading the chunk five times: a sender of 62 M samples whose
+// sample misleads in one of sixty chunks of 2^20, or in all of them, takes 900 to 1080 us instead of 135, one of 20 M in chunks of 2^18 330 instead of 59.
 template <int LANES>
 __device__ __forceinline__ Digit select_samples(const float* __restrict__ X, uint32_t present, uint32_t L, uint32_t Tn, uint32_t need,
                                                           uint32_t* h, uint32_t* tgt, uint32_t* teq, uint32_t& vm)
@@ -2250,11 +2250,6 @@ static bool resolve_in_emit(const Extent& x, int time_domain)
 {
     return x.most <= kMergedTiles && x.tiles <= (time_domain && x.most > 32 ? 256 : 512);
 }
-// k_sample instead of the histogram.  Shorter chunks would have half or a quarter of their samples looked at, longer ones have more tiles than
-// k_resolve holds the summaries of.  Sender and receiver in us, 8-bit codes of 20 %, histogram / sample:  2^18 6 M samples 47.7 / 49.3, 8 M 53.9 /
-// 53.8, 10 M 76.7 / 67.7, 18 M 104 / 84;  2^19 6 M 54.3 / 56.3, 8 M 61.3 / 67.3, 10 M 85.9 / 74.0, 18 M 107 / 94;  2^20 6 M 59.3 / 62.2, 8 M 67.5 / 66.4, 10 M
-// 76.7 / 74.6, 18 M 147 / 127;  62 M, 15 % kept at 32 bits 2^20 253 / 219, 85 % at 8 bits 2^18 276 / 239;  2^16, 30 % at 32 bits 251 / 258.
-static bool sampled(uint32_t chunk_tiles, size_t tiles) { return chunk_tiles >= 128 && chunk_tiles <= kKeptTiles && tiles > 4096; }
 // In k_decode it is the bitmap up to the tile, at most 256 bytes for each tile of the chunk, to read beside the tile's codes.
 // Decompress: one chunk of 2^16 21.7 -> 17.7 us, 2^23 samples in chunks of 2^20 (2056 tiles) 49.4 -> 48.8, 2^24 76.6 -> 77.8, one
 // chunk of 2^22 (1025 tiles) 50.3 -> 52.5.  Chunks of a few tiles always: Top-k of 2^24 samples in chunks of 2^12 32.8 -> 16.2.
@@ -2278,7 +2273,7 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
     if (a.half && (a.tab || a.time_domain || !a.pair_log || !hist_ready)) return hipErrorInvalidValue;
     if (a.tab && !hist_ready) return hipErrorInvalidValue;
 
-    const bool window = a.time_domain && sampled(u.Tn, x.tiles);
+    const bool window = a.time_domain && sampled(u.Tn, x.tiles, a.n % a.L == 0);
     if (window) {
         FFTSP_LAUNCH("sample", k_sample, dim3((unsigned)a.C), dim3(kSampleLanes), 0, s, spec, a.L, a.k, a.n, sel,
                      reinterpret_cast<uint32_t*>(ws_base + w.status));
