@@ -353,20 +353,24 @@ __device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, b
 // candidates, and k_resolve, which knows how many are above, sees whether the k-th largest is among the candidates.  Where it is not, it selects
 // from the samples themselves (select_samples): the result is exact whatever was sampled.
 //
-// The sample: 2^11 stretches of sixteen neighbours, one from each 2^11-th of the chunk, at a place in it that a hash of its number says,
+// The sample: 2^12 stretches of eight neighbours, one from each 2^12-th of the chunk, at a place in it that a hash of its number says,
 // so that no period of the gradient's layout is met again and again.  Neighbours are alike in a gradient, so how far the sample's ranks are off
 // is taken from the stretches: half the squared differences between one's count above the estimate and the next one's, which is what independent
-// samples' ranks vary by too where there is no likeness (sample_variance).  Five and a half of these standard deviations either side: 46 candidates to a
-// tile of 2048 at 15 % kept, where a bucket of the histogram has 10 to 40.
+// samples' ranks vary by too where there is no likeness (sample_variance).  Four and a half of these standard deviations either side: 38 candidates to a
+// tile of 2048 at 15 % kept, where a bucket of the histogram has 10 to 40, and one chunk in 150000 whose threshold lies outside.
+// Stretches of sixteen are read faster, but are more alike within, and more than 128 candidates to a tile are slow.  Senders of 62 M samples in chunks of 2^20, 15 %
+// kept, sixteen with five and a half deviations / this / histogram: independent 133.7 / 134.6 / 165.9, rows of 1024 with a scale each 153.6 / 133.8 / 165.8, of 64
+// 166.2 / 143.9 / 166.9, autoregressive (0.9) 146.8 / 142.5 / 170.4, 8-bit floats 338.4 / 289.3 / 310.8 (of which one value for a crowd 22), half of a sine 351 / 191 / 224.  Stretches of
+// four: 144 where those of eight took 135.
 //
 // Zeros are never candidates: a gradient can be half zeros (a rectifier's), and a window that reached them would have k_collect write most of
 // the chunk.  Where the window's lower end is the smallest key above zero and the candidates do not have the threshold, it is zero.
 //
 // Bound by latency: one trip to memory, behind what the call before has left to write, and the barriers of three scans.  Sixty chunks of 2^20:
-// 16 us, where clearing the histograms, counting 62 M samples and finding the buckets took 83; k_collect, which then is the first to read the
+// 19 us, where clearing the histograms, counting 62 M samples and finding the buckets took 83; k_collect, which then is the first to read the
 // gradient, 42 -> 64, k_resolve 21 -> 27.
 constexpr int kSampleLanes = 1024, kSampleLoads = 8;
-static_assert(kSampleLanes / 4 * kSampleLoads == kSampleStretches, "a load is a quarter of a stretch");
+static_assert(kSampleLanes / 2 * kSampleLoads == kSampleStretches && kStretch == 8, "a lane's load is half of a stretch");
 __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict__ in, uint32_t L, uint32_t k, size_t n, uint32_t* __restrict__ sel,
                                                         uint32_t* __restrict__ ctl)
 {
@@ -385,7 +389,7 @@ __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict
     uint32_t key[4 * kSampleLoads];
 #pragma unroll
     for (int j = 0; j < kSampleLoads; ++j) {
-        const uint32_t g = (uint32_t)(j * (kSampleLanes / 4) + (tid >> 2)), at = 16u * (g * slots + sample_slot(g, slots)) + 4u * ((uint32_t)tid & 3u);
+        const uint32_t g = (uint32_t)(j * (kSampleLanes / 2) + (tid >> 1)), at = kStretch * (g * slots + sample_slot(g, slots)) + 4u * ((uint32_t)tid & 1u);
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (at + 4u <= present) {
             v = *reinterpret_cast<const float4*>(X + at);
@@ -463,9 +467,8 @@ __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict
             else if (d <= range)
                 atomicAdd(&fine[d >> shift], 1u);
         }
-        in += __builtin_amdgcn_mov_dpp(in, 0xB1, 0xF, 0xF, false);  // of the four lanes of a stretch
-        in += __builtin_amdgcn_mov_dpp(in, 0x4E, 0xF, 0xF, false);
-        const int next = __builtin_amdgcn_update_dpp(in, in, 0x104, 0xF, 0xF, false);  // four lanes on; itself in a row's last four
+        in += __builtin_amdgcn_mov_dpp(in, 0xB1, 0xF, 0xF, false);                      // of the two lanes of a stretch
+        const int next = __builtin_amdgcn_update_dpp(in, in, 0x102, 0xF, 0xF, false);  // two lanes on; itself in a row's last two
         off += (uint32_t)((next - in) * (next - in));
     }
     above = wave_sum(above);
@@ -477,8 +480,8 @@ __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict
     __syncthreads();
     above = wave_sum(lane < NW ? sums[1][lane] : 0u);
     off = wave_sum(lane < NW ? sums[2][lane] : 0u);
-    // half of the differences, each seen by four lanes, and three of them to four stretches
-    const float wide = 5.5f * sqrtf(sample_variance((float)off * (0.5f / 4.f * 4.f / 3.f), k, L, present)) + sample_margin(L, present);
+    // half of the differences, each seen by two lanes, and seven of them to eight stretches
+    const float wide = kSampleDeviations * sqrtf(sample_variance((float)off * (0.5f / 2.f * 8.f / 7.f), k, L, present)) + sample_margin(L, present);
     const float at = share * kSamples;
     const uint32_t r0 = clamped(at - wide, kSamples), r1 = clamped(at + wide, kSamples), digit = (uint32_t)(kHist2Bins - 1 - tid);
     const uint32_t cnt = fine[digit], run = above + before(cnt, sums[0]), end = run + cnt;
@@ -1245,7 +1248,22 @@ __device__ __forceinline__ Threshold resolve_chunk(const Place& at, const Resolv
         __syncthreads();
     } else if (any) {
         if constexpr (WINDOW) {
-            for (int top = low; top > 0;) {  // the rest of the bits, ten at a time
+            // Crowds are most often one value: a gradient on a grid, of 8 bits once.  Then it is known, and otherwise its bits are found, ten at a time.
+            uint32_t least = 0, most = 0;  // least: of the complements
+            every_row([&](uint32_t, uint32_t x, bool valid, uint32_t) __attribute__((always_inline)) {
+                const bool in = valid && (int)(rel(x) >> low) == prefix;
+                most = in && rel(x) > most ? rel(x) : most;
+                least = in && ~rel(x) > least ? ~rel(x) : least;
+            });
+            least = wave_max(least);
+            most = wave_max(most);
+            if (lane == 0) lds.sums[wave] = make_uint2(least, most);
+            __syncthreads();
+            const uint2 v = lane < NW ? lds.sums[lane] : make_uint2(0u, 0u);
+            most = wave_max(v.y);
+            const bool one = most == ~wave_max(v.x);
+            if (one) tau = most;
+            for (int top = one ? 0 : low; top > 0;) {
                 const int shift = top > kHist2Bits ? top - kHist2Bits : 0;
                 __syncthreads();
                 for (int i = tid; i < kHist2Bins; i += LANES) h[i] = 0u;

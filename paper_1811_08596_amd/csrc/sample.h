@@ -5,7 +5,8 @@
 
 namespace fftsp {
 
-constexpr uint32_t kSampleStretches = 2048, kSamples = 16u * kSampleStretches;
+constexpr uint32_t kSampleStretches = 4096, kStretch = 8, kSamples = kStretch * kSampleStretches;
+constexpr float kSampleDeviations = 4.5f;  // of the threshold's rank that are looked at, either side
 // where stretch g lies among the `slots` (a power of two) of its part
 constexpr uint32_t sample_slot(uint32_t g, uint32_t slots) { return (g * 2654435761u >> 15) & (slots - 1u); }
 
@@ -19,15 +20,17 @@ constexpr float sample_variance(float differences, uint32_t k, uint32_t L, uint3
 }
 
 // and how far it can be off whatever the gradient is: a stretch at the gradient's end is in the sample or not
-constexpr float sample_margin(uint32_t L, uint32_t present) { return present < L ? 20.f : 4.f; }
+constexpr float sample_margin(uint32_t L, uint32_t present) { return present < L ? 4.f + (float)kStretch : 4.f; }
 
 // Chunks of chunk_tiles tiles in a call of `tiles` of them; whole: the last one is full.
 // Shorter chunks would have half or a quarter of their samples looked at, longer ones have more tiles than k_resolve holds the summaries of.
-// Whole calls in us, histogram / sample, full chunks: 2^18 4224 tiles 50.4 / 51.8, 5888 59.6 / 61.4, 6656 66.8 / 67.3, 7680 75.0 / 73.4, 10240 89.9 / 84.6;  2^19 5888 63.6 /
-// 65.1, 6656 69.7 / 70.4, 7680 78.5 / 76.9, 8960 86.1 / 83.8;  2^20 5120 65.8 / 67.1, 6144 72.3 / 74.0, 7168 81.0 / 80.9, 8192 87.2 / 87.3, 10240 100.0 / 96.3, 62 M samples 253 / 219.
+// Whole calls in us, 15 % kept at 32 bits, histogram / sample.  Full chunks: 2^18 7680 tiles 75.1 / 75.9, 10240 88.8 / 86.6;  2^19 7680 76.9 / 79.7, 10240 91.7 / 91.5;  2^20
+// 8192 87.3 / 90.8, 10240 97.9 / 98.9, 15360 135.6 / 128.6, 20480 168.4 / 153.6.
 // Where the last one is not, its zeros queue for one counter of the histogram, and are candidates where more is kept than there is: 2^20, nine chunks, the
-// last 2, 5, 10, 16, 20, 30, 40, 50, 70, 90 % full, 126 / 66, 99 / 66, 98 / 66, 63 / 66, 71 / 69, 63 / 66, 69 / 64, 62 / 64, 73 / 64, 71 / 64; 2^18, forty, 73 / 58, 81 / 58, 77 /
-// 58, 65 / 58, 56 / 59, 65 / 58, 60 / 57, 55 / 57, 57 / 57, 59 / 57.
-constexpr bool sampled(uint32_t chunk_tiles, size_t tiles, bool whole) { return chunk_tiles >= 128 && chunk_tiles <= 513 && tiles > (whole ? 7168u : 4096u); }
+// last 2, 5, 10, 16, 20, 30, 40, 50, 70, 90 % full, 126 / 65, 99 / 65, 99 / 65, 63 / 66, 71 / 68, 63 / 65, 70 / 65, 62 / 65, 72 / 65, 72 / 66; 2^19, twenty, 84 / 63, 86 / 62, 77 /
+// 61, 60 / 63, 62 / 64, 68 / 64, 70 / 62, 60 / 62, 62 / 61, 71 / 62; 2^18, forty, 73 / 58, 81 / 58, 76 / 57, 62 / 59, 55 / 59, 67 / 59, 61 / 59, 56 / 59, 56 / 57, 60 / 59.
+// Neighbours that are alike make the window wider.  Senders, rows of 64 with a scale each: 2^18 8.6 M 49.5 / 42.4, 2^19 9.1 M 47.7 / 52.4, 20.2 M 72.8 / 63.8, 2^20 8.9 M 50.6 / 67.2,
+// 12.4 M 67.6 / 60.8, 30.3 M 96.4 / 85.6; rows of 1024: 2^20 8.9 M 50.7 / 55.5, 12.4 M 68.7 / 57.4; 8-bit floats: 2^18 8.6 M 95.8 / 83.9, 2^20 12.4 M 170.8 / 178.0, 40.3 M 244.0 / 234.4.
+constexpr bool sampled(uint32_t chunk_tiles, size_t tiles, bool whole) { return chunk_tiles >= 128 && chunk_tiles <= 513 && tiles > (whole ? 10240u : 4096u); }
 
 }  // namespace fftsp

@@ -8,7 +8,7 @@ from paper_1811_08596_amd import workloads
 from tests.gpu_harness import Device
 
 pytestmark = pytest.mark.gpu
-STRETCHES = 2048
+STRETCHES, LONG = 4096, 8
 
 
 @pytest.fixture(scope="module")
@@ -17,9 +17,9 @@ def dev():
 
 
 def sampled(L):
-    g, slots = np.arange(STRETCHES, dtype=np.uint64), L // (16 * STRETCHES)
+    g, slots = np.arange(STRETCHES, dtype=np.uint64), L // (LONG * STRETCHES)
     at = g * slots + ((g * 2654435761 & 0xFFFFFFFF) >> 15 & (slots - 1))
-    return (16 * at[:, None] + np.arange(16, dtype=np.uint64)).astype(np.int64).ravel()
+    return (LONG * at[:, None] + np.arange(LONG, dtype=np.uint64)).astype(np.int64).ravel()
 
 
 def check(dev, ref, g, L, theta, bits):

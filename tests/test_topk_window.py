@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from paper_1811_08596_amd import workloads
-from tests.test_gpu_topk_sampled import STRETCHES, misleading, sampled, with_zeros
+from tests.test_gpu_topk_sampled import LONG, STRETCHES, misleading, sampled, with_zeros
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = r"""
@@ -19,6 +19,7 @@ extern "C" float variance(float d, uint32_t k, uint32_t L, uint32_t present) { r
 extern "C" float margin(uint32_t L, uint32_t present) { return fftsp::sample_margin(L, present); }
 extern "C" int takes(uint32_t chunk_tiles, size_t tiles, int whole) { return fftsp::sampled(chunk_tiles, tiles, whole); }
 extern "C" uint32_t samples(void) { return fftsp::kSamples; }
+extern "C" float deviations(void) { return fftsp::kSampleDeviations; }
 """
 
 
@@ -28,10 +29,10 @@ def lib(tmp_path_factory):
     (d / "sample.cpp").write_text(SOURCE % ROOT)
     subprocess.run(["g++", "-O2", "-ffp-contract=off", "-shared", "-fPIC", "-std=c++17", "-o", str(d / "sample.so"), str(d / "sample.cpp")], check=True)
     s = ctypes.CDLL(str(d / "sample.so"))
-    s.variance.restype = s.margin.restype = ctypes.c_float
+    s.variance.restype = s.margin.restype = s.deviations.restype = ctypes.c_float
     s.variance.argtypes = [ctypes.c_float] + [ctypes.c_uint32] * 3
     s.takes.argtypes = [ctypes.c_uint32, ctypes.c_size_t, ctypes.c_int]
-    assert s.samples() == 16 * STRETCHES
+    assert s.samples() == LONG * STRETCHES
     return s
 
 
@@ -50,10 +51,10 @@ def window(lib, X, k, present):
     """The two keys between which k_sample has candidates lie, of a chunk with its padding."""
     f, L = np.float32, len(X)
     S = lib.samples()
-    keys = keys_of(X[sampled(L)]).reshape(STRETCHES, 16)
+    keys = keys_of(X[sampled(L)]).reshape(STRETCHES, LONG)
     share = f(k) / f(L)
     # a quarter by its top twelve bits: of four neighbours one, another one in every eighth of the stretches
-    quarter = keys.reshape(STRETCHES, 4, 4)[np.arange(STRETCHES), :, (np.arange(STRETCHES) // (STRETCHES // 8)) & 3].ravel()
+    quarter = keys.reshape(STRETCHES, LONG // 4, 4)[np.arange(STRETCHES), :, (np.arange(STRETCHES) // (STRETCHES // 8)) & 3].ravel()
     coarse, few = np.bincount(quarter >> 19, minlength=4096), S // 4
     at, wide = share * f(few), f(20) * np.sqrt(share * (f(1) - share) * f(few)) + f(20)
     clamp = lambda r, most: int(min(max(r, 1), most))
@@ -62,9 +63,9 @@ def window(lib, X, k, present):
     shift = extent.bit_length() - 10
     d = keys.ravel() - base
     fine, above = np.bincount(d[(d >= 0) & (d <= extent)] >> shift, minlength=1024), int((d > extent).sum())
-    rows = (keys >= middle << 19).sum(axis=1).reshape(-1, 4)
-    differences = f(4 * int((np.diff(rows, axis=1) ** 2).sum())) * f(0.5 / 4 * 4 / 3)
-    wide = f(5.5) * np.sqrt(f(lib.variance(differences, k, L, present))) + f(lib.margin(L, present))
+    rows = (keys >= middle << 19).sum(axis=1).reshape(-1, 8)
+    differences = f(2 * int((np.diff(rows, axis=1) ** 2).sum())) * f(0.5 / 2 * 8 / 7)
+    wide = f(lib.deviations()) * np.sqrt(f(lib.variance(differences, k, L, present))) + f(lib.margin(L, present))
     at = share * f(S)
     r0, r1 = clamp(at - wide, S), clamp(at + wide, S)
     hi, lo = 0x7FFFFFFF, 1
@@ -112,6 +113,17 @@ def test_a_chunk_that_the_gradient_fills_in_part(lib, logL, theta):
     assert outcome(lib, np.pad(g[:k // 2], (0, L - k // 2)), k, k // 2)[0] == "zero"
 
 
+def test_rows_with_a_scale_each(lib):
+    """Neighbours that are alike: the window is no wider than k_resolve's first rows."""
+    L, k = 1 << 20, kept(0.15, 1 << 20)
+    for seed in range(4):
+        rng = np.random.default_rng(seed)
+        for row in (64, 1024):
+            X = (rng.normal(size=(L // row, row)) * 10.0 ** rng.uniform(-4, 0, (L // row, 1))).astype(np.float32).ravel()
+            way, candidates = outcome(lib, X, k, L)
+            assert way == "inside" and candidates <= 128 * L // 2048, (row, candidates * 2048 / L)
+
+
 @pytest.mark.parametrize("logL", (18, 19, 20))
 def test_ways_to_the_threshold(lib, logL):
     L, ways = 1 << logL, {}
@@ -132,4 +144,4 @@ def test_ways_with_zeros(lib):
 
 
 def test_which_calls_take_the_sample(lib):
-    assert [lib.takes(c, n, w) for c, n, w in ((64, 9000, 1), (128, 7168, 1), (128, 7169, 1), (512, 4096, 0), (512, 4097, 0), (1024, 9000, 0))] == [0, 0, 1, 0, 1, 0]
+    assert [lib.takes(c, n, w) for c, n, w in ((64, 11000, 1), (128, 10240, 1), (128, 10241, 1), (512, 4096, 0), (512, 4097, 0), (1024, 11000, 0))] == [0, 0, 1, 0, 1, 0]
