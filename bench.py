@@ -54,7 +54,7 @@ def topk_kernel_bytes(name: str, n: int, L: int, theta: float, bits: int) -> flo
     """The same for the time-domain Top-k kernels: they read the gradient itself (no spectrum)."""
     C = (n + L - 1) // L
     payload = C * L / 8.0 + C * round(theta * L) * bits / 8.0   # bitmap + one code per kept sample
-    table = {"hist": 4.0 * n, "collect": 4.0 * n, "emit": 4.0 * n + payload,
+    table = {"hist": 4.0 * n, "sample": 4.0 * C * min(L, 1 << 15), "collect": 4.0 * n, "emit": 4.0 * n + payload,
              "group_prefix": C * L / 8.0 + C * L / (8.0 * 16), "decode": payload + 4.0 * n}
     return table.get(name, 0.0)
 
@@ -173,18 +173,20 @@ def measure_half(fftsp, torch, gd, out, n, L, theta, bits, scale_log2, steps, st
             "note": "own parity bound 1.5e-3 (two binary16 roundings), not the 1e-5 of the headline path"}
 
 
+# the kernels of the benchmark's step by the names they are timed under
+TRAFFIC_KERNELS = {"rfft_pass_a": "k_fwd_a", "rfft_pass_b": "k_fwd_b", "find_bucket": "k_find_bucket", "collect": "k_collect", "resolve": "k_resolve",
+                   "emit": "k_emit", "bitmap_table": "k_bitmap_table", "irfft_pass_b": "k_receive_pairs", "irfft_pass_a": "k_inv_a_split"}
+
+
 def measured_traffic(kernel: str):
     """(HBM bytes per launch, name of the summary) of `kernel` from the committed rocprofv3 --pmc summary
     (FETCH_SIZE + WRITE_SIZE, each scaled by the plain-copy calibration stated in that file), or (None, None) if the
     summary does not cover it.  The figure belongs to the build the summary was taken from, not to this run."""
-    names = {"rfft_pass_a": "k_fwd_a", "rfft_pass_b": "k_fwd_b", "irfft_pass_b": "k_receive_b", "irfft_pass_a": "k_inv_a",
-             "rfft_fused": "k_fused_fwd", "irfft_fused": "k_fused_inv", "collect": "k_collect", "emit": "k_emit",
-             "decode": "k_decode", "bitmap_table": "k_bitmap_table"}
     rel = os.path.join("profiles", "codec_config3_hbm_traffic.txt")
     try:
         for line in open(os.path.join(ROOT, rel)):
             f = line.split()
-            if len(f) >= 8 and f[0] == names.get(kernel):
+            if len(f) >= 8 and f[0] == TRAFFIC_KERNELS.get(kernel):
                 return int((float(f[4]) + float(f[5])) * 1e6), rel
     except OSError:
         pass

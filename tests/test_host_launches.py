@@ -257,3 +257,16 @@ def test_topk_finds_its_threshold_beside_the_codes_in_short_calls(runtime, tmp_p
     calls = [["fftsp_topk_compress", ["big", C * L, L, 0.3, 8, "big", "big", "big", "big", None]] for C in (most, most + 1)]
     within, beyond = kernels(runtime, tmp_path, calls)
     assert not any("k_resolve" in k for k in within) and any("k_resolve" in k for k in beyond)
+
+
+def test_the_benchmarks_traffic_is_that_of_the_kernels_it_launches(runtime, tmp_path):
+    """bench.py quotes a kernel's measured traffic from profiles/; its names and the summary's rows are the kernels of the step."""
+    import bench
+    n, L = 62378344, 1 << 20
+    made = kernels(runtime, tmp_path, [compress(n, L, 0.5), decompress(n, L, 0.5)])
+    launched = {re.search(r"\d(k_[a-z_]+?)I?(?=[A-Z])", name)[1].rstrip("_") for call in made for name in call}
+    assert set(bench.TRAFFIC_KERNELS.values()) == launched
+    with open(os.path.join(ROOT, "profiles", "codec_config3_hbm_traffic.txt")) as f:
+        rows = {line.split()[0] for line in f if line.startswith("k_")}
+    assert rows == launched and all(bench.measured_traffic(k)[0] for k in bench.TRAFFIC_KERNELS)
+    assert bench.topk_kernel_bytes("sample", n, L, 0.15, 32) > 0
