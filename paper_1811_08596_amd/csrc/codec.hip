@@ -367,8 +367,8 @@ __device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, b
 // the chunk.  Where the window's lower end is the smallest key above zero and the candidates do not have the threshold, it is zero.
 //
 // Bound by latency: one trip to memory, behind what the call before has left to write, and the barriers of three scans.  Sixty chunks of 2^20:
-// 19 us, where clearing the histograms, counting 62 M samples and finding the buckets took 83; k_collect, which then is the first to read the
-// gradient, 42 -> 64, k_resolve 21 -> 27.
+// 22 us, where clearing the histograms, counting 62 M samples and finding the buckets took 83; k_collect, which then is the first to read all of the
+// gradient, 42 -> 59, k_resolve 21 -> 30.
 constexpr int kSampleLanes = 1024, kSampleLoads = 8;
 static_assert(kSampleLanes / 2 * kSampleLoads == kSampleStretches && kStretch == 8, "a lane's load is half of a stretch");
 __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict__ in, uint32_t L, uint32_t k, size_t n, uint32_t* __restrict__ sel,
@@ -1421,8 +1421,10 @@ __global__ __launch_bounds__(NW * 64) void k_resolve(Shape u, ResolveArgs a, uin
 // The last tiles come first: k_collect has just read them, and of what does not fit the 256 MB cache the first ones are gone
 // (62 M samples in chunks of 2^20 67 -> 61 us, the step 537 -> 532; 138 M in 2^22 150 -> 138, 1320 -> 1306; top-k 223 -> 218.5).  After a kernel that
 // wrote the bins instead of reading them the order makes no difference.  Eight by eight, so that a tile stays on the XCD whose L2 may have it from
-// k_collect: one by one, calls of 100 to 450 tiles of 2^14 points lost 3 to 12 us (13 tensors 183 -> 195, so 186; 29 186 -> 196, so 187; 42 275 -> 281,
-// so 270).  Below kEmitBackwards tiles of 16 KB the first ones are still there, and the order stays.
+// k_collect: one by one, calls of 100 to 450 tiles of 2^14 points lost 3 to 12 us.  Below kEmitBackwards tiles of 16 KB the first ones are still there, and
+// the order stays.  Above it, forwards / backwards: senders 2^16 17 M 101.6 / 98.8, 60 M 303.0 / 295.2, 2^20 20 M 122.8 / 122.2, 62 M 322.4 / 315.7, 2^22 138 M 776 / 760, binary16 34 M
+// 149.8 / 149.7; top-k 34 M 141.9 / 143.8, 62 M 244.5 / 237.5; tensors 18 of 2^20 195.3 / 193.7, 48 442.0 / 440.9, random sets of 60 298.8 / 299.9, 90 326.0 / 328.3, 150 460.4 / 461.0
+// (builds differ by as much below the line, where the order is the same).
 constexpr uint32_t kEmitBackwards = 4096;
 // tiles from the first on whose order is reversed, a multiple of eight; an argument, since asking for the launch's size cost every launch 0.5 us
 inline uint32_t emit_reversed(uint32_t tiles) { return tiles >= kEmitBackwards ? tiles & ~7u : 0u; }

@@ -640,9 +640,10 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b(const typename Cx<HA
 // other's mirrored rows, and swap, so that a lane stores pairs.
 //
 // Bound by the two trips to memory that nothing hides but the other workgroups of the compute unit, and by the stages.  Binary16, 62 M samples in
-// chunks of 2^20: 80 us for 50 of traffic (99 as fwd_b_workgroup).  Six waves a SIMD: eight spill twenty registers (125 us), and the
+// chunks of 2^20: 80 us for 50 of traffic (99 as fwd_b_workgroup).  Six waves a SIMD, two registers spilled: eight spill twenty (125 us), and the
 // histogram in the tile's place, which they would need, costs two barriers and 11 us with six.  Runs of tiles that share a
-// histogram spill, too (115).
+// histogram spill, too (115).  Rows of 2^10 are workgroups of sixteen waves, so it is four waves a SIMD or eight; eight spill twenty-three registers, and two
+// workgroups beside each other are worth it: senders, four / eight, 2^21 17 M 120.2 / 113.1, 62 M 294.5 / 270.1; 2^22 62 M 323.0 / 292.4 (fwd_b_workgroup 116.8, 287.3, 324.7).
 __device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b)  // lanes 32 .. 63 of a with lanes 0 .. 31 of b
 {
     const auto v = __builtin_amdgcn_permlane32_swap(a, b, false, false);
@@ -1311,7 +1312,9 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b_long(const float2* _
     run(std::integral_constant<int, 10>{});
 }
 
-// A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of less than 2^10
+// A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of less than 2^10.  Eight waves a SIMD, twelve registers spilled with
+// three or four transforms in one kernel; none with six (TOP 13) or four waves: receivers of 100 tensors 138.5 / 158.5, 150 164.7 / 191.3, 60 of 2^20 208.7 / 226.1, five of
+// 3 M 84.8 / 96.2.
 template <int TOP>
 __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_inv_a_split_long(
     const float2* __restrict__ mid, float* __restrict__ out, Tables tb, int aligned, uint32_t total, LongTable tab, LongStarts at)
@@ -1760,7 +1763,9 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
         constexpr int LOGE = decltype(size)::value;
         // Sender and receiver in us, k_fwd_b_long / this: sets of 2^20 6 111 / 105, 12 163.5 / 152;  16 of 2^19 118.4 / 114.2;  two each of 2^16 .. 2^20 83.5 / 81.5;
-        // ResNet-50-like 150 tensors 586 / 575, 60 338.4 / 338.9, 200 819 / 820.
+        // ResNet-50-like 150 tensors 586 / 575, 60 338.4 / 338.9, 200 819 / 820.  One launch for all small tiles: where rows of 2^10 are among them k_fwd_b_long takes
+        // them all, since a second launch, with tiles of 2^14 for those rows, gains about as often as it loses: 20 of 600 k and one of 1.5 M 240.2 / 235.6, 40 and three
+        // 426.2 / 412.3, 10 of 500 k and six of 2 M 227.2 / 224.1, random sets 29 192.7 / 195.6, 42 267.1 / 264.5 and 189.4 / 194.5, 60 219.8 / 214.9.
         if (LOGE == 13 && log_rows(b.tab.t[end - 1].logM) <= kPairsTop) {
             const hipError_t err = set_lds(k_fwd_b_pairs_long, kPairsLds);
             if (err != hipSuccess) return err;

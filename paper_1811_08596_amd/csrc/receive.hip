@@ -10,15 +10,15 @@
 // codes.  Workgroups are dealt out to the XCDs round-robin, so each XCD gets a stretch of chunks of its own and its workgroups neighbouring
 // tiles of it: the lines come over the fabric once and then out of that XCD's L2.
 //
-// What bounds it: the two dependent trips to memory before a tile's transform, the barriers in it, and about 90 vector instructions a point
-// (40 to 80 of the 104 us below).  None of them alone: what helps is tiles beside each other in a compute unit, whose waits another
+// What bounds it: the two dependent trips to memory before a tile's transform, the barriers in it, and about 80 vector instructions a point
+// (34 to 67 of the 101 us below).  None of them alone: what helps is tiles beside each other in a compute unit, whose waits another
 // one's work fills.  Launches with enough tiles keep a tile in half of the LDS (receive_pairs), which makes it four tiles a compute unit
 // for rows of 2^9 and two for 2^10; in shorter ones, a tile or two a compute unit anyhow, the fewer barriers of receive_tile do better.
 // (Persistent workgroups of sixteen points a lane that fetched the next tile's entries and codes during the transform took 124 to 134 us where
 // receive_tile took 116; a lane that looked up each of its bins alone 187.)
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against counting, decoding and the pass: 6 + 54 + 110
-// -> 6 + 104 us; 138 M in chunks of 2^22 15 + 118 + 275 -> 12 + 254; binary16 5 + 33 + 95 -> 6 + 82.
-// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 6 + 36 + 33.
+// -> 8 + 101 us; 138 M in chunks of 2^22 15 + 118 + 275 -> 15 + 249; binary16 5 + 33 + 95 -> 7 + 83.
+// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 7 + 34 + 34.
 // Several senders' streams are decoded into a spectrum first (codec.hip): eight of them took 444 us this way against 285, since every
 // stretch of eight bins is two and a half lines out of L2.
 #include "fft_core.h"
