@@ -255,7 +255,7 @@ bool receive_without_spectrum(const Plan& p, const uint8_t* in, const CodecArgs&
         *e = launch_receive(in, a, logM, ws + p.ws.spec, mid, t, verdicts, ctl, note, s);
     else
         return false;
-    if (*e == hipSuccess) *e = launch_inverse_a(mid, logM, p.C, out, p.n, t, gain, a.half, 0, s);
+    if (*e == hipSuccess) *e = launch_inverse_a(mid, logM, p.C, out, p.n, t, gain, a.half, s);
     return true;
 }
 

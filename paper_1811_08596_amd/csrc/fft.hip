@@ -1462,17 +1462,12 @@ hipError_t inv_b_tiled(const float2* spec_f32, uint32_t sstride, int logM, size_
 //   1622.4 / 1529.1;  2^16 40 M receiver 122.9 / 103.5 and 209.1 / 199.8.  A kernel that reads and writes elsewhere: 62 M step 611.3 / 597.5.
 // Smaller ones lose alone: 2^20 17 M 167 / 171, 2^19 26 M 224 / 228, 60 tensors 288 / 297.  Stores alone, with that reader: 62 M step 645.7, 138 M 1577.6;
 // loads alone 653.0, 1635.5.  The gradient read this way: 62 M step 535 / 551.
-// Columns of 2^8 behind a spectrum in memory (several senders' streams; codes of 16 and 32 bits) have a higher line, below which the reader pays more
-// than the call gains: 2^16 four streams 34 M 167.0 / 160.0 and 228.7 / 240.4, 2^17 40 M 188.6 / 184.4 and 266.6 / 275.1, 2^16 eight streams 48 M 275.1 / 278.2 and
-// 372.7 / 375.3, 54 M 309.1 / 313.0 and 420.3 / 419.7, 60 M 345.5 / 344.4 and 467.8 / 463.0, 72 M 418.0 / 417.7 and 569.6 / 556.0.  Longer columns there: 2^18 four
-// streams 34 M 166.8 / 160.2 and 233.8 / 233.7.  Binary16 right above the line gives with a reader what it takes alone, and gains from 38 M on: 2^16 33.6 M 89.3 / 84.2
-// and 155.4 / 160.2, 2^22 126.6 / 122.8 and 195.8 / 199.8, 2^20 94.6 / 85.1 and 158.9 / 160.2;  2^16 42 M 101.2 / 98.2 and 197.6 / 189.6.
-constexpr size_t kOnceBytes = (size_t)1 << 27, kOnceBytesSpectrum8 = (size_t)7 << 25;
-template <int LOGN1, bool HALF>
-bool passes_by(size_t n, int from_spectrum)
-{
-    return 4 * n >= (!HALF && LOGN1 == 8 && from_spectrum ? kOnceBytesSpectrum8 : kOnceBytes);
-}
+// Where the two are about even, columns of 2^8 behind a spectrum in memory and binary16 right above the line, it depends on what else is read: 2^16, four
+// streams of 34.8 M samples, 8-bit codes of 10 % 174.9 / 168.2 and 242.2 / 250.2, of 50 % 169.2 / 163.0 and 233.9 / 244.0, of 90 % 177.9 / 166.9 and 241.8 / 245.0, 32-bit
+// codes of 50 % 211.4 / 196.1 and 278.0 / 266.2, of 90 % 261.4 / 233.7 and 329.7 / 314.8; 45 M, 8 bits, 50 % 216.0 / 214.1 and 304.5 / 309.3; binary16, 2^16 33.6 M 89.3 /
+// 84.2 and 155.4 / 160.2, 2^22 126.6 / 122.8 and 195.8 / 199.8, 2^20 94.6 / 85.1 and 158.9 / 160.2, 2^16 42 M 101.2 / 98.2 and 197.6 / 189.6.  A line of their own takes
+// them longer in sum.
+constexpr size_t kOnceBytes = (size_t)1 << 27;
 template <int LOGN1, int LOGE, bool HALF, bool ONCE>
 hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
                   hipStream_t s, const uint32_t* only_if)
@@ -1543,11 +1538,11 @@ hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_
     return hipGetLastError();
 }
 template <int LOGN1, bool HALF>
-hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, int from_spectrum,
+hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
                  hipStream_t s, const uint32_t* only_if = nullptr)
 {
     const size_t wide = wide_tiles(C, logM);
-    const bool once = passes_by<LOGN1, HALF>(n, from_spectrum);
+    const bool once = 4 * n >= kOnceBytes;
     auto persistent = [&](auto size, auto by) {
         return inv_a_tiled<LOGN1, decltype(size)::value, HALF, decltype(by)::value>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
     };
@@ -1720,11 +1715,11 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
             default: return hipErrorInvalidValue;
         }
     }
-    return e == hipSuccess ? launch_inverse_a(mid, logM, C, out, n, t, gain, 0, 1, s, only_if) : e;
+    return e == hipSuccess ? launch_inverse_a(mid, logM, C, out, n, t, gain, 0, s, only_if) : e;
 }
 
-hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, int from_spectrum,
-                            hipStream_t s, const uint32_t* only_if)
+hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, hipStream_t s,
+                            const uint32_t* only_if)
 {
     if (half) gain *= half_lift(logM);
     if (!only_if && short_inverse(logM, C)) return launch_short_inverse_a(mid, logM, C, out, n, t, gain, half, s);
@@ -1732,11 +1727,11 @@ hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, s
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     auto run = [&](auto columns) {
         constexpr int LOGN1 = decltype(columns)::value;
-        return half ? inv_a<LOGN1, true>(mid, logM, C, out, n, t, aligned, gain, from_spectrum, s, only_if)
-                    : inv_a<LOGN1, false>(mid, logM, C, out, n, t, aligned, gain, from_spectrum, s, only_if);
+        return half ? inv_a<LOGN1, true>(mid, logM, C, out, n, t, aligned, gain, s, only_if)
+                    : inv_a<LOGN1, false>(mid, logM, C, out, n, t, aligned, gain, s, only_if);
     };
     switch ((logM + 1) / 2) {
-        case 7: return half ? inv_a<7, true>(mid, logM, C, out, n, t, aligned, gain, from_spectrum, s) : hipErrorInvalidValue;
+        case 7: return half ? inv_a<7, true>(mid, logM, C, out, n, t, aligned, gain, s) : hipErrorInvalidValue;
         case 8: return run(std::integral_constant<int, 8>{});
         case 9: return run(std::integral_constant<int, 9>{});
         case 10: return run(std::integral_constant<int, 10>{});
@@ -1899,7 +1894,7 @@ hipError_t launch_irfft_half(const void* spec, uint32_t sstride, size_t n, int l
             default: return hipErrorInvalidValue;
         }
     }
-    return e == hipSuccess ? launch_inverse_a(md, logM, C, out, n, t, gain, 1, 1, s) : e;
+    return e == hipSuccess ? launch_inverse_a(md, logM, C, out, n, t, gain, 1, s) : e;
 }
 
 }  // namespace fftsp

@@ -312,10 +312,9 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
 hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, float2* mid, Tables t, uint32_t* hist,
                             uint32_t* zero_ptr, size_t zero_words, hipStream_t s);
 hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out, float2* mid, Tables t, hipStream_t s);
-// Their second kernels alone (pass A), where something else has filled mid.  half: mid holds binary16 pairs.  from_spectrum: out of a
-// spectrum in memory, not out of the records.
-hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, int from_spectrum,
-                            hipStream_t s, const uint32_t* only_if = nullptr);
+// Their second kernels alone (pass A), where something else has filled mid.  half: mid holds binary16 pairs.
+hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, hipStream_t s,
+                            const uint32_t* only_if = nullptr);
 hipError_t launch_inverse_a_long(const float2* mid, const LongBatch& b, float* out, Tables t, hipStream_t s);
 // A first-pass sum of N1 terms is about sqrt(N2) times smaller than a spectrum value, an unnormalised inverse second-pass sum
 // about sqrt(N2) times larger: the half-precision variant's stored intermediate is lifted (lowered) by 2^(log2 N2 / 2) so that
