@@ -353,15 +353,12 @@ __device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, b
 // candidates, and k_resolve, which knows how many are above, sees whether the k-th largest is among the candidates.  Where it is not, it selects
 // from the samples themselves (select_samples): the result is exact whatever was sampled.
 //
-// The sample: 2^12 stretches of eight neighbours, one from each 2^12-th of the chunk, at a place in it that a hash of its number says,
-// so that no period of the gradient's layout is met again and again.  Neighbours are alike in a gradient, so how far the sample's ranks are off
+// The sample: stretches of eight or sixteen neighbours (sample_stretch), one from each equal part of the chunk, at a place in it that a hash of its number
+// says, so that no period of the gradient's layout is met again and again.  Neighbours are alike in a gradient, so how far the sample's ranks are off
 // is taken from the stretches: half the squared differences between one's count above the estimate and the next one's, which is what independent
 // samples' ranks vary by too where there is no likeness (sample_variance).  Four and a half of these standard deviations either side: 38 candidates to a
-// tile of 2048 at 15 % kept, where a bucket of the histogram has 10 to 40, and one chunk in 150000 whose threshold lies outside.
-// Stretches of sixteen are read faster, but are more alike within, and more than 128 candidates to a tile are slow.  Senders of 62 M samples in chunks of 2^20, 15 %
-// kept, sixteen with five and a half deviations / this / histogram: independent 133.7 / 134.6 / 165.9, rows of 1024 with a scale each 153.6 / 133.8 / 165.8, of 64
-// 166.2 / 143.9 / 166.9, autoregressive (0.9) 146.8 / 142.5 / 170.4, 8-bit floats 338.4 / 289.3 / 310.8 (of which one value for a crowd 22), half of a sine 351 / 191 / 224.  Stretches of
-// four: 144 where those of eight took 135.
+// tile of 2048 at 15 % kept, where a bucket of the histogram has 10 to 40, and one chunk in 150000 whose threshold lies outside.  More than 128 to a tile are
+// slow: with five and a half, and stretches of sixteen, 62 M samples in chunks of 2^20, 15 % kept, took 133.7 us, rows of 64 with a scale each 166, 50 % of a sine 351.
 //
 // Zeros are never candidates: a gradient can be half zeros (a rectifier's), and a window that reached them would have k_collect write most of
 // the chunk.  Where the window's lower end is the smallest key above zero and the candidates do not have the threshold, it is zero.
@@ -370,7 +367,9 @@ __device__ __forceinline__ void count_digit(uint32_t* h, bool hit, uint32_t d, b
 // 22 us, where clearing the histograms, counting 62 M samples and finding the buckets took 83; k_collect, which then is the first to read all of the
 // gradient, 42 -> 59, k_resolve 21 -> 30.
 constexpr int kSampleLanes = 1024, kSampleLoads = 8;
-static_assert(kSampleLanes / 2 * kSampleLoads == kSampleStretches && kStretch == 8, "a lane's load is half of a stretch");
+static_assert(4 * kSampleLanes * kSampleLoads == kSamples, "four samples a load");
+// SHARE: log2 of the lanes that share a stretch
+template <int SHARE>
 __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict__ in, uint32_t L, uint32_t k, size_t n, uint32_t* __restrict__ sel,
                                                         uint32_t* __restrict__ ctl)
 {
@@ -389,7 +388,7 @@ __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict
     uint32_t key[4 * kSampleLoads];
 #pragma unroll
     for (int j = 0; j < kSampleLoads; ++j) {
-        const uint32_t g = (uint32_t)(j * (kSampleLanes / 2) + (tid >> 1)), at = kStretch * (g * slots + sample_slot(g, slots)) + 4u * ((uint32_t)tid & 1u);
+        const uint32_t g = (uint32_t)(j * (kSampleLanes >> SHARE) + (tid >> SHARE)), at = (4u << SHARE) * (g * slots + sample_slot(g, slots)) + 4u * ((uint32_t)tid & ((1u << SHARE) - 1u));
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (at + 4u <= present) {
             v = *reinterpret_cast<const float4*>(X + at);
@@ -467,8 +466,9 @@ __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict
             else if (d <= range)
                 atomicAdd(&fine[d >> shift], 1u);
         }
-        in += __builtin_amdgcn_mov_dpp(in, 0xB1, 0xF, 0xF, false);                      // of the two lanes of a stretch
-        const int next = __builtin_amdgcn_update_dpp(in, in, 0x102, 0xF, 0xF, false);  // two lanes on; itself in a row's last two
+        in += __builtin_amdgcn_mov_dpp(in, 0xB1, 0xF, 0xF, false);  // of the lanes of a stretch
+        if constexpr (SHARE > 1) in += __builtin_amdgcn_mov_dpp(in, 0x4E, 0xF, 0xF, false);
+        const int next = __builtin_amdgcn_update_dpp(in, in, 0x100 + (1 << SHARE), 0xF, 0xF, false);  // a stretch on; itself in a row's last one
         off += (uint32_t)((next - in) * (next - in));
     }
     above = wave_sum(above);
@@ -480,8 +480,9 @@ __global__ __launch_bounds__(kSampleLanes) void k_sample(const float* __restrict
     __syncthreads();
     above = wave_sum(lane < NW ? sums[1][lane] : 0u);
     off = wave_sum(lane < NW ? sums[2][lane] : 0u);
-    // half of the differences, each seen by two lanes, and seven of them to eight stretches
-    const float wide = kSampleDeviations * sqrtf(sample_variance((float)off * (0.5f / 2.f * 8.f / 7.f), k, L, present)) + sample_margin(L, present);
+    // half of the differences, each seen by all lanes of a stretch, and one fewer to a row of sixteen lanes than it has stretches
+    constexpr float kRow = 16 >> SHARE, kSeen = 0.5f / (1 << SHARE) * (kRow / (kRow - 1.f));
+    const float wide = kSampleDeviations * sqrtf(sample_variance((float)off * kSeen, k, L, present)) + sample_margin(L, present);
     const float at = share * kSamples;
     const uint32_t r0 = clamped(at - wide, kSamples), r1 = clamped(at + wide, kSamples), digit = (uint32_t)(kHist2Bins - 1 - tid);
     const uint32_t cnt = fine[digit], run = above + before(cnt, sums[0]), end = run + cnt;
@@ -2295,8 +2296,8 @@ hipError_t launch_encode(const float* spec, const CodecArgs& a, uint8_t* stream_
 
     const bool window = a.time_domain && sampled(u.Tn, x.tiles, a.n % a.L == 0);
     if (window) {
-        FFTSP_LAUNCH("sample", k_sample, dim3((unsigned)a.C), dim3(kSampleLanes), 0, s, spec, a.L, a.k, a.n, sel,
-                     reinterpret_cast<uint32_t*>(ws_base + w.status));
+        const auto sample = sample_stretch(a.L) == 8 ? k_sample<1> : k_sample<2>;
+        FFTSP_LAUNCH("sample", sample, dim3((unsigned)a.C), dim3(kSampleLanes), 0, s, spec, a.L, a.k, a.n, sel, reinterpret_cast<uint32_t*>(ws_base + w.status));
     } else if (!hist_ready) {
         hipError_t e = launch_zero_control(ws_base, w, a.C, s);
         if (e != hipSuccess) return e;

@@ -5,7 +5,16 @@
 
 namespace fftsp {
 
-constexpr uint32_t kSampleStretches = 4096, kStretch = 8, kSamples = kStretch * kSampleStretches;
+constexpr uint32_t kSamples = 1u << 15;
+// The sample is stretches of so many neighbours, each out of an equal part of the chunk.  Neighbours are alike: shorter stretches know more, and longer ones
+// are read faster.  Senders in us, histogram / stretches of sixteen / of eight, 15 and 50 % kept:
+//   2^18 20 M samples, independent 67.4 / 53.0 / 55.2 and 72.4 / 58.0 / 60.8, rows of 1024 with a scale each 69.5 / 53.6 / 56.0 and 75.1 / 60.9 / 63.9, of 64 67.0 / 62.2 / 57.1 and 72.0 /
+//     75.5 / 69.1, autoregressive (0.9) 68.7 / 55.1 / 56.7 and 72.5 / 59.8 / 61.6;
+//   2^19 20 M 72.1 / 56.3 / 58.1 and 78.3 / 63.5 / 65.1, 73.1 / 57.5 / 59.9 and 77.1 / 66.1 / 68.1, 72.4 / 69.5 / 63.8 and 80.5 / 84.6 / 75.1, 75.2 / 61.5 / 62.3 and 78.1 / 67.8 / 67.1;
+//   2^20 30 M 94.8 / 78.9 / 82.8 and 105.5 / 90.7 / 94.1, 96.5 / 94.3 / 83.3 and 103.9 / 119.5 / 99.1, 96.1 / 94.9 / 85.9 and 105.3 / 130.4 / 110.9, 93.9 / 80.8 / 84.2 and 105.7 / 93.9 / 96.1;
+//     62 M 168.2 / 131.0 / 134.3 and 209.4 / 152.5 / 155.5, 166.3 / 143.7 / 134.1 and 207.2 / 180.0 / 160.7, 166.1 / 151.9 / 143.6 and 209.2 / 193.6 / 171.4; half of a sine 223 / 226 / 191.
+// Of four, 62 M 144 where those of eight took 135.
+constexpr uint32_t sample_stretch(uint32_t L) { return L >= 1u << 20 ? 8u : 16u; }
 constexpr float kSampleDeviations = 4.5f;  // of the threshold's rank that are looked at, either side
 // where stretch g lies among the `slots` (a power of two) of its part
 constexpr uint32_t sample_slot(uint32_t g, uint32_t slots) { return (g * 2654435761u >> 15) & (slots - 1u); }
@@ -20,7 +29,7 @@ constexpr float sample_variance(float differences, uint32_t k, uint32_t L, uint3
 }
 
 // and how far it can be off whatever the gradient is: a stretch at the gradient's end is in the sample or not
-constexpr float sample_margin(uint32_t L, uint32_t present) { return present < L ? 4.f + (float)kStretch : 4.f; }
+constexpr float sample_margin(uint32_t L, uint32_t present) { return present < L ? 4.f + (float)sample_stretch(L) : 4.f; }
 
 // Chunks of chunk_tiles tiles in a call of `tiles` of them; whole: the last one is full.
 // Shorter chunks would have half or a quarter of their samples looked at, longer ones have more tiles than k_resolve holds the summaries of.

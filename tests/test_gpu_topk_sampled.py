@@ -8,7 +8,7 @@ from paper_1811_08596_amd import workloads
 from tests.gpu_harness import Device
 
 pytestmark = pytest.mark.gpu
-STRETCHES, LONG = 4096, 8
+SAMPLES = 1 << 15
 
 
 @pytest.fixture(scope="module")
@@ -16,10 +16,14 @@ def dev():
     return Device()
 
 
+def stretch(L):
+    return 8 if L >= 1 << 20 else 16
+
+
 def sampled(L):
-    g, slots = np.arange(STRETCHES, dtype=np.uint64), L // (LONG * STRETCHES)
+    g, slots = np.arange(SAMPLES // stretch(L), dtype=np.uint64), L // SAMPLES
     at = g * slots + ((g * 2654435761 & 0xFFFFFFFF) >> 15 & (slots - 1))
-    return (LONG * at[:, None] + np.arange(LONG, dtype=np.uint64)).astype(np.int64).ravel()
+    return (stretch(L) * at[:, None] + np.arange(stretch(L), dtype=np.uint64)).astype(np.int64).ravel()
 
 
 def check(dev, ref, g, L, theta, bits):

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 from paper_1811_08596_amd import workloads
-from tests.test_gpu_topk_sampled import LONG, STRETCHES, misleading, sampled, with_zeros
+from tests.test_gpu_topk_sampled import SAMPLES, misleading, sampled, stretch, with_zeros
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCE = r"""
@@ -19,6 +19,7 @@ extern "C" float variance(float d, uint32_t k, uint32_t L, uint32_t present) { r
 extern "C" float margin(uint32_t L, uint32_t present) { return fftsp::sample_margin(L, present); }
 extern "C" int takes(uint32_t chunk_tiles, size_t tiles, int whole) { return fftsp::sampled(chunk_tiles, tiles, whole); }
 extern "C" uint32_t samples(void) { return fftsp::kSamples; }
+extern "C" uint32_t length(uint32_t L) { return fftsp::sample_stretch(L); }
 extern "C" float deviations(void) { return fftsp::kSampleDeviations; }
 """
 
@@ -32,7 +33,7 @@ def lib(tmp_path_factory):
     s.variance.restype = s.margin.restype = s.deviations.restype = ctypes.c_float
     s.variance.argtypes = [ctypes.c_float] + [ctypes.c_uint32] * 3
     s.takes.argtypes = [ctypes.c_uint32, ctypes.c_size_t, ctypes.c_int]
-    assert s.samples() == LONG * STRETCHES
+    assert s.samples() == SAMPLES and all(s.length(1 << p) == stretch(1 << p) for p in range(18, 21))
     return s
 
 
@@ -51,10 +52,11 @@ def window(lib, X, k, present):
     """The two keys between which k_sample has candidates lie, of a chunk with its padding."""
     f, L = np.float32, len(X)
     S = lib.samples()
-    keys = keys_of(X[sampled(L)]).reshape(STRETCHES, LONG)
+    many, lanes = S // stretch(L), stretch(L) // 4
+    keys = keys_of(X[sampled(L)]).reshape(many, 4 * lanes)
     share = f(k) / f(L)
     # a quarter by its top twelve bits: of four neighbours one, another one in every eighth of the stretches
-    quarter = keys.reshape(STRETCHES, LONG // 4, 4)[np.arange(STRETCHES), :, (np.arange(STRETCHES) // (STRETCHES // 8)) & 3].ravel()
+    quarter = keys.reshape(many, lanes, 4)[np.arange(many), :, (np.arange(many) // (many // 8)) & 3].ravel()
     coarse, few = np.bincount(quarter >> 19, minlength=4096), S // 4
     at, wide = share * f(few), f(20) * np.sqrt(share * (f(1) - share) * f(few)) + f(20)
     clamp = lambda r, most: int(min(max(r, 1), most))
@@ -63,8 +65,9 @@ def window(lib, X, k, present):
     shift = extent.bit_length() - 10
     d = keys.ravel() - base
     fine, above = np.bincount(d[(d >= 0) & (d <= extent)] >> shift, minlength=1024), int((d > extent).sum())
-    rows = (keys >= middle << 19).sum(axis=1).reshape(-1, 8)
-    differences = f(2 * int((np.diff(rows, axis=1) ** 2).sum())) * f(0.5 / 2 * 8 / 7)
+    row = 16 // lanes
+    rows = (keys >= middle << 19).sum(axis=1).reshape(-1, row)
+    differences = f(lanes * int((np.diff(rows, axis=1) ** 2).sum())) * f(0.5 / lanes * row / (row - 1))
     wide = f(lib.deviations()) * np.sqrt(f(lib.variance(differences, k, L, present))) + f(lib.margin(L, present))
     at = share * f(S)
     r0, r1 = clamp(at - wide, S), clamp(at + wide, S)
