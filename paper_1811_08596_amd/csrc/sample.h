@@ -33,13 +33,17 @@ constexpr float sample_margin(uint32_t L, uint32_t present) { return present < L
 
 // Chunks of chunk_tiles tiles in a call of `tiles` of them; whole: the last one is full.
 // Shorter chunks would have half or a quarter of their samples looked at, longer ones have more tiles than k_resolve holds the summaries of.
-// Whole calls in us, 15 % kept at 32 bits, histogram / sample.  Full chunks: 2^18 7680 tiles 75.1 / 75.9, 10240 88.8 / 86.6;  2^19 7680 76.9 / 79.7, 10240 91.7 / 91.5;  2^20
-// 8192 87.3 / 90.8, 10240 97.9 / 98.9, 15360 135.6 / 128.6, 20480 168.4 / 153.6.
+// Whole calls in us, 15 % kept at 32 bits, histogram / sample.  Full chunks: 2^18 5888 tiles 59.6 / 61.4, 6656 66.8 / 66.8, 7680 75.0 / 73.2, 10240 89.9 / 84.0;  2^19 5888 63.6 / 64.6,
+// 6656 69.7 / 70.3, 7680 78.5 / 76.8, 10240 92.9 / 88.9;  2^20 8192 87.3 / 90.8, 10240 97.9 / 98.9, 15360 136.5 / 129.3, 20480 172.9 / 155.0.
 // Where the last one is not, its zeros queue for one counter of the histogram, and are candidates where more is kept than there is: 2^20, nine chunks, the
-// last 2, 5, 10, 16, 20, 30, 40, 50, 70, 90 % full, 126 / 65, 99 / 65, 99 / 65, 63 / 66, 71 / 68, 63 / 65, 70 / 65, 62 / 65, 72 / 65, 72 / 66; 2^19, twenty, 84 / 63, 86 / 62, 77 /
-// 61, 60 / 63, 62 / 64, 68 / 64, 70 / 62, 60 / 62, 62 / 61, 71 / 62; 2^18, forty, 73 / 58, 81 / 58, 76 / 57, 62 / 59, 55 / 59, 67 / 59, 61 / 59, 56 / 59, 56 / 57, 60 / 59.
-// Neighbours that are alike make the window wider.  Senders, rows of 64 with a scale each: 2^18 8.6 M 49.5 / 42.4, 2^19 9.1 M 47.7 / 52.4, 20.2 M 72.8 / 63.8, 2^20 8.9 M 50.6 / 67.2,
-// 12.4 M 67.6 / 60.8, 30.3 M 96.4 / 85.6; rows of 1024: 2^20 8.9 M 50.7 / 55.5, 12.4 M 68.7 / 57.4; 8-bit floats: 2^18 8.6 M 95.8 / 83.9, 2^20 12.4 M 170.8 / 178.0, 40.3 M 244.0 / 234.4.
-constexpr bool sampled(uint32_t chunk_tiles, size_t tiles, bool whole) { return chunk_tiles >= 128 && chunk_tiles <= 513 && tiles > (whole ? 10240u : 4096u); }
+// last 2, 5, 10, 16, 20, 30, 40, 50, 70, 90 % full, 125 / 66, 98 / 65, 99 / 66, 62 / 65, 71 / 68, 62 / 65, 70 / 65, 62 / 65, 73 / 66, 71 / 66; 2^19, twenty, 86 / 60, 85 / 60, 78 /
+// 61, 60 / 60, 62 / 63, 66 / 59, 70 / 59, 59 / 59, 62 / 59, 70 / 60; 2^18, forty, 74 / 57, 80 / 57, 77 / 58, 62 / 57, 56 / 59, 66 / 57, 61 / 56, 55 / 56, 57 / 56, 59 / 56.
+// Neighbours that are alike make the window wider, gradients on a grid crowd it, and the shortest of these calls lose.  Senders, rows of 64 with a scale each: 2^18 8.6 M 49.5 /
+// 44.8, 2^19 9.1 M 47.5 / 54.7, 20.2 M 72.1 / 69.5, 2^20 8.9 M 50.0 / 67.1, 12.4 M 64.0 / 60.7, 30.3 M 94.0 / 85.4; rows of 1024: 2^20 8.9 M 51.3 / 55.1, 12.4 M 67.7 / 57.1; 8-bit
+// floats: 2^18 8.6 M 95.2 / 81.5, 2^20 12.4 M 170.3 / 177.7, 40.3 M 246.6 / 233.8.
+constexpr bool sampled(uint32_t chunk_tiles, size_t tiles, bool whole)
+{
+    return chunk_tiles >= 128 && chunk_tiles <= 513 && tiles > (!whole ? 4096u : chunk_tiles < 512 ? 7168u : 10240u);
+}
 
 }  // namespace fftsp

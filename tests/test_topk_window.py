@@ -147,4 +147,5 @@ def test_ways_with_zeros(lib):
 
 
 def test_which_calls_take_the_sample(lib):
-    assert [lib.takes(c, n, w) for c, n, w in ((64, 11000, 1), (128, 10240, 1), (128, 10241, 1), (512, 4096, 0), (512, 4097, 0), (1024, 11000, 0))] == [0, 0, 1, 0, 1, 0]
+    calls = [(64, 11000, 1), (128, 7168, 1), (128, 7169, 1), (256, 7169, 1), (512, 10240, 1), (512, 10241, 1), (512, 4096, 0), (512, 4097, 0), (128, 4097, 0), (1024, 11000, 0)]
+    assert [lib.takes(*c) for c in calls] == [0, 0, 1, 1, 0, 1, 0, 1, 1, 0]
