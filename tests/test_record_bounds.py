@@ -48,10 +48,10 @@ def lib(tmp_path_factory):
 @pytest.mark.parametrize("logL", (16, 17, 19, 22))
 def test_reads_stay_in_the_record(lib, logL, bits):
     L, bins = 1 << logL, (1 << logL >> 1) + 1
-    windows = [(8 * widest + 31 + 31) // 32 for widest in (16, 30)]  # Stretch<8, ...>::WORDS
+    windows = [(8 * widest + 31 + 31) // 32 for widest in (16, 30)] + [4]  # Stretch<8, ...>::WORDS, and ByteWindow's
     for theta in (0.0, 1.0 / bins, 2.0 / bins, 40.0 / bins, 0.1, 1.0):
         k, S = fftsp.kept_per_chunk(L, theta), fftsp.packed_bytes(L, L, theta, bits) - 64
         W = (bins + 31) // 32
         assert S == (16 + 4 * W + (2 * bits * k + 31) // 32 * 4 + 15) // 16 * 16
         # all bins claimed by the bitmap, its padding bits too
-        assert lib(S, W, k, (ctypes.c_int * 2)(*windows), 2, 2 * bits * 32 * W) == 0
+        assert lib(S, W, k, (ctypes.c_int * 3)(*windows), 3, 2 * bits * 32 * W) == 0
