@@ -43,7 +43,7 @@ namespace {
 // reads in narrow pieces, was slower that way (columns of 2^10: 119 / 124 us; of 2^11: 340 us against 327 with four
 // 2^13-point tiles of a line walked in step).  Binary16 storage: the same lines within 3 us.
 constexpr int kTileFA = 13;
-constexpr int kWideMin = 10;  // columns (inverse first pass) or rows (second passes) of at least 2^kWideMin
+constexpr int kWideMin = 10;  // rows (second passes) of at least 2^kWideMin
 constexpr size_t kWideForward = 128, kWideInverseB = 1152;  // large tiles from which a pass takes them
 constexpr size_t kWideInverseA = 256;  // columns of 2^11
 inline size_t wide_tiles(size_t C, int logM) { return C << (logM - 14); }
@@ -1312,7 +1312,7 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b_long(const float2* _
     run(std::integral_constant<int, 10>{});
 }
 
-// A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of less than 2^10.  Eight waves a SIMD, twelve registers spilled with
+// A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of less than 2^10.  Eight waves a SIMD, eleven or twelve registers spilled with
 // three or four transforms in one kernel; none with six (TOP 13) or four waves: receivers of 100 tensors 138.5 / 158.5, 150 164.7 / 191.3, 60 of 2^20 208.7 / 226.1, five of
 // 3 M 84.8 / 96.2.
 template <int TOP>
@@ -1815,8 +1815,9 @@ hipError_t launch_inverse_a_long(const float2* mid, const LongBatch& b, float* o
     const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     LongStarts at;
     // Tiles of 2^13 as in uniform calls; launches with columns of 2^11 have them beside tiles of 2^14, two to a workgroup.  Receivers in us,
-    // persistent (a launch for each tile size) / this: ResNet-50's 161 tensors 144 / 134, 150 of 10 to 2.4 M samples 275.5 / 241, 60 144 / 137, 48 of 2^19 95 / 80
-    // (two tiles to a workgroup 100), 18 of 2^20 72 / 66, 30 107.5 / 107.8, 60 (tiles of 2^14) 224 / 214, 120 of 2^18 124 / 115, 5 of 3 M 93 / 86, 180 of 2^16 67 / 67.
+    // persistent (a launch for each tile size) / this: ResNet-50's 161 tensors 159 / 136, 150 of 10 to 2.4 M samples 224 / 161, 100 164 / 134, 60 82 / 79 and (longer)
+    // 124 / 101.5, 48 of 2^19 89 / 79, of 2^19 - 1 107 / 83, 18 of 2^20 78 / 68, 30 116 / 103, 60 (tiles of 2^14) 266.5 / 210, of 2^20 - 3 328 / 266, 120 of 2^18 138.5 / 115.5,
+    // 5 of 3 M 100 / 85, of 3 000 001 117 / 89.5, 180 of 2^16 63.6 / 63.7.
     const bool small = log_columns(b.tab.t[b.count - 1].logM) <= (launch_tiles(b) < kSplitInverse10 ? 10 : 9);
     auto run = [&](auto size) {
         constexpr int TOP = decltype(size)::value;
