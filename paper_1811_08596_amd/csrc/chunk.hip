@@ -267,7 +267,7 @@ struct UniformChunks {
         slots = C - c0 < (size_t)T ? (uint32_t)(C - c0) : T;
     }
     __device__ __forceinline__ bool exists(int b) const { return (uint32_t)b < slots; }
-    __device__ __forceinline__ Span span(int b) const { return Span{first_sample + (size_t)((uint32_t)b * chunk_len), n, aligned}; }
+    __device__ __forceinline__ Span span(int b) const { return Span{first_sample + (size_t)((uint32_t)b * chunk_len), n}; }
     // all T slots hold whole chunks: the samples are one aligned run from first_sample on
     __device__ __forceinline__ bool whole(int T) const { return aligned && first_sample + (size_t)((uint32_t)T * chunk_len) <= n; }
     __device__ __forceinline__ size_t record(int b) const { return first_record + (size_t)((uint32_t)b * S); }
@@ -278,8 +278,8 @@ struct UniformChunks {
 struct ListedChunk {
     size_t first_sample, first_record, number;
     uint32_t length;
-    int slot, aligned;  // slot: -1 if the group has none
-    __device__ __forceinline__ ListedChunk(const TensorTable& t, const TensorPiece& piece, int group, int cpw, int aligned_)
+    int slot;  // -1 if the group has none
+    __device__ __forceinline__ ListedChunk(const TensorTable& t, const TensorPiece& piece, int group, int cpw)
     {
         const bool has = group < (int)piece.count;
         const uint32_t entry = (uint32_t)piece.first + (has ? (uint32_t)group : 0u);
@@ -288,12 +288,11 @@ struct ListedChunk {
         length = t.glen[entry];
         number = (size_t)(t.base + entry);
         slot = has ? group * cpw : -1;
-        aligned = aligned_ && !(first_sample & 1u);
     }
     __device__ __forceinline__ bool exists(int b) const { return b == slot; }
     __device__ __forceinline__ Span span(int b) const
     {
-        return exists(b) ? Span{first_sample, first_sample + length, aligned} : Span{0, 0, 0};
+        return exists(b) ? Span{first_sample, first_sample + length} : Span{0, 0};
     }
     __device__ __forceinline__ bool whole(int) const { return false; }
     __device__ __forceinline__ size_t record(int) const { return first_record; }
@@ -303,7 +302,7 @@ struct ListedChunk {
 // Forward transform of the workgroup's chunks up to Z[k] in d, visible to the group.
 // The stage twiddle table must have been filled before (the barrier for it is taken here, behind the loads).
 template <typename G, int LOGM, typename Where>
-__device__ __forceinline__ void forward_tile(const float* __restrict__ in, const Where& where, float2* d, const float2* tw, int tid)
+__device__ __forceinline__ void forward_tile(const float* __restrict__ in, const Where& where, const Tables& tb, float2* d, const float2* tw, int tid)
 {
     constexpr int RL = stage_radix_log(LOGM);
     using B = Butterflies<LOGM, G::LOGE, G::NT, RL>;
@@ -320,10 +319,7 @@ __device__ __forceinline__ void forward_tile(const float* __restrict__ in, const
 #pragma unroll
         for (int q = 0; q < B::PER; ++q) {
             const int w = B::index(tid, q);
-            const Span sp = where.span(B::b(w));
-#pragma unroll
-            for (int t = 0; t < B::RHO; ++t)
-                v[q][t] = load_pair(in, sp.first + 2 * (size_t)(B::j(w) + t * B::STEP), sp.limit, sp.pairs);
+            load_pairs(v[q], in, where.span(B::b(w)), (uint32_t)G::M, (uint32_t)B::j(w), (uint32_t)B::STEP, tb);
         }
     }
     __syncthreads();
@@ -779,7 +775,7 @@ __device__ __forceinline__ void compress_workgroup(const float* __restrict__ in,
     float2* tw = reinterpret_cast<float2*>(regions + G::GROUPS * G::REGION);
     uint32_t* images = reinterpret_cast<uint32_t*>(tw + G::TW);  // short chunks only
     load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
-    forward_tile<G, LOGM>(in, where, d, tw, tid);
+    forward_tile<G, LOGM>(in, where, tb, d, tw, tid);
     uint32_t* mine = reinterpret_cast<uint32_t*>(region);
     auto bins_of = [&](int b, float2 (&z)[G::R], float2& zn) __attribute__((always_inline)) {
         const int base = b << LOGM;
@@ -853,25 +849,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT / 256, NT
 }
 
 template <typename G>
-__device__ __forceinline__ ListedChunk listed(const TensorTable& t, const TensorPiece& piece, int aligned, int tid)
+__device__ __forceinline__ ListedChunk listed(const TensorTable& t, const TensorPiece& piece, int tid)
 {
-    return ListedChunk(t, piece, tid / G::NL, G::CPW, aligned);
+    return ListedChunk(t, piece, tid / G::NL, G::CPW);
 }
 template <int LOGM>
 __device__ __forceinline__ void compress_tensors(const float* __restrict__ in, const TensorTable& t, const TensorPiece& piece,
-                                                 int aligned, const Tables& tb, const PackArgs& a,
-                                                 uint8_t* __restrict__ records, uint8_t* lds, int tid)
+                                                 const Tables& tb, const PackArgs& a, uint8_t* __restrict__ records, uint8_t* lds, int tid)
 {
     constexpr int NT = uniform_threads<LOGM>();
     if (tid >= NT) return;
-    compress_workgroup<LOGM, NT>(in, listed<Geo<LOGM, NT>>(t, piece, aligned, tid), tb, a, records, lds, tid);
+    compress_workgroup<LOGM, NT>(in, listed<Geo<LOGM, NT>>(t, piece, tid), tb, a, records, lds, tid);
 }
 
 // The tensors of a per-tensor call that fit one workgroup, whatever their lengths, as one launch: workgroup i does the
 // tensors of piece i.  Waves its length has no use for leave at once (an ended wave takes part in no barrier).
 // TOP: the longest a launch may hold, 2^(TOP+1) samples.
 template <int TOP>
-__global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_compress(const float* __restrict__ in, int aligned, Tables tb,
+__global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_compress(const float* __restrict__ in, Tables tb,
                                                                             QuantizerArgs q, uint8_t* __restrict__ stream,
                                                                             uint8_t* __restrict__ records, HeaderInfo hdr,
                                                                             uint32_t* __restrict__ ctl, TensorTable t)
@@ -884,7 +879,7 @@ __global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_compress(con
     }
     const TensorPiece piece = t.piece[blockIdx.x];
     const PackArgs a = pack_args_of(q, t, piece.logm);
-#define X(p) else if (p <= TOP && piece.logm == p) compress_tensors<(p <= TOP ? p : 4)>(in, t, piece, aligned, tb, a, records, lds, tid);
+#define X(p) else if (p <= TOP && piece.logm == p) compress_tensors<(p <= TOP ? p : 4)>(in, t, piece, tb, a, records, lds, tid);
     if (false) {
     }
     FFTSP_CHUNK_SIZES(X)
@@ -1125,7 +1120,7 @@ __device__ __forceinline__ void decompress_workgroup(const PeerList& streams, ui
     } else {
         fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
             const Span sp = where.span(b);
-            store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, sp.pairs, make_float2(v.x * scale, v.y * scale));
+            store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, make_float2(v.x * scale, v.y * scale));
         });
     }
 }
@@ -1154,19 +1149,19 @@ __host__ __device__ constexpr uint32_t tensor_region(uint32_t stride)
 }
 template <int LOGM>
 __device__ __forceinline__ void decompress_tensors(const PeerList& streams, const TensorTable& t, const TensorPiece& piece,
-                                                   int aligned, const Tables& tb, const PackArgs& a, const HeaderInfo& hdr,
+                                                   const Tables& tb, const PackArgs& a, const HeaderInfo& hdr,
                                                    float* __restrict__ out, uint32_t* __restrict__ verdicts, uint8_t* lds, int tid)
 {
     constexpr int NT = uniform_threads<LOGM>();
     using G = Geo<LOGM, NT>;
     if (tid >= NT) return;
-    decompress_workgroup<LOGM, NT>(streams, 1u, 1, listed<G>(t, piece, aligned, tid), tb, a, hdr, out, 1.0f,
+    decompress_workgroup<LOGM, NT>(streams, 1u, 1, listed<G>(t, piece, tid), tb, a, hdr, out, 1.0f,
                                    tensor_region<G>(a.S), a.S + 16u, 0, verdicts, lds, tid);
 }
 
 template <int TOP>
 __global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_decompress(PeerList streams, Tables tb, QuantizerArgs q,
-                                                                              HeaderInfo hdr, float* __restrict__ out, int aligned,
+                                                                              HeaderInfo hdr, float* __restrict__ out,
                                                                               uint32_t* __restrict__ ctl, StatusNote note,
                                                                               int clear, uint32_t* __restrict__ verdicts,
                                                                               TensorTable t)
@@ -1177,7 +1172,7 @@ __global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_decompress(P
     const TensorPiece piece = t.piece[blockIdx.x];
     const PackArgs a = pack_args_of(q, t, piece.logm);
 #define X(p) \
-    else if (p <= TOP && piece.logm == p) decompress_tensors<(p <= TOP ? p : 4)>(streams, t, piece, aligned, tb, a, hdr, out, verdicts, lds, tid);
+    else if (p <= TOP && piece.logm == p) decompress_tensors<(p <= TOP ? p : 4)>(streams, t, piece, tb, a, hdr, out, verdicts, lds, tid);
     if (false) {
     }
     FFTSP_CHUNK_SIZES(X)
@@ -1196,7 +1191,7 @@ __global__ __launch_bounds__(NT) void k_chunk_rfft(const float* __restrict__ in,
     const int tid = threadIdx.x;
     const size_t c0 = (size_t)blockIdx.x * G::T;
     load_chunk_twiddles<LOGM, NT>(tw, tb, tid);
-    forward_tile<G, LOGM>(in, UniformChunks(n, C, G::T, 2u * G::M, 0u, aligned), d, tw, tid);
+    forward_tile<G, LOGM>(in, UniformChunks(n, C, G::T, 2u * G::M, 0u, aligned), tb, d, tw, tid);
     __syncthreads();
     for (int w = tid; w < G::E; w += NT) {
         const int k = w & (G::M - 1), b = w >> LOGM;
@@ -1242,7 +1237,7 @@ __global__ __launch_bounds__(NT) void k_chunk_irfft(const float2* __restrict__ s
     const float scale = 1.0f / (float)(2 * G::M);
     fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
         const Span sp = UniformChunks(n, C, G::T, 2u * G::M, 0u, aligned).span(b);
-        store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, sp.pairs, make_float2(v.x * scale, v.y * scale));
+        store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, make_float2(v.x * scale, v.y * scale));
     });
 }
 
@@ -1481,10 +1476,10 @@ hipError_t launch_tensors_compress(const float* in, const TensorTable& t, uint32
     if (e != hipSuccess) return e;
     if (low)
         FFTSP_LAUNCH("tensors_compress", k_tensors_compress<11>, dim3(pieces), dim3(uniform_threads<11>()), lds, s, in,
-                     alignment(in), tb, q, stream, records, header_info(hdr, hdr.write_header), ctl, t);
+                     tb, q, stream, records, header_info(hdr, hdr.write_header), ctl, t);
     else
         FFTSP_LAUNCH("tensors_compress", k_tensors_compress<14>, dim3(pieces), dim3(uniform_threads<14>()), lds, s, in,
-                     alignment(in), tb, q, stream, records, header_info(hdr, hdr.write_header), ctl, t);
+                     tb, q, stream, records, header_info(hdr, hdr.write_header), ctl, t);
     return hipGetLastError();
 }
 
@@ -1501,10 +1496,10 @@ hipError_t launch_tensors_decompress(const uint8_t* stream, const TensorTable& t
     one.p[0] = stream;
     if (low)
         FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<11>, dim3(pieces), dim3(uniform_threads<11>()), lds, s, one, tb, q,
-                     header_info(hdr, hdr.write_header), out, alignment(out), ctl, note, clear, verdicts, t);
+                     header_info(hdr, hdr.write_header), out, ctl, note, clear, verdicts, t);
     else
         FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<14>, dim3(pieces), dim3(uniform_threads<14>()), lds, s, one, tb, q,
-                     header_info(hdr, hdr.write_header), out, alignment(out), ctl, note, clear, verdicts, t);
+                     header_info(hdr, hdr.write_header), out, ctl, note, clear, verdicts, t);
     return hipGetLastError();
 }
 

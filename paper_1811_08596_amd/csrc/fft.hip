@@ -159,16 +159,12 @@ __device__ __forceinline__ void fwd_a_tile(uint32_t t, uint32_t tiles, int logM,
 
 // Forward pass A: N1-point FFTs down the columns of the N1 x N2 view of z, for tiles of TA adjacent columns.
 // kWhole: every tile of this workgroup's run lies in a chunk that is wholly inside the input, and the input is
-// 16-byte aligned: two columns per 16-byte load, no guards.  kQuads: the input is aligned and ends on a multiple of four
-// samples: every 16-byte piece is inside or outside, and those outside read a valid address and count as zeros (tensors
-// that do not fill their chunk).  They become zeros on the way into LDS: choosing right behind the loads waits for them
-// before the stages they are to run beside (ResNet-50's long tensors 93 -> 79 us).  kGuarded: every element is loaded under a guard (other ragged ends, unaligned tensors).
+// 16-byte aligned: two columns per 16-byte load, no guards.  kGuarded: every element is loaded under a guard (ragged ends).
 // The variants are separate loops so that no branches stand between the unguarded ones' loads and their use.
-enum Reads { kGuarded, kWhole, kQuads };
+enum Reads { kGuarded, kWhole };
 template <int LOGN1, Reads MODE, bool HALF>
-__device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t first, size_t n, int logM,
-                                          typename Cx<HALF>::One* __restrict__ mid, const Tables& tb, int aligned,
-                                          uint32_t t, uint32_t tend, uint32_t tstep, float2* d, const float2* tw, int tid0,
+__device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t n, int logM,
+                                          typename Cx<HALF>::One* __restrict__ mid, const Tables& tb, uint32_t t, uint32_t tend, uint32_t tstep, float2* d, const float2* tw, int tid0,
                                           float in_scale)
 {
     constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE), PER2 = kLanePairs;
@@ -176,28 +172,13 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t f
     static_assert(LOGT >= 2 && (NT % (TA / 2)) == 0, "tile shape");
     const uint32_t M = 1u << logM, N2 = M >> LOGN1, tiles = N2 >> LOGT;
 
-    // 16-byte pieces of a chunk that exist
-    auto quads_of = [&](const Span& sp) __attribute__((always_inline)) {
-        const size_t left = sp.limit > sp.first ? (sp.limit - sp.first) >> 2 : 0;
-        return left < (size_t)(M >> 1) ? (uint32_t)left : M >> 1;
-    };
     // live = false: the tile does not exist; the fast loads are still issued, all to one valid address
     // part p of spread_parts(): loads q with q * parts / PER2 == p; prologue calls pass every part in turn
     auto load_tile = [&](float4 (&r)[PER2], uint32_t tile, int tid, bool live, int part) {
         // every tile lies in a real chunk, so the span needs no chunk count
-        const Span sp = chunk_span(first, n, tile / tiles, 2 * (size_t)M, aligned & 1);
+        const Span sp = chunk_span(0, n, tile / tiles, 2 * (size_t)M);
         const uint32_t col0 = tile_in_chunk(tile, tiles) << LOGT;
-        if constexpr (MODE == kQuads) {
-            const float4* src = live ? reinterpret_cast<const float4*>(in + sp.first) : reinterpret_cast<const float4*>(tb.hi);
-            const uint32_t quads = quads_of(sp);
-#pragma unroll
-            for (int q = 0; q < PER2; ++q) {
-                if (q * spread_parts<LOGN1>() / PER2 != part) continue;
-                const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
-                const uint32_t i = (uint32_t)n1 * (N2 >> 1) + (col0 >> 1) + bp;
-                r[q] = src[live && i < quads ? i : 0u];
-            }
-        } else if constexpr (MODE == kWhole) {
+        if constexpr (MODE == kWhole) {
             const float4* src = live ? reinterpret_cast<const float4*>(in + sp.first) + (col0 >> 1)
                                      : reinterpret_cast<const float4*>(tb.hi);
 #pragma unroll
@@ -212,22 +193,13 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t f
             for (int q = 0; q < PER2; ++q) {
                 const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
                 const size_t gi = sp.first + 2 * ((size_t)n1 * N2 + col0 + 2 * bp);
-                r[q] = join(load_pair(in, gi, sp.limit, sp.pairs), load_pair(in, gi + 2, sp.limit, sp.pairs));
+                r[q] = join(load_pair(in, gi, sp.limit), load_pair(in, gi + 2, sp.limit));
             }
         }
     };
     // r[q] holds rows (tid >> (LOGT-1)) + q * N1/8 of one column pair: the first stage runs on the way into LDS
     static_assert(PER2 == 8 && (NT >> (LOGT - 1)) == N1 / 8, "a lane's loads are the inputs of two radix-8 butterflies");
     auto fill = [&](float4 (&r)[PER2], uint32_t tile, int tid) {
-        if constexpr (MODE == kQuads) {  // here, where the loads have to have arrived anyway
-            const uint32_t quads = quads_of(chunk_span(first, n, tile / tiles, 2 * (size_t)M, aligned & 1));
-            const uint32_t at = (tile_in_chunk(tile, tiles) << LOGT) >> 1;
-#pragma unroll
-            for (int q = 0; q < PER2; ++q) {
-                const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
-                if ((uint32_t)n1 * (N2 >> 1) + at + (uint32_t)bp >= quads) r[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-        }
         first_stage_store<LOGT, false>(d, tid >> (LOGT - 1), 2 * (tid & (TA / 2 - 1)), r);
     };
     float4 r[PER2];
@@ -249,11 +221,10 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t f
     }
 }
 
-// The tiles of workgroup blk of a pass A over the chunks of in[first .. first + n), in chunks of 2^(logM+1).
+// The tiles of workgroup blk of a pass A over the chunks of in[0 .. n), in chunks of 2^(logM+1).
 // `aligned`: bit 0 = `in` is 8-byte aligned, bit 1 = 16-byte aligned.
-// LONG: one tensor, which may be much shorter than its chunk and start anywhere.
-template <int LOGN1, bool LONG, bool HALF>
-__device__ __forceinline__ void fwd_a_workgroup(uint32_t blk, const float* __restrict__ in, size_t first, size_t n, int logM,
+template <int LOGN1, bool HALF>
+__device__ __forceinline__ void fwd_a_workgroup(uint32_t blk, const float* __restrict__ in, size_t n, int logM,
                                                 typename Cx<HALF>::One* __restrict__ mid, const Tables& tb, int aligned,
                                                 uint32_t total, uint32_t per_wg, int glog, float in_scale)
 {
@@ -267,13 +238,10 @@ __device__ __forceinline__ void fwd_a_workgroup(uint32_t blk, const float* __res
     load_stage_twiddles<LOGN1, NT>(tw, tb, tid0);
     const uint32_t tiles = (1u << logM) >> LOGE;  // tiles per chunk
     const size_t last_chunk_end = ((size_t)((tend - 1) / tiles) + 1) << (logM + 1);
-    const bool quads = (aligned & 2) && (first & 3u) == 0;
-    if (!LONG && quads && last_chunk_end <= n)
-        fwd_a_run<LOGN1, kWhole, HALF>(in, first, n, logM, mid, tb, aligned, t, tend, 1u << glog, d, tw, tid0, in_scale);
-    else if (LONG && quads && (n & 3u) == 0)
-        fwd_a_run<LOGN1, kQuads, HALF>(in, first, n, logM, mid, tb, aligned, t, tend, 1u << glog, d, tw, tid0, in_scale);
+    if ((aligned & 2) && last_chunk_end <= n)
+        fwd_a_run<LOGN1, kWhole, HALF>(in, n, logM, mid, tb, t, tend, 1u << glog, d, tw, tid0, in_scale);
     else
-        fwd_a_run<LOGN1, kGuarded, HALF>(in, first, n, logM, mid, tb, aligned, t, tend, 1u << glog, d, tw, tid0, in_scale);
+        fwd_a_run<LOGN1, kGuarded, HALF>(in, n, logM, mid, tb, t, tend, 1u << glog, d, tw, tid0, in_scale);
 }
 
 template <int LOGN1, bool HALF>
@@ -286,7 +254,7 @@ __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __re
     if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
     // clears the status words and key histograms the next kernels of the sender accumulate into
     for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < zero_words; i += gridDim.x * NT) zero_ptr[i] = 0u;
-    fwd_a_workgroup<LOGN1, false, HALF>(blockIdx.x, in, 0, n, logM, mid, tb, aligned, total, per_wg, glog, in_scale);
+    fwd_a_workgroup<LOGN1, HALF>(blockIdx.x, in, n, logM, mid, tb, aligned, total, per_wg, glog, in_scale);
 }
 
 
@@ -295,7 +263,8 @@ __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __re
 // are read 64 bytes wide instead of 32.  What it costs is LDS instructions of four bytes instead of eight, and the persistent kernel's loads ahead.
 // The same radices, twiddles and order of operations as fwd_a_run and fwd_a_tile: the bits are the same.
 // Calls in us, persistent / this, 2^22 by number of tiles of 2^14: binary32 512 120.7 / 119.7, 1024 208 / 222, 1280 242.6 / 241.8, 1536 281 / 284,
-//   1920 354.8 / 348.1, 3072 582 / 578, 4224 (138 M samples) 817.7 / 759.5, kernel 330 / 264;  binary16 1024 176 / 187, 1280 209 / 205, 1536 246 / 242.5,
+//   1920 354.8 / 348.1, 3072 582 / 578, 4224 (138 M samples) 817.7 / 759.5, kernel 330 / 264 (with reads that ask for no alignment and leave out a
+//   branch 230 -> 220);  binary16 1024 176 / 187, 1280 209 / 205, 1536 246 / 242.5,
 //   1920 302 / 289.  Columns of 2^10, tiles of 2^13, binary16: 512 93.7 / 97.4, 640 120.5 / 121.1, 1024 146.4 / 144.7, 1280 173.5 / 172.7, 1920 261.1 / 253.2 and
 //   (2^21) 272.7 / 265.9; binary32 1920 313.7 / 317.1, and with tiles of 2^14 326.  Shorter columns: equal at best.
 template <bool HALF>
@@ -359,39 +328,37 @@ struct SplitTile {
 };
 
 // One tile, columns col0 .. of a chunk whose samples are `sp` and whose intermediate is `mid`; d: 2^LOGE words; tw: the stage twiddles, which
-// other lanes may still be writing.  quads: every 16-byte piece is inside the input or outside it.
+// other lanes may still be writing.
 template <int LOGN1, int LOGE, bool HALF>
-__device__ __forceinline__ void fwd_a_split(const float* __restrict__ in, const Span& sp, bool quads, int logM, typename Cx<HALF>::One* __restrict__ mid,
+__device__ __forceinline__ void fwd_a_split(const float* __restrict__ in, const Span& sp, int logM, typename Cx<HALF>::One* __restrict__ mid,
                                             const Tables& tb, uint32_t col0, float* d, const float2* tw, int tid, float in_scale)
 {
     using G = SplitTile<LOGN1, LOGE>;
     constexpr int N1 = G::N1, HP = G::HP, T = G::T;
     const uint32_t M = 1u << logM, N2 = M >> LOGN1;
     const int bp = tid & (T / 2 - 1), j0 = tid >> (G::LOGT - 1);
+    const size_t left = sp.limit > sp.first ? sp.limit - sp.first : 0;
+    const uint32_t end = left >> 2 < (size_t)(M >> 1) ? (uint32_t)(left >> 2) : M >> 1;  // pieces of four samples that are whole
+    const float* src = end ? in + sp.first : reinterpret_cast<const float*>(tb.hi);
+    auto piece = [&](int q) __attribute__((always_inline)) { return (uint32_t)(j0 + q * (N1 / 8)) * (N2 >> 1) + (col0 >> 1) + (uint32_t)bp; };
     float2 v[16];
-    if (quads) {
-        const size_t left = sp.limit > sp.first ? (sp.limit - sp.first) >> 2 : 0;
-        const uint32_t end = left < (size_t)(M >> 1) ? (uint32_t)left : M >> 1;
-        const float4* src = end ? reinterpret_cast<const float4*>(in + sp.first) : reinterpret_cast<const float4*>(tb.hi);
-        float4 r[8];
+    Floats4 r[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const uint32_t i = (uint32_t)(j0 + q * (N1 / 8)) * (N2 >> 1) + (col0 >> 1) + (uint32_t)bp;
-            r[q] = src[i < end ? i : 0u];
-        }
+    for (int q = 0; q < 8; ++q) r[q] = *reinterpret_cast<const Floats4*>(src + 4 * (size_t)(piece(q) < end ? piece(q) : 0u));
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const bool there = (uint32_t)(j0 + q * (N1 / 8)) * (N2 >> 1) + (col0 >> 1) + (uint32_t)bp < end;
-            v[q] = there ? lo2(r[q]) : make_float2(0.f, 0.f);
-            v[8 + q] = there ? hi2(r[q]) : make_float2(0.f, 0.f);
-        }
-    } else {
+    for (int q = 0; q < 8; ++q) {
+        const bool there = piece(q) < end;
+        v[q] = there ? make_float2(r[q][0], r[q][1]) : make_float2(0.f, 0.f);
+        v[8 + q] = there ? make_float2(r[q][2], r[q][3]) : make_float2(0.f, 0.f);
+    }
+    if ((left & 3u) != 0 && end < M >> 1) {  // the piece that the end cuts
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const size_t gi = sp.first + 2 * ((size_t)(j0 + q * (N1 / 8)) * N2 + col0 + 2 * bp);
-            v[q] = load_pair(in, gi, sp.limit, sp.pairs);
-            v[8 + q] = load_pair(in, gi + 2, sp.limit, sp.pairs);
-        }
+        for (int q = 0; q < 8; ++q)
+            if (piece(q) == end) {
+                const size_t gi = sp.first + 4 * (size_t)end;
+                v[q] = load_pair(in, gi, sp.limit);
+                v[8 + q] = load_pair(in, gi + 2, sp.limit);
+            }
     }
     bf8<false>(v);
     bf8<false>(v + 8);
@@ -448,7 +415,7 @@ __device__ __forceinline__ void fwd_a_split(const float* __restrict__ in, const 
 
 template <int LOGN1, int LOGE, bool HALF>
 __global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fwd_a_split(
-    const float* __restrict__ in, size_t n, int logM, typename Cx<HALF>::One* __restrict__ mid, Tables tb, int aligned, uint32_t total,
+    const float* __restrict__ in, size_t n, int logM, typename Cx<HALF>::One* __restrict__ mid, Tables tb, uint32_t total,
     uint32_t* __restrict__ zero_ptr, uint32_t zero_words, float in_scale)
 {
     using G = SplitTile<LOGN1, LOGE>;
@@ -462,10 +429,9 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_e
     if (t >= total) return;
     const int log_tiles = logM - LOGE;
     const uint32_t c = t >> log_tiles;
-    const Span sp = chunk_span(0, n, c, (size_t)2 << logM, aligned & 1);
-    const bool quads = (aligned & 2) && (sp.first + ((size_t)2 << logM) <= n || (n & 3u) == 0);
+    const Span sp = chunk_span(0, n, c, (size_t)2 << logM);
     load_stage_twiddles<LOGN1, G::NT>(tw, tb, tid);
-    fwd_a_split<LOGN1, LOGE, HALF>(in, sp, quads, logM, mid + ((size_t)c << logM), tb, (t & ((1u << log_tiles) - 1u)) << G::LOGT, d, tw, tid, in_scale);
+    fwd_a_split<LOGN1, LOGE, HALF>(in, sp, logM, mid + ((size_t)c << logM), tb, (t & ((1u << log_tiles) - 1u)) << G::LOGT, d, tw, tid, in_scale);
 }
 
 // Forward pass B: N2-point FFTs along n2 for a tile of rows and their mirrors, then the real-FFT split.
@@ -1001,7 +967,7 @@ __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<
         run_fft_between<LOGN1, LOGT, NT, true, 0>(d, tw, tid, [&](int k) {
             if (k + 1 < PARTS) load_tile(more ? t + tstep : t, tid, more, k + 1);
         });
-        const Span sp = chunk_span(0, n, t / tiles, 2 * (size_t)M, aligned & 1);
+        const Span sp = chunk_span(0, n, t / tiles, 2 * (size_t)M);
         const size_t cbase = sp.first;
         const uint32_t col0 = tile_in_chunk(t, tiles) << LOGT;
         if ((aligned & 2) && (cbase & 3u) == 0 && (cbase + 2 * (size_t)M <= sp.limit || (sp.limit & 3u) == 0)) {
@@ -1022,8 +988,8 @@ __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<
                 const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGT - 1);
                 const float4 v = lds_load2<LOGT>(d, n1, 2 * bp);
                 const size_t gi = cbase + 2 * ((size_t)n1 * N2 + col0 + 2 * bp);
-                store_pair(out, gi, sp.limit, sp.pairs, make_float2(v.x * scale, v.y * scale));
-                store_pair(out, gi + 2, sp.limit, sp.pairs, make_float2(v.z * scale, v.w * scale));
+                store_pair(out, gi, sp.limit, make_float2(v.x * scale, v.y * scale));
+                store_pair(out, gi + 2, sp.limit, make_float2(v.z * scale, v.w * scale));
             }
         }
         if (!more) break;
@@ -1087,27 +1053,17 @@ struct SplitInverse {
         }
     }
 };
-// Four, or two, neighbouring samples wherever they start, those that are there: most tensors start at any multiple of four bytes.  One instruction, since
-// lanes that store a float at a time touch every line many times (receivers: 37 tensors of up to 4 M samples 101.5 -> 90.9 us, 33 of up to 1.7 M 71.3 -> 67.3,
+// Four neighbouring samples wherever they start, those that are there, in one instruction (receivers: 37 tensors of up to 4 M samples 101.5 -> 90.9 us, 33 of up to 1.7 M 71.3 -> 67.3,
 // 66 of up to 2.4 M 105.7 -> 101.4).
 __device__ __forceinline__ void store_floats(float* __restrict__ out, size_t gi, size_t limit, float4 z)
 {
-    using F4 = float __attribute__((ext_vector_type(4), aligned(4)));
     if (gi + 4 <= limit) {
-        *reinterpret_cast<F4*>(out + gi) = F4{z.x, z.y, z.z, z.w};
+        *reinterpret_cast<Floats4*>(out + gi) = Floats4{z.x, z.y, z.z, z.w};
     } else {
         if (gi < limit) out[gi] = z.x;
         if (gi + 1 < limit) out[gi + 1] = z.y;
         if (gi + 2 < limit) out[gi + 2] = z.z;
     }
-}
-__device__ __forceinline__ void store_floats(float* __restrict__ out, size_t gi, size_t limit, float2 z)
-{
-    using F2 = float __attribute__((ext_vector_type(2), aligned(4)));
-    if (gi + 2 <= limit)
-        *reinterpret_cast<F2*>(out + gi) = F2{z.x, z.y};
-    else if (gi < limit)
-        out[gi] = z.x;
 }
 // TOP: 2^(TOP - LOGE) tiles beside each other, each with words d of its own, share the stage twiddles
 template <int LOGN1, int LOGE, bool HALF, bool ONCE, int TOP = LOGE>
@@ -1180,7 +1136,7 @@ __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __rest
             const uint32_t i = (uint32_t)((tid >> LOGT) + n * (N1 / 16)) * N2 + col0 + (uint32_t)b;
             const float2 z = make_float2(v[n].x * scale, v[n].y * scale);
             if (!quads)
-                store_floats(out, sp.first + 2 * (size_t)i, sp.limit, z);
+                store_pair(out, sp.first + 2 * (size_t)i, sp.limit, z);
             else if (i < 2 * end)
                 dst[i] = z;
         }
@@ -1228,7 +1184,7 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_e
     if (t >= total) return;
     const int log_tiles = logM - LOGE;
     const uint32_t c = t >> log_tiles;
-    const Span sp = chunk_span(0, n, c, (size_t)2 << logM, aligned & 1);
+    const Span sp = chunk_span(0, n, c, (size_t)2 << logM);
     const bool quads = (aligned & 2) && (sp.first + ((size_t)2 << logM) <= n || (n & 3u) == 0);
     inv_a_split<LOGN1, LOGE, HALF, ONCE>(mid + ((size_t)c << logM), logM, out, sp, quads, tb, (t & ((1u << log_tiles) - 1u)) << G::LOGT,
                                    reinterpret_cast<float*>(smem), smem + (1 << LOGE) / 2, threadIdx.x, gain);
@@ -1247,26 +1203,38 @@ constexpr int kLongMax = kMaxLogL - 1;                            // log2 M
 
 __host__ __device__ __forceinline__ uint32_t power_tiles(int logM, int loge) { return 1u << (logM - loge); }
 
-__global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a_long(const float* __restrict__ in, float2* __restrict__ mid, Tables tb,
-                                                   int aligned, uint32_t per_wg, uint32_t* __restrict__ zero_ptr,
-                                                   uint32_t zero_words, LongTable tab, LongStarts at)
+// A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of up to 2^10.  Bound by memory, and by what few tiles to a
+// compute unit leave idle: a tile in half of the LDS has twice as many in flight as a persistent workgroup with one in all of it, which most launch
+// sets of tensors, with one or two tiles to a workgroup, paid for without having a next tile to load ahead; and tensors that start anywhere
+// are read 16 bytes at a time.  Pass in us, the persistent kernel / this: ResNet-50's 161 tensors 77 / 74, 100 of 10 to 2.4 M samples 58.6 / 53.4, 200
+// 138.5 / 110; senders 240 / 234, 193 / 181, 412 / 380, 24 tensors of 4.2 M padded samples 117 / 109.  Tiles of 2^14 for columns of 2^10: equal.
+template <int TOP>
+__global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fwd_a_split_long(
+    const float* __restrict__ in, float2* __restrict__ mid, Tables tb, uint32_t total, uint32_t* __restrict__ zero_ptr, uint32_t zero_words,
+    LongTable tab, LongStarts at)
 {
-    constexpr int NT = tile_lanes(kTileFA);
-    for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < zero_words; i += gridDim.x * NT) zero_ptr[i] = 0u;
-    const LongShare share = long_share(at);
+    extern __shared__ float2 smem[];
+    for (uint32_t i = blockIdx.x * tile_lanes(TOP) + threadIdx.x; i < zero_words; i += gridDim.x * tile_lanes(TOP)) zero_ptr[i] = 0u;
+    const uint32_t t = in_stretches(total);
+    if (t >= total) return;
+    const LongShare share = long_share(at, t);
     const LongTensor& x = tab.t[share.tensor];
     const int logM = x.logM;
+    const Span sp = chunk_span((size_t)x.goff, x.glen, 0, 0);
     auto run = [&](auto n1) __attribute__((always_inline)) {
-        constexpr int LOGN1 = decltype(n1)::value, GLOG = group_log(kTileFA, LOGN1);
-        fwd_a_workgroup<LOGN1, true, false>(share.blk, in, (size_t)x.goff, x.glen, logM, mid + long_mid(x), tb, aligned,
-                                            power_tiles(logM, kTileFA) >> GLOG, per_wg, GLOG, 1.0f);
+        constexpr int LOGN1 = decltype(n1)::value, LOGE = LOGN1 > 10 ? TOP : 13;
+        using G = SplitTile<LOGN1, LOGE>;
+        const uint32_t sub = LOGE < TOP ? (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / G::NT) : 0u, tile = (share.blk << (TOP - LOGE)) + sub;
+        float2* const tw = smem + (1 << TOP) / 2;
+        load_stage_twiddles<LOGN1, tile_lanes(TOP)>(tw, tb, (int)threadIdx.x);
+        fwd_a_split<LOGN1, LOGE, false>(in, sp, logM, mid + long_mid(x), tb, tile << G::LOGT, reinterpret_cast<float*>(smem) + (sub << LOGE), tw,
+                                        (int)threadIdx.x & (G::NT - 1), 1.0f);
     };
-    switch (log_columns(logM)) {
-        case 8: return run(std::integral_constant<int, 8>{});
-        case 9: return run(std::integral_constant<int, 9>{});
-        case 10: return run(std::integral_constant<int, 10>{});
-        default: return run(std::integral_constant<int, 11>{});
-    }
+    const int columns = log_columns(logM);
+    if (columns == 8) return run(std::integral_constant<int, 8>{});
+    if (columns == 9) return run(std::integral_constant<int, 9>{});
+    if (TOP == 13 || columns == 10) return run(std::integral_constant<int, 10>{});
+    if constexpr (TOP == 14) run(std::integral_constant<int, 11>{});
 }
 
 template <int LOGE>
@@ -1325,7 +1293,7 @@ __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu
     const LongShare share = long_share(at, t);
     const LongTensor& x = tab.t[share.tensor];
     const int logM = x.logM;
-    const Span sp{(size_t)x.goff, (size_t)x.goff + x.glen, (aligned & 1) && !(x.goff & 1u)};
+    const Span sp = chunk_span((size_t)x.goff, x.glen, 0, 0);
     const bool quads = (aligned & 2) && (x.goff & 3u) == 0 && (x.glen & 3u) == 0;
     auto run = [&](auto n1) __attribute__((always_inline)) {
         constexpr int LOGN1 = decltype(n1)::value, LOGE = LOGN1 >= 10 ? TOP : 13;
@@ -1383,7 +1351,7 @@ Grid grouped_grid(size_t groups, int glog, uint32_t kMaxWgs = 512)
 }
 
 template <int LOGN1, int LOGE, bool HALF>
-hipError_t fwd_a_halved(const float* in, size_t n, int logM, size_t C, typename Cx<HALF>::One* mid, Tables t, int aligned, uint32_t* zero_ptr,
+hipError_t fwd_a_halved(const float* in, size_t n, int logM, size_t C, typename Cx<HALF>::One* mid, Tables t, uint32_t* zero_ptr,
                         uint32_t zero_words, float in_scale, hipStream_t s)
 {
     using G = SplitTile<LOGN1, LOGE>;
@@ -1391,8 +1359,8 @@ hipError_t fwd_a_halved(const float* in, size_t n, int logM, size_t C, typename 
     const hipError_t e = set_lds(kern, G::kLds);
     if (e != hipSuccess) return e;
     const size_t total = C << (logM - LOGE);
-    FFTSP_LAUNCH("rfft_pass_a", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(G::NT), G::kLds, s, in, n, logM, mid, t, aligned, (uint32_t)total,
-                 zero_ptr, zero_words, in_scale);
+    FFTSP_LAUNCH("rfft_pass_a", kern, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(G::NT), G::kLds, s, in, n, logM, mid, t, (uint32_t)total, zero_ptr,
+                 zero_words, in_scale);
     return hipGetLastError();
 }
 // HALF launchers take the same buffer pointers; the kernels read them as binary16 pairs
@@ -1408,9 +1376,9 @@ hipError_t fwd_a(const float* in, size_t n, int logM, size_t C, float2* mid_f32,
     hipError_t e = set_lds(kern, lds);
     if (e != hipSuccess) return e;
     if constexpr (LOGN1 == 11)
-        if (!only_if && wide_tiles(C, logM) >= kSplitForward<HALF>) return fwd_a_halved<LOGN1, 14, HALF>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, in_scale, s);
+        if (!only_if && wide_tiles(C, logM) >= kSplitForward<HALF>) return fwd_a_halved<LOGN1, 14, HALF>(in, n, logM, C, mid, t, zero_ptr, zero_words, in_scale, s);
     if constexpr (LOGN1 == 10 && HALF)
-        if (!only_if && wide_tiles(C, logM) >= 1024) return fwd_a_halved<LOGN1, 13, HALF>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, in_scale, s);
+        if (!only_if && wide_tiles(C, logM) >= 1024) return fwd_a_halved<LOGN1, 13, HALF>(in, n, logM, C, mid, t, zero_ptr, zero_words, in_scale, s);
     const size_t total = C * (((size_t)1 << (logM - LOGN1)) >> (LOGE - LOGN1));
     constexpr int glog = group_log(LOGE, LOGN1);  // a chunk has at least that many tiles
     // measured: 143 us against 149 with 512; a stand-by launch (only_if) takes the small grid, which leaves sooner
@@ -1623,14 +1591,6 @@ hipError_t by_tile_size(const LongBatch& b, uint32_t wide, Pass&& pass)
 constexpr int kLongLogN = log_columns(kLongMax);  // the longest row or column
 // LDS of a pass: the tile and the stage twiddles
 constexpr size_t long_lds(int loge) { return ((size_t)(1 << loge) + (1 << kLongLogN)) * sizeof(float2); }
-// workgroups of a tensor in a pass A (see grouped_grid)
-uint32_t pass_a_wgs(const LongTensor& x, int loge, uint32_t per_wg)
-{
-    const int glog = group_log(loge, log_columns(x.logM));
-    const uint32_t groups = (1u << (x.logM - loge)) >> glog, used = (groups + per_wg - 1) / per_wg, unit = 8u << glog;
-    return (((used << glog) + unit - 1) / unit) * unit;
-}
-
 }  // namespace
 
 int fft_pair_log(int logL)
@@ -1745,15 +1705,19 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
 {
     if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors || zero_words > 0xffffffffu) return hipErrorInvalidValue;
     if (short_forward(b)) return launch_short_rfft_long(in, b, spec, mid, t, hist, zero_ptr, (uint32_t)zero_words, s);
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(in);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
     LongStarts at;
-    hipError_t e = set_lds(k_fwd_a_long, long_lds(kTileFA));
+    auto pass_a = [&](auto size) {
+        constexpr int TOP = decltype(size)::value;
+        constexpr size_t lds = SplitTile<TOP == 14 ? 11 : 10, TOP>::kLds;
+        const hipError_t err = set_lds(k_fwd_a_split_long<TOP>, lds);
+        if (err != hipSuccess) return err;
+        const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, TOP); });
+        FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_split_long<TOP>, dim3((total + 7) / 8 * 8), dim3(tile_lanes(TOP)), lds, s, in, mid, t, total, zero_ptr,
+                     (uint32_t)zero_words, b.tab, at);
+        return hipGetLastError();
+    };
+    const hipError_t e = log_columns(b.tab.t[b.count - 1].logM) <= 10 ? pass_a(std::integral_constant<int, 13>{}) : pass_a(std::integral_constant<int, 14>{});
     if (e != hipSuccess) return e;
-    const uint32_t run = long_run(b, 0, b.count, kTileFA, kPassAWgs);
-    const uint32_t wgs = long_starts(b, 0, b.count, &at, [&](const LongTensor& x) { return pass_a_wgs(x, kTileFA, run); });
-    FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long, dim3(wgs), dim3(tile_lanes(kTileFA)), long_lds(kTileFA), s, in, mid, t, aligned, run,
-                 zero_ptr, (uint32_t)zero_words, b.tab, at);
     const uint32_t wide = first_wide(b, log_rows, kWideForward, kWideForwardBeside);
     return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
         constexpr int LOGE = decltype(size)::value;

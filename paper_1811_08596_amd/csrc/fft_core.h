@@ -392,40 +392,69 @@ __device__ __forceinline__ void load_stage_twiddles(float2* tw, const Tables& tb
     }
 }
 
-__device__ __forceinline__ float2 load_pair(const float* __restrict__ in, size_t gi, size_t n, int aligned)
+// Neighbouring samples wherever they start: accesses of 8 and 16 bytes need an alignment of four.  Most tensors start at any multiple of
+// four bytes, and lanes that move a float at a time touch every line many times.
+using Floats2 = float __attribute__((ext_vector_type(2), aligned(4)));
+using Floats4 = float __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float2 load_pair(const float* __restrict__ in, size_t gi, size_t n)
 {
     if (gi + 1 < n) {
-        if (aligned) return *reinterpret_cast<const float2*>(in + gi);
-        return make_float2(in[gi], in[gi + 1]);
+        const Floats2 v = *reinterpret_cast<const Floats2*>(in + gi);
+        return make_float2(v[0], v[1]);
     }
     if (gi < n) return make_float2(in[gi], 0.f);
     return make_float2(0.f, 0.f);
 }
 
-__device__ __forceinline__ void store_pair(float* __restrict__ out, size_t gi, size_t n, int aligned, float2 v)
+// Where chunk c's samples live: elements [first, limit) of the gradient.
+struct Span {
+    size_t first, limit;
+};
+// Pairs at + t * step of a span of at most `all` of them, zeros behind its end.  No load stands in a branch but that of a pair cut in two,
+// so that all are on their way together; those that do not exist read a table.
+template <int N>
+__device__ __forceinline__ void load_pairs(float2 (&v)[N], const float* __restrict__ in, const Span& sp, uint32_t all, uint32_t at, uint32_t step,
+                                           const Tables& tb)
 {
-    if (gi + 1 < n) {
-        if (aligned)
-            *reinterpret_cast<float2*>(out + gi) = v;
-        else {
-            out[gi] = v.x;
-            out[gi + 1] = v.y;
+    const size_t left = sp.limit > sp.first ? sp.limit - sp.first : 0;
+    const uint32_t whole = left >> 1 < all ? (uint32_t)(left >> 1) : all;
+    const float* src = whole ? in + sp.first : reinterpret_cast<const float*>(tb.hi);
+    Floats2 r[N];
+    if (whole == all) {
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            r[t] = *reinterpret_cast<const Floats2*>(src + 2 * (size_t)(at + (uint32_t)t * step));
+            v[t] = make_float2(r[t][0], r[t][1]);
         }
-    } else if (gi < n) {
-        out[gi] = v.x;
+        return;
+    }
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        const uint32_t i = at + (uint32_t)t * step;
+        r[t] = *reinterpret_cast<const Floats2*>(src + 2 * (size_t)(i < whole ? i : 0u));
+    }
+#pragma unroll
+    for (int t = 0; t < N; ++t) v[t] = at + (uint32_t)t * step < whole ? make_float2(r[t][0], r[t][1]) : make_float2(0.f, 0.f);
+    if (left & 1u) {
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+            if (at + (uint32_t)t * step == whole) v[t].x = in[sp.limit - 1];
     }
 }
 
-
-// Where chunk c's samples live: elements [first, limit) of the gradient; pairs != 0 allows 8-byte accesses.
-struct Span {
-    size_t first, limit;
-    int pairs;
-};
-// what a launch covers: samples [first, first + count), cut into chunks
-__device__ __forceinline__ Span chunk_span(size_t first, size_t count, size_t c, size_t chunk_len, int aligned8)
+__device__ __forceinline__ void store_pair(float* __restrict__ out, size_t gi, size_t n, float2 v)
 {
-    return Span{first + c * chunk_len, first + count, aligned8 && !(first & 1u)};
+    if (gi + 1 < n)
+        *reinterpret_cast<Floats2*>(out + gi) = Floats2{v.x, v.y};
+    else if (gi < n)
+        out[gi] = v.x;
+}
+
+
+// what a launch covers: samples [first, first + count), cut into chunks
+__device__ __forceinline__ Span chunk_span(size_t first, size_t count, size_t c, size_t chunk_len)
+{
+    return Span{first + c * chunk_len, first + count};
 }
 
 // X[k] from a = Z[k], b = Z[M-k], w = W_L^k   (0 < k < M); times 2 half, a power of two

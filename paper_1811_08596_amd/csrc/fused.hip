@@ -227,7 +227,7 @@ __device__ __forceinline__ void fused_fwd_run(const float* __restrict__ in, size
             for (int q = 0; q < PER2; ++q) {
                 const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGTA - 1);
                 const size_t gi = first + 2 * ((size_t)n1 * N2 + col0 + 2 * bp);
-                r[q] = join(load_pair(in, gi, n, aligned & 1), load_pair(in, gi + 2, n, aligned & 1));
+                r[q] = join(load_pair(in, gi, n), load_pair(in, gi + 2, n));
             }
         }
     };
@@ -635,8 +635,8 @@ __device__ __forceinline__ void fused_inv_run(const float2* __restrict__ spec, u
                     const int w = tid + q * NT, bp = w & (TA / 2 - 1), n1 = w >> (LOGTA - 1);
                     const float4 v = lds_load2<LOGTA>(d, n1, 2 * bp);
                     const size_t gi = cbase + 2 * ((size_t)n1 * N2 + col0 + 2 * bp);
-                    store_pair(out, gi, n, aligned & 1, make_float2(v.x * scale, v.y * scale));
-                    store_pair(out, gi + 2, n, aligned & 1, make_float2(v.z * scale, v.w * scale));
+                    store_pair(out, gi, n, make_float2(v.x * scale, v.y * scale));
+                    store_pair(out, gi + 2, n, make_float2(v.z * scale, v.w * scale));
                 }
             }
             __syncthreads();

@@ -65,15 +65,7 @@ __device__ __forceinline__ void fwd_a_short(uint32_t tile, const float* __restri
     float2 v[8];
     const int slot = tid & (T - 1), j = tid >> LOGT;
     static_assert((NT >> LOGT) == N1 / 8, "a lane's loads are the inputs of a radix-8 butterfly");
-    const size_t first = sp.first + 2 * ((size_t)j * N2 + cols.column((uint32_t)slot));
-    const size_t step = 2 * (size_t)(N1 / 8) * N2;
-    if (sp.pairs && sp.first + 2 * (size_t)M <= sp.limit) {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = *reinterpret_cast<const float2*>(in + first + t * step);
-    } else {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = load_pair(in, first + t * step, sp.limit, sp.pairs);
-    }
+    load_pairs(v, in, sp, M, (uint32_t)j * N2 + cols.column((uint32_t)slot), (uint32_t)(N1 / 8) * N2, tb);
     const int sh = 22 - logM;
     float2 cur_a[KN], cur_b[KN], ratio_a[KN], ratio_b[KN];
 #pragma unroll
@@ -158,8 +150,8 @@ __device__ __forceinline__ void inv_a_short(uint32_t tile, const typename Cx<HAL
         if (quads_ok && 4 * (size_t)i + 4 <= left) {
             reinterpret_cast<float4*>(out + sp.first)[i] = s;
         } else {
-            store_pair(out, sp.first + 4 * (size_t)i, sp.limit, sp.pairs, lo2(s));
-            store_pair(out, sp.first + 4 * (size_t)i + 2, sp.limit, sp.pairs, hi2(s));
+            store_pair(out, sp.first + 4 * (size_t)i, sp.limit, lo2(s));
+            store_pair(out, sp.first + 4 * (size_t)i + 2, sp.limit, hi2(s));
         }
     }
 }
@@ -441,13 +433,13 @@ __device__ __forceinline__ uint32_t beside()
 // chunks of one length: a workgroup per tile, `tiles` (a power of two) of them to a chunk
 template <int LOGN1, bool HALF>
 __global__ __launch_bounds__(short_lanes_a(LOGN1)) void k_fwd_a_short(const float* __restrict__ in, size_t n, int logM,
-                                                          typename Cx<HALF>::One* __restrict__ mid, Tables tb, int aligned,
+                                                          typename Cx<HALF>::One* __restrict__ mid, Tables tb,
                                                           uint32_t* __restrict__ zero_ptr, uint32_t zero_words, float in_scale)
 {
     clear_words(zero_ptr, zero_words, short_lanes_a(LOGN1));
     const int log_tiles = logM - short_log_a(LOGN1);
     const uint32_t place = beside<ShortColumns<LOGN1>::LOGSPLIT>(), c = place >> log_tiles;
-    fwd_a_short<LOGN1, HALF>(place & ((1u << log_tiles) - 1u), in, chunk_span(0, n, c, (size_t)2 << logM, aligned & 1), logM,
+    fwd_a_short<LOGN1, HALF>(place & ((1u << log_tiles) - 1u), in, chunk_span(0, n, c, (size_t)2 << logM), logM,
                              mid + ((size_t)c << logM), tb, in_scale);
 }
 template <int LOGN1, bool HALF>
@@ -457,7 +449,7 @@ __global__ __launch_bounds__(short_lanes_a(LOGN1)) void k_inv_a_short(const type
     const int log_tiles = logM - short_log_a(LOGN1);
     const uint32_t place = beside<2>(), c = place >> log_tiles;
     inv_a_short<LOGN1, HALF>(place & ((1u << log_tiles) - 1u), mid + ((size_t)c << logM), logM, out,
-                             chunk_span(0, n, c, (size_t)2 << logM, aligned & 1), tb, (aligned & 2) != 0, gain);
+                             chunk_span(0, n, c, (size_t)2 << logM), tb, (aligned & 2) != 0, gain);
 }
 template <int LOGN2, bool CODEC, bool HALF>
 __global__ __launch_bounds__(1 << LOGN2) void k_fwd_b_short(const typename Cx<HALF>::One* __restrict__ mid, int logM,
@@ -495,14 +487,14 @@ __global__ __launch_bounds__(1 << LOGN2) void k_decode_inv_b(const uint8_t* __re
 constexpr int short_columns(int logM) { return (logM + 1) / 2; }
 constexpr int short_rows(int logM) { return logM / 2; }
 constexpr int kShortMostA = short_lanes_a(10);
-__global__ __launch_bounds__(kShortMostA) void k_fwd_a_long_short(const float* __restrict__ in, float2* __restrict__ mid, Tables tb, int aligned,
+__global__ __launch_bounds__(kShortMostA) void k_fwd_a_long_short(const float* __restrict__ in, float2* __restrict__ mid, Tables tb,
                                                                uint32_t* __restrict__ zero_ptr, uint32_t zero_words, LongTable tab,
                                                                LongStarts at)
 {
     clear_words(zero_ptr, zero_words, (int)blockDim.x);
     const LongShare share = long_share(at);
     const LongTensor& x = tab.t[share.tensor];
-    const Span sp = chunk_span((size_t)x.goff, x.glen, 0, 0, aligned & 1);
+    const Span sp = chunk_span((size_t)x.goff, x.glen, 0, 0);
     float2* to = mid + long_mid(x);
     if (threadIdx.x >= (uint32_t)short_lanes_a(short_columns(x.logM))) return;
     switch (short_columns(x.logM)) {
@@ -516,7 +508,7 @@ __global__ __launch_bounds__(kShortMostA) void k_inv_a_long_short(const float2* 
 {
     const LongShare share = long_share(at);
     const LongTensor& x = tab.t[share.tensor];
-    const Span sp = chunk_span((size_t)x.goff, x.glen, 0, 0, aligned & 1);
+    const Span sp = chunk_span((size_t)x.goff, x.glen, 0, 0);
     const bool quads = (aligned & 2) && (sp.first & 3u) == 0;
     const float2* from = mid + long_mid(x);
     if (threadIdx.x >= (uint32_t)short_lanes_a(short_columns(x.logM))) return;
@@ -608,11 +600,11 @@ constexpr size_t lds_b(int logn2, bool hist)
 }
 
 template <int LOGN1, bool HALF>
-hipError_t launch_a_fwd(const float* in, size_t n, int logM, size_t C, float2* mid, Tables t, int aligned, uint32_t* zero_ptr,
+hipError_t launch_a_fwd(const float* in, size_t n, int logM, size_t C, float2* mid, Tables t, uint32_t* zero_ptr,
                         uint32_t zero_words, float in_scale, hipStream_t s)
 {
     FFTSP_LAUNCH("rfft_pass_a", (k_fwd_a_short<LOGN1, HALF>), dim3((unsigned)(C << (logM - short_log_a(LOGN1)))), dim3(short_lanes_a(LOGN1)), lds_a(LOGN1), s,
-                 in, n, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, aligned, zero_ptr, zero_words, in_scale);
+                 in, n, logM, reinterpret_cast<typename Cx<HALF>::One*>(mid), t, zero_ptr, zero_words, in_scale);
     return hipGetLastError();
 }
 template <int LOGN1, bool HALF>
@@ -669,11 +661,11 @@ hipError_t launch_b_decode(const uint8_t* stream, const CodecArgs& a, int logM, 
 }
 
 template <bool CODEC, bool HALF>
-hipError_t rfft_short(const float* in, size_t n, int logM, size_t C, float2* spec, uint32_t sstride, float2* mid, Tables t, int aligned,
+hipError_t rfft_short(const float* in, size_t n, int logM, size_t C, float2* spec, uint32_t sstride, float2* mid, Tables t,
                       uint32_t* hist, uint32_t* zero_ptr, uint32_t zero_words, float in_scale, float mid_scale, hipStream_t s)
 {
     hipError_t e = hipErrorInvalidValue;
-#define FWD_A(p) launch_a_fwd<p, HALF>(in, n, logM, C, mid, t, aligned, zero_ptr, zero_words, in_scale, s)
+#define FWD_A(p) launch_a_fwd<p, HALF>(in, n, logM, C, mid, t, zero_ptr, zero_words, in_scale, s)
     switch (short_columns(logM)) {
         case 8: e = FWD_A(8); break;
         case 9: e = FWD_A(9); break;
@@ -789,8 +781,8 @@ bool short_decode(const LongBatch& b) { return longest(b) <= kDecodeMost && tile
 hipError_t launch_short_rfft(const float* in, size_t n, int logM, size_t C, float2* spec, uint32_t sstride, float2* mid, Tables t,
                              uint32_t* hist, uint32_t* zero_ptr, uint32_t zero_words, hipStream_t s)
 {
-    return hist ? rfft_short<true, false>(in, n, logM, C, spec, sstride, mid, t, alignment(in), hist, zero_ptr, zero_words, 1.0f, 1.0f, s)
-                : rfft_short<false, false>(in, n, logM, C, spec, sstride, mid, t, alignment(in), nullptr, zero_ptr, 0u, 1.0f, 1.0f, s);
+    return hist ? rfft_short<true, false>(in, n, logM, C, spec, sstride, mid, t, hist, zero_ptr, zero_words, 1.0f, 1.0f, s)
+                : rfft_short<false, false>(in, n, logM, C, spec, sstride, mid, t, nullptr, zero_ptr, 0u, 1.0f, 1.0f, s);
 }
 hipError_t launch_short_inverse_b(const float2* spec, uint32_t sstride, int logM, size_t C, float2* mid, Tables t, int pair_spec,
                                   hipStream_t s)
@@ -810,7 +802,7 @@ hipError_t launch_short_inverse_a(const float2* mid, int logM, size_t C, float* 
 hipError_t launch_short_rfft_half(const float* in, size_t n, int logM, size_t C, float2* spec, uint32_t sstride, float2* mid, Tables t,
                                   uint32_t* hist, uint32_t* zero_ptr, uint32_t zero_words, float in_scale, float mid_scale, hipStream_t s)
 {
-    return rfft_short<true, true>(in, n, logM, C, spec, sstride, mid, t, alignment(in), hist, zero_ptr, zero_words, in_scale, mid_scale, s);
+    return rfft_short<true, true>(in, n, logM, C, spec, sstride, mid, t, hist, zero_ptr, zero_words, in_scale, mid_scale, s);
 }
 hipError_t launch_short_decode(const uint8_t* stream, const CodecArgs& a, int logM, float2* mid, Tables t, uint32_t* verdicts,
                                uint32_t* ctl, const StatusNote& note, hipStream_t s)
@@ -849,7 +841,7 @@ hipError_t launch_short_rfft_long(const float* in, const LongBatch& b, float2* s
     LongStarts at;
     const int top = short_columns(longest(b));
     uint32_t wgs = starts_of(b, &at, [](int logM) { return logM - short_log_a(short_columns(logM)); });
-    FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long_short, dim3(wgs), dim3(short_lanes_a(top)), lds_a(top), s, in, mid, t, alignment(in), zero_ptr, zero_words,
+    FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long_short, dim3(wgs), dim3(short_lanes_a(top)), lds_a(top), s, in, mid, t, zero_ptr, zero_words,
                  b.tab, at);
     wgs = starts_of(b, &at, [](int logM) { return logM - short_rows(logM) - kShortLogSlots; });
     auto pass_b = [&](auto top) {
