@@ -645,7 +645,8 @@ __device__ __forceinline__ void fwd_b_pairs(const typename Cx<HALF>::One* __rest
     const uint32_t M = 1u << logM, N1 = 1u << logN1, pp = pp0 + (uint32_t)p;
     Two raw[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) raw[q] = reinterpret_cast<const Two*>(mid)[((uint32_t)(kq + q * DK) << (logN1 - 1)) + pp];
+    for (int q = 0; q < 8; ++q)
+        raw[q] = *reinterpret_cast<const Two*>(reinterpret_cast<const uint8_t*>(mid) + (((uint32_t)(kq + q * DK) << (logN1 - 1)) + pp) * (uint32_t)sizeof(Two));
     load_stage_twiddles<LOGN2, NT>(tw, tb, tid);
     for (int i = 4 * lane; i < kHistLdsWords; i += 4 * LANES) *reinterpret_cast<uint4*>(h16 + i) = make_uint4(0u, 0u, 0u, 0u);
     // a wave has four rows of a pair in its lower lanes and their mirrors in the upper ones
@@ -653,9 +654,12 @@ __device__ __forceinline__ void fwd_b_pairs(const typename Cx<HALF>::One* __rest
     const MirroredRows<LOGN2> rows(pp, hi ? DK - 1 - low_row : low_row);
     // W_L^(k1 + N1*k2): k2 advances by N2/8 per step, i.e. by a sixteenth of a turn
     float2 base[2];
+    auto split_twiddles = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-        base[i] = twiddle(tb, ((rows.upper(i) ? mirror_row(pp, N1) : pp) + ((uint32_t)rows.at(i) << logN1)) << (21 - logM));
+        for (int i = 0; i < 2; ++i)
+            base[i] = twiddle(tb, ((rows.upper(i) ? mirror_row(pp, N1) : pp) + ((uint32_t)rows.at(i) << logN1)) << (21 - logM));
+    };
+    if constexpr (TOP < 10) split_twiddles();  // eight waves have no registers to hold them in meanwhile
     float2 v[16];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -678,6 +682,7 @@ __device__ __forceinline__ void fwd_b_pairs(const typename Cx<HALF>::One* __rest
         static_assert(G::RL3 == 0 || G::LAST == 3, "two butterflies of eight rows");
         G::template stage<false, 3 + G::RL2, G::LAST>(v, tw, [&](int q) __attribute__((always_inline)) { return rows.at(q); });
     }
+    if constexpr (TOP >= 10) split_twiddles();
     const float unlift = HALF ? mid_scale : 1.f, half = 0.5f * unlift;
     auto turned = [&](int i, int q) __attribute__((always_inline)) { return cmul(base[i], make_float2(kW32re[2 * q], kW32im[2 * q])); };
     auto count = [&](One st) __attribute__((always_inline)) {  // what the selection will read back
@@ -706,7 +711,9 @@ __device__ __forceinline__ void fwd_b_pairs(const typename Cx<HALF>::One* __rest
             put(1, q, split_fwd(v[8 + q], pb, turned(1, q), half));
         }
     } else {
-        Two* const out = reinterpret_cast<Two*>(spec);
+        auto put = [&](uint32_t i, Two z) __attribute__((always_inline)) {
+            *reinterpret_cast<Two*>(reinterpret_cast<uint8_t*>(spec) + i * (uint32_t)sizeof(Two)) = z;
+        };
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             __builtin_amdgcn_sched_barrier(0);
@@ -720,8 +727,8 @@ __device__ __forceinline__ void fwd_b_pairs(const typename Cx<HALF>::One* __rest
             swap_halves(xt, xu);
             swap_halves(yt, yu);
             const uint32_t q = (uint32_t)(hi ? u : t) * DK;
-            out[(((uint32_t)low_row + q) << (logN1 - 1)) + pp] = two_of(xt, yu);
-            out[(((uint32_t)(DK - 1 - low_row) + q) << (logN1 - 1)) + pp] = two_of(xu, yt);
+            put((((uint32_t)low_row + q) << (logN1 - 1)) + pp, two_of(xt, yu));
+            put((((uint32_t)(DK - 1 - low_row) + q) << (logN1 - 1)) + pp, two_of(xu, yt));
         }
     }
     __syncthreads();
@@ -745,10 +752,12 @@ __global__ __launch_bounds__(HalfTile<LOGN2>::NT) __attribute__((amdgpu_waves_pe
                              reinterpret_cast<uint32_t*>(smem), threadIdx.x, mid_scale);
 }
 
-// Tensors of different lengths: those with rows of up to 2^9, a workgroup does one tile of rows of 2^9, two of 2^8 or four of 2^7.
-constexpr int kPairsTop = 9;
-constexpr size_t kPairsLds = HalfTile<kPairsTop>::kLds + kHistLdsWords * sizeof(uint32_t);
-__global__ __launch_bounds__(HalfTile<kPairsTop>::NT) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_fwd_b_pairs_long(
+// Tensors of different lengths: a workgroup does one tile of rows of 2^TOP, two of half the length, four of a quarter, and so on.  Rows of 2^9 spill in
+// workgroups of sixteen waves, too (see fwd_b_pairs), and those of 2^10 in any; it is fewer tails that gain.
+template <int TOP>
+constexpr size_t kPairsLds = HalfTile<TOP>::kLds + kHistLdsWords * sizeof(uint32_t);
+template <int TOP>
+__global__ __launch_bounds__(HalfTile<TOP>::NT) __attribute__((amdgpu_waves_per_eu(TOP == 10 ? 8 : 6, TOP == 10 ? 8 : 6))) void k_fwd_b_pairs_long(
     const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb, uint32_t* __restrict__ hist, uint32_t total, LongTable tab, LongStarts at)
 {
     extern __shared__ float2 smem[];
@@ -757,16 +766,17 @@ __global__ __launch_bounds__(HalfTile<kPairsTop>::NT) __attribute__((amdgpu_wave
     const LongShare share = long_share(at, t);
     const LongTensor& x = tab.t[share.tensor];
     auto run = [&](auto n2) __attribute__((always_inline)) {
-        constexpr int LOGN2 = decltype(n2)::value, LOGSUB = kPairsTop - LOGN2;
+        constexpr int LOGN2 = decltype(n2)::value, LOGSUB = TOP - LOGN2;
         using G = HalfTile<LOGN2>;
         const uint32_t sub = LOGSUB ? (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / G::NT) : 0u, pp0 = ((share.blk << LOGSUB) + sub) * G::PAIRS;
-        fwd_b_pairs<LOGN2, false, kPairsTop>(mid + long_mid(x), x.logM, spec + long_spec(x, share.tensor), tb, hist + (size_t)share.tensor * kHistBins, pp0,
-                                  share.blk == 0, reinterpret_cast<uint32_t*>(smem), threadIdx.x, 1.0f);
+        fwd_b_pairs<LOGN2, false, TOP>(mid + long_mid(x), x.logM, spec + long_spec(x, share.tensor), tb, hist + (size_t)share.tensor * kHistBins, pp0,
+                                       share.blk == 0, reinterpret_cast<uint32_t*>(smem), threadIdx.x, 1.0f);
     };
     const int rows = x.logM / 2;
     if (rows == 7) return run(std::integral_constant<int, 7>{});
     if (rows == 8) return run(std::integral_constant<int, 8>{});
-    run(std::integral_constant<int, 9>{});
+    if (TOP == 9 || rows == 9) return run(std::integral_constant<int, 9>{});
+    if constexpr (TOP == 10) run(std::integral_constant<int, 10>{});
 }
 
 // Inverse pass B: undo the split, inverse N2-point FFTs over k2, times conj W_M^(n2 k1).
@@ -1202,6 +1212,7 @@ constexpr int log_rows(int logM) { return logM / 2; }           // log2 N2
 constexpr int kLongMax = kMaxLogL - 1;                            // log2 M
 
 __host__ __device__ __forceinline__ uint32_t power_tiles(int logM, int loge) { return 1u << (logM - loge); }
+constexpr int kTallTile = 14;  // of rows of 2^10, where a launch has no others
 
 // A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of up to 2^10.  Bound by memory, and by what few tiles to a
 // compute unit leave idle: a tile in half of the LDS has twice as many in flight as a persistent workgroup with one in all of it, which most launch
@@ -1237,26 +1248,15 @@ __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu
     if constexpr (TOP == 14) run(std::integral_constant<int, 11>{});
 }
 
-template <int LOGE>
-__global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b_long(const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb,
-                                                uint32_t* __restrict__ hist, uint32_t per_wg, LongTable tab, LongStarts at)
+// rows of 2^10
+__global__ __launch_bounds__(tile_lanes(kTallTile)) void k_fwd_b_long(const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb,
+                                                                     uint32_t* __restrict__ hist, uint32_t per_wg, LongTable tab, LongStarts at)
 {
     const LongShare share = long_share(at);
     const LongTensor& x = tab.t[share.tensor];
-    const int logM = x.logM;
-    auto run = [&](auto n2) __attribute__((always_inline)) {
-        const uint32_t total = power_tiles(logM, LOGE), per = per_wg < total ? per_wg : total;
-        fwd_b_workgroup<decltype(n2)::value, LOGE, true, false>(share.blk, total / per, mid + long_mid(x), logM,
-                                                                spec + long_spec(x, share.tensor), 0u, tb,
-                                                                hist + (size_t)share.tensor * kHistBins, total, per, 1.0f);
-    };
-    const int rows = log_rows(logM);
-    if constexpr (LOGE == 13) {
-        if (rows == 7) return run(std::integral_constant<int, 7>{});
-        if (rows == 8) return run(std::integral_constant<int, 8>{});
-        if (rows == 9) return run(std::integral_constant<int, 9>{});
-    }
-    run(std::integral_constant<int, 10>{});
+    const uint32_t total = power_tiles(x.logM, kTallTile), per = per_wg < total ? per_wg : total;
+    fwd_b_workgroup<10, kTallTile, true, false>(share.blk, total / per, mid + long_mid(x), x.logM, spec + long_spec(x, share.tensor), 0u, tb,
+                                                hist + (size_t)share.tensor * kHistBins, total, per, 1.0f);
 }
 
 template <int LOGE>
@@ -1538,15 +1538,12 @@ hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Ta
     }
 }
 
-// The tensors come shortest first, so those whose rows or columns ask for the larger tile are the last ones.  Beside shorter
-// tensors they are a launch of their own, with two tails instead of one, 8 to 15 us, so the lines lie higher than in uniform
-// calls.  Senders and receivers in us, small / large tiles, of sixty batches of 12 to 200 tensors of 10 to 2.4 M samples, not in
-// the caches, by number of large tiles (of what the launch would hold):
-//   forward second pass: 64 104 / 113, 192 158 / 162, 384 194 / 205, 448 236 / 243, 512 (of 778) 223 / 215, (of 900) 235 / 235,
-//     (of 1044, ResNet-50) 261 / 254, 640 236 / 243, 704 265 / 263 and 283 / 287, 768 313 / 317, 896 334 / 333, 1024 351 / 334,
-//     1280 445 / 428, 1536 438 / 411;
-//   inverse second pass: loses up to 1472 (of 2324) 458 / 476, 512 (of 1044) 206 / 210; 1536 (of 2048) 366 / 346.
-constexpr size_t kWideForwardBeside = 512, kWideInverseBBeside = 1536;
+// The tensors come shortest first, so those whose rows ask for the larger tile are the last ones.  Beside shorter
+// tensors they are a launch of their own, with two tails instead of one, 8 to 15 us, so the line lies higher than in uniform
+// calls.  Senders and receivers in us, small / large tiles, of batches of 12 to 200 tensors of 10 to 2.4 M samples, not in
+// the caches, by number of large tiles (of what the launch would hold): loses up to 1472 (of 2324) 458 / 476, 512 (of 1044)
+// 206 / 210; 1536 (of 2048) 366 / 346.
+constexpr size_t kWideInverseBBeside = 1536;
 size_t launch_tiles(const LongBatch& b) { return (size_t)b.units << (kLongUnitLog - 14); }  // of 2^14 points
 // The first of them, or count; alone, beside: large tiles that are enough.
 template <typename Logs>
@@ -1718,32 +1715,33 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     };
     const hipError_t e = log_columns(b.tab.t[b.count - 1].logM) <= 10 ? pass_a(std::integral_constant<int, 13>{}) : pass_a(std::integral_constant<int, 14>{});
     if (e != hipSuccess) return e;
-    const uint32_t wide = first_wide(b, log_rows, kWideForward, kWideForwardBeside);
-    return by_tile_size(b, wide, [&](auto size, uint32_t first, uint32_t end) {
-        constexpr int LOGE = decltype(size)::value;
-        // Sender and receiver in us, k_fwd_b_long / this: sets of 2^20 6 111 / 105, 12 163.5 / 152;  16 of 2^19 118.4 / 114.2;  two each of 2^16 .. 2^20 83.5 / 81.5;
-        // ResNet-50-like 150 tensors 586 / 575, 60 338.4 / 338.9, 200 819 / 820.  One launch for all small tiles: where rows of 2^10 are among them k_fwd_b_long takes
-        // them all, since a second launch, with tiles of 2^14 for those rows, gains about as often as it loses: 20 of 600 k and one of 1.5 M 240.2 / 235.6, 40 and three
-        // 426.2 / 412.3, 10 of 500 k and six of 2 M 227.2 / 224.1, random sets 29 192.7 / 195.6, 42 267.1 / 264.5 and 189.4 / 194.5, 60 219.8 / 214.9.
-        if (LOGE == 13 && log_rows(b.tab.t[end - 1].logM) <= kPairsTop) {
-            const hipError_t err = set_lds(k_fwd_b_pairs_long, kPairsLds);
-            if (err != hipSuccess) return err;
-            const uint32_t total = long_starts(b, first, end, &at, [](const LongTensor& x) { return power_tiles(x.logM, 13); });
-            FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_pairs_long, dim3((total + 7) / 8 * 8), dim3(HalfTile<kPairsTop>::NT), kPairsLds, s, mid, spec, t, hist, total,
-                         b.tab, at);
-            return hipGetLastError();
-        }
-        const size_t lds = long_lds(LOGE) + kHistLdsWords * sizeof(uint32_t);
-        const hipError_t err = set_lds(k_fwd_b_long<LOGE>, lds);
+    // One launch, whatever the rows' lengths.  Persistent workgroups (k_fwd_b_long) pay for their runs of tiles in most launch sets, and a launch of their
+    // own for rows of 2^10 for a tail.  Sender and receiver in us, before (k_fwd_b_long<13> where rows of 2^10 were among few tiles, a launch for either from
+    // 512 large tiles on) / this: random sets of 30 248 / 236.5, 40 279 / 269, 60 272.5 / 264, 100 471 / 450,
+    // 200 746 / 723, 40 of 1 M and four of 2^21 470 / 445, 30 and ten 502 / 473, ten of 500 k and sixteen 371 / 364, 55 of 70 k and one 158 / 151.
+    // Rows of 2^10 alone it gains about as often as it loses: 2^21 four 122 / 127, eight 174 / 173, twelve 243 / 238, 24 431 / 422, 32 565 / 581;  2^22 eight
+    // 314 / 321, sixteen 579 / 586.
+    auto pairs = [&](auto size) {
+        constexpr int TOP = decltype(size)::value;
+        const hipError_t err = set_lds(k_fwd_b_pairs_long<TOP>, kPairsLds<TOP>);
         if (err != hipSuccess) return err;
-        const uint32_t per = long_run(b, first, end, LOGE, most_wgs(LOGE, 512));
-        const uint32_t g = long_starts(b, first, end, &at, [&](const LongTensor& x) {
-            const uint32_t tiles = 1u << (x.logM - LOGE);
-            return tiles > per ? tiles / per : 1u;
-        });
-        FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), lds, s, mid, spec, t, hist, per, b.tab, at);
+        const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, TOP + 4); });
+        FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_pairs_long<TOP>, dim3((total + 7) / 8 * 8), dim3(HalfTile<TOP>::NT), kPairsLds<TOP>, s, mid, spec, t, hist, total,
+                     b.tab, at);
         return hipGetLastError();
+    };
+    if (log_rows(b.tab.t[0].logM) < 10)  // the longest come last
+        return log_rows(b.tab.t[b.count - 1].logM) < 10 ? pairs(std::integral_constant<int, 9>{}) : pairs(std::integral_constant<int, 10>{});
+    const size_t lds = long_lds(kTallTile) + kHistLdsWords * sizeof(uint32_t);
+    const hipError_t err = set_lds(k_fwd_b_long, lds);
+    if (err != hipSuccess) return err;
+    const uint32_t per = long_run(b, 0, b.count, kTallTile, most_wgs(kTallTile, 512));
+    const uint32_t g = long_starts(b, 0, b.count, &at, [&](const LongTensor& x) {
+        const uint32_t tiles = power_tiles(x.logM, kTallTile);
+        return tiles > per ? tiles / per : 1u;
     });
+    FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_long, dim3(g), dim3(tile_lanes(kTallTile)), lds, s, mid, spec, t, hist, per, b.tab, at);
+    return hipGetLastError();
 }
 
 hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out, float2* mid, Tables t, hipStream_t s)

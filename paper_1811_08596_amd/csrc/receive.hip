@@ -18,7 +18,7 @@
 // receive_tile took 116; a lane that looked up each of its bins alone 187.)
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against counting, decoding and the pass: 6 + 54 + 110
 // -> 8 + 101 us; 138 M in chunks of 2^22 15 + 118 + 275 -> 15 + 249; binary16 5 + 33 + 95 -> 7 + 83.
-// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 7 + 34 + 34.
+// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 7 + 58 (in launches by row length 34 + 34).
 // Several senders' streams are decoded into a spectrum first (codec.hip): eight of them took 444 us this way against 285, since every
 // stretch of eight bins is two and a half lines out of L2.
 #include "fft_core.h"
@@ -419,8 +419,8 @@ __global__ __launch_bounds__(HalfTile<LOGN2>::NT) __attribute__((amdgpu_waves_pe
     receive_pairs<LOGN2, HALF, WIDEST>(records + (size_t)c * S, W, S, bits, m, table + (size_t)c * table_stride(logM), logM, mid + ((size_t)c << logM), tb,
                                        pp0, pp0 == 0, reinterpret_cast<uint32_t*>(smem), threadIdx.x, mid_scale);
 }
-// Tensors of different lengths: those with rows of up to 2^9 are one launch, a workgroup of 1024 lanes does one tile of rows of 2^9,
-// two of 2^8 or four of 2^7; those with rows of 2^10 are another (TOP 10).
+// Tensors of different lengths, rows of up to 2^9 (TOP 9: a workgroup of 1024 lanes does one tile of rows of 2^9, two of 2^8 or four of 2^7) or of 2^10
+// alone (TOP 10).
 template <int TOP, int WIDEST>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(Receive<TOP>::WAVES, Receive<TOP>::WAVES))) void k_receive_b_long(
     const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total,
@@ -449,6 +449,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(Receive<TO
     run(std::integral_constant<int, TOP>{});
 }
 
+// The same in halves of the LDS, rows of any lengths up to 2^TOP: a tile of rows of 2^TOP, two of half the length, and so on.
 template <int TOP, int WIDEST>
 __global__ __launch_bounds__(HalfTile<TOP>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_receive_pairs_long(
     const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total,
@@ -467,12 +468,11 @@ __global__ __launch_bounds__(HalfTile<TOP>::NT) __attribute__((amdgpu_waves_per_
                                             mid + long_mid(x), tb, pp0, share.blk == 0, reinterpret_cast<uint32_t*>(smem) + sub * (G::kLds / 4),
                                             threadIdx.x & (G::NT - 1), 1.0f);
     };
-    if constexpr (TOP == 9) {
-        const int rows = x.logM / 2;
-        if (rows == 7) return run(std::integral_constant<int, 7>{});
-        if (rows == 8) return run(std::integral_constant<int, 8>{});
-    }
-    run(std::integral_constant<int, TOP>{});
+    const int rows = x.logM / 2;
+    if (rows == 7) return run(std::integral_constant<int, 7>{});
+    if (rows == 8) return run(std::integral_constant<int, 8>{});
+    if (TOP == 9 || rows == 9) return run(std::integral_constant<int, 9>{});
+    if constexpr (TOP == 10) run(std::integral_constant<int, 10>{});
 }
 
 // ------------------------------------------------------------------ launch ----
@@ -547,13 +547,13 @@ hipError_t launch_receive(const uint8_t* stream, const CodecArgs& a, int logM, v
     }
 }
 
-// Tensors with rows of 2^10 are a launch of their own, a workgroup a compute unit: beside others it costs a tail more, and few of its
-// workgroups leave compute units idle.  Whole receivers of per-tensor calls in us, by tiles, decode and inverse pass B / these
-// kernels, half of the bins as 8-bit codes:
+// Tensors of different lengths.  Whole receivers of per-tensor calls in us, by tiles, decode and inverse pass B / these kernels, half of the bins as
+// 8-bit codes:
 //   rows of up to 2^9 alone 128 26.8 / 26.1, 192 31.4 / 29.0, 480 52.7 / 45.2 and 47.5 / 40.7;  of 2^10 alone 128 31.2 / 34.5, 256
-//   43.5 / 41.8, 512 62.3 / 50.7;  both 252 41.7 / 50.8, 420 74.4 / 76.8, 650 95.1 / 95.2, 700 99.3 / 105.5, 1190 130.5 / 120.1, 1400 154.6 / 147.7
-//   and 152.7 / 141.3, 2760 295.5 / 250.0, 3320 346.0 / 284.4.
-constexpr size_t kReceiveTallFrom = 192, kReceiveBothFrom = 1024;
+//   43.5 / 41.8, 512 62.3 / 50.7;
+// both, one launch, sender and receiver, 30 % as 8-bit codes: 180 142.3 / 143.8, 216 145.7 / 147.0, 268 161.3 / 157.0, 292 161.9 / 158.7 and 159.3 / 154.7,
+//   320 161.9 / 159.3, 412 172.0 / 165.4, 512 174.0 / 164.1, 616 211.3 / 199.4, 732 221.2 / 208.0, 880 241.2 / 221.0, 944 260.2 / 235.4.
+constexpr size_t kReceiveTallFrom = 192, kReceiveBothFrom = 256;
 bool receive_applies(const LongBatch& b, int bits)
 {
     auto tall = [&](uint32_t i) { return b.tab.t[i].logM / 2 >= 10; };  // the longest come last
@@ -585,9 +585,12 @@ hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* 
     hipError_t e = hipGetLastError();
     uint32_t split = b.count;  // the longest come last
     while (split > 0 && b.tab.t[split - 1].logM / 2 >= 10) --split;
-    // receive_pairs from four tiles of 2^13 points a compute unit on, or one of 2^14.  Whole calls (sender too) in us, receive_tile / receive_pairs:
-    // 2^13 points 256 73.6 / 74.3, 512 119 / 119.5, 768 164.6 / 166.6;  ResNet-50-like 344 / 334, 606 / 588;  2^14 192 114 / 117.5, 256 142.7 / 145.1, 320 166.8 / 164.7,
-    // 384 197.9 / 194.5, 512 197.3 / 193.1.
+    // Rows of up to 2^9 alone, or rows of 2^10 alone: receive_pairs from four tiles of 2^13 points a compute unit on, or one of 2^14.  Whole calls (sender
+    // too) in us, receive_tile / receive_pairs:
+    // 2^13 points 256 73.6 / 74.3, 512 119 / 119.5, 768 164.6 / 166.6;  2^14 192 114 / 117.5, 256 142.7 / 145.1, 320 166.8 / 164.7,
+    // 384 197.9 / 194.5, 512 197.3 / 193.1.  Both kinds are one launch of receive_pairs, which has one tail: a launch for either / one, ResNet-50 382 / 374,
+    // random sets of 60 262 / 257, 100 451 / 438, 150 431 / 422 and 394 / 383, 200 741 / 732, 50 of 200 k and six of 2^21 266 / 255, 30 of 1 M and ten 471 / 462;
+    // 30 of 70 k and 24, whose 1536 large tiles are whole rounds of the chip by themselves, 487 / 493.
     auto pass = [&](auto kern, auto pairs, uint32_t pairs_from, unsigned lanes, size_t lds, size_t pairs_lds, uint32_t from, uint32_t end, int log_points) {
         const uint32_t total = starts(from, end, [&](int logM) { return 1u << (logM - log_points); });
         const bool long_one = total >= pairs_from;
@@ -602,6 +605,9 @@ hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* 
         return hipGetLastError();
     };
     const bool narrow = a.bits <= 8;
+    if (e == hipSuccess && split > 0 && split < b.count)
+        return pass(narrow ? k_receive_b_long<10, 16> : k_receive_b_long<10, 30>, narrow ? k_receive_pairs_long<10, 16> : k_receive_pairs_long<10, 30>, 0u,
+                    HalfTile<10>::NT, Receive<10>::kLds, HalfTile<10>::kLds, 0, b.count, 14);
     if (e == hipSuccess && split > 0)
         e = pass(narrow ? k_receive_b_long<9, 16> : k_receive_b_long<9, 30>, narrow ? k_receive_pairs_long<9, 16> : k_receive_pairs_long<9, 30>, 1025u,
                  HalfTile<9>::NT, Receive<9>::kLds, HalfTile<9>::kLds, 0, split, 13);
