@@ -1027,6 +1027,21 @@ int fftsp_compress_segments(const float* d_grad, const size_t* seg_offsets, int 
     uint8_t* out = static_cast<uint8_t*>(d_packed);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const SegmentPlan plan = plan_segments(seg_offsets, nseg, theta, bits, true);
+    if (plan.shorts.size() == 1 && plan.longs.size() == 1 && tensors_compress_beside(plan.longs[0])) {
+        const LongBatch& b = plan.longs[0];
+        const Workspace w = make_long_workspace(b);
+        CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
+        hdr.write_header = 1;
+        float2 *spec = reinterpret_cast<float2*>(ws + w.spec), *mid = reinterpret_cast<float2*>(ws + w.mid);
+        uint32_t* hist = reinterpret_cast<uint32_t*>(ws + w.hist);
+        hipError_t pe = launch_tensors_compress_beside(d_grad, plan.shorts[0].tab, plan.shorts[0].pieces, QuantizerArgs{bits, m}, hdr, out,
+                                                       out + kStreamHeader, b, mid, reinterpret_cast<uint32_t*>(ws + w.status),
+                                                       (uint32_t)((w.hist - w.status) / 4 + b.count * (size_t)kHistBins), t, s);
+        if (pe == hipSuccess) pe = launch_short_rfft_b_long(b, spec, mid, t, hist, s);
+        if (pe == hipSuccess)
+            pe = launch_encode(reinterpret_cast<float*>(spec), segment_args(b, seg_offsets, nseg, theta, bits, m), out, out + kStreamHeader, ws, w, 1, s);
+        return hip_status(pe);
+    }
     const hipError_t e = run_segments(
         plan, s,
         [&](hipStream_t st) {
@@ -1080,6 +1095,16 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
     const size_t verd = segment_verdicts(plan);
     uint32_t* verdicts = reinterpret_cast<uint32_t*>(ws + verd);
     const StatusNote note = status_note((size_t)nseg, verd);
+    if (plan.shorts.size() == 1 && plan.longs.size() == 1 && tensors_decompress_beside(plan.shorts[0].tab, plan.shorts[0].pieces, plan.longs[0])) {
+        const LongBatch& b = plan.longs[0];
+        CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
+        hdr.write_header = 1;
+        float2* mid = reinterpret_cast<float2*>(ws + make_long_workspace(b).mid);
+        hipError_t pe = launch_tensors_decompress_beside(in, plan.shorts[0].tab, plan.shorts[0].pieces, QuantizerArgs{bits, m}, hdr, d_grad_out,
+                                                         reinterpret_cast<uint32_t*>(ws), note, verdicts, b, mid, verdicts + plan.short_count, t, s);
+        if (pe == hipSuccess) pe = launch_inverse_a_long(mid, b, d_grad_out, t, s);
+        return hip_status(pe);
+    }
     const hipError_t e = run_segments(
         plan, s,
         [&](hipStream_t st) {

@@ -23,6 +23,8 @@
 #include "chunk.h"
 #include "codec_core.h"
 #include "fft_core.h"
+#include "short.h"
+#include "short_core.h"
 
 #include <type_traits>
 
@@ -862,6 +864,19 @@ __device__ __forceinline__ void compress_tensors(const float* __restrict__ in, c
     compress_workgroup<LOGM, NT>(in, listed<Geo<LOGM, NT>>(t, piece, tid), tb, a, records, lds, tid);
 }
 
+template <int TOP>
+__device__ __forceinline__ void compress_piece(const float* __restrict__ in, const TensorTable& t, const Tables& tb, const QuantizerArgs& q,
+                                               uint8_t* __restrict__ records, uint8_t* lds, int tid)
+{
+    const TensorPiece piece = t.piece[blockIdx.x];
+    const PackArgs a = pack_args_of(q, t, piece.logm);
+#define X(p) else if (p <= TOP && piece.logm == p) compress_tensors<(p <= TOP ? p : 4)>(in, t, piece, tb, a, records, lds, tid);
+    if (false) {
+    }
+    FFTSP_CHUNK_SIZES(X)
+#undef X
+}
+
 // The tensors of a per-tensor call that fit one workgroup, whatever their lengths, as one launch: workgroup i does the
 // tensors of piece i.  Waves its length has no use for leave at once (an ended wave takes part in no barrier).
 // TOP: the longest a launch may hold, 2^(TOP+1) samples.
@@ -877,13 +892,26 @@ __global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_compress(con
         if (ctl) write_control(ctl, StatusNote{}, true, tid);
         if (hdr.write && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
     }
-    const TensorPiece piece = t.piece[blockIdx.x];
-    const PackArgs a = pack_args_of(q, t, piece.logm);
-#define X(p) else if (p <= TOP && piece.logm == p) compress_tensors<(p <= TOP ? p : 4)>(in, t, piece, tb, a, records, lds, tid);
-    if (false) {
+    compress_piece<TOP>(in, t, tb, q, records, lds, tid);
+}
+// The same, and behind them the tiles of the forward pass A of a few longer tensors.
+__global__ __launch_bounds__(uniform_threads<14>()) void k_tensors_compress_beside(const float* __restrict__ in, Tables tb, QuantizerArgs q,
+                                                                                  uint8_t* __restrict__ stream, uint8_t* __restrict__ records,
+                                                                                  HeaderInfo hdr, TensorTable t, uint32_t pieces, FewLong few,
+                                                                                  float2* __restrict__ mid, uint32_t* __restrict__ zero_ptr,
+                                                                                  uint32_t zero_words)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    constexpr uint32_t NT = uniform_threads<14>();
+    const int tid = threadIdx.x;
+    if (blockIdx.x >= pieces) {
+        const uint32_t wg = blockIdx.x - pieces;
+        for (uint32_t i = wg * NT + (uint32_t)tid; i < zero_words; i += (gridDim.x - pieces) * NT) zero_ptr[i] = 0u;
+        const LongShare share = share_of(few.at, few.count, wg);
+        return fwd_a_tensor(few.t[share.tensor], share.blk, in, mid, tb);
     }
-    FFTSP_CHUNK_SIZES(X)
-#undef X
+    if (blockIdx.x == 0 && hdr.write && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
+    compress_piece<14>(in, t, tb, q, records, lds, tid);
 }
 
 // ------------------------------------------------------- time-domain Top-k ----
@@ -1160,6 +1188,19 @@ __device__ __forceinline__ void decompress_tensors(const PeerList& streams, cons
 }
 
 template <int TOP>
+__device__ __forceinline__ void decompress_piece(const PeerList& streams, const TensorTable& t, const Tables& tb, const QuantizerArgs& q,
+                                                 const HeaderInfo& hdr, float* __restrict__ out, uint32_t* __restrict__ verdicts, uint8_t* lds, int tid)
+{
+    const TensorPiece piece = t.piece[blockIdx.x];
+    const PackArgs a = pack_args_of(q, t, piece.logm);
+#define X(p) \
+    else if (p <= TOP && piece.logm == p) decompress_tensors<(p <= TOP ? p : 4)>(streams, t, piece, tb, a, hdr, out, verdicts, lds, tid);
+    if (false) {
+    }
+    FFTSP_CHUNK_SIZES(X)
+#undef X
+}
+template <int TOP>
 __global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_decompress(PeerList streams, Tables tb, QuantizerArgs q,
                                                                               HeaderInfo hdr, float* __restrict__ out,
                                                                               uint32_t* __restrict__ ctl, StatusNote note,
@@ -1169,14 +1210,28 @@ __global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_decompress(P
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x;
     if (blockIdx.x == 0 && note.count) write_control(ctl, note, clear != 0, tid);
-    const TensorPiece piece = t.piece[blockIdx.x];
-    const PackArgs a = pack_args_of(q, t, piece.logm);
-#define X(p) \
-    else if (p <= TOP && piece.logm == p) decompress_tensors<(p <= TOP ? p : 4)>(streams, t, piece, tb, a, hdr, out, verdicts, lds, tid);
-    if (false) {
+    decompress_piece<TOP>(streams, t, tb, q, hdr, out, verdicts, lds, tid);
+}
+// The same, and behind them the tiles of the inverse pass B of a few longer tensors.
+__global__ __launch_bounds__(uniform_threads<14>()) void k_tensors_decompress_beside(const uint8_t* __restrict__ stream, Tables tb, QuantizerArgs q,
+                                                                                    HeaderInfo hdr, float* __restrict__ out, uint32_t* __restrict__ ctl,
+                                                                                    StatusNote note, uint32_t* __restrict__ verdicts, TensorTable t,
+                                                                                    uint32_t pieces, FewLong few, float2* __restrict__ mid,
+                                                                                    uint32_t* __restrict__ long_verdicts)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const int tid = threadIdx.x;
+    if (blockIdx.x >= pieces) {
+        const LongShare share = share_of(few.at, few.count, blockIdx.x - pieces);
+        HeaderInfo none = hdr;
+        none.write = 0;  // the shorter tensors' workgroups look at the stream's header
+        return decode_tensor<kDecodeMost / 2>(few.t[share.tensor], share.blk, stream, stream + 64, q.bits, q.m, none,
+                                              share.blk == 0 ? long_verdicts + share.tensor : nullptr, false, mid, tb);
     }
-    FFTSP_CHUNK_SIZES(X)
-#undef X
+    if (blockIdx.x == 0) write_control(ctl, note, true, tid);
+    PeerList one;
+    one.p[0] = stream;
+    decompress_piece<14>(one, t, tb, q, hdr, out, verdicts, lds, tid);
 }
 
 // ------------------------------------------------- stage-level transforms ----
@@ -1500,6 +1555,69 @@ hipError_t launch_tensors_decompress(const uint8_t* stream, const TensorTable& t
     else
         FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress<14>, dim3(pieces), dim3(uniform_threads<14>()), lds, s, one, tb, q,
                      header_info(hdr, hdr.write_header), out, ctl, note, clear, verdicts, t);
+    return hipGetLastError();
+}
+
+// the few longer tensors of a launch, tiles(logM) workgroups each; returns how many in all
+template <typename Tiles>
+static uint32_t few_of(const LongBatch& b, FewLong* few, Tiles&& tiles)
+{
+    uint32_t sum = 0;
+    few->count = b.count;
+    for (uint32_t i = 0; i < b.count; ++i) {
+        few->t[i] = b.tab.t[i];
+        few->at[i] = (uint16_t)sum;
+        sum += tiles((int)b.tab.t[i].logM);
+    }
+    return sum;
+}
+static uint32_t few_forward(const LongBatch& b, FewLong* few)
+{
+    return few_of(b, few, [](int logM) { return 1u << (logM - short_log_a(short_columns(logM))); });
+}
+static uint32_t few_inverse(const LongBatch& b, FewLong* few)
+{
+    return few_of(b, few, [](int logM) { return 1u << (logM - short_rows(logM) - kShortLogSlots); });
+}
+constexpr size_t kRecordBinsLds = 256;  // what RecordBins keeps outside of the dynamic LDS, and more
+static int longest_of(const LongBatch& b) { return b.tab.t[b.count - 1].logM; }  // it comes last
+// Wherever the longer tensors take the kernels of short calls and there is room for them in the launch's arguments: their first kernel's 5 to 9 us and a
+// launch's 3 hide behind the shorter ones' workgroups, which the grid starts with, also where they are more than compute units.  Sender and receiver in us, two launches /
+// one: ResNet-20's 22 tensors 85.6 / 72.7, one of 2^16 and three of 300 54.4 / 41.5, three and one of 2^15 81.9 / 69.1, random sets of ten 99.0 / 82.1, 93.8 / 77.4 and 115 / 106;
+// five of 20 k and twelve of 2^16 89.9 / 76.4, four of 2^18 94.9 / 81.0, six 103.0 / 86.4, three of 2^19 104.3 / 86.7; sixty of 9 k, six of 2^16 and two of 2^18 77.4 / 63.6.
+bool tensors_compress_beside(const LongBatch& b) { return b.count <= (uint32_t)kFewLong && short_forward(b); }
+bool tensors_decompress_beside(const TensorTable& t, uint32_t pieces, const LongBatch& b)
+{
+    return b.count <= (uint32_t)kFewLong && short_decode(b) && tensors_lds(t, pieces, false) + kRecordBinsLds <= kLdsBytes;
+}
+
+hipError_t launch_tensors_compress_beside(const float* in, const TensorTable& t, uint32_t pieces, const QuantizerArgs& q, const CodecArgs& hdr,
+                                          uint8_t* stream, uint8_t* records, const LongBatch& b, float2* mid, uint32_t* zero_ptr, uint32_t zero_words,
+                                          Tables tb, hipStream_t s)
+{
+    if (!tensors_compress_beside(b)) return hipErrorInvalidValue;
+    FewLong few{};
+    const uint32_t wgs = few_forward(b, &few);
+    const size_t own = tensors_lds(t, pieces, true), theirs = lds_a(short_columns(longest_of(b))), lds = own > theirs ? own : theirs;
+    const hipError_t e = allow_lds(k_tensors_compress_beside, most_tensors_lds<14>(true));
+    if (e != hipSuccess) return e;
+    FFTSP_LAUNCH("tensors_compress", k_tensors_compress_beside, dim3(pieces + wgs), dim3(uniform_threads<14>()), lds, s, in, tb, q, stream, records,
+                 header_info(hdr, hdr.write_header), t, pieces, few, mid, zero_ptr, zero_words);
+    return hipGetLastError();
+}
+
+hipError_t launch_tensors_decompress_beside(const uint8_t* stream, const TensorTable& t, uint32_t pieces, const QuantizerArgs& q, const CodecArgs& hdr,
+                                            float* out, uint32_t* ctl, const StatusNote& note, uint32_t* verdicts, const LongBatch& b, float2* mid,
+                                            uint32_t* long_verdicts, Tables tb, hipStream_t s)
+{
+    if (!tensors_decompress_beside(t, pieces, b)) return hipErrorInvalidValue;
+    FewLong few{};
+    const uint32_t wgs = few_inverse(b, &few);
+    const size_t own = tensors_lds(t, pieces, false), theirs = lds_decode(longest_of(b), short_rows(longest_of(b))), lds = own > theirs ? own : theirs;
+    const hipError_t e = allow_lds(k_tensors_decompress_beside, kLdsBytes - kRecordBinsLds);
+    if (e != hipSuccess) return e;
+    FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress_beside, dim3(pieces + wgs), dim3(uniform_threads<14>()), lds, s, stream, tb, q,
+                 header_info(hdr, hdr.write_header), out, ctl, note, verdicts, t, pieces, few, mid, long_verdicts);
     return hipGetLastError();
 }
 

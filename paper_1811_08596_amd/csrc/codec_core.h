@@ -132,11 +132,17 @@ __device__ __forceinline__ uint32_t dequantize_field(uint32_t word, uint32_t at,
 struct LongShare {
     uint32_t tensor, blk;
 };
+__device__ __forceinline__ LongShare share_of(const uint16_t* at, uint32_t count, uint32_t workgroup)
+{
+    const uint32_t lane = threadIdx.x & 63u, start = lane < count ? (uint32_t)at[lane] : ~0u;
+    const int i = (int)__popcll(__ballot(start <= workgroup)) - 1;
+    return LongShare{(uint32_t)i, workgroup - (uint32_t)__builtin_amdgcn_readlane((int)start, i)};
+}
 __device__ __forceinline__ LongShare long_share(const LongStarts& at, uint32_t workgroup)
 {
-    const uint32_t lane = threadIdx.x & 63u, start = lane < at.count ? (uint32_t)at.at[lane] : ~0u;
-    const int i = (int)__popcll(__ballot(start <= workgroup)) - 1;
-    return LongShare{at.first + (uint32_t)i, workgroup - (uint32_t)__builtin_amdgcn_readlane((int)start, i)};
+    LongShare share = share_of(at.at, at.count, workgroup);
+    share.tensor += at.first;
+    return share;
 }
 __device__ __forceinline__ LongShare long_share(const LongStarts& at) { return long_share(at, blockIdx.x); }
 

@@ -172,6 +172,13 @@ struct LongBatch {
     LongTable tab;
     uint32_t count, units;  // tensors, units of work area
 };
+// A few of them, as many as there is room for beside a table of shorter ones in a launch's arguments (chunk.h).  at[i]: the first workgroup of tensor i's share.
+constexpr int kFewLong = 12;
+struct FewLong {
+    LongTensor t[kFewLong];
+    uint16_t at[kFewLong];
+    uint32_t count;
+};
 // where tensor i of a launch finds its part of the work areas
 __host__ __device__ inline size_t long_mid(const LongTensor& t) { return (size_t)t.base << kLongUnitLog; }
 __host__ __device__ inline size_t long_spec(const LongTensor& t, uint32_t i) { return long_mid(t) + 16u * i; }

@@ -25,8 +25,11 @@ SETS = {
 @pytest.mark.parametrize("theta,bits", [(0.3, 8), (0.15, 11), (0.6, 6)])
 @pytest.mark.parametrize("name", list(SETS))
 def test_every_tensor_is_what_it_is_alone(name, theta, bits):
+    check_alone(name, [s for s, many in SETS[name] for _ in range(many)], theta, bits)
+
+
+def check_alone(name, sizes, theta, bits):
     dev = torch.device("cuda")
-    sizes = [s for s, many in SETS[name] for _ in range(many)]
     sizes = sizes[::2] + sizes[1::2]  # not in the order of their lengths
     offsets = [0]
     for s in sizes:

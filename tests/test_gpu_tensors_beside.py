@@ -1,0 +1,50 @@
+"""Small sets of tensors: those of one workgroup each and the first kernel of a few longer ones, twelve at most, are one launch
+(csrc/chunk.hip), whether every workgroup has a compute unit to itself or not.  Every record and every sample is what a call with that
+tensor as its only chunk gives, bit for bit, on either side of that line; a bitmap that claims too many bins is reported."""
+import pytest
+import torch
+
+from paper_1811_08596_amd import fftsp, workloads
+from tests.test_gpu_tensor_rows import check_alone
+
+pytestmark = pytest.mark.gpu
+
+# A sender's longer tensor of 2^16 is 16 workgroups, a receiver's 32; a shorter one of 2^13 samples or more is one.
+SETS = {
+    "ResNet-20": workloads.resnet20_sizes(),
+    "the shortest, and one of 2^18": [1, 200003],
+    "shorter ones of 2^5 to 2^15, one of 2^17 and one of 2^18": [32768, 32767, 16385, 9000, 4097, 2049, 700, 300, 100, 64, 33, 7, 131072, 131075],
+    "sender alone: one of 2^20": [20000, 5, 1000001],
+    "neither: one of 2^21": [20000, 5, 1048577],
+    "a compute unit to every workgroup": [9000] * 32 + [60001] * 7,
+    "more workgroups than compute units": [8193] * 65 + [40001] * 12,
+    "as many of either as go": [20001] * 128 + [60001] * 4 + [100001] * 6 + [200001] * 2,
+    "two launches of shorter ones": [300] * 129 + [60001] * 2,
+    "thirteen": [300] + [40001] * 13,
+}
+
+
+@pytest.mark.parametrize("theta,bits", [(0.3, 6), (0.5, 8), (0.1, 12), (0.2, 32), (0.0, 8)])
+@pytest.mark.parametrize("name", list(SETS))
+def test_every_tensor_is_what_it_is_alone(name, theta, bits):
+    check_alone(name, SETS[name], theta, bits)
+
+
+@pytest.mark.parametrize("tensor", [1, 21])  # a short one of ResNet-20's tensors and one of 2^16
+def test_a_wrong_bitmap_is_reported(tensor):
+    sizes, theta, bits = sorted(workloads.resnet20_sizes()), 0.3, 8
+    offsets = [0]
+    for s in sizes:
+        offsets.append(offsets[-1] + s)
+    grad = torch.randn(offsets[-1], device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    packed = torch.empty(fftsp.packed_bytes_segments(offsets, theta, bits), dtype=torch.uint8, device="cuda")
+    work = torch.empty(fftsp.workspace_bytes_segments(offsets, bits), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(grad)
+    fftsp.compress_segments(grad, offsets, theta, bits, packed, work)
+    at = 64
+    for s in sizes[:tensor]:
+        length = max(32, 1 << (s - 1).bit_length())
+        at += fftsp.packed_bytes(s, length, theta, bits) - 64
+    packed[at + 16:at + 18] = 255
+    fftsp.decompress_segments(packed, packed.numel(), out, offsets, theta, bits, work)
+    assert fftsp.device_status(work) == 6
