@@ -1027,7 +1027,7 @@ int fftsp_compress_segments(const float* d_grad, const size_t* seg_offsets, int 
     uint8_t* out = static_cast<uint8_t*>(d_packed);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const SegmentPlan plan = plan_segments(seg_offsets, nseg, theta, bits, true);
-    if (plan.shorts.size() == 1 && plan.longs.size() == 1 && tensors_compress_beside(plan.longs[0])) {
+    if (plan.shorts.size() == 1 && plan.longs.size() == 1 && tensors_compress_beside(plan.shorts[0].tab, plan.longs[0])) {
         const LongBatch& b = plan.longs[0];
         const Workspace w = make_long_workspace(b);
         CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
@@ -1037,7 +1037,7 @@ int fftsp_compress_segments(const float* d_grad, const size_t* seg_offsets, int 
         hipError_t pe = launch_tensors_compress_beside(d_grad, plan.shorts[0].tab, plan.shorts[0].pieces, QuantizerArgs{bits, m}, hdr, out,
                                                        out + kStreamHeader, b, mid, reinterpret_cast<uint32_t*>(ws + w.status),
                                                        (uint32_t)((w.hist - w.status) / 4 + b.count * (size_t)kHistBins), t, s);
-        if (pe == hipSuccess) pe = launch_short_rfft_b_long(b, spec, mid, t, hist, s);
+        if (pe == hipSuccess) pe = launch_rfft_b_long(b, spec, mid, t, hist, s);
         if (pe == hipSuccess)
             pe = launch_encode(reinterpret_cast<float*>(spec), segment_args(b, seg_offsets, nseg, theta, bits, m), out, out + kStreamHeader, ws, w, 1, s);
         return hip_status(pe);

@@ -25,6 +25,7 @@
 #include "fft_core.h"
 #include "short.h"
 #include "short_core.h"
+#include "split_tile.h"
 
 #include <type_traits>
 
@@ -894,7 +895,8 @@ __global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_compress(con
     }
     compress_piece<TOP>(in, t, tb, q, records, lds, tid);
 }
-// The same, and behind them the tiles of the forward pass A of a few longer tensors.
+// The same, and behind them the tiles of the forward pass A of a few longer tensors: those of short calls, or 2^14 points in half of the LDS (SPLIT).
+template <bool SPLIT>
 __global__ __launch_bounds__(uniform_threads<14>()) void k_tensors_compress_beside(const float* __restrict__ in, Tables tb, QuantizerArgs q,
                                                                                   uint8_t* __restrict__ stream, uint8_t* __restrict__ records,
                                                                                   HeaderInfo hdr, TensorTable t, uint32_t pieces, FewLong few,
@@ -908,7 +910,13 @@ __global__ __launch_bounds__(uniform_threads<14>()) void k_tensors_compress_besi
         const uint32_t wg = blockIdx.x - pieces;
         for (uint32_t i = wg * NT + (uint32_t)tid; i < zero_words; i += (gridDim.x - pieces) * NT) zero_ptr[i] = 0u;
         const LongShare share = share_of(few.at, few.count, wg);
-        return fwd_a_tensor(few.t[share.tensor], share.blk, in, mid, tb);
+        if constexpr (SPLIT) {
+            static_assert(NT == tile_lanes(14), "two tiles of columns of up to 2^10, or one of 2^11");
+            fwd_a_split_tensor<14>(few.t[share.tensor], share.blk, in, mid, tb);
+        } else {
+            fwd_a_tensor(few.t[share.tensor], share.blk, in, mid, tb);
+        }
+        return;
     }
     if (blockIdx.x == 0 && hdr.write && tid < 16) reinterpret_cast<uint32_t*>(stream)[tid] = header_word(hdr, tid);
     compress_piece<14>(in, t, tb, q, records, lds, tid);
@@ -1573,6 +1581,7 @@ static uint32_t few_of(const LongBatch& b, FewLong* few, Tiles&& tiles)
 }
 static uint32_t few_forward(const LongBatch& b, FewLong* few)
 {
+    if (!short_forward(b)) return few_of(b, few, [](int logM) { return power_tiles(logM, 14); });
     return few_of(b, few, [](int logM) { return 1u << (logM - short_log_a(short_columns(logM))); });
 }
 static uint32_t few_inverse(const LongBatch& b, FewLong* few)
@@ -1581,11 +1590,19 @@ static uint32_t few_inverse(const LongBatch& b, FewLong* few)
 }
 constexpr size_t kRecordBinsLds = 256;  // what RecordBins keeps outside of the dynamic LDS, and more
 static int longest_of(const LongBatch& b) { return b.tab.t[b.count - 1].logM; }  // it comes last
-// Wherever the longer tensors take the kernels of short calls and there is room for them in the launch's arguments: their first kernel's 5 to 9 us and a
+// Where the longer tensors take the kernels of short calls and there is room for them in the launch's arguments: their first kernel's 5 to 9 us and a
 // launch's 3 hide behind the shorter ones' workgroups, which the grid starts with, also where they are more than compute units.  Sender and receiver in us, two launches /
 // one: ResNet-20's 22 tensors 85.6 / 72.7, one of 2^16 and three of 300 54.4 / 41.5, three and one of 2^15 81.9 / 69.1, random sets of ten 99.0 / 82.1, 93.8 / 77.4 and 115 / 106;
 // five of 20 k and twelve of 2^16 89.9 / 76.4, four of 2^18 94.9 / 81.0, six 103.0 / 86.4, three of 2^19 104.3 / 86.7; sixty of 9 k, six of 2^16 and two of 2^18 77.4 / 63.6.
-bool tensors_compress_beside(const LongBatch& b) { return b.count <= (uint32_t)kFewLong && short_forward(b); }
+// Senders have forward pass A of larger sets there, too, in half of the LDS, up to where run_segments takes two streams, or half of that beside tensors that
+// are done before it is: ten tensors 158 / 143, 20 164 / 149, 30 176 / 159, five of 20 k and two of 2^21 147 / 135, 30 of 30 k and seven 234 / 209, 20 of 20 k and three of 2^22
+// 234 / 218;  five of 500 and two of 2^21 116 / 112, four 147 / 145.5, six 189 / 197;  30 of 9 k and eight 220 / 232.
+constexpr uint32_t kBesideUnits = 1u << (23 - kLongUnitLog);
+bool tensors_compress_beside(const TensorTable& t, const LongBatch& b)
+{
+    const bool brief = t.piece[0].logm <= 11;  // they come longest first
+    return b.count <= (uint32_t)kFewLong && (short_forward(b) || (brief ? b.units <= kBesideUnits / 2 : b.units < kBesideUnits));
+}
 bool tensors_decompress_beside(const TensorTable& t, uint32_t pieces, const LongBatch& b)
 {
     return b.count <= (uint32_t)kFewLong && short_decode(b) && tensors_lds(t, pieces, false) + kRecordBinsLds <= kLdsBytes;
@@ -1595,13 +1612,15 @@ hipError_t launch_tensors_compress_beside(const float* in, const TensorTable& t,
                                           uint8_t* stream, uint8_t* records, const LongBatch& b, float2* mid, uint32_t* zero_ptr, uint32_t zero_words,
                                           Tables tb, hipStream_t s)
 {
-    if (!tensors_compress_beside(b)) return hipErrorInvalidValue;
+    if (!tensors_compress_beside(t, b)) return hipErrorInvalidValue;
     FewLong few{};
     const uint32_t wgs = few_forward(b, &few);
-    const size_t own = tensors_lds(t, pieces, true), theirs = lds_a(short_columns(longest_of(b))), lds = own > theirs ? own : theirs;
-    const hipError_t e = allow_lds(k_tensors_compress_beside, most_tensors_lds<14>(true));
+    const bool split = !short_forward(b);
+    const size_t own = tensors_lds(t, pieces, true), theirs = split ? SplitTile<11, 14>::kLds : lds_a(short_columns(longest_of(b))), lds = own > theirs ? own : theirs;
+    const auto kern = split ? k_tensors_compress_beside<true> : k_tensors_compress_beside<false>;
+    const hipError_t e = allow_lds(kern, most_tensors_lds<14>(true));
     if (e != hipSuccess) return e;
-    FFTSP_LAUNCH("tensors_compress", k_tensors_compress_beside, dim3(pieces + wgs), dim3(uniform_threads<14>()), lds, s, in, tb, q, stream, records,
+    FFTSP_LAUNCH("tensors_compress", kern, dim3(pieces + wgs), dim3(uniform_threads<14>()), lds, s, in, tb, q, stream, records,
                  header_info(hdr, hdr.write_header), t, pieces, few, mid, zero_ptr, zero_words);
     return hipGetLastError();
 }

@@ -318,6 +318,8 @@ hipError_t launch_irfft(const float* spec, uint32_t sstride, size_t n, int logL,
 // long_mid say.
 hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, float2* mid, Tables t, uint32_t* hist,
                             uint32_t* zero_ptr, size_t zero_words, hipStream_t s);
+// its second pass alone, where something else has filled mid and cleared what launch_rfft_long clears
+hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mid, Tables t, uint32_t* hist, hipStream_t s);
 hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out, float2* mid, Tables t, hipStream_t s);
 // Their second kernels alone (pass A), where something else has filled mid.  half: mid holds binary16 pairs.
 hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, int half, hipStream_t s,

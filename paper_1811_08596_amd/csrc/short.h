@@ -17,7 +17,7 @@ hipError_t launch_short_rfft_half(const float* in, size_t n, int logM, size_t C,
                                   uint32_t* hist, uint32_t* zero_ptr, uint32_t zero_words, float in_scale, float mid_scale, hipStream_t s);
 hipError_t launch_short_rfft_long(const float* in, const LongBatch& b, float2* spec, float2* mid, Tables t, uint32_t* hist,
                                   uint32_t* zero_ptr, uint32_t zero_words, hipStream_t s);
-// its second pass alone, where another launch has done the first (launch_tensors_compress_beside)
+// its second pass alone
 hipError_t launch_short_rfft_b_long(const LongBatch& b, float2* spec, const float2* mid, Tables t, uint32_t* hist, hipStream_t s);
 // the inverse's two passes, B first
 hipError_t launch_short_inverse_b(const float2* spec, uint32_t sstride, int logM, size_t C, float2* mid, Tables t, int pair_spec,

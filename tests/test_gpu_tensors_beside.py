@@ -15,7 +15,11 @@ SETS = {
     "the shortest, and one of 2^18": [1, 200003],
     "shorter ones of 2^5 to 2^15, one of 2^17 and one of 2^18": [32768, 32767, 16385, 9000, 4097, 2049, 700, 300, 100, 64, 33, 7, 131072, 131075],
     "sender alone: one of 2^20": [20000, 5, 1000001],
-    "neither: one of 2^21": [20000, 5, 1048577],
+    "sender, halves of the LDS: columns of 2^8 to 2^11": [20000, 5, 40001, 131072, 300001, 600003, 1048577, 2097155],
+    "the same, as many as go": [9000] * 3 + [2097151] * 7 + [70001, 100003],
+    "the same, one more": [9000] * 3 + [2097151] * 8,
+    "beside brief ones, as many as go": [500, 4096] + [1048577] * 4,
+    "beside brief ones, more": [500, 4096] + [1048577] * 4 + [40000],
     "a compute unit to every workgroup": [9000] * 32 + [60001] * 7,
     "more workgroups than compute units": [8193] * 65 + [40001] * 12,
     "as many of either as go": [20001] * 128 + [60001] * 4 + [100001] * 6 + [200001] * 2,
