@@ -10,8 +10,11 @@
 // codes.  Workgroups are dealt out to the XCDs round-robin, so each XCD gets a stretch of chunks of its own and its workgroups neighbouring
 // tiles of it: the lines come over the fabric once and then out of that XCD's L2.
 //
-// What bounds it: the two dependent trips to memory before a tile's transform, the barriers in it, and about 80 vector instructions a point
-// (34 to 67 of the 101 us below).  None of them alone: what helps is tiles beside each other in a compute unit, whose waits another
+// What bounds receive_pairs: the lines that its lanes fetch, since a lane's run of bins is one of its own in the record and one in the table, 16 to 20
+// bytes used of each.  In timing builds of whole steps, 62 M samples in chunks of 2^20 / 138 M in 2^22: without the records' windows -27 / -50 us, with windows at neighbouring
+// addresses -22 / -41, without the table's entries -12 / -37, without the transform's stages 0 / -9, without the stores 0 / -26.  Its 80 vector instructions a point
+// are hidden: codes' values looked up in LDS, a tenth of them less, changed nothing.  A table in the order of the lanes took 7 and 11 us off this kernel and put 6 and 9 on
+// the table's.  What helps is tiles beside each other in a compute unit, whose waits another
 // one's work fills.  Launches with enough tiles keep a tile in half of the LDS (receive_pairs), which makes it four tiles a compute unit
 // for rows of 2^9 and two for 2^10; in shorter ones, a tile or two a compute unit anyhow, the fewer barriers of receive_tile do better.
 // (Persistent workgroups of sixteen points a lane that fetched the next tile's entries and codes during the transform took 124 to 134 us where
