@@ -1095,13 +1095,15 @@ int fftsp_decompress_segments(const void* d_packed, size_t packed_bytes, float* 
     const size_t verd = segment_verdicts(plan);
     uint32_t* verdicts = reinterpret_cast<uint32_t*>(ws + verd);
     const StatusNote note = status_note((size_t)nseg, verd);
-    if (plan.shorts.size() == 1 && plan.longs.size() == 1 && tensors_decompress_beside(plan.shorts[0].tab, plan.shorts[0].pieces, plan.longs[0])) {
+    if (plan.shorts.size() == 1 && plan.longs.size() == 1 && tensors_decompress_beside(plan.shorts[0].tab, plan.shorts[0].pieces, bits, plan.longs[0])) {
         const LongBatch& b = plan.longs[0];
         CodecArgs hdr = segment_header(seg_offsets, nseg, theta, bits, m);
         hdr.write_header = 1;
-        float2* mid = reinterpret_cast<float2*>(ws + make_long_workspace(b).mid);
+        const Workspace w = make_long_workspace(b);
+        float2* mid = reinterpret_cast<float2*>(ws + w.mid);
         hipError_t pe = launch_tensors_decompress_beside(in, plan.shorts[0].tab, plan.shorts[0].pieces, QuantizerArgs{bits, m}, hdr, d_grad_out,
-                                                         reinterpret_cast<uint32_t*>(ws), note, verdicts, b, mid, verdicts + plan.short_count, t, s);
+                                                         reinterpret_cast<uint32_t*>(ws), note, verdicts, b, mid, ws + w.spec, verdicts + plan.short_count, t, s);
+        if (pe == hipSuccess && !short_decode(b)) pe = launch_receive_b_long(in, segment_args(b, seg_offsets, nseg, theta, bits, m), ws + w.spec, mid, t, s);
         if (pe == hipSuccess) pe = launch_inverse_a_long(mid, b, d_grad_out, t, s);
         return hip_status(pe);
     }

@@ -56,15 +56,16 @@ hipError_t launch_tensors_decompress(const uint8_t* stream, const TensorTable& t
                                      const StatusNote& note, int clear, uint32_t* verdicts, Tables tb, hipStream_t s);
 // The same beside the first kernel of a few longer tensors, whose workgroups come behind theirs: one launch instead of two behind each other.
 bool tensors_compress_beside(const TensorTable& t, const LongBatch& b);
-bool tensors_decompress_beside(const TensorTable& t, uint32_t pieces, const LongBatch& b);
+bool tensors_decompress_beside(const TensorTable& t, uint32_t pieces, int bits, const LongBatch& b);
 // and the forward pass A of b; clears zero_words at zero_ptr (launch_rfft_b_long goes on)
 hipError_t launch_tensors_compress_beside(const float* in, const TensorTable& t, uint32_t pieces, const QuantizerArgs& q, const CodecArgs& hdr,
                                           uint8_t* stream, uint8_t* records, const LongBatch& b, float2* mid, uint32_t* zero_ptr, uint32_t zero_words,
                                           Tables tb, hipStream_t s);
-// and b's inverse pass B out of the records, with verdicts of their own (launch_inverse_a_long goes on)
+// and, with verdicts of their own, b's inverse pass B out of the records, to mid (launch_inverse_a_long goes on), or, without short_decode, its records'
+// table (launch_receive_b_long goes on)
 hipError_t launch_tensors_decompress_beside(const uint8_t* stream, const TensorTable& t, uint32_t pieces, const QuantizerArgs& q, const CodecArgs& hdr,
                                             float* out, uint32_t* ctl, const StatusNote& note, uint32_t* verdicts, const LongBatch& b, float2* mid,
-                                            uint32_t* long_verdicts, Tables tb, hipStream_t s);
+                                            void* table, uint32_t* long_verdicts, Tables tb, hipStream_t s);
 // stage-level transforms, dense natural-order spectra
 hipError_t launch_chunk_rfft(const float* in, size_t n, int logL, size_t C, float* spec, uint32_t sstride, Tables t,
                              hipStream_t s);

@@ -23,6 +23,8 @@
 #include "chunk.h"
 #include "codec_core.h"
 #include "fft_core.h"
+#include "receive.h"
+#include "receive_table.h"
 #include "short.h"
 #include "short_core.h"
 #include "split_tile.h"
@@ -1220,12 +1222,13 @@ __global__ __launch_bounds__(uniform_threads<TOP>()) void k_tensors_decompress(P
     if (blockIdx.x == 0 && note.count) write_control(ctl, note, clear != 0, tid);
     decompress_piece<TOP>(streams, t, tb, q, hdr, out, verdicts, lds, tid);
 }
-// The same, and behind them the tiles of the inverse pass B of a few longer tensors.
+// The same, and behind them the first kernel of a few longer tensors: the tiles of their inverse pass B, to mid, or (TABLE) their bitmaps' table.
+template <bool TABLE>
 __global__ __launch_bounds__(uniform_threads<14>()) void k_tensors_decompress_beside(const uint8_t* __restrict__ stream, Tables tb, QuantizerArgs q,
                                                                                     HeaderInfo hdr, float* __restrict__ out, uint32_t* __restrict__ ctl,
                                                                                     StatusNote note, uint32_t* __restrict__ verdicts, TensorTable t,
                                                                                     uint32_t pieces, FewLong few, float2* __restrict__ mid,
-                                                                                    uint32_t* __restrict__ long_verdicts)
+                                                                                    uint2* __restrict__ table, uint32_t* __restrict__ long_verdicts)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x;
@@ -1233,8 +1236,14 @@ __global__ __launch_bounds__(uniform_threads<14>()) void k_tensors_decompress_be
         const LongShare share = share_of(few.at, few.count, blockIdx.x - pieces);
         HeaderInfo none = hdr;
         none.write = 0;  // the shorter tensors' workgroups look at the stream's header
-        return decode_tensor<kDecodeMost / 2>(few.t[share.tensor], share.blk, stream, stream + 64, q.bits, q.m, none,
-                                              share.blk == 0 ? long_verdicts + share.tensor : nullptr, false, mid, tb);
+        if constexpr (TABLE) {
+            static_assert(kTableLanes == uniform_threads<14>(), "a lane has four words");
+            bitmap_part_of_tensor(stream, few.t[share.tensor], share, none, table, long_verdicts);
+        } else {
+            decode_tensor<kDecodeMost / 2>(few.t[share.tensor], share.blk, stream, stream + 64, q.bits, q.m, none,
+                                           share.blk == 0 ? long_verdicts + share.tensor : nullptr, false, mid, tb);
+        }
+        return;
     }
     if (blockIdx.x == 0) write_control(ctl, note, true, tid);
     PeerList one;
@@ -1586,9 +1595,10 @@ static uint32_t few_forward(const LongBatch& b, FewLong* few)
 }
 static uint32_t few_inverse(const LongBatch& b, FewLong* few)
 {
+    if (!short_decode(b)) return few_of(b, few, [](int logM) { return table_parts(logM); });
     return few_of(b, few, [](int logM) { return 1u << (logM - short_rows(logM) - kShortLogSlots); });
 }
-constexpr size_t kRecordBinsLds = 256;  // what RecordBins keeps outside of the dynamic LDS, and more
+constexpr size_t kStaticLds = 256;  // what RecordBins or bitmap_part keeps outside of the dynamic LDS, and more
 static int longest_of(const LongBatch& b) { return b.tab.t[b.count - 1].logM; }  // it comes last
 // Where the longer tensors take the kernels of short calls and there is room for them in the launch's arguments: their first kernel's 5 to 9 us and a
 // launch's 3 hide behind the shorter ones' workgroups, which the grid starts with, also where they are more than compute units.  Sender and receiver in us, two launches /
@@ -1603,9 +1613,12 @@ bool tensors_compress_beside(const TensorTable& t, const LongBatch& b)
     const bool brief = t.piece[0].logm <= 11;  // they come longest first
     return b.count <= (uint32_t)kFewLong && (short_forward(b) || (brief ? b.units <= kBesideUnits / 2 : b.units < kBesideUnits));
 }
-bool tensors_decompress_beside(const TensorTable& t, uint32_t pieces, const LongBatch& b)
+// Receivers of larger sets have the table of the longer ones' bitmaps there, 7 us and a launch's 3.  Sender and receiver in us, the table a launch of its own / there: ten
+// tensors 143.5 / 137.8, 20 153.0 / 147.8 and 141.7 / 135.5, 30 158.9 / 153.4, five of 500 and two of 2^21 112.3 / 106.7, six 189.5 / 184.2, 30 of 9 k and seven 209.5 / 204.1.
+bool tensors_decompress_beside(const TensorTable& t, uint32_t pieces, int bits, const LongBatch& b)
 {
-    return b.count <= (uint32_t)kFewLong && short_decode(b) && tensors_lds(t, pieces, false) + kRecordBinsLds <= kLdsBytes;
+    return b.count <= (uint32_t)kFewLong && (short_decode(b) || (b.units < kBesideUnits && receive_applies(b, bits))) &&
+           tensors_lds(t, pieces, false) + kStaticLds <= kLdsBytes;
 }
 
 hipError_t launch_tensors_compress_beside(const float* in, const TensorTable& t, uint32_t pieces, const QuantizerArgs& q, const CodecArgs& hdr,
@@ -1627,16 +1640,18 @@ hipError_t launch_tensors_compress_beside(const float* in, const TensorTable& t,
 
 hipError_t launch_tensors_decompress_beside(const uint8_t* stream, const TensorTable& t, uint32_t pieces, const QuantizerArgs& q, const CodecArgs& hdr,
                                             float* out, uint32_t* ctl, const StatusNote& note, uint32_t* verdicts, const LongBatch& b, float2* mid,
-                                            uint32_t* long_verdicts, Tables tb, hipStream_t s)
+                                            void* table, uint32_t* long_verdicts, Tables tb, hipStream_t s)
 {
-    if (!tensors_decompress_beside(t, pieces, b)) return hipErrorInvalidValue;
+    if (!tensors_decompress_beside(t, pieces, q.bits, b)) return hipErrorInvalidValue;
     FewLong few{};
     const uint32_t wgs = few_inverse(b, &few);
-    const size_t own = tensors_lds(t, pieces, false), theirs = lds_decode(longest_of(b), short_rows(longest_of(b))), lds = own > theirs ? own : theirs;
-    const hipError_t e = allow_lds(k_tensors_decompress_beside, kLdsBytes - kRecordBinsLds);
+    const bool tables = !short_decode(b);
+    const size_t own = tensors_lds(t, pieces, false), theirs = tables ? 0 : lds_decode(longest_of(b), short_rows(longest_of(b))), lds = own > theirs ? own : theirs;
+    const auto kern = tables ? k_tensors_decompress_beside<true> : k_tensors_decompress_beside<false>;
+    const hipError_t e = allow_lds(kern, kLdsBytes - kStaticLds);
     if (e != hipSuccess) return e;
-    FFTSP_LAUNCH("tensors_decompress", k_tensors_decompress_beside, dim3(pieces + wgs), dim3(uniform_threads<14>()), lds, s, stream, tb, q,
-                 header_info(hdr, hdr.write_header), out, ctl, note, verdicts, t, pieces, few, mid, long_verdicts);
+    FFTSP_LAUNCH("tensors_decompress", kern, dim3(pieces + wgs), dim3(uniform_threads<14>()), lds, s, stream, tb, q, header_info(hdr, hdr.write_header), out,
+                 ctl, note, verdicts, t, pieces, few, mid, static_cast<uint2*>(table), long_verdicts);
     return hipGetLastError();
 }
 

@@ -16,4 +16,7 @@ bool receive_applies(const LongBatch& b, int bits);
 hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* table, float2* mid, Tables t, int check_header, uint32_t* verdicts,
                                uint32_t* ctl, const StatusNote* first, hipStream_t s);
 
+// its second kernel alone, where another launch has made the table (launch_tensors_decompress_beside)
+hipError_t launch_receive_b_long(const uint8_t* stream, const CodecArgs& a, const void* table, float2* mid, Tables t, hipStream_t s);
+
 }  // namespace fftsp

@@ -27,6 +27,7 @@
 #include "fft_core.h"
 #include "codec_core.h"
 #include "receive.h"
+#include "receive_table.h"
 
 #include <type_traits>
 
@@ -34,52 +35,6 @@ namespace fftsp {
 namespace {
 
 // ------------------------------------------------------------ bitmap table ----
-constexpr int kTableLanes = 1024, kTableWaves = kTableLanes / 64;
-__host__ __device__ constexpr uint32_t table_stride(int logM) { return (1u << (logM - 5)) + 2u; }  // entries, one to a bitmap word
-
-// Entry i of a record's table: word i of its bitmap and the number of bits set before it.  A workgroup makes kTableWords of them
-// and counts the words before its own itself, four loads in flight; the last one of a record leaves the record's verdict.
-// (A workgroup per record: sixty records of 2^20 samples 10.8 -> 6.1 us, thirty-three of 2^22 39 -> 12.)
-constexpr uint32_t kTableWords = 4 * kTableLanes;
-__host__ __device__ constexpr uint32_t table_parts(int logM) { return ((1u << (logM - 5)) + kTableWords - 1u) / kTableWords; }
-__device__ __forceinline__ void bitmap_part(const uint8_t* __restrict__ stream, const uint8_t* __restrict__ record, bool first_of_stream, uint32_t k,
-                                            uint32_t word3, const HeaderInfo& hdr, int logM, uint32_t part, uint2* __restrict__ out,
-                                            uint32_t* __restrict__ verdict)
-{
-    __shared__ uint32_t own[kTableWaves], earlier[kTableWaves];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t parts = table_parts(logM);
-    const uint4* quads = reinterpret_cast<const uint4*>(record + 16);
-    const uint32_t words = 1u << (logM - 5), at = part * kTableLanes + (uint32_t)tid;  // this lane's four
-    auto ones = [](uint4 v) __attribute__((always_inline)) { return (uint32_t)(__popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w)); };
-    const bool in = 4u * at < words;
-    const uint4 w = in ? quads[at] : make_uint4(0u, 0u, 0u, 0u);
-    uint32_t before = 0;
-#pragma unroll 4
-    for (uint32_t i = 0; i < part; ++i) before += ones(quads[i * kTableLanes + (uint32_t)tid]);
-    const uint32_t sum = ones(w), incl = wave_scan_incl(sum);
-    before = wave_sum(before);
-    if (lane == 63) {
-        own[wave] = incl;
-        earlier[wave] = before;
-    }
-    __syncthreads();
-    // every wave sums for itself, a lane to each of the others' sums
-    const uint32_t one = lane < kTableWaves ? own[lane] : 0u, upto = wave_scan_incl(one), base = wave_sum(lane < kTableWaves ? earlier[lane] : 0u);
-    const uint32_t all = base + (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-    const uint32_t run = base + (uint32_t)__builtin_amdgcn_readlane((int)(upto - one), wave) + incl - sum;
-    if (in) {
-        const uint32_t r1 = run + (uint32_t)__popc(w.x), r2 = r1 + (uint32_t)__popc(w.y), r3 = r2 + (uint32_t)__popc(w.z);
-        uint4* p = reinterpret_cast<uint4*>(out + 4u * at);  // the stride is even
-        p[0] = make_uint4(w.x, run, w.y, r1);
-        p[1] = make_uint4(w.z, r2, w.w, r3);
-    }
-    if (part + 1u == parts && tid == 0) {
-        const uint32_t last = reinterpret_cast<const uint32_t*>(quads)[words];  // the Nyquist bin has a word to itself
-        *reinterpret_cast<uint4*>(out + words) = make_uint4(last, all, 0u, 0u);
-        *verdict = record_verdict(record, stream, first_of_stream, all + (uint32_t)__popc(last), k, word3, hdr);
-    }
-}
 __global__ __launch_bounds__(kTableLanes) void k_bitmap_table(const uint8_t* __restrict__ stream, uint32_t C, size_t S, uint32_t k, HeaderInfo hdr, int logM,
                                                              uint2* __restrict__ table, uint32_t* __restrict__ verdicts,
                                                              uint32_t* __restrict__ ctl, StatusNote note)
@@ -90,17 +45,13 @@ __global__ __launch_bounds__(kTableLanes) void k_bitmap_table(const uint8_t* __r
     if (c >= C) return;
     bitmap_part(stream, stream + 64 + (size_t)c * S, c == 0, k, 0u, hdr, logM, y % parts, table + (size_t)c * table_stride(logM), verdicts + c);
 }
-// where tensor i of a launch has its entries, in the spectrum's region
-__device__ __forceinline__ size_t long_entries(const LongTensor& x, uint32_t i) { return (long_mid(x) >> 5) + 2u * i; }
 __global__ __launch_bounds__(kTableLanes) void k_bitmap_table_long(const uint8_t* __restrict__ stream, HeaderInfo hdr, uint2* __restrict__ table,
                                                                   uint32_t* __restrict__ verdicts, uint32_t* __restrict__ ctl, StatusNote note,
                                                                   LongTable tab, LongStarts at)
 {
     if (ctl && blockIdx.x == 0) clear_control(ctl, note, threadIdx.x, kTableLanes);
     const LongShare share = long_share(at);
-    const LongTensor& x = tab.t[share.tensor];
-    bitmap_part(stream, stream + 64 + x.roff, share.tensor == 0, x.kept, 2u << x.logM, hdr, x.logM, share.blk, table + long_entries(x, share.tensor),
-                verdicts + share.tensor);
+    bitmap_part_of_tensor(stream, tab.t[share.tensor], share, hdr, table, verdicts);
 }
 
 // ---------------------------------------------------------- inverse pass B ----
@@ -564,6 +515,19 @@ bool receive_applies(const LongBatch& b, int bits)
     return bits <= 15 && tiles >= (tall(0) ? kReceiveTallFrom : (tall(b.count - 1) ? kReceiveBothFrom : kReceiveFrom));
 }
 
+// starts of tensors from .. end - 1, wgs(logM) workgroups each; returns how many in all
+template <typename Wgs>
+static uint32_t share_out(const LongBatch& b, uint32_t from, uint32_t end, LongStarts* at, Wgs&& wgs)
+{
+    uint32_t sum = 0;
+    at->first = from;
+    at->count = end - from;
+    for (uint32_t i = from; i < end; ++i) {
+        at->at[i - from] = (uint16_t)sum;
+        sum += wgs((int)b.tab.t[i].logM);
+    }
+    return sum;
+}
 hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* table, float2* mid, Tables t, int check_header, uint32_t* verdicts,
                                uint32_t* ctl, const StatusNote* first, hipStream_t s)
 {
@@ -572,20 +536,20 @@ hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* 
     const HeaderInfo h{check_header, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
     uint2* entries = static_cast<uint2*>(table);
     LongStarts at;
-    auto starts = [&](uint32_t from, uint32_t end, auto wgs) {
-        uint32_t sum = 0;
-        at.first = from;
-        at.count = end - from;
-        for (uint32_t i = from; i < end; ++i) {
-            at.at[i - from] = (uint16_t)sum;
-            sum += wgs((int)b.tab.t[i].logM);
-        }
-        return sum;
-    };
-    const uint32_t parts = starts(0, b.count, [](int logM) { return table_parts(logM); });
+    const uint32_t parts = share_out(b, 0, b.count, &at, [](int logM) { return table_parts(logM); });
     FFTSP_LAUNCH("bitmap_table", k_bitmap_table_long, dim3(parts), dim3(kTableLanes), 0, s, stream, h, entries, verdicts, first ? ctl : nullptr,
                  first ? *first : StatusNote{}, b.tab, at);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_receive_b_long(stream, a, table, mid, t, s) : e;
+}
+
+hipError_t launch_receive_b_long(const uint8_t* stream, const CodecArgs& a, const void* table, float2* mid, Tables t, hipStream_t s)
+{
+    const LongBatch& b = *a.tab;
+    if (!receive_applies(b, a.bits)) return hipErrorInvalidValue;
+    const uint2* entries = static_cast<const uint2*>(table);
+    LongStarts at;
+    hipError_t e = hipSuccess;
     uint32_t split = b.count;  // the longest come last
     while (split > 0 && b.tab.t[split - 1].logM / 2 >= 10) --split;
     // Rows of up to 2^9 alone, or rows of 2^10 alone: receive_pairs from four tiles of 2^13 points a compute unit on, or one of 2^14.  Whole calls (sender
@@ -595,7 +559,7 @@ hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* 
     // random sets of 60 262 / 257, 100 451 / 438, 150 431 / 422 and 394 / 383, 200 741 / 732, 50 of 200 k and six of 2^21 266 / 255, 30 of 1 M and ten 471 / 462;
     // 30 of 70 k and 24, whose 1536 large tiles are whole rounds of the chip by themselves, 487 / 493.
     auto pass = [&](auto kern, auto pairs, uint32_t pairs_from, unsigned lanes, size_t lds, size_t pairs_lds, uint32_t from, uint32_t end, int log_points) {
-        const uint32_t total = starts(from, end, [&](int logM) { return 1u << (logM - log_points); });
+        const uint32_t total = share_out(b, from, end, &at, [&](int logM) { return 1u << (logM - log_points); });
         const bool long_one = total >= pairs_from;
         if (long_one) {
             kern = pairs;

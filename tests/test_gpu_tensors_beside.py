@@ -1,4 +1,4 @@
-"""Small sets of tensors: those of one workgroup each and the first kernel of a few longer ones, twelve at most, are one launch
+"""Sets of tensors: those of one workgroup each and the first kernel of a few longer ones, twelve at most, are one launch
 (csrc/chunk.hip), whether every workgroup has a compute unit to itself or not.  Every record and every sample is what a call with that
 tensor as its only chunk gives, bit for bit, on either side of that line; a bitmap that claims too many bins is reported."""
 import pytest
@@ -34,9 +34,10 @@ def test_every_tensor_is_what_it_is_alone(name, theta, bits):
     check_alone(name, SETS[name], theta, bits)
 
 
-@pytest.mark.parametrize("tensor", [1, 21])  # a short one of ResNet-20's tensors and one of 2^16
-def test_a_wrong_bitmap_is_reported(tensor):
-    sizes, theta, bits = sorted(workloads.resnet20_sizes()), 0.3, 8
+# a short one of ResNet-20's tensors and one of 2^16; a short one and two long ones of a set whose bitmaps' table is beside the short ones
+@pytest.mark.parametrize("name,tensor", [("ResNet-20", 1), ("ResNet-20", 21), ("tables", 0), ("tables", 2), ("tables", 5)])
+def test_a_wrong_bitmap_is_reported(name, tensor):
+    sizes, theta, bits = sorted(SETS.get(name, [300, 9000, 300001, 600003, 1048577, 2097155])), 0.3, 8
     offsets = [0]
     for s in sizes:
         offsets.append(offsets[-1] + s)
