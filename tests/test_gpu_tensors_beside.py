@@ -1,4 +1,4 @@
-"""Sets of tensors: those of one workgroup each and the first kernel of a few longer ones, twelve at most, are one launch
+"""Sets of tensors: those of one workgroup each and the first kernel of a few longer ones, nineteen at most, are one launch
 (csrc/chunk.hip), whether every workgroup has a compute unit to itself or not.  Every record and every sample is what a call with that
 tensor as its only chunk gives, bit for bit, on either side of that line; a bitmap that claims too many bins is reported."""
 import pytest
@@ -22,9 +22,10 @@ SETS = {
     "beside brief ones, more": [500, 4096] + [1048577] * 4 + [40000],
     "a compute unit to every workgroup": [9000] * 32 + [60001] * 7,
     "more workgroups than compute units": [8193] * 65 + [40001] * 12,
-    "as many of either as go": [20001] * 128 + [60001] * 4 + [100001] * 6 + [200001] * 2,
+    "as many of either as go": [20001] * 128 + [60001] * 9 + [100001] * 8 + [200001] * 2,
     "two launches of shorter ones": [300] * 129 + [60001] * 2,
-    "thirteen": [300] + [40001] * 13,
+    "twenty long ones": [300] + [40001] * 20,
+    "nineteen, halves of the LDS": [9000] * 20 + [70001] * 6 + [200001] * 6 + [300001] * 4 + [1100001] * 3,
 }
 
 
