@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfftsp.so")
 SOURCES = ["fft.hip", "short.hip", "receive.hip", "chunk.hip", "fused.hip", "codec.hip", "api.hip", "prof.hip"]
-HEADERS = [os.path.join(CSRC, "internal.h"), os.path.join(CSRC, "codec_core.h"), os.path.join(CSRC, "chunk.h"), os.path.join(CSRC, "short.h"), os.path.join(CSRC, "short_core.h"), os.path.join(CSRC, "split_tile.h"), os.path.join(CSRC, "receive.h"), os.path.join(CSRC, "receive_table.h"), os.path.join(CSRC, "record_bounds.h"), os.path.join(CSRC, "sample.h"), os.path.join(CSRC, "fft_core.h"), os.path.join(CSRC, "twiddle_table.h"), os.path.join(os.path.dirname(HERE), "include", "fftsp.h")]
+HEADERS = [os.path.join(CSRC, "internal.h"), os.path.join(CSRC, "codec_core.h"), os.path.join(CSRC, "chunk.h"), os.path.join(CSRC, "short.h"), os.path.join(CSRC, "short_core.h"), os.path.join(CSRC, "split_tile.h"), os.path.join(CSRC, "receive.h"), os.path.join(CSRC, "receive_table.h"), os.path.join(CSRC, "record_bounds.h"), os.path.join(CSRC, "sample.h"), os.path.join(CSRC, "stretches.h"), os.path.join(CSRC, "fft_core.h"), os.path.join(CSRC, "twiddle_table.h"), os.path.join(os.path.dirname(HERE), "include", "fftsp.h")]
 
 # no fast-math, and no fused multiply-adds but those the sources write out: twiddles, keys and the split must round the same way
 # in every kernel that computes them

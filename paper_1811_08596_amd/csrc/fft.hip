@@ -605,10 +605,10 @@ template <int TOP>
 constexpr size_t kPairsLds = HalfTile<TOP>::kLds + kHistLdsWords * sizeof(uint32_t);
 template <int TOP>
 __global__ __launch_bounds__(HalfTile<TOP>::NT) __attribute__((amdgpu_waves_per_eu(TOP == 10 ? 8 : 6, TOP == 10 ? 8 : 6))) void k_fwd_b_pairs_long(
-    const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb, uint32_t* __restrict__ hist, uint32_t total, LongTable tab, LongStarts at)
+    const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb, uint32_t* __restrict__ hist, uint32_t total, uint32_t few, LongTable tab, LongStarts at)
 {
     extern __shared__ float2 smem[];
-    const uint32_t t = in_stretches(total);
+    const uint32_t t = in_stretches(total, few);
     if (t >= total) return;
     const LongShare share = long_share(at, t);
     const LongTensor& x = tab.t[share.tensor];
@@ -1551,6 +1551,8 @@ hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mi
     if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors) return hipErrorInvalidValue;
     if (short_forward(b)) return launch_short_rfft_b_long(b, spec, mid, t, hist, s);
     LongStarts at;
+    uint32_t tall = b.count;  // the first with rows of 2^10: the longest come last
+    while (tall > 0 && log_rows(b.tab.t[tall - 1].logM) >= 10) --tall;
     // One launch, whatever the rows' lengths.  Persistent workgroups (k_fwd_b_long) pay for their runs of tiles in most launch sets, and a launch of their
     // own for rows of 2^10 for a tail.  Sender and receiver in us, before (k_fwd_b_long<13> where rows of 2^10 were among few tiles, a launch for either from
     // 512 large tiles on) / this: random sets of 30 248 / 236.5, 40 279 / 269, 60 272.5 / 264, 100 471 / 450,
@@ -1562,12 +1564,12 @@ hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mi
         const hipError_t err = set_lds(k_fwd_b_pairs_long<TOP>, kPairsLds<TOP>);
         if (err != hipSuccess) return err;
         const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, TOP + 4); });
-        FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_pairs_long<TOP>, dim3((total + 7) / 8 * 8), dim3(HalfTile<TOP>::NT), kPairsLds<TOP>, s, mid, spec, t, hist, total,
-                     b.tab, at);
+        const uint32_t few = TOP == 10 ? at.at[tall] : 0u;
+        FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_pairs_long<TOP>, dim3(stretch_places(total, few)), dim3(HalfTile<TOP>::NT), kPairsLds<TOP>, s, mid, spec, t, hist,
+                     total, few, b.tab, at);
         return hipGetLastError();
     };
-    if (log_rows(b.tab.t[0].logM) < 10)  // the longest come last
-        return log_rows(b.tab.t[b.count - 1].logM) < 10 ? pairs(std::integral_constant<int, 9>{}) : pairs(std::integral_constant<int, 10>{});
+    if (tall > 0) return tall == b.count ? pairs(std::integral_constant<int, 9>{}) : pairs(std::integral_constant<int, 10>{});
     const size_t lds = long_lds(kTallTile) + kHistLdsWords * sizeof(uint32_t);
     const hipError_t err = set_lds(k_fwd_b_long, lds);
     if (err != hipSuccess) return err;

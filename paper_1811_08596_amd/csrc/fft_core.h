@@ -2,6 +2,7 @@
 // fft.hip, the fused, cache-resident kernels in fused.hip and the chunk-resident codec in chunk.hip).  Internal: nothing here is part of the C ABI.
 #pragma once
 #include "internal.h"
+#include "stretches.h"
 
 namespace fftsp {
 namespace {
@@ -318,13 +319,9 @@ struct MirroredRows {
     __device__ __forceinline__ int upper(int i) const { return i ? upper1 : upper0; }
 };
 
-// every XCD has a stretch of the launch's workgroups of its own; at or above `total`: none
-__device__ __forceinline__ uint32_t in_stretches(uint32_t total)
-{
-    const uint32_t xcd = blockIdx.x & 7u, lo = (uint32_t)((uint64_t)total * xcd >> 3), hi = (uint32_t)((uint64_t)total * (xcd + 1u) >> 3);
-    const uint32_t t = lo + (blockIdx.x >> 3);
-    return t < hi ? t : total;
-}
+// this workgroup's tile; at or above `total`: none
+__device__ __forceinline__ uint32_t in_stretches(uint32_t total) { return stretch_tile(blockIdx.x, total); }
+__device__ __forceinline__ uint32_t in_stretches(uint32_t total, uint32_t few) { return stretch_tile(blockIdx.x, total, few); }
 
 // Accesses that leave the caches to others (ONCE), for what the call does not touch again: whole calls choose, see kOnceBytes.
 template <bool ONCE>

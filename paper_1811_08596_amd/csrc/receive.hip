@@ -377,12 +377,12 @@ __global__ __launch_bounds__(HalfTile<LOGN2>::NT) __attribute__((amdgpu_waves_pe
 // alone (TOP 10).
 template <int TOP, int WIDEST>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(Receive<TOP>::WAVES, Receive<TOP>::WAVES))) void k_receive_b_long(
-    const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total,
+    const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total, uint32_t few,
     LongTable tab, LongStarts at)
 {
     static_assert(Receive<TOP>::NT == 1024, "one tile of the longest rows");
     extern __shared__ float2 smem[];
-    const uint32_t t = in_stretches(total);
+    const uint32_t t = in_stretches(total, few);
     if (t >= total) return;
     const LongShare share = long_share(at, t);
     const LongTensor& x = tab.t[share.tensor];
@@ -406,11 +406,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(Receive<TO
 // The same in halves of the LDS, rows of any lengths up to 2^TOP: a tile of rows of 2^TOP, two of half the length, and so on.
 template <int TOP, int WIDEST>
 __global__ __launch_bounds__(HalfTile<TOP>::NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_receive_pairs_long(
-    const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total,
+    const uint8_t* __restrict__ records, int bits, int m, const uint2* __restrict__ table, float2* __restrict__ mid, Tables tb, uint32_t total, uint32_t few,
     LongTable tab, LongStarts at)
 {
     extern __shared__ float2 smem[];
-    const uint32_t t = in_stretches(total);
+    const uint32_t t = in_stretches(total, few);
     if (t >= total) return;
     const LongShare share = long_share(at, t);
     const LongTensor& x = tab.t[share.tensor];
@@ -557,7 +557,7 @@ hipError_t launch_receive_b_long(const uint8_t* stream, const CodecArgs& a, cons
     // 2^13 points 256 73.6 / 74.3, 512 119 / 119.5, 768 164.6 / 166.6;  2^14 192 114 / 117.5, 256 142.7 / 145.1, 320 166.8 / 164.7,
     // 384 197.9 / 194.5, 512 197.3 / 193.1.  Both kinds are one launch of receive_pairs, which has one tail: a launch for either / one, ResNet-50 382 / 374,
     // random sets of 60 262 / 257, 100 451 / 438, 150 431 / 422 and 394 / 383, 200 741 / 732, 50 of 200 k and six of 2^21 266 / 255, 30 of 1 M and ten 471 / 462;
-    // 30 of 70 k and 24, whose 1536 large tiles are whole rounds of the chip by themselves, 487 / 493.
+    // every XCD with its share of either kind (stretches.h), 30 of 70 k and 16 of 2^21 364 / 356, 24 513 / 483, 32 750 / 734, one of 2^16 and 24 485 / 457.
     auto pass = [&](auto kern, auto pairs, uint32_t pairs_from, unsigned lanes, size_t lds, size_t pairs_lds, uint32_t from, uint32_t end, int log_points) {
         const uint32_t total = share_out(b, from, end, &at, [&](int logM) { return 1u << (logM - log_points); });
         const bool long_one = total >= pairs_from;
@@ -567,8 +567,9 @@ hipError_t launch_receive_b_long(const uint8_t* stream, const CodecArgs& a, cons
         }
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err != hipSuccess) return err;
-        FFTSP_LAUNCH("irfft_pass_b", kern, dim3((total + 7) / 8 * 8), dim3(long_one ? lanes : 1024u), lds, s, stream + 64, a.bits, a.m, entries, mid, t,
-                     total, b.tab, at);
+        const uint32_t few = from < split && split < end ? at.at[split - from] : 0u;
+        FFTSP_LAUNCH("irfft_pass_b", kern, dim3(stretch_places(total, few)), dim3(long_one ? lanes : 1024u), lds, s, stream + 64, a.bits, a.m, entries, mid, t,
+                     total, few, b.tab, at);
         return hipGetLastError();
     };
     const bool narrow = a.bits <= 8;

@@ -1,0 +1,29 @@
+// Which of a launch's tiles a workgroup does.  Workgroups are dealt out to the eight XCDs round-robin, and every XCD has a stretch of the tiles of
+// its own, so that neighbours, which share lines, are in one L2.  Host code too, so that it can be checked there.
+#pragma once
+#include <stdint.h>
+
+namespace fftsp {
+
+constexpr uint32_t stretch_start(uint32_t xcd, uint32_t tiles) { return (uint32_t)((uint64_t)tiles * xcd >> 3); }
+// tile of workgroup `place` of 8 * ceil(total / 8); at or above `total`: none
+constexpr uint32_t stretch_tile(uint32_t place, uint32_t total)
+{
+    const uint32_t xcd = place & 7u, t = stretch_start(xcd, total) + (place >> 3);
+    return t < stretch_start(xcd + 1u, total) ? t : total;
+}
+// The same where the first `few` tiles are of another kind, which take longer or less long: an XCD has its stretch of either.  With one stretch over both,
+// one XCD has all of those few.  Sender and receiver in us of tensors whose rows are of 2^10 and shorter, the shorter ones first, one stretch / one of
+// either: 30 of 70 k and 16 of 2^21 376 / 356, 24 511 / 483, 32 772 / 734 (a launch for either kind 751);  30 of 150 k and 24 541 / 513;  24 of 300 k and 24 566 / 552, 16 416 / 416.
+// Receivers of ResNet-50's 161 tensors 140.5 / 134.4.  The shorter ones last: 488 and 734 where these take 483 and 734, random sets of 60 299 / 295.
+constexpr uint32_t stretch_tile(uint32_t place, uint32_t total, uint32_t few)
+{
+    const uint32_t xcd = place & 7u, i = place >> 3, mine = stretch_start(xcd + 1u, few) - stretch_start(xcd, few);
+    if (i < mine) return stretch_start(xcd, few) + i;
+    const uint32_t t = stretch_start(xcd, total - few) + i - mine;
+    return t < stretch_start(xcd + 1u, total - few) ? few + t : total;
+}
+// workgroups that have a tile for everyone
+constexpr uint32_t stretch_places(uint32_t total, uint32_t few = 0) { return 8u * ((few + 7u) / 8u + (total - few + 7u) / 8u); }
+
+}  // namespace fftsp
