@@ -1071,7 +1071,7 @@ __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu
 {
     extern __shared__ float2 smem[];
     for (uint32_t i = blockIdx.x * tile_lanes(TOP) + threadIdx.x; i < zero_words; i += gridDim.x * tile_lanes(TOP)) zero_ptr[i] = 0u;
-    const uint32_t t = in_stretches(total);
+    const uint32_t t = in_turned_stretches(total);
     if (t >= total) return;
     const LongShare share = long_share(at, t);
     fwd_a_split_tensor<TOP>(tab.t[share.tensor], share.blk, in, mid, tb);

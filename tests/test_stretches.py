@@ -11,6 +11,7 @@ SOURCE = r"""
 #include "%s/paper_1811_08596_amd/csrc/stretches.h"
 extern "C" uint32_t tile(uint32_t place, uint32_t total) { return fftsp::stretch_tile(place, total); }
 extern "C" uint32_t tile_of_two(uint32_t place, uint32_t total, uint32_t few) { return fftsp::stretch_tile(place, total, few); }
+extern "C" uint32_t turned(uint32_t place, uint32_t total) { return fftsp::turned_tile(place, total); }
 extern "C" uint32_t places(uint32_t total, uint32_t few) { return fftsp::stretch_places(total, few); }
 """
 
@@ -47,3 +48,14 @@ def test_a_launch_of_two_kinds(lib, few, others):
         first, then = [t for t in ts if t < few], [t for t in ts if t >= few]
         assert ts == first + then and len(first) <= -(-few // 8) and len(then) <= -(-others // 8)
         assert all(b == a + 1 for part in (first, then) for a, b in zip(part, part[1:]))
+
+
+@pytest.mark.parametrize("total", [1, 7, 8, 9, 64, 65, 1000, 1024, 1537, 2048, 4096])
+def test_stretches_that_begin_at_different_columns(lib, total):
+    """The same stretches, each gone round once from another place on: the XCDs begin in different eighths of a tensor of 128 tiles."""
+    straight = per_xcd(lib.places(total, 0), lambda p: lib.tile(p, total), total)
+    turned = per_xcd(lib.places(total, 0), lambda p: lib.turned(p, total), total)
+    for a, b in zip(straight, turned):
+        assert sorted(b) == a and (not b or b == a[a.index(b[0]):] + a[:a.index(b[0])])
+    if total >= 1024:
+        assert len({ts[0] % 128 // 16 for ts in turned}) == 8
