@@ -256,6 +256,41 @@ __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __re
     fwd_a_workgroup<LOGN1, HALF>(blockIdx.x, in, n, logM, mid, tb, aligned, total, per_wg, glog, in_scale);
 }
 
+// The tiles of a few tensors, 2^13 points to a workgroup of their own, whole in the LDS: two to a compute unit and half as many trips through it as in
+// half of it.  Figures at kWholeForwardLong.
+__global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a_long(const float* __restrict__ in, float2* __restrict__ mid, Tables tb, uint32_t total,
+                                                                   uint32_t* __restrict__ zero_ptr, uint32_t zero_words, LongTable tab, LongStarts at)
+{
+    constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE);
+    extern __shared__ float2 smem[];
+    float2 *const d = smem, *const tw = smem + (1 << LOGE);
+    for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < zero_words; i += gridDim.x * NT) zero_ptr[i] = 0u;
+    const uint32_t t = in_turned_stretches(total);
+    if (t >= total) return;
+    const LongShare share = long_share(at, t);
+    const LongTensor& x = tab.t[share.tensor];
+    const int logM = x.logM, tid = threadIdx.x;
+    auto run = [&](auto n1) __attribute__((always_inline)) {
+        constexpr int LOGN1 = decltype(n1)::value, LOGT = LOGE - LOGN1;
+        load_stage_twiddles<LOGN1, NT>(tw, tb, tid);
+        float2 v[16];
+        load_columns<LOGN1, LOGT>(v, in, chunk_span((size_t)x.goff, x.glen, 0, 0), logM, tb, share.blk << LOGT, tid);
+        const PassARatios<LOGN1> ratio = pass_a_ratios<LOGN1>(tb, logM, tid);
+        float4 r[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r[q] = join(v[q], v[8 + q]);
+        first_stage_store<LOGT, false>(d, tid >> (LOGT - 1), 2 * (tid & ((1 << LOGT) / 2 - 1)), r);
+        __syncthreads();
+        fwd_a_tile<LOGN1, false>(share.blk, power_tiles(logM, LOGE), logM, mid + long_mid(x), tb, d, tw, tid, 1.0f, ratio, [](int) {});
+    };
+    switch (log_columns(logM)) {
+        case 8: return run(std::integral_constant<int, 8>{});
+        case 9: return run(std::integral_constant<int, 9>{});
+        case 10: return run(std::integral_constant<int, 10>{});
+        default: return run(std::integral_constant<int, 11>{});
+    }
+}
+
 
 // From how many tiles of 2^14, columns of 2^11, forward pass A has them in half of the LDS (split_tile.h); figures there.
 template <bool HALF>
@@ -1414,6 +1449,14 @@ hipError_t by_tile_size(const LongBatch& b, uint32_t wide, Pass&& pass)
     if (e == hipSuccess && wide < b.count) e = pass(std::integral_constant<int, 14>{}, wide, b.count);
     return e;
 }
+// Up to how many tiles of 2^14 forward pass A has them as tiles of 2^13 whole in the LDS; with columns of 2^11 among them, which are 32 bytes wide then, as long as
+// tiles of 2^14 would leave compute units idle.  Senders in us, in half of the LDS / whole, tensors of whole powers of two (and five samples less):
+//   2^17 128 50.0 / 47.5 (50.1 / 47.8), 192 58.5 / 55.2;  2^18 128 50.5 / 47.4 (50.0 / 47.9), 256 68.7 / 65.6 (68.6 / 65.5), 384 87.4 / 86.2 (86.9 / 85.7);  2^19 128 53.4 / 50.9, 256 72.4 / 69.7
+//   (72.0 / 69.1), 512 111 / 109 (109 / 110), 768 153.6 / 148.0 (153 / 150);  2^20 128 54.7 / 53.6 (55.4 / 53.9), 256 73.2 / 71.8 (74.1 / 72.8), 512 115 / 112 (119 / 115), 768 151 / 152 (154 / 156),
+//   1536 253 / 256;  2^21 128 60.9 / 59.4 (61.2 / 59.9), 256 78.4 / 77.2 (79.5 / 77.9), 512 119.6 / 115.8 (122 / 118), 768 163.5 / 163.4 (167 / 167), 1024 199 / 197, 1536 277 / 279;
+//   random sets 60 190 / 193, 100 205 / 210;  2^22 128 75.4 / 71.9 (75.2 / 71.8), beside shorter ones 130 78.9 / 76.8, 160 81.2 / 79.9, 192 84.1 / 82.1 and 80.2 /
+//   77.8, 224 90.6 / 90.4, 256 89.7 / 90.0 (89.9 / 91.4) and 94.7 / 97.0, 384 120.1 / 122.2, 512 125.6 / 134.1.
+constexpr size_t kWholeForwardLong = 512, kWholeForwardLong11 = 255;
 constexpr int kLongLogN = log_columns(kLongMax);  // the longest row or column
 // LDS of a pass: the tile and the stage twiddles
 constexpr size_t long_lds(int loge) { return ((size_t)(1 << loge) + (1 << kLongLogN)) * sizeof(float2); }
@@ -1532,6 +1575,14 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors || zero_words > 0xffffffffu) return hipErrorInvalidValue;
     if (short_forward(b)) return launch_short_rfft_long(in, b, spec, mid, t, hist, zero_ptr, (uint32_t)zero_words, s);
     LongStarts at;
+    auto whole = [&]() {
+        const hipError_t err = set_lds(k_fwd_a_long, long_lds(kTileFA));
+        if (err != hipSuccess) return err;
+        const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, kTileFA); });
+        FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long, dim3(stretch_places(total)), dim3(tile_lanes(kTileFA)), long_lds(kTileFA), s, in, mid, t, total, zero_ptr,
+                     (uint32_t)zero_words, b.tab, at);
+        return hipGetLastError();
+    };
     auto pass_a = [&](auto size) {
         constexpr int TOP = decltype(size)::value;
         constexpr size_t lds = SplitTile<TOP == 14 ? 11 : 10, TOP>::kLds;
@@ -1542,7 +1593,8 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
                      (uint32_t)zero_words, b.tab, at);
         return hipGetLastError();
     };
-    const hipError_t e = log_columns(b.tab.t[b.count - 1].logM) <= 10 ? pass_a(std::integral_constant<int, 13>{}) : pass_a(std::integral_constant<int, 14>{});
+    const bool narrow = log_columns(b.tab.t[b.count - 1].logM) <= 10;  // the longest come last
+    const hipError_t e = launch_tiles(b) <= (narrow ? kWholeForwardLong : kWholeForwardLong11) ? whole() : narrow ? pass_a(std::integral_constant<int, 13>{}) : pass_a(std::integral_constant<int, 14>{});
     return e == hipSuccess ? launch_rfft_b_long(b, spec, mid, t, hist, s) : e;
 }
 

@@ -79,21 +79,17 @@ struct SplitTile {
     }
 };
 
-// One tile, columns col0 .. of a chunk whose samples are `sp` and whose intermediate is `mid`; d: 2^LOGE words; tw: the stage twiddles, which
-// other lanes may still be writing.
-template <int LOGN1, int LOGE, bool HALF>
-__device__ __forceinline__ void fwd_a_split(const float* __restrict__ in, const Span& sp, int logM, typename Cx<HALF>::One* __restrict__ mid,
-                                            const Tables& tb, uint32_t col0, float* d, const float2* tw, int tid, float in_scale)
+// Samples of a lane's two butterflies of the first stage, v[q] and v[8 + q]: rows j0 + q * N1 / 8 of two neighbouring columns.
+template <int LOGN1, int LOGT>
+__device__ __forceinline__ void load_columns(float2 (&v)[16], const float* __restrict__ in, const Span& sp, int logM, const Tables& tb, uint32_t col0, int tid)
 {
-    using G = SplitTile<LOGN1, LOGE>;
-    constexpr int N1 = G::N1, HP = G::HP, T = G::T;
+    constexpr int N1 = 1 << LOGN1, T = 1 << LOGT;
     const uint32_t M = 1u << logM, N2 = M >> LOGN1;
-    const int bp = tid & (T / 2 - 1), j0 = tid >> (G::LOGT - 1);
+    const int bp = tid & (T / 2 - 1), j0 = tid >> (LOGT - 1);
     const size_t left = sp.limit > sp.first ? sp.limit - sp.first : 0;
     const uint32_t end = left >> 2 < (size_t)(M >> 1) ? (uint32_t)(left >> 2) : M >> 1;  // pieces of four samples that are whole
     const float* src = end ? in + sp.first : reinterpret_cast<const float*>(tb.hi);
     auto piece = [&](int q) __attribute__((always_inline)) { return (uint32_t)(j0 + q * (N1 / 8)) * (N2 >> 1) + (col0 >> 1) + (uint32_t)bp; };
-    float2 v[16];
     Floats4 r[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) r[q] = *reinterpret_cast<const Floats4*>(src + 4 * (size_t)(piece(q) < end ? piece(q) : 0u));
@@ -112,6 +108,18 @@ __device__ __forceinline__ void fwd_a_split(const float* __restrict__ in, const 
                 v[8 + q] = load_pair(in, gi + 2, sp.limit);
             }
     }
+}
+
+// One tile, columns col0 .. of a chunk whose samples are `sp` and whose intermediate is `mid`; d: 2^LOGE words; tw: the stage twiddles, which
+// other lanes may still be writing.
+template <int LOGN1, int LOGE, bool HALF>
+__device__ __forceinline__ void fwd_a_split(const float* __restrict__ in, const Span& sp, int logM, typename Cx<HALF>::One* __restrict__ mid,
+                                            const Tables& tb, uint32_t col0, float* d, const float2* tw, int tid, float in_scale)
+{
+    using G = SplitTile<LOGN1, LOGE>;
+    constexpr int N1 = G::N1, HP = G::HP, T = G::T;
+    float2 v[16];
+    load_columns<LOGN1, G::LOGT>(v, in, sp, logM, tb, col0, tid);
     bf8<false>(v);
     bf8<false>(v + 8);
     G::exchange(

@@ -1,5 +1,5 @@
 """Tensors that start and end anywhere: pieces of eight and sixteen bytes are read where they lie, and the piece that a tensor's end cuts
-is read by samples (csrc/fft_core.h, csrc/fft.hip).  Every record is that of the tensor alone in a chunk filled up with zeros, where no
+is read by samples (csrc/fft_core.h, csrc/split_tile.h).  Every record is that of the tensor alone in a chunk filled up with zeros, where no
 piece is cut, and nothing of a neighbour gets in."""
 import numpy as np
 import pytest
@@ -12,6 +12,8 @@ SETS = {
     "one_workgroup": [1, 2, 3, 5, 31, 33, 34, 63, 127, 1021, 1022, 4095, 8190, 16381, 16387, 32765],
     "small_tiles": [32769, 32771, 65534, 65537, 1 << 17, 131070, 262143, 262149, 7],          # columns of 2^8 to 2^9
     "columns_to_2^10": [3, 65537, 131069, 131075, 262142, 524287, 524285, (1 << 20) - 1, (1 << 20) + 6, 70001],
+    "whole_tiles": [40001, 65537, 131069, 131075, 262142, 524287, 524285, (1 << 20) - 1, (1 << 20) + 6],  # no short ones: columns of 2^8 to 2^10
+    "whole_tiles_of_2^11": [40001, 300002, (1 << 20) + 6, (1 << 22) - 3],
     "columns_of_2^11": [1, 40001, 131074, 600003, (1 << 21) + 5, (1 << 22) - 2, 50002],
 }
 

@@ -185,6 +185,16 @@ def test_tensors_leave_the_small_tiles_where_they_stop_paying(runtime, tmp_path,
     assert any("k_inv_a_long_short" in k for k in receiver) == receive_a
 
 
+# tiles of 2^14 points: a tensor of 2^18 is eight of them, of 2^21 64 and of 2^22 128
+@pytest.mark.parametrize("sizes, kernel", [
+    ([1 << 18] * 12, "short"), ([1 << 18] * 13, "long"), ([1 << 18] * 16, "long"), ([1 << 21] * 8, "long"), ([1 << 21] * 8 + [1 << 16], "split"), ([1 << 22], "long"),
+    ([1 << 22, 1 << 21], "long"), ([1 << 22, 1 << 22], "split"), ([(1 << 19) - 5] * 32, "long"), ([(1 << 19) - 5] * 33, "split")])
+def test_few_tensors_have_their_first_pass_whole_in_the_lds(runtime, tmp_path, sizes, kernel):
+    sender, _ = kernels(runtime, tmp_path, segments(sizes, 0.5, 8))
+    first, = [k for k in sender if "k_fwd_a" in k]
+    assert kernel == ("short" if "long_short" in first else "split" if "split" in first else "long")
+
+
 # chunks of 2^20 and 2^22 hold 32 and 128 tiles of 2^14 points
 @pytest.mark.parametrize("logL, half, C, forward, inverse", [
     (19, 0, 16, False, True), (19, 1, 120, False, True), (20, 0, 31, False, True), (20, 0, 32, False, True), (20, 1, 31, False, True), (20, 1, 32, True, True),
