@@ -1112,15 +1112,25 @@ __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu
     fwd_a_split_tensor<TOP>(tab.t[share.tensor], share.blk, in, mid, tb);
 }
 
-// rows of 2^10
-__global__ __launch_bounds__(tile_lanes(kTallTile)) void k_fwd_b_long(const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb,
-                                                                     uint32_t* __restrict__ hist, uint32_t per_wg, LongTable tab, LongStarts at)
+// rows of 2^10 in tiles of 2^14, or few tensors of any rows in tiles of 2^13
+template <int LOGE>
+__global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b_long(const float2* __restrict__ mid, float2* __restrict__ spec, Tables tb,
+                                                                uint32_t* __restrict__ hist, uint32_t per_wg, LongTable tab, LongStarts at)
 {
     const LongShare share = long_share(at);
     const LongTensor& x = tab.t[share.tensor];
-    const uint32_t total = power_tiles(x.logM, kTallTile), per = per_wg < total ? per_wg : total;
-    fwd_b_workgroup<10, kTallTile, true, false>(share.blk, total / per, mid + long_mid(x), x.logM, spec + long_spec(x, share.tensor), 0u, tb,
-                                                hist + (size_t)share.tensor * kHistBins, total, per, 1.0f);
+    auto run = [&](auto n2) __attribute__((always_inline)) {
+        const uint32_t total = power_tiles(x.logM, LOGE), per = per_wg < total ? per_wg : total;
+        fwd_b_workgroup<decltype(n2)::value, LOGE, true, false>(share.blk, total / per, mid + long_mid(x), x.logM, spec + long_spec(x, share.tensor), 0u,
+                                                                tb, hist + (size_t)share.tensor * kHistBins, total, per, 1.0f);
+    };
+    if constexpr (LOGE < kTallTile) {
+        const int rows = log_rows(x.logM);
+        if (rows == 7) return run(std::integral_constant<int, 7>{});
+        if (rows == 8) return run(std::integral_constant<int, 8>{});
+        if (rows == 9) return run(std::integral_constant<int, 9>{});
+    }
+    run(std::integral_constant<int, 10>{});
 }
 
 template <int LOGE>
@@ -1457,6 +1467,10 @@ hipError_t by_tile_size(const LongBatch& b, uint32_t wide, Pass&& pass)
 //   random sets 60 190 / 193, 100 205 / 210;  2^22 128 75.4 / 71.9 (75.2 / 71.8), beside shorter ones 130 78.9 / 76.8, 160 81.2 / 79.9, 192 84.1 / 82.1 and 80.2 /
 //   77.8, 224 90.6 / 90.4, 256 89.7 / 90.0 (89.9 / 91.4) and 94.7 / 97.0, 384 120.1 / 122.2, 512 125.6 / 134.1.
 constexpr size_t kWholeForwardLong = 512, kWholeForwardLong11 = 255;
+// and up to how many, with rows of 2^10 and shorter ones, forward pass B has them as tiles of 2^13, one to a compute unit, where tiles of 2^14 would leave half of them
+// idle.  Senders in us, tiles of 2^14 / this: 98 56.5 / 54.5, 104 57.0 / 55.3, 112 57.9 / 56.0, 128 60.7 / 58.8, 60.7 / 58.9 and 60.2 / 59.9, 130 63.8 / 63.9 and 76.2 / 74.8, 132 63.5 / 67.4 and
+// 74.7 / 80.5, 136 64.0 / 67.3, 144 65.1 / 69.1, 160 66.4 / 70.1 and 68.2 / 69.5, 192 71.6 / 75.6.
+constexpr size_t kFewBothRows = 130;
 constexpr int kLongLogN = log_columns(kLongMax);  // the longest row or column
 // LDS of a pass: the tile and the stage twiddles
 constexpr size_t long_lds(int loge) { return ((size_t)(1 << loge) + (1 << kLongLogN)) * sizeof(float2); }
@@ -1605,7 +1619,7 @@ hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mi
     LongStarts at;
     uint32_t tall = b.count;  // the first with rows of 2^10: the longest come last
     while (tall > 0 && log_rows(b.tab.t[tall - 1].logM) >= 10) --tall;
-    // One launch, whatever the rows' lengths.  Persistent workgroups (k_fwd_b_long) pay for their runs of tiles in most launch sets, and a launch of their
+    // One launch, whatever the rows' lengths.  From 131 tiles on persistent workgroups (k_fwd_b_long) pay for their runs of tiles in most launch sets, and a launch of their
     // own for rows of 2^10 for a tail.  Sender and receiver in us, before (k_fwd_b_long<13> where rows of 2^10 were among few tiles, a launch for either from
     // 512 large tiles on) / this: random sets of 30 248 / 236.5, 40 279 / 269, 60 272.5 / 264, 100 471 / 450,
     // 200 746 / 723, 40 of 1 M and four of 2^21 470 / 445, 30 and ten 502 / 473, ten of 500 k and sixteen 371 / 364, 55 of 70 k and one 158 / 151.
@@ -1621,17 +1635,22 @@ hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mi
                      total, few, b.tab, at);
         return hipGetLastError();
     };
-    if (tall > 0) return tall == b.count ? pairs(std::integral_constant<int, 9>{}) : pairs(std::integral_constant<int, 10>{});
-    const size_t lds = long_lds(kTallTile) + kHistLdsWords * sizeof(uint32_t);
-    const hipError_t err = set_lds(k_fwd_b_long, lds);
-    if (err != hipSuccess) return err;
-    const uint32_t per = long_run(b, 0, b.count, kTallTile, most_wgs(kTallTile, 512));
-    const uint32_t g = long_starts(b, 0, b.count, &at, [&](const LongTensor& x) {
-        const uint32_t tiles = power_tiles(x.logM, kTallTile);
-        return tiles > per ? tiles / per : 1u;
-    });
-    FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_long, dim3(g), dim3(tile_lanes(kTallTile)), lds, s, mid, spec, t, hist, per, b.tab, at);
-    return hipGetLastError();
+    if (tall == b.count) return pairs(std::integral_constant<int, 9>{});
+    if (tall > 0 && launch_tiles(b) > kFewBothRows) return pairs(std::integral_constant<int, 10>{});
+    auto runs = [&](auto size) {
+        constexpr int LOGE = decltype(size)::value;
+        const size_t lds = long_lds(LOGE) + kHistLdsWords * sizeof(uint32_t);
+        const hipError_t err = set_lds(k_fwd_b_long<LOGE>, lds);
+        if (err != hipSuccess) return err;
+        const uint32_t per = long_run(b, 0, b.count, LOGE, most_wgs(LOGE, 512));
+        const uint32_t g = long_starts(b, 0, b.count, &at, [&](const LongTensor& x) {
+            const uint32_t tiles = power_tiles(x.logM, LOGE);
+            return tiles > per ? tiles / per : 1u;
+        });
+        FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), lds, s, mid, spec, t, hist, per, b.tab, at);
+        return hipGetLastError();
+    };
+    return tall > 0 ? runs(std::integral_constant<int, 13>{}) : runs(std::integral_constant<int, kTallTile>{});
 }
 
 hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out, float2* mid, Tables t, hipStream_t s)

@@ -18,6 +18,7 @@ SETS = {
     "just below it, then at it": [(65536, 31), (2097152, 1), (33000, 1)],
     "at it": [(65536, 32), (2097152, 1), (33000, 1), (32, 1)],
     "one short tensor beside long ones": [(40000, 1), (1500000, 4)],
+    "rows of every length, few tiles": [(40001, 1), (131072, 1), (200003, 1), (524288, 2), (1500000, 1)],
     "rows of 2^10 alone": [(1500000, 4), (3000001, 1)],
 }
 

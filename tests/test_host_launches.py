@@ -195,6 +195,16 @@ def test_few_tensors_have_their_first_pass_whole_in_the_lds(runtime, tmp_path, s
     assert kernel == ("short" if "long_short" in first else "split" if "split" in first else "long")
 
 
+# the same tiles
+@pytest.mark.parametrize("sizes, kernel", [
+    ([1 << 21] + [1 << 18] * 4, "short"), ([1 << 21] + [1 << 18] * 5, "small"), ([1 << 21] + [1 << 20] * 2, "small"), ([1 << 21] * 2 + [1 << 16], "small"),
+    ([1 << 21] * 2 + [1 << 16] * 2, "pairs"), ([1 << 21] * 2, "large"), ([1 << 18] * 16, "pairs")])
+def test_few_tensors_of_both_rows_have_a_tile_for_every_compute_unit(runtime, tmp_path, sizes, kernel):
+    sender, _ = kernels(runtime, tmp_path, segments(sizes, 0.5, 8))
+    second, = [k for k in sender if "k_fwd_b" in k]
+    assert kernel == ("short" if "long_short" in second else "pairs" if "pairs" in second else "small" if "ILi13E" in second else "large" if "ILi14E" in second else second)
+
+
 # chunks of 2^20 and 2^22 hold 32 and 128 tiles of 2^14 points
 @pytest.mark.parametrize("logL, half, C, forward, inverse", [
     (19, 0, 16, False, True), (19, 1, 120, False, True), (20, 0, 31, False, True), (20, 0, 32, False, True), (20, 1, 31, False, True), (20, 1, 32, True, True),
