@@ -1613,11 +1613,28 @@ bool tensors_compress_beside(const TensorTable& t, const LongBatch& b)
     const bool brief = t.piece[0].logm <= 11;  // they come longest first
     return b.count <= (uint32_t)kFewLong && (short_forward(b) || (brief ? b.units <= kBesideUnits / 2 : b.units < kBesideUnits));
 }
+// Receivers' tiles of rows of 2^8 have a quarter of a workgroup's lanes there, and of 2^7 an eighth, with a compute unit to themselves, where launches of their own hold several on one.
+// What hides that is the shorter tensors' time, by the longest of them, and as many compute units as they leave.  Receivers in us, two launches / one, beside 20 and 128 of 300, 4096, 9000 and 30 000:
+//   eight of 2^18 (512 workgroups) 27.2 / 28.0 and 28.8 / 29.8, 28.2 / 28.1 and 29.6 / 30.7, 31.4 / 28.2 and 33.3 / 31.3, 37.6 / 29.0 and 40.5 / 36.9;
+//   twelve (768) 31.8 / 35.4 and 32.8 / 37.3, 32.6 / 35.3 and 34.4 / 37.8, 35.8 / 35.5 and 37.7 / 38.4, 41.9 / 36.2 and 44.5 / 44.2;
+//   fifteen (960) 34.5 / 38.2 and 36.5 / 39.9, 35.6 / 38.2 and 36.8 / 41.1, 39.0 / 38.3 and 40.6 / 45.1, 45.1 / 42.2 and 47.8 / 50.9;
+//   nineteen of 2^16 (608) 24.1 / 24.2 and 28.6 / 26.3, 25.4 / 24.4 and 29.2 / 26.9;  of 2^17 (608) 27.1 / 27.5 and 28.9 / 29.0, 28.4 / 27.6 and 29.8 / 29.3, 31.5 / 27.7 and 33.2 / 34.2;
+//   nine of 2^19 (576, rows of 2^9: half of the lanes) 41.4 / 39.3 and 42.9 / 40.6.
+static bool decode_beside(const TensorTable& t, uint32_t pieces, const LongBatch& b)
+{
+    uint32_t idle = 0;  // rows of 2^8: two for a workgroup, of 2^7: one
+    for (uint32_t i = 0; i < b.count; ++i) {
+        const int logM = b.tab.t[i].logM, rows = short_rows(logM);
+        if (rows < 9) idle += (uint32_t)(rows - 6) << (logM - rows - kShortLogSlots);
+    }
+    const int longest = t.piece[0].logm;  // they come longest first
+    return idle < (longest <= 11 ? 1024u : longest <= 13 ? 1536u : 1920u) || (longest > 13 && pieces <= 64);
+}
 // Receivers of larger sets have the table of the longer ones' bitmaps there, 7 us and a launch's 3.  Sender and receiver in us, the table a launch of its own / there: ten
 // tensors 143.5 / 137.8, 20 153.0 / 147.8 and 141.7 / 135.5, 30 158.9 / 153.4, five of 500 and two of 2^21 112.3 / 106.7, six 189.5 / 184.2, 30 of 9 k and seven 209.5 / 204.1.
 bool tensors_decompress_beside(const TensorTable& t, uint32_t pieces, int bits, const LongBatch& b)
 {
-    return b.count <= (uint32_t)kFewLong && (short_decode(b) || (b.units < kBesideUnits && receive_applies(b, bits))) &&
+    return b.count <= (uint32_t)kFewLong && (short_decode(b) ? decode_beside(t, pieces, b) : b.units < kBesideUnits && receive_applies(b, bits)) &&
            tensors_lds(t, pieces, false) + kStaticLds <= kLdsBytes;
 }
 

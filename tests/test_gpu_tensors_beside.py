@@ -23,6 +23,7 @@ SETS = {
     "a compute unit to every workgroup": [9000] * 32 + [60001] * 7,
     "more workgroups than compute units": [8193] * 65 + [40001] * 12,
     "as many of either as go": [20001] * 128 + [60001] * 9 + [100001] * 8 + [200001] * 2,
+    "sender alone: many tiles of rows of 2^8": [300] * 20 + [150001] * 10,
     "two launches of shorter ones": [300] * 129 + [60001] * 2,
     "twenty long ones": [300] + [40001] * 20,
     "nineteen, halves of the LDS": [9000] * 20 + [70001] * 6 + [200001] * 6 + [300001] * 4 + [1100001] * 3,
