@@ -36,22 +36,48 @@ def test_every_tensor_is_what_it_is_alone(name, theta, bits):
     check_alone(name, SETS[name], theta, bits)
 
 
+TABLES = [300, 9000, 300001, 600003, 1048577, 2097155]  # the bitmaps' table of the longer ones is beside the short ones
+
+
+class Stream:
+    def __init__(self, sizes, theta=0.3, bits=8):
+        self.sizes, self.theta, self.bits, self.offsets = sizes, theta, bits, [0]
+        for s in sizes:
+            self.offsets.append(self.offsets[-1] + s)
+        grad = torch.randn(self.offsets[-1], device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+        self.packed = torch.empty(fftsp.packed_bytes_segments(self.offsets, theta, bits), dtype=torch.uint8, device="cuda")
+        self.work = torch.empty(fftsp.workspace_bytes_segments(self.offsets, bits), dtype=torch.uint8, device="cuda")
+        self.out = torch.empty_like(grad)
+        fftsp.compress_segments(grad, self.offsets, theta, bits, self.packed, self.work)
+
+    def status(self, theta=None):
+        fftsp.decompress_segments(self.packed, self.packed.numel(), self.out, self.offsets, theta or self.theta, self.bits, self.work)
+        return fftsp.device_status(self.work)
+
+
 # a short one of ResNet-20's tensors and one of 2^16; a short one and two long ones of a set whose bitmaps' table is beside the short ones
 @pytest.mark.parametrize("name,tensor", [("ResNet-20", 1), ("ResNet-20", 21), ("tables", 0), ("tables", 2), ("tables", 5)])
 def test_a_wrong_bitmap_is_reported(name, tensor):
-    sizes, theta, bits = sorted(SETS.get(name, [300, 9000, 300001, 600003, 1048577, 2097155])), 0.3, 8
-    offsets = [0]
-    for s in sizes:
-        offsets.append(offsets[-1] + s)
-    grad = torch.randn(offsets[-1], device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
-    packed = torch.empty(fftsp.packed_bytes_segments(offsets, theta, bits), dtype=torch.uint8, device="cuda")
-    work = torch.empty(fftsp.workspace_bytes_segments(offsets, bits), dtype=torch.uint8, device="cuda")
-    out = torch.empty_like(grad)
-    fftsp.compress_segments(grad, offsets, theta, bits, packed, work)
+    st = Stream(sorted(SETS.get(name, TABLES)))
+    assert st.status() == 0
     at = 64
-    for s in sizes[:tensor]:
+    for s in st.sizes[:tensor]:
         length = max(32, 1 << (s - 1).bit_length())
-        at += fftsp.packed_bytes(s, length, theta, bits) - 64
-    packed[at + 16:at + 18] = 255
-    fftsp.decompress_segments(packed, packed.numel(), out, offsets, theta, bits, work)
-    assert fftsp.device_status(work) == 6
+        at += fftsp.packed_bytes(s, length, st.theta, st.bits) - 64
+    st.packed[at + 16:at + 18] = 255
+    assert st.status() == 6
+
+
+# Receivers whose first kernel has the shorter and the longer tensors, either kind of it; launches of their own; and sets of one kind of tensors.  The
+# stream's header is looked at once, by whichever kernel is the call's first.
+@pytest.mark.parametrize("name", ["ResNet-20", "tables", "two launches of shorter ones", "sender alone: many tiles of rows of 2^8", "shorter ones", "longer ones"])
+def test_a_wrong_header_is_reported(name):
+    st = Stream({"tables": TABLES, "shorter ones": [300, 9000], "longer ones": [60001] * 2}.get(name) or SETS[name])
+    assert st.status() == 0
+    for word in (0, 1, 2, 3, 5, 6, 7, 12):  # what it is, its version, samples, tensors, code bits, mantissa, scale
+        st.packed[4 * word] ^= 1
+        assert st.status() == 6, word
+        st.packed[4 * word] ^= 1
+        assert st.status() == 0, word
+    assert st.status(theta=0.25) == 6  # a shorter stream, other numbers of kept bins
+    assert st.status() == 0
