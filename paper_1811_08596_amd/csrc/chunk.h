@@ -40,7 +40,6 @@ struct TensorTable {
     uint32_t kept[kChunkMaxLogL - 4], stride[kChunkMaxLogL - 4];  // kept bins and record bytes, by logm - 4
     uint32_t base;               // number of the table's first entry among all such tensors of the call
 };
-static_assert(sizeof(TensorTable) + sizeof(FewLong) + 192 <= 4096, "kernel arguments are at most 4 KiB");
 struct QuantizerArgs {
     int bits, m;
 };

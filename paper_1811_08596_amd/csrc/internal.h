@@ -6,6 +6,7 @@
 #include <stdint.h>
 #include <stddef.h>
 #include <string>
+#include <type_traits>
 
 namespace fftsp {
 
@@ -166,15 +167,15 @@ struct LongTable {
     LongTensor t[kMaxLongTensors];
     LongStarts tiles;  // the codec kernels' share: a workgroup per tile of bins
 };
-static_assert(sizeof(LongTable) + sizeof(LongStarts) + 256 <= 4096, "kernel arguments are at most 4 KiB");
 // a launch set of the long tensors (host)
 struct LongBatch {
     LongTable tab;
     uint32_t count, units;  // tensors, units of work area
 };
-// A few of them, as many as there is room for beside a table of shorter ones in a launch's arguments (chunk.h).  at[i]: the first workgroup of tensor i's share.
+// A few of them, as many as there is room for beside a table of shorter ones in a launch's arguments (with one more the receiver's are too many: FFTSP_LAUNCH).  at[i]: the first workgroup of tensor i's share.
 // Sender and receiver in us, up to twelve / up to nineteen: random sets of 30 tensors 207.8 / 188.0, 40 182.6 / 169.1, 50 192.9 / 180.6 and 220.6 / 200.9.
-constexpr int kFewLong = 19;
+// In launches of their own / there, twenty and twenty-two: of 40 k beside 60 of 9 k 83.2 / 74.4 and 83.9 / 77.9, of 2^17 beside 20 of 300 83.2 / 81.0 and 84.8 / 82.3, of 300 k 144 / 140 and 147 / 144.
+constexpr int kFewLong = 22;
 struct FewLong {
     LongTensor t[kFewLong];
     uint16_t at[kFewLong];
@@ -288,9 +289,18 @@ void enable(bool on);
 std::string report();
 }  // namespace prof
 
+// bytes of a kernel's arguments
+template <typename... A>
+constexpr size_t argument_bytes(void (*)(A...))
+{
+    size_t at = 0;
+    ((at = (at + alignof(A) - 1) / alignof(A) * alignof(A) + sizeof(A)), ...);
+    return at;
+}
 // Launch `kernel` and, when profiling is on, bracket it with events under `name`.
 #define FFTSP_LAUNCH(name, kernel, grid, block, lds, stream, ...)                    \
     do {                                                                             \
+        static_assert(::fftsp::argument_bytes(std::decay_t<decltype(kernel)>{}) <= 4096, "kernel arguments are at most 4 KiB"); \
         const int fftsp_prof_id_ = ::fftsp::prof::enabled() ? ::fftsp::prof::begin(name, stream) : -1; \
         hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);           \
         if (fftsp_prof_id_ >= 0) ::fftsp::prof::end(fftsp_prof_id_, stream);         \

@@ -1,4 +1,4 @@
-"""Sets of tensors: those of one workgroup each and the first kernel of a few longer ones, nineteen at most, are one launch
+"""Sets of tensors: those of one workgroup each and the first kernel of a few longer ones, twenty-two at most, are one launch
 (csrc/chunk.hip), whether every workgroup has a compute unit to itself or not.  Every record and every sample is what a call with that
 tensor as its only chunk gives, bit for bit, on either side of that line; a bitmap that claims too many bins is reported."""
 import pytest
@@ -26,6 +26,9 @@ SETS = {
     "sender alone: many tiles of rows of 2^8": [300] * 20 + [150001] * 10,
     "two launches of shorter ones": [300] * 129 + [60001] * 2,
     "twenty long ones": [300] + [40001] * 20,
+    "as many long ones as go": [300] + [40001] * 22,
+    "one more of them": [300] + [40001] * 23,
+    "twenty-two, halves of the LDS": [9000] * 20 + [70001] * 9 + [200001] * 6 + [300001] * 4 + [1100001] * 3,
     "nineteen, halves of the LDS": [9000] * 20 + [70001] * 6 + [200001] * 6 + [300001] * 4 + [1100001] * 3,
 }
 
