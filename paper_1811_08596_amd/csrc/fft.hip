@@ -258,14 +258,14 @@ __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __re
 
 // The tiles of a few tensors, 2^13 points to a workgroup of their own, whole in the LDS: two to a compute unit and half as many trips through it as in
 // half of it.  Figures at kWholeForwardLong.
-__global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a_long(const float* __restrict__ in, float2* __restrict__ mid, Tables tb, uint32_t total,
+__global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a_long(const float* __restrict__ in, float2* __restrict__ mid, Tables tb, uint32_t total, uint32_t step,
                                                                    uint32_t* __restrict__ zero_ptr, uint32_t zero_words, LongTable tab, LongStarts at)
 {
     constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE);
     extern __shared__ float2 smem[];
     float2 *const d = smem, *const tw = smem + (1 << LOGE);
     for (uint32_t i = blockIdx.x * NT + threadIdx.x; i < zero_words; i += gridDim.x * NT) zero_ptr[i] = 0u;
-    const uint32_t t = in_turned_stretches(total);
+    const uint32_t t = in_turned_stretches(total, step);
     if (t >= total) return;
     const LongShare share = long_share(at, t);
     const LongTensor& x = tab.t[share.tensor];
@@ -1101,12 +1101,12 @@ constexpr int kTallTile = 14;  // of rows of 2^10, where a launch has no others
 // 138.5 / 110; senders 240 / 234, 193 / 181, 412 / 380, 24 tensors of 4.2 M padded samples 117 / 109.  Tiles of 2^14 for columns of 2^10: equal.
 template <int TOP>
 __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_fwd_a_split_long(
-    const float* __restrict__ in, float2* __restrict__ mid, Tables tb, uint32_t total, uint32_t* __restrict__ zero_ptr, uint32_t zero_words,
+    const float* __restrict__ in, float2* __restrict__ mid, Tables tb, uint32_t total, uint32_t step, uint32_t* __restrict__ zero_ptr, uint32_t zero_words,
     LongTable tab, LongStarts at)
 {
     extern __shared__ float2 smem[];
     for (uint32_t i = blockIdx.x * tile_lanes(TOP) + threadIdx.x; i < zero_words; i += gridDim.x * tile_lanes(TOP)) zero_ptr[i] = 0u;
-    const uint32_t t = in_turned_stretches(total);
+    const uint32_t t = in_turned_stretches(total, step);
     if (t >= total) return;
     const LongShare share = long_share(at, t);
     fwd_a_split_tensor<TOP>(tab.t[share.tensor], share.blk, in, mid, tb);
@@ -1589,12 +1589,17 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors || zero_words > 0xffffffffu) return hipErrorInvalidValue;
     if (short_forward(b)) return launch_short_rfft_long(in, b, spec, mid, t, hist, zero_ptr, (uint32_t)zero_words, s);
     LongStarts at;
+    // What the XCDs begin further into a tensor each (stretches.h): tensors of 128 tiles, or of 64 where all of the launch is on the chip at once.  Sender in us, from the
+    // stretch's start / further: 20 of 2^20 131.1 / 133.4, 32 184.8 / 189.5, 48 of 2^19 148.9 / 150.1, 30 of 600 k 166.4 / 170.5;  eight of 2^20 (512 tiles) 74.6 / 72.1, twelve 91.1 / 92.4.
+    auto step_of = [&](uint32_t total, int loge) {
+        return power_tiles(b.tab.t[b.count - 1].logM, loge) >= (loge == kTileFA && total <= 512u ? 64u : 128u) ? kTurnStep : 0u;
+    };
     auto whole = [&]() {
         const hipError_t err = set_lds(k_fwd_a_long, long_lds(kTileFA));
         if (err != hipSuccess) return err;
         const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, kTileFA); });
-        FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long, dim3(stretch_places(total)), dim3(tile_lanes(kTileFA)), long_lds(kTileFA), s, in, mid, t, total, zero_ptr,
-                     (uint32_t)zero_words, b.tab, at);
+        FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long, dim3(stretch_places(total)), dim3(tile_lanes(kTileFA)), long_lds(kTileFA), s, in, mid, t, total, step_of(total, kTileFA),
+                     zero_ptr, (uint32_t)zero_words, b.tab, at);
         return hipGetLastError();
     };
     auto pass_a = [&](auto size) {
@@ -1603,7 +1608,7 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
         const hipError_t err = set_lds(k_fwd_a_split_long<TOP>, lds);
         if (err != hipSuccess) return err;
         const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, TOP); });
-        FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_split_long<TOP>, dim3((total + 7) / 8 * 8), dim3(tile_lanes(TOP)), lds, s, in, mid, t, total, zero_ptr,
+        FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_split_long<TOP>, dim3((total + 7) / 8 * 8), dim3(tile_lanes(TOP)), lds, s, in, mid, t, total, step_of(total, TOP), zero_ptr,
                      (uint32_t)zero_words, b.tab, at);
         return hipGetLastError();
     };

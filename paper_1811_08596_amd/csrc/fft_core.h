@@ -322,7 +322,7 @@ struct MirroredRows {
 // this workgroup's tile; at or above `total`: none
 __device__ __forceinline__ uint32_t in_stretches(uint32_t total) { return stretch_tile(blockIdx.x, total); }
 __device__ __forceinline__ uint32_t in_stretches(uint32_t total, uint32_t few) { return stretch_tile(blockIdx.x, total, few); }
-__device__ __forceinline__ uint32_t in_turned_stretches(uint32_t total) { return turned_tile(blockIdx.x, total); }
+__device__ __forceinline__ uint32_t in_turned_stretches(uint32_t total, uint32_t step) { return turned_tile(blockIdx.x, total, step); }
 
 // Accesses that leave the caches to others (ONCE), for what the call does not touch again: whole calls choose, see kOnceBytes.
 template <bool ONCE>

@@ -23,16 +23,17 @@ constexpr uint32_t stretch_tile(uint32_t place, uint32_t total, uint32_t few)
     const uint32_t t = stretch_start(xcd, total - few) + i - mine;
     return t < stretch_start(xcd + 1u, total - few) ? few + t : total;
 }
-// One kind, with the XCDs beginning their stretches 16 tiles further into a tensor each.  For passes whose tiles are a few columns of a tensor, up to 128 tiles to
-// one: rows are 8 or 16 KiB apart, and XCDs that are at the same columns of tensors a power of two apart ask the same channels of the memory.  Forward
-// pass A of tensors' senders, sender in us, each from its stretch's start / this (in brackets a persistent kernel that dealt the tiles out otherwise): 2^21 16 208.3 / 199.8 (201.7),
-// 24 276 / 277 (289), 28 317 / 316 (333), 32 363 / 352 (355), 48 572 / 552 (558);  2^22 four 132 / 127 (134), eight 227 / 209 (225), sixteen 374 / 372 (394).  An eighth of the stretch
-// further each: 28 of 2^21 324, 12 and thirty of 70 k 183 where this takes 177.
-constexpr uint32_t turned_tile(uint32_t place, uint32_t total)
+// One kind, with the XCDs beginning their stretches `step` tiles further into a tensor each, and going round (0: where they start).  For passes whose tiles are a few
+// columns of a tensor, 128 tiles to the longest: their rows are 8 KiB apart, and XCDs that are at the same columns of tensors a power of two apart ask the same channels of the
+// memory.  Forward pass A of tensors' senders, sender in us, each from its stretch's start / this (in brackets a persistent kernel that dealt the tiles out
+// otherwise): 2^21 16 208.3 / 199.8 (201.7), 24 276 / 277 (289), 28 317 / 316 (333), 32 363 / 352 (355), 48 572 / 552 (558);  2^22 four 132 / 127 (134), eight 227 / 209 (225),
+// sixteen 374 / 372 (394).  An eighth of the stretch further each: 28 of 2^21 324, 12 and thirty of 70 k 183 where this takes 177.
+constexpr uint32_t kTurnStep = 16;
+constexpr uint32_t turned_tile(uint32_t place, uint32_t total, uint32_t step)
 {
     const uint32_t xcd = place & 7u, lo = stretch_start(xcd, total), hi = stretch_start(xcd + 1u, total), t = lo + (place >> 3);
     if (t >= hi) return total;
-    const uint32_t to = t + ((16u * xcd - lo) & 127u) % (hi - lo);
+    const uint32_t to = t + (step ? ((step * xcd - lo) & (8u * step - 1u)) % (hi - lo) : 0u);
     return to < hi ? to : to - (hi - lo);
 }
 // workgroups that have a tile for everyone

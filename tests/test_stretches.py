@@ -11,7 +11,7 @@ SOURCE = r"""
 #include "%s/paper_1811_08596_amd/csrc/stretches.h"
 extern "C" uint32_t tile(uint32_t place, uint32_t total) { return fftsp::stretch_tile(place, total); }
 extern "C" uint32_t tile_of_two(uint32_t place, uint32_t total, uint32_t few) { return fftsp::stretch_tile(place, total, few); }
-extern "C" uint32_t turned(uint32_t place, uint32_t total) { return fftsp::turned_tile(place, total); }
+extern "C" uint32_t turned(uint32_t place, uint32_t total, uint32_t step) { return fftsp::turned_tile(place, total, step); }
 extern "C" uint32_t places(uint32_t total, uint32_t few) { return fftsp::stretch_places(total, few); }
 """
 
@@ -54,7 +54,8 @@ def test_a_launch_of_two_kinds(lib, few, others):
 def test_stretches_that_begin_at_different_columns(lib, total):
     """The same stretches, each gone round once from another place on: the XCDs begin in different eighths of a tensor of 128 tiles."""
     straight = per_xcd(lib.places(total, 0), lambda p: lib.tile(p, total), total)
-    turned = per_xcd(lib.places(total, 0), lambda p: lib.turned(p, total), total)
+    turned = per_xcd(lib.places(total, 0), lambda p: lib.turned(p, total, 16), total)
+    assert per_xcd(lib.places(total, 0), lambda p: lib.turned(p, total, 0), total) == straight
     for a, b in zip(straight, turned):
         assert sorted(b) == a and (not b or b == a[a.index(b[0]):] + a[:a.index(b[0])])
     if total >= 1024:
