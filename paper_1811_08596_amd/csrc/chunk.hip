@@ -1619,7 +1619,7 @@ bool tensors_compress_beside(const TensorTable& t, const LongBatch& b)
 //   twelve (768) 31.8 / 35.4 and 32.8 / 37.3, 32.6 / 35.3 and 34.4 / 37.8, 35.8 / 35.5 and 37.7 / 38.4, 41.9 / 36.2 and 44.5 / 44.2;
 //   fifteen (960) 34.5 / 38.2 and 36.5 / 39.9, 35.6 / 38.2 and 36.8 / 41.1, 39.0 / 38.3 and 40.6 / 45.1, 45.1 / 42.2 and 47.8 / 50.9;
 //   nineteen of 2^16 (608) 24.1 / 24.2 and 28.6 / 26.3, 25.4 / 24.4 and 29.2 / 26.9;  of 2^17 (608) 27.1 / 27.5 and 28.9 / 29.0, 28.4 / 27.6 and 29.8 / 29.3, 31.5 / 27.7 and 33.2 / 34.2;
-//   nine of 2^19 (576, rows of 2^9: half of the lanes) 41.4 / 39.3 and 42.9 / 40.6.
+//   nine of 2^19 (576, rows of 2^9: half of the lanes) 41.4 / 39.3 and 42.9 / 40.6;  twenty and twenty-two of 2^17 beside 60 and 128 of 9000 32.7 / 28.9 and 31.2 / 32.3, 32.9 / 33.1 and 31.5 / 32.8.
 static bool decode_beside(const TensorTable& t, uint32_t pieces, const LongBatch& b)
 {
     uint32_t idle = 0;  // rows of 2^8: two for a workgroup, of 2^7: one
@@ -1628,7 +1628,7 @@ static bool decode_beside(const TensorTable& t, uint32_t pieces, const LongBatch
         if (rows < 9) idle += (uint32_t)(rows - 6) << (logM - rows - kShortLogSlots);
     }
     const int longest = t.piece[0].logm;  // they come longest first
-    return idle < (longest <= 11 ? 1024u : longest <= 13 ? 1536u : 1920u) || (longest > 13 && pieces <= 64);
+    return longest <= 11 ? idle < 1024u : longest <= 13 ? idle + 4u * pieces < 1700u : idle < 1920u || pieces <= 64u;
 }
 // Receivers of larger sets have the table of the longer ones' bitmaps there, 7 us and a launch's 3.  Sender and receiver in us, the table a launch of its own / there: ten
 // tensors 143.5 / 137.8, 20 153.0 / 147.8 and 141.7 / 135.5, 30 158.9 / 153.4, five of 500 and two of 2^21 112.3 / 106.7, six 189.5 / 184.2, 30 of 9 k and seven 209.5 / 204.1.

@@ -208,8 +208,8 @@ def test_few_tensors_of_both_rows_have_a_tile_for_every_compute_unit(runtime, tm
 # a tensor of 2^18 is 64 workgroups of a receiver's inverse pass B, of 2^17 and 2^16 32, with a quarter and an eighth of the lanes
 @pytest.mark.parametrize("shorter, longer, beside", [
     ([300] * 128, [1 << 18] * 7, True), ([300] * 128, [1 << 18] * 8, False), ([300], [1 << 18] * 8, False), ([4096] * 20, [1 << 17] * 15, True),
-    ([4096] * 20, [1 << 17] * 16, False), ([300] * 128, [1 << 16] * 19, True), ([300] * 20, [1 << 19] * 9, True), ([9000] * 128, [1 << 18] * 11, True),
-    ([9000] * 128, [1 << 18] * 12, False), ([30000] * 64, [1 << 18] * 18, True), ([30000] * 65, [1 << 18] * 15, False), ([30000] * 128, [1 << 18] * 14, True)])
+    ([4096] * 20, [1 << 17] * 16, False), ([300] * 128, [1 << 16] * 19, True), ([300] * 20, [1 << 19] * 9, True), ([9000] * 128, [1 << 18] * 9, True),
+    ([9000] * 128, [1 << 18] * 10, False), ([9000], [1 << 18] * 13, True), ([30000] * 64, [1 << 18] * 18, True), ([30000] * 65, [1 << 18] * 15, False), ([30000] * 128, [1 << 18] * 14, True)])
 def test_receivers_leave_the_shorter_tensors_launch_where_its_workgroups_lie_idle(runtime, tmp_path, shorter, longer, beside):
     _, receiver = kernels(runtime, tmp_path, segments(shorter + longer, 0.3, 8))
     assert ("beside" in receiver[0]) == beside and any("k_decode_inv_b_long" in k for k in receiver) == (not beside)
