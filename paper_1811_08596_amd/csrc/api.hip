@@ -972,8 +972,7 @@ static hipError_t run_beside(hipStream_t user, S&& side, M&& main)
 //   2^17 132 / 94 and 145 / 111;  2^21 135 / 119 and 158 / 133;  2^22 143 / 140 and 165 / 157, waited for 167 / 160 and 183 / 190;
 //   2^23 180 / 192 and 182 / 208, waited for 226 / 215 and 238 / 244;  2^24 278 / 290 and 280 / 301, waited for 307 / 310 and
 //   326 / 333;  2^26 1010 / 1028 and 1014 / 1039, waited for 1054 / 1056 and 1074 / 1081.
-// From 2^24 on both gain; below, with up to kFewLong longer tensors, their first kernel is in the short ones' launch (chunk.hip).  Per-kernel timing wants one chain.
-constexpr uint32_t kSideUnits = 1u << (23 - kLongUnitLog);
+// From 2^24 on (kSideUnits) both gain; below, with up to kFewLong longer tensors, their first kernel is in the short ones' launch (chunk.hip).  Per-kernel timing wants one chain.
 template <typename S, typename M>
 static hipError_t run_segments(const SegmentPlan& plan, hipStream_t user, S&& side, M&& main)
 {

@@ -40,6 +40,9 @@ struct TensorTable {
     uint32_t kept[kChunkMaxLogL - 4], stride[kChunkMaxLogL - 4];  // kept bins and record bytes, by logm - 4
     uint32_t base;               // number of the table's first entry among all such tensors of the call
 };
+// From so many units of longer tensors on they have a stream of their own beside the shorter ones (api.hip, with the figures); below, their first kernel may be in
+// the shorter ones' launch.
+constexpr uint32_t kSideUnits = 1u << (23 - kLongUnitLog);
 struct QuantizerArgs {
     int bits, m;
 };

@@ -1604,14 +1604,16 @@ static int longest_of(const LongBatch& b) { return b.tab.t[b.count - 1].logM; } 
 // launch's 3 hide behind the shorter ones' workgroups, which the grid starts with, also where they are more than compute units.  Sender and receiver in us, two launches /
 // one: ResNet-20's 22 tensors 85.6 / 72.7, one of 2^16 and three of 300 54.4 / 41.5, three and one of 2^15 81.9 / 69.1, random sets of ten 99.0 / 82.1, 93.8 / 77.4 and 115 / 106;
 // five of 20 k and twelve of 2^16 89.9 / 76.4, four of 2^18 94.9 / 81.0, six 103.0 / 86.4, three of 2^19 104.3 / 86.7; sixty of 9 k, six of 2^16 and two of 2^18 77.4 / 63.6.
-// Senders have forward pass A of larger sets there, too, in half of the LDS, up to where run_segments takes two streams, or half of that beside tensors that
-// are done before it is: ten tensors 158 / 143, 20 164 / 149, 30 176 / 159, five of 20 k and two of 2^21 147 / 135, 30 of 30 k and seven 234 / 209, 20 of 20 k and three of 2^22
+// Senders have forward pass A of larger sets there, too, up to where run_segments takes two streams.  The kernel has the codec's 118 registers, so a compute unit holds one of
+// its workgroups, and its tiles in half of the LDS have no other one beside them (in launches of their own two): what pays for that is the shorter tensors' time, and beside tensors that are
+// done sooner the line lies at half as many.  Ten tensors 158 / 143, 20 164 / 149, 30 176 / 159, five of 20 k and two of 2^21 147 / 135, 30 of 30 k and seven 234 / 209, 20 of 20 k and three of 2^22
 // 234 / 218;  five of 500 and two of 2^21 116 / 112, four 147 / 145.5, six 189 / 197;  30 of 9 k and eight 220 / 232.
-constexpr uint32_t kBesideUnits = 1u << (23 - kLongUnitLog);
+// Against launches of their own as they are now (k_fwd_a_long), senders: five of 500 and two of 2^21 67.4 / 66.1, three 76.1 / 74.4, four 85.8 / 87.9;  128 of 4096 and three 83.8 / 74.1, four
+// 93.5 / 91.3;  30 of 9 k and three 86.9 / 74.1, four 96.7 / 96.9, seven 137 / 131;  128 of 9 k and seven 136 / 138;  100 of 30 k and seven 146 / 137.
 bool tensors_compress_beside(const TensorTable& t, const LongBatch& b)
 {
     const bool brief = t.piece[0].logm <= 11;  // they come longest first
-    return b.count <= (uint32_t)kFewLong && (short_forward(b) || (brief ? b.units <= kBesideUnits / 2 : b.units < kBesideUnits));
+    return b.count <= (uint32_t)kFewLong && (short_forward(b) || (brief ? b.units <= kSideUnits / 2 : b.units < kSideUnits));
 }
 // Receivers' tiles of rows of 2^8 have a quarter of a workgroup's lanes there, and of 2^7 an eighth, with a compute unit to themselves, where launches of their own hold several on one.
 // What hides that is the shorter tensors' time, by the longest of them, and as many compute units as they leave.  Receivers in us, two launches / one, beside 20 and 128 of 300, 4096, 9000 and 30 000:
@@ -1634,7 +1636,7 @@ static bool decode_beside(const TensorTable& t, uint32_t pieces, const LongBatch
 // tensors 143.5 / 137.8, 20 153.0 / 147.8 and 141.7 / 135.5, 30 158.9 / 153.4, five of 500 and two of 2^21 112.3 / 106.7, six 189.5 / 184.2, 30 of 9 k and seven 209.5 / 204.1.
 bool tensors_decompress_beside(const TensorTable& t, uint32_t pieces, int bits, const LongBatch& b)
 {
-    return b.count <= (uint32_t)kFewLong && (short_decode(b) ? decode_beside(t, pieces, b) : b.units < kBesideUnits && receive_applies(b, bits)) &&
+    return b.count <= (uint32_t)kFewLong && (short_decode(b) ? decode_beside(t, pieces, b) : b.units < kSideUnits && receive_applies(b, bits)) &&
            tensors_lds(t, pieces, false) + kStaticLds <= kLdsBytes;
 }
 

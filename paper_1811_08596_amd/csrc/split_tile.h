@@ -13,8 +13,8 @@ constexpr int log_columns(int logM) { return (logM + 1) / 2; }  // log2 N1
 __host__ __device__ __forceinline__ uint32_t power_tiles(int logM, int loge) { return 1u << (logM - loge); }
 
 // Forward pass A with a tile in half of the LDS: 16 points a lane stay in registers, and between the stages real and imaginary parts go
-// through LDS one after the other.  Two tiles of 2^14 points or four of 2^13 are on a compute unit, all 32 waves of it, so columns of 2^11
-// are read 64 bytes wide instead of 32.  What it costs is LDS instructions of four bytes instead of eight, and the persistent kernel's loads ahead.
+// through LDS one after the other.  In kernels of 64 registers two tiles of 2^14 points or four of 2^13 are on a compute unit, all 32 waves of it, so
+// columns of 2^11 are read 64 bytes wide instead of 32 (chunk.hip has such tiles in a kernel of 118, one to a compute unit).  What it costs is LDS instructions of four bytes instead of eight, and the persistent kernel's loads ahead.
 // The same radices, twiddles and order of operations as fwd_a_run and fwd_a_tile: the bits are the same.
 // Calls in us, persistent / this, 2^22 by number of tiles of 2^14: binary32 512 120.7 / 119.7, 1024 208 / 222, 1280 242.6 / 241.8, 1536 281 / 284,
 //   1920 354.8 / 348.1, 3072 582 / 578, 4224 (138 M samples) 817.7 / 759.5, kernel 330 / 264 (with reads that ask for no alignment and leave out a
