@@ -99,7 +99,6 @@ size_t record_stride(uint32_t L, uint32_t k, int bits)
 
 constexpr size_t kStreamHeader = 64;
 
-bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 uint32_t segment_length(size_t size)
 {

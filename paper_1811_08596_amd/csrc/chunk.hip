@@ -1277,7 +1277,7 @@ __global__ __launch_bounds__(NT) void k_chunk_rfft(const float* __restrict__ in,
 
 template <int LOGM, int NT>
 __global__ __launch_bounds__(NT) void k_chunk_irfft(const float2* __restrict__ spec, uint32_t sstride, size_t C, Tables tb,
-                                                    float* __restrict__ out, size_t n, int aligned)
+                                                    float* __restrict__ out, size_t n)
 {
     using G = Geo<LOGM, NT>;
     constexpr int RL = stage_radix_log(LOGM);
@@ -1308,7 +1308,7 @@ __global__ __launch_bounds__(NT) void k_chunk_irfft(const float2* __restrict__ s
     __syncthreads();
     const float scale = 1.0f / (float)(2 * G::M);
     fft_from_registers<LOGM, G::LOGE, NT, G::WAVES, true, false, RL>(x, d, tw, tid, [&](int b, int i, int o, float2 v) {
-        const Span sp = UniformChunks(n, C, G::T, 2u * G::M, 0u, aligned).span(b);
+        const Span sp = UniformChunks(n, C, G::T, 2u * G::M, 0u, 0).span(b);
         store_pair(out, sp.first + 2 * (size_t)(i + o), sp.limit, make_float2(v.x * scale, v.y * scale));
     });
 }
@@ -1340,7 +1340,7 @@ HeaderInfo header_info(const CodecArgs& a, int write)
     return HeaderInfo{write, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S,
                       a.hdr_theta, a.time_domain ? 1u : 0u, (uint32_t)a.hdr_scale};
 }
-int alignment(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; }
+int aligned8(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; }
 
 template <int LOGM, int NT>
 constexpr size_t sender_lds()
@@ -1396,7 +1396,7 @@ hipError_t compress_as(const float* in, size_t n, const CodecArgs& a, uint8_t* s
     const hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     FFTSP_LAUNCH("chunk_compress", kern, dim3((unsigned)((a.C + G::T - 1) / G::T)), dim3(NT), lds, s, in, n, a.C,
-                 alignment(in), t, pack_args(a), stream, records, header_info(a, 1), ctl);
+                 aligned8(in), t, pack_args(a), stream, records, header_info(a, 1), ctl);
     return hipGetLastError();
 }
 
@@ -1431,7 +1431,7 @@ hipError_t decompress_as(const PeerList& streams, int npeers, int plain, const C
     const hipError_t e = allow_lds(kern, most_receiver_lds<LOGM, NT>(G::CPW));
     if (e != hipSuccess) return e;
     FFTSP_LAUNCH("chunk_decompress", kern, dim3((unsigned)((a.C + G::T - 1) / G::T)), dim3(NT), lds, s, streams,
-                 (uint32_t)npeers, plain, a.C, t, pack_args(a), header_info(a, 1), out, n, alignment(out), gain,
+                 (uint32_t)npeers, plain, a.C, t, pack_args(a), header_info(a, 1), out, n, aligned8(out), gain,
                  (uint32_t)region, stride, ctl, note, verdicts);
     return hipGetLastError();
 }
@@ -1445,7 +1445,7 @@ hipError_t rfft_as(const float* in, size_t n, size_t C, float2* spec, uint32_t s
     auto kern = k_chunk_rfft<LOGM, NT>;
     const hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
-    FFTSP_LAUNCH("rfft_chunk", kern, dim3((unsigned)((C + G::T - 1) / G::T)), dim3(NT), lds, s, in, n, C, alignment(in), t,
+    FFTSP_LAUNCH("rfft_chunk", kern, dim3((unsigned)((C + G::T - 1) / G::T)), dim3(NT), lds, s, in, n, C, aligned8(in), t,
                  spec, sstride);
     return hipGetLastError();
 }
@@ -1458,8 +1458,7 @@ hipError_t irfft_as(const float2* spec, uint32_t sstride, size_t n, size_t C, fl
     auto kern = k_chunk_irfft<LOGM, NT>;
     const hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
-    FFTSP_LAUNCH("irfft_chunk", kern, dim3((unsigned)((C + G::T - 1) / G::T)), dim3(NT), lds, s, spec, sstride, C, t, out, n,
-                 alignment(out));
+    FFTSP_LAUNCH("irfft_chunk", kern, dim3((unsigned)((C + G::T - 1) / G::T)), dim3(NT), lds, s, spec, sstride, C, t, out, n);
     return hipGetLastError();
 }
 

@@ -221,10 +221,10 @@ __device__ __forceinline__ void fwd_a_run(const float* __restrict__ in, size_t n
 }
 
 // The tiles of workgroup blk of a pass A over the chunks of in[0 .. n), in chunks of 2^(logM+1).
-// `aligned`: bit 0 = `in` is 8-byte aligned, bit 1 = 16-byte aligned.
+// `aligned`: `in` is 16-byte aligned.
 template <int LOGN1, bool HALF>
 __device__ __forceinline__ void fwd_a_workgroup(uint32_t blk, const float* __restrict__ in, size_t n, int logM,
-                                                typename Cx<HALF>::One* __restrict__ mid, const Tables& tb, int aligned,
+                                                typename Cx<HALF>::One* __restrict__ mid, const Tables& tb, bool aligned,
                                                 uint32_t total, uint32_t per_wg, int glog, float in_scale)
 {
     constexpr int LOGE = kTileFA, NT = tile_lanes(LOGE), ELEMS = 1 << LOGE;
@@ -237,7 +237,7 @@ __device__ __forceinline__ void fwd_a_workgroup(uint32_t blk, const float* __res
     load_stage_twiddles<LOGN1, NT>(tw, tb, tid0);
     const uint32_t tiles = (1u << logM) >> LOGE;  // tiles per chunk
     const size_t last_chunk_end = ((size_t)((tend - 1) / tiles) + 1) << (logM + 1);
-    if ((aligned & 2) && last_chunk_end <= n)
+    if (aligned && last_chunk_end <= n)
         fwd_a_run<LOGN1, kWhole, HALF>(in, n, logM, mid, tb, t, tend, 1u << glog, d, tw, tid0, in_scale);
     else
         fwd_a_run<LOGN1, kGuarded, HALF>(in, n, logM, mid, tb, t, tend, 1u << glog, d, tw, tid0, in_scale);
@@ -245,7 +245,7 @@ __device__ __forceinline__ void fwd_a_workgroup(uint32_t blk, const float* __res
 
 template <int LOGN1, bool HALF>
 __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __restrict__ in, size_t n, int logM,
-                                               typename Cx<HALF>::One* __restrict__ mid, Tables tb, int aligned,
+                                               typename Cx<HALF>::One* __restrict__ mid, Tables tb, bool aligned,
                                                uint32_t total, uint32_t per_wg, int glog, uint32_t* __restrict__ zero_ptr,
                                                uint32_t zero_words, float in_scale, const uint32_t* __restrict__ only_if)
 {
@@ -804,11 +804,11 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b(const typename Cx<HA
 }
 
 // Inverse pass A: inverse N1-point FFTs over k1 for a tile of columns n2; writes the real samples to out[first .. first + n),
-// chunk by chunk.  `aligned`: bit 0 = `out` is 8-byte aligned, bit 1 = 16-byte aligned.
+// chunk by chunk.  `aligned`: `out` is 16-byte aligned.
 // ONCE: what it reads and writes passes the caches by.
 template <int LOGN1, int LOGE, bool HALF, bool ONCE>
 __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<HALF>::One* __restrict__ mid, int logM,
-                                                float* __restrict__ out, size_t n, const Tables& tb, int aligned,
+                                                float* __restrict__ out, size_t n, const Tables& tb, bool aligned,
                                                 uint32_t total, uint32_t per_wg, int glog, float gain)
 {
     using Two = typename Cx<HALF>::Two;
@@ -862,7 +862,7 @@ __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<
         const Span sp = chunk_span(0, n, t / tiles, 2 * (size_t)M);
         const size_t cbase = sp.first;
         const uint32_t col0 = tile_in_chunk(t, tiles) << LOGT;
-        if ((aligned & 2) && (cbase & 3u) == 0 && (cbase + 2 * (size_t)M <= sp.limit || (sp.limit & 3u) == 0)) {
+        if (aligned && (cbase & 3u) == 0 && (cbase + 2 * (size_t)M <= sp.limit || (sp.limit & 3u) == 0)) {
             // 16-byte pieces, each inside the output or outside it
             float4* dst = reinterpret_cast<float4*>(out + cbase);
             const size_t left = sp.limit > cbase ? (sp.limit - cbase) >> 2 : 0;
@@ -894,7 +894,7 @@ __device__ __forceinline__ void inv_a_workgroup(uint32_t blk, const typename Cx<
 
 template <int LOGN1, int LOGE, bool HALF, bool ONCE>
 __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_a(const typename Cx<HALF>::One* __restrict__ mid, int logM,
-                                               float* __restrict__ out, size_t n, Tables tb, int aligned, uint32_t total,
+                                               float* __restrict__ out, size_t n, Tables tb, bool aligned, uint32_t total,
                                                uint32_t per_wg, int glog, float gain, const uint32_t* __restrict__ only_if)
 {
     if (only_if && *only_if == 0u) return;  // stand-by launch behind a fused kernel that did finish
@@ -1066,7 +1066,7 @@ __device__ __forceinline__ void inv_a_split(const typename Cx<HALF>::One* __rest
 }
 template <int LOGN1, int LOGE, bool HALF, bool ONCE>
 __global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_inv_a_split(
-    const typename Cx<HALF>::One* __restrict__ mid, int logM, float* __restrict__ out, size_t n, Tables tb, int aligned, uint32_t total, float gain,
+    const typename Cx<HALF>::One* __restrict__ mid, int logM, float* __restrict__ out, size_t n, Tables tb, bool aligned, uint32_t total, float gain,
     const uint32_t* __restrict__ only_if)
 {
     using G = SplitInverse<LOGN1, LOGE>;
@@ -1077,7 +1077,7 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) __attribute__((amdgpu_waves_per_e
     const int log_tiles = logM - LOGE;
     const uint32_t c = t >> log_tiles;
     const Span sp = chunk_span(0, n, c, (size_t)2 << logM);
-    const bool quads = (aligned & 2) && (sp.first + ((size_t)2 << logM) <= n || (n & 3u) == 0);
+    const bool quads = aligned && (sp.first + ((size_t)2 << logM) <= n || (n & 3u) == 0);
     inv_a_split<LOGN1, LOGE, HALF, ONCE>(mid + ((size_t)c << logM), logM, out, sp, quads, tb, (t & ((1u << log_tiles) - 1u)) << G::LOGT,
                                    reinterpret_cast<float*>(smem), smem + (1 << LOGE) / 2, threadIdx.x, gain);
 }
@@ -1159,7 +1159,7 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_inv_b_long(const float2* _
 // 3 M 84.8 / 96.2.
 template <int TOP>
 __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_inv_a_split_long(
-    const float2* __restrict__ mid, float* __restrict__ out, Tables tb, int aligned, uint32_t total, LongTable tab, LongStarts at)
+    const float2* __restrict__ mid, float* __restrict__ out, Tables tb, bool aligned, uint32_t total, LongTable tab, LongStarts at)
 {
     extern __shared__ float2 smem[];
     const uint32_t t = in_stretches(total);
@@ -1168,7 +1168,7 @@ __global__ __launch_bounds__(tile_lanes(TOP)) __attribute__((amdgpu_waves_per_eu
     const LongTensor& x = tab.t[share.tensor];
     const int logM = x.logM;
     const Span sp = chunk_span((size_t)x.goff, x.glen, 0, 0);
-    const bool quads = (aligned & 2) && (x.goff & 3u) == 0 && (x.glen & 3u) == 0;
+    const bool quads = aligned && (x.goff & 3u) == 0 && (x.glen & 3u) == 0;
     auto run = [&](auto n1) __attribute__((always_inline)) {
         constexpr int LOGN1 = decltype(n1)::value, LOGE = LOGN1 >= 10 ? TOP : 13;
         using G = SplitInverse<LOGN1, LOGE>;
@@ -1239,7 +1239,7 @@ hipError_t fwd_a_halved(const float* in, size_t n, int logM, size_t C, typename 
 }
 // HALF launchers take the same buffer pointers; the kernels read them as binary16 pairs
 template <int LOGN1, bool HALF>
-hipError_t fwd_a(const float* in, size_t n, int logM, size_t C, float2* mid_f32, Tables t, int aligned,
+hipError_t fwd_a(const float* in, size_t n, int logM, size_t C, float2* mid_f32, Tables t, bool aligned,
                  uint32_t* zero_ptr, uint32_t zero_words, float in_scale, hipStream_t s,
                  const uint32_t* only_if = nullptr)
 {
@@ -1311,7 +1311,7 @@ hipError_t inv_b_tiled(const float2* spec_f32, uint32_t sstride, int logM, size_
 // them longer in sum.
 constexpr size_t kOnceBytes = (size_t)1 << 27;
 template <int LOGN1, int LOGE, bool HALF, bool ONCE>
-hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
+hipError_t inv_a_tiled(const float2* mid_f32, int logM, size_t C, float* out, size_t n, Tables t, bool aligned, float gain,
                   hipStream_t s, const uint32_t* only_if)
 {
     const size_t lds = ((size_t)(1 << LOGE) + (1 << LOGN1)) * sizeof(float2);
@@ -1368,7 +1368,7 @@ hipError_t inv_b(const float2* spec, uint32_t sstride, int logM, size_t C, float
     return inv_b_tiled<LOGN2, 13, PAIR, HALF>(spec, sstride, logM, C, mid, t, mid_scale, s, only_if);
 }
 template <int LOGN1, int LOGE, bool HALF, bool ONCE>
-hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, hipStream_t s, const uint32_t* only_if)
+hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, bool aligned, float gain, hipStream_t s, const uint32_t* only_if)
 {
     using G = SplitInverse<LOGN1, LOGE>;
     const auto kern = k_inv_a_split<LOGN1, LOGE, HALF, ONCE>;
@@ -1380,7 +1380,7 @@ hipError_t inv_a_halved(const float2* mid, int logM, size_t C, float* out, size_
     return hipGetLastError();
 }
 template <int LOGN1, bool HALF>
-hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain,
+hipError_t inv_a(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, bool aligned, float gain,
                  hipStream_t s, const uint32_t* only_if = nullptr)
 {
     const size_t wide = wide_tiles(C, logM);
@@ -1490,8 +1490,7 @@ hipError_t launch_rfft(const float* in, size_t n, int logL, size_t C, float* spe
     if (zero_words > 0xffffffffu) return hipErrorInvalidValue;
     if (!hist) zero_words = 0;
     const int logM = logL - 1;
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(in);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    const bool aligned = aligned16(in);
     float2* sp = reinterpret_cast<float2*>(spec);
     if (logM < 15 || C * ((size_t)1 << (logM - 13)) > 0x7fffffffu) return hipErrorInvalidValue;
     // the codec stores its own spectrum in the paired order and wants the histogram; the stage-level entry point
@@ -1566,8 +1565,7 @@ hipError_t launch_inverse_a(const float2* mid, int logM, size_t C, float* out, s
 {
     if (half) gain *= half_lift(logM);
     if (!only_if && short_inverse(logM, C)) return launch_short_inverse_a(mid, logM, C, out, n, t, gain, half, s);
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    const bool aligned = aligned16(out);
     auto run = [&](auto columns) {
         constexpr int LOGN1 = decltype(columns)::value;
         return half ? inv_a<LOGN1, true>(mid, logM, C, out, n, t, aligned, gain, s, only_if)
@@ -1687,8 +1685,7 @@ hipError_t launch_inverse_a_long(const float2* mid, const LongBatch& b, float* o
 {
     if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors) return hipErrorInvalidValue;
     if (short_inverse(b)) return launch_short_inverse_a_long(b, out, mid, t, s);
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    const bool aligned = aligned16(out);
     LongStarts at;
     // Tiles of 2^13 as in uniform calls; launches with columns of 2^11 have them beside tiles of 2^14, two to a workgroup.  Receivers in us,
     // persistent (a launch for each tile size) / this: ResNet-50's 161 tensors 159 / 136, 150 of 10 to 2.4 M samples 224 / 161, 100 164 / 134, 60 82 / 79 and (longer)
@@ -1717,8 +1714,7 @@ hipError_t launch_rfft_half(const float* in, size_t n, int logL, size_t C, void*
     const int logM = logL - 1;
     if (logM < 14 || !hist || zero_words > 0xffffffffu) return hipErrorInvalidValue;
     if (C * ((size_t)1 << (logM - 13)) > 0x7fffffffu) return hipErrorInvalidValue;
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(in);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    const bool aligned = aligned16(in);
     float2* sp = static_cast<float2*>(spec);
     float2* md = static_cast<float2*>(mid);
     const int logN1 = (logM + 1) / 2, logN2 = logM / 2;

@@ -162,7 +162,7 @@ __device__ __forceinline__ void run_fft_1024(float2* d, const float2* tw, int ti
 // One member's walk over its team's turns.  FAST: every chunk this member reads lies wholly inside a 16-byte aligned
 // input (no guards on the loads).
 template <int LOGN1, int LOGN2, bool FAST>
-__device__ __forceinline__ void fused_fwd_run(const float* __restrict__ in, size_t n, uint32_t C, int aligned,
+__device__ __forceinline__ void fused_fwd_run(const float* __restrict__ in, size_t n, uint32_t C,
                                               float2* __restrict__ scratch, float2* __restrict__ spec, uint32_t sstride,
                                               const Tables& tb, uint32_t* __restrict__ hist, uint32_t x, uint32_t mi,
                                               uint32_t members, const TeamCtl& tc, float2* d,
@@ -403,7 +403,7 @@ constexpr int kCtlStored = 128;  // + 64 x
 constexpr int kCtlLoaded = 160;  // + 64 x
 
 template <int LOGN1, int LOGN2>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_fused_fwd(const float* __restrict__ in, size_t n, uint32_t C, int aligned,
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_fused_fwd(const float* __restrict__ in, size_t n, uint32_t C, bool aligned,
                                                    float2* __restrict__ scratch_all, float2* __restrict__ spec,
                                                    uint32_t sstride, Tables tb, uint32_t* __restrict__ hist,
                                                    uint32_t* __restrict__ ctl, uint32_t spin_limit)
@@ -439,13 +439,13 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     const uint32_t last_group = (C - 1u) / CPR;
     const bool ragged = ((size_t)C << (LOGN1 + LOGN2 + 1)) != n;
     const bool mine = (last_group % (uint32_t)kXcds) == x;
-    const bool fast = (aligned & 2) != 0 && !(ragged && mine);
+    const bool fast = aligned && !(ragged && mine);
     __syncthreads();
     if (fast)
-        fused_fwd_run<LOGN1, LOGN2, true>(in, n, C, aligned, scratch, spec, sstride, tb, hist, x, mi,
+        fused_fwd_run<LOGN1, LOGN2, true>(in, n, C, scratch, spec, sstride, tb, hist, x, mi,
                                           members, tc, d, tw, h16, s_ok, tid0);
     else
-        fused_fwd_run<LOGN1, LOGN2, false>(in, n, C, aligned, scratch, spec, sstride, tb, hist, x, mi,
+        fused_fwd_run<LOGN1, LOGN2, false>(in, n, C, scratch, spec, sstride, tb, hist, x, mi,
                                            members, tc, d, tw, h16, s_ok, tid0);
 }
 
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // N1-point transforms of a tile of columns (loaded from the region past the L1, stored as real samples).
 template <int LOGN1, int LOGN2>
 __device__ __forceinline__ void fused_inv_run(const float2* __restrict__ spec, uint32_t sstride, size_t n, uint32_t C,
-                                              int aligned, float gain, float2* __restrict__ scratch,
+                                              bool aligned, float gain, float2* __restrict__ scratch,
                                               float* __restrict__ out, const Tables& tb, uint32_t x, uint32_t mi,
                                               uint32_t members, const TeamCtl& tc, float2* d,
                                               const float2* tw, uint32_t* s_ok, int tid0)
@@ -621,7 +621,7 @@ __device__ __forceinline__ void fused_inv_run(const float2* __restrict__ spec, u
             // a chunk past the end starts beyond n: the guarded branch below then stores nothing
             const size_t cbase = (size_t)c * (2 * (size_t)M);
             const uint32_t col0 = tl << LOGTA;
-            if ((aligned & 2) && cbase + 2 * (size_t)M <= n) {  // whole chunk inside the output: no guards
+            if (aligned && cbase + 2 * (size_t)M <= n) {  // whole chunk inside the output: no guards
                 float4* dst = reinterpret_cast<float4*>(out + cbase) + (col0 >> 1);
 #pragma unroll
                 for (int q = 0; q < PER2; ++q) {
@@ -646,7 +646,7 @@ __device__ __forceinline__ void fused_inv_run(const float2* __restrict__ spec, u
 
 template <int LOGN1, int LOGN2>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_fused_inv(
-    const float2* __restrict__ spec, uint32_t sstride, size_t n, uint32_t C, int aligned, float gain,
+    const float2* __restrict__ spec, uint32_t sstride, size_t n, uint32_t C, bool aligned, float gain,
     float2* __restrict__ scratch_all, float* __restrict__ out, Tables tb, uint32_t* __restrict__ ctl,
     uint32_t spin_limit)
 {
@@ -700,8 +700,7 @@ hipError_t launch_fused_rfft(const float* in, size_t n, int logL, size_t C, floa
 {
     const int logM = logL - 1;
     if (!fused_applies(logL, C) || C > 0x7fffffu) return hipErrorInvalidValue;
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(in);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    const bool aligned = aligned16(in);
 #define FFTSP_FUSED_FWD(a, b)                                                                                         \
     do {                                                                                                              \
         auto kern = k_fused_fwd<a, b>;                                                                                \
@@ -729,8 +728,7 @@ hipError_t launch_fused_irfft(const float2* spec, uint32_t sstride, size_t n, in
 {
     const int logM = logL - 1;
     if (!fused_applies(logL, C) || C > 0x7fffffu) return hipErrorInvalidValue;
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(out);
-    const int aligned = ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
+    const bool aligned = aligned16(out);
 #define FFTSP_FUSED_INV(a, b)                                                                                            \
     do {                                                                                                                 \
         auto kern = k_fused_inv<a, b>;                                                                                   \

@@ -143,6 +143,7 @@ struct Workspace {
 };
 
 static inline size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
+static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Per-tensor mode, tensors longer than one workgroup takes: every launch covers up to kMaxLongTensors of them, each a
 // single chunk of its own length 2^(logM+1).  What the kernels need to know about them travels by value as a kernel

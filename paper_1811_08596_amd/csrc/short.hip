@@ -51,12 +51,12 @@ __global__ __launch_bounds__(short_lanes_a(LOGN1)) void k_fwd_a_short(const floa
 }
 template <int LOGN1, bool HALF>
 __global__ __launch_bounds__(short_lanes_a(LOGN1)) void k_inv_a_short(const typename Cx<HALF>::One* __restrict__ mid, int logM,
-                                                          float* __restrict__ out, size_t n, Tables tb, int aligned, float gain)
+                                                          float* __restrict__ out, size_t n, Tables tb, bool aligned, float gain)
 {
     const int log_tiles = logM - short_log_a(LOGN1);
     const uint32_t place = beside<2>(), c = place >> log_tiles;
     inv_a_short<LOGN1, HALF>(place & ((1u << log_tiles) - 1u), mid + ((size_t)c << logM), logM, out,
-                             chunk_span(0, n, c, (size_t)2 << logM), tb, (aligned & 2) != 0, gain);
+                             chunk_span(0, n, c, (size_t)2 << logM), tb, aligned, gain);
 }
 template <int LOGN2, bool CODEC, bool HALF>
 __global__ __launch_bounds__(1 << LOGN2) void k_fwd_b_short(const typename Cx<HALF>::One* __restrict__ mid, int logM,
@@ -101,13 +101,13 @@ __global__ __launch_bounds__(kShortMostA) void k_fwd_a_long_short(const float* _
     const LongTensor& x = tab.t[share.tensor];
     fwd_a_tensor(x, share.blk, in, mid, tb);
 }
-__global__ __launch_bounds__(kShortMostA) void k_inv_a_long_short(const float2* __restrict__ mid, float* __restrict__ out, Tables tb, int aligned,
+__global__ __launch_bounds__(kShortMostA) void k_inv_a_long_short(const float2* __restrict__ mid, float* __restrict__ out, Tables tb, bool aligned,
                                                                LongTable tab, LongStarts at)
 {
     const LongShare share = long_share(at);
     const LongTensor& x = tab.t[share.tensor];
     const Span sp = chunk_span((size_t)x.goff, x.glen, 0, 0);
-    const bool quads = (aligned & 2) && (sp.first & 3u) == 0;
+    const bool quads = aligned && (sp.first & 3u) == 0;
     const float2* from = mid + long_mid(x);
     if (threadIdx.x >= (uint32_t)short_lanes_a(short_columns(x.logM))) return;
     switch (short_columns(x.logM)) {
@@ -187,7 +187,7 @@ hipError_t launch_a_fwd(const float* in, size_t n, int logM, size_t C, float2* m
     return hipGetLastError();
 }
 template <int LOGN1, bool HALF>
-hipError_t launch_a_inv(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, int aligned, float gain, hipStream_t s)
+hipError_t launch_a_inv(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, bool aligned, float gain, hipStream_t s)
 {
     FFTSP_LAUNCH("irfft_pass_a", (k_inv_a_short<LOGN1, HALF>), dim3((unsigned)(C << (logM - short_log_a(LOGN1)))), dim3(short_lanes_a(LOGN1)), lds_a(LOGN1), s,
                  reinterpret_cast<const typename Cx<HALF>::One*>(mid), logM, out, n, t, aligned, gain);
@@ -254,15 +254,10 @@ hipError_t rfft_short(const float* in, size_t n, int logM, size_t C, float2* spe
     }
 #undef FWD_B
 }
-int alignment(const void* p)
-{
-    const uintptr_t addr = reinterpret_cast<uintptr_t>(p);
-    return ((addr & 7u) == 0 ? 1 : 0) | ((addr & 15u) == 0 ? 2 : 0);
-}
 template <bool HALF>
 hipError_t inv_a_any(const float2* mid, int logM, size_t C, float* out, size_t n, Tables t, float gain, hipStream_t s)
 {
-    const int aligned = alignment(out);
+    const bool aligned = aligned16(out);
 #define INV_A(p) launch_a_inv<p, HALF>(mid, logM, C, out, n, t, aligned, gain, s)
     switch (short_columns(logM)) {
         case 8: return INV_A(8);
@@ -459,7 +454,7 @@ hipError_t launch_short_inverse_a_long(const LongBatch& b, float* out, const flo
     LongStarts at;
     const int top = short_columns(longest(b));
     const uint32_t wgs = starts_of(b, &at, [](int logM) { return logM - short_log_a(short_columns(logM)); });
-    FFTSP_LAUNCH("irfft_pass_a", k_inv_a_long_short, dim3(wgs), dim3(short_lanes_a(top)), lds_a(top), s, mid, out, t, alignment(out), b.tab, at);
+    FFTSP_LAUNCH("irfft_pass_a", k_inv_a_long_short, dim3(wgs), dim3(short_lanes_a(top)), lds_a(top), s, mid, out, t, aligned16(out), b.tab, at);
     return hipGetLastError();
 }
 
