@@ -1578,14 +1578,9 @@ hipError_t launch_tensors_decompress(const uint8_t* stream, const TensorTable& t
 template <typename Tiles>
 static uint32_t few_of(const LongBatch& b, FewLong* few, Tiles&& tiles)
 {
-    uint32_t sum = 0;
     few->count = b.count;
-    for (uint32_t i = 0; i < b.count; ++i) {
-        few->t[i] = b.tab.t[i];
-        few->at[i] = (uint16_t)sum;
-        sum += tiles((int)b.tab.t[i].logM);
-    }
-    return sum;
+    for (uint32_t i = 0; i < b.count; ++i) few->t[i] = b.tab.t[i];
+    return first_workgroups(b, 0, b.count, few->at, tiles);
 }
 static uint32_t few_forward(const LongBatch& b, FewLong* few)
 {

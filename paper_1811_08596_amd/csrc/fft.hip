@@ -1428,19 +1428,6 @@ uint32_t first_wide(const LongBatch& b, Logs&& logs, size_t alone, size_t beside
     for (; i > 0 && logs(b.tab.t[i - 1].logM) >= kWideMin; --i) tiles += (size_t)1 << (b.tab.t[i - 1].logM - 14);
     return tiles >= (i == 0 ? alone : beside) ? i : b.count;
 }
-// starts of the workgroups' shares; wgs(tensor) workgroups each.  Returns the total.
-template <typename Wgs>
-uint32_t long_starts(const LongBatch& b, uint32_t first, uint32_t end, LongStarts* at, Wgs&& wgs)
-{
-    at->first = first;
-    at->count = end - first;
-    uint32_t sum = 0;
-    for (uint32_t i = first; i < end; ++i) {
-        at->at[i - first] = (uint16_t)sum;
-        sum += wgs(b.tab.t[i]);
-    }
-    return sum;
-}
 // tiles per workgroup (a power of two) that keep a launch over tensors [first, end) to about `most` workgroups
 uint32_t long_run(const LongBatch& b, uint32_t first, uint32_t end, int loge, uint32_t most)
 {
@@ -1595,7 +1582,7 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     auto whole = [&]() {
         const hipError_t err = set_lds(k_fwd_a_long, long_lds(kTileFA));
         if (err != hipSuccess) return err;
-        const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, kTileFA); });
+        const uint32_t total = long_starts(b, 0, b.count, &at, [](int logM) { return power_tiles(logM, kTileFA); });
         FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long, dim3(stretch_places(total)), dim3(tile_lanes(kTileFA)), long_lds(kTileFA), s, in, mid, t, total, step_of(total, kTileFA),
                      zero_ptr, (uint32_t)zero_words, b.tab, at);
         return hipGetLastError();
@@ -1605,7 +1592,7 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
         constexpr size_t lds = SplitTile<TOP == 14 ? 11 : 10, TOP>::kLds;
         const hipError_t err = set_lds(k_fwd_a_split_long<TOP>, lds);
         if (err != hipSuccess) return err;
-        const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, TOP); });
+        const uint32_t total = long_starts(b, 0, b.count, &at, [](int logM) { return power_tiles(logM, TOP); });
         FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_split_long<TOP>, dim3((total + 7) / 8 * 8), dim3(tile_lanes(TOP)), lds, s, in, mid, t, total, step_of(total, TOP), zero_ptr,
                      (uint32_t)zero_words, b.tab, at);
         return hipGetLastError();
@@ -1632,7 +1619,7 @@ hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mi
         constexpr int TOP = decltype(size)::value;
         const hipError_t err = set_lds(k_fwd_b_pairs_long<TOP>, kPairsLds<TOP>);
         if (err != hipSuccess) return err;
-        const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, TOP + 4); });
+        const uint32_t total = long_starts(b, 0, b.count, &at, [](int logM) { return power_tiles(logM, TOP + 4); });
         const uint32_t few = TOP == 10 ? at.at[tall] : 0u;
         FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_pairs_long<TOP>, dim3(stretch_places(total, few)), dim3(HalfTile<TOP>::NT), kPairsLds<TOP>, s, mid, spec, t, hist,
                      total, few, b.tab, at);
@@ -1646,8 +1633,8 @@ hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mi
         const hipError_t err = set_lds(k_fwd_b_long<LOGE>, lds);
         if (err != hipSuccess) return err;
         const uint32_t per = long_run(b, 0, b.count, LOGE, most_wgs(LOGE, 512));
-        const uint32_t g = long_starts(b, 0, b.count, &at, [&](const LongTensor& x) {
-            const uint32_t tiles = power_tiles(x.logM, LOGE);
+        const uint32_t g = long_starts(b, 0, b.count, &at, [&](int logM) {
+            const uint32_t tiles = power_tiles(logM, LOGE);
             return tiles > per ? tiles / per : 1u;
         });
         FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), lds, s, mid, spec, t, hist, per, b.tab, at);
@@ -1670,8 +1657,8 @@ hipError_t launch_irfft_long(const float2* spec, const LongBatch& b, float* out,
             const hipError_t err = set_lds(k_inv_b_long<LOGE>, long_lds(LOGE));
             if (err != hipSuccess) return err;
             const uint32_t per = long_run(b, first, end, LOGE, most_wgs(LOGE, 1536));
-            const uint32_t g = long_starts(b, first, end, &at, [&](const LongTensor& x) {
-                const uint32_t tiles = 1u << (x.logM - LOGE);
+            const uint32_t g = long_starts(b, first, end, &at, [&](int logM) {
+                const uint32_t tiles = power_tiles(logM, LOGE);
                 return tiles > per ? tiles / per : 1u;
             });
             FFTSP_LAUNCH("irfft_pass_b", k_inv_b_long<LOGE>, dim3(g), dim3(tile_lanes(LOGE)), long_lds(LOGE), s, spec, mid, t, per, b.tab, at);
@@ -1697,7 +1684,7 @@ hipError_t launch_inverse_a_long(const float2* mid, const LongBatch& b, float* o
         constexpr size_t lds = SplitInverse<TOP == 14 ? 11 : 10, TOP>::kLds;
         const hipError_t err = set_lds(k_inv_a_split_long<TOP>, lds);
         if (err != hipSuccess) return err;
-        const uint32_t total = long_starts(b, 0, b.count, &at, [](const LongTensor& x) { return power_tiles(x.logM, TOP); });
+        const uint32_t total = long_starts(b, 0, b.count, &at, [](int logM) { return power_tiles(logM, TOP); });
         FFTSP_LAUNCH("irfft_pass_a", k_inv_a_split_long<TOP>, dim3((total + 7) / 8 * 8), dim3(tile_lanes(TOP)), lds, s, mid, out, t, aligned, total, b.tab, at);
         return hipGetLastError();
     };

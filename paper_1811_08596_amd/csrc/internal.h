@@ -182,6 +182,24 @@ struct FewLong {
     uint16_t at[kFewLong];
     uint32_t count;
 };
+// The first workgroups of tensors from .. end - 1 of a launch, wgs(logM) workgroups to each; returns how many in all.
+template <typename Wgs>
+uint32_t first_workgroups(const LongBatch& b, uint32_t from, uint32_t end, uint16_t* at, Wgs&& wgs)
+{
+    uint32_t sum = 0;
+    for (uint32_t i = from; i < end; ++i) {
+        at[i - from] = (uint16_t)sum;
+        sum += wgs((int)b.tab.t[i].logM);
+    }
+    return sum;
+}
+template <typename Wgs>
+uint32_t long_starts(const LongBatch& b, uint32_t from, uint32_t end, LongStarts* at, Wgs&& wgs)
+{
+    at->first = from;
+    at->count = end - from;
+    return first_workgroups(b, from, end, at->at, wgs);
+}
 // where tensor i of a launch finds its part of the work areas
 __host__ __device__ inline size_t long_mid(const LongTensor& t) { return (size_t)t.base << kLongUnitLog; }
 __host__ __device__ inline size_t long_spec(const LongTensor& t, uint32_t i) { return long_mid(t) + 16u * i; }

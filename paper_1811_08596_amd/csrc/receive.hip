@@ -515,19 +515,6 @@ bool receive_applies(const LongBatch& b, int bits)
     return bits <= 15 && tiles >= (tall(0) ? kReceiveTallFrom : (tall(b.count - 1) ? kReceiveBothFrom : kReceiveFrom));
 }
 
-// starts of tensors from .. end - 1, wgs(logM) workgroups each; returns how many in all
-template <typename Wgs>
-static uint32_t share_out(const LongBatch& b, uint32_t from, uint32_t end, LongStarts* at, Wgs&& wgs)
-{
-    uint32_t sum = 0;
-    at->first = from;
-    at->count = end - from;
-    for (uint32_t i = from; i < end; ++i) {
-        at->at[i - from] = (uint16_t)sum;
-        sum += wgs((int)b.tab.t[i].logM);
-    }
-    return sum;
-}
 hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* table, float2* mid, Tables t, int check_header, uint32_t* verdicts,
                                uint32_t* ctl, const StatusNote* first, hipStream_t s)
 {
@@ -536,7 +523,7 @@ hipError_t launch_receive_long(const uint8_t* stream, const CodecArgs& a, void* 
     const HeaderInfo h{check_header, a.hdr_n, a.hdr_L, a.hdr_C, (uint32_t)a.bits, (uint32_t)a.m, a.hdr_k, a.hdr_S, a.hdr_theta, 0u, 0u};
     uint2* entries = static_cast<uint2*>(table);
     LongStarts at;
-    const uint32_t parts = share_out(b, 0, b.count, &at, [](int logM) { return table_parts(logM); });
+    const uint32_t parts = long_starts(b, 0, b.count, &at, [](int logM) { return table_parts(logM); });
     FFTSP_LAUNCH("bitmap_table", k_bitmap_table_long, dim3(parts), dim3(kTableLanes), 0, s, stream, h, entries, verdicts, first ? ctl : nullptr,
                  first ? *first : StatusNote{}, b.tab, at);
     const hipError_t e = hipGetLastError();
@@ -559,7 +546,7 @@ hipError_t launch_receive_b_long(const uint8_t* stream, const CodecArgs& a, cons
     // random sets of 60 262 / 257, 100 451 / 438, 150 431 / 422 and 394 / 383, 200 741 / 732, 50 of 200 k and six of 2^21 266 / 255, 30 of 1 M and ten 471 / 462;
     // every XCD with its share of either kind (stretches.h), 30 of 70 k and 16 of 2^21 364 / 356, 24 513 / 483, 32 750 / 734, one of 2^16 and 24 485 / 457.
     auto pass = [&](auto kern, auto pairs, uint32_t pairs_from, unsigned lanes, size_t lds, size_t pairs_lds, uint32_t from, uint32_t end, int log_points) {
-        const uint32_t total = share_out(b, from, end, &at, [&](int logM) { return 1u << (logM - log_points); });
+        const uint32_t total = long_starts(b, from, end, &at, [&](int logM) { return 1u << (logM - log_points); });
         const bool long_one = total >= pairs_from;
         if (long_one) {
             kern = pairs;

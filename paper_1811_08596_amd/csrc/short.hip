@@ -294,19 +294,6 @@ hipError_t decode_b_any(const uint8_t* stream, const CodecArgs& a, int logM, flo
     }
 #undef DECODE_B
 }
-// workgroups of every tensor's share: 2^log(logM) each
-template <typename Log>
-uint32_t starts_of(const LongBatch& b, LongStarts* at, Log&& log)
-{
-    uint32_t sum = 0;
-    at->first = 0;
-    at->count = b.count;
-    for (uint32_t i = 0; i < b.count; ++i) {
-        at->at[i] = (uint16_t)sum;
-        sum += 1u << log((int)b.tab.t[i].logM);
-    }
-    return sum;
-}
 
 }  // namespace
 
@@ -385,7 +372,7 @@ hipError_t launch_short_decode_long(const uint8_t* stream, const CodecArgs& a, f
     const StatusNote note = first ? *first : StatusNote{};
     const int logM = longest(b);
     LongStarts at;
-    const uint32_t wgs = starts_of(b, &at, [](int log) { return log - short_rows(log) - kShortLogSlots; });
+    const uint32_t wgs = long_starts(b, 0, b.count, &at, [](int logM) { return 1u << (logM - short_rows(logM) - kShortLogSlots); });
     auto pass_b = [&](auto top) {
         constexpr int TOP = decltype(top)::value;
         auto kern = k_decode_inv_b_long<TOP>;
@@ -407,7 +394,7 @@ hipError_t launch_short_rfft_long(const float* in, const LongBatch& b, float2* s
 {
     LongStarts at;
     const int top = short_columns(longest(b));
-    const uint32_t wgs = starts_of(b, &at, [](int logM) { return logM - short_log_a(short_columns(logM)); });
+    const uint32_t wgs = long_starts(b, 0, b.count, &at, [](int logM) { return 1u << (logM - short_log_a(short_columns(logM))); });
     FFTSP_LAUNCH("rfft_pass_a", k_fwd_a_long_short, dim3(wgs), dim3(short_lanes_a(top)), lds_a(top), s, in, mid, t, zero_ptr, zero_words,
                  b.tab, at);
     const hipError_t e = hipGetLastError();
@@ -416,7 +403,7 @@ hipError_t launch_short_rfft_long(const float* in, const LongBatch& b, float2* s
 hipError_t launch_short_rfft_b_long(const LongBatch& b, float2* spec, const float2* mid, Tables t, uint32_t* hist, hipStream_t s)
 {
     LongStarts at;
-    const uint32_t wgs = starts_of(b, &at, [](int logM) { return logM - short_rows(logM) - kShortLogSlots; });
+    const uint32_t wgs = long_starts(b, 0, b.count, &at, [](int logM) { return 1u << (logM - short_rows(logM) - kShortLogSlots); });
     auto pass_b = [&](auto top) {
         constexpr int TOP = decltype(top)::value;
         auto kern = k_fwd_b_long_short<TOP>;
@@ -435,7 +422,7 @@ hipError_t launch_short_rfft_b_long(const LongBatch& b, float2* spec, const floa
 hipError_t launch_short_inverse_b_long(const float2* spec, const LongBatch& b, float2* mid, Tables t, hipStream_t s)
 {
     LongStarts at;
-    const uint32_t wgs = starts_of(b, &at, [](int logM) { return logM - short_rows(logM) - kShortLogSlots; });
+    const uint32_t wgs = long_starts(b, 0, b.count, &at, [](int logM) { return 1u << (logM - short_rows(logM) - kShortLogSlots); });
     auto pass_b = [&](auto top) {
         constexpr int TOP = decltype(top)::value;
         auto kern = k_inv_b_long_short<TOP>;
@@ -453,7 +440,7 @@ hipError_t launch_short_inverse_a_long(const LongBatch& b, float* out, const flo
 {
     LongStarts at;
     const int top = short_columns(longest(b));
-    const uint32_t wgs = starts_of(b, &at, [](int logM) { return logM - short_log_a(short_columns(logM)); });
+    const uint32_t wgs = long_starts(b, 0, b.count, &at, [](int logM) { return 1u << (logM - short_log_a(short_columns(logM))); });
     FFTSP_LAUNCH("irfft_pass_a", k_inv_a_long_short, dim3(wgs), dim3(short_lanes_a(top)), lds_a(top), s, mid, out, t, aligned16(out), b.tab, at);
     return hipGetLastError();
 }
