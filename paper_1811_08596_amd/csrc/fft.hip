@@ -1620,7 +1620,7 @@ hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mi
         const hipError_t err = set_lds(k_fwd_b_pairs_long<TOP>, kPairsLds<TOP>);
         if (err != hipSuccess) return err;
         const uint32_t total = long_starts(b, 0, b.count, &at, [](int logM) { return power_tiles(logM, TOP + 4); });
-        const uint32_t few = TOP == 10 ? at.at[tall] : 0u;
+        const uint32_t few = TOP == 10 ? few_apart(total, at.at[tall]) : 0u;
         FFTSP_LAUNCH("rfft_pass_b", k_fwd_b_pairs_long<TOP>, dim3(stretch_places(total, few)), dim3(HalfTile<TOP>::NT), kPairsLds<TOP>, s, mid, spec, t, hist,
                      total, few, b.tab, at);
         return hipGetLastError();

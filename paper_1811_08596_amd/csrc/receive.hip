@@ -554,7 +554,7 @@ hipError_t launch_receive_b_long(const uint8_t* stream, const CodecArgs& a, cons
         }
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err != hipSuccess) return err;
-        const uint32_t few = from < split && split < end ? at.at[split - from] : 0u;
+        const uint32_t few = from < split && split < end ? few_apart(total, at.at[split - from]) : 0u;
         FFTSP_LAUNCH("irfft_pass_b", kern, dim3(stretch_places(total, few)), dim3(long_one ? lanes : 1024u), lds, s, stream + 64, a.bits, a.m, entries, mid, t,
                      total, few, b.tab, at);
         return hipGetLastError();

@@ -15,7 +15,7 @@ constexpr uint32_t stretch_tile(uint32_t place, uint32_t total)
 // The same where the first `few` tiles are of another kind, which take longer or less long: an XCD has its stretch of either.  With one stretch over both,
 // one XCD has all of those few.  Sender and receiver in us of tensors whose rows are of 2^10 and shorter, the shorter ones first, one stretch / one of
 // either: 30 of 70 k and 16 of 2^21 376 / 356, 24 511 / 483, 32 772 / 734 (a launch for either kind 751);  30 of 150 k and 24 541 / 513;  24 of 300 k and 24 566 / 552, 16 416 / 416.
-// Receivers of ResNet-50's 161 tensors 140.5 / 134.4.  The shorter ones last: 488 and 734 where these take 483 and 734, random sets of 60 299 / 295.
+// The shorter ones last: 24 and 32 488 and 734.
 constexpr uint32_t stretch_tile(uint32_t place, uint32_t total, uint32_t few)
 {
     const uint32_t xcd = place & 7u, i = place >> 3, mine = stretch_start(xcd + 1u, few) - stretch_start(xcd, few);
@@ -36,6 +36,10 @@ constexpr uint32_t turned_tile(uint32_t place, uint32_t total, uint32_t step)
     const uint32_t to = t + (step ? ((step * xcd - lo) & (8u * step - 1u)) % (hi - lo) : 0u);
     return to < hi ? to : to - (hi - lo);
 }
+// How many of a launch's first `few` tiles have stretches of their own: up to three tenths of the launch.  More lie on several XCDs anyhow, and the order of the passes before and
+// after is worth more.  Sender and receiver in us of random sets of tensors, one stretch / one of either, by share: 23 % 692 / 684, 24 % 376 / 366, 27 % 269 / 266, 29 % 336 / 334;
+// 31 % 468 / 476, 35 % 389 / 395, 36 % 445 / 463, 45 % 451 / 459 and 432 / 440.
+constexpr uint32_t few_apart(uint32_t total, uint32_t few) { return 10u * few < 3u * total ? few : 0u; }
 // workgroups that have a tile for everyone
 constexpr uint32_t stretch_places(uint32_t total, uint32_t few = 0) { return 8u * ((few + 7u) / 8u + (total - few + 7u) / 8u); }
 

@@ -11,6 +11,7 @@ SOURCE = r"""
 #include "%s/paper_1811_08596_amd/csrc/stretches.h"
 extern "C" uint32_t tile(uint32_t place, uint32_t total) { return fftsp::stretch_tile(place, total); }
 extern "C" uint32_t tile_of_two(uint32_t place, uint32_t total, uint32_t few) { return fftsp::stretch_tile(place, total, few); }
+extern "C" uint32_t apart(uint32_t total, uint32_t few) { return fftsp::few_apart(total, few); }
 extern "C" uint32_t turned(uint32_t place, uint32_t total, uint32_t step) { return fftsp::turned_tile(place, total, step); }
 extern "C" uint32_t places(uint32_t total, uint32_t few) { return fftsp::stretch_places(total, few); }
 """
@@ -60,3 +61,8 @@ def test_stretches_that_begin_at_different_columns(lib, total):
         assert sorted(b) == a and (not b or b == a[a.index(b[0]):] + a[:a.index(b[0])])
     if total >= 1024:
         assert len({ts[0] % 128 // 16 for ts in turned}) == 8
+
+
+@pytest.mark.parametrize("total, few, apart", [(2168, 120, 120), (1656, 120, 120), (1288, 584, 0), (1304, 472, 0), (1000, 299, 299), (1000, 300, 0), (64, 0, 0)])
+def test_stretches_of_their_own_are_for_few_tiles(lib, total, few, apart):
+    assert lib.apart(total, few) == apart
