@@ -1574,10 +1574,14 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
     if (b.count < 1 || b.count > (uint32_t)kMaxLongTensors || zero_words > 0xffffffffu) return hipErrorInvalidValue;
     if (short_forward(b)) return launch_short_rfft_long(in, b, spec, mid, t, hist, zero_ptr, (uint32_t)zero_words, s);
     LongStarts at;
-    // What the XCDs begin further into a tensor each (stretches.h): tensors of 128 tiles, or of 64 where all of the launch is on the chip at once.  Sender in us, from the
-    // stretch's start / further: 20 of 2^20 131.1 / 133.4, 32 184.8 / 189.5, 48 of 2^19 148.9 / 150.1, 30 of 600 k 166.4 / 170.5;  eight of 2^20 (512 tiles) 74.6 / 72.1, twelve 91.1 / 92.4.
+    // What the XCDs begin further into a tensor each (stretches.h): three quarters of the launch are tensors of 128 tiles, or of 64 where all of it is on the chip at once.  Sender in us,
+    // from the stretch's start / further: 20 of 2^20 131.1 / 133.4, 32 184.8 / 189.5, 48 of 2^19 148.9 / 150.1, 30 of 600 k 166.4 / 170.5;  eight of 2^20 (512 tiles) 74.6 / 72.1, twelve
+    // 91.1 / 92.4;  beside shorter ones, of 2^21 32 and eight of 1 M 446 / 437, and 24 of 300 k 467 / 462, 16 and 24 254.2 / 254.9, random sets 292.7 / 297.1 and 265.3 / 267.7.
     auto step_of = [&](uint32_t total, int loge) {
-        return power_tiles(b.tab.t[b.count - 1].logM, loge) >= (loge == kTileFA && total <= 512u ? 64u : 128u) ? kTurnStep : 0u;
+        const uint32_t least = loge == kTileFA && total <= 512u ? 64u : 128u;
+        uint32_t tiles = 0;  // of those
+        for (uint32_t i = b.count; i > 0 && power_tiles(b.tab.t[i - 1].logM, loge) >= least; --i) tiles += power_tiles(b.tab.t[i - 1].logM, loge);
+        return 4u * tiles >= 3u * total ? kTurnStep : 0u;
     };
     auto whole = [&]() {
         const hipError_t err = set_lds(k_fwd_a_long, long_lds(kTileFA));
