@@ -220,10 +220,12 @@ int fftsp_topk_decompress(const void* d_packed, size_t packed_bytes, float* d_gr
  *      and is consumed before the call returns.  Sizes above 2^22 are FFTSP_EUNSUPPORTED.
  *      Records follow tensor order in the stream.  Tensors of up to 2^15 samples, whatever their lengths, run as one
  *      launch per direction (up to 128 at a time).  All longer ones share one launch per kernel, whatever their lengths (up
- *      to 64 of them and 2^26 padded samples at a time).  Where the longer ones take a while, the others run beside
- *      them on a stream of the library's own that forks from and joins back into the caller's, so the call is still
- *      one unit of work on the caller's stream and can be captured into a graph.  That stream belongs to the device
- *      and is shared by all callers: calls from several host threads enqueue one after the other.  A captured call
+ *      to 64 of them and 2^26 padded samples at a time).  Where up to 22 longer ones are done soon, their first kernel is
+ *      part of the others' launch (and of what fftsp_profile_report calls tensors_compress and tensors_decompress).
+ *      Where they take a while, the others run beside them on a stream of the library's own that forks from and
+ *      joins back into the caller's, so the call is still one unit of work on the caller's stream and can be
+ *      captured into a graph.  That stream belongs to the device and is shared by all callers: calls from several
+ *      host threads enqueue one after the other.  A captured call
  *      keeps it inside its capture until that capture ends; a call made meanwhile on another stream, and a captured
  *      call made before it exists, runs everything on the caller's stream alone (same bytes, less overlap). ---- */
 size_t fftsp_packed_bytes_segments(const size_t* seg_offsets, int nseg, float theta, int bits);

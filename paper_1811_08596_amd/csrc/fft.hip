@@ -490,8 +490,9 @@ __global__ __launch_bounds__(tile_lanes(LOGE)) void k_fwd_b(const typename Cx<HA
 // Bound by the two trips to memory that nothing hides but the other workgroups of the compute unit, and by the stages.  Binary16, 62 M samples in
 // chunks of 2^20: 80 us for 50 of traffic (99 as fwd_b_workgroup).  Six waves a SIMD, two registers spilled: eight spill twenty (125 us), and the
 // histogram in the tile's place, which they would need, costs two barriers and 11 us with six.  Runs of tiles that share a
-// histogram spill, too (115).  Rows of 2^10 are workgroups of sixteen waves, so it is four waves a SIMD or eight; eight spill twenty-three registers, and two
+// histogram spill, too (115).  Rows of 2^10 are workgroups of sixteen waves, so it is four waves a SIMD or eight; eight spill twenty registers, and two
 // workgroups beside each other are worth it: senders, four / eight, 2^21 17 M 120.2 / 113.1, 62 M 294.5 / 270.1; 2^22 62 M 323.0 / 292.4 (fwd_b_workgroup 116.8, 287.3, 324.7).
+// With eight, the split's twiddles looked up before the stages / behind them, when registers are free again: 2^21 40 M 192.1 / 186.9, 62 M 267.7 / 259.7; 2^22 62 M 293.7 / 284.6.
 __device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b)  // lanes 32 .. 63 of a with lanes 0 .. 31 of b
 {
     const auto v = __builtin_amdgcn_permlane32_swap(a, b, false, false);
@@ -1094,7 +1095,7 @@ constexpr int kLongMax = kMaxLogL - 1;                            // log2 M
 
 constexpr int kTallTile = 14;  // of rows of 2^10, where a launch has no others
 
-// A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of up to 2^10.  Bound by memory, and by what few tiles to a
+// A workgroup has 2^TOP points of a tensor: one tile, or with TOP = 14 two of columns of up to 2^10 (fewer tensors: k_fwd_a_long).  Bound by memory, and by what few tiles to a
 // compute unit leave idle: a tile in half of the LDS has twice as many in flight as a persistent workgroup with one in all of it, which most launch
 // sets of tensors, with one or two tiles to a workgroup, paid for without having a next tile to load ahead; and tensors that start anywhere
 // are read 16 bytes at a time.  Pass in us, the persistent kernel / this: ResNet-50's 161 tensors 77 / 74, 100 of 10 to 2.4 M samples 58.6 / 53.4, 200
@@ -1616,7 +1617,8 @@ hipError_t launch_rfft_b_long(const LongBatch& b, float2* spec, const float2* mi
     // One launch, whatever the rows' lengths.  From 131 tiles on persistent workgroups (k_fwd_b_long) pay for their runs of tiles in most launch sets, and a launch of their
     // own for rows of 2^10 for a tail.  Sender and receiver in us, before (k_fwd_b_long<13> where rows of 2^10 were among few tiles, a launch for either from
     // 512 large tiles on) / this: random sets of 30 248 / 236.5, 40 279 / 269, 60 272.5 / 264, 100 471 / 450,
-    // 200 746 / 723, 40 of 1 M and four of 2^21 470 / 445, 30 and ten 502 / 473, ten of 500 k and sixteen 371 / 364, 55 of 70 k and one 158 / 151.
+    // 200 746 / 723, 40 of 1 M and four of 2^21 470 / 445, 30 and ten 502 / 473, ten of 500 k and sixteen 371 / 364, 55 of 70 k and one 158 / 151.  Senders, a launch of persistent workgroups for rows of 2^10 beside one for the others / one
+    // for all: one of 2^16 and eight of 2^21 130.3 / 124.2, 24 287 / 268, 32 420 / 412, 48 596 / 586, and eight of 2^22 236.5 / 230.5, 16 454 / 434.
     // Rows of 2^10 alone it gains about as often as it loses: 2^21 four 122 / 127, eight 174 / 173, twelve 243 / 238, 24 431 / 422, 32 565 / 581;  2^22 eight
     // 314 / 321, sixteen 579 / 586.
     auto pairs = [&](auto size) {

@@ -507,6 +507,8 @@ hipError_t launch_receive(const uint8_t* stream, const CodecArgs& a, int logM, v
 //   43.5 / 41.8, 512 62.3 / 50.7;
 // both, one launch, sender and receiver, 30 % as 8-bit codes: 180 142.3 / 143.8, 216 145.7 / 147.0, 268 161.3 / 157.0, 292 161.9 / 158.7 and 159.3 / 154.7,
 //   320 161.9 / 159.3, 412 172.0 / 165.4, 512 174.0 / 164.1, 616 211.3 / 199.4, 732 221.2 / 208.0, 880 241.2 / 221.0, 944 260.2 / 235.4.
+//   Receivers alone by codes, at 256 tiles, 5 / 30 / 90 % as 8-bit codes 42.4 / 38.5, 42.6 / 40.0, 42.5 / 41.6, as 12-bit ones 42.5 / 39.3, - , 42.9 / 42.1, 30 % as 15-bit ones 42.8 /
+//   40.6;  at 416 5 and 90 % as 8-bit codes 47.8 / 41.5 and 48.1 / 44.2, as 12-bit ones 48.8 / 42.4 and 50.9 / 44.7.
 constexpr size_t kReceiveTallFrom = 192, kReceiveBothFrom = 256;
 bool receive_applies(const LongBatch& b, int bits)
 {
