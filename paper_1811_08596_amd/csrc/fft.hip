@@ -257,7 +257,7 @@ __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a(const float* __re
 }
 
 // The tiles of a few tensors, 2^13 points to a workgroup of their own, whole in the LDS: two to a compute unit and half as many trips through it as in
-// half of it.  Figures at kWholeForwardLong.
+// half of it.  Figures at whole_forward.
 __global__ __launch_bounds__(tile_lanes(kTileFA)) void k_fwd_a_long(const float* __restrict__ in, float2* __restrict__ mid, Tables tb, uint32_t total, uint32_t step,
                                                                    uint32_t* __restrict__ zero_ptr, uint32_t zero_words, LongTable tab, LongStarts at)
 {
@@ -1454,7 +1454,15 @@ hipError_t by_tile_size(const LongBatch& b, uint32_t wide, Pass&& pass)
 //   1536 253 / 256;  2^21 128 60.9 / 59.4 (61.2 / 59.9), 256 78.4 / 77.2 (79.5 / 77.9), 512 119.6 / 115.8 (122 / 118), 768 163.5 / 163.4 (167 / 167), 1024 199 / 197, 1536 277 / 279;
 //   random sets 60 190 / 193, 100 205 / 210;  2^22 128 75.4 / 71.9 (75.2 / 71.8), beside shorter ones 130 78.9 / 76.8, 160 81.2 / 79.9, 192 84.1 / 82.1 and 80.2 /
 //   77.8, 224 90.6 / 90.4, 256 89.7 / 90.0 (89.9 / 91.4) and 94.7 / 97.0, 384 120.1 / 122.2, 512 125.6 / 134.1.
-constexpr size_t kWholeForwardLong = 512, kWholeForwardLong11 = 255;
+// 256 are on the chip at once, and a few more a second round, which columns of 2^10 do not pay for: 2^21 and shorter ones 258 83.5 / 82.8, 264 85.2 / 88.9, 272 86.3 / 90.1 and 87.5 / 91.3, 288 90.8 /
+// 92.4;  2^20 288 81.8 / 83.2, 320 84.0 / 87.5, 344 89.4 / 88.3, 352 90.6 / 89.6 and 99.9 / 98.5;  2^19 272 78.3 / 77.5, 304 81.8 / 80.5, 320 83.4 / 81.8;  2^18 264 74.2 / 73.9, 320 80.7 / 78.8.
+bool whole_forward(const LongBatch& b)
+{
+    const size_t tiles = launch_tiles(b);
+    const int columns = log_columns(b.tab.t[b.count - 1].logM);  // the longest come last
+    if (columns > 10) return tiles < 256;
+    return tiles <= 512 && (columns < 10 || tiles <= 256 || tiles >= 336);
+}
 // and up to how many, with rows of 2^10 and shorter ones, forward pass B has them as tiles of 2^13, one to a compute unit, where tiles of 2^14 would leave half of them
 // idle.  Senders in us, tiles of 2^14 / this: 98 56.5 / 54.5, 104 57.0 / 55.3, 112 57.9 / 56.0, 128 60.7 / 58.8, 60.7 / 58.9 and 60.2 / 59.9, 130 63.8 / 63.9 and 76.2 / 74.8, 132 63.5 / 67.4 and
 // 74.7 / 80.5, 136 64.0 / 67.3, 144 65.1 / 69.1, 160 66.4 / 70.1 and 68.2 / 69.5, 192 71.6 / 75.6.
@@ -1602,8 +1610,8 @@ hipError_t launch_rfft_long(const float* in, const LongBatch& b, float2* spec, f
                      (uint32_t)zero_words, b.tab, at);
         return hipGetLastError();
     };
-    const bool narrow = log_columns(b.tab.t[b.count - 1].logM) <= 10;  // the longest come last
-    const hipError_t e = launch_tiles(b) <= (narrow ? kWholeForwardLong : kWholeForwardLong11) ? whole() : narrow ? pass_a(std::integral_constant<int, 13>{}) : pass_a(std::integral_constant<int, 14>{});
+    const bool narrow = log_columns(b.tab.t[b.count - 1].logM) <= 10;
+    const hipError_t e = whole_forward(b) ? whole() : narrow ? pass_a(std::integral_constant<int, 13>{}) : pass_a(std::integral_constant<int, 14>{});
     return e == hipSuccess ? launch_rfft_b_long(b, spec, mid, t, hist, s) : e;
 }
 

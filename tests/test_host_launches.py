@@ -188,7 +188,7 @@ def test_tensors_leave_the_small_tiles_where_they_stop_paying(runtime, tmp_path,
 # tiles of 2^14 points: a tensor of 2^18 is eight of them, of 2^21 64 and of 2^22 128
 @pytest.mark.parametrize("sizes, kernel", [
     ([1 << 18] * 12, "short"), ([1 << 18] * 13, "long"), ([1 << 18] * 16, "long"), ([1 << 21] * 8, "long"), ([1 << 21] * 8 + [1 << 16], "split"), ([1 << 22], "long"),
-    ([1 << 22, 1 << 21], "long"), ([1 << 22, 1 << 22], "split"), ([(1 << 19) - 5] * 32, "long"), ([(1 << 19) - 5] * 33, "split")])
+    ([1 << 21] * 4, "long"), ([1 << 21] * 4 + [1 << 16], "split"), ([1 << 21] * 5 + [1 << 19], "long"), ([1 << 18] * 33, "long"), ([1 << 22, 1 << 21], "long"), ([1 << 22, 1 << 22], "split"), ([(1 << 19) - 5] * 32, "long"), ([(1 << 19) - 5] * 33, "split")])
 def test_few_tensors_have_their_first_pass_whole_in_the_lds(runtime, tmp_path, sizes, kernel):
     sender, _ = kernels(runtime, tmp_path, segments(sizes, 0.5, 8))
     first, = [k for k in sender if "k_fwd_a" in k]
