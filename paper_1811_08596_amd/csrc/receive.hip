@@ -21,7 +21,7 @@
 // receive_tile took 116; a lane that looked up each of its bins alone 187.)
 // Measured, 62 M samples in chunks of 2^20, half of the bins kept as 8-bit codes, against counting, decoding and the pass: 6 + 54 + 110
 // -> 8 + 101 us; 138 M in chunks of 2^22 15 + 118 + 275 -> 15 + 249; binary16 5 + 33 + 95 -> 7 + 83.
-// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 7 + 58 (in launches by row length 34 + 34).
+// Tensors of different lengths (ResNet-50's, 34 M samples with their padding): 7 + 32 + 70 -> 7 + 62 (in launches by row length 34 + 34).
 // Several senders' streams are decoded into a spectrum first (codec.hip): eight of them took 444 us this way against 285, since every
 // stretch of eight bins is two and a half lines out of L2.
 #include "fft_core.h"
